@@ -165,43 +165,55 @@ def _stream():
     return torch.cuda.current_stream().cuda_stream
 
 
-def _w4_weights(d_out, d, Gs, gen):
-    """Prepared W4A16 weights of one module."""
+def _w4_codes(d_out, d, Gs, gen):
+    """Packed nibbles, scales and zero-points of one module."""
     wq = _words((d_out, d // 8), gen)
     sc = torch.exp(0.1 * torch.randn(d_out, d // Gs, generator=gen, device="cuda")).mul_(STEP).to(torch.float16)
     zp = torch.randint(5, 11, (d_out, d // Gs), generator=gen, device="cuda").to(torch.float16)
-    buf = torch.empty(G.glowq_prepared_bytes(d_out, d, Gs), dtype=torch.uint8, device="cuda")
-    G.glowq_prepare_weights(wq.data_ptr(), sc.data_ptr(), zp.data_ptr(), d_out, d, Gs, buf.data_ptr(), _stream())
-    return buf
+    return wq, sc, zp
 
 
-def _mx_weights(d_out, d, gen):
-    """Prepared MXFP4 weights of one module."""
+def _mx_codes(d_out, d, gen):
+    """Packed MXFP4 elements and block scales of one module."""
     codes = _words((d_out, d // 8), gen)
-    sc = torch.randint(117, 123, (d_out, d // 32), generator=gen, device="cuda").to(torch.uint8)
-    buf = torch.empty(G.glowq_mx_prepared_bytes(d_out, d), dtype=torch.uint8, device="cuda")
-    G.glowq_mx_prepare_weights(codes.data_ptr(), sc.data_ptr(), d_out, d, buf.data_ptr(), _stream())
-    return buf
+    return codes, torch.randint(117, 123, (d_out, d // 32), generator=gen, device="cuda").to(torch.uint8)
+
+
+def _operands(case, gen):
+    """The stored operands, drawn unit by unit: (d_in, restored, X, B, iterator over (d_out, codes, A))."""
+    r, dt = case["r"], ACT[case["act"]][1]
+
+    def modules(d, d_outs, sigma):
+        for d_out in d_outs:
+            codes = _mx_codes(d_out, d, gen) if case["kind"] == "mx" else _w4_codes(d_out, d, case["G"], gen)
+            yield d_out, codes, _normal((d_out, r), gen, math.sqrt(sigma / sum(d_outs)), dt)
+
+    for d, d_outs, on in _units(case):
+        sigma = STEP / math.sqrt(12.0) * (math.sqrt(sum(d_outs)) + math.sqrt(d))
+        X, B = _activations(case["T"], d, gen, dt), _normal((r, d), gen, math.sqrt(sigma / d), dt)
+        yield d, on, X, B, modules(d, d_outs, sigma)
 
 
 def _prepare_forward(case, gen):
     T, r, Gs = case["T"], case["r"], case["G"]
-    act, dt = ACT[case["act"]]
+    act = ACT[case["act"]][0]
     out, odt = ACT[case["act"] if case["out"] == "act" else case["out"]]
     keep, outs, units, mask = [], [], [], []
     shapes = _units(case)
-    for n, (d, d_outs, on) in enumerate(shapes):
-        rows = sum(d_outs)
+    for n, (d, on, X, B, modules) in enumerate(_operands(case, gen)):
         if n % 4 == 0:                          # one output buffer per layer (or group), module after module
             total = sum(sum(o) for _, o, _ in shapes[n:n + 4])
             outs.append(torch.empty(T * total, dtype=odt, device="cuda"))
             used = 0
-        sigma = STEP / math.sqrt(12.0) * (math.sqrt(rows) + math.sqrt(d))
-        X, B = _activations(T, d, gen, dt), _normal((r, d), gen, math.sqrt(sigma / d), dt)
         mods = []
-        for d_out in d_outs:
-            w = _mx_weights(d_out, d, gen) if case["kind"] == "mx" else _w4_weights(d_out, d, Gs, gen)
-            A = _normal((d_out, r), gen, math.sqrt(sigma / rows), dt)
+        for d_out, codes, A in modules:
+            ptrs = [c.data_ptr() for c in codes]
+            if case["kind"] == "mx":
+                w = torch.empty(G.glowq_mx_prepared_bytes(d_out, d), dtype=torch.uint8, device="cuda")
+                G.glowq_mx_prepare_weights(*ptrs, d_out, d, w.data_ptr(), _stream())
+            else:
+                w = torch.empty(G.glowq_prepared_bytes(d_out, d, Gs), dtype=torch.uint8, device="cuda")
+                G.glowq_prepare_weights(*ptrs, d_out, d, Gs, w.data_ptr(), _stream())
             Y = outs[-1][used:used + T * d_out]
             mods.append(G.make_module(w.data_ptr(), A.data_ptr(), Y.data_ptr(), d_out, d_out))
             keep += [w, A]
@@ -220,12 +232,21 @@ def _prepare_forward(case, gen):
             "mask": G.pack_mask(mask), "ws": ws, "bytes": nbytes, "outs": outs, "keep": keep}
 
 
+def _offline_inputs(case, gen):
+    """fp32 weights, variances of anisotropic calibration inputs, the Gaussian test matrix."""
+    d = case["d_in"]
+    W = [_normal((int(v), d), gen, 0.02, torch.float32) for v in case["d_outs"].split(",")]
+    variance = torch.exp(torch.randn(d, generator=gen, device="cuda", dtype=torch.float64))
+    return W, variance, torch.randn(d, case["r"] + case["p"], generator=gen, device="cuda", dtype=torch.float64)
+
+
 def _prepare_offline(case, gen):
     d, r, p, Gs = case["d_in"], case["r"], case["p"], case["G"]
     act, dt = ACT[case["act"]]
-    mods, W, A, quant, prepared = [], [], [], [], []
-    for d_out in (int(v) for v in case["d_outs"].split(",")):
-        W.append(_normal((d_out, d), gen, 0.02, torch.float32))
+    mods, A, quant, prepared = [], [], [], []
+    W, variance, omega = _offline_inputs(case, gen)
+    for w in W:
+        d_out = w.shape[0]
         A.append(torch.empty(d_out, r, dtype=dt, device="cuda"))
         quant.append((torch.empty(d_out, d // 8, dtype=torch.int32, device="cuda"),
                       torch.empty(d_out, d // Gs, dtype=torch.float16, device="cuda"),
@@ -234,9 +255,6 @@ def _prepare_offline(case, gen):
         mods.append(G.make_module(prepared[-1].data_ptr(), A[-1].data_ptr(), 0, d_out, d_out))
     B = torch.empty(r, d, dtype=dt, device="cuda")
     unit = G.make_unit(0, B.data_ptr(), mods, 1, d, r, Gs, act, act)
-    # variances of anisotropic calibration inputs, and the Gaussian test matrix
-    variance = torch.exp(torch.randn(d, generator=gen, device="cuda", dtype=torch.float64))
-    omega = torch.randn(d, r + p, generator=gen, device="cuda", dtype=torch.float64)
     ws = torch.empty(G.glowq_factorize_workspace_bytes(unit, r, p), dtype=torch.uint8, device="cuda")
     return {"kind": "offline", "unit": unit, "d": d, "r": r, "p": p, "q": case["q"], "G": Gs, "W": W, "A": A, "B": B,
             "quant": quant, "prepared": prepared, "variance": variance, "omega": omega, "ws": ws,
@@ -247,9 +265,14 @@ def _prepare_offline(case, gen):
             "scores": torch.empty(2, dtype=torch.float64, device="cuda")}
 
 
-def prepare(case, seed):
+def _generator(seed):
     gen = torch.Generator(device="cuda")
     gen.manual_seed(int(seed))
+    return gen
+
+
+def prepare(case, seed):
+    gen = _generator(seed)
     return _prepare_offline(case, gen) if case["kind"] == "offline" else _prepare_forward(case, gen)
 
 
@@ -286,3 +309,85 @@ def _run_offline(s, st):
     return {"codes": [q[0] for q in s["quant"]], "scales": [q[1] for q in s["quant"]],
             "zeros": [q[2] for q in s["quant"]], "prepared": s["prepared"], "A": A, "B": B,
             "sigma": s["sigma"], "scores": s["scores"]}
+
+
+# ---- the same in 64 bits ----------------------------------------------------------------
+def exact(case, seed):
+    gen = _generator(seed)
+    return _exact_offline(case, gen) if case["kind"] == "offline" else _exact_forward(case, gen)
+
+
+def _nibbles(words):
+    """[rows][d / 8] words -> [rows][d] codes, element 8 j + e in bits 4 e .. 4 e + 3 of word j."""
+    shift = torch.arange(0, 32, 4, device=words.device, dtype=torch.int32)
+    return ((words.unsqueeze(-1) >> shift) & 15).reshape(words.shape[0], -1)
+
+
+def _mx_activations(X):
+    """MXFP8 values of X (the format's own rounding is part of the result, not an error of it)."""
+    v = X.double().reshape(X.shape[0], -1, 32)
+    top = v.abs().amax(dim=2, keepdim=True)
+    power = torch.where(top > 0, torch.floor(torch.log2(top)) - 8.0, torch.zeros_like(top)).clamp(-127, 127)
+    q = torch.ldexp(v, -power).clamp(-448, 448).to(torch.float32).to(torch.float8_e4m3fn).double()
+    return torch.ldexp(q, power).reshape(X.shape)
+
+
+def _weight(case, codes):
+    """The stored weight: (q - z) s in the activation type, or element times block scale."""
+    q = _nibbles(codes[0])
+    if case["kind"] == "mx":
+        values = torch.tensor([0, .5, 1, 1.5, 2, 3, 4, 6], dtype=torch.float64, device="cuda")
+        values = torch.cat([values, -values])
+        return values[q.long()] * torch.exp2(codes[1].double() - 127.0).repeat_interleave(32, dim=1)
+    s, z = (c.double().repeat_interleave(case["G"], dim=1) for c in codes[1:])
+    return ((q - z) * s).to(ACT[case["act"]][1]).double()
+
+
+def _exact_forward(case, gen):
+    outs = []
+    for n, (d, on, X, B, modules) in enumerate(_operands(case, gen)):
+        if n % 4 == 0:
+            outs.append([])
+        x = X.double()
+        R = x @ B.double().T
+        if case["kind"] == "mx":
+            x = _mx_activations(X)
+        for _, codes, A in modules:
+            y = x @ _weight(case, codes).T
+            outs[-1].append((y + R @ A.double().T if on else y).reshape(-1))
+    return [torch.cat(o) for o in outs]
+
+
+def _exact_offline(case, gen):
+    """RTN, Alg. 1 without re-orthonormalisation between the power steps, scores of the stored factors."""
+    W, variance, omega = _offline_inputs(case, gen)
+    r, Gs, dt = case["r"], case["G"], ACT[case["act"]][1]
+    scales, zeros, errors = [], [], []
+    for w in W:
+        v = w.double().reshape(w.shape[0], -1, Gs)
+        lo, hi = v.amin(dim=2).clamp(max=0.0), v.amax(dim=2).clamp(min=0.0)
+        s = ((hi - lo) / 15.0).clamp(min=2.0**-14).to(torch.float16)
+        z = torch.round(-lo / s.double()).clamp(0, 15)
+        q = (torch.round(v / s.double().unsqueeze(2)) + z.unsqueeze(2)).clamp(0, 15)
+        stored = ((q - z.unsqueeze(2)) * s.double().unsqueeze(2)).to(dt).double()
+        scales.append(s.double())
+        zeros.append(z)
+        errors.append((v - stored).reshape(w.shape))
+    E = torch.cat(errors)
+    M = E * variance.sqrt()
+    Y = M @ omega
+    for _ in range(case["q"]):
+        Y = M @ (M.T @ Y)
+    Q = torch.linalg.qr(Y.cpu()).Q.to(Y.device)
+    U, S, Vt = (t.cuda() for t in torch.linalg.svd((Q.T @ M).cpu(), full_matrices=False))
+    root = S[:r].sqrt()
+    A, B = Q @ (U[:, :r] * root), root[:, None] * Vt[:r] / variance.sqrt()
+    sign = torch.where(B[:, :1] < 0, -1.0, 1.0).double()
+    A, B = A * sign.T, B * sign
+    captured = (A.to(dt).double().square().sum(0) * B.to(dt).double().square().sum(1)).sum()
+    energy = E.square().sum()
+    whole = sum(w.double().square().sum() for w in W)
+    none = [None] * len(W)
+    return {"codes": none, "scales": scales, "zeros": zeros, "prepared": none,
+            "A": list(A.split([w.shape[0] for w in W])), "B": B, "sigma": S,
+            "scores": torch.stack([energy / whole, captured / energy])}
