@@ -346,7 +346,9 @@ glowq_status glowq_block_forward(const glowq_unit* units, int32_t n_units,
     if (misaligned(workspace)) return GLOWQ_ERR_ALIGN;
     if (workspace_bytes < need) return GLOWQ_ERR_WORKSPACE;
   }
-  return forward_all(units, n_units, restore_mask, (char*)workspace, (hipStream_t)stream);
+  // (with no unit restored the workspace may be absent or of any size)
+  const bool whole = workspace && workspace_bytes >= need && !misaligned(workspace);
+  return forward_all(units, n_units, restore_mask, any_corr || whole ? (char*)workspace : nullptr, (hipStream_t)stream);
 }
 
 // Every module of the units as a one-module unit, module j (counted over all units) with

@@ -254,3 +254,15 @@ def test_graph_replay_matches_eager(T):
         G.glowq_group_forward(du.desc, True, ws.ptr, ws.bytes, stream())
         _check(du.outputs(), ref, TOL)
     ws.assert_idle()
+
+
+def test_a_workspace_too_small_is_left_alone():
+    # no unit restored: the workspace may be of any size, and what is too small for the K slices of a
+    # long contraction is not written to
+    u = recipe_unit(O, 1, 0, 600, r=8, shape=UnitShape("s", 8192, (2048,)), method="alg1", qr="none")
+    du = DeviceUnit(u, "f32", 8)
+    buf = torch.full((4096,), 7, dtype=torch.int32, device="cuda")
+    G.glowq_group_forward(du.desc, False, buf.data_ptr(), 256, stream())
+    for y, ref in zip(du.outputs(), O.group_forward(u, False)):
+        assert rel_err(y, ref) <= TOL
+    assert (buf == 7).all()
