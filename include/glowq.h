@@ -140,7 +140,8 @@ glowq_status glowq_prepare_weights(const uint32_t* wq, const uint16_t* scales,
  * unique per kernel launch, so nothing in the buffer ever has to be reset.  Calls
  * that may overlap in time need separate workspaces.
  *
- * A unit of more than 64 tokens whose contraction is long (d_in >= 8192) on few tiles
+ * A call of more than 64 tokens runs on large tiles, or on the small ones of the batched kernel
+ * where its tiles would leave the chip idle.  On large tiles a unit whose contraction is long (d_in >= 8192) on few tiles
  * (at most 128 tiles of 128 tokens x 256 rows, 192 rows for bfloat16) is multiplied in two
  * to four slices of K, so that its few workgroups do not each run the whole contraction
  * while the chip idles: every slice leaves an fp32 partial result in the unit's slice of
@@ -172,7 +173,7 @@ glowq_status glowq_workspace_status(const glowq_unit* units, int32_t n_units,
  * glowq_shared_proj: Eq. 8 alone.  R_out DEVICE fp32 [T][r] receives X B^T
  * (fp32 accumulation, K slices added in slice order).  Exists so that the cached
  * projection can be inspected; the group forward does not need it to be called
- * first (it computes R itself, inside its own launch for T <= 32).  r must be > 0. */
+ * first (it computes R itself, inside its own launch).  r must be > 0. */
 glowq_status glowq_shared_proj(const glowq_unit* u, float* R_out, void* workspace,
                                size_t workspace_bytes, void* stream);
 

@@ -49,9 +49,8 @@ UnitWorkspace plan_unit_workspace(const glowq_unit& u, char* base) {
   // K slices of the projection: prefill already has T / 16 token blocks and only needs
   // enough slices to fill the chip
   // (a handful of tokens: one wave per (rank, part) and parts of about 2048 channels, so
-  // that a wave has all its loads in flight at once, at most four parts; up to 32 tokens:
-  // four slices, two workgroups each (one per half of the ranks); the consumers add the
-  // parts themselves)
+  // that a wave has all its loads in flight at once, at most four parts, which the consumers
+  // add; up to 64 tokens: slices of about 1024 channels, at most four)
   const bool direct = u.T <= 4;
   int ksplit = direct ? (u.d_in + 2047) / 2048 : is_decode(u.T) ? 4 : (256 + tblocks - 1) / tblocks;
   if (direct && ksplit > 4) ksplit = 4;
@@ -62,7 +61,8 @@ UnitWorkspace plan_unit_workspace(const glowq_unit& u, char* base) {
   w.kslice = per * 32;
   w.ksplit = (u.d_in + w.kslice - 1) / w.kslice;
   w.kstride = (w.ksplit + 3) / 4 * 4;
-  // T > 32: the projection tiles that lead the GEMM launch take parts of about 2048
+  if (!direct && is_decode(u.T)) plan_batch_projection(u, w);     // (at most the four slices sized for above)
+  // T > 64: the projection tiles that lead the GEMM launch take parts of about 2048
   // channels (at most 8), so that the longest contraction's R is ready as early as the
   // shortest one's
   const int stages = u.d_in / 64;
@@ -71,12 +71,12 @@ UnitWorkspace plan_unit_workspace(const glowq_unit& u, char* base) {
   w.pf_part_stages = (stages + parts - 1) / parts;
   w.pf_parts = (stages + w.pf_part_stages - 1) / w.pf_part_stages;
   w.off_rpart = w.ctl_bytes;
-  // (T > 32: room for eight slices, which is what the stand-alone projection uses)
+  // (T > 64: room for eight slices, which is what the stand-alone projection uses)
   int slabs = is_decode(u.T) ? w.kstride : (w.kstride > w.pf_parts ? w.kstride : w.pf_parts);
   if (!is_decode(u.T) && slabs < 8) slabs = 8;
   size_t rpart = (u.r > 0) ? (size_t)slabs * u.T * u.r * (is_decode(u.T) ? 8 : 4) : 0;
   w.off_r16 = align_up(w.off_rpart + rpart, 256);
-  size_t r16 = (u.r > 0) ? (size_t)u.T * u.r * 2 : 0;
+  size_t r16 = (u.r > 0) ? (size_t)u.T * u.r * (u.T <= BATCH_MAX_T ? 4 : 2) : 0;
   w.off_splitk = align_up(w.off_r16 + r16, 256);
   w.splitk_bytes = is_decode(u.T) ? 0 : prefill_splitk_bytes(u);
   w.bytes = align_up(w.off_splitk + w.splitk_bytes, 256);
@@ -151,13 +151,15 @@ static glowq_status forward_all(const glowq_unit* units, int n_units, const uint
   while (i < n_units) {
     const glowq_unit& u = units[i];
     if (is_decode(u.T)) {
-      // consecutive few-token units of one kind share a launch
+      // consecutive units of one kind share a launch
       const glowq_unit* dbatch[32];
       UnitWorkspace dws[32];
       bool dcorr[32];
+      const bool few = u.T <= 4;
+      const int most = std::min(32, few ? decode_max_batch() : batch_max_units());
       int nd = 0;
-      while (i < n_units && nd < decode_max_batch() && nd < 32 && is_decode(units[i].T) &&
-             (nd == 0 || decode_batch_compatible(*dbatch[0], units[i]))) {
+      while (i < n_units && nd < most && is_decode(units[i].T) &&
+             (nd == 0 || (few ? decode_batch_compatible(*dbatch[0], units[i]) : batch_compatible(*dbatch[0], units[i])))) {
         dbatch[nd] = &units[i];
         dws[nd] = plan_unit_workspace(units[i], workspace ? workspace + off : nullptr);
         dcorr[nd] = (!mask || mask[i]) && units[i].r > 0;
@@ -165,7 +167,7 @@ static glowq_status forward_all(const glowq_unit* units, int n_units, const uint
         ++nd;
         ++i;
       }
-      hipError_t e = launch_decode_multi(dbatch, dws, dcorr, nd, st);
+      hipError_t e = few ? launch_decode_multi(dbatch, dws, dcorr, nd, st) : launch_decode_batch(dbatch, dws, dcorr, nd, st);
       if (e != hipSuccess) return hip_status(e);
       continue;
     }
@@ -183,6 +185,16 @@ static glowq_status forward_all(const glowq_unit* units, int n_units, const uint
       nmods += units[i].n_modules;
       ++nb;
       ++i;
+    }
+    // Few or small tiles leave the tiled kernel's workgroups alone on their compute units with the
+    // whole contraction each; there the smaller tiles of the batched kernel are faster.
+    bool small = true;
+    for (int k = 0; k < nb; ++k) small = small && batch[k]->T <= BATCH_MAX_T;
+    if (small && batch_cost(batch, nb) < prefill_cost(batch, nb)) {
+      for (int k = 0; k < nb; ++k) plan_batch_projection(*batch[k], bws[k]);
+      hipError_t e = launch_decode_batch(batch, bws, corr, nb, st);
+      if (e != hipSuccess) return hip_status(e);
+      continue;
     }
     // (the projections of the batch run as the first tiles of the same launch)
     hipError_t e = launch_prefill_multi(batch, bws, corr, nb, allow_split && workspace != nullptr, st);

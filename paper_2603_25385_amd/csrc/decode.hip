@@ -1,4 +1,4 @@
-// Decode path (T <= 32 tokens): Y_i = X dequant(W_q,i)^T + R A_i^T  (paper Eq. 9)
+// Decode path (T <= 4 tokens): Y_i = X dequant(W_q,i)^T + R A_i^T  (paper Eq. 9)
 // in one pass over the packed weights.
 //
 // The work is bound by the bytes of W_q, so the kernel is organised around the
@@ -31,28 +31,13 @@
 // loads and their use; otherwise the compiler makes each buffer's first use wait for ALL
 // loads in flight, the next buffer's included, and nothing overlaps.
 #include "decode_device.hpp"
+#include "decode_batch.hpp"
 #include "proj_device.hpp"
 #include "launch.hpp"
 
 namespace glowq {
 
 static_assert(GLOWQ_MAX_RANK <= DEC_WAVES * 32, "one 32-rank correction step per wave");
-
-// Grid: [n_prod projection workgroups][one workgroup per DEC_RG 16-row blocks].
-template <int ACT, int TBK, int NW>
-__global__ void __launch_bounds__(NW * 64) k_decode(DecodeArgs a, ProjArgs p, int n_prod,
-                                                   int n_blocks) {
-  __shared__ float lds[DEC_RG * NW * TBK * 4 * 64];
-  __shared__ __attribute__((aligned(16))) uint16_t r_lds[16 * TBK * GLOWQ_MAX_RANK];
-  __shared__ uint32_t r_flag;
-  __shared__ __attribute__((aligned(1024))) uint32_t lds_af[NW * DEC_RG * 256];
-  if ((int)blockIdx.x < n_prod) {
-    const int per_tb = p.ksplit * p.groups, rem = (int)blockIdx.x % per_tb;
-    proj_workgroup<ACT>(p, (int)blockIdx.x / per_tb, rem % p.ksplit, rem / p.ksplit, lds);
-    return;
-  }
-  decode_workgroup<ACT, TBK, NW>(a, p, (int)blockIdx.x - n_prod, n_blocks, lds, r_lds, &r_flag, lds_af);
-}
 
 // Up to NB units of the same kind (activation type, token class) in one launch: the grid
 // is the concatenation of the units' [projection waves][row blocks].  The descriptor
@@ -188,47 +173,13 @@ static hipError_t launch_decode_small(const glowq_unit* const* units, const Unit
 }
 
 // units[i] uses workspace slice ws[i]; all of them pass decode_batch_compatible with
-// units[0] (or n == 1, any decode-sized unit).
+// units[0].
 hipError_t launch_decode_multi(const glowq_unit* const* units, const UnitWorkspace* ws,
                                const bool* restore, int n, hipStream_t st) {
-  const glowq_unit& u0 = *units[0];
-  const bool f16 = (u0.act_dtype == GLOWQ_F16);
-  dim3 block(DEC_WAVES * 64);
-  if (u0.T <= DEC_SMALL_T) {
-    if (n == 1) return launch_decode_small<1>(units, ws, restore, n, st);
-    if (n <= 2) return launch_decode_small<2>(units, ws, restore, n, st);
-    if (n <= 8) return launch_decode_small<8>(units, ws, restore, n, st);
-    return launch_decode_small<DEC_MAX_BATCH>(units, ws, restore, n, st);
-  }
-  // 4 < T <= 32: one unit per launch
-  for (int i = 0; i < n; ++i) {
-    const glowq_unit& u = *units[i];
-    DecodeArgs a;
-    const int blocks = fill_decode_args(u, ws[i], restore[i], a);
-    ProjArgs p = {};
-    int n_prod = 0;
-    a.ctl = (Control*)ws[i].base;
-    if (restore[i]) {
-      p = make_proj_args(u, ws[i], nullptr, true);
-      // (few K slices, so that the consumers gather few partial sums per rank, and two
-      // workgroups per slice, so that a projection workgroup reads no more of B than before)
-      p.groups = u.r > 16 ? 2 : 1;
-      n_prod = ((u.T + 15) / 16) * ws[i].ksplit * p.groups;
-    }
-    dim3 grid((unsigned)(n_prod + (blocks + DEC_RG - 1) / DEC_RG));
-    // (eight waves per workgroup, i.e. twice the tiles in flight per compute unit, were
-    // measured for up to 16 tokens: the stream took as long and the correction longer)
-    if (u.T <= 16) {
-      if (f16) k_decode<ACT_F16, 1, DEC_WAVES><<<grid, block, 0, st>>>(a, p, n_prod, blocks);
-      else k_decode<ACT_BF16, 1, DEC_WAVES><<<grid, block, 0, st>>>(a, p, n_prod, blocks);
-    } else {
-      if (f16) k_decode<ACT_F16, 2, DEC_WAVES><<<grid, block, 0, st>>>(a, p, n_prod, blocks);
-      else k_decode<ACT_BF16, 2, DEC_WAVES><<<grid, block, 0, st>>>(a, p, n_prod, blocks);
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  if (n == 1) return launch_decode_small<1>(units, ws, restore, n, st);
+  if (n <= 2) return launch_decode_small<2>(units, ws, restore, n, st);
+  if (n <= 8) return launch_decode_small<8>(units, ws, restore, n, st);
+  return launch_decode_small<DEC_MAX_BATCH>(units, ws, restore, n, st);
 }
 
 }  // namespace glowq

@@ -1,0 +1,669 @@
+// Batched decode and prompts on few or small tiles (more than four tokens, see BATCH_MAX_T):
+// Y_i = X dequant(W_q,i)^T + R A_i^T  (paper Eq. 9), R = X B^T (Eq. 8) in the same launch.
+//
+// What bounds it: the packed weights come from memory once, but with this many tokens the
+// activations travel too (T x 256 bytes per 128 channels against 1088 bytes per 16 rows), and a
+// weight costs about as many vector-ALU cycles to dequantise as the memory needs to deliver
+// it.  Hence:
+//  - a workgroup's row waves share one copy of X: each K tile of X (128 channels) is staged
+//    in LDS by direct loads, already in operand order (every lane fetches the 16 bytes that
+//    the same lane of the matrix instruction holds), so that LDS is written and read 1 KiB
+//    lane after lane;
+//  - weights and scales take the same way, so that no register holds data in flight: the
+//    kernel fits three to four workgroups per compute unit, and a ring of DEPTH K tiles keeps
+//    two or three tiles per wave on their way;
+//  - all waits are placed by hand (loads of a wave complete in issue order, every stage
+//    issues the same number of them), one barrier per K tile;
+//  - units of one call share a launch, longest contraction first.
+// Four or eight waves per workgroup: RW of them take RB 16-row blocks each, and NW / RW groups share
+// the contraction (their sums meet in LDS at the end).  The tile is chosen per launch from the
+// units' sizes (choose_batch_tile).
+// Measured against one launch per unit with X in registers (up to 32 tokens: 256 registers, one
+// wave per SIMD with two token blocks) and against 128- and 64-token tiles of 256 rows beyond: a
+// layer of 4096 / 1024 / 14336 at 24 tokens, r = 128, 102 -> 48 us (2.9 TB/s of weights and
+// activations); 2 x 14336 rows x 4096 at 8 tokens, bfloat16, 25.5 -> 18.0 us (3.9 TB/s); four
+// layers of 1536 / 384 / 6912 at 17 tokens 191 -> 26 us; 3 x 960 rows x 5888 at 124 tokens
+// 82 -> 19 us.
+//
+// The projection workgroups lead the grid: (16-token block, K slice, 32 ranks).  Slices are
+// published as self-validating 8-byte slots {fp32, launch tag}; the last slice's workgroup
+// adds them in slice order, rounds to the activation type and publishes R as slots {two
+// 16-bit values, launch tag}, so that a consumer gathers 4 bytes per element of R instead
+// of 8 per element and slice.  (With the slices gathered by every consumer, T = 24 at rank 128
+// moved 98 KB of device-scope loads per workgroup.)
+#pragma once
+#include "common.hpp"
+#include "decode_device.hpp"
+#include "launch.hpp"
+#include <algorithm>
+#include <cmath>
+
+namespace glowq {
+
+constexpr int BATCH_MAX_UNITS = 16;
+constexpr int BATCH_WB = 1024 + 256;      // bytes per wave and K tile: one record's words, its (s, z) words
+constexpr int BATCH_PNB = 2;              // 16-rank blocks per projection workgroup
+
+struct BatchUnit {
+  ModuleArgs mod[GLOWQ_MAX_MODULES];
+  const uint16_t* X;
+  const uint16_t* B;
+  float* part;                 // slots {fp32, tag}: (t ksplit + slice) r + rank
+  uint32_t* rslots;            // slots {two ranks, tag}: t r / 2 + rank pair
+  Control* ctl;
+  int T, K, r, n_modules;
+  int n_blocks;                // 16-row blocks of the unit
+  int n_groups, n_ttiles;      // its workgroups: groups of row blocks x tiles of 16 MB tokens
+  int restore, out_f32;
+  int ksplit, kslice;          // K slices of the projection
+  int prod_start, n_prod;      // this unit's projection workgroups
+  int wg_start;                // first row-block workgroup
+};
+template <int NB> struct BatchArgs {
+  BatchUnit u[NB];
+  int n, n_prod;               // units; projection workgroups of all units (they lead the grid)
+};
+
+__device__ inline const ModuleArgs& find_batch_module(const BatchUnit& u, int blk) {
+  int mi = 0;
+#pragma unroll
+  for (int i = 1; i < GLOWQ_MAX_MODULES; ++i)
+    if (i < u.n_modules && blk >= u.mod[i].blk_start) mi = i;
+  return u.mod[mi];
+}
+
+// direct global -> LDS loads with a scalar base and a 32-bit lane offset (see lds_dma16)
+__device__ inline void lds_dma16_s(const void* base, uint32_t off, uint32_t lds_base) {
+  const uint32_t m = __builtin_amdgcn_readfirstlane(lds_base);
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+               : : "v"(off), "s"(base), "s"(m) : "memory", "m0");
+}
+__device__ inline void lds_dma4_s(const void* base, uint32_t off, uint32_t lds_base) {
+  const uint32_t m = __builtin_amdgcn_readfirstlane(lds_base);
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
+               : : "v"(off), "s"(base), "s"(m) : "memory", "m0");
+}
+template <typename T> __device__ inline T* scalar_ptr(T* p) {
+  const unsigned long long v = (unsigned long long)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return (T*)(((unsigned long long)hi << 32) | lo);
+}
+
+// Four 16-byte loads at device scope (not served from an L2 line that may be older than another
+// compute unit's store), waited for in the same place.
+__device__ inline void load4_device(u32x4_t (&v)[4], const void* p0, const void* p1, const void* p2, const void* p3) {
+  asm volatile("global_load_dwordx4 %0, %4, off sc1\n\tglobal_load_dwordx4 %1, %5, off sc1\n\t"
+               "global_load_dwordx4 %2, %6, off sc1\n\tglobal_load_dwordx4 %3, %7, off sc1\n\t"
+               "s_waitcnt vmcnt(0)"
+               : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]) : "v"(p0), "v"(p1), "v"(p2), "v"(p3) : "memory");
+}
+
+// One projection workgroup: tokens 16 tb .., K slice kz, ranks 32 ng .. + 32.
+template <int ACT, int NW>
+__device__ inline void batch_projection(const BatchUnit& u, int local, float* lds) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int kz = local % u.ksplit, rest = local / u.ksplit;
+  const int n_groups = (u.r + 31) >> 5;
+  const int ng = rest % n_groups, tb = rest / n_groups;
+  const int i = lane & 15, kq = lane >> 4;
+  const int T = u.T, K = u.K, r = u.r, ksplit = u.ksplit;
+  // tokens past T and ranks past r: clamped (valid) rows, computed and not stored
+  const uint16_t* xrow = u.X + (size_t)min(tb * 16 + i, T - 1) * K + 8 * kq;
+  const uint16_t* brow[BATCH_PNB];
+#pragma unroll
+  for (int nb = 0; nb < BATCH_PNB; ++nb) brow[nb] = u.B + (size_t)min(ng * 32 + nb * 16 + i, r - 1) * K + 8 * kq;
+  const int k_begin = kz * u.kslice, k_end = min(K, k_begin + u.kslice);
+  float4_t acc[BATCH_PNB];
+#pragma unroll
+  for (int nb = 0; nb < BATCH_PNB; ++nb) acc[nb] = float4_t{0.f, 0.f, 0.f, 0.f};
+  constexpr int PB = 4;                          // steps of 32 channels whose loads are in flight together
+  for (int k0 = k_begin + wave * 32; k0 < k_end; k0 += PB * NW * 32) {
+    u32x4_t xf[PB], bf[PB][BATCH_PNB];
+#pragma unroll
+    for (int s = 0; s < PB; ++s) {
+      const int k = k0 + s * NW * 32;
+      const bool in = k < k_end;                 // past the end: the first step again, times zero
+      const int kc = in ? k : k0;
+      xf[s] = *(const u32x4_t*)(xrow + kc);
+      if (!in) xf[s] = u32x4_t{0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int nb = 0; nb < BATCH_PNB; ++nb) {
+        bf[s][nb] = *(const u32x4_t*)(brow[nb] + kc);
+        if (!in) bf[s][nb] = u32x4_t{0u, 0u, 0u, 0u};
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < PB; ++s)
+#pragma unroll
+      for (int nb = 0; nb < BATCH_PNB; ++nb) acc[nb] = mfma16<ACT>(xf[s], bf[s][nb], acc[nb]);   // D[token][rank]
+  }
+#pragma unroll
+  for (int nb = 0; nb < BATCH_PNB; ++nb)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) lds[((wave * BATCH_PNB + nb) * 4 + v) * 64 + lane] = acc[nb][v];
+  __syncthreads();
+  // thread -> (token, pair of ranks)
+  const int tl = tid >> 4, rp = tid & 15;
+  const int t = tb * 16 + tl, rank = ng * 32 + 2 * rp;
+  if (tid >= 256 || t >= T || rank >= r) return; // (no barrier follows)
+  float s[2] = {0.f, 0.f};
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const int rl = 2 * rp + e, ln = (rl & 15) + 16 * (tl >> 2);
+#pragma unroll
+    for (int w = 0; w < NW; ++w) s[e] += lds[((w * BATCH_PNB + (rl >> 4)) * 4 + (tl & 3)) * 64 + ln];
+  }
+  const uint32_t tag = (uint32_t)(launch_tag() & 0xffffffffull);
+  const unsigned long long tag_hi = (unsigned long long)tag << 32;
+  if (ksplit > 1) {
+    unsigned long long* slot = (unsigned long long*)u.part + ((size_t)t * ksplit + kz) * r + rank;
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+      __hip_atomic_store(slot + e, tag_hi | (unsigned long long)__builtin_bit_cast(uint32_t, s[e]),
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (kz != ksplit - 1) return;
+    // the last slice's workgroup (the highest index of the group: everybody it waits for is
+    // already running) adds the slices in slice order
+    const unsigned long long* q = (const unsigned long long*)u.part + (size_t)t * ksplit * r + rank;
+    bool ok = false;
+    for (int spin = 0; spin < (1 << 13) && !ok; ++spin) {
+      u32x4_t v[4];
+      load4_device(v, q, q + (size_t)min(1, ksplit - 1) * r, q + (size_t)min(2, ksplit - 1) * r, q + (size_t)(ksplit - 1) * r);
+      ok = true;
+      s[0] = s[1] = 0.f;
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const uint32_t w0 = v[p][0], t0 = v[p][1], w1 = v[p][2], t1 = v[p][3];
+        ok = ok && t0 == tag && t1 == tag;
+        if (p < ksplit) {
+          s[0] += __builtin_bit_cast(float, w0);
+          s[1] += __builtin_bit_cast(float, w1);
+        }
+      }
+      if (!ok) __builtin_amdgcn_s_sleep(8);
+    }
+    if (!ok) {                                   // (the consumers' waits then expire too)
+      atomicOr(&u.ctl->status, 1u);
+      return;
+    }
+  }
+  const uint32_t pk = (uint32_t)to_act16<ACT>(s[0]) | ((uint32_t)to_act16<ACT>(s[1]) << 16);
+  __hip_atomic_store((unsigned long long*)u.rslots + (size_t)t * (r >> 1) + (rank >> 1),
+                     tag_hi | (unsigned long long)pk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// R of the tokens tok0 .. tok0 + n_tok into LDS (act dtype [n_tok][r]), gathered by the whole workgroup; false (in every thread) if
+// the bounded wait expired: the status word is set and the correction left out.
+template <int NT>
+__device__ inline bool batch_fetch_r(const BatchUnit& u, int tok0, int n_tok, uint32_t* r_lds, uint32_t* flag) {
+  const int tid = threadIdx.x;
+  const int n_el = n_tok * (u.r >> 2);           // 16-byte units: two slots, four ranks
+  const uint32_t tag = (uint32_t)(launch_tag() & 0xffffffffull);
+  const u32x4_t* src = (const u32x4_t*)u.rslots + (size_t)tok0 * (u.r >> 2);
+  if (tid == 0) *flag = 0u;
+  __syncthreads();
+  for (int spin = 0; spin < (1 << 12); ++spin) {
+    bool ok = true;
+    for (int e0 = 0; e0 < n_el; e0 += 4 * NT) {
+      u32x4_t v[4];
+      load4_device(v, src + min(e0 + tid, n_el - 1), src + min(e0 + NT + tid, n_el - 1),
+                   src + min(e0 + 2 * NT + tid, n_el - 1), src + min(e0 + 3 * NT + tid, n_el - 1));
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int el = e0 + k * NT + tid;
+        const uint32_t w0 = v[k][0], t0 = v[k][1], w1 = v[k][2], t1 = v[k][3];
+        ok = ok && t0 == tag && t1 == tag;
+        if (el < n_el) {
+          r_lds[2 * el] = w0;
+          r_lds[2 * el + 1] = w1;
+        }
+      }
+    }
+    if (!ok) *flag = 1u;
+    __syncthreads();
+    const bool failed = *flag != 0u;
+    if (!failed) return true;
+    __syncthreads();
+    if (tid == 0) *flag = 0u;
+    __builtin_amdgcn_s_sleep(32);
+    __syncthreads();
+  }
+  if (tid == 0) atomicOr(&u.ctl->status, 1u);
+  return false;
+}
+
+// bfloat16 weights of one word in 17 instructions (see DequantLockstep<ACT_BF16>)
+__device__ inline u32x4_t dequant_word_mix(uint32_t w, float s, float c1024, float c64) {
+  using D = DequantLockstep<ACT_BF16, 1>;
+  const u32x4_t f = nibble_forms_f16(w);
+  u32x4_t out;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t fi = f[i];
+    const float c = (i & 1) ? c64 : c1024;
+    bf16x2_t v;
+    v[0] = (__bf16)D::mix<0>(fi, s, c);
+    v[1] = (__bf16)D::mix<1>(fi, s, c);
+    out[i] = __builtin_bit_cast(uint32_t, v);
+  }
+  return out;
+}
+
+// RB records against MB blocks of 16 tokens.  EXACT (binary16, calls of up to 32 tokens): the
+// exact (q - z) are multiplied and the group's fp32 sum is scaled (see decode_tile); with more
+// tokens the scaling of the sums would cost more than the rounding multiply of the weights.
+template <int ACT, int MB, int RB, bool EXACT, bool G128, class XF>
+__device__ inline void batch_tile(const u32x4_t (&w)[RB], const uint32_t (&sz)[RB][2], XF xfrag, float4_t (&acc)[RB][MB]) {
+  if constexpr (EXACT) {
+#pragma unroll
+    for (int b = 0; b < RB; ++b) decode_tile<ACT, MB, G128>(w[b], sz[b][0], sz[b][1], xfrag, acc[b]);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      u32x4_t wf[RB];
+#pragma unroll
+      for (int b = 0; b < RB; ++b) {
+        GroupConst<ACT> g;
+        g.set(sz[b][(G128 || j < 2) ? 0 : 1]);
+        const uint32_t wj = w[b][j];
+        if constexpr (ACT == ACT_BF16) wf[b] = dequant_word_mix(wj, g.s, g.c1024(), g.c64());
+        else wf[b] = dequant_word<ACT>(wj, g);
+      }
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        const u32x4_t xf = xfrag(mb, j);
+#pragma unroll
+        for (int b = 0; b < RB; ++b) acc[b][mb] = mfma16<ACT>(wf[b], xf, acc[b][mb]);   // D[row][token]
+      }
+    }
+  }
+}
+
+template <int MB, int RB, int RW, int NW> struct BatchShape {
+  static constexpr int KS = NW / RW;                               // groups that share the contraction
+  static constexpr int DEPTH = (KS == 1 && MB <= 2) ? 4 : 3;       // K tiles in the ring
+  static constexpr int XB = MB * 4096;                             // bytes of X per group and K tile
+  static constexpr int STAGE = KS * XB + NW * RB * BATCH_WB;
+  static constexpr int XL = 4 * MB / RW;                           // X loads per wave and K tile
+  static constexpr int LOADS = XL + 2 * RB;                        // all loads per wave and K tile
+  static constexpr int LDS = DEPTH * STAGE;
+  static constexpr int WGS = LDS <= 40960 ? 4 : LDS <= 54613 ? 3 : LDS <= 81920 ? 2 : 1;   // per compute unit
+  static constexpr int WAVES_EU = WGS * NW / 4;
+  static_assert(MB * 4096 + (KS - 1) * RW * RB * MB * 1024 <= LDS, "R and the fold fit the ring");
+};
+
+template <int ACT, int MB, int RB, int RW, int NW, bool EXACT, bool G128, int NB>
+__global__ void __launch_bounds__(NW * 64, (BatchShape<MB, RB, RW, NW>::WAVES_EU)) k_decode_batch(BatchArgs<NB> b) {
+  using S = BatchShape<MB, RB, RW, NW>;
+  __shared__ __attribute__((aligned(1024))) char ring[S::LDS];
+  __shared__ uint32_t flag;
+  if ((int)blockIdx.x < b.n_prod) {
+    int ui = 0;
+#pragma unroll
+    for (int i = 1; i < NB; ++i)
+      if (i < b.n && b.u[i].n_prod > 0 && (int)blockIdx.x >= b.u[i].prod_start) ui = i;
+    batch_projection<ACT, NW>(b.u[ui], (int)blockIdx.x - b.u[ui].prod_start, (float*)ring);
+    return;
+  }
+  int ui = 0;
+#pragma unroll
+  for (int i = 1; i < NB; ++i)
+    if (i < b.n && (int)blockIdx.x >= b.u[i].wg_start) ui = i;
+  const BatchUnit& u = b.u[ui];
+  int grp = (int)blockIdx.x - u.wg_start, tok0 = 0;
+  if (u.n_ttiles > 1) {
+    // workgroups go to the eight XCDs round robin: residue class c takes the c-th eighth of the
+    // list (token tile fastest), so that the token tiles of a row group share an L2
+    const int n_wg = u.n_groups * u.n_ttiles, c = grp & 7, t = c * (n_wg >> 3) + min(c, n_wg & 7) + (grp >> 3);
+    grp = t / u.n_ttiles;
+    tok0 = (t - grp * u.n_ttiles) * 16 * MB;
+  }
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = lane & 15, kq = lane >> 4;
+  const int rw = wave % RW, kg = wave / RW;
+  constexpr int REC = G128 ? 1088 : 1152;        // bytes per tile record
+  const int ktiles = u.K >> 7, T = u.T, K = u.K;
+  const int kt0 = ktiles * kg / S::KS, nkt = ktiles * (kg + 1) / S::KS - kt0;
+  const int n_st = (ktiles + S::KS - 1) / S::KS;  // every group runs this many stages
+
+  // this wave's 16-row blocks; past the unit's last one: that one again, not stored
+  const int blk0 = (grp * RW + rw) * RB;
+  const char* wsrc[RB];
+#pragma unroll
+  for (int b_ = 0; b_ < RB; ++b_) {
+    const int blk = min(blk0 + b_, u.n_blocks - 1);
+    const ModuleArgs& M = find_batch_module(u, blk);
+    wsrc[b_] = scalar_ptr((const char*)M.rec + ((size_t)(blk - M.blk_start) * ktiles + kt0) * REC);
+  }
+  const char* xsrc = scalar_ptr((const char*)u.X + (size_t)kt0 * 256);
+  // X: LDS chunk c = 4 mb + j holds, lane after lane, X[tok0 + 16 mb + n][32 j + 8 kq .. + 8]
+  uint32_t xoff[S::XL];
+#pragma unroll
+  for (int i = 0; i < S::XL; ++i) {
+    const int c = rw + RW * i;
+    xoff[i] = (uint32_t)min(tok0 + 16 * (c >> 2) + n, T - 1) * (uint32_t)K * 2u + (uint32_t)((c & 3) * 64 + kq * 16);
+  }
+  const uint32_t szoff = 1024u + 4u * (uint32_t)(lane & (G128 ? 15 : 31));
+  const uint32_t ring_lds = lds_address(ring);
+  const uint32_t x_lds = ring_lds + (uint32_t)(kg * S::XB), w_lds = ring_lds + (uint32_t)(S::KS * S::XB + wave * RB * BATCH_WB);
+  auto issue = [&](int st, int slot) {
+    // (past the end: the last tile again, into a slot nobody reads; a group without a tile of its
+    // own, possible when K has fewer tiles than groups, reads the next group's first one)
+    const int k = max(min(st, nkt - 1), 0);
+    const uint32_t so = (uint32_t)(slot * S::STAGE);
+    const char* xk = scalar_ptr(xsrc + (ptrdiff_t)k * 256);
+#pragma unroll
+    for (int b_ = 0; b_ < RB; ++b_) {
+      const char* wk = scalar_ptr(wsrc[b_] + (ptrdiff_t)k * REC);
+      lds_dma16_s(wk, (uint32_t)lane * 16u, w_lds + so + (uint32_t)(b_ * BATCH_WB));
+      lds_dma4_s(wk, szoff, w_lds + so + (uint32_t)(b_ * BATCH_WB + 1024));
+    }
+#pragma unroll
+    for (int i = 0; i < S::XL; ++i) lds_dma16_s(xk, xoff[i], x_lds + so + (uint32_t)(rw + RW * i) * 1024u);
+  };
+
+  float4_t acc[RB][MB];
+#pragma unroll
+  for (int b_ = 0; b_ < RB; ++b_)
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) acc[b_][mb] = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < S::DEPTH - 1; ++s) issue(s, s);
+  int slot = 0, slot_new = S::DEPTH - 1;
+  for (int st = 0; st < n_st; ++st) {
+    // this stage's loads have landed (the ones of the DEPTH - 2 younger stages may be on their
+    // way) and so, behind the barrier, have everybody's; everybody is done with the slot that
+    // is loaded next (no LDS read of a wave is pending when it arrives here)
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"((S::DEPTH - 2) * S::LOADS) : "memory");
+    issue(st + S::DEPTH - 1, slot_new);
+    if (S::KS == 1 || st < nkt) {
+      const char* base = ring + slot * S::STAGE;
+      const char* ws = base + S::KS * S::XB + wave * RB * BATCH_WB;
+      const char* xs = base + kg * S::XB + lane * 16;
+      u32x4_t w[RB];
+      uint32_t sz[RB][2];
+#pragma unroll
+      for (int b_ = 0; b_ < RB; ++b_) {
+        w[b_] = *(const u32x4_t*)(ws + b_ * BATCH_WB + lane * 16);
+        sz[b_][0] = *(const uint32_t*)(ws + b_ * BATCH_WB + 1024 + n * 4);
+        sz[b_][1] = G128 ? sz[b_][0] : *(const uint32_t*)(ws + b_ * BATCH_WB + 1088 + n * 4);
+      }
+      batch_tile<ACT, MB, RB, EXACT, G128>(w, sz, [&](int mb, int j) { return *(const u32x4_t*)(xs + (mb * 4 + j) * 1024); }, acc);
+    }
+    slot = slot == S::DEPTH - 1 ? 0 : slot + 1;
+    slot_new = slot_new == S::DEPTH - 1 ? 0 : slot_new + 1;
+  }
+  // nothing may be on its way into LDS any more, and everybody is done reading it
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+
+  if (u.restore) {                               // uniform; r > 0
+    const int r = u.r, n_tok = min(T - tok0, 16 * MB);
+    u32x4_t af[RB][4];
+#pragma unroll
+    for (int b_ = 0; b_ < RB; ++b_) {
+      const int blk = min(blk0 + b_, u.n_blocks - 1);
+      const ModuleArgs& M = find_batch_module(u, blk);
+      const int row = min((blk - M.blk_start) * 16 + n, M.d_out - 1);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {              // correction steps of 32 ranks, dealt to the groups
+        const int j0 = 32 * s + 8 * kq;
+        af[b_][s] = u32x4_t{0u, 0u, 0u, 0u};
+        if (s % S::KS == kg && j0 < r) af[b_][s] = *(const u32x4_t*)(M.A + (size_t)row * r + j0);
+      }
+    }
+    uint32_t* r_lds = (uint32_t*)ring;
+    if (batch_fetch_r<NW * 64>(u, tok0, n_tok, r_lds, &flag)) {
+      const uint16_t* R = (const uint16_t*)r_lds;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        if (s % S::KS == kg && 32 * s < r) {     // uniform per wave
+          const int j0 = 32 * s + 8 * kq;
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb) {
+            // (ranks past r: zero on both sides; tokens past T: never stored)
+            u32x4_t rf = u32x4_t{0u, 0u, 0u, 0u};
+            if (j0 < r && 16 * mb + n < n_tok) rf = *(const u32x4_t*)(R + (size_t)(16 * mb + n) * r + j0);
+#pragma unroll
+            for (int b_ = 0; b_ < RB; ++b_)
+              acc[b_][mb] = EXACT ? mfma16<ACT>(rf, af[b_][s], acc[b_][mb]) : mfma16<ACT>(af[b_][s], rf, acc[b_][mb]);
+          }
+        }
+      }
+    }
+  }
+  if constexpr (S::KS > 1) {
+    // the groups' sums meet in LDS (behind R), added in group order
+    float4_t* fold = (float4_t*)(ring + MB * 4096);
+    auto at = [&](int g, int b_, int mb) -> float4_t& { return fold[(((g * RW + rw) * RB + b_) * MB + mb) * 64 + lane]; };
+    if (kg > 0) {
+#pragma unroll
+      for (int b_ = 0; b_ < RB; ++b_)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) at(kg - 1, b_, mb) = acc[b_][mb];
+    }
+    __syncthreads();
+    if (kg > 0) return;
+#pragma unroll
+    for (int g = 1; g < S::KS; ++g)
+#pragma unroll
+      for (int b_ = 0; b_ < RB; ++b_)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+          const float4_t o = at(g - 1, b_, mb);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) acc[b_][mb][v] += o[v];
+        }
+  }
+#pragma unroll
+  for (int b_ = 0; b_ < RB; ++b_) {
+    const int blk = blk0 + b_;
+    if (blk >= u.n_blocks) break;
+    const ModuleArgs& M = find_batch_module(u, blk);
+    const int row0 = (blk - M.blk_start) * 16;
+    if constexpr (EXACT) {
+      // lane holds row n and tokens 16 mb + 4 kq + v
+      if (row0 + n >= M.d_out) continue;
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int t = tok0 + 16 * mb + 4 * kq + v;
+          if (t < T) {
+            const size_t off = (size_t)t * M.ldy + row0 + n;
+            const float s = acc[b_][mb][v];
+            if (u.out_f32) ((float*)M.Y)[off] = s;
+            else ((uint16_t*)M.Y)[off] = to_act16<ACT>(s);
+          }
+        }
+    } else {
+      // lane holds rows 4 kq .. + 4 and token 16 mb + n
+      if (row0 + 4 * kq >= M.d_out) continue;
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        const int t = tok0 + 16 * mb + n;
+        if (t < T) {
+          const size_t off = (size_t)t * M.ldy + row0 + 4 * kq;
+          const float4_t v = acc[b_][mb];
+          if (u.out_f32) {
+            *(float4_t*)((float*)M.Y + off) = v;
+          } else {
+            uint2 pk;
+            pk.x = (uint32_t)to_act16<ACT>(v[0]) | ((uint32_t)to_act16<ACT>(v[1]) << 16);
+            pk.y = (uint32_t)to_act16<ACT>(v[2]) | ((uint32_t)to_act16<ACT>(v[3]) << 16);
+            *(uint2*)((uint16_t*)M.Y + off) = pk;
+          }
+        }
+      }
+    }
+  }
+}
+
+bool batch_compatible(const glowq_unit& a, const glowq_unit& b) {
+  return a.T > DEC_SMALL_T && a.T <= BATCH_MAX_T && b.T > DEC_SMALL_T && b.T <= BATCH_MAX_T && a.act_dtype == b.act_dtype &&
+         a.group_size == b.group_size && (a.T <= 16) == (b.T <= 16) && (a.T <= 32) == (b.T <= 32);
+}
+int batch_max_units() { return BATCH_MAX_UNITS; }
+
+// Workgroup tiles: 16 mb tokens x 16 rb rw rows, nw / rw groups of waves sharing the contraction.
+// What a tile costs was measured over 70 shapes (5 to 1001 tokens, 144 to 48000 rows, 256 to 13696
+// channels, calls of one unit and of whole layers) with every tile, in us per K tile of a wave
+// group: `chain`, when the compute unit has nothing else to do, and `busy`, each workgroup's
+// share of a compute unit that is full.  A launch then takes the longer of its longest
+// contraction and its share of the chip; picking the cheapest tile by that was within 2 % of
+// the best one on average, 13 % at worst.
+struct BatchTile {
+  int mb, rb, rw, nw;
+  float chain, busy_f16, busy_bf16;
+};
+constexpr BatchTile BATCH_TILES[] = {
+    {1, 1, 1, 4, 0.45f, 0.65f, 0.69f}, {1, 1, 4, 4, 0.25f, 0.19f, 0.24f}, {1, 1, 4, 8, 0.25f, 0.38f, 0.51f},
+    {2, 1, 4, 4, 0.30f, 0.30f, 0.32f}, {2, 1, 4, 8, 0.45f, 0.63f, 0.73f}, {4, 1, 4, 4, 0.42f, 0.53f, 0.59f},
+    {4, 2, 4, 4, 0.75f, 0.73f, 0.84f},
+};
+constexpr int BATCH_N_TILES = sizeof(BATCH_TILES) / sizeof(BATCH_TILES[0]);
+
+template <int I> constexpr int batch_tile_resident() {
+  constexpr BatchTile t = BATCH_TILES[I];
+  return BatchShape<t.mb, t.rb, t.rw, t.nw>::WGS;
+}
+constexpr int BATCH_RESIDENT[] = {batch_tile_resident<0>(), batch_tile_resident<1>(), batch_tile_resident<2>(),
+                                  batch_tile_resident<3>(), batch_tile_resident<4>(), batch_tile_resident<5>(),
+                                  batch_tile_resident<6>()};
+static_assert(sizeof(BATCH_RESIDENT) / sizeof(int) == BATCH_N_TILES, "one entry per tile");
+
+static int row_blocks(const glowq_unit& u) {
+  int b = 0;
+  for (int i = 0; i < u.n_modules; ++i) b += (u.modules[i].d_out + 15) / 16;
+  return b;
+}
+
+// The cheapest tile for these units in one launch, and what it is taken to cost (us beyond the
+// launch itself).
+static int choose_batch_tile(const glowq_unit* const* units, int n, float* cost) {
+  const bool f16 = units[0]->act_dtype == GLOWQ_F16, exact = f16 && units[0]->T <= 32;
+  int best = -1;
+  for (int i = 0; i < BATCH_N_TILES; ++i) {
+    const BatchTile& t = BATCH_TILES[i];
+    if (exact && t.mb > 2) continue;
+    const int ks = t.nw / t.rw;
+    double work = 0.0, wgs = 0.0;
+    int chain = 0;
+    for (int k = 0; k < n; ++k) {
+      const glowq_unit& u = *units[k];
+      const int stages = (u.d_in / 128 + ks - 1) / ks;
+      const double w = (double)((row_blocks(u) + t.rb * t.rw - 1) / (t.rb * t.rw)) * ((u.T + 16 * t.mb - 1) / (16 * t.mb));
+      wgs += w;
+      work += w * stages;
+      chain = std::max(chain, stages);
+    }
+    double per_cu = wgs / 256.0;
+    if (per_cu <= BATCH_RESIDENT[i]) per_cu = std::ceil(per_cu);
+    const float c = (float)std::max((double)chain * t.chain, work / wgs * per_cu * (f16 ? t.busy_f16 : t.busy_bf16));
+    if (best < 0 || c < *cost) {
+      best = i;
+      *cost = c;
+    }
+  }
+  return best;
+}
+float batch_cost(const glowq_unit* const* units, int n) {
+  float c = 0.f;
+  choose_batch_tile(units, n, &c);
+  return c;
+}
+
+// K slices of the projection inside the launch: about 1024 channels each, at most four, and no
+// more workgroups than the chip takes beside the first row blocks
+void plan_batch_projection(const glowq_unit& u, UnitWorkspace& w) {
+  const int pieces = (u.T + 15) / 16 * std::max(1, (u.r + 31) / 32);
+  const int ksplit = std::max(1, std::min(std::min(4, (u.d_in + 1023) / 1024), (512 + pieces - 1) / pieces));
+  const int steps = u.d_in / 32, per = (steps + ksplit - 1) / ksplit;
+  w.kslice = per * 32;
+  w.ksplit = (u.d_in + w.kslice - 1) / w.kslice;
+}
+
+template <int ACT, bool EXACT, bool G128, int NB, int I>
+static void launch_batch_tile(const BatchArgs<NB>& b, int tile, int n_wgs, hipStream_t st) {
+  constexpr BatchTile t = BATCH_TILES[I];
+  if constexpr (!EXACT || t.mb <= 2) {
+    if (tile == I) k_decode_batch<ACT, t.mb, t.rb, t.rw, t.nw, EXACT, G128, NB><<<dim3((unsigned)n_wgs), dim3(t.nw * 64), 0, st>>>(b);
+  }
+  if constexpr (I + 1 < BATCH_N_TILES) launch_batch_tile<ACT, EXACT, G128, NB, I + 1>(b, tile, n_wgs, st);
+}
+
+template <int NB>
+static hipError_t launch_batch(const glowq_unit* const* units, const UnitWorkspace* ws, const bool* restore, int n,
+                               hipStream_t st) {
+  BatchArgs<NB> b;
+  // longest contraction first: the hardware starts workgroups in index order
+  int order[NB];
+  for (int i = 0; i < n; ++i) order[i] = i;
+  for (int i = 1; i < n; ++i)
+    for (int j = i; j > 0 && units[order[j]]->d_in > units[order[j - 1]]->d_in; --j) {
+      const int t = order[j]; order[j] = order[j - 1]; order[j - 1] = t;
+    }
+  int n_prod = 0;
+  for (int oi = 0; oi < n; ++oi) {
+    const glowq_unit& u = *units[order[oi]];
+    const UnitWorkspace& w = ws[order[oi]];
+    BatchUnit& bu = b.u[oi];
+    int blk = 0;
+    for (int i = 0; i < u.n_modules; ++i) {
+      const glowq_module& m = u.modules[i];
+      PreparedView v = prepared_view(m.w_prepared, m.d_out, u.d_in, u.group_size);
+      bu.mod[i] = ModuleArgs{v.base, (const uint16_t*)m.A, m.Y, m.d_out, m.ldy, v.rows16, blk};
+      blk += v.rows16;
+    }
+    for (int i = u.n_modules; i < GLOWQ_MAX_MODULES; ++i) bu.mod[i] = bu.mod[0];
+    bu.X = (const uint16_t*)u.X;
+    bu.B = (const uint16_t*)u.B;
+    bu.T = u.T; bu.K = u.d_in; bu.r = u.r; bu.n_modules = u.n_modules;
+    bu.n_blocks = blk;
+    bu.out_f32 = u.out_dtype == GLOWQ_F32 ? 1 : 0;
+    bu.restore = restore[order[oi]] ? 1 : 0;
+    bu.part = nullptr; bu.rslots = nullptr; bu.ctl = nullptr;
+    bu.ksplit = w.ksplit; bu.kslice = w.kslice;
+    bu.prod_start = n_prod;
+    bu.n_prod = 0;
+    if (bu.restore) {
+      bu.part = (float*)(w.base + w.off_rpart);
+      bu.rslots = (uint32_t*)(w.base + w.off_r16);
+      bu.ctl = (Control*)w.base;
+      bu.n_prod = (u.T + 15) / 16 * w.ksplit * ((u.r + 31) / 32);
+      n_prod += bu.n_prod;
+    }
+  }
+  float cost = 0.f;
+  const int ti = choose_batch_tile(units, n, &cost);
+  const BatchTile tile = BATCH_TILES[ti];
+  int wg = n_prod;
+  for (int oi = 0; oi < n; ++oi) {
+    b.u[oi].wg_start = wg;
+    b.u[oi].n_ttiles = (b.u[oi].T + 16 * tile.mb - 1) / (16 * tile.mb);
+    b.u[oi].n_groups = (b.u[oi].n_blocks + tile.rb * tile.rw - 1) / (tile.rb * tile.rw);
+    wg += b.u[oi].n_groups * b.u[oi].n_ttiles;
+  }
+  for (int i = n; i < NB; ++i) b.u[i] = b.u[0];
+  b.n = n;
+  b.n_prod = n_prod;
+  const bool f16 = units[0]->act_dtype == GLOWQ_F16, g128 = units[0]->group_size == 128;
+  const bool exact = f16 && units[0]->T <= 32;
+  if (exact && g128) launch_batch_tile<ACT_F16, true, true, NB, 0>(b, ti, wg, st);
+  else if (exact) launch_batch_tile<ACT_F16, true, false, NB, 0>(b, ti, wg, st);
+  else if (f16 && g128) launch_batch_tile<ACT_F16, false, true, NB, 0>(b, ti, wg, st);
+  else if (f16) launch_batch_tile<ACT_F16, false, false, NB, 0>(b, ti, wg, st);
+  else if (g128) launch_batch_tile<ACT_BF16, false, true, NB, 0>(b, ti, wg, st);
+  else launch_batch_tile<ACT_BF16, false, false, NB, 0>(b, ti, wg, st);
+  return hipGetLastError();
+}
+
+// units[i] uses workspace slice ws[i]; all of them pass batch_compatible with units[0]
+hipError_t launch_decode_batch(const glowq_unit* const* units, const UnitWorkspace* ws, const bool* restore, int n,
+                               hipStream_t st) {
+  if (n == 1) return launch_batch<1>(units, ws, restore, n, st);
+  return launch_batch<BATCH_MAX_UNITS>(units, ws, restore, n, st);
+}
+
+}  // namespace glowq

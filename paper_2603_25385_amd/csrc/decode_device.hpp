@@ -1,5 +1,5 @@
 // Workgroup body of the decode path: one 16-row block of one module against up
-// to 32 tokens, streamed once over the packed weights (paper Eq. 9).
+// to 4 tokens, streamed once over the packed weights (paper Eq. 9).
 #pragma once
 #include "common.hpp"
 #include "proj_device.hpp"
@@ -125,106 +125,6 @@ constexpr int DEC_XROW = 1040;                       // bytes per token and chun
 // single-token instance leaves room for four workgroups per compute unit); a wave has two
 __host__ __device__ constexpr int dec_xbuf_bytes(int T) { return (T * DEC_XROW + 63) / 64 * 64; }
 
-
-// 4 < T <= 32: a workgroup takes DEC_RG consecutive 16-row blocks of the unit (they may
-// belong to different modules) and runs them against the same X fragments, held in
-// registers: X is read once per workgroup instead of once per row block.  Two tiles per
-// register buffer, two buffers in flight.
-constexpr int DEC_RG = 3;
-#ifndef GLOWQ_DEC_RCH
-#define GLOWQ_DEC_RCH 2
-#endif
-constexpr int DEC_RCH = GLOWQ_DEC_RCH;
-
-// `mark(n)` runs after the n-th buffer has been consumed.
-template <int ACT, int TBK, bool G128, int NW, typename MARK>
-__device__ inline void decode_stream_rows(const DecodeArgs& a, const uint32_t* const (&recb)[DEC_RG],
-                                          int wave, int lane, float4_t (&acc)[DEC_RG][TBK], MARK mark) {
-  const int n = lane & 15, kq = lane >> 4;
-  const int ktiles = a.K >> 7;
-  const int rw = G128 ? 272 : 288;             // words per tile record
-  // this wave's tiles: kb = wave + NW * t, t = 0 .. ntw - 1
-  const int ntw = (ktiles - wave + NW - 1) / NW;
-  if (ntw <= 0) return;
-  // tokens past T read the last valid token: their rows of D are never stored
-  const uint16_t* xrow[TBK];
-#pragma unroll
-  for (int tb = 0; tb < TBK; ++tb)
-    xrow[tb] = a.X + (size_t)min(16 * tb + n, a.T - 1) * a.K + 8 * kq + 128 * wave;
-
-  struct Buf {
-    u32x4_t x[DEC_RCH][TBK][4];
-    u32x4_t w[DEC_RCH][DEC_RG];
-    uint32_t s[DEC_RCH][DEC_RG][2];
-  };
-  Buf A, B;
-  auto load = [&](int t0, Buf& b) {
-#pragma unroll
-    for (int c = 0; c < DEC_RCH; ++c) {
-      const int t = min(t0 + c, ntw - 1);          // clamped: a duplicate tile is never used
-#pragma unroll
-      for (int tb = 0; tb < TBK; ++tb)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          b.x[c][tb][j] = *(const u32x4_t*)(xrow[tb] + (size_t)t * (128 * NW) + 32 * j);
-#pragma unroll
-      for (int g = 0; g < DEC_RG; ++g) {
-        const uint32_t* rec = recb[g] + (size_t)t * (NW * rw);
-        b.w[c][g] = __builtin_nontemporal_load((const u32x4_t*)rec + lane);
-        b.s[c][g][0] = __builtin_nontemporal_load(rec + 256 + n);
-        if constexpr (G128) b.s[c][g][1] = b.s[c][g][0];
-        else b.s[c][g][1] = __builtin_nontemporal_load(rec + 272 + n);
-      }
-    }
-  };
-  auto run = [&](int t0, const Buf& b) {
-#pragma unroll
-    for (int c = 0; c < DEC_RCH; ++c) {
-      if (t0 + c < ntw) {
-#pragma unroll
-        for (int g = 0; g < DEC_RG; ++g)
-          decode_tile<ACT, TBK, G128>(b.w[c][g], b.s[c][g][0], b.s[c][g][1],
-                                      [&](int tb, int j) { return b.x[c][tb][j]; }, acc[g]);
-      }
-    }
-  };
-  // Between the issue of a buffer's loads and its use every load is issued unconditionally:
-  // the compiler can then count, at the wait, how many younger loads may stay in flight
-  // (a load behind a branch in between makes it wait for ALL loads, the next buffer's
-  // included, and the double buffering is gone).  Hence the peeled tail.
-  // (and the scheduler may not move a buffer's first use up into the previous buffer's
-  // run, behind which that buffer's loads have only just been issued)
-  auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
-  int done = 0;                                    // buffers consumed; `mark` hears of each
-  load(0, A);
-  int t0 = 0;
-  while (t0 + 2 * DEC_RCH < ntw) {                 // both next buffers hold at least one tile
-    load(t0 + DEC_RCH, B);
-    fence();
-    run(t0, A);
-    mark(++done);
-    fence();
-    load(t0 + 2 * DEC_RCH, A);
-    fence();
-    run(t0 + DEC_RCH, B);
-    mark(++done);
-    fence();
-    t0 += 2 * DEC_RCH;
-  }
-  if (t0 + DEC_RCH < ntw) {
-    load(t0 + DEC_RCH, B);
-    fence();
-    run(t0, A);
-    mark(++done);
-    fence();
-    run(t0 + DEC_RCH, B);
-    mark(++done);
-  } else {
-    fence();
-    run(t0, A);
-    mark(++done);
-  }
-}
 
 // X staging and its ordering.  Loads of a wave complete in the order they were issued,
 // so a chunk's X has landed as soon as any load issued after it has: with room for three
@@ -494,89 +394,6 @@ __device__ inline void correction_take(CorrFrag& c, const uint32_t* lds_row, int
   if (c.active && c.ok) c.af = *(const u32x4_t*)(lds_row + 4 * lane);
 }
 
-// Correction R A_i^T as r more channels of the contraction (4 < T <= 32).  R comes from
-// the projection workgroups of the same launch as self-validating 8-byte slots
-// {fp32 partial sum, launch tag}, slot (t, part, j) at slots[(t ksplit + part) r + j]: one
-// contiguous region per unit.  The workgroup gathers it together: a thread owns pairs of
-// adjacent ranks of a token and reads their slots of every part with 16-byte
-// device-coherent loads (consecutive lanes read consecutive addresses), checks the tags,
-// adds the parts in part order, rounds to the activation type and leaves R in LDS, from
-// where every lane takes the operand words of its token and rank chunk.  (Eight-byte
-// loads per lane, token and rank straight from memory cost several times the whole
-// weight stream's tail: one request per lane and slot.)  The projection workgroups lead
-// the grid and wait for nothing; the wait is bounded all the same, and a workgroup that
-// gives up records it in ctl->status and leaves the correction out.
-// r_lds: act dtype [16 TBK][r]; flag: one LDS word.  Returns false if the bounded wait
-// expired (the same answer in every thread of the workgroup).
-__device__ inline void vm_load_dev(u32x4_t& v, const void* p) {
-  asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(v) : "v"(p) : "memory");
-}
-template <int ACT, int TBK, int NW, int MAXP>
-__device__ inline bool fetch_r_coop_parts(const DecodeArgs& a, const ProjArgs& p, uint16_t* r_lds, uint32_t* flag) {
-  const int tid = threadIdx.x;
-  const int hp = a.r >> 1;                     // rank pairs (16-byte units) per token and part
-  const int n_el = a.T * hp;                   // (token, rank pair) elements, <= 32 * 64
-  const uint32_t tag = (uint32_t)(launch_tag() & 0xffffffffull);
-  const u32x4_t* units = (const u32x4_t*)p.Rpart;
-  constexpr int EPR = 2;                       // elements per thread and round
-  if (tid == 0) *flag = 0u;
-  __syncthreads();
-  for (int spin = 0; spin < (1 << 12); ++spin) {
-    bool ok = true;
-    for (int e0 = 0; e0 < n_el; e0 += EPR * NW * 64) {
-      u32x4_t v[EPR][MAXP];
-      int el[EPR];
-#pragma unroll
-      for (int k = 0; k < EPR; ++k) {
-        el[k] = e0 + k * NW * 64 + tid;
-        const int ec = min(el[k], n_el - 1);   // clamped: loaded again, not used
-        const int tok = ec / hp, rp = ec - tok * hp;
-        const size_t u0 = (size_t)tok * p.ksplit * hp + rp;
-#pragma unroll
-        for (int part = 0; part < MAXP; ++part) {
-          vm_load_dev(v[k][part], units + u0 + (size_t)min(part, p.ksplit - 1) * hp);
-        }
-      }
-      vm_wait<0>();
-#pragma unroll
-      for (int k = 0; k < EPR; ++k) {
-        float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-        for (int part = 0; part < MAXP; ++part) {
-          after_wait(v[k][part]);
-          if (part < p.ksplit) {
-            // (elements copied to scalars first: a bit cast applied directly to a vector
-            // element reads element 0)
-            const uint32_t w0 = v[k][part][0], t0 = v[k][part][1], w1 = v[k][part][2], t1 = v[k][part][3];
-            ok = ok && t0 == tag && t1 == tag;
-            s0 += __builtin_bit_cast(float, w0);
-            s1 += __builtin_bit_cast(float, w1);
-          }
-        }
-        if (el[k] < n_el)
-          ((uint32_t*)r_lds)[el[k]] = (uint32_t)to_act16<ACT>(s0) | ((uint32_t)to_act16<ACT>(s1) << 16);
-      }
-    }
-    if (!ok) *flag = 1u;
-    __syncthreads();
-    const bool failed = *flag != 0u;
-    if (!failed) return true;                  // R is complete in LDS
-    __syncthreads();
-    if (tid == 0) *flag = 0u;
-    __builtin_amdgcn_s_sleep(32);
-    __syncthreads();
-  }
-  if (tid == 0) atomicOr(&a.ctl->status, 1u);
-  return false;
-}
-
-template <int ACT, int TBK, int NW>
-__device__ inline bool fetch_r_coop(const DecodeArgs& a, const ProjArgs& p, uint16_t* r_lds, uint32_t* flag) {
-  // (MAXP: the parts a thread loads per element; at most four for these token counts)
-  if (p.ksplit <= 4) return fetch_r_coop_parts<ACT, TBK, NW, 4>(a, p, r_lds, flag);
-  return fetch_r_coop_parts<ACT, TBK, NW, 8>(a, p, r_lds, flag);
-}
-
 // Folds the NW waves' fp32 tiles of one row block through LDS and stores the result.
 // lds: NW * TBK * 256 floats
 template <int ACT, int TBK, int NW = DEC_WAVES>
@@ -628,103 +445,6 @@ __device__ inline DecodeArgs decode_scalars(const DecodeArgs& a) {
   l.out_f32 = a.out_f32;
   l.ctl = a.ctl;
   return l;
-}
-
-// grp: index of the workgroup's group of DEC_RG row blocks; n_blocks: row blocks of the unit
-// NW: waves of the workgroup (they take the K tiles round robin).
-// lds: DEC_RG * NW * TBK * 256 floats (fold); r_lds: act dtype [16 TBK][GLOWQ_MAX_RANK];
-// flag: one word; lds_af: NW * DEC_RG rows of 256 words (the A_i fragments' landing place)
-template <int ACT, int TBK, int NW>
-__device__ inline void decode_workgroup(const DecodeArgs& a_arg, const ProjArgs& p_arg, int grp, int n_blocks,
-                                        float* lds, uint16_t* r_lds, uint32_t* flag, uint32_t* lds_af) {
-  const DecodeArgs a = decode_scalars(a_arg);
-  const ProjArgs p = p_arg;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int ktiles = a.K >> 7;
-  const int rw = a.G == 128 ? 272 : 288;
-
-  float4_t acc[DEC_RG][TBK];
-  const uint32_t* recb[DEC_RG];
-  CorrFrag cf[DEC_RG];
-#pragma unroll
-  for (int g = 0; g < DEC_RG; ++g) {
-#pragma unroll
-    for (int tb = 0; tb < TBK; ++tb) acc[g][tb] = float4_t{0.f, 0.f, 0.f, 0.f};
-    // a group past the unit's last block repeats it (computed, not stored)
-    const int blk = min(grp * DEC_RG + g, n_blocks - 1);
-    const ModuleArgs M = find_module(a_arg, blk);
-    const int rb = blk - M.blk_start;
-    recb[g] = M.rec + ((size_t)rb * ktiles + wave) * rw;
-    cf[g] = correction_prefetch(a, M, rb, wave, lane, lds_af + (wave * DEC_RG + g) * 256);
-  }
-  const bool corr = a.restore && a.r > 0;                       // uniform
-  GLOWQ_WTRACE_DECL;
-  GLOWQ_WSTAMP(0);
-  GLOWQ_WTRACE_HWID(7);
-  auto mark = [&](int done) {
-    if (done == 1) GLOWQ_WSTAMP(1);
-  };
-  if (a.G == 128) decode_stream_rows<ACT, TBK, true, NW>(a, recb, wave, lane, acc, mark);
-  else decode_stream_rows<ACT, TBK, false, NW>(a, recb, wave, lane, acc, mark);
-  GLOWQ_WSTAMP(2);
-  // R, once per workgroup (all row blocks of the group use the same fragments)
-  u32x4_t rf[TBK];
-#pragma unroll
-  for (int tb = 0; tb < TBK; ++tb) rf[tb] = u32x4_t{0u, 0u, 0u, 0u};
-  bool have_r = false;
-  if (corr) {                                      // uniform
-    // (waits for all the wave's loads)
-    have_r = fetch_r_coop<ACT, TBK, NW>(a, p, r_lds, flag);
-#pragma unroll
-    for (int g = 0; g < DEC_RG; ++g) correction_take(cf[g], lds_af + (wave * DEC_RG + g) * 256, lane);
-    if (have_r && cf[0].active && cf[0].ok) {
-#pragma unroll
-      for (int tb = 0; tb < TBK; ++tb) {
-        const int tok = 16 * tb + (lane & 15);
-        if (tok < a.T) rf[tb] = *(const u32x4_t*)(r_lds + (size_t)tok * a.r + cf[0].j0c);
-      }
-    }
-  }
-  GLOWQ_WSTAMP(3);
-  // all row blocks' tiles go through LDS together: one barrier for the group
-#pragma unroll
-  for (int g = 0; g < DEC_RG; ++g) {
-    if (cf[g].active && have_r) {
-#pragma unroll
-      for (int tb = 0; tb < TBK; ++tb) acc[g][tb] = mfma16<ACT>(rf[tb], cf[g].af, acc[g][tb]);
-    }
-#pragma unroll
-    for (int tb = 0; tb < TBK; ++tb)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) lds[(((g * NW + wave) * TBK + tb) * 4 + v) * 64 + lane] = acc[g][tb][v];
-  }
-  __syncthreads();
-  GLOWQ_WSTAMP(4);
-  if (wave < 4) {                                  // 256 threads <-> (v, lane) of one token block
-#pragma unroll
-    for (int g = 0; g < DEC_RG; ++g) {
-      const int blk = grp * DEC_RG + g;
-      if (blk >= n_blocks) break;                  // uniform
-      const ModuleArgs M = find_module(a_arg, blk);
-      const int v = wave;
-      const int row = (blk - M.blk_start) * 16 + (lane & 15);
-#pragma unroll
-      for (int tb = 0; tb < TBK; ++tb) {
-        const int t = 16 * tb + 4 * (lane >> 4) + v;
-        if (t < a.T && row < M.d_out) {
-          float s = 0.f;
-#pragma unroll
-          for (int w = 0; w < NW; ++w) s += lds[(((g * NW + w) * TBK + tb) * 4 + v) * 64 + lane];
-          const size_t off = (size_t)t * M.ldy + row;
-          if (a.out_f32) ((float*)M.Y)[off] = s;
-          else ((uint16_t*)M.Y)[off] = to_act16<ACT>(s);
-        }
-      }
-    }
-  }
-  GLOWQ_WSTAMP(6);
-  GLOWQ_WTRACE_FLUSH();
 }
 
 // T <= 4.  lds: DEC_WAVES * 256 floats for the fold; lds_x: DEC_WAVES * DecX<TM>::WAVE_BYTES;

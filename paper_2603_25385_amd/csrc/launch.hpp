@@ -10,22 +10,23 @@ namespace glowq {
 struct UnitWorkspace {
   char* base;         // start of the slice (256-byte aligned)
   size_t bytes;       // size of the slice
-  size_t off_counters;  // T > 32: per token tile, a ready flag and an arrival counter of K parts
-  size_t off_rpart;   // partial sums of the projection (T <= 32: 8-byte slots {fp32, launch tag},
-                      // [T][ksplit][r]; T > 32 and glowq_shared_proj: fp32 [part][T][r])
-  size_t off_r16;     // T > 32: R in the activation type, [T][r]
+  size_t off_counters;  // T > 64: per token tile, a ready flag and an arrival counter of K parts
+  size_t off_rpart;   // partial sums of the projection (T <= 64: 8-byte slots {fp32, launch tag},
+                      // [T][ksplit][r]; T > 64 and glowq_shared_proj: fp32 [part][T][r])
+  size_t off_r16;     // R in the activation type: T > 64 [T][r]; 4 < T <= 64 8-byte slots
+                      // {two ranks, launch tag}, [T][r / 2]
   size_t off_splitk;  // T > 64: fp32 slabs of a long contraction cut into K slices (0 bytes if not cut)
   size_t splitk_bytes;
   size_t ctl_bytes;   // leading bytes that must be zero between calls
   int ksplit;         // K slices of the projection
   int kslice;         // channels per slice (multiple of 32)
   int kstride;        // ksplit rounded up to a multiple of 4 (sizes the partial-sum area)
-  int pf_parts;       // T > 32: K parts of a projection tile inside the GEMM launch
+  int pf_parts;       // T > 64: K parts of a projection tile inside the GEMM launch
   int pf_part_stages; // 64-channel stages per such part
 };
 
-// decode path = one pass over the weights with all tokens in one matrix-core tile
-static inline bool is_decode(int T) { return T <= 32; }
+// decode path = one pass over the weights with all tokens of the call in one workgroup
+static inline bool is_decode(int T) { return T <= 64; }
 
 UnitWorkspace plan_unit_workspace(const glowq_unit& u, char* base);
 
@@ -86,13 +87,24 @@ ProjArgs make_proj_args(const glowq_unit& u, const UnitWorkspace& ws, float* R32
 // slice order into R32 (optional) and R16 (optional).
 hipError_t launch_proj(const glowq_unit& u, const UnitWorkspace& ws, float* R32, bool want_r16,
                        hipStream_t st);
-// T <= 32: streaming pass over the prepared weights; when restore, the projection runs
+// T <= 4: streaming pass over the prepared weights; when restore, the projection runs
 // in the first workgroups of the same launch
 bool decode_batch_compatible(const glowq_unit& a, const glowq_unit& b);
 int decode_max_batch();
 hipError_t launch_decode_multi(const glowq_unit* const* units, const UnitWorkspace* ws,
                                const bool* restore, int n, hipStream_t st);
-// T > 32: tiled matrix-core GEMM, correction folded in as an extra K slab.  One launch
+// 4 < T <= 64: the same with X shared through LDS; compatible units share a launch
+// T > 64 of few or small tiles goes the same way, up to this many tokens (the workspace of a unit
+// holds the slots up to here)
+constexpr int BATCH_MAX_T = 2048;
+void plan_batch_projection(const glowq_unit& u, UnitWorkspace& w);
+float batch_cost(const glowq_unit* const* units, int n);
+float prefill_cost(const glowq_unit* const* units, int n);
+bool batch_compatible(const glowq_unit& a, const glowq_unit& b);
+int batch_max_units();
+hipError_t launch_decode_batch(const glowq_unit* const* units, const UnitWorkspace* ws,
+                               const bool* restore, int n, hipStream_t st);
+// T > 64: tiled matrix-core GEMM, correction folded in as an extra K slab.  One launch
 // covers several compatible units (same types, group size and token-tile size).
 bool prefill_compatible(const glowq_unit& a, const glowq_unit& b);
 int prefill_max_units();

@@ -837,7 +837,7 @@ static hipError_t launch_mx_small(const glowq_unit& u, bool restore, char* works
   p.kslice = ((u.d_in / 32 + want - 1) / want) * 32;
   p.ksplit = (u.d_in + p.kslice - 1) / p.kslice;
   p.Rpart = (float*)(workspace + w.off_rpart);
-  p.R32 = nullptr; p.R16 = nullptr; p.ctl = nullptr; p.groups = 1;
+  p.R32 = nullptr; p.R16 = nullptr; p.ctl = nullptr;
   const int n_prod = corrected ? (u.r * p.ksplit + 3) / 4 : 0;        // one wave per (rank, part)
   const size_t lds = 4096 + (size_t)(u.d_in / 128) * (512 + 16) + 4 * MXS_MAX_PARTS * 1024;
   dim3 grid((unsigned)(n_prod + blocks)), block(256);

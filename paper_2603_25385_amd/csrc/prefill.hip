@@ -1,4 +1,4 @@
-// Prefill path (T > 32 tokens): Y_i = X dequant(W_q,i)^T + R A_i^T  (paper Eq. 9)
+// Prefill path (T > 64 tokens): Y_i = X dequant(W_q,i)^T + R A_i^T  (paper Eq. 9)
 // as a tiled matrix-core GEMM with the correction folded in as r extra channels, and
 // R = X B^T (paper Eq. 8) computed by the leading tiles of the same launch.
 //
@@ -36,7 +36,7 @@ template <int ACT> struct PfShape {
 };
 
 // One launch covers up to PF_MAX_UNITS units (PF_MAX_MODS modules in all) that share the
-// activation type, group size, output type and token-tile size; the grid is the
+// activation type, group size and output type; the grid is the
 // concatenation of the modules' tile lists, longest contraction first, so that the
 // hardware's in-order dispatch starts the long tiles first.
 constexpr int PF_MAX_UNITS = 8;
@@ -713,7 +713,7 @@ static hipError_t launch_prefill_t(const PrefillArgs& a, int n_wgs, int G, hipSt
   return hipGetLastError();
 }
 
-static inline int prefill_mb(int T) { return T <= 64 ? 4 : 8; }
+constexpr int PF_MB = 8;          // 16-token blocks per tile
 
 // Slices of K for a unit whose tiles would each run a long contraction while most of the chip
 // idles: at least 8192 channels on at most 128 tiles (a quarter of the workgroups the chip
@@ -769,7 +769,29 @@ __global__ void k_splitk_sum(const float* __restrict__ P, int S, int T, int d_ou
 
 bool prefill_compatible(const glowq_unit& a, const glowq_unit& b) {
   return a.act_dtype == b.act_dtype && a.out_dtype == b.out_dtype &&
-         a.group_size == b.group_size && prefill_mb(a.T) == prefill_mb(b.T);
+         a.group_size == b.group_size;
+}
+
+// What one launch over these units is taken to cost, in the same terms as the batched kernel's
+// tiles (us beyond the launch): 1.57 us per K tile for a workgroup alone on its compute unit,
+// 1.43 times that for two sharing one; 2 us more than the batched kernel to start and end.
+float prefill_cost(const glowq_unit* const* units, int n) {
+  double work = 0.0, wgs = 0.0;
+  int chain = 0;
+  for (int k = 0; k < n; ++k) {
+    const glowq_unit& u = *units[k];
+    const int tile_blocks = u.act_dtype == GLOWQ_F16 ? PfShape<ACT_F16>::TILE_BLOCKS : PfShape<ACT_BF16>::TILE_BLOCKS;
+    const int S = prefill_k_slices(u), kt = (u.d_in / 128 + S - 1) / S;
+    double tiles = 0.0;
+    for (int i = 0; i < u.n_modules; ++i)
+      tiles += (double)(((u.modules[i].d_out + 15) / 16 + tile_blocks - 1) / tile_blocks) * ((u.T + 127) / 128) * S;
+    wgs += tiles;
+    work += tiles * kt;
+    chain = std::max(chain, kt);
+  }
+  const double per_cu = wgs / 256.0;
+  const double share = per_cu <= 1.0 ? 1.0 : std::max(1.43, 0.72 * per_cu);
+  return (float)(2.0 + 1.57 * std::max((double)chain, work / wgs * share));
 }
 
 int prefill_max_units() { return PF_MAX_UNITS; }
@@ -780,7 +802,7 @@ hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorksp
                                 const bool* restore, int n_units, bool allow_split, hipStream_t st) {
   PrefillArgs a;
   const glowq_unit& u0 = *units[0];
-  const int MB = prefill_mb(u0.T);
+  constexpr int MB = PF_MB;
   const int tile_blocks = u0.act_dtype == GLOWQ_F16 ? PfShape<ACT_F16>::TILE_BLOCKS
                                                     : PfShape<ACT_BF16>::TILE_BLOCKS;
   // longest contraction first
@@ -876,13 +898,8 @@ hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorksp
   a.n_mods = n_mods;
   a.out_f32 = (u0.out_dtype == GLOWQ_F32) ? 1 : 0;
   const bool f16 = (u0.act_dtype == GLOWQ_F16);
-  hipError_t err;
-  if (MB == 4)
-    err = f16 ? launch_prefill_t<ACT_F16, 4>(a, wg, u0.group_size, st)
-              : launch_prefill_t<ACT_BF16, 4>(a, wg, u0.group_size, st);
-  else
-    err = f16 ? launch_prefill_t<ACT_F16, 8>(a, wg, u0.group_size, st)
-              : launch_prefill_t<ACT_BF16, 8>(a, wg, u0.group_size, st);
+  hipError_t err = f16 ? launch_prefill_t<ACT_F16, MB>(a, wg, u0.group_size, st)
+                       : launch_prefill_t<ACT_BF16, MB>(a, wg, u0.group_size, st);
   if (err != hipSuccess) return err;
   // the sliced units' outputs
   for (int ui = 0; ui < n_units; ++ui) {

@@ -17,89 +17,7 @@ struct ProjArgs {
   float* R32;          // optional fp32 [T][r]
   uint16_t* R16;       // optional act dtype [T][r]
   Control* ctl;        // control words of the unit's workspace slice
-  int groups;          // in-launch projection of 5 to 32 tokens: workgroups that share a K
-                       // slice, each with its own run of 16-rank blocks (1 or 2)
 };
-
-// One workgroup = (16-token block tb, K slice kz, group ng of the slice's 16-rank blocks);
-// any whole number of waves.
-// lds: blockDim.x / 64 * 256 floats.
-// No reduction here: every partial sum is published as one 8-byte device-scope store
-// {fp32 bits, low word of the launch tag}, slot (t, kz, j) = slots[(t ksplit + kz) r + j],
-// and the consumers add the slices (no fence, no counter, nothing to wait for).
-template <int ACT>
-__device__ inline void proj_workgroup(const ProjArgs& a, int tb, int kz, int ng, float* lds) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
-  const int nbs = (a.r + 15) >> 4;
-  const int nb_per = (nbs + a.groups - 1) / a.groups;
-  const int nb0 = ng * nb_per, nb1 = min(nbs, nb0 + nb_per);      // this workgroup's rank blocks
-  const int i = lane & 15, kq = lane >> 4;
-  // tokens past T and ranks past r are computed from clamped (valid, finite) rows and
-  // never stored: row i of D depends on row i of the first operand only, column n on
-  // column n of the second only
-  const int tok = min(tb * 16 + i, a.T - 1);
-
-  float4_t acc[8];
-#pragma unroll
-  for (int nb = 0; nb < 8; ++nb) acc[nb] = float4_t{0.f, 0.f, 0.f, 0.f};
-  GLOWQ_STAMP(0);
-
-  const int k_begin = kz * a.kslice;
-  const int k_end = min(a.K, k_begin + a.kslice);
-  const uint16_t* xrow = a.X + (size_t)tok * a.K + 8 * kq;
-  // steps of 32 channels, interleaved over the waves; the loads of PB steps are in
-  // flight together (a step past the end re-reads the first one and multiplies by zero)
-  constexpr int PB = 4;
-  for (int k0 = k_begin + wave * 32; k0 < k_end; k0 += PB * nw * 32) {
-    u32x4_t xf[PB], bf[PB][8];
-#pragma unroll
-    for (int s = 0; s < PB; ++s) {
-      const int k = k0 + s * nw * 32;
-      const bool in = k < k_end;
-      const int kc = in ? k : k0;
-      xf[s] = *(const u32x4_t*)(xrow + kc);
-      if (!in) xf[s] = u32x4_t{0u, 0u, 0u, 0u};
-#pragma unroll
-      for (int nb = 0; nb < 8; ++nb) {
-        if (nb >= nb0 && nb < nb1) {
-          const int rank = min(nb * 16 + i, a.r - 1);
-          bf[s][nb] = *(const u32x4_t*)(a.B + (size_t)rank * a.K + kc + 8 * kq);
-        }
-      }
-    }
-#pragma unroll
-    for (int s = 0; s < PB; ++s)
-#pragma unroll
-      for (int nb = 0; nb < 8; ++nb)
-        if (nb >= nb0 && nb < nb1) acc[nb] = mfma16<ACT>(xf[s], bf[s][nb], acc[nb]);   // D[token][rank]
-  }
-
-  GLOWQ_STAMP(1);
-  // fold the waves' tiles and store this slice's partial sum
-#pragma unroll
-  for (int nb = 0; nb < 8; ++nb) {
-    if (nb >= nb0 && nb < nb1) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) lds[(wave * 4 + v) * 64 + lane] = acc[nb][v];
-      __syncthreads();
-      for (int o = tid; o < 256; o += blockDim.x) {
-        const int v = o >> 6, ln = o & 63;
-        float s = 0.f;
-        for (int w = 0; w < nw; ++w) s += lds[(w * 4 + v) * 64 + ln];
-        const int t = tb * 16 + 4 * (ln >> 4) + v;
-        const int rank = nb * 16 + (ln & 15);
-        if (t < a.T && rank < a.r) {
-          const unsigned long long tag_hi = (launch_tag() & 0xffffffffull) << 32;
-          __hip_atomic_store((unsigned long long*)a.Rpart + ((size_t)t * a.ksplit + kz) * a.r + rank,
-                             tag_hi | (unsigned long long)__builtin_bit_cast(uint32_t, s),
-                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-      }
-      __syncthreads();
-    }
-  }
-  GLOWQ_STAMP(2);
-}
 
 // Projection for a handful of tokens (T <= 4), built for the shortest dependency chain:
 // one WAVE computes, for one rank j and one of `ksplit` K parts, the T partial sums

@@ -1,0 +1,56 @@
+"""GPU parity of the batched kernel (more than four tokens): every workgroup tile its rule can
+choose, at the edges of tiles, token blocks, K tiles and wave groups."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2603_25385_amd as G
+from glowq_inputs import UnitShape
+from oracle import glowq_oracle as O
+from gpu_util import DeviceUnit, Workspace, run_group, stream
+from util import recipe_unit, rel_err
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-3                     # the forward's bar: fp32 accumulation, R rounded once
+ULP = {"f16": 2.0 ** -11, "bf16": 2.0 ** -8}
+
+# (T, d_in, d_outs): one K tile for four wave groups; wave groups with unequal shares of K; ragged
+# row blocks that straddle modules; token tiles of 16, 32 and 64 with ragged last ones; from a
+# workgroup or two to several per compute unit; more than 64 tokens
+SHAPES = [(16, 128, (40, 264, 96)), (5, 1152, (40, 264, 96)), (9, 1024, (4096, 4120)), (17, 640, (2000, 2008)),
+          (32, 384, (12000,)), (20, 2048, (8000,)), (33, 128, (40, 264)), (45, 1024, (1000,)), (64, 640, (6000,)),
+          (64, 512, (20000,)), (65, 1152, (40, 264)), (79, 1152, (1960, 1960)), (129, 640, (520,)),
+          (200, 384, (4000,)), (300, 256, (264,))]
+
+
+@pytest.mark.parametrize("act,Gs", [("f16", 128), ("f16", 64), ("bf16", 128), ("bf16", 64)])
+@pytest.mark.parametrize("T,d_in,d_outs", SHAPES)
+def test_tiles_match_the_oracle(T, d_in, d_outs, act, Gs):
+    r = 72 if Gs == 128 else 16             # two whole correction steps and a ragged one; half a step
+    u = recipe_unit(O, 1, 0, T, r=r, shape=UnitShape("g", d_in, d_outs), act=act, G=Gs, method="alg1", qr="none")
+    for restore, out in ((True, "act"), (True, "f32"), (False, "f32")):
+        ys, _, _ = run_group(u, restore, out=out, ldy_pad=8)
+        tol = TOL + (ULP[act] if out == "act" else 0.0)
+        for y, ref in zip(ys, O.group_forward(u, restore)):
+            assert np.isfinite(y).all() and rel_err(y, ref) <= tol
+
+
+@pytest.mark.parametrize("T", [7, 24, 50, 90])
+def test_units_of_one_call_share_a_launch(T):
+    # units of different widths, ranks and gating in one call (more than one launch holds), called
+    # longest last, twice through one workspace: every unit's result is its own
+    shapes = [UnitShape("a", 256, (64, 40)), UnitShape("b", 128, (48,)), UnitShape("c", 2176, (136, 16)),
+              UnitShape("d", 384, (24, 24, 24))] * 5
+    mask = [(i % 3) != 1 for i in range(len(shapes))]
+    units = [recipe_unit(O, 1, 0, T, seed=50 + i, r=(8, 40, 24, 64)[i % 4], shape=s, G=128) for i, s in enumerate(shapes)]
+    dus = [DeviceUnit(u) for u in units]
+    ws = Workspace([d.desc for d in dus])
+    refs = [O.group_forward(u, f) for u, f in zip(units, mask)]
+    for _ in range(2):
+        for d in dus:
+            d.clear()
+        G.glowq_block_forward([d.desc for d in dus], bytes(mask), ws.ptr, ws.bytes, stream())
+        for d, ref in zip(dus, refs):
+            for y, yr in zip(d.outputs(), ref):
+                assert rel_err(y, yr) <= TOL
+        ws.assert_idle()
