@@ -29,7 +29,7 @@ namespace glowq {
 typedef double double4_t __attribute__((ext_vector_type(4)));
 
 constexpr int FZ_NT = 5;            // 16-column blocks per pass of a product (80 columns)
-constexpr int FZ_TARGET_WAVES = 2048;
+constexpr int FZ_TARGET_WAVES = 4096;
 
 // ---------------------------------------------------------------------------------------
 // the stack
@@ -79,31 +79,62 @@ __global__ void __launch_bounds__(256) k_error_stack(const float* __restrict__ W
 // ---------------------------------------------------------------------------------------
 // float64 products on the matrix cores.  v_mfma_f64_16x16x4: lane l holds A[l & 15][l >> 4],
 // B[l >> 4][l & 15] and, in register v, D[(l >> 4) + 4 v][l & 15].
-// One wave owns a tile of 16 RB rows x 16 NT columns over one K slice and writes it to
-// slice ks of P ([KS][M][ldp]).  Operands come straight from global memory (the small one
+// One workgroup owns a tile of 16 RB rows x 16 NT columns over one K slice, its four waves a
+// quarter of the slice each: their sums meet in LDS in wave order and go to slice ks of P
+// ([KS][M][ldp]).  (A slice per wave wrote and read four times as many partial tiles: 84 MB for
+// 3072 x 80 over 5120; the next step's operands loaded a step ahead cost the registers of half
+// the waves and 15 % of the time.)  Operands come straight from global memory (the small one
 // stays in the L2s); rows, columns and K past the edge are clamped on the load and dropped
 // (zeroed, for K) afterwards.
 // ---------------------------------------------------------------------------------------
 struct GemmShape {
   int M, N, K;
   int n0;          // first column of this pass
-  int kslice;      // channels of K per slice (multiple of 16)
+  int kslice;      // channels of K per wave (multiple of 16), four waves per slice
   int n_slices;
   int row_tiles;   // ceil(M / (16 RB))
+  const int* done; // iterated steps: nothing to do once *done <= pass (null: always run)
+  int pass;
 };
+
+// the four waves' tiles added in wave order, in wave 0's registers
+template <int RB, int NT>
+__device__ inline void fold_waves(double4_t (&acc)[RB][NT], double* fold, int wave, int lane) {
+  for (int w = 1; w < 4; ++w) {
+    if (wave == w) {
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) fold[((rb * NT + nt) * 4 + v) * 64 + lane] = acc[rb][nt][v];
+    }
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) acc[rb][nt][v] += fold[((rb * NT + nt) * 4 + v) * 64 + lane];
+    }
+    __syncthreads();
+  }
+}
 
 // C = A B, A [M][lda] and B [K][ldb] row-major.  Within a step of 16 channels lane group g
 // owns channels 4g .. 4g + 3 (contiguous in a row of A); instruction t multiplies channel
 // 4g + t of every group.
 template <int RB, int NT>
-__global__ void __launch_bounds__(256) k_gemm_nn(const double* __restrict__ A, long long lda,
+__global__ void __launch_bounds__(256) k_gemm_nn(const double* A, long long lda,
                                                  const double* __restrict__ B, long long ldb,
-                                                 double* __restrict__ P, long long ldp, GemmShape s) {
-  const int wave = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int tile = wave % s.row_tiles, ks = wave / s.row_tiles;
-  if (ks >= s.n_slices) return;
+                                                 double* P, long long ldp, GemmShape s) {
+  __shared__ double fold[RB * NT * 256];
+  const int wave = threadIdx.x >> 6;
+  const int tile = blockIdx.x % s.row_tiles, ks = blockIdx.x / s.row_tiles;
+  if (s.done && *s.done <= s.pass) return;
   const int l = threadIdx.x & 63, i = l & 15, g = l >> 4;
-  const int kbeg = ks * s.kslice, kend = min(s.K, kbeg + s.kslice);
+  const int kbeg = (4 * ks + wave) * s.kslice, kend = min(s.K, kbeg + s.kslice);
   double4_t acc[RB][NT];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb)
@@ -136,6 +167,8 @@ __global__ void __launch_bounds__(256) k_gemm_nn(const double* __restrict__ A, l
         for (int rb = 0; rb < RB; ++rb)
           acc[rb][nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rb][t], b[t][nt], acc[rb][nt], 0, 0, 0);
   }
+  fold_waves<RB, NT>(acc, fold, wave, l);
+  if (wave != 0) return;
   double* Ps = P + (long long)ks * s.M * ldp;
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb)
@@ -154,11 +187,12 @@ template <int RB, int NT>
 __global__ void __launch_bounds__(256) k_gemm_tn(const double* __restrict__ A, long long lda,
                                                  const double* __restrict__ B, long long ldb,
                                                  double* __restrict__ P, long long ldp, GemmShape s) {
-  const int wave = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int tile = wave % s.row_tiles, ks = wave / s.row_tiles;
-  if (ks >= s.n_slices) return;
+  __shared__ double fold[RB * NT * 256];
+  const int wave = threadIdx.x >> 6;
+  const int tile = blockIdx.x % s.row_tiles, ks = blockIdx.x / s.row_tiles;
+  if (s.done && *s.done <= s.pass) return;
   const int l = threadIdx.x & 63, i = l & 15, g = l >> 4;
-  const int kbeg = ks * s.kslice, kend = min(s.K, kbeg + s.kslice);
+  const int kbeg = (4 * ks + wave) * s.kslice, kend = min(s.K, kbeg + s.kslice);
   double4_t acc[RB][NT];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb)
@@ -190,6 +224,8 @@ __global__ void __launch_bounds__(256) k_gemm_tn(const double* __restrict__ A, l
         for (int rb = 0; rb < RB; ++rb)
           acc[rb][nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t][rb], b[t][nt], acc[rb][nt], 0, 0, 0);
   }
+  fold_waves<RB, NT>(acc, fold, wave, l);
+  if (wave != 0) return;
   double* Ps = P + (long long)ks * s.M * ldp;
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb)
@@ -204,9 +240,9 @@ __global__ void __launch_bounds__(256) k_gemm_tn(const double* __restrict__ A, l
 
 // C[row][col] (or C[col][row] when transposed) = sum over slices, in slice order
 __global__ void k_reduce_slices(const double* __restrict__ P, long long ldp, int n_slices, int M, int N,
-                                double* __restrict__ C, long long ldc, int transposed) {
+                                double* __restrict__ C, long long ldc, int transposed, const int* done, int pass) {
   const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (long long)M * N) return;
+  if (idx >= (long long)M * N || (done && *done <= pass)) return;
   const int row = (int)(idx / N), col = (int)(idx - (long long)row * N);
   double sum = 0.0;
   for (int sl = 0; sl < n_slices; ++sl) sum += P[((long long)sl * M + row) * ldp + col];
@@ -221,17 +257,17 @@ struct GemmPlan {
 static GemmPlan plan_gemm(int M, int K, int RB) {
   GemmPlan p;
   p.row_tiles = (M + 16 * RB - 1) / (16 * RB);
-  int want = (FZ_TARGET_WAVES + p.row_tiles - 1) / p.row_tiles;
-  const int max_slices = (K + 15) / 16;
+  int want = (FZ_TARGET_WAVES / 4 + p.row_tiles - 1) / p.row_tiles;
+  const int max_slices = (K + 63) / 64;
   if (want > max_slices) want = max_slices;
-  if (want > 64) want = 64;
+  if (want > 16) want = 16;
   if (want < 1) want = 1;
-  p.kslice = (((K + want - 1) / want) + 15) / 16 * 16;
-  p.n_slices = (K + p.kslice - 1) / p.kslice;
+  p.kslice = (((K + 4 * want - 1) / (4 * want)) + 15) / 16 * 16;
+  p.n_slices = (K + 4 * p.kslice - 1) / (4 * p.kslice);
   return p;
 }
 
-constexpr int NN_RB = 2, TN_RB = 4;
+constexpr int NN_RB = 2, TN_RB = 2;
 
 static size_t gemm_slice_doubles(int M, int N, int K, int RB) {
   const GemmPlan p = plan_gemm(M, K, RB);
@@ -241,21 +277,30 @@ static size_t gemm_slice_doubles(int M, int N, int K, int RB) {
 template <bool TN, int NT>
 static void launch_gemm_pass(const double* A, long long lda, const double* B, long long ldb, double* P,
                              long long ldp, const GemmShape& s, hipStream_t st) {
-  const int waves = s.row_tiles * s.n_slices;
-  dim3 grid((unsigned)((waves + 3) / 4)), block(256);
+  dim3 grid((unsigned)(s.row_tiles * s.n_slices)), block(256);
   if (TN) k_gemm_tn<TN_RB, NT><<<grid, block, 0, st>>>(A, lda, B, ldb, P, ldp, s);
   else k_gemm_nn<NN_RB, NT><<<grid, block, 0, st>>>(A, lda, B, ldb, P, ldp, s);
 }
 
-// C [M][N] = op(A) B through the slice buffer
+// C [M][N] = op(A) B through the slice buffer (C may be A: it is written when A has been read).
+// A short contraction on one pass of columns (A B, K <= 80) needs no slices: every workgroup has
+// the whole sum of its rows and writes them to C itself.
 template <bool TN>
 static hipError_t gemm(const double* A, long long lda, const double* B, long long ldb, double* C,
                        long long ldc, bool c_transposed, int M, int N, int K, double* slices,
-                       hipStream_t st) {
-  const GemmPlan p = plan_gemm(M, K, TN ? TN_RB : NN_RB);
-  const long long ldp = (N + 15) / 16 * 16;
+                       hipStream_t st, const int* done = nullptr, int pass = 0) {
+  GemmPlan p = plan_gemm(M, K, TN ? TN_RB : NN_RB);
+  long long ldp = (N + 15) / 16 * 16;
+  const bool direct = !TN && !c_transposed && K <= 16 * FZ_NT && N <= 16 * FZ_NT;
+  if (direct) {
+    p.kslice = (K + 63) / 64 * 16;
+    p.n_slices = 1;
+    slices = C;
+    ldp = ldc;
+  }
   GemmShape s;
   s.M = M; s.N = N; s.K = K;
+  s.done = done; s.pass = pass;
   s.kslice = p.kslice; s.n_slices = p.n_slices; s.row_tiles = p.row_tiles;
   for (int n0 = 0; n0 < N; n0 += 16 * FZ_NT) {
     s.n0 = n0;
@@ -268,14 +313,209 @@ static hipError_t gemm(const double* A, long long lda, const double* B, long lon
       default: launch_gemm_pass<TN, 5>(A, lda, B, ldb, slices, ldp, s, st); break;
     }
   }
+  if (direct) return hipGetLastError();
   const long long n = (long long)M * N;
   k_reduce_slices<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st>>>(slices, ldp, p.n_slices, M, N, C,
-                                                                          ldc, c_transposed ? 1 : 0);
+                                                                          ldc, c_transposed ? 1 : 0, done, pass);
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------------
-// Q = orth(Y): classical Gram-Schmidt, every column projected twice.  Y is [m][ld], l
+// Q = orth(Y) for sketches of up to FZ_SMALL columns: Cholesky QR, iterated.  A pass forms the
+// Gram matrix of Y (matrix cores), factors it in one workgroup's LDS and multiplies Y with the
+// inverse factor, so that a pass costs four launches whatever l is (80 columns x 5120 rows: 170 us;
+// column by column, three launches each, 1930 us).  A Cholesky factor of a Gram matrix only resolves columns whose part
+// outside the span of the columns before them is well above its rounding.  So a column whose
+// share of norm^2 outside that span falls below FZ_ACCEPT is deferred: this pass takes the
+// span out of it but does not project anybody on it, and the next pass, where it starts at
+// length one again, decides anew.  `kept` follows the product of those shares; a column that
+// kept less than FZ_RANK_TOL2 of its norm^2 is dependent and cleared.  The passes end when all
+// remaining columns were accepted with pivots above one half, i.e. when the columns were
+// orthogonal before the pass up to what the pass itself corrects to rounding.  Two passes for a
+// sketch of condition 10^4, five for 10^12.
+// ---------------------------------------------------------------------------------------
+constexpr int FZ_SMALL = 128;
+constexpr int FZ_QR_PASSES = 6;
+constexpr double FZ_ACCEPT = 1e-8;
+constexpr double FZ_RANK_TOL2 = 1e-24;      // a column whose norm^2 fell by this factor is dependent
+constexpr int FZ_LD = FZ_SMALL + 2;
+enum { FZ_PENDING = 0, FZ_KEPT = 1, FZ_DROPPED = 2 };
+
+// 1 / sqrt(x) to working precision: the hardware's estimate and two Newton steps
+__device__ inline double inv_sqrt(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  const double h = 0.5 * x;
+  y = y * __builtin_fma(-h * y, y, 1.5);
+  return y * __builtin_fma(-h * y, y, 1.5);
+}
+
+// D += sum over 16 channels of A B, 16 x 16 blocks of doubles anywhere (element (i, k) of A at
+// A[i ai + k ak], and so on): four matrix instructions.
+__device__ inline double4_t block_product(const double* A, int ai, int ak, const double* B, int bk, double4_t acc) {
+  const int l = (int)threadIdx.x & 63, i = l & 15, g = l >> 4;
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[i * ai + (4 * t + g) * ak], B[(4 * t + g) * bk + i], acc, 0, 0, 0);
+  return acc;
+}
+__device__ inline double read_lane(double v, int lane) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// Cholesky factor R (upper, S = R^T R) of a symmetric matrix of nb x nb blocks of 16 in LDS
+// (S [16 nb][LD], upper blocks and whole diagonal blocks), by one workgroup; with INVERSE, S
+// ends as the upper triangular T = R^-1, without it as R.  Panels of 16 rows: one wave factors
+// and inverts the diagonal block with a column per lane, matrix instructions do the rest.  The
+// code is kept small on purpose: a lone workgroup that runs through it once is bound by fetching
+// its instructions (unrolled over registers, element by element, 80 columns took 230 us, this
+// about 20).  pivot(j, d, own) returns 1 / sqrt(d) if column j is to be used and 0 if not;
+// `own` then scales what stays of its own column in T.  E, F, Rb: LDS, 256, 256 and 16 LD
+// doubles (Rb only with INVERSE).
+template <bool INVERSE, class PIVOT>
+__device__ inline void block_cholesky(double* S, int LD, int nb, double* E, double* F, double* Rb, PIVOT pivot) {
+  const int t = threadIdx.x, wave = t >> 6, lane = t & 63, i = lane & 15, g = lane >> 4, waves = (int)blockDim.x >> 6;
+  auto put = [&](double* D, int ld, double4_t v) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) D[(g + 4 * q) * ld + i] = v[q];
+  };
+  auto get = [&](const double* D, int ld) {
+    double4_t v;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = D[(g + 4 * q) * ld + i];
+    return v;
+  };
+  const double4_t zero = double4_t{0.0, 0.0, 0.0, 0.0};
+  for (int J = 0; J < nb; ++J) {
+    double* Sj = S + 16 * J * LD;                    // block row J
+    __syncthreads();
+    if (wave == 0) {
+      double a[16];
+      bool used = false;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) a[k] = Sj[k * LD + 16 * J + i];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        double own = 0.0;
+        const double ri = pivot(16 * J + j, read_lane(a[j], j), own);
+        const double w = -a[j] * ri * ri;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+          if (k == j) continue;
+          const double v = read_lane(a[k], j);
+          if (i > j) a[k] = __builtin_fma(v, w, a[k]);
+          else if (i == j && k < j) a[k] *= own;
+        }
+        if (i > j) a[j] = w;
+        else if (i == j) {
+          a[j] = own;
+          used = ri > 0.0;
+        }
+      }
+      if (lane < 16) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+          const double f = k <= i ? a[k] : 0.0;
+          F[k * 16 + i] = f;
+          E[k * 16 + i] = used ? f : 0.0;
+        }
+      }
+    }
+    __syncthreads();
+    // row J of the factor, E^T S_JK, and of the inverse, -E R_JK
+    for (int K = J + (INVERSE ? 1 : 0) + wave; K < nb; K += waves) {
+      double* R = INVERSE ? Rb + 16 * K : Sj + 16 * K;
+      const int LR = LD;
+      const double4_t v = block_product(E, 1, 16, Sj + 16 * K, LD, zero);
+      put(R, LR, v);
+      if (INVERSE) {
+        const double4_t u = block_product(E, 16, 1, R, LR, zero);
+        put(Sj + 16 * K, LD, -u);
+      }
+    }
+    __syncthreads();
+    const double* R = INVERSE ? Rb : Sj;
+    const int rest = nb - 1 - J, below = rest * rest, total = below + (INVERSE ? J * rest : 0);
+    for (int b = wave; b < total; b += waves) {
+      if (b < below) {
+        const int I = J + 1 + b / rest, K = J + 1 + b % rest;
+        if (K < I) continue;
+        double* D = S + 16 * I * LD + 16 * K;
+        const double4_t v = block_product(R + 16 * I, 1, LD, R + 16 * K, LD, zero);
+        put(D, LD, get(D, LD) - v);
+      } else {
+        const int I = (b - below) / rest, K = J + 1 + (b - below) % rest;
+        double* D = S + 16 * I * LD + 16 * K;
+        put(D, LD, block_product(S + 16 * I * LD + 16 * J, LD, 1, Sj + 16 * K, LD, get(D, LD)));
+      }
+    }
+    if (INVERSE) {
+      __syncthreads();
+      for (int I = wave; I <= J; I += waves) {
+        double* D = S + 16 * I * LD + 16 * J;
+        if (I < J) put(D, LD, block_product(D, LD, 1, F, 16, zero));
+        else put(D, LD, get(F, 16));
+      }
+    }
+  }
+  __syncthreads();
+}
+
+// One workgroup.  G: Gram matrix [l][ldg]; Tinv (upper triangular): Y Tinv is the next Y.
+__global__ void __launch_bounds__(1024) k_cholesky_step(const double* __restrict__ G, long long ldg, int l,
+                                                        double* __restrict__ Tinv, long long ldt, double* kept,
+                                                        int* state, int* done, int pass) {
+  __shared__ double S[FZ_SMALL * FZ_LD], Rb[16 * FZ_LD], E[256], F[256], scale[FZ_SMALL];
+  __shared__ int st[FZ_SMALL], pending;
+  __shared__ double least;
+  if (pass > 0 && *done <= pass) return;
+  const int t = threadIdx.x, nb = (l + 15) >> 4, n16 = 16 * nb, LD = n16 + 2;
+  const bool last = pass == FZ_QR_PASSES - 1;
+  if (t < n16) {
+    const double gg = t < l ? G[(long long)t * ldg + t] : 0.0;
+    double k2 = pass && t < l ? kept[t] : 1.0;
+    int s0 = pass && t < l ? state[t] : FZ_PENDING;
+    if (pass && s0 == FZ_PENDING) k2 *= gg;
+    if (!(gg > 0.0) || k2 <= FZ_RANK_TOL2) s0 = FZ_DROPPED;
+    scale[t] = s0 == FZ_DROPPED ? 0.0 : 1.0 / sqrt(gg);
+    st[t] = s0;
+    if (t < l) kept[t] = k2;
+  }
+  if (t == 0) {
+    least = 1.0;
+    pending = 0;
+  }
+  __syncthreads();
+  for (int idx = t; idx < n16 * n16; idx += 1024) {
+    const int i = idx / n16, k = idx - i * n16;
+    const double w = scale[i] * scale[k];
+    S[i * LD + k] = w > 0.0 && (i >> 4) <= (k >> 4) ? G[(long long)i * ldg + k] * w : 0.0;
+  }
+  block_cholesky<true>(S, LD, nb, E, F, Rb, [&](int j, double d, double& own) {
+    // (wave 0 only.)  Kept: scaled to length one; deferred: as the projections left it; dropped:
+    // cleared
+    const bool dropped = scale[j] == 0.0, keep = !dropped && d > FZ_ACCEPT;
+    const double ri = keep ? inv_sqrt(d) : 0.0;
+    own = keep ? ri : (dropped || last ? 0.0 : 1.0);
+    if (t == 0) {
+      st[j] = keep ? FZ_KEPT : (dropped || last ? FZ_DROPPED : FZ_PENDING);
+      if (keep) least = fmin(least, d);
+      else if (!dropped) pending = 1;
+    }
+    return ri;
+  });
+  for (int idx = t; idx < l * l; idx += 1024) {
+    const int i = idx / l, k = idx - i * l;
+    Tinv[(long long)i * ldt + k] = k >= i ? scale[i] * S[i * LD + k] : 0.0;
+  }
+  if (t < l) state[t] = st[t];
+  if (t == 0) *done = pending == 0 && least > 0.5 ? pass + 1 : 1 << 30;
+}
+
+// ---------------------------------------------------------------------------------------
+// The same for wider sketches: classical Gram-Schmidt, every column projected twice.  Y is [m][ld], l
 // columns, l <= 256.  Workgroup b owns rows [b rpw, (b + 1) rpw), rpw <= 256, in every
 // launch; sums over rows go through per-workgroup partials that every workgroup adds in the
 // same order.  Three launches per column j:
@@ -291,8 +531,6 @@ struct CgsBuffers {
   double* norm;     // [n_groups]      |y_j|^2 after both projections
   double* norm0;    // [2][n_groups]   |y_j|^2 before, by parity of j
 };
-
-constexpr double FZ_RANK_TOL2 = 1e-24;      // a column whose norm^2 fell by this factor is dependent
 
 __device__ inline double wave_sum(double v) {
 #pragma unroll
@@ -408,7 +646,6 @@ __global__ void __launch_bounds__(256) k_cgs(double* __restrict__ Y, long long l
 // rotations of sweep w; once a sweep made none, the launches of later sweeps return at once.
 // ---------------------------------------------------------------------------------------
 constexpr int FZ_MAX_SWEEPS = 16;
-constexpr int FZ_POLISH_SWEEPS = 8;     // after the rotation by the Gram matrix's eigenvectors
 constexpr double FZ_JACOBI_TOL2 = 1e-28;     // rotate while (a.b)^2 > tol^2 |a|^2 |b|^2, tol = 1e-14
 
 constexpr int FZ_JT = 1024;       // threads of a Jacobi workgroup
@@ -471,99 +708,186 @@ __global__ void __launch_bounds__(FZ_JT) k_jacobi_round(double* __restrict__ Bs,
   }
 }
 
-// Eigenvectors of the l x l Gram matrix T = Bs Bs^T by two-sided Jacobi rotations, one
-// workgroup, T in LDS (l <= FZ_EIG_MAX): with Um = its eigenvectors, the rows of Um^T Bs
-// are orthogonal up to the rounding of the Gram matrix, so that the one-sided rotations on
-// the long rows that follow only polish (one or two sweeps instead of eight or nine).  The
-// same rotation G = [[c, -s], [s, c]] on the pair (a, b) as above: T <- G T G^T, rows then
-// columns, and the columns of Um.  Rounds pair the players as above; all pairs of a round
-// are disjoint and are rotated together.
-constexpr int FZ_EIG_MAX = 128;
-constexpr int FZ_EIG_SWEEPS = 8;
-constexpr int FZ_EIG_LDS_DOUBLES = 19 * 1024;     // 152 KiB: T, and Um beside it when both fit (l <= 97)
-constexpr double FZ_EIG_TOL2 = 1e-20;             // rotate while (T_ab)^2 > tol^2 T_aa T_bb, tol = 1e-10 ...
-constexpr double FZ_EIG_ABS = 1e-13;              // ... and |T_ab| is above the rounding of the largest entry
+// The same for up to FZ_SMALL rows, through the l x l Gram matrix G of the rows.  G = L L^T
+// (Cholesky), and one-sided rotations V make the columns of Z = L V orthogonal: then G = Z Z^T,
+// the columns of Z divided by their lengths are the rotation U itself, and nothing has to be
+// collected beside Z.  One workgroup with Z in LDS: 16 lanes per pair of columns, all pairs of a
+// round at once, one barrier per round.  U is applied to the long rows by one product, and the
+// next pass starts from their new Gram matrix, which knows every small row relative to its own
+// length: a second pass removes what the first one's rounding left (relative to the largest
+// row), a third only runs when the second still found something to rotate.  Any orthogonal U is
+// exact work whatever G was, so a pivot that is only rounding is replaced by FZ_PIVOT and costs
+// convergence, not accuracy.  80 rows of 3072: 540 us, of them 510 in seven to eight sweeps of 79
+// rounds, bound by issue and LDS (1600 cycles a round); two-sided rotations with three barriers a
+// round followed by one launch per round on the long rows took 1830 + 1620 us.
+constexpr int FZ_SVD_PASSES = 3;
+constexpr int FZ_SMALL_SWEEPS = 12;
+constexpr double FZ_LAST_SWEEP2 = 1e-15;
+constexpr double FZ_QUIET2 = 1e-26;         // rows whose (a.b)^2 is below this share of |a|^2 |b|^2 need no further pass
+constexpr double FZ_PIVOT = 1e-13;          // of a unit diagonal: below, the row's remainder is rounding
 
-__global__ void __launch_bounds__(1024) k_gram_eigenvectors(const double* __restrict__ Tg, long long ldt, int l,
-                                                            double* __restrict__ Um, long long ldu) {
-  __shared__ double pool[FZ_EIG_LDS_DOUBLES];
-  __shared__ double cs[FZ_EIG_MAX / 2], sn[FZ_EIG_MAX / 2];
-  __shared__ int pa[FZ_EIG_MAX / 2], pb[FZ_EIG_MAX / 2];
-  __shared__ int rotated;
-  __shared__ double tmax;
-  const int t = threadIdx.x, LD = l + 1;
-  double* T = pool;
-  const bool u_in_lds = 2 * l * LD <= FZ_EIG_LDS_DOUBLES;
-  double* U = u_in_lds ? pool + l * LD : Um;           // (generic pointer: LDS or global)
-  const long long LDU = u_in_lds ? LD : ldu;
-  for (int idx = t; idx < l * l; idx += 1024) {
-    const int i = idx / l, k = idx - i * l;
-    T[i * LD + k] = Tg[(long long)i * ldt + k];
-    U[(long long)i * LDU + k] = i == k ? 1.0 : 0.0;
-  }
-  __syncthreads();
-  if (t == 0) {
-    double mx = 0.0;
-    for (int i = 0; i < l; ++i) mx = fmax(mx, T[i * LD + i]);
-    tmax = mx;
-  }
-  const int n = (l + 1) & ~1, pairs = n / 2;
-  for (int sweep = 0; sweep < FZ_EIG_SWEEPS; ++sweep) {
-    __syncthreads();
-    if (t == 0) rotated = 0;
-    for (int round = 0; round < n - 1; ++round) {
-      __syncthreads();
-      if (t < pairs) {
-        int a, b;
-        if (t == 0) { a = n - 1; b = round; }
-        else { a = (round + t) % (n - 1); b = (round - t + (n - 1)) % (n - 1); }
-        double c = 1.0, s = 0.0;
-        if (a < l && b < l) {
-          const double aa = T[a * LD + a], bb = T[b * LD + b], ab = T[a * LD + b];
-          if (ab * ab > FZ_EIG_TOL2 * aa * bb && fabs(ab) > FZ_EIG_ABS * tmax) {
-            const double zeta = (bb - aa) / (2.0 * ab);
-            const double tt = (zeta >= 0.0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-            c = 1.0 / sqrt(1.0 + tt * tt);
-            s = c * tt;
-            rotated = 1;
-          }
-        } else {
-          a = b = -1;
-        }
-        pa[t] = a; pb[t] = b; cs[t] = c; sn[t] = s;
-      }
-      __syncthreads();
-      // rows a, b of every pair
-      for (int idx = t; idx < pairs * l; idx += 1024) {
-        const int k = idx / l, i = idx - k * l, a = pa[k], b = pb[k];
-        if (a < 0 || sn[k] == 0.0) continue;
-        const double x = T[a * LD + i], y = T[b * LD + i];
-        T[a * LD + i] = cs[k] * x - sn[k] * y;
-        T[b * LD + i] = sn[k] * x + cs[k] * y;
-      }
-      __syncthreads();
-      // columns a, b of every pair, of T and of the eigenvector matrix
-      for (int idx = t; idx < pairs * l; idx += 1024) {
-        const int k = idx / l, i = idx - k * l, a = pa[k], b = pb[k];
-        if (a < 0 || sn[k] == 0.0) continue;
-        const double x = T[i * LD + a], y = T[i * LD + b];
-        T[i * LD + a] = cs[k] * x - sn[k] * y;
-        T[i * LD + b] = sn[k] * x + cs[k] * y;
-        double* u = U + (long long)i * LDU;
-        const double ux = u[a], uy = u[b];
-        u[a] = cs[k] * ux - sn[k] * uy;
-        u[b] = sn[k] * ux + cs[k] * uy;
-      }
-    }
-    __syncthreads();
-    if (rotated == 0) break;
-  }
-  if (u_in_lds) {
-    __syncthreads();
+// sum over the 16 lanes of a DPP row, in every lane
+template <int ROR> __device__ inline double row_rotate(double v) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x120 | ROR, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x120 | ROR, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+__device__ inline double row_sum16(double v) {
+  v += row_rotate<8>(v);
+  v += row_rotate<4>(v);
+  v += row_rotate<2>(v);
+  v += row_rotate<1>(v);
+  return v;
+}
+
+// NQ: 16-element pieces of a column (l <= 16 NQ).  Zt[k] is column k of Z.
+template <int NQ>
+__global__ void __launch_bounds__(1024) k_row_rotations(const double* __restrict__ G, long long ldg, int l,
+                                                        double* __restrict__ U, const double* __restrict__ Um_old,
+                                                        double* __restrict__ Um_new, long long ldu, int* done, int pass) {
+  constexpr int LW = 16 * NQ, LD = LW + (NQ > 6 ? 4 : 16);      // (the pad spreads columns over the banks)
+  __shared__ double Zt[16 * NQ * LD];
+  __shared__ double E[256], F[256], len2[16 * NQ], tiny[16 * NQ];
+  __shared__ int rotated[2];
+  const int t = threadIdx.x;
+  if (pass > 0 && *done <= pass) {
     for (int idx = t; idx < l * l; idx += 1024) {
       const int i = idx / l, k = idx - i * l;
-      Um[(long long)i * ldu + k] = U[(long long)i * LDU + k];
+      Um_new[(long long)i * ldu + k] = Um_old[(long long)i * ldu + k];
     }
+    return;
+  }
+  if (t < LW) {
+    const double gg = t < l ? G[(long long)t * ldg + t] : 0.0;
+    len2[t] = gg > 0.0 ? sqrt(gg) : 0.0;            // (row lengths for now)
+    tiny[t] = 0.0;
+  }
+  if (t == 0) rotated[0] = 0;
+  __syncthreads();
+  for (int idx = t; idx < LW * LW; idx += 1024) {
+    const int i = idx / LW, k = idx - i * LW;
+    const double w = len2[i] * len2[k];
+    const double c = w > 0.0 ? G[(long long)i * ldg + k] / w : 0.0;
+    if (i != k && c * c > FZ_QUIET2) rotated[0] = 1;
+    Zt[i * LD + k] = (i >> 4) <= (k >> 4) ? c : 0.0;
+  }
+  __syncthreads();
+  const bool quiet = pass > 0 && rotated[0] == 0;   // already orthogonal: nothing to apply
+  if (!quiet) {
+    block_cholesky<false>(Zt, LD, NQ, E, F, nullptr, [&](int j, double d, double& own) {
+      const bool real = d > FZ_PIVOT;
+      if (!real && t == 0) tiny[j] = sqrt(FZ_PIVOT);
+      const double ri = real ? inv_sqrt(d) : 0.0;
+      own = ri;
+      return ri;
+    });
+    // column j of Z: row j of the factor, every element scaled back by its row's length
+    for (int idx = t; idx < LW * LW; idx += 1024) {
+      const int j = idx / LW, k = idx - j * LW;
+      Zt[j * LD + k] = k < j ? 0.0 : (k == j && tiny[j] > 0.0 ? tiny[j] : Zt[j * LD + k]) * len2[k];
+    }
+  }
+  const int n = (l + 1) & ~1, pairs = n / 2, p = t >> 4, sub = t & 15;
+  for (int sweep = 0; sweep < FZ_SMALL_SWEEPS && !quiet; ++sweep) {
+    __syncthreads();
+    if (t == 0) rotated[sweep & 1] = 0;
+    for (int i = p; i < l; i += 64) {
+      double s = 0.0;
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const double x = Zt[i * LD + sub + 16 * q];
+        s += x * x;
+      }
+      s = row_sum16(s);
+      if (sub == 0) len2[i] = s;
+    }
+    for (int round = 0; round < n - 1; ++round) {
+      __syncthreads();
+      if (p >= pairs) continue;
+      int a, b;
+      if (p == 0) { a = n - 1; b = round; }
+      else {
+        a = round + p;
+        if (a >= n - 1) a -= n - 1;
+        b = round - p;
+        if (b < 0) b += n - 1;
+      }
+      if (a >= l || b >= l) continue;               // the odd player out
+      double* za = Zt + a * LD + sub;
+      double* zb = Zt + b * LD + sub;
+      double xa[NQ], xb[NQ], ab = 0.0;
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        xa[q] = za[16 * q];
+        xb[q] = zb[16 * q];
+        ab += xa[q] * xb[q];
+      }
+      ab = row_sum16(ab);
+      const double aa = len2[a], bb = len2[b];
+      if (!(ab * ab > FZ_JACOBI_TOL2 * aa * bb)) continue;
+      // the tangent of the angle from the hardware's estimates (the next sweep takes what they
+      // leave), cosine and sine to working precision: they must belong to one angle
+      const double zeta = (bb - aa) * 0.5 * __builtin_amdgcn_rcp(ab);
+      const double az = fmin(fabs(zeta), 1e100), h = __builtin_fma(az, az, 1.0);
+      const double tt = copysign(__builtin_amdgcn_rcp(az + h * __builtin_amdgcn_rsq(h)), zeta);
+      const double cs = inv_sqrt(__builtin_fma(tt, tt, 1.0)), sn = cs * tt;
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        za[16 * q] = cs * xa[q] - sn * xb[q];
+        zb[16 * q] = sn * xa[q] + cs * xb[q];
+      }
+      if (sub == 0) {
+        len2[a] = fmax(aa - tt * ab, 0.0);
+        len2[b] = bb + tt * ab;
+        // (rotations this small leave the square of it: no other sweep has to look)
+        if (ab * ab > FZ_LAST_SWEEP2 * aa * bb) rotated[sweep & 1] = 1;
+      }
+    }
+    __syncthreads();
+    if (rotated[sweep & 1] == 0) break;
+  }
+  __syncthreads();
+  // U = Z with columns of length one (a zero row of G is a direction of its own)
+  for (int i = p; i < l && !quiet; i += 64) {
+    double s = 0.0;
+    for (int q = 0; q < NQ; ++q) {
+      const double x = Zt[i * LD + sub + 16 * q];
+      s += x * x;
+    }
+    s = row_sum16(s);
+    const double is = s > 0.0 ? 1.0 / sqrt(s) : 0.0;
+    for (int q = 0; q < NQ; ++q) {
+      const int k = sub + 16 * q;
+      Zt[i * LD + k] = s > 0.0 ? Zt[i * LD + k] * is : (k == i ? 1.0 : 0.0);
+    }
+  }
+  __syncthreads();
+  for (int idx = t; idx < l * l; idx += 1024) {
+    const int i = idx / l, k = idx - i * l;
+    double v = Zt[k * LD + i];
+    if (!quiet) U[(long long)i * ldu + k] = v;
+    if (quiet) {
+      v = Um_old[(long long)i * ldu + k];
+    } else if (pass > 0) {
+      v = 0.0;
+      for (int c = 0; c < l; ++c) v += Um_old[(long long)i * ldu + c] * Zt[k * LD + c];
+    }
+    Um_new[(long long)i * ldu + k] = v;
+  }
+  if (t == 0) *done = quiet ? pass : 1 << 30;
+}
+
+static void launch_row_rotations(const double* G, long long ldg, int l, double* U, const double* Um_old, double* Um_new,
+                                 long long ldu, int* done, int pass, hipStream_t st) {
+  const dim3 g(1), b(1024);
+  switch ((l + 15) / 16) {
+    case 1: case 2: k_row_rotations<2><<<g, b, 0, st>>>(G, ldg, l, U, Um_old, Um_new, ldu, done, pass); break;
+    case 3: k_row_rotations<3><<<g, b, 0, st>>>(G, ldg, l, U, Um_old, Um_new, ldu, done, pass); break;
+    case 4: k_row_rotations<4><<<g, b, 0, st>>>(G, ldg, l, U, Um_old, Um_new, ldu, done, pass); break;
+    case 5: k_row_rotations<5><<<g, b, 0, st>>>(G, ldg, l, U, Um_old, Um_new, ldu, done, pass); break;
+    case 6: k_row_rotations<6><<<g, b, 0, st>>>(G, ldg, l, U, Um_old, Um_new, ldu, done, pass); break;
+    default: k_row_rotations<8><<<g, b, 0, st>>>(G, ldg, l, U, Um_old, Um_new, ldu, done, pass); break;
   }
 }
 
@@ -574,13 +898,13 @@ __global__ void k_identity(double* U, long long ld, int l) {
   U[(long long)a * ld + i] = a == i ? 1.0 : 0.0;
 }
 
-// sig2[a] = |row a of Bs|^2; one block per row
-__global__ void __launch_bounds__(256) k_row_norms(const double* __restrict__ Bs, long long ldb, int d,
+// sig2[a] = |row a of Bs|^2; one block per row.  Element (a, i) of Bs is at a rs + i cs.
+__global__ void __launch_bounds__(256) k_row_norms(const double* __restrict__ Bs, long long rs, long long cs, int d,
                                                    double* sig2) {
   __shared__ double red[4];
-  const double* r = Bs + (long long)blockIdx.x * ldb;
+  const double* r = Bs + (long long)blockIdx.x * rs;
   double s = 0.0;
-  for (int i = threadIdx.x; i < d; i += 256) s += r[i] * r[i];
+  for (int i = threadIdx.x; i < d; i += 256) s += r[i * cs] * r[i * cs];
   s = block_sum(s, red);
   if (threadIdx.x == 0) sig2[blockIdx.x] = s;
 }
@@ -621,14 +945,14 @@ __global__ void k_store_A(const double* __restrict__ A64, long long lda, long lo
 
 // B[jr][k] = row perm jr of Bs / sqrt(sigma_jr) * Sigma_x^(-1/2)[k]
 template <int ACT>
-__global__ void k_store_B(const double* __restrict__ Bs, long long ldb, const double* sigma_sorted,
+__global__ void k_store_B(const double* __restrict__ Bs, long long rs, long long cs, const double* sigma_sorted,
                           const int* perm, const double* __restrict__ inv_root, int r, int d,
                           uint16_t* __restrict__ B) {
   const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= (long long)r * d) return;
   const int jr = (int)(idx / d), k = (int)(idx - (long long)jr * d);
   const double s = sigma_sorted[jr];
-  double v = s > 0.0 ? Bs[(long long)perm[jr] * ldb + k] / sqrt(s) : 0.0;
+  double v = s > 0.0 ? Bs[(long long)perm[jr] * rs + k * cs] / sqrt(s) : 0.0;
   if (inv_root) v *= inv_root[k];
   B[idx] = (uint16_t)act16_round<ACT>(v);
 }
@@ -670,7 +994,9 @@ FactorizePlan plan_factorize(const glowq_unit& u, int r, int p) {
   size_t s3 = gemm_slice_doubles((int)m, r, f.l, NN_RB);                        // A = Q P
   size_t s4 = gemm_slice_doubles(f.l, f.l, f.d, TN_RB);                         // Gram of Bs
   size_t s5 = gemm_slice_doubles(f.d, f.l, f.l, NN_RB);                         // rows = Um^T Bs
-  for (size_t o : {s2, s3, s4, s5})
+  size_t s6 = gemm_slice_doubles((int)m, f.l, f.l, NN_RB);                      // Y Tinv
+  size_t s7 = gemm_slice_doubles(f.l, f.l, (int)m, TN_RB);                      // Gram of Y
+  for (size_t o : {s2, s3, s4, s5, s6, s7})
     if (o > sl) sl = o;
   f.off_slices = take(sl * 8);
   f.off_root = take((size_t)f.d * 8);
@@ -683,6 +1009,11 @@ FactorizePlan plan_factorize(const glowq_unit& u, int r, int p) {
   f.off_sigma = take(256 * 8);
   f.off_perm = take(256 * 4);
   f.off_counters = take(FZ_MAX_SWEEPS * 4);
+  f.off_rot = take((size_t)f.l * f.l16 * 8);
+  f.off_um2 = take((size_t)f.l * f.l16 * 8);
+  f.off_kept = take(256 * 8);
+  f.off_state = take(256 * 4);
+  f.off_done = take(2 * 4);
   f.bytes = off;
   return f;
 }
@@ -700,6 +1031,7 @@ hipError_t launch_factorize(const glowq_unit& u, const float* const* W_modules, 
   double* Um = (double*)(ws + f.off_ut);
   double* gram = (double*)(ws + f.off_gram);
   double* lift = (double*)(ws + f.off_lift);
+  double* factor = (double*)(ws + f.off_rot);      // [l][l16]: the matrix a pass multiplies with
   double* A64 = (double*)(ws + f.off_a64);
   double* slices = (double*)(ws + f.off_slices);
   double* root = sigma_x ? (double*)(ws + f.off_root) : nullptr;
@@ -734,40 +1066,60 @@ hipError_t launch_factorize(const glowq_unit& u, const float* const* W_modules, 
     if (err == hipSuccess) err = gemm<false>(Ms, d, Z, f.l16, Y, f.l16, false, m, l, d, slices, st);
   }
   if (err != hipSuccess) return err;
-  // orthonormal basis of the range
-  for (int j = 0; j <= l; ++j) {
-    k_cgs<<<dim3((unsigned)f.n_groups), dim3(256), 0, st>>>(Y, f.l16, m, l, f.rpw, f.n_groups, j, 0, cb);
-    if (j == l) break;
-    if (j > 0) {
-      k_cgs<<<dim3((unsigned)f.n_groups), dim3(256), 0, st>>>(Y, f.l16, m, l, f.rpw, f.n_groups, j, 1, cb);
-      k_cgs<<<dim3((unsigned)f.n_groups), dim3(256), 0, st>>>(Y, f.l16, m, l, f.rpw, f.n_groups, j, 2, cb);
-    } else {
-      // the first column has nothing to be projected against: its norm is the one just taken
-      k_cgs<<<dim3((unsigned)f.n_groups), dim3(256), 0, st>>>(Y, f.l16, m, l, f.rpw, f.n_groups, 0, 2, cb);
+  // orthonormal basis of the range, compressed matrix Bs = Q^T Ms and its SVD
+  const double* rows;          // element (a, i) of Um^T Bs at a rows_rs + i rows_cs
+  long long rows_rs, rows_cs;
+  if (l <= FZ_SMALL) {
+    int* done = (int*)(ws + f.off_done);
+    for (int pass = 0; pass < FZ_QR_PASSES; ++pass) {
+      const int* stop = pass ? done : nullptr;
+      err = gemm<true>(Y, f.l16, Y, f.l16, gram, f.l16, false, l, l, m, slices, st, stop, pass);
+      if (err != hipSuccess) return err;
+      k_cholesky_step<<<dim3(1), dim3(1024), 0, st>>>(gram, f.l16, l, factor, f.l16, (double*)(ws + f.off_kept),
+                                                      (int*)(ws + f.off_state), done, pass);
+      err = gemm<false>(Y, f.l16, factor, f.l16, Y, f.l16, false, m, l, l, slices, st, stop, pass);
+      if (err != hipSuccess) return err;
     }
-  }
-  // compressed matrix Bs = Q^T Ms and its SVD.  When the small Gram matrix fits one
-  // workgroup's LDS its eigenvectors rotate the rows first, and the one-sided rotations on
-  // the long rows only polish.
-  int sweeps = FZ_MAX_SWEEPS;
-  if (l <= FZ_EIG_MAX) {
     double* BsT = Z;                                                               // [d][l16]
     err = gemm<true>(Ms, d, Y, f.l16, BsT, f.l16, false, d, l, m, slices, st);     // Ms^T Q
-    if (err == hipSuccess) err = gemm<true>(BsT, f.l16, BsT, f.l16, gram, f.l16, false, l, l, d, slices, st);
+    double* Um_old = (double*)(ws + f.off_um2);
+    for (int pass = 0; pass < FZ_SVD_PASSES && err == hipSuccess; ++pass) {
+      const int* stop = pass ? done + 1 : nullptr;
+      err = gemm<true>(BsT, f.l16, BsT, f.l16, gram, f.l16, false, l, l, d, slices, st, stop, pass);
+      if (err != hipSuccess) return err;
+      launch_row_rotations(gram, f.l16, l, factor, Um_old, Um, f.l16, done + 1, pass, st);
+      // (a pass that found nothing to rotate has set the flag to its own number)
+      err = gemm<false>(BsT, f.l16, factor, f.l16, BsT, f.l16, false, d, l, l, slices, st, done + 1, pass);
+      if (pass + 1 < FZ_SVD_PASSES) std::swap(Um, Um_old);
+    }
     if (err != hipSuccess) return err;
-    k_gram_eigenvectors<<<dim3(1), dim3(1024), 0, st>>>(gram, f.l16, l, Um, f.l16);
-    err = gemm<false>(BsT, f.l16, Um, f.l16, Bs, d, true, d, l, l, slices, st);    // (BsT Um)^T = Um^T Bs
-    sweeps = FZ_POLISH_SWEEPS;
+    rows = BsT;
+    rows_rs = 1;
+    rows_cs = f.l16;
   } else {
+    for (int j = 0; j <= l; ++j) {
+      k_cgs<<<dim3((unsigned)f.n_groups), dim3(256), 0, st>>>(Y, f.l16, m, l, f.rpw, f.n_groups, j, 0, cb);
+      if (j == l) break;
+      if (j > 0) {
+        k_cgs<<<dim3((unsigned)f.n_groups), dim3(256), 0, st>>>(Y, f.l16, m, l, f.rpw, f.n_groups, j, 1, cb);
+        k_cgs<<<dim3((unsigned)f.n_groups), dim3(256), 0, st>>>(Y, f.l16, m, l, f.rpw, f.n_groups, j, 2, cb);
+      } else {
+        // the first column has nothing to be projected against: its norm is the one just taken
+        k_cgs<<<dim3((unsigned)f.n_groups), dim3(256), 0, st>>>(Y, f.l16, m, l, f.rpw, f.n_groups, 0, 2, cb);
+      }
+    }
     err = gemm<true>(Ms, d, Y, f.l16, Bs, d, true, d, l, m, slices, st);           // (Ms^T Q)^T
+    if (err != hipSuccess) return err;
     k_identity<<<dim3((unsigned)((l * l + 255) / 256)), dim3(256), 0, st>>>(Um, f.l16, l);
+    const int n = (l + 1) & ~1;
+    for (int sweep = 0; sweep < FZ_MAX_SWEEPS; ++sweep)
+      for (int round = 0; round < n - 1; ++round)
+        k_jacobi_round<<<dim3((unsigned)(n / 2)), dim3(FZ_JT), 0, st>>>(Bs, d, d, Um, f.l16, l, n, round, sweep, counters);
+    rows = Bs;
+    rows_rs = d;
+    rows_cs = 1;
   }
-  if (err != hipSuccess) return err;
-  const int n = (l + 1) & ~1;
-  for (int sweep = 0; sweep < sweeps; ++sweep)
-    for (int round = 0; round < n - 1; ++round)
-      k_jacobi_round<<<dim3((unsigned)(n / 2)), dim3(FZ_JT), 0, st>>>(Bs, d, d, Um, f.l16, l, n, round, sweep, counters);
-  k_row_norms<<<dim3((unsigned)l), dim3(256), 0, st>>>(Bs, d, d, sig2);
+  k_row_norms<<<dim3((unsigned)l), dim3(256), 0, st>>>(rows, rows_rs, rows_cs, d, sig2);
   k_sort_sigma<<<dim3(1), dim3(256), 0, st>>>(sig2, l, sigma_sorted, perm);
   // truncate, balance, lift
   k_build_lift<<<dim3((unsigned)((l * r + 255) / 256)), dim3(256), 0, st>>>(Um, f.l16, sigma_sorted, perm, l, r, lift, f.r16);
@@ -785,8 +1137,8 @@ hipError_t launch_factorize(const glowq_unit& u, const float* const* W_modules, 
   {
     const long long n_el = (long long)r * d;
     dim3 grid((unsigned)((n_el + 255) / 256)), block(256);
-    if (f16) k_store_B<ACT_F16><<<grid, block, 0, st>>>(Bs, d, sigma_sorted, perm, inv_root, r, d, (uint16_t*)B_out);
-    else k_store_B<ACT_BF16><<<grid, block, 0, st>>>(Bs, d, sigma_sorted, perm, inv_root, r, d, (uint16_t*)B_out);
+    if (f16) k_store_B<ACT_F16><<<grid, block, 0, st>>>(rows, rows_rs, rows_cs, sigma_sorted, perm, inv_root, r, d, (uint16_t*)B_out);
+    else k_store_B<ACT_BF16><<<grid, block, 0, st>>>(rows, rows_rs, rows_cs, sigma_sorted, perm, inv_root, r, d, (uint16_t*)B_out);
   }
   if (sigma_out) k_copy_doubles<<<dim3(1), dim3(256), 0, st>>>(sigma_sorted, sigma_out, l);
   return hipGetLastError();

@@ -198,3 +198,39 @@ def test_large_stack():
     r, p, q = 64, 16, 1
     Omega = np.random.default_rng(18).standard_normal((4096, r + p))
     check_against_oracle(u, W, r, p, q, Omega, qr="none")
+
+
+@pytest.mark.parametrize("r,p", [(8, 3), (16, 0), (32, 1), (64, 17), (72, 24), (96, 1), (112, 16), (128, 1)])
+def test_sketch_widths_at_the_edges_of_the_blocked_steps(r, p):
+    # one block of 16 columns, exactly one, one column more than whole blocks, more than 80 columns
+    # (two passes of a product), the widest that orthonormalises and rotates in one workgroup
+    # (128) and the narrowest that does not (129)
+    shape = UnitShape("g", 384, (136, 200))
+    u, W = make_unit(shape, "f16", 128, seed=20)
+    Omega = np.random.default_rng(21).standard_normal((shape.d_in, r + p))
+    check_against_oracle(u, W, r, p, 1, Omega)
+
+
+def test_graded_spectrum():
+    # singular values from 1 to 1e-6 in a sketch without power steps: the columns of the sketch lose
+    # up to 12 digits of norm^2 to the ones before them, so the orthonormalisation defers some of
+    # them to later passes; small values are found relative to the float64 rounding of the
+    # largest (1e-16 / 1e-6, times the few hundred terms of a sum)
+    shape = UnitShape("g", 256, (96, 136))
+    u, W0 = make_unit(shape, "bf16", 128, seed=22)
+    What = [O.dequant(O.unpack_int4(m["wq"]), m["scales"], m["zeros"], 128, "bf16") for m in u["modules"]]
+    rng = np.random.default_rng(23)
+    rows = sum(shape.d_outs)
+    U, _ = np.linalg.qr(rng.standard_normal((rows, 40)))
+    V, _ = np.linalg.qr(rng.standard_normal((256, 40)))
+    L = (U * np.logspace(0, -6, 40)) @ V.T
+    W, o = [], 0
+    for Wh in What:
+        W.append((Wh + L[o:o + Wh.shape[0]]).astype(np.float32))
+        o += Wh.shape[0]
+    E = O.stack_errors(W, What)
+    Omega = rng.standard_normal((256, 40))
+    _, _, sig = gpu_factors(u, W, 32, 8, 0, Omega)
+    Q, _ = np.linalg.qr(E @ Omega)
+    s = np.linalg.svd(Q.T @ E, compute_uv=False)
+    np.testing.assert_allclose(sig, s, rtol=1e-7)
