@@ -308,9 +308,9 @@ __device__ inline u32x4_t load16_device(const uint16_t* p) {
   return v;
 }
 
-template <int ACT, int MB, bool G128>
+template <int ACT, int MB, int RB, bool G128>
 __global__ void __launch_bounds__(PfShape<ACT>::WAVES * 64, PfShape<ACT>::OCC) k_prefill(PrefillArgs a) {
-  constexpr int PF_WAVES = PfShape<ACT>::WAVES, RB = PfShape<ACT>::RB;
+  constexpr int PF_WAVES = PfShape<ACT>::WAVES;
   constexpr int MT = 16 * MB;          // tokens per workgroup tile
   constexpr int XR = PF_WAVES * 8;     // X rows covered by one load instruction of the workgroup
   constexpr int XI = MT / XR;          // 16-byte X loads per thread and stage
@@ -705,11 +705,11 @@ __global__ void __launch_bounds__(PfShape<ACT>::WAVES * 64, PfShape<ACT>::OCC) k
   GLOWQ_STAMP(6);
 }
 
-template <int ACT, int MB>
+template <int ACT, int MB, int RB>
 static hipError_t launch_prefill_t(const PrefillArgs& a, int n_wgs, int G, hipStream_t st) {
   dim3 grid((unsigned)n_wgs), block(PfShape<ACT>::WAVES * 64);
-  if (G == 128) k_prefill<ACT, MB, true><<<grid, block, 0, st>>>(a);
-  else k_prefill<ACT, MB, false><<<grid, block, 0, st>>>(a);
+  if (G == 128) k_prefill<ACT, MB, RB, true><<<grid, block, 0, st>>>(a);
+  else k_prefill<ACT, MB, RB, false><<<grid, block, 0, st>>>(a);
   return hipGetLastError();
 }
 
@@ -772,26 +772,51 @@ bool prefill_compatible(const glowq_unit& a, const glowq_unit& b) {
          a.group_size == b.group_size;
 }
 
+// A wave's 16-row blocks in the half-size tiles (128 tokens x 128 rows): more vector-ALU work per
+// product, but twice as many workgroups where the large tiles are too few or the last of them
+// would run alone.
+constexpr int PF_HALF_RB = 2;
+static inline int prefill_tile_blocks(int act_dtype, bool half) {
+  if (half) return 4 * PF_HALF_RB;
+  return act_dtype == GLOWQ_F16 ? PfShape<ACT_F16>::TILE_BLOCKS : PfShape<ACT_BF16>::TILE_BLOCKS;
+}
+
 // What one launch over these units is taken to cost, in the same terms as the batched kernel's
-// tiles (us beyond the launch): 1.57 us per K tile for a workgroup alone on its compute unit,
-// 1.43 times that for two sharing one; 2 us more than the batched kernel to start and end.
-float prefill_cost(const glowq_unit* const* units, int n) {
+// tiles (us beyond a launch of that one).  Measured over 25 calls of 68 to 2048 tokens, in us per
+// K tile: for a workgroup alone on its compute unit, for two sharing one (the vector ALU and
+// the matrix pipe take turns, so a second workgroup adds little, and the clock falls), and per
+// workgroup when several rounds keep all compute units busy.  The half-size tiles took
+// 502 tokens x 2 x 6240 rows x 6784 from 124 to 101 us and 1032 x 3 x 760 x 3840 from 48 to 39 us;
+// on a long prompt that fills the chip they are 4 to 13 % slower.
+struct PrefillCost {
+  float start, alone, pair, busy;
+};
+static float prefill_cost_of(const glowq_unit* const* units, int n, bool half) {
+  const bool f16 = units[0]->act_dtype == GLOWQ_F16;
+  const PrefillCost c = half ? (f16 ? PrefillCost{1.1f, 1.05f, 2.54f, 1.05f} : PrefillCost{0.4f, 1.21f, 2.47f, 1.05f})
+                             : (f16 ? PrefillCost{3.0f, 1.56f, 3.93f, 1.75f} : PrefillCost{1.4f, 1.53f, 3.16f, 1.5f});
   double work = 0.0, wgs = 0.0;
   int chain = 0;
   for (int k = 0; k < n; ++k) {
     const glowq_unit& u = *units[k];
-    const int tile_blocks = u.act_dtype == GLOWQ_F16 ? PfShape<ACT_F16>::TILE_BLOCKS : PfShape<ACT_BF16>::TILE_BLOCKS;
+    const int tile_blocks = prefill_tile_blocks(u.act_dtype, half);
     const int S = prefill_k_slices(u), kt = (u.d_in / 128 + S - 1) / S;
     double tiles = 0.0;
     for (int i = 0; i < u.n_modules; ++i)
       tiles += (double)(((u.modules[i].d_out + 15) / 16 + tile_blocks - 1) / tile_blocks) * ((u.T + 127) / 128) * S;
-    wgs += tiles;
-    work += tiles * kt;
+    // (the projection's workgroups, about 2048 channels each, hold their places beside the tiles)
+    const double proj = u.r > 0 ? (double)((u.T + 127) / 128) * std::min(8, (u.d_in + 2047) / 2048) : 0.0;
+    wgs += tiles + proj;
+    work += tiles * kt + proj * std::min(kt, 8);
     chain = std::max(chain, kt);
   }
   const double per_cu = wgs / 256.0;
-  const double share = per_cu <= 1.0 ? 1.0 : std::max(1.43, 0.72 * per_cu);
-  return (float)(2.0 + 1.57 * std::max((double)chain, work / wgs * share));
+  // (beyond two per compute unit the last round is partly empty)
+  const double share = per_cu <= 1.0 ? c.alone : per_cu <= 2.0 ? c.pair : std::max((double)c.pair, c.busy * per_cu + 0.8 * c.alone);
+  return (float)(c.start + std::max((double)chain * c.alone, work / wgs * share));
+}
+float prefill_cost(const glowq_unit* const* units, int n) {
+  return std::min(prefill_cost_of(units, n, false), prefill_cost_of(units, n, true));
 }
 
 int prefill_max_units() { return PF_MAX_UNITS; }
@@ -803,8 +828,9 @@ hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorksp
   PrefillArgs a;
   const glowq_unit& u0 = *units[0];
   constexpr int MB = PF_MB;
-  const int tile_blocks = u0.act_dtype == GLOWQ_F16 ? PfShape<ACT_F16>::TILE_BLOCKS
-                                                    : PfShape<ACT_BF16>::TILE_BLOCKS;
+  // (a clear advantage: the estimates are good to about 10 %)
+  const bool half = prefill_cost_of(units, n_units, true) < 0.9f * prefill_cost_of(units, n_units, false);
+  const int tile_blocks = prefill_tile_blocks(u0.act_dtype, half);
   // longest contraction first
   int order[PF_MAX_UNITS];
   for (int i = 0; i < n_units; ++i) order[i] = i;
@@ -898,8 +924,11 @@ hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorksp
   a.n_mods = n_mods;
   a.out_f32 = (u0.out_dtype == GLOWQ_F32) ? 1 : 0;
   const bool f16 = (u0.act_dtype == GLOWQ_F16);
-  hipError_t err = f16 ? launch_prefill_t<ACT_F16, MB>(a, wg, u0.group_size, st)
-                       : launch_prefill_t<ACT_BF16, MB>(a, wg, u0.group_size, st);
+  hipError_t err;
+  if (half) err = f16 ? launch_prefill_t<ACT_F16, MB, PF_HALF_RB>(a, wg, u0.group_size, st)
+                      : launch_prefill_t<ACT_BF16, MB, PF_HALF_RB>(a, wg, u0.group_size, st);
+  else err = f16 ? launch_prefill_t<ACT_F16, MB, PfShape<ACT_F16>::RB>(a, wg, u0.group_size, st)
+                 : launch_prefill_t<ACT_BF16, MB, PfShape<ACT_BF16>::RB>(a, wg, u0.group_size, st);
   if (err != hipSuccess) return err;
   // the sliced units' outputs
   for (int ui = 0; ui < n_units; ++ui) {
