@@ -34,6 +34,7 @@
 #pragma once
 #include "common.hpp"
 #include "decode_device.hpp"
+#include "proj_device.hpp"
 #include "launch.hpp"
 #include <algorithm>
 #include <cmath>
@@ -42,7 +43,6 @@ namespace glowq {
 
 constexpr int BATCH_MAX_UNITS = 16;
 constexpr int BATCH_WB = 1024 + 256;      // bytes per wave and K tile: one record's words, its (s, z) words
-constexpr int BATCH_PNB = 2;              // 16-rank blocks per projection workgroup
 
 struct BatchUnit {
   ModuleArgs mod[GLOWQ_MAX_MODULES];
@@ -90,107 +90,16 @@ template <typename T> __device__ inline T* scalar_ptr(T* p) {
   return (T*)(((unsigned long long)hi << 32) | lo);
 }
 
-// Four 16-byte loads at device scope (not served from an L2 line that may be older than another
-// compute unit's store), waited for in the same place.
-__device__ inline void load4_device(u32x4_t (&v)[4], const void* p0, const void* p1, const void* p2, const void* p3) {
-  asm volatile("global_load_dwordx4 %0, %4, off sc1\n\tglobal_load_dwordx4 %1, %5, off sc1\n\t"
-               "global_load_dwordx4 %2, %6, off sc1\n\tglobal_load_dwordx4 %3, %7, off sc1\n\t"
-               "s_waitcnt vmcnt(0)"
-               : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]) : "v"(p0), "v"(p1), "v"(p2), "v"(p3) : "memory");
-}
-
-// One projection workgroup: tokens 16 tb .., K slice kz, ranks 32 ng .. + 32.
+// One projection workgroup (see proj_sliced): R as slots {two ranks, tag}.
 template <int ACT, int NW>
 __device__ inline void batch_projection(const BatchUnit& u, int local, float* lds) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int kz = local % u.ksplit, rest = local / u.ksplit;
-  const int n_groups = (u.r + 31) >> 5;
-  const int ng = rest % n_groups, tb = rest / n_groups;
-  const int i = lane & 15, kq = lane >> 4;
-  const int T = u.T, K = u.K, r = u.r, ksplit = u.ksplit;
-  // tokens past T and ranks past r: clamped (valid) rows, computed and not stored
-  const uint16_t* xrow = u.X + (size_t)min(tb * 16 + i, T - 1) * K + 8 * kq;
-  const uint16_t* brow[BATCH_PNB];
-#pragma unroll
-  for (int nb = 0; nb < BATCH_PNB; ++nb) brow[nb] = u.B + (size_t)min(ng * 32 + nb * 16 + i, r - 1) * K + 8 * kq;
-  const int k_begin = kz * u.kslice, k_end = min(K, k_begin + u.kslice);
-  float4_t acc[BATCH_PNB];
-#pragma unroll
-  for (int nb = 0; nb < BATCH_PNB; ++nb) acc[nb] = float4_t{0.f, 0.f, 0.f, 0.f};
-  constexpr int PB = 4;                          // steps of 32 channels whose loads are in flight together
-  for (int k0 = k_begin + wave * 32; k0 < k_end; k0 += PB * NW * 32) {
-    u32x4_t xf[PB], bf[PB][BATCH_PNB];
-#pragma unroll
-    for (int s = 0; s < PB; ++s) {
-      const int k = k0 + s * NW * 32;
-      const bool in = k < k_end;                 // past the end: the first step again, times zero
-      const int kc = in ? k : k0;
-      xf[s] = *(const u32x4_t*)(xrow + kc);
-      if (!in) xf[s] = u32x4_t{0u, 0u, 0u, 0u};
-#pragma unroll
-      for (int nb = 0; nb < BATCH_PNB; ++nb) {
-        bf[s][nb] = *(const u32x4_t*)(brow[nb] + kc);
-        if (!in) bf[s][nb] = u32x4_t{0u, 0u, 0u, 0u};
-      }
-    }
-#pragma unroll
-    for (int s = 0; s < PB; ++s)
-#pragma unroll
-      for (int nb = 0; nb < BATCH_PNB; ++nb) acc[nb] = mfma16<ACT>(xf[s], bf[s][nb], acc[nb]);   // D[token][rank]
-  }
-#pragma unroll
-  for (int nb = 0; nb < BATCH_PNB; ++nb)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) lds[((wave * BATCH_PNB + nb) * 4 + v) * 64 + lane] = acc[nb][v];
-  __syncthreads();
-  // thread -> (token, pair of ranks)
-  const int tl = tid >> 4, rp = tid & 15;
-  const int t = tb * 16 + tl, rank = ng * 32 + 2 * rp;
-  if (tid >= 256 || t >= T || rank >= r) return; // (no barrier follows)
-  float s[2] = {0.f, 0.f};
-#pragma unroll
-  for (int e = 0; e < 2; ++e) {
-    const int rl = 2 * rp + e, ln = (rl & 15) + 16 * (tl >> 2);
-#pragma unroll
-    for (int w = 0; w < NW; ++w) s[e] += lds[((w * BATCH_PNB + (rl >> 4)) * 4 + (tl & 3)) * 64 + ln];
-  }
-  const uint32_t tag = (uint32_t)(launch_tag() & 0xffffffffull);
-  const unsigned long long tag_hi = (unsigned long long)tag << 32;
-  if (ksplit > 1) {
-    unsigned long long* slot = (unsigned long long*)u.part + ((size_t)t * ksplit + kz) * r + rank;
-#pragma unroll
-    for (int e = 0; e < 2; ++e)
-      __hip_atomic_store(slot + e, tag_hi | (unsigned long long)__builtin_bit_cast(uint32_t, s[e]),
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (kz != ksplit - 1) return;
-    // the last slice's workgroup (the highest index of the group: everybody it waits for is
-    // already running) adds the slices in slice order
-    const unsigned long long* q = (const unsigned long long*)u.part + (size_t)t * ksplit * r + rank;
-    bool ok = false;
-    for (int spin = 0; spin < (1 << 13) && !ok; ++spin) {
-      u32x4_t v[4];
-      load4_device(v, q, q + (size_t)min(1, ksplit - 1) * r, q + (size_t)min(2, ksplit - 1) * r, q + (size_t)(ksplit - 1) * r);
-      ok = true;
-      s[0] = s[1] = 0.f;
-#pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        const uint32_t w0 = v[p][0], t0 = v[p][1], w1 = v[p][2], t1 = v[p][3];
-        ok = ok && t0 == tag && t1 == tag;
-        if (p < ksplit) {
-          s[0] += __builtin_bit_cast(float, w0);
-          s[1] += __builtin_bit_cast(float, w1);
-        }
-      }
-      if (!ok) __builtin_amdgcn_s_sleep(8);
-    }
-    if (!ok) {                                   // (the consumers' waits then expire too)
-      atomicOr(&u.ctl->status, 1u);
-      return;
-    }
-  }
-  const uint32_t pk = (uint32_t)to_act16<ACT>(s[0]) | ((uint32_t)to_act16<ACT>(s[1]) << 16);
-  __hip_atomic_store((unsigned long long*)u.rslots + (size_t)t * (r >> 1) + (rank >> 1),
-                     tag_hi | (unsigned long long)pk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const ProjSliced p{u.X, u.B, u.part, u.T, u.K, u.r, u.ksplit, u.kslice};
+  proj_sliced<ACT, NW>(p, local, lds, [&](int t, int rank, uint32_t pair, uint32_t tag, bool ok) {
+    if (ok)
+      __hip_atomic_store((unsigned long long*)u.rslots + (size_t)t * (u.r >> 1) + (rank >> 1),
+                         ((unsigned long long)tag << 32) | pair, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else atomicOr(&u.ctl->status, 1u);           // (the consumers' waits then expire too)
+  });
 }
 
 // R of the tokens tok0 .. tok0 + n_tok into LDS (act dtype [n_tok][r]), gathered by the whole workgroup; false (in every thread) if

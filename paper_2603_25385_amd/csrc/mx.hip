@@ -20,6 +20,7 @@
 // Weight storage (glowq_mx_prepare_weights): codes region [row block][tile][lane][4 words],
 // then scales region [row block][tile][lane] bytes.  Rows past d_out: code 0, scale 127.
 #include <algorithm>
+#include <cmath>
 #include "common.hpp"
 #include "launch.hpp"
 #include "proj_device.hpp"
@@ -695,6 +696,202 @@ __global__ void __launch_bounds__(256) k_mx_gemm(MxGemmArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------
+// more than 16 tokens on small tiles: the same product where 128 x 128 tiles would be too few for
+// the chip.  A lone workgroup of the kernel above takes 1.2 us per K tile (it waits for the next
+// tile's loads at every step), so a short prompt on a narrow unit took 18 us for sixteen K
+// tiles whatever its size (2 x 2048 rows x 2048 at 40 to 600 tokens; 43 tokens x 2 x 1832 x 8704
+// 49 -> 16 us, 307 tokens x 2 x 168 x 9216 80 -> 27 us for the whole call).  Here a ring of three or four K tiles keeps the loads of two or three
+// steps on their way, tiles go down to 16 x 64, and groups of waves may share the contraction
+// (their sums meet in LDS).  Tiles are chosen like the W4A16 batched kernel's.
+// Weights are the first operand, so that a lane ends up with four rows of one token.
+// ---------------------------------------------------------------------------------------
+template <int MB, int RB, int RW, int NW> struct MxTileShape {
+  static constexpr int KS = NW / RW;
+  static constexpr int DEPTH = KS == 1 && RB == 1 ? 4 : 3;
+  static constexpr int XB = MB * 2048 + 256;                       // codes and scales of a group's tokens
+  static constexpr int WB = RB * 1024 + 256;                       // codes and scales of a wave's rows
+  static constexpr int STAGE = KS * XB + NW * WB;
+  static constexpr int XL = (2 * MB + RW - 1) / RW;                // 1 KiB activation loads per wave
+  static constexpr int LOADS = XL + RB + 2;
+  static constexpr int LDS = DEPTH * STAGE;
+  static constexpr int WGS = LDS <= 40960 ? 4 : LDS <= 54613 ? 3 : LDS <= 81920 ? 2 : 1;
+  static_assert((KS - 1) * RW * RB * MB * 1024 <= LDS, "the fold fits the ring");
+  static_assert(MB <= 4 && RB <= 4, "one load covers four blocks' scales");
+};
+
+template <int ACT, int MB, int RB, int RW, int NW>
+__global__ void __launch_bounds__(NW * 64, (MxTileShape<MB, RB, RW, NW>::WGS * NW / 4)) k_mx_tile(MxGemmArgs a) {
+  using S = MxTileShape<MB, RB, RW, NW>;
+  __shared__ __attribute__((aligned(1024))) uint8_t ring[S::LDS];
+  int mi = 0;
+#pragma unroll
+  for (int i = 1; i < GLOWQ_MAX_MODULES; ++i)
+    if (i < a.n_modules && (int)blockIdx.x >= a.mod[i].first_block) mi = i;
+  const MxModule& m = a.mod[mi];
+  const int local = (int)blockIdx.x - m.first_block;
+  const int tt = local % a.tok_tiles, grp = local / a.tok_tiles;
+  const int n_rb = (m.d_out + 15) / 16, n_tb = (a.T + 15) / 16, ktiles = a.d_in / 128;
+  const int l = threadIdx.x & 63, i = l & 15, g = l >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), rw = w % RW, kg = w / RW;
+  const int kt0 = ktiles * kg / S::KS, nkt = ktiles * (kg + 1) / S::KS - kt0, n_st = (ktiles + S::KS - 1) / S::KS;
+  const int tb0 = tt * MB, rb0 = (grp * RW + rw) * RB;
+  // sources at this group's first K tile: activation chunks (token block, half), weight row blocks
+  // and their scales; blocks past the last one repeat it and are not stored
+  const uint8_t* xs[S::XL];
+  uint32_t xd[S::XL];
+#pragma unroll
+  for (int q = 0; q < S::XL; ++q) {
+    const int c = (rw + RW * q) % (2 * MB);
+    xs[q] = a.xcodes + (((long long)min(tb0 + (c >> 1), n_tb - 1) * ktiles + kt0) * 2 + (c & 1)) * 1024 + l * 16;
+    xd[q] = (uint32_t)c * 1024u;
+  }
+  const uint8_t* ws[RB];
+#pragma unroll
+  for (int b = 0; b < RB; ++b)
+    ws[b] = (const uint8_t*)m.codes + ((long long)min(rb0 + b, n_rb - 1) * ktiles + kt0) * 1024 + l * 16;
+  const uint8_t* xsc = a.xscales + ((long long)min(tb0 + min(g, MB - 1), n_tb - 1) * ktiles + kt0) * 64 + 4 * i;
+  const uint8_t* wsc = m.scales + ((long long)min(rb0 + min(g, RB - 1), n_rb - 1) * ktiles + kt0) * 64 + 4 * i;
+  const uint32_t x_lds = lds_address(ring) + (uint32_t)(kg * S::XB);
+  const uint32_t w_lds = lds_address(ring) + (uint32_t)(S::KS * S::XB + w * S::WB);
+  auto issue = [&](int st, int slot) {
+    const int k = max(min(st, nkt - 1), 0);          // (past the end: the last tile again, not read)
+    const uint32_t so = (uint32_t)(slot * S::STAGE);
+#pragma unroll
+    for (int b = 0; b < RB; ++b) lds_dma16(ws[b] + (long long)k * 1024, w_lds + so + (uint32_t)b * 1024u);
+    lds_dma4(wsc + (long long)k * 64, w_lds + so + (uint32_t)RB * 1024u);
+#pragma unroll
+    for (int q = 0; q < S::XL; ++q) lds_dma16(xs[q] + (long long)k * 2048, x_lds + so + xd[q]);
+    lds_dma4(xsc + (long long)k * 64, x_lds + so + (uint32_t)MB * 2048u);
+  };
+  float4_t acc[RB][MB];
+#pragma unroll
+  for (int b = 0; b < RB; ++b)
+#pragma unroll
+    for (int tb = 0; tb < MB; ++tb) acc[b][tb] = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < S::DEPTH - 1; ++s) issue(s, s);
+  int slot = 0, slot_new = S::DEPTH - 1;
+  for (int st = 0; st < n_st; ++st) {
+    // this stage has landed, everybody's part of it behind the barrier, and everybody is done
+    // with the slot that is loaded next (no LDS read is pending here)
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"((S::DEPTH - 2) * S::LOADS) : "memory");
+    issue(st + S::DEPTH - 1, slot_new);
+    if (S::KS == 1 || st < nkt) {
+      const uint8_t* X = ring + slot * S::STAGE + kg * S::XB;
+      const uint8_t* W = ring + slot * S::STAGE + S::KS * S::XB + w * S::WB;
+      v8i_t wv[RB];
+      int sw[RB];
+#pragma unroll
+      for (int b = 0; b < RB; ++b) {
+        const u32x4_t q = *(const u32x4_t*)(W + b * 1024 + l * 16);
+        wv[b] = v8i_t{(int)q[0], (int)q[1], (int)q[2], (int)q[3], 0, 0, 0, 0};
+        sw[b] = W[RB * 1024 + b * 64 + l];
+      }
+#pragma unroll
+      for (int tb = 0; tb < MB; ++tb) {
+        const u32x4_t lo = *(const u32x4_t*)(X + (2 * tb) * 1024 + l * 16);
+        const u32x4_t hi = *(const u32x4_t*)(X + (2 * tb + 1) * 1024 + l * 16);
+        const int sx = X[MB * 2048 + tb * 64 + l];
+        const v8i_t xv = {(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+#pragma unroll
+        for (int b = 0; b < RB; ++b)
+          acc[b][tb] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(wv[b], xv, acc[b][tb], 4, 0, 0, sw[b], 0, sx);
+      }
+    }
+    slot = slot == S::DEPTH - 1 ? 0 : slot + 1;
+    slot_new = slot_new == S::DEPTH - 1 ? 0 : slot_new + 1;
+  }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  if (a.R16) {                                       // correction steps of 32 ranks, dealt to the groups
+    for (int s = kg; 32 * s < a.r; s += S::KS) {
+      const int j0 = 32 * s + 8 * g;
+      u32x4_t af[RB];
+#pragma unroll
+      for (int b = 0; b < RB; ++b) {
+        const int row = (rb0 + b) * 16 + i;
+        af[b] = (j0 < a.r && row < m.d_out) ? *(const u32x4_t*)(m.A + (long long)row * a.r + j0) : u32x4_t{0, 0, 0, 0};
+      }
+#pragma unroll
+      for (int tb = 0; tb < MB; ++tb) {
+        const int tok = (tb0 + tb) * 16 + i;
+        const u32x4_t rf = (j0 < a.r && tok < a.T) ? *(const u32x4_t*)(a.R16 + (long long)tok * a.r + j0) : u32x4_t{0, 0, 0, 0};
+#pragma unroll
+        for (int b = 0; b < RB; ++b) acc[b][tb] = mfma16<ACT>(af[b], rf, acc[b][tb]);
+      }
+    }
+  }
+  if constexpr (S::KS > 1) {
+    float4_t* fold = (float4_t*)ring;
+    auto at = [&](int q, int b, int tb) -> float4_t& { return fold[(((q * RW + rw) * RB + b) * MB + tb) * 64 + l]; };
+    if (kg > 0) {
+#pragma unroll
+      for (int b = 0; b < RB; ++b)
+#pragma unroll
+        for (int tb = 0; tb < MB; ++tb) at(kg - 1, b, tb) = acc[b][tb];
+    }
+    __syncthreads();
+    if (kg > 0) return;
+#pragma unroll
+    for (int q = 1; q < S::KS; ++q)
+#pragma unroll
+      for (int b = 0; b < RB; ++b)
+#pragma unroll
+        for (int tb = 0; tb < MB; ++tb) {
+          const float4_t o = at(q - 1, b, tb);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) acc[b][tb][v] += o[v];
+        }
+  }
+  // lane holds rows 4 g .. + 4 of each block and token i
+#pragma unroll
+  for (int b = 0; b < RB; ++b) {
+    const int row = (rb0 + b) * 16 + 4 * g;
+    if (row >= m.d_out) continue;
+#pragma unroll
+    for (int tb = 0; tb < MB; ++tb) {
+      const int tok = (tb0 + tb) * 16 + i;
+      if (tok >= a.T) continue;
+      const long long off = (long long)tok * m.ldy + row;
+      const float4_t v = acc[b][tb];
+      if (a.out_f32) {
+        *(float4_t*)((float*)m.Y + off) = v;
+      } else {
+        uint2 pk;
+        pk.x = (uint32_t)to_act16<ACT>(v[0]) | ((uint32_t)to_act16<ACT>(v[1]) << 16);
+        pk.y = (uint32_t)to_act16<ACT>(v[2]) | ((uint32_t)to_act16<ACT>(v[3]) << 16);
+        *(uint2*)((uint16_t*)m.Y + off) = pk;
+      }
+    }
+  }
+}
+
+// First launch of a call of more than 16 tokens: the leading workgroups compute R = X B^T (16
+// tokens, 32 ranks, a K slice each: a lone workgroup reads its operands at about 50 GB/s, so a long
+// contraction in one piece took 27 us), the others quantise the activations.  (As three launches,
+// the quantiser, the projection's slices and their sum, this took 11 to 15 us.)
+struct MxFrontTiles {
+  ProjSliced p;              // p.B NULL when not restored
+  uint16_t* R16;             // act dtype [T][r]
+  uint8_t* xcodes;
+  uint8_t* xscales;
+  int n_proj;
+};
+
+template <int ACT>
+__global__ void __launch_bounds__(MX_FRONT_THREADS) k_mx_front_tiles(MxFrontTiles a) {
+  __shared__ float part[MX_FRONT_THREADS / 64 * PROJ_NB * 256];
+  if ((int)blockIdx.x >= a.n_proj) {
+    mx_quantize_block<ACT, true>(a.p.X, a.p.T, a.p.K, a.xcodes, a.xscales,
+                                 (long long)((int)blockIdx.x - a.n_proj) * MX_FRONT_THREADS + threadIdx.x);
+    return;
+  }
+  proj_sliced<ACT, MX_FRONT_THREADS / 64>(a.p, (int)blockIdx.x, part, [&](int t, int rank, uint32_t pair, uint32_t, bool ok) {
+    // (this path has no status word: a slice that never came becomes NaN, which no caller overlooks)
+    ((uint32_t*)a.R16)[((long long)t * a.p.r + rank) >> 1] = ok ? pair : 0x7fff7fffu;
+  });
+}
+
+// ---------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------
 size_t mx_prepared_bytes(int d_out, int d_in) {
@@ -753,21 +950,75 @@ MxWorkspace plan_mx_workspace(const glowq_unit& u) {
   return w;
 }
 
+// Workgroup tiles and what they were measured to cost (us per K tile of a wave group: `chain` alone,
+// `busy` as a workgroup's share of a full compute unit; 50 shapes of 17 to 1884 tokens).  Tile 0 is
+// k_mx_gemm's.  A launch takes the longer of the two for each K tile of its contraction.
+struct MxTile {
+  int mb, rb, rw, nw;
+  float chain, busy;
+};
+constexpr MxTile MX_TILES[] = {{8, 4, 2, 4, 0.57f, 0.49f}, {1, 1, 4, 4, 0.17f, 0.075f}, {2, 1, 4, 8, 0.30f, 0.173f},
+                               {2, 2, 4, 4, 0.235f, 0.18f}, {4, 2, 4, 4, 0.35f, 0.25f}};
+constexpr double MX_ENDS = 8.7;      // K tiles that a workgroup's start, correction and stores weigh
+constexpr int MX_N_TILES = sizeof(MX_TILES) / sizeof(MX_TILES[0]);
+constexpr int MX_RESIDENT[] = {3, MxTileShape<1, 1, 4, 4>::WGS, MxTileShape<2, 1, 4, 8>::WGS, MxTileShape<2, 2, 4, 4>::WGS,
+                               MxTileShape<4, 2, 4, 4>::WGS};
+
+static int choose_mx_tile(const glowq_unit& u) {
+  int best = 0;
+  double cost = 0.0;
+  for (int i = 0; i < MX_N_TILES; ++i) {
+    const MxTile& t = MX_TILES[i];
+    const int ks = i == 0 ? 1 : t.nw / t.rw, tok = 16 * t.mb, rows = 16 * t.rb * t.rw;
+    double wgs = 0.0;
+    for (int m = 0; m < u.n_modules; ++m) wgs += (double)((u.modules[m].d_out + rows - 1) / rows) * ((u.T + tok - 1) / tok);
+    double per_cu = wgs / 256.0;
+    if (per_cu <= MX_RESIDENT[i]) per_cu = std::ceil(per_cu);
+    const double stages = (u.d_in / 128 + ks - 1) / ks;
+    const double c = (stages + MX_ENDS) * std::max((double)t.chain, per_cu * t.busy);
+    if (i == 0 || c < cost) {
+      best = i;
+      cost = c;
+    }
+  }
+  return best;
+}
+
+template <int ACT, int I>
+static void launch_mx_tile(const MxGemmArgs& a, int tile, int n_wgs, hipStream_t st) {
+  constexpr MxTile t = MX_TILES[I];
+  if (tile == I) k_mx_tile<ACT, t.mb, t.rb, t.rw, t.nw><<<dim3((unsigned)n_wgs), dim3(t.nw * 64), 0, st>>>(a);
+  if constexpr (I + 1 < MX_N_TILES) launch_mx_tile<ACT, I + 1>(a, tile, n_wgs, st);
+}
+
 static hipError_t launch_mx_gemm(const glowq_unit& u, bool restore, char* workspace, hipStream_t st) {
   const MxWorkspace w = plan_mx_workspace(u);
   uint8_t* xcodes = (uint8_t*)(workspace + w.off_xcodes);
   uint8_t* xscales = (uint8_t*)(workspace + w.off_xscales);
-  hipError_t err = launch_mx_quantize_x(u.X, u.T, u.d_in, u.act_dtype, xcodes, xscales, true, st);
-  if (err != hipSuccess) return err;
-  const bool corrected = restore && u.r > 0;
+  const bool corrected = restore && u.r > 0, f16 = u.act_dtype == GLOWQ_F16;
   const UnitWorkspace uw = plan_unit_workspace(u, workspace);
-  if (corrected) {
-    err = launch_proj(u, uw, nullptr, true, st);          // R = X B^T in the activation type
-    if (err != hipSuccess) return err;
-  }
+  // K slices of the projection: the sum over slices costs about 3 us more than a slice's own work, so
+  // only contractions past 4096 channels are cut, in slices of about 2048, at most four (the area
+  // of partial sums holds their slots) and no more than 256 workgroups
+  const int pieces16 = (u.T + 15) / 16 * std::max(1, (u.r + 31) / 32);
+  const int want = u.d_in <= 4096 ? 1 : std::max(1, std::min(std::min(4, (u.d_in + 2047) / 2048), 256 / pieces16));
+  const int kslice = (u.d_in / 32 + want - 1) / want * 32, ksplit = (u.d_in + kslice - 1) / kslice;
+  MxFrontTiles fa;
+  fa.p = ProjSliced{(const uint16_t*)u.X, corrected ? (const uint16_t*)u.B : nullptr, (float*)(uw.base + uw.off_rpart),
+                    u.T, u.d_in, u.r, ksplit, kslice};
+  fa.R16 = (uint16_t*)(uw.base + uw.off_r16);
+  fa.xcodes = xcodes;
+  fa.xscales = xscales;
+  fa.n_proj = corrected ? (u.T + 15) / 16 * ((u.r + 31) / 32) * ksplit : 0;
+  const long long pieces = (long long)u.T * (u.d_in / 16);
+  dim3 fgrid((unsigned)((pieces + MX_FRONT_THREADS - 1) / MX_FRONT_THREADS + fa.n_proj));
+  if (f16) k_mx_front_tiles<ACT_F16><<<fgrid, dim3(MX_FRONT_THREADS), 0, st>>>(fa);
+  else k_mx_front_tiles<ACT_BF16><<<fgrid, dim3(MX_FRONT_THREADS), 0, st>>>(fa);
+  const int ti = choose_mx_tile(u);
+  const int tile_tok = 16 * MX_TILES[ti].mb, tile_rows = 16 * MX_TILES[ti].rb * MX_TILES[ti].rw;
   MxGemmArgs a;
   a.n_modules = u.n_modules;
-  a.tok_tiles = (u.T + MXG_TOK - 1) / MXG_TOK;
+  a.tok_tiles = (u.T + tile_tok - 1) / tile_tok;
   int blocks = 0;
   for (int i = 0; i < u.n_modules; ++i) {
     const glowq_module& m = u.modules[i];
@@ -779,14 +1030,17 @@ static hipError_t launch_mx_gemm(const glowq_unit& u, bool restore, char* worksp
     a.mod[i].d_out = m.d_out;
     a.mod[i].ldy = m.ldy;
     a.mod[i].first_block = blocks;
-    blocks += ((m.d_out + MXG_ROWS - 1) / MXG_ROWS) * a.tok_tiles;
+    blocks += ((m.d_out + tile_rows - 1) / tile_rows) * a.tok_tiles;
   }
   a.xcodes = xcodes;
   a.xscales = xscales;
-  a.R16 = corrected ? (const uint16_t*)(uw.base + uw.off_r16) : nullptr;
+  a.R16 = corrected ? fa.R16 : nullptr;
   a.T = u.T; a.d_in = u.d_in; a.r = u.r;
   a.out_f32 = u.out_dtype == GLOWQ_F32;
-  if (u.act_dtype == GLOWQ_F16) k_mx_gemm<ACT_F16><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(a);
+  if (ti > 0) {
+    if (f16) launch_mx_tile<ACT_F16, 1>(a, ti, blocks, st);
+    else launch_mx_tile<ACT_BF16, 1>(a, ti, blocks, st);
+  } else if (f16) k_mx_gemm<ACT_F16><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(a);
   else k_mx_gemm<ACT_BF16><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(a);
   return hipGetLastError();
 }

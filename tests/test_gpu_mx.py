@@ -270,3 +270,20 @@ def test_full_size_prefill():
     ref = MX.mx_group_forward(u, True)
     for g, y in zip(got, ref):
         assert rel_err(g, y) <= TOL
+
+
+# one K tile and fewer tokens than a tile; ragged row blocks and a token tile that ends in one block;
+# a contraction whose projection is cut into K slices, on few rows (groups of waves share K) and on
+# more; several tiles per compute unit; enough of them for the 128 x 128 tiles
+@pytest.mark.parametrize("act", ["f16", "bf16"])
+@pytest.mark.parametrize("T,d_in,d_outs,r", [(17, 128, (40,), 8), (40, 640, (264, 96), 72), (49, 4352, (136,), 24),
+                                             (130, 8320, (72, 264), 128), (100, 256, (9000, 9008), 40),
+                                             (257, 1152, (1000,), 16), (600, 384, (8200,), 8)])
+def test_small_tiles(act, T, d_in, d_outs, r):
+    u = make_unit(UnitShape("g", d_in, d_outs), T, r, act, seed=31)
+    for out in ("f32", "act"):
+        du = MxDeviceUnit(u, out=out)
+        for restore in (True, False):
+            got = du.forward(restore)
+            for g, y in zip(got, MX.mx_group_forward(u, restore)):
+                assert np.isfinite(g).all() and rel_err(g, y) <= TOL + (ULP[act] if out == "act" else 0.0)
