@@ -5,8 +5,9 @@
 //
 //   Ms     = E_cat Sigma_x^(1/2)            E_cat = [W_i - dequant(W_q,i)]_i stacked by rows
 //   Y      = Ms Omega,  q times  Y <- Ms (Ms^T Y)
-//   Q      = orth(Y)                        classical Gram-Schmidt, every column twice
-//   Bs     = Q^T Ms = U~ S V^T              one-sided Jacobi on the rows of Bs
+//   Q      = orth(Y)                        Cholesky QR in passes (wide sketches: Gram-Schmidt)
+//   Bs     = Q^T Ms = U~ S V^T              rotations from the rows' Gram matrix (wide: one-sided
+//                                           Jacobi on the rows)
 //   A      = Q U~_r S_r^(1/2),  B = S_r^(1/2) V_r^T Sigma_x^(-1/2)
 //
 // The algorithm in the paper first replaces the m x d stack by the d x d triangular factor
