@@ -337,8 +337,13 @@ glowq_status glowq_mx_workspace_bytes(const glowq_unit* u, size_t* bytes);
 glowq_status glowq_mx_group_forward(const glowq_unit* u, int32_t restore, void* workspace,
                                     size_t workspace_bytes, void* stream);
 
-/* ---- inspection hooks (bit-exactness checks of the storage format) ---------
- * Both read the prepared layout of one module (the buffer the forward kernels
+/* ---- inspection hooks (bit-exactness checks of the storage format, kernel choice) ---------
+ * glowq_debug_route / glowq_debug_mx_route: which kernel would serve each unit of a forward call
+ * over `units` (HOST only, nothing is enqueued; modules must be given, other pointers may be
+ * NULL).  The choice is made from sizes and types, by the code that the forward calls run; it may
+ * change from one build to the next.  slabs != 0: as with a workspace of glowq_workspace_bytes;
+ * 0: as without one, or as glowq_group_forward_static.
+ * The other two read the prepared layout of one module (the buffer the forward kernels
  * stream) with small kernels of their own.
  * glowq_debug_unpack:  q_out DEVICE uint8 [d_out][d_in], values 0..15.
  * glowq_debug_dequant: w_out DEVICE act dtype [d_out][d_in],
@@ -347,6 +352,25 @@ glowq_status glowq_mx_group_forward(const glowq_unit* u, int32_t restore, void* 
  *                      use instruction sequences of their own; what THEY multiply
  *                      with can be read through a forward call whose X is rows of
  *                      the identity and r = 0. */
+enum {
+  GLOWQ_ROUTE_FEW = 0,        /* up to four tokens, one pass over the weights                  */
+  GLOWQ_ROUTE_BATCHED = 1,    /* batched kernel; tile: index of its workgroup tile             */
+  GLOWQ_ROUTE_TILED = 2,      /* tiled kernel; tile: 0 its large tiles, 1 the half-size ones   */
+  GLOWQ_ROUTE_MX_ONE = 3,     /* microscaling, one launch                                      */
+  GLOWQ_ROUTE_MX_SMALL = 4,   /* microscaling, up to 16 tokens, two launches                   */
+  GLOWQ_ROUTE_MX_TILED = 5    /* microscaling, more tokens; tile: index of its workgroup tile  */
+};
+typedef struct {
+  int32_t launch;      /* index of the launch; units of one launch share it                   */
+  int32_t kernel;      /* GLOWQ_ROUTE_...                                                     */
+  int32_t tile;        /* see above (0 where there is no choice)                              */
+  int32_t k_slices;    /* slices of K whose partial results a second kernel adds              */
+  int32_t wait_polls;  /* looks that an in-launch wait for the projection takes before it
+                          gives up; 0: nothing waits inside a launch                          */
+} glowq_route;
+glowq_status glowq_debug_route(const glowq_unit* units, int32_t n_units, int32_t slabs,
+                               glowq_route* routes);
+glowq_status glowq_debug_mx_route(const glowq_unit* u, glowq_route* route);
 glowq_status glowq_debug_unpack(const void* w_prepared, int32_t d_out, int32_t d_in,
                                 int32_t group_size, uint8_t* q_out, void* stream);
 glowq_status glowq_debug_dequant(const void* w_prepared, int32_t d_out, int32_t d_in,

@@ -36,6 +36,15 @@ class glowq_unit(ctypes.Structure):
                 ("out_dtype", ctypes.c_int32)]
 
 
+GLOWQ_ROUTE_FEW, GLOWQ_ROUTE_BATCHED, GLOWQ_ROUTE_TILED = 0, 1, 2
+GLOWQ_ROUTE_MX_ONE, GLOWQ_ROUTE_MX_SMALL, GLOWQ_ROUTE_MX_TILED = 3, 4, 5
+
+
+class glowq_route(ctypes.Structure):
+    _fields_ = [("launch", ctypes.c_int32), ("kernel", ctypes.c_int32), ("tile", ctypes.c_int32),
+                ("k_slices", ctypes.c_int32), ("wait_polls", ctypes.c_int32)]
+
+
 def _share_hip_runtime_with_torch() -> None:
     """One process must hold ONE HIP runtime.  A PyTorch-ROCm wheel bundles its own
     libamdhip64; if this library pulled in the system copy first, torch would then be
@@ -88,6 +97,8 @@ def _load():
         "glowq_mx_quantize_activations": (ctypes.c_int, [vp, i32, i32, i32, vp, vp, vp]),
         "glowq_mx_workspace_bytes": (ctypes.c_int, [up, ctypes.POINTER(sz)]),
         "glowq_mx_group_forward": (ctypes.c_int, [up, i32, vp, sz, vp]),
+        "glowq_debug_route": (ctypes.c_int, [up, i32, i32, ctypes.POINTER(glowq_route)]),
+        "glowq_debug_mx_route": (ctypes.c_int, [up, ctypes.POINTER(glowq_route)]),
         "glowq_debug_unpack": (ctypes.c_int, [vp, i32, i32, i32, vp, vp]),
         "glowq_debug_dequant": (ctypes.c_int, [vp, i32, i32, i32, i32, vp, vp]),
         # include/glowq_probe.h
@@ -325,6 +336,19 @@ def glowq_mx_group_forward(unit: glowq_unit, restore: int, workspace: int, works
                            stream: int = 0) -> None:
     _check(_lib.glowq_mx_group_forward(ctypes.byref(unit), restore, workspace or None, workspace_bytes,
                                        stream or None), "glowq_mx_group_forward")
+
+
+def glowq_debug_route(units: Sequence[glowq_unit], slabs: bool = True) -> list:
+    """One glowq_route per unit."""
+    routes = (glowq_route * len(units))()
+    _check(_lib.glowq_debug_route(_units_array(units), len(units), 1 if slabs else 0, routes), "glowq_debug_route")
+    return list(routes)
+
+
+def glowq_debug_mx_route(unit: glowq_unit) -> glowq_route:
+    route = glowq_route()
+    _check(_lib.glowq_debug_mx_route(ctypes.byref(unit), ctypes.byref(route)), "glowq_debug_mx_route")
+    return route
 
 
 def glowq_debug_unpack(w_prepared: int, d_out: int, d_in: int, group_size: int, q_out: int,

@@ -142,63 +142,78 @@ static inline glowq_status hip_status(hipError_t e) {
   return GLOWQ_ERR_HIP;
 }
 
-// Enqueue all units: decode-sized units one launch each (projection inside); prefill-sized
-// units in batches of compatible neighbours, projections first, then one GEMM launch.
+// The launch that serves units[0] and, as far as they are compatible with it, its neighbours.
+// Sizes and types decide, never the restore mask.
+constexpr int MAX_LAUNCH_UNITS = 32;
+struct LaunchChoice {
+  int kernel;                      // GLOWQ_ROUTE_...
+  int n;                           // units
+  int tile;                        // batched: the workgroup tile; tiled: 1 for the half-size tiles
+  int slices[MAX_LAUNCH_UNITS];    // K slices of every unit
+};
+static LaunchChoice choose_launch(const glowq_unit* units, int n_units, bool slabs) {
+  LaunchChoice c = {};
+  const glowq_unit* batch[MAX_LAUNCH_UNITS];
+  for (int& s : c.slices) s = 1;
+  float cost = 0.f;
+  if (is_decode(units[0].T)) {
+    const bool few = units[0].T <= 4;
+    const int most = std::min(std::min(MAX_LAUNCH_UNITS, n_units), few ? decode_max_batch() : batch_max_units());
+    while (c.n < most && is_decode(units[c.n].T) &&
+           (c.n == 0 || (few ? decode_batch_compatible(units[0], units[c.n]) : batch_compatible(units[0], units[c.n])))) {
+      batch[c.n] = &units[c.n];
+      ++c.n;
+    }
+    c.kernel = few ? GLOWQ_ROUTE_FEW : GLOWQ_ROUTE_BATCHED;
+    if (!few) c.tile = choose_batch_tile(batch, c.n, &cost);
+    return c;
+  }
+  const int most = std::min(std::min(MAX_LAUNCH_UNITS, n_units), std::min(prefill_max_units(), batch_max_units()));
+  int nmods = 0;
+  bool small = true;
+  while (c.n < most && !is_decode(units[c.n].T) && (c.n == 0 || prefill_compatible(units[0], units[c.n])) &&
+         nmods + units[c.n].n_modules <= prefill_max_modules()) {
+    small = small && units[c.n].T <= BATCH_MAX_T;
+    nmods += units[c.n].n_modules;
+    batch[c.n] = &units[c.n];
+    ++c.n;
+  }
+  const bool half = choose_prefill_tile(batch, c.n, &cost);
+  // Few or small tiles leave the tiled kernel's workgroups alone on their compute units with the
+  // whole contraction each; there the smaller tiles of the batched kernel are faster.
+  // (a clear advantage: both estimates are good to about 10 %)
+  float small_cost = 0.f;
+  const int tile = small ? choose_batch_tile(batch, c.n, &small_cost) : 0;
+  if (small && small_cost < 0.85f * cost) {
+    c.kernel = GLOWQ_ROUTE_BATCHED;
+    c.tile = tile;
+    return c;
+  }
+  c.kernel = GLOWQ_ROUTE_TILED;
+  c.tile = half ? 1 : 0;
+  plan_prefill_slices(batch, c.n, slabs, c.slices);
+  return c;
+}
+
+// Enqueue all units, launch by launch.  slabs: the workspace holds the slabs of K slices.
 static glowq_status forward_all(const glowq_unit* units, int n_units, const uint8_t* mask,
-                                char* workspace, hipStream_t st, bool allow_split = true) {
+                                char* workspace, bool slabs, hipStream_t st) {
   size_t off = 0;
-  int i = 0;
-  while (i < n_units) {
-    const glowq_unit& u = units[i];
-    if (is_decode(u.T)) {
-      // consecutive units of one kind share a launch
-      const glowq_unit* dbatch[32];
-      UnitWorkspace dws[32];
-      bool dcorr[32];
-      const bool few = u.T <= 4;
-      const int most = std::min(32, few ? decode_max_batch() : batch_max_units());
-      int nd = 0;
-      while (i < n_units && nd < most && is_decode(units[i].T) &&
-             (nd == 0 || (few ? decode_batch_compatible(*dbatch[0], units[i]) : batch_compatible(*dbatch[0], units[i])))) {
-        dbatch[nd] = &units[i];
-        dws[nd] = plan_unit_workspace(units[i], workspace ? workspace + off : nullptr);
-        dcorr[nd] = (!mask || mask[i]) && units[i].r > 0;
-        off += dws[nd].bytes;
-        ++nd;
-        ++i;
-      }
-      hipError_t e = few ? launch_decode_multi(dbatch, dws, dcorr, nd, st) : launch_decode_batch(dbatch, dws, dcorr, nd, st);
-      if (e != hipSuccess) return hip_status(e);
-      continue;
+  for (int i = 0; i < n_units;) {
+    const LaunchChoice c = choose_launch(units + i, n_units - i, slabs);
+    const glowq_unit* batch[MAX_LAUNCH_UNITS];
+    UnitWorkspace ws[MAX_LAUNCH_UNITS];
+    bool corr[MAX_LAUNCH_UNITS];
+    for (int k = 0; k < c.n; ++k, ++i) {
+      batch[k] = &units[i];
+      ws[k] = plan_unit_workspace(units[i], workspace ? workspace + off : nullptr);
+      off += ws[k].bytes;
+      corr[k] = (!mask || mask[i]) && units[i].r > 0;
+      if (c.kernel == GLOWQ_ROUTE_BATCHED) plan_batch_projection(units[i], ws[k]);
     }
-    const glowq_unit* batch[8];
-    UnitWorkspace bws[8];
-    bool corr[8];
-    int nb = 0, nmods = 0;
-    while (i < n_units && nb < prefill_max_units() && nb < 8 && !is_decode(units[i].T) &&
-           (nb == 0 || prefill_compatible(*batch[0], units[i])) &&
-           nmods + units[i].n_modules <= prefill_max_modules()) {
-      batch[nb] = &units[i];
-      bws[nb] = plan_unit_workspace(units[i], workspace ? workspace + off : nullptr);
-      corr[nb] = (!mask || mask[i]) && units[i].r > 0;
-      off += bws[nb].bytes;
-      nmods += units[i].n_modules;
-      ++nb;
-      ++i;
-    }
-    // Few or small tiles leave the tiled kernel's workgroups alone on their compute units with the
-    // whole contraction each; there the smaller tiles of the batched kernel are faster.
-    bool small = true;
-    for (int k = 0; k < nb; ++k) small = small && batch[k]->T <= BATCH_MAX_T;
-    // (a clear advantage: both estimates are good to about 10 %)
-    if (small && batch_cost(batch, nb) < 0.85f * prefill_cost(batch, nb)) {
-      for (int k = 0; k < nb; ++k) plan_batch_projection(*batch[k], bws[k]);
-      hipError_t e = launch_decode_batch(batch, bws, corr, nb, st);
-      if (e != hipSuccess) return hip_status(e);
-      continue;
-    }
-    // (the projections of the batch run as the first tiles of the same launch)
-    hipError_t e = launch_prefill_multi(batch, bws, corr, nb, allow_split && workspace != nullptr, st);
+    const hipError_t e = c.kernel == GLOWQ_ROUTE_FEW       ? launch_decode_multi(batch, ws, corr, c.n, st)
+                         : c.kernel == GLOWQ_ROUTE_BATCHED ? launch_decode_batch(batch, ws, corr, c.n, c.tile, st)
+                                                           : launch_prefill_multi(batch, ws, corr, c.n, c.tile == 1, c.slices, st);
     if (e != hipSuccess) return hip_status(e);
   }
   return GLOWQ_OK;
@@ -324,7 +339,7 @@ glowq_status glowq_group_forward_static(const glowq_unit* u, int32_t restore, vo
   glowq_status s = validate(u, true, corrected);
   if (s != GLOWQ_OK) return s;
   uint8_t mask = restore ? 1 : 0;
-  if (!corrected) return forward_all(u, 1, &mask, nullptr, (hipStream_t)stream);
+  if (!corrected) return forward_all(u, 1, &mask, nullptr, false, (hipStream_t)stream);
   // (the static array holds the projection's words; a long contraction is not cut here)
   const UnitWorkspace plan = plan_unit_workspace(*u, nullptr);
   if (plan.off_splitk > (size_t)GLOWQ_STATIC_SCRATCH_BYTES) return GLOWQ_ERR_WORKSPACE;
@@ -336,7 +351,7 @@ glowq_status glowq_group_forward_static(const glowq_unit* u, int32_t restore, vo
   // node, so that the call can be captured into a graph)
   e = launch_fill_zero(scratch, plan.ctl_bytes, (hipStream_t)stream);
   if (e != hipSuccess) return hip_status(e);
-  return forward_all(u, 1, &mask, (char*)scratch, (hipStream_t)stream, false);
+  return forward_all(u, 1, &mask, (char*)scratch, false, (hipStream_t)stream);
 }
 
 glowq_status glowq_block_forward(const glowq_unit* units, int32_t n_units,
@@ -361,7 +376,7 @@ glowq_status glowq_block_forward(const glowq_unit* units, int32_t n_units,
   }
   // (with no unit restored the workspace may be absent or of any size)
   const bool whole = workspace && workspace_bytes >= need && !misaligned(workspace);
-  return forward_all(units, n_units, restore_mask, any_corr || whole ? (char*)workspace : nullptr, (hipStream_t)stream);
+  return forward_all(units, n_units, restore_mask, whole ? (char*)workspace : nullptr, whole, (hipStream_t)stream);
 }
 
 // Every module of the units as a one-module unit, module j (counted over all units) with
@@ -554,6 +569,33 @@ glowq_status glowq_mx_group_forward(const glowq_unit* u, int32_t restore, void* 
   if ((uintptr_t)workspace & 255u) return GLOWQ_ERR_ALIGN;
   if (workspace_bytes < plan_mx_workspace(*u).bytes) return GLOWQ_ERR_WORKSPACE;
   return hip_status(launch_mx_forward(*u, restore != 0, (char*)workspace, (hipStream_t)stream));
+}
+
+glowq_status glowq_debug_route(const glowq_unit* units, int32_t n_units, int32_t slabs, glowq_route* routes) {
+  if (!units || !routes) return GLOWQ_ERR_NULL;
+  if (n_units < 1) return GLOWQ_ERR_SHAPE;
+  for (int i = 0; i < n_units; ++i) {
+    glowq_status s = validate(&units[i], false, false);
+    if (s != GLOWQ_OK) return s;
+    if (!units[i].modules) return GLOWQ_ERR_NULL;
+  }
+  for (int i = 0, launch = 0; i < n_units; ++launch) {
+    const LaunchChoice c = choose_launch(units + i, n_units - i, slabs != 0);
+    for (int k = 0; k < c.n; ++k, ++i)
+      routes[i] = glowq_route{launch, c.kernel, c.tile, c.slices[k],
+                              c.kernel == GLOWQ_ROUTE_FEW       ? decode_wait_polls()
+                              : c.kernel == GLOWQ_ROUTE_BATCHED ? batch_wait_polls()
+                                                                : prefill_wait_polls()};
+  }
+  return GLOWQ_OK;
+}
+
+glowq_status glowq_debug_mx_route(const glowq_unit* u, glowq_route* route) {
+  glowq_status s = validate_mx(u, false, false);
+  if (s != GLOWQ_OK) return s;
+  if (!route || !u->modules) return GLOWQ_ERR_NULL;
+  mx_route(*u, route);
+  return GLOWQ_OK;
 }
 
 glowq_status glowq_debug_unpack(const void* w_prepared, int32_t d_out, int32_t d_in,

@@ -121,6 +121,7 @@ bool decode_batch_compatible(const glowq_unit& a, const glowq_unit& b) {
          decode_small_class(a.T) == decode_small_class(b.T);
 }
 int decode_max_batch() { return DEC_MAX_BATCH; }
+int decode_wait_polls() { return DEC_WAIT_POLLS; }
 
 template <int NB>
 static hipError_t launch_decode_small(const glowq_unit* const* units, const UnitWorkspace* ws,

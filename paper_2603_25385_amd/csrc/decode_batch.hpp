@@ -42,6 +42,7 @@
 namespace glowq {
 
 constexpr int BATCH_MAX_UNITS = 16;
+constexpr int BATCH_WAIT_POLLS = 1 << 12;
 constexpr int BATCH_WB = 1024 + 256;      // bytes per wave and K tile: one record's words, its (s, z) words
 
 struct BatchUnit {
@@ -112,7 +113,7 @@ __device__ inline bool batch_fetch_r(const BatchUnit& u, int tok0, int n_tok, ui
   const u32x4_t* src = (const u32x4_t*)u.rslots + (size_t)tok0 * (u.r >> 2);
   if (tid == 0) *flag = 0u;
   __syncthreads();
-  for (int spin = 0; spin < (1 << 12); ++spin) {
+  for (int spin = 0; spin < BATCH_WAIT_POLLS; ++spin) {
     bool ok = true;
     for (int e0 = 0; e0 < n_el; e0 += 4 * NT) {
       u32x4_t v[4];
@@ -414,6 +415,7 @@ bool batch_compatible(const glowq_unit& a, const glowq_unit& b) {
          a.group_size == b.group_size && (a.T <= 16) == (b.T <= 16) && (a.T <= 32) == (b.T <= 32);
 }
 int batch_max_units() { return BATCH_MAX_UNITS; }
+int batch_wait_polls() { return BATCH_WAIT_POLLS; }
 
 // Workgroup tiles: 16 mb tokens x 16 rb rw rows, nw / rw groups of waves sharing the contraction.
 // What a tile costs was measured over 70 shapes (5 to 1001 tokens, 144 to 48000 rows, 256 to 13696
@@ -450,7 +452,7 @@ static int row_blocks(const glowq_unit& u) {
 
 // The cheapest tile for these units in one launch, and what it is taken to cost (us beyond the
 // launch itself).
-static int choose_batch_tile(const glowq_unit* const* units, int n, float* cost) {
+int choose_batch_tile(const glowq_unit* const* units, int n, float* cost) {
   const bool f16 = units[0]->act_dtype == GLOWQ_F16, exact = f16 && units[0]->T <= 32;
   int best = -1;
   for (int i = 0; i < BATCH_N_TILES; ++i) {
@@ -477,11 +479,6 @@ static int choose_batch_tile(const glowq_unit* const* units, int n, float* cost)
   }
   return best;
 }
-float batch_cost(const glowq_unit* const* units, int n) {
-  float c = 0.f;
-  choose_batch_tile(units, n, &c);
-  return c;
-}
 
 // K slices of the projection inside the launch: about 1024 channels each, at most four, and no
 // more workgroups than the chip takes beside the first row blocks
@@ -504,7 +501,7 @@ static void launch_batch_tile(const BatchArgs<NB>& b, int tile, int n_wgs, hipSt
 
 template <int NB>
 static hipError_t launch_batch(const glowq_unit* const* units, const UnitWorkspace* ws, const bool* restore, int n,
-                               hipStream_t st) {
+                               int ti, hipStream_t st) {
   BatchArgs<NB> b;
   // longest contraction first: the hardware starts workgroups in index order
   int order[NB];
@@ -544,8 +541,6 @@ static hipError_t launch_batch(const glowq_unit* const* units, const UnitWorkspa
       n_prod += bu.n_prod;
     }
   }
-  float cost = 0.f;
-  const int ti = choose_batch_tile(units, n, &cost);
   const BatchTile tile = BATCH_TILES[ti];
   int wg = n_prod;
   for (int oi = 0; oi < n; ++oi) {
@@ -570,9 +565,9 @@ static hipError_t launch_batch(const glowq_unit* const* units, const UnitWorkspa
 
 // units[i] uses workspace slice ws[i]; all of them pass batch_compatible with units[0]
 hipError_t launch_decode_batch(const glowq_unit* const* units, const UnitWorkspace* ws, const bool* restore, int n,
-                               hipStream_t st) {
-  if (n == 1) return launch_batch<1>(units, ws, restore, n, st);
-  return launch_batch<BATCH_MAX_UNITS>(units, ws, restore, n, st);
+                               int tile, hipStream_t st) {
+  if (n == 1) return launch_batch<1>(units, ws, restore, n, tile, st);
+  return launch_batch<BATCH_MAX_UNITS>(units, ws, restore, n, tile, st);
 }
 
 }  // namespace glowq

@@ -270,6 +270,7 @@ __device__ inline void decode_stream_small(const DecodeArgs& a, const ModuleArgs
 // nothing, so it cannot expire); if it did, ctl->status is set and the correction is left
 // out rather than hang.
 constexpr int DEC_MAX_PARTS = 4;   // K parts of the direct projection (see plan_unit_workspace)
+constexpr int DEC_WAIT_POLLS = 1 << 14;
 struct RFetch {
   u32x4_t v[DEC_MAX_PARTS][4];     // per part: 8 slots = 64 bytes
   const unsigned long long* q;     // this lane's first slot of part 0
@@ -315,7 +316,7 @@ __device__ inline bool r_fetch_finish(const ProjArgs& p, RFetch& f, u32x4_t& rf)
   const uint32_t tag = (uint32_t)(launch_tag() & 0xffffffffull);
   float s[8];
   bool done = false;
-  for (int spin = 0; spin < (1 << 14); ++spin) {
+  for (int spin = 0; spin < DEC_WAIT_POLLS; ++spin) {
     bool ok = true;
 #pragma unroll
     for (int e = 0; e < 8; ++e) s[e] = 0.f;

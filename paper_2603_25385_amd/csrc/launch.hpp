@@ -71,6 +71,7 @@ hipError_t launch_mx_prepare(const uint32_t* codes, const uint8_t* scales, int d
 hipError_t launch_mx_quantize_x(const void* X, int T, int d_in, int act, uint8_t* codes, uint8_t* scales,
                                 bool fragment_order, hipStream_t st);
 hipError_t launch_mx_forward(const glowq_unit& u, bool restore, char* workspace, hipStream_t st);
+void mx_route(const glowq_unit& u, glowq_route* route);
 // slices' start offsets in units of 256 bytes (every slice is 256-byte aligned)
 constexpr int STATUS_BATCH = 256;
 struct StatusBatch {
@@ -91,6 +92,7 @@ hipError_t launch_proj(const glowq_unit& u, const UnitWorkspace& ws, float* R32,
 // in the first workgroups of the same launch
 bool decode_batch_compatible(const glowq_unit& a, const glowq_unit& b);
 int decode_max_batch();
+int decode_wait_polls();
 hipError_t launch_decode_multi(const glowq_unit* const* units, const UnitWorkspace* ws,
                                const bool* restore, int n, hipStream_t st);
 // 4 < T <= 64: the same with X shared through LDS; compatible units share a launch
@@ -98,19 +100,26 @@ hipError_t launch_decode_multi(const glowq_unit* const* units, const UnitWorkspa
 // holds the slots up to here)
 constexpr int BATCH_MAX_T = 2048;
 void plan_batch_projection(const glowq_unit& u, UnitWorkspace& w);
-float batch_cost(const glowq_unit* const* units, int n);
-float prefill_cost(const glowq_unit* const* units, int n);
+// the workgroup tile for these units in one launch, and what it is taken to cost
+int choose_batch_tile(const glowq_unit* const* units, int n, float* cost);
+int batch_wait_polls();
 bool batch_compatible(const glowq_unit& a, const glowq_unit& b);
 int batch_max_units();
 hipError_t launch_decode_batch(const glowq_unit* const* units, const UnitWorkspace* ws,
-                               const bool* restore, int n, hipStream_t st);
+                               const bool* restore, int n, int tile, hipStream_t st);
 // T > 64: tiled matrix-core GEMM, correction folded in as an extra K slab.  One launch
 // covers several compatible units (same types, group size and token-tile size).
 bool prefill_compatible(const glowq_unit& a, const glowq_unit& b);
 int prefill_max_units();
 int prefill_max_modules();
+// K slices of every unit of a launch: where the unit's shapes ask for them, the workspace has the
+// slabs (`slabs`) and the module table has room
+void plan_prefill_slices(const glowq_unit* const* units, int n, bool slabs, int* slices);
+// whether the launch takes the half-size tiles, and what it is taken to cost
+bool choose_prefill_tile(const glowq_unit* const* units, int n, float* cost);
+int prefill_wait_polls();
 hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorkspace* ws,
-                                const bool* restore, int n_units, bool allow_split, hipStream_t st);
+                                const bool* restore, int n_units, bool half, const int* slices, hipStream_t st);
 int prefill_k_slices(const glowq_unit& u);
 size_t prefill_splitk_bytes(const glowq_unit& u);
 

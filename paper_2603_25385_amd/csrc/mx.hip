@@ -353,6 +353,7 @@ __global__ void __launch_bounds__(256) k_mx_decode(MxArgs a) {
 // the scale codes [tile][block][4 tokens], then per wave and K part 1 KiB of slots.
 // ---------------------------------------------------------------------------------------
 constexpr int MXS_MAX_TOKENS = 4;
+constexpr int MXS_WAIT_POLLS = 1 << 16;
 constexpr int MXS_ITEMS = 4;          // 16-channel pieces of X per thread, at most
 constexpr int MXS_ROUND = 8;          // tiles per wave and register buffer
 constexpr int MXS_MAX_PARTS = 2;      // K parts of the in-launch projection
@@ -492,7 +493,7 @@ __global__ void __launch_bounds__(256, 4) k_mx_decode_small(MxArgs a, ProjArgs p
     const u32x4_t* mine = (const u32x4_t*)(rfw + (size_t)(g * 4 + (tok ? i : 0)) * 64);
     float s[8];
     bool done = false;
-    for (int spin = 0; spin < (1 << 16); ++spin) {
+    for (int spin = 0; spin < MXS_WAIT_POLLS; ++spin) {
       vm_wait<0>();                                   // the slots asked for last have landed in LDS
       bool ok = true;
 #pragma unroll
@@ -991,18 +992,24 @@ static void launch_mx_tile(const MxGemmArgs& a, int tile, int n_wgs, hipStream_t
   if constexpr (I + 1 < MX_N_TILES) launch_mx_tile<ACT, I + 1>(a, tile, n_wgs, st);
 }
 
+// K slices of the projection: the sum over slices costs about 3 us more than a slice's own work, so
+// only contractions past 4096 channels are cut, in slices of about 2048, at most four (the area
+// of partial sums holds their slots) and no more than 256 workgroups
+static int mx_proj_slices(const glowq_unit& u, int* kslice) {
+  const int pieces16 = (u.T + 15) / 16 * std::max(1, (u.r + 31) / 32);
+  const int want = u.d_in <= 4096 ? 1 : std::max(1, std::min(std::min(4, (u.d_in + 2047) / 2048), 256 / pieces16));
+  *kslice = (u.d_in / 32 + want - 1) / want * 32;
+  return (u.d_in + *kslice - 1) / *kslice;
+}
+
 static hipError_t launch_mx_gemm(const glowq_unit& u, bool restore, char* workspace, hipStream_t st) {
   const MxWorkspace w = plan_mx_workspace(u);
   uint8_t* xcodes = (uint8_t*)(workspace + w.off_xcodes);
   uint8_t* xscales = (uint8_t*)(workspace + w.off_xscales);
   const bool corrected = restore && u.r > 0, f16 = u.act_dtype == GLOWQ_F16;
   const UnitWorkspace uw = plan_unit_workspace(u, workspace);
-  // K slices of the projection: the sum over slices costs about 3 us more than a slice's own work, so
-  // only contractions past 4096 channels are cut, in slices of about 2048, at most four (the area
-  // of partial sums holds their slots) and no more than 256 workgroups
-  const int pieces16 = (u.T + 15) / 16 * std::max(1, (u.r + 31) / 32);
-  const int want = u.d_in <= 4096 ? 1 : std::max(1, std::min(std::min(4, (u.d_in + 2047) / 2048), 256 / pieces16));
-  const int kslice = (u.d_in / 32 + want - 1) / want * 32, ksplit = (u.d_in + kslice - 1) / kslice;
+  int kslice = 0;
+  const int ksplit = mx_proj_slices(u, &kslice);
   MxFrontTiles fa;
   fa.p = ProjSliced{(const uint16_t*)u.X, corrected ? (const uint16_t*)u.B : nullptr, (float*)(uw.base + uw.off_rpart),
                     u.T, u.d_in, u.r, ksplit, kslice};
@@ -1098,6 +1105,19 @@ static hipError_t launch_mx_small(const glowq_unit& u, bool restore, char* works
   if (u.act_dtype == GLOWQ_F16) k_mx_decode_small<ACT_F16><<<grid, block, lds, st>>>(a, p, n_prod);
   else k_mx_decode_small<ACT_BF16><<<grid, block, lds, st>>>(a, p, n_prod);
   return hipGetLastError();
+}
+
+void mx_route(const glowq_unit& u, glowq_route* route) {
+  *route = glowq_route{0, GLOWQ_ROUTE_MX_SMALL, 0, 1, 0};
+  if (u.T > MX_MAX_TOKENS) {
+    int kslice = 0;
+    route->kernel = GLOWQ_ROUTE_MX_TILED;
+    route->tile = choose_mx_tile(u);
+    route->wait_polls = u.r > 0 && mx_proj_slices(u, &kslice) > 1 ? PROJ_WAIT_POLLS : 0;
+  } else if (mx_one_launch(u)) {
+    route->kernel = GLOWQ_ROUTE_MX_ONE;
+    route->wait_polls = MXS_WAIT_POLLS;
+  }
 }
 
 hipError_t launch_mx_forward(const glowq_unit& u, bool restore, char* workspace, hipStream_t st) {

@@ -285,10 +285,11 @@ __device__ inline void proj_tile(const PrefillArgs& a, uint16_t* xs) {
 // whole contraction they have long finished; the loop is bounded all the same, and a
 // wave that gives up records it in the unit's status word and leaves the correction out
 // rather than hang.
+constexpr int PF_WAIT_POLLS = 1 << 20;
 __device__ inline bool wait_tile_ready(const uint32_t* flag, uint32_t* status) {
   const uint32_t tag = (uint32_t)launch_tag();
   bool ok = false;
-  for (int spin = 0; spin < (1 << 20); ++spin) {
+  for (int spin = 0; spin < PF_WAIT_POLLS; ++spin) {
     if (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == tag) { ok = true; break; }
     __builtin_amdgcn_s_sleep(8);
   }
@@ -815,21 +816,34 @@ static float prefill_cost_of(const glowq_unit* const* units, int n, bool half) {
   const double share = per_cu <= 1.0 ? c.alone : per_cu <= 2.0 ? c.pair : std::max((double)c.pair, c.busy * per_cu + 0.8 * c.alone);
   return (float)(c.start + std::max((double)chain * c.alone, work / wgs * share));
 }
-float prefill_cost(const glowq_unit* const* units, int n) {
-  return std::min(prefill_cost_of(units, n, false), prefill_cost_of(units, n, true));
+bool choose_prefill_tile(const glowq_unit* const* units, int n, float* cost) {
+  const float full = prefill_cost_of(units, n, false), half = prefill_cost_of(units, n, true);
+  *cost = std::min(full, half);
+  return half < 0.9f * full;            // (a clear advantage: the estimates are good to about 10 %)
+}
+
+void plan_prefill_slices(const glowq_unit* const* units, int n, bool slabs, int* slices) {
+  int total = 0;
+  for (int ui = 0; ui < n; ++ui) total += units[ui]->n_modules;
+  for (int ui = 0; ui < n; ++ui) {
+    const glowq_unit& u = *units[ui];
+    int S = slabs ? prefill_k_slices(u) : 1;
+    if (total + (S - 1) * u.n_modules > PF_MAX_MODS) S = 1;
+    total += (S - 1) * u.n_modules;
+    slices[ui] = S;
+  }
 }
 
 int prefill_max_units() { return PF_MAX_UNITS; }
 int prefill_max_modules() { return PF_MAX_MODS; }
+int prefill_wait_polls() { return PF_WAIT_POLLS; }
 
 // units[i] uses workspace slice ws[i]; restore[i] says whether its R16 is valid.
 hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorkspace* ws,
-                                const bool* restore, int n_units, bool allow_split, hipStream_t st) {
+                                const bool* restore, int n_units, bool half, const int* slices, hipStream_t st) {
   PrefillArgs a;
   const glowq_unit& u0 = *units[0];
   constexpr int MB = PF_MB;
-  // (a clear advantage: the estimates are good to about 10 %)
-  const bool half = prefill_cost_of(units, n_units, true) < 0.9f * prefill_cost_of(units, n_units, false);
   const int tile_blocks = prefill_tile_blocks(u0.act_dtype, half);
   // longest contraction first
   int order[PF_MAX_UNITS];
@@ -855,20 +869,6 @@ hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorksp
   }
   a.n_proj_wgs = n_proj;
   a.n_units = n_units;
-  // K slices per unit: where the unit's shapes ask for them, its workspace has the slabs and
-  // the module table has room
-  int slices[PF_MAX_UNITS];
-  {
-    int total = 0;
-    for (int ui = 0; ui < n_units; ++ui) total += units[ui]->n_modules;
-    for (int ui = 0; ui < n_units; ++ui) {
-      const glowq_unit& u = *units[ui];
-      int S = (allow_split && ws[ui].base && ws[ui].splitk_bytes > 0) ? prefill_k_slices(u) : 1;
-      if (total + (S - 1) * u.n_modules > PF_MAX_MODS) S = 1;
-      total += (S - 1) * u.n_modules;
-      slices[ui] = S;
-    }
-  }
   int n_mods = 0, wg = n_proj;
   for (int oi = 0; oi < n_units; ++oi) {
     const int ui = order[oi];

@@ -102,6 +102,7 @@ __device__ inline void load4_device(u32x4_t (&v)[4], const void* p0, const void*
 }
 
 constexpr int PROJ_NB = 2;               // 16-rank blocks per workgroup
+constexpr int PROJ_WAIT_POLLS = 1 << 13;
 struct ProjSliced {
   const uint16_t* X;
   const uint16_t* B;
@@ -180,7 +181,7 @@ __device__ inline void proj_sliced(const ProjSliced& u, int local, float* lds, O
     // already running) adds the slices in slice order
     const unsigned long long* q = (const unsigned long long*)u.part + (size_t)t * ksplit * r + rank;
     bool ok = false;
-    for (int spin = 0; spin < (1 << 13) && !ok; ++spin) {
+    for (int spin = 0; spin < PROJ_WAIT_POLLS && !ok; ++spin) {
       u32x4_t v[4];
       load4_device(v, q, q + (size_t)min(1, ksplit - 1) * r, q + (size_t)min(2, ksplit - 1) * r, q + (size_t)(ksplit - 1) * r);
       ok = true;

@@ -1,0 +1,54 @@
+"""Which kernel serves a forward call, asked of the library on the host (no GPU): the limits of the
+classes, what shares a launch, K slices and what waits inside a launch."""
+import pytest
+
+import paper_2603_25385_amd as G
+
+
+def unit(T, d_in, d_outs, r=16, Gs=128, act=G.GLOWQ_F16, out=G.GLOWQ_F32):
+    mods = [G.make_module(0, 0, 0, d, d) for d in d_outs]
+    return G.make_unit(0, 0, mods, T, d_in, r, Gs, act, out)
+
+
+def route(*args, slabs=True, **kw):
+    return G.glowq_debug_route([unit(*args, **kw)], slabs)[0]
+
+
+def test_classes_by_token_count():
+    K = [(T, route(T, 4096, (4096,)).kernel) for T in (1, 4, 5, 64, 65, 2048, 2049)]
+    assert K == [(1, G.GLOWQ_ROUTE_FEW), (4, G.GLOWQ_ROUTE_FEW), (5, G.GLOWQ_ROUTE_BATCHED), (64, G.GLOWQ_ROUTE_BATCHED),
+                 (65, G.GLOWQ_ROUTE_BATCHED), (2048, G.GLOWQ_ROUTE_TILED), (2049, G.GLOWQ_ROUTE_TILED)]
+    assert route(2049, 256, (64,)).kernel == G.GLOWQ_ROUTE_TILED      # never batched past 2048 tokens
+    M = [(T, G.glowq_debug_mx_route(unit(T, 4096, (4096,))).kernel) for T in (1, 4, 5, 16, 17)]
+    assert M == [(1, G.GLOWQ_ROUTE_MX_ONE), (4, G.GLOWQ_ROUTE_MX_ONE), (5, G.GLOWQ_ROUTE_MX_SMALL),
+                 (16, G.GLOWQ_ROUTE_MX_SMALL), (17, G.GLOWQ_ROUTE_MX_TILED)]
+
+
+def test_units_that_share_a_launch():
+    few = [unit(T, 256, (64,)) for T in (1, 1, 2, 1)]
+    assert [r.launch for r in G.glowq_debug_route(few)] == [0, 0, 1, 2]
+    batched = [unit(T, 256, (64,)) for T in (9, 16, 17, 32, 33, 64)] + [unit(64, 256, (64,), act=G.GLOWQ_BF16)]
+    assert [r.launch for r in G.glowq_debug_route(batched)] == [0, 0, 1, 1, 2, 2, 3]
+    assert [r.launch for r in G.glowq_debug_route([unit(24, 256, (64,))] * 17)] == [0] * 16 + [1]
+    tiled = [unit(512, 4096, (4096,) * 8)] * 3                        # sixteen module entries per launch
+    assert [r.launch for r in G.glowq_debug_route(tiled)] == [0, 0, 1]
+
+
+def test_k_slices_need_their_slabs():
+    assert route(512, 14336, (4096,)).k_slices == 3
+    assert route(512, 14336, (4096,), slabs=False).k_slices == 1
+    assert route(512, 4096, (4096,)).k_slices == 1
+
+
+def test_argument_checks():
+    for units, status in [([unit(0, 256, (64,))], G.GLOWQ_ERR_SHAPE), ([unit(4, 192, (64,))], G.GLOWQ_ERR_SHAPE),
+                          ([unit(4, 320, (64,), Gs=64)], G.GLOWQ_ERR_UNSUPPORTED)]:
+        with pytest.raises(G.GlowqError) as e:
+            G.glowq_debug_route(units)
+        assert e.value.status == status
+    bare = unit(20, 256, (64,))
+    bare.modules = None
+    for call in (lambda: G.glowq_debug_route([bare]), lambda: G.glowq_debug_mx_route(bare)):
+        with pytest.raises(G.GlowqError) as e:
+            call()
+        assert e.value.status == G.GLOWQ_ERR_NULL
