@@ -26,7 +26,7 @@
 // 82 -> 19 us.
 //
 // The projection workgroups lead the grid: (16-token block, K slice, 32 ranks).  Slices are
-// published as self-validating 8-byte slots {fp32, launch tag}; the last slice's workgroup
+// published as self-validating 8-byte slots {fp32, launch tag}; whoever finds them complete
 // adds them in slice order, rounds to the activation type and publishes R as slots {two
 // 16-bit values, launch tag}, so that a consumer gathers 4 bytes per element of R instead
 // of 8 per element and slice.  (With the slices gathered by every consumer, T = 24 at rank 128
@@ -95,11 +95,9 @@ template <typename T> __device__ inline T* scalar_ptr(T* p) {
 template <int ACT, int NW>
 __device__ inline void batch_projection(const BatchUnit& u, int local, float* lds) {
   const ProjSliced p{u.X, u.B, u.part, u.T, u.K, u.r, u.ksplit, u.kslice};
-  proj_sliced<ACT, NW>(p, local, lds, [&](int t, int rank, uint32_t pair, uint32_t tag, bool ok) {
-    if (ok)
-      __hip_atomic_store((unsigned long long*)u.rslots + (size_t)t * (u.r >> 1) + (rank >> 1),
-                         ((unsigned long long)tag << 32) | pair, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else atomicOr(&u.ctl->status, 1u);           // (the consumers' waits then expire too)
+  proj_sliced<ACT, NW>(p, local, lds, [&](int t, int rank, uint32_t pair, uint32_t tag) {
+    __hip_atomic_store((unsigned long long*)u.rslots + (size_t)t * (u.r >> 1) + (rank >> 1),
+                       ((unsigned long long)tag << 32) | pair, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   });
 }
 

@@ -886,9 +886,8 @@ __global__ void __launch_bounds__(MX_FRONT_THREADS) k_mx_front_tiles(MxFrontTile
                                  (long long)((int)blockIdx.x - a.n_proj) * MX_FRONT_THREADS + threadIdx.x);
     return;
   }
-  proj_sliced<ACT, MX_FRONT_THREADS / 64>(a.p, (int)blockIdx.x, part, [&](int t, int rank, uint32_t pair, uint32_t, bool ok) {
-    // (this path has no status word: a slice that never came becomes NaN, which no caller overlooks)
-    ((uint32_t*)a.R16)[((long long)t * a.p.r + rank) >> 1] = ok ? pair : 0x7fff7fffu;
+  proj_sliced<ACT, MX_FRONT_THREADS / 64>(a.p, (int)blockIdx.x, part, [&](int t, int rank, uint32_t pair, uint32_t) {
+    ((uint32_t*)a.R16)[((long long)t * a.p.r + rank) >> 1] = pair;
   });
 }
 
@@ -1110,10 +1109,8 @@ static hipError_t launch_mx_small(const glowq_unit& u, bool restore, char* works
 void mx_route(const glowq_unit& u, glowq_route* route) {
   *route = glowq_route{0, GLOWQ_ROUTE_MX_SMALL, 0, 1, 0};
   if (u.T > MX_MAX_TOKENS) {
-    int kslice = 0;
     route->kernel = GLOWQ_ROUTE_MX_TILED;
     route->tile = choose_mx_tile(u);
-    route->wait_polls = u.r > 0 && mx_proj_slices(u, &kslice) > 1 ? PROJ_WAIT_POLLS : 0;
   } else if (mx_one_launch(u)) {
     route->kernel = GLOWQ_ROUTE_MX_ONE;
     route->wait_polls = MXS_WAIT_POLLS;

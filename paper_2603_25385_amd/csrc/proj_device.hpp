@@ -102,7 +102,6 @@ __device__ inline void load4_device(u32x4_t (&v)[4], const void* p0, const void*
 }
 
 constexpr int PROJ_NB = 2;               // 16-rank blocks per workgroup
-constexpr int PROJ_WAIT_POLLS = 1 << 13;
 struct ProjSliced {
   const uint16_t* X;
   const uint16_t* B;
@@ -111,9 +110,12 @@ struct ProjSliced {
 };
 
 // One workgroup of NW waves: tokens 16 tb .., K slice kz, ranks 32 ng .. + 32.  Slices are
-// published as self-validating slots; the last slice's workgroup adds them in slice order and
-// out(t, rank, pair, tag, ok) receives two ranks rounded to the activation type (ok false if the
-// bounded wait for the other slices expired).  lds: NW * PROJ_NB * 256 floats.
+// published as self-validating slots, and nobody waits for anybody: a thread whose own slots are
+// out looks at its elements' slots of all slices once, and whoever finds them complete adds them in
+// slice order; out(t, rank, pair, tag) receives two ranks rounded to the activation type.  Of two
+// slices at least one finds the other's slots: a look is issued when the thread's own stores have
+// completed at device scope, so the later of the two looks comes behind both stores.  Several may
+// find them all; they hand out the same bits.  lds: NW * PROJ_NB * 256 floats.
 template <int ACT, int NW, class OUT>
 __device__ inline void proj_sliced(const ProjSliced& u, int local, float* lds, OUT out) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -176,34 +178,25 @@ __device__ inline void proj_sliced(const ProjSliced& u, int local, float* lds, O
     for (int e = 0; e < 2; ++e)
       __hip_atomic_store(slot + e, tag_hi | (unsigned long long)__builtin_bit_cast(uint32_t, s[e]),
                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (kz != ksplit - 1) return;
-    // the last slice's workgroup (the highest index of the group: everybody it waits for is
-    // already running) adds the slices in slice order
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // (counts stores, too)
     const unsigned long long* q = (const unsigned long long*)u.part + (size_t)t * ksplit * r + rank;
-    bool ok = false;
-    for (int spin = 0; spin < PROJ_WAIT_POLLS && !ok; ++spin) {
-      u32x4_t v[4];
-      load4_device(v, q, q + (size_t)min(1, ksplit - 1) * r, q + (size_t)min(2, ksplit - 1) * r, q + (size_t)(ksplit - 1) * r);
-      ok = true;
-      s[0] = s[1] = 0.f;
+    u32x4_t v[4];
+    load4_device(v, q, q + (size_t)min(1, ksplit - 1) * r, q + (size_t)min(2, ksplit - 1) * r, q + (size_t)(ksplit - 1) * r);
+    bool all = true;
+    s[0] = s[1] = 0.f;
 #pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        const uint32_t w0 = v[p][0], t0 = v[p][1], w1 = v[p][2], t1 = v[p][3];
-        ok = ok && t0 == tag && t1 == tag;
-        if (p < ksplit) {
-          s[0] += __builtin_bit_cast(float, w0);
-          s[1] += __builtin_bit_cast(float, w1);
-        }
+    for (int p = 0; p < 4; ++p) {
+      const uint32_t w0 = v[p][0], t0 = v[p][1], w1 = v[p][2], t1 = v[p][3];
+      all = all && t0 == tag && t1 == tag;
+      if (p < ksplit) {
+        s[0] += __builtin_bit_cast(float, w0);
+        s[1] += __builtin_bit_cast(float, w1);
       }
-      if (!ok) __builtin_amdgcn_s_sleep(8);
     }
-    if (!ok) {
-      out(t, rank, 0u, tag, false);
-      return;
-    }
+    if (!all) return;
   }
   const uint32_t pk = (uint32_t)to_act16<ACT>(s[0]) | ((uint32_t)to_act16<ACT>(s[1]) << 16);
-  out(t, rank, pk, tag, true);
+  out(t, rank, pk, tag);
 }
 
 }  // namespace glowq

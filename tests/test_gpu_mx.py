@@ -287,3 +287,19 @@ def test_small_tiles(act, T, d_in, d_outs, r):
             got = du.forward(restore)
             for g, y in zip(got, MX.mx_group_forward(u, restore)):
                 assert np.isfinite(g).all() and rel_err(g, y) <= TOL + (ULP[act] if out == "act" else 0.0)
+
+
+@pytest.mark.parametrize("T,d_in,r", [(40, 8320, 128), (130, 4352, 24)])
+def test_tiled_calls_in_a_row_with_a_sliced_projection(T, d_in, r):
+    # the projection's K slices meet inside the first launch, whichever comes last: 500 calls in a row
+    # through one workspace of any contents, every look at the result equal to the first one's bits
+    u = make_unit(UnitShape("g", d_in, (136, 72)), T, r, "f16", seed=24)
+    du = MxDeviceUnit(u)
+    first = du.forward(True)
+    for g, y in zip(first, MX.mx_group_forward(u, True)):
+        assert rel_err(g, y) <= TOL
+    for it in range(10):
+        du.ws.fill_(0xFF if it & 1 else 0)
+        for _ in range(50):
+            G.glowq_mx_group_forward(du.desc, 1, du.ws.data_ptr(), du.ws_bytes, stream())
+        assert all(np.array_equal(a, b) for a, b in zip(first, du.forward(True)))

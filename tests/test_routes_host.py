@@ -40,6 +40,15 @@ def test_k_slices_need_their_slabs():
     assert route(512, 4096, (4096,)).k_slices == 1
 
 
+def test_only_consumers_of_r_wait():
+    # the projection's own workgroups wait for nothing, so launches whose consumers come in a launch of
+    # their own have no wait at all, whether the projection is cut into K slices (past 4096 channels) or not
+    for d_in in (4096, 4352, 8192, 16384):
+        for T in (17, 130, 2048):
+            assert G.glowq_debug_mx_route(unit(T, d_in, (4096,), r=64)).wait_polls == 0, (T, d_in)
+        assert G.glowq_debug_mx_route(unit(16, d_in, (4096,), r=64)).wait_polls == 0
+
+
 def test_argument_checks():
     for units, status in [([unit(0, 256, (64,))], G.GLOWQ_ERR_SHAPE), ([unit(4, 192, (64,))], G.GLOWQ_ERR_SHAPE),
                           ([unit(4, 320, (64,), Gs=64)], G.GLOWQ_ERR_UNSUPPORTED)]:
