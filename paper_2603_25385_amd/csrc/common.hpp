@@ -400,6 +400,10 @@ template <int N> __device__ inline void vm_wait() {
 __device__ inline void after_wait(u32x4_t& v) { asm volatile("" : "+v"(v)); }
 __device__ inline void after_wait32(uint32_t& v) { asm volatile("" : "+v"(v)); }
 
+// Looks that a workgroup takes at R, when the projection of its launch is still under way, before it
+// gives up (about a second and more: long enough for another stream's kernels to make room).
+constexpr int R_WAIT_POLLS = 1 << 20;
+
 // Control words at the head of a unit's workspace slice.
 struct Control {
   uint32_t unused[3];

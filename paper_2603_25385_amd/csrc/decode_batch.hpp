@@ -42,7 +42,6 @@
 namespace glowq {
 
 constexpr int BATCH_MAX_UNITS = 16;
-constexpr int BATCH_WAIT_POLLS = 1 << 12;
 constexpr int BATCH_WB = 1024 + 256;      // bytes per wave and K tile: one record's words, its (s, z) words
 
 struct BatchUnit {
@@ -111,7 +110,7 @@ __device__ inline bool batch_fetch_r(const BatchUnit& u, int tok0, int n_tok, ui
   const u32x4_t* src = (const u32x4_t*)u.rslots + (size_t)tok0 * (u.r >> 2);
   if (tid == 0) *flag = 0u;
   __syncthreads();
-  for (int spin = 0; spin < BATCH_WAIT_POLLS; ++spin) {
+  for (int spin = 0; spin < R_WAIT_POLLS; ++spin) {
     bool ok = true;
     for (int e0 = 0; e0 < n_el; e0 += 4 * NT) {
       u32x4_t v[4];
@@ -413,7 +412,7 @@ bool batch_compatible(const glowq_unit& a, const glowq_unit& b) {
          a.group_size == b.group_size && (a.T <= 16) == (b.T <= 16) && (a.T <= 32) == (b.T <= 32);
 }
 int batch_max_units() { return BATCH_MAX_UNITS; }
-int batch_wait_polls() { return BATCH_WAIT_POLLS; }
+int batch_wait_polls() { return R_WAIT_POLLS; }
 
 // Workgroup tiles: 16 mb tokens x 16 rb rw rows, nw / rw groups of waves sharing the contraction.
 // What a tile costs was measured over 70 shapes (5 to 1001 tokens, 144 to 48000 rows, 256 to 13696

@@ -285,11 +285,10 @@ __device__ inline void proj_tile(const PrefillArgs& a, uint16_t* xs) {
 // whole contraction they have long finished; the loop is bounded all the same, and a
 // wave that gives up records it in the unit's status word and leaves the correction out
 // rather than hang.
-constexpr int PF_WAIT_POLLS = 1 << 20;
 __device__ inline bool wait_tile_ready(const uint32_t* flag, uint32_t* status) {
   const uint32_t tag = (uint32_t)launch_tag();
   bool ok = false;
-  for (int spin = 0; spin < PF_WAIT_POLLS; ++spin) {
+  for (int spin = 0; spin < R_WAIT_POLLS; ++spin) {
     if (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == tag) { ok = true; break; }
     __builtin_amdgcn_s_sleep(8);
   }
@@ -836,7 +835,7 @@ void plan_prefill_slices(const glowq_unit* const* units, int n, bool slabs, int*
 
 int prefill_max_units() { return PF_MAX_UNITS; }
 int prefill_max_modules() { return PF_MAX_MODS; }
-int prefill_wait_polls() { return PF_WAIT_POLLS; }
+int prefill_wait_polls() { return R_WAIT_POLLS; }
 
 // units[i] uses workspace slice ws[i]; restore[i] says whether its R16 is valid.
 hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorkspace* ws,

@@ -49,6 +49,17 @@ def test_only_consumers_of_r_wait():
         assert G.glowq_debug_mx_route(unit(16, d_in, (4096,), r=64)).wait_polls == 0
 
 
+def test_the_wait_for_r_is_as_long_on_small_tiles():
+    # whichever kernel a call of more than four tokens takes, its consumers look for R a million times
+    # (a second and more) before they leave the correction out: a call must not lose it sooner
+    # because its tiles are small
+    tiled = route(2048, 4096, (14336,))
+    assert tiled.kernel == G.GLOWQ_ROUTE_TILED and tiled.wait_polls >= 1 << 20
+    for T in (5, 16, 32, 33, 64, 65, 300, 1000):
+        small = route(T, 512, (264,))
+        assert small.kernel == G.GLOWQ_ROUTE_BATCHED and small.wait_polls >= tiled.wait_polls, T
+
+
 def test_argument_checks():
     for units, status in [([unit(0, 256, (64,))], G.GLOWQ_ERR_SHAPE), ([unit(4, 192, (64,))], G.GLOWQ_ERR_SHAPE),
                           ([unit(4, 320, (64,), Gs=64)], G.GLOWQ_ERR_UNSUPPORTED)]:
