@@ -209,7 +209,7 @@ static glowq_status forward_all(const glowq_unit* units, int n_units, const uint
       ws[k] = plan_unit_workspace(units[i], workspace ? workspace + off : nullptr);
       off += ws[k].bytes;
       corr[k] = (!mask || mask[i]) && units[i].r > 0;
-      if (c.kernel == GLOWQ_ROUTE_BATCHED) plan_batch_projection(units[i], ws[k]);
+      if (c.kernel == GLOWQ_ROUTE_BATCHED && !is_decode(units[i].T)) plan_batch_projection(*batch[k], ws[k]);
     }
     const hipError_t e = c.kernel == GLOWQ_ROUTE_FEW       ? launch_decode_multi(batch, ws, corr, c.n, st)
                          : c.kernel == GLOWQ_ROUTE_BATCHED ? launch_decode_batch(batch, ws, corr, c.n, c.tile, st)

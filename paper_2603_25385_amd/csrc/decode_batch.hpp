@@ -37,11 +37,11 @@
 #include "proj_device.hpp"
 #include "launch.hpp"
 #include <algorithm>
-#include <cmath>
 
 namespace glowq {
 
 constexpr int BATCH_MAX_UNITS = 16;
+constexpr int BATCH_QUICK_POLLS = 64;    // looks at R with hardly a pause in between
 constexpr int BATCH_WB = 1024 + 256;      // bytes per wave and K tile: one record's words, its (s, z) words
 
 struct BatchUnit {
@@ -133,7 +133,10 @@ __device__ inline bool batch_fetch_r(const BatchUnit& u, int tok0, int n_tok, ui
     if (!failed) return true;
     __syncthreads();
     if (tid == 0) *flag = 0u;
-    __builtin_amdgcn_s_sleep(32);
+    // (short pauses at first: in the smallest calls R comes while the consumers already look for it,
+    // and a pause of a microsecond between two looks cost half of one: 7.1 -> 6.4 us)
+    if (spin < BATCH_QUICK_POLLS) __builtin_amdgcn_s_sleep(1);
+    else __builtin_amdgcn_s_sleep(32);
     __syncthreads();
   }
   if (tid == 0) atomicOr(&u.ctl->status, 1u);
@@ -420,15 +423,18 @@ int batch_wait_polls() { return R_WAIT_POLLS; }
 // group: `chain`, when the compute unit has nothing else to do, and `busy`, each workgroup's
 // share of a compute unit that is full.  A launch then takes the longer of its longest
 // contraction and its share of the chip; picking the cheapest tile by that was within 2 % of
-// the best one on average, 19 % at worst.
+// the best one on average, 19 % at worst.  `start`: eight waves begin and meet later than four.
+// (Kernel times of 70 calls of 5 to 64 tokens on every tile: two K tiles of 3 x 256 rows at 16 tokens
+// 5.6 us on four waves, 6.4 on eight; with the term the choice was 1.8 % above the best on average,
+// without it 2.3 %.)
 struct BatchTile {
   int mb, rb, rw, nw;
-  float chain, busy_f16, busy_bf16;
+  float start, chain, busy_f16, busy_bf16;
 };
 constexpr BatchTile BATCH_TILES[] = {
-    {1, 1, 1, 4, 0.45f, 0.65f, 0.69f}, {1, 1, 4, 4, 0.25f, 0.19f, 0.24f}, {1, 1, 4, 8, 0.25f, 0.38f, 0.51f},
-    {2, 1, 4, 4, 0.30f, 0.30f, 0.32f}, {2, 1, 4, 8, 0.45f, 0.63f, 0.73f}, {4, 1, 4, 4, 0.42f, 0.53f, 0.59f},
-    {4, 2, 4, 4, 0.75f, 0.73f, 0.84f},
+    {1, 1, 1, 4, 0.0f, 0.45f, 0.65f, 0.69f}, {1, 1, 4, 4, 0.0f, 0.25f, 0.19f, 0.24f}, {1, 1, 4, 8, 0.4f, 0.25f, 0.38f, 0.51f},
+    {2, 1, 4, 4, 0.0f, 0.30f, 0.30f, 0.32f}, {2, 1, 4, 8, 0.4f, 0.45f, 0.63f, 0.73f}, {4, 1, 4, 4, 0.0f, 0.42f, 0.53f, 0.59f},
+    {4, 2, 4, 4, 0.0f, 0.75f, 0.73f, 0.84f},
 };
 constexpr int BATCH_N_TILES = sizeof(BATCH_TILES) / sizeof(BATCH_TILES[0]);
 
@@ -441,39 +447,49 @@ constexpr int BATCH_RESIDENT[] = {batch_tile_resident<0>(), batch_tile_resident<
                                   batch_tile_resident<6>()};
 static_assert(sizeof(BATCH_RESIDENT) / sizeof(int) == BATCH_N_TILES, "one entry per tile");
 
-static int row_blocks(const glowq_unit& u) {
-  int b = 0;
-  for (int i = 0; i < u.n_modules; ++i) b += (u.modules[i].d_out + 15) / 16;
-  return b;
+// What the tiles from I on cost for units of `blocks` row blocks, `kt` K tiles and T tokens (a tile
+// at a time as constants, so that a call pays for shifts instead of divisions: one call of the
+// smallest group is a few hundred instructions of host code in all)
+struct BatchSize {
+  int blocks, kt, T;
+};
+template <int I>
+static inline void cheapest_batch_tile(const BatchSize* u, int n, bool f16, int max_mb, int* best, float* cost) {
+  constexpr BatchTile t = BATCH_TILES[I];
+  constexpr int ks = t.nw / t.rw, rows = t.rb * t.rw, tok = 16 * t.mb;
+  if (t.mb <= max_mb) {
+    long long work = 0, wgs = 0;
+    int chain = 0;
+    for (int k = 0; k < n; ++k) {
+      const int stages = (u[k].kt + ks - 1) / ks;
+      const long long w = (long long)((u[k].blocks + rows - 1) / rows) * ((u[k].T + tok - 1) / tok);
+      wgs += w;
+      work += w * stages;
+      chain = std::max(chain, stages);
+    }
+    const float busy = f16 ? t.busy_f16 : t.busy_bf16;
+    const float per_cu = wgs <= 256 * BATCH_RESIDENT[I] ? (float)((wgs + 255) / 256) : (float)wgs / 256.f;
+    const float c = t.start + std::max((float)chain * t.chain, (float)work / (float)wgs * per_cu * busy);
+    if (*best < 0 || c < *cost) {
+      *best = I;
+      *cost = c;
+    }
+  }
+  if constexpr (I + 1 < BATCH_N_TILES) cheapest_batch_tile<I + 1>(u, n, f16, max_mb, best, cost);
 }
 
 // The cheapest tile for these units in one launch, and what it is taken to cost (us beyond the
 // launch itself).
 int choose_batch_tile(const glowq_unit* const* units, int n, float* cost) {
   const bool f16 = units[0]->act_dtype == GLOWQ_F16, exact = f16 && units[0]->T <= 32;
-  int best = -1;
-  for (int i = 0; i < BATCH_N_TILES; ++i) {
-    const BatchTile& t = BATCH_TILES[i];
-    if (exact && t.mb > 2) continue;
-    const int ks = t.nw / t.rw;
-    double work = 0.0, wgs = 0.0;
-    int chain = 0;
-    for (int k = 0; k < n; ++k) {
-      const glowq_unit& u = *units[k];
-      const int stages = (u.d_in / 128 + ks - 1) / ks;
-      const double w = (double)((row_blocks(u) + t.rb * t.rw - 1) / (t.rb * t.rw)) * ((u.T + 16 * t.mb - 1) / (16 * t.mb));
-      wgs += w;
-      work += w * stages;
-      chain = std::max(chain, stages);
-    }
-    double per_cu = wgs / 256.0;
-    if (per_cu <= BATCH_RESIDENT[i]) per_cu = std::ceil(per_cu);
-    const float c = (float)std::max((double)chain * t.chain, work / wgs * per_cu * (f16 ? t.busy_f16 : t.busy_bf16));
-    if (best < 0 || c < *cost) {
-      best = i;
-      *cost = c;
-    }
+  BatchSize sizes[BATCH_MAX_UNITS];
+  for (int k = 0; k < n; ++k) {
+    const glowq_unit& u = *units[k];
+    sizes[k] = BatchSize{0, u.d_in / 128, u.T};
+    for (int i = 0; i < u.n_modules; ++i) sizes[k].blocks += (u.modules[i].d_out + 15) / 16;
   }
+  int best = -1;
+  cheapest_batch_tile<0>(sizes, n, f16, exact ? 2 : 4, &best, cost);
   return best;
 }
 

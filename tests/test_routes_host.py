@@ -60,6 +60,15 @@ def test_the_wait_for_r_is_as_long_on_small_tiles():
         assert small.kernel == G.GLOWQ_ROUTE_BATCHED and small.wait_polls >= tiled.wait_polls, T
 
 
+def test_the_smallest_calls_start_four_waves():
+    # two or three K tiles on few rows: a workgroup of eight waves (tiles 2 and 4) takes longer to start
+    # and to meet than its second wave group saves
+    for T, d_in, d_outs, Gs in [(16, 256, (256,) * 3, 64), (13, 256, (1408,), 128), (9, 384, (512, 512), 128),
+                                (24, 256, (256,), 128)]:
+        for act in (G.GLOWQ_F16, G.GLOWQ_BF16):
+            assert route(T, d_in, d_outs, Gs=Gs, act=act).tile not in (2, 4), (T, d_in, d_outs)
+
+
 def test_argument_checks():
     for units, status in [([unit(0, 256, (64,))], G.GLOWQ_ERR_SHAPE), ([unit(4, 192, (64,))], G.GLOWQ_ERR_SHAPE),
                           ([unit(4, 320, (64,), Gs=64)], G.GLOWQ_ERR_UNSUPPORTED)]:
