@@ -61,6 +61,7 @@ UnitWorkspace plan_unit_workspace(const glowq_unit& u, char* base) {
   w.kslice = per * 32;
   w.ksplit = (u.d_in + w.kslice - 1) / w.kslice;
   w.kstride = (w.ksplit + 3) / 4 * 4;
+  w.gather = 0;
   if (!direct && is_decode(u.T)) plan_batch_projection(u, w);     // (at most the four slices sized for above)
   // T > 64: the projection tiles that lead the GEMM launch take parts of about 2048
   // channels (at most 8), so that the longest contraction's R is ready as early as the

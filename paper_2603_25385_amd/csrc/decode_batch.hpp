@@ -30,7 +30,8 @@
 // adds them in slice order, rounds to the activation type and publishes R as slots {two
 // 16-bit values, launch tag}, so that a consumer gathers 4 bytes per element of R instead
 // of 8 per element and slice.  (With the slices gathered by every consumer, T = 24 at rank 128
-// moved 98 KB of device-scope loads per workgroup.)
+// moved 98 KB of device-scope loads per workgroup; a small R is gathered that way all the same, see
+// plan_batch_projection.)
 #pragma once
 #include "common.hpp"
 #include "decode_device.hpp"
@@ -56,6 +57,7 @@ struct BatchUnit {
   int n_groups, n_ttiles;      // its workgroups: groups of row blocks x tiles of 16 MB tokens
   int restore, out_f32;
   int ksplit, kslice;          // K slices of the projection
+  int gather;                  // the consumers add the slices themselves (see plan_batch_projection)
   int prod_start, n_prod;      // this unit's projection workgroups
   int wg_start;                // first row-block workgroup
 };
@@ -93,16 +95,17 @@ template <typename T> __device__ inline T* scalar_ptr(T* p) {
 // One projection workgroup (see proj_sliced): R as slots {two ranks, tag}.
 template <int ACT, int NW>
 __device__ inline void batch_projection(const BatchUnit& u, int local, float* lds) {
-  const ProjSliced p{u.X, u.B, u.part, u.T, u.K, u.r, u.ksplit, u.kslice};
+  const ProjSliced p{u.X, u.B, u.part, u.T, u.K, u.r, u.ksplit, u.kslice, u.gather != 0};
   proj_sliced<ACT, NW>(p, local, lds, [&](int t, int rank, uint32_t pair, uint32_t tag) {
     __hip_atomic_store((unsigned long long*)u.rslots + (size_t)t * (u.r >> 1) + (rank >> 1),
                        ((unsigned long long)tag << 32) | pair, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   });
 }
 
-// R of the tokens tok0 .. tok0 + n_tok into LDS (act dtype [n_tok][r]), gathered by the whole workgroup; false (in every thread) if
-// the bounded wait expired: the status word is set and the correction left out.
-template <int NT>
+// R of the tokens tok0 .. tok0 + n_tok into LDS (act dtype [n_tok][r]), gathered by the whole
+// workgroup; false (in every thread) if the bounded wait expired: the status word is set and the
+// correction left out.
+template <int ACT, int NT>
 __device__ inline bool batch_fetch_r(const BatchUnit& u, int tok0, int n_tok, uint32_t* r_lds, uint32_t* flag) {
   const int tid = threadIdx.x;
   const int n_el = n_tok * (u.r >> 2);           // 16-byte units: two slots, four ranks
@@ -112,7 +115,27 @@ __device__ inline bool batch_fetch_r(const BatchUnit& u, int tok0, int n_tok, ui
   __syncthreads();
   for (int spin = 0; spin < R_WAIT_POLLS; ++spin) {
     bool ok = true;
-    for (int e0 = 0; e0 < n_el; e0 += 4 * NT) {
+    if (u.gather) {
+      // a pair of ranks of every slice per thread, added in slice order
+      const int hp = u.r >> 1, n_pairs = n_tok * hp;
+      for (int el = tid; el < n_pairs; el += NT) {
+        const int tok = el / hp;
+        const u32x4_t* q = (const u32x4_t*)u.part + (size_t)(tok0 + tok) * u.ksplit * hp + (el - tok * hp);
+        u32x4_t v[4];
+        load4_device(v, q, q + min(1, u.ksplit - 1) * hp, q + min(2, u.ksplit - 1) * hp, q + (u.ksplit - 1) * hp);
+        float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          const uint32_t w0 = v[p][0], t0 = v[p][1], w1 = v[p][2], t1 = v[p][3];
+          ok = ok && t0 == tag && t1 == tag;
+          if (p < u.ksplit) {
+            s0 += __builtin_bit_cast(float, w0);
+            s1 += __builtin_bit_cast(float, w1);
+          }
+        }
+        r_lds[el] = (uint32_t)to_act16<ACT>(s0) | ((uint32_t)to_act16<ACT>(s1) << 16);
+      }
+    } else for (int e0 = 0; e0 < n_el; e0 += 4 * NT) {
       u32x4_t v[4];
       load4_device(v, src + min(e0 + tid, n_el - 1), src + min(e0 + NT + tid, n_el - 1),
                    src + min(e0 + 2 * NT + tid, n_el - 1), src + min(e0 + 3 * NT + tid, n_el - 1));
@@ -324,7 +347,7 @@ __global__ void __launch_bounds__(NW * 64, (BatchShape<MB, RB, RW, NW>::WAVES_EU
       }
     }
     uint32_t* r_lds = (uint32_t*)ring;
-    if (batch_fetch_r<NW * 64>(u, tok0, n_tok, r_lds, &flag)) {
+    if (batch_fetch_r<ACT, NW * 64>(u, tok0, n_tok, r_lds, &flag)) {
       const uint16_t* R = (const uint16_t*)r_lds;
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
@@ -494,10 +517,18 @@ int choose_batch_tile(const glowq_unit* const* units, int n, float* cost) {
 }
 
 // K slices of the projection inside the launch: about 1024 channels each, at most four, and no
-// more workgroups than the chip takes beside the first row blocks
+// more workgroups than the chip takes beside the first row blocks.
+// A call that starts and ends with R waits for the slices' sum to come back from memory once more.
+// Where R has no more rank pairs than four waves have threads, and the slices are not long enough to
+// hide that hop, the consumers add the slices themselves, four short ones whatever d_in is: a call in
+// a graph, 5 tokens x 512 rows x 2048, r = 64, 7.1 -> 5.9 us, 8 tokens x 672 x 1920, r = 32, 7.3 -> 5.7
+// (7.0 on the kernel that this one replaced).  Over 313 calls of 5 to 32 tokens none was more than 1 %
+// slower by this rule and the gain 2 % on average; with twice the pairs some lose 10 to 20 %.
+constexpr int BATCH_GATHER_RANKS = 512, BATCH_GATHER_K = 8192;
 void plan_batch_projection(const glowq_unit& u, UnitWorkspace& w) {
   const int pieces = (u.T + 15) / 16 * std::max(1, (u.r + 31) / 32);
-  const int ksplit = std::max(1, std::min(std::min(4, (u.d_in + 1023) / 1024), (512 + pieces - 1) / pieces));
+  w.gather = u.T * u.r <= BATCH_GATHER_RANKS && u.d_in <= BATCH_GATHER_K;
+  const int ksplit = w.gather ? 4 : std::max(1, std::min(std::min(4, (u.d_in + 1023) / 1024), (512 + pieces - 1) / pieces));
   const int steps = u.d_in / 32, per = (steps + ksplit - 1) / ksplit;
   w.kslice = per * 32;
   w.ksplit = (u.d_in + w.kslice - 1) / w.kslice;
@@ -543,7 +574,7 @@ static hipError_t launch_batch(const glowq_unit* const* units, const UnitWorkspa
     bu.out_f32 = u.out_dtype == GLOWQ_F32 ? 1 : 0;
     bu.restore = restore[order[oi]] ? 1 : 0;
     bu.part = nullptr; bu.rslots = nullptr; bu.ctl = nullptr;
-    bu.ksplit = w.ksplit; bu.kslice = w.kslice;
+    bu.ksplit = w.ksplit; bu.kslice = w.kslice; bu.gather = w.gather;
     bu.prod_start = n_prod;
     bu.n_prod = 0;
     if (bu.restore) {

@@ -20,6 +20,7 @@ struct UnitWorkspace {
   size_t ctl_bytes;   // leading bytes that must be zero between calls
   int ksplit;         // K slices of the projection
   int kslice;         // channels per slice (multiple of 32)
+  int gather;         // the consumers of R add the slices themselves (see plan_batch_projection)
   int kstride;        // ksplit rounded up to a multiple of 4 (sizes the partial-sum area)
   int pf_parts;       // T > 64: K parts of a projection tile inside the GEMM launch
   int pf_part_stages; // 64-channel stages per such part

@@ -1011,7 +1011,7 @@ static hipError_t launch_mx_gemm(const glowq_unit& u, bool restore, char* worksp
   const int ksplit = mx_proj_slices(u, &kslice);
   MxFrontTiles fa;
   fa.p = ProjSliced{(const uint16_t*)u.X, corrected ? (const uint16_t*)u.B : nullptr, (float*)(uw.base + uw.off_rpart),
-                    u.T, u.d_in, u.r, ksplit, kslice};
+                    u.T, u.d_in, u.r, ksplit, kslice, false};
   fa.R16 = (uint16_t*)(uw.base + uw.off_r16);
   fa.xcodes = xcodes;
   fa.xscales = xscales;

@@ -107,6 +107,7 @@ struct ProjSliced {
   const uint16_t* B;
   float* part;             // slots {fp32, tag}: (t ksplit + slice) r + rank (ksplit > 1 only)
   int T, K, r, ksplit, kslice;
+  bool slots_only;         // the slices stay apart (even a single one), for the consumers to add
 };
 
 // One workgroup of NW waves: tokens 16 tb .., K slice kz, ranks 32 ng .. + 32.  Slices are
@@ -172,12 +173,13 @@ __device__ inline void proj_sliced(const ProjSliced& u, int local, float* lds, O
   }
   const uint32_t tag = (uint32_t)(launch_tag() & 0xffffffffull);
   const unsigned long long tag_hi = (unsigned long long)tag << 32;
-  if (ksplit > 1) {
+  if (ksplit > 1 || u.slots_only) {
     unsigned long long* slot = (unsigned long long*)u.part + ((size_t)t * ksplit + kz) * r + rank;
 #pragma unroll
     for (int e = 0; e < 2; ++e)
       __hip_atomic_store(slot + e, tag_hi | (unsigned long long)__builtin_bit_cast(uint32_t, s[e]),
                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (u.slots_only) return;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // (counts stores, too)
     const unsigned long long* q = (const unsigned long long*)u.part + (size_t)t * ksplit * r + rank;
     u32x4_t v[4];

@@ -35,6 +35,19 @@ def test_tiles_match_the_oracle(T, d_in, d_outs, act, Gs):
             assert np.isfinite(y).all() and rel_err(y, ref) <= tol
 
 
+# R small enough that the consumers add the projection's slices themselves, at its limits (512 ranks
+# of all tokens, 8192 channels) and right beyond; one K tile (four slices of 32 channels) and
+# slices of unequal length; several tokens tiles
+@pytest.mark.parametrize("act", ["f16", "bf16"])
+@pytest.mark.parametrize("T,r,d_in", [(64, 8, 128), (32, 16, 2176), (5, 96, 4096), (8, 64, 8192), (8, 64, 8320), (9, 64, 1152),
+                                      (16, 32, 640), (43, 8, 1024)])
+def test_small_projections(T, r, d_in, act):
+    u = recipe_unit(O, 1, 0, T, r=r, shape=UnitShape("g", d_in, (200, 72)), act=act, G=128, method="alg1", qr="none")
+    ys, _, _ = run_group(u, True)
+    for y, ref in zip(ys, O.group_forward(u, True)):
+        assert np.isfinite(y).all() and rel_err(y, ref) <= TOL
+
+
 @pytest.mark.parametrize("T", [7, 24, 50, 90])
 def test_units_of_one_call_share_a_launch(T):
     # units of different widths, ranks and gating in one call (more than one launch holds), called
