@@ -55,9 +55,8 @@ struct BatchUnit {
   int T, K, r, n_modules;
   int n_blocks;                // 16-row blocks of the unit
   int n_groups, n_ttiles;      // its workgroups: groups of row blocks x tiles of 16 MB tokens
-  int restore, out_f32;
+  int restore, out_f32;        // restore 2: the consumers add the projection's slices (see plan_batch_projection)
   int ksplit, kslice;          // K slices of the projection
-  int gather;                  // the consumers add the slices themselves (see plan_batch_projection)
   int prod_start, n_prod;      // this unit's projection workgroups
   int wg_start;                // first row-block workgroup
 };
@@ -95,28 +94,48 @@ template <typename T> __device__ inline T* scalar_ptr(T* p) {
 // One projection workgroup (see proj_sliced): R as slots {two ranks, tag}.
 template <int ACT, int NW>
 __device__ inline void batch_projection(const BatchUnit& u, int local, float* lds) {
-  const ProjSliced p{u.X, u.B, u.part, u.T, u.K, u.r, u.ksplit, u.kslice, u.gather != 0};
+  const ProjSliced p{u.X, u.B, u.part, u.T, u.K, u.r, u.ksplit, u.kslice, u.restore == 2};
   proj_sliced<ACT, NW>(p, local, lds, [&](int t, int rank, uint32_t pair, uint32_t tag) {
     __hip_atomic_store((unsigned long long*)u.rslots + (size_t)t * (u.r >> 1) + (rank >> 1),
                        ((unsigned long long)tag << 32) | pair, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   });
 }
 
-// R of the tokens tok0 .. tok0 + n_tok into LDS (act dtype [n_tok][r]), gathered by the whole
-// workgroup; false (in every thread) if the bounded wait expired: the status word is set and the
-// correction left out.
-template <int ACT, int NT>
-__device__ inline bool batch_fetch_r(const BatchUnit& u, int tok0, int n_tok, uint32_t* r_lds, uint32_t* flag) {
+// look(): one look of the whole workgroup at R, true where all that this thread saw was of this
+// launch; repeated until that holds for every thread.  False (in every thread) if the bounded wait
+// expired: the status word is set and the correction left out.
+template <class LOOK> __device__ inline bool batch_poll_r(const BatchUnit& u, uint32_t* flag, LOOK look) {
   const int tid = threadIdx.x;
-  const int n_el = n_tok * (u.r >> 2);           // 16-byte units: two slots, four ranks
-  const uint32_t tag = (uint32_t)(launch_tag() & 0xffffffffull);
-  const u32x4_t* src = (const u32x4_t*)u.rslots + (size_t)tok0 * (u.r >> 2);
   if (tid == 0) *flag = 0u;
   __syncthreads();
   for (int spin = 0; spin < R_WAIT_POLLS; ++spin) {
-    bool ok = true;
-    if (u.gather) {
+    if (!look()) *flag = 1u;
+    __syncthreads();
+    const bool failed = *flag != 0u;
+    if (!failed) return true;
+    __syncthreads();
+    if (tid == 0) *flag = 0u;
+    // (short pauses at first: in the smallest calls R comes while the consumers already look for it,
+    // and a pause of a microsecond between two looks cost half of one: 7.1 -> 6.4 us)
+    if (spin < BATCH_QUICK_POLLS) __builtin_amdgcn_s_sleep(1);
+    else __builtin_amdgcn_s_sleep(32);
+    __syncthreads();
+  }
+  if (tid == 0) atomicOr(&u.ctl->status, 1u);
+  return false;
+}
+
+// R of the tokens tok0 .. tok0 + n_tok into LDS (act dtype [n_tok][r]), gathered by the whole
+// workgroup.  Two loops, so that the descriptor's words that only one of them needs are not loaded
+// on the other's way (0.1 us of every call).
+template <int ACT, int NT>
+__device__ inline bool batch_fetch_r(const BatchUnit& u, bool gather, int tok0, int n_tok, uint32_t* r_lds, uint32_t* flag) {
+  const int tid = threadIdx.x;
+  const uint32_t tag = (uint32_t)(launch_tag() & 0xffffffffull);
+  if (gather)
+    return batch_poll_r(u, flag, [&] {
       // a pair of ranks of every slice per thread, added in slice order
+      bool ok = true;
       const int hp = u.r >> 1, n_pairs = n_tok * hp;
       for (int el = tid; el < n_pairs; el += NT) {
         const int tok = el / hp;
@@ -135,7 +154,13 @@ __device__ inline bool batch_fetch_r(const BatchUnit& u, int tok0, int n_tok, ui
         }
         r_lds[el] = (uint32_t)to_act16<ACT>(s0) | ((uint32_t)to_act16<ACT>(s1) << 16);
       }
-    } else for (int e0 = 0; e0 < n_el; e0 += 4 * NT) {
+      return ok;
+    });
+  const int n_el = n_tok * (u.r >> 2);           // 16-byte units: two slots, four ranks
+  const u32x4_t* src = (const u32x4_t*)u.rslots + (size_t)tok0 * (u.r >> 2);
+  return batch_poll_r(u, flag, [&] {
+    bool ok = true;
+    for (int e0 = 0; e0 < n_el; e0 += 4 * NT) {
       u32x4_t v[4];
       load4_device(v, src + min(e0 + tid, n_el - 1), src + min(e0 + NT + tid, n_el - 1),
                    src + min(e0 + 2 * NT + tid, n_el - 1), src + min(e0 + 3 * NT + tid, n_el - 1));
@@ -150,20 +175,8 @@ __device__ inline bool batch_fetch_r(const BatchUnit& u, int tok0, int n_tok, ui
         }
       }
     }
-    if (!ok) *flag = 1u;
-    __syncthreads();
-    const bool failed = *flag != 0u;
-    if (!failed) return true;
-    __syncthreads();
-    if (tid == 0) *flag = 0u;
-    // (short pauses at first: in the smallest calls R comes while the consumers already look for it,
-    // and a pause of a microsecond between two looks cost half of one: 7.1 -> 6.4 us)
-    if (spin < BATCH_QUICK_POLLS) __builtin_amdgcn_s_sleep(1);
-    else __builtin_amdgcn_s_sleep(32);
-    __syncthreads();
-  }
-  if (tid == 0) atomicOr(&u.ctl->status, 1u);
-  return false;
+    return ok;
+  });
 }
 
 // bfloat16 weights of one word in 17 instructions (see DequantLockstep<ACT_BF16>)
@@ -331,7 +344,8 @@ __global__ void __launch_bounds__(NW * 64, (BatchShape<MB, RB, RW, NW>::WAVES_EU
   // nothing may be on its way into LDS any more, and everybody is done reading it
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
-  if (u.restore) {                               // uniform; r > 0
+  const int restore = u.restore;
+  if (restore) {                                 // uniform; r > 0
     const int r = u.r, n_tok = min(T - tok0, 16 * MB);
     u32x4_t af[RB][4];
 #pragma unroll
@@ -347,7 +361,7 @@ __global__ void __launch_bounds__(NW * 64, (BatchShape<MB, RB, RW, NW>::WAVES_EU
       }
     }
     uint32_t* r_lds = (uint32_t*)ring;
-    if (batch_fetch_r<ACT, NW * 64>(u, tok0, n_tok, r_lds, &flag)) {
+    if (batch_fetch_r<ACT, NW * 64>(u, restore == 2, tok0, n_tok, r_lds, &flag)) {
       const uint16_t* R = (const uint16_t*)r_lds;
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
@@ -572,9 +586,9 @@ static hipError_t launch_batch(const glowq_unit* const* units, const UnitWorkspa
     bu.T = u.T; bu.K = u.d_in; bu.r = u.r; bu.n_modules = u.n_modules;
     bu.n_blocks = blk;
     bu.out_f32 = u.out_dtype == GLOWQ_F32 ? 1 : 0;
-    bu.restore = restore[order[oi]] ? 1 : 0;
+    bu.restore = restore[order[oi]] ? 1 + w.gather : 0;
     bu.part = nullptr; bu.rslots = nullptr; bu.ctl = nullptr;
-    bu.ksplit = w.ksplit; bu.kslice = w.kslice; bu.gather = w.gather;
+    bu.ksplit = w.ksplit; bu.kslice = w.kslice;
     bu.prod_start = n_prod;
     bu.n_prod = 0;
     if (bu.restore) {

@@ -107,7 +107,7 @@ struct ProjSliced {
   const uint16_t* B;
   float* part;             // slots {fp32, tag}: (t ksplit + slice) r + rank (ksplit > 1 only)
   int T, K, r, ksplit, kslice;
-  bool slots_only;         // the slices stay apart (even a single one), for the consumers to add
+  bool slots_only;         // the slices (two at least) stay apart, for the consumers to add
 };
 
 // One workgroup of NW waves: tokens 16 tb .., K slice kz, ranks 32 ng .. + 32.  Slices are
@@ -173,7 +173,7 @@ __device__ inline void proj_sliced(const ProjSliced& u, int local, float* lds, O
   }
   const uint32_t tag = (uint32_t)(launch_tag() & 0xffffffffull);
   const unsigned long long tag_hi = (unsigned long long)tag << 32;
-  if (ksplit > 1 || u.slots_only) {
+  if (ksplit > 1) {
     unsigned long long* slot = (unsigned long long*)u.part + ((size_t)t * ksplit + kz) * r + rank;
 #pragma unroll
     for (int e = 0; e < 2; ++e)
