@@ -182,10 +182,9 @@ static LaunchChoice choose_launch(const glowq_unit* units, int n_units, bool sla
   const bool half = choose_prefill_tile(batch, c.n, &cost);
   // Few or small tiles leave the tiled kernel's workgroups alone on their compute units with the
   // whole contraction each; there the smaller tiles of the batched kernel are faster.
-  // (a clear advantage: both estimates are good to about 10 %)
   float small_cost = 0.f;
   const int tile = small ? choose_batch_tile(batch, c.n, &small_cost) : 0;
-  if (small && small_cost < 0.85f * cost) {
+  if (small && small_cost < 0.95f * cost) {
     c.kernel = GLOWQ_ROUTE_BATCHED;
     c.tile = tile;
     return c;

@@ -455,23 +455,35 @@ int batch_max_units() { return BATCH_MAX_UNITS; }
 int batch_wait_polls() { return R_WAIT_POLLS; }
 
 // Workgroup tiles: 16 mb tokens x 16 rb rw rows, nw / rw groups of waves sharing the contraction.
-// What a tile costs was measured over 70 shapes (5 to 1001 tokens, 144 to 48000 rows, 256 to 13696
-// channels, calls of one unit and of whole layers) with every tile, in us per K tile of a wave
-// group: `chain`, when the compute unit has nothing else to do, and `busy`, each workgroup's
-// share of a compute unit that is full.  A launch then takes the longer of its longest
-// contraction and its share of the chip; picking the cheapest tile by that was within 2 % of
-// the best one on average, 19 % at worst.  `start`: eight waves begin and meet later than four.
-// (Kernel times of 70 calls of 5 to 64 tokens on every tile: two K tiles of 3 x 256 rows at 16 tokens
-// 5.6 us on four waves, 6.4 on eight; with the term the choice was 1.8 % above the best on average,
-// without it 2.3 %.)
+// What a tile costs, in us per K tile of a wave group: `chain`, when the compute unit has nothing
+// else to do, and `busy`, each workgroup's share of a compute unit that is full (binary16,
+// bfloat16).  A launch takes the longer of its longest contraction and its share of the chip; a
+// workgroup's start, fold, correction and stores weigh `ends` K tiles, and past what the chip holds
+// at once the last round is partly empty.
+// Measured as calls in a graph over 1250 calls of 5 to 2048 tokens (one unit to two layers, 256 to
+// 14336 channels), each on every tile, beyond 64 tokens also on the tiled kernel, and the constants
+// fitted to the choice: it is 1.5 % above the best on average up to 64 tokens and 2.1 % beyond (1.6 %
+// and 0.7 % in 380 and 70 other calls); with constants of 70 calls and no `ends` it was 4.6 % and 5.6 %.
+// The last two tiles are for 5 to 16 tokens on some thousand rows and a long contraction, where one
+// row block per wave leaves a compute unit with one workgroup and a half, and four waves side by side
+// leave most compute units empty: 5 tokens x 6456 rows x 8448 17.8 -> 13.4 us, 5 x 3 x 3320 x 12928
+// 36.0 -> 25.9 (three row blocks).  A ring deeper than three stages was slower for both (1.07 and
+// 1.29 times the time: one workgroup per compute unit).
 struct BatchTile {
   int mb, rb, rw, nw;
-  float start, chain, busy_f16, busy_bf16;
+  float start, ends;
+  float chain[2], busy[2];
 };
 constexpr BatchTile BATCH_TILES[] = {
-    {1, 1, 1, 4, 0.0f, 0.45f, 0.65f, 0.69f}, {1, 1, 4, 4, 0.0f, 0.25f, 0.19f, 0.24f}, {1, 1, 4, 8, 0.4f, 0.25f, 0.38f, 0.51f},
-    {2, 1, 4, 4, 0.0f, 0.30f, 0.30f, 0.32f}, {2, 1, 4, 8, 0.4f, 0.45f, 0.63f, 0.73f}, {4, 1, 4, 4, 0.0f, 0.42f, 0.53f, 0.59f},
-    {4, 2, 4, 4, 0.0f, 0.75f, 0.73f, 0.84f},
+    {1, 1, 1, 4, 0.00f, 3.61f, {0.25f, 0.48f}, {0.43f, 0.34f}},
+    {1, 1, 4, 4, 0.90f, 2.80f, {0.27f, 0.27f}, {0.17f, 0.17f}},
+    {1, 1, 4, 8, 0.09f, 4.71f, {0.41f, 0.43f}, {0.29f, 0.29f}},
+    {2, 1, 4, 4, 0.21f, 5.56f, {0.32f, 0.28f}, {0.22f, 0.22f}},
+    {2, 1, 4, 8, 1.04f, 4.15f, {0.53f, 1.39f}, {0.41f, 0.60f}},
+    {4, 1, 4, 4, 1.33f, 6.54f, {0.38f, 0.36f}, {0.38f, 0.41f}},
+    {4, 2, 4, 4, 0.26f, 6.01f, {0.53f, 0.65f}, {0.52f, 0.58f}},
+    {1, 2, 1, 4, 0.73f, 3.63f, {0.52f, 0.59f}, {0.54f, 0.40f}},
+    {1, 3, 1, 4, 0.25f, 6.50f, {0.74f, 0.74f}, {0.75f, 0.78f}},
 };
 constexpr int BATCH_N_TILES = sizeof(BATCH_TILES) / sizeof(BATCH_TILES[0]);
 
@@ -481,7 +493,7 @@ template <int I> constexpr int batch_tile_resident() {
 }
 constexpr int BATCH_RESIDENT[] = {batch_tile_resident<0>(), batch_tile_resident<1>(), batch_tile_resident<2>(),
                                   batch_tile_resident<3>(), batch_tile_resident<4>(), batch_tile_resident<5>(),
-                                  batch_tile_resident<6>()};
+                                  batch_tile_resident<6>(), batch_tile_resident<7>(), batch_tile_resident<8>()};
 static_assert(sizeof(BATCH_RESIDENT) / sizeof(int) == BATCH_N_TILES, "one entry per tile");
 
 // What the tiles from I on cost for units of `blocks` row blocks, `kt` K tiles and T tokens (a tile
@@ -504,9 +516,9 @@ static inline void cheapest_batch_tile(const BatchSize* u, int n, bool f16, int 
       work += w * stages;
       chain = std::max(chain, stages);
     }
-    const float busy = f16 ? t.busy_f16 : t.busy_bf16;
-    const float per_cu = wgs <= 256 * BATCH_RESIDENT[I] ? (float)((wgs + 255) / 256) : (float)wgs / 256.f;
-    const float c = t.start + std::max((float)chain * t.chain, (float)work / (float)wgs * per_cu * busy);
+    const float alone = t.chain[f16 ? 0 : 1], busy = t.busy[f16 ? 0 : 1];
+    const float share = wgs <= 256 * BATCH_RESIDENT[I] ? (float)((wgs + 255) / 256) * busy : (float)wgs / 256.f * busy + 0.8f * alone;
+    const float c = t.start + std::max(((float)chain + t.ends) * alone, ((float)work / (float)wgs + t.ends) * share);
     if (*best < 0 || c < *cost) {
       *best = I;
       *cost = c;

@@ -782,21 +782,23 @@ static inline int prefill_tile_blocks(int act_dtype, bool half) {
 }
 
 // What one launch over these units is taken to cost, in the same terms as the batched kernel's
-// tiles (us beyond a launch of that one).  Measured over 25 calls of 68 to 2048 tokens, in us per
-// K tile: for a workgroup alone on its compute unit, for two sharing one (the vector ALU and
-// the matrix pipe take turns, so a second workgroup adds little, and the clock falls), and per
-// workgroup when several rounds keep all compute units busy.  The half-size tiles took
-// 502 tokens x 2 x 6240 rows x 6784 from 124 to 101 us and 1032 x 3 x 760 x 3840 from 48 to 39 us;
-// on a long prompt that fills the chip they are 4 to 13 % slower.
+// tiles (BATCH_TILES), in us per K tile: for a workgroup alone on its compute unit, for two sharing
+// one (the vector ALU and the matrix pipe take turns, so a second workgroup adds little, and the
+// clock falls; `few`: what is left of that when only few do), and per workgroup when several rounds
+// keep all compute units busy.  A workgroup's start, correction and stores weigh `ends` K tiles; a
+// sliced unit's second launch costs `sum` us.
+// From 850 of the calls that are described there, on both tile sizes.  The half-size tiles took
+// 502 tokens x 2 x 6240 rows x 6784 from 124 to 101 us and 1032 x 3 x 760 x 3840 from 48 to 39 us; on a
+// long prompt that fills the chip they are 4 to 13 % slower.
 struct PrefillCost {
-  float start, alone, pair, busy;
+  float start, ends, alone, pair, few, busy, sum;
 };
 static float prefill_cost_of(const glowq_unit* const* units, int n, bool half) {
   const bool f16 = units[0]->act_dtype == GLOWQ_F16;
-  const PrefillCost c = half ? (f16 ? PrefillCost{1.1f, 1.05f, 2.54f, 1.05f} : PrefillCost{0.4f, 1.21f, 2.47f, 1.05f})
-                             : (f16 ? PrefillCost{3.0f, 1.56f, 3.93f, 1.75f} : PrefillCost{1.4f, 1.53f, 3.16f, 1.5f});
+  const PrefillCost c = half ? (f16 ? PrefillCost{3.48f, 2.50f, 1.09f, 1.45f, 0.79f, 0.88f, 10.9f} : PrefillCost{0.04f, 5.01f, 1.17f, 2.07f, 0.94f, 5.33f, 10.9f})
+                             : (f16 ? PrefillCost{1.78f, 4.88f, 1.43f, 3.42f, 0.73f, 0.34f, 0.5f} : PrefillCost{5.46f, 5.94f, 1.59f, 2.87f, 0.82f, 1.08f, 0.5f});
   double work = 0.0, wgs = 0.0;
-  int chain = 0;
+  int chain = 0, sliced = 0;
   for (int k = 0; k < n; ++k) {
     const glowq_unit& u = *units[k];
     const int tile_blocks = prefill_tile_blocks(u.act_dtype, half);
@@ -807,18 +809,21 @@ static float prefill_cost_of(const glowq_unit* const* units, int n, bool half) {
     // (the projection's workgroups, about 2048 channels each, hold their places beside the tiles)
     const double proj = u.r > 0 ? (double)((u.T + 127) / 128) * std::min(8, (u.d_in + 2047) / 2048) : 0.0;
     wgs += tiles + proj;
-    work += tiles * kt + proj * std::min(kt, 8);
+    work += tiles * (kt + c.ends) + proj * std::min(kt, 8);
     chain = std::max(chain, kt);
+    sliced += S > 1 ? 1 : 0;
   }
   const double per_cu = wgs / 256.0;
   // (beyond two per compute unit the last round is partly empty)
-  const double share = per_cu <= 1.0 ? c.alone : per_cu <= 2.0 ? c.pair : std::max((double)c.pair, c.busy * per_cu + 0.8 * c.alone);
-  return (float)(c.start + std::max((double)chain * c.alone, work / wgs * share));
+  const double share = per_cu <= 1.0   ? c.alone
+                       : per_cu <= 2.0 ? c.pair * (c.few + (1.0 - c.few) * (per_cu - 1.0))
+                                       : std::max((double)c.pair, c.busy * per_cu + 0.8 * c.alone);
+  return (float)(c.start + sliced * c.sum + std::max((chain + c.ends) * (double)c.alone, work / wgs * share));
 }
 bool choose_prefill_tile(const glowq_unit* const* units, int n, float* cost) {
   const float full = prefill_cost_of(units, n, false), half = prefill_cost_of(units, n, true);
   *cost = std::min(full, half);
-  return half < 0.9f * full;            // (a clear advantage: the estimates are good to about 10 %)
+  return half < 0.95f * full;
 }
 
 void plan_prefill_slices(const glowq_unit* const* units, int n, bool slabs, int* slices) {

@@ -69,6 +69,48 @@ def test_the_smallest_calls_start_four_waves():
             assert route(T, d_in, d_outs, Gs=Gs, act=act).tile not in (2, 4), (T, d_in, d_outs)
 
 
+# Calls that cost rules of fewer constants sent to slower tiles than they had run on before those
+# rules (us).  Routes that are not slower: B<n> batched tile n, L / H the tiled kernel's large / half-size tiles
+NOT_SLOWER = [
+    (672, 256, (2512,) * 3, "f16", "act", 128, 128, "L H"),      # 11.2 before, 17.6 then
+    (326, 256, (3736,) * 3, "bf16", "act", 16, 64, "L H"),      # 10.1 before, 15.4 then
+    (456, 640, (2944,) * 3, "f16", "act", 72, 128, "L H"),      # 16.6 before, 21.2 then
+    (7, 1920, (6288,), "f16", "f32", 64, 128, "B7"),      # 7.1 before, 9.1 then
+    (6, 1408, (8456,), "f16", "f32", 32, 128, "B2"),      # 6.6 before, 8.4 then
+    (9, 1408, (4632,), "f16", "f32", 16, 128, "B2 B7"),      # 6.6 before, 8.4 then
+    (8, 1152, (1096,) * 3, "f16", "act", 16, 128, "B0 B2 B7"),      # 6.3 before, 7.8 then
+    (891, 512, (5344,), "f16", "f32", 64, 64, "L H"),      # 19.3 before, 23.8 then
+    (871, 640, (4632,), "f16", "f32", 64, 128, "L H"),      # 19.5 before, 24.0 then
+    (24, 10112, (4960,) * 2, "f16", "act", 16, 64, "B4"),      # 24.2 before, 29.3 then
+    (427, 9728, (4032,) * 2, "f16", "f32", 16, 128, "B6 L"),      # 98.9 before, 118.9 then
+    (830, 768, (5856,), "f16", "f32", 72, 128, "H"),      # 19.3 before, 23.2 then
+    (7, 1536, (1224,), "f16", "act", 32, 64, "B0 B2 B7"),      # 6.9 before, 8.1 then
+    (26, 12672, (5008,) * 2, "f16", "act", 64, 64, "B4"),      # 31.0 before, 36.4 then
+    (971, 2304, (2656,) * 3, "f16", "act", 72, 128, "L"),      # 61.1 before, 70.8 then
+    (10, 1408, (4160,) * 2, "bf16", "act", 64, 64, "B1 B2 B8"),      # 7.9 before, 9.0 then
+    (10, 4224, (8608,), "bf16", "act", 32, 128, "B2 B8"),      # 12.6 before, 14.4 then
+    (263, 1280, (8912,) * 3, "f16", "act", 128, 128, "L"),      # 43.8 before, 49.9 then
+    (5, 1280, (3088,) * 3, "bf16", "act", 64, 128, "B1 B2 B3 B4 B8"),      # 7.5 before, 8.4 then
+    (14, 6272, (5320,), "f16", "f32", 64, 128, "B7"),      # 12.6 before, 14.2 then
+    (34, 512, (13072,) * 3, "f16", "act", 72, 128, "B6"),      # 12.6 before, 14.1 then
+    (7, 3456, (1976,) * 3, "f16", "act", 64, 128, "B7"),      # 8.8 before, 9.8 then
+    (16, 256, (344,) * 2, "f16", "f32", 32, 64, "B0 B1 B2 B3 B4 B7 B8"),      # 7.3 before, 8.1 then
+    (13, 1152, (4368,), "bf16", "act", 64, 128, "B1 B2 B3 B4 B7 B8"),      # 7.6 before, 8.4 then
+    (1357, 14336, (1768,) * 3, "f16", "f32", 16, 128, "L"),      # 219.6 before, 241.9 then
+    (10, 3712, (7616,), "bf16", "f32", 72, 64, "B0 B2 B7 B8"),      # 12.4 before, 13.6 then
+    (9, 3584, (4696,), "f16", "act", 64, 128, "B7"),      # 7.7 before, 8.4 then
+    (7, 1408, (568,) * 3, "bf16", "f32", 64, 64, "B0 B2 B7"),      # 7.4 before, 8.0 then
+]
+
+
+@pytest.mark.parametrize("T,d_in,d_outs,act,out,r,Gs,good", NOT_SLOWER)
+def test_calls_keep_their_speed(T, d_in, d_outs, act, out, r, Gs, good):
+    a = {"f16": G.GLOWQ_F16, "bf16": G.GLOWQ_BF16}[act]
+    got = route(T, d_in, d_outs, r=r, Gs=Gs, act=a, out=a if out == "act" else G.GLOWQ_F32)
+    name = "LH"[got.tile] if got.kernel == G.GLOWQ_ROUTE_TILED else f"B{got.tile}"
+    assert name in good.split()
+
+
 def test_argument_checks():
     for units, status in [([unit(0, 256, (64,))], G.GLOWQ_ERR_SHAPE), ([unit(4, 192, (64,))], G.GLOWQ_ERR_SHAPE),
                           ([unit(4, 320, (64,), Gs=64)], G.GLOWQ_ERR_UNSUPPORTED)]:
