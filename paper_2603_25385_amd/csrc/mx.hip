@@ -950,16 +950,22 @@ MxWorkspace plan_mx_workspace(const glowq_unit& u) {
   return w;
 }
 
-// Workgroup tiles and what they were measured to cost (us per K tile of a wave group: `chain` alone,
-// `busy` as a workgroup's share of a full compute unit; 50 shapes of 17 to 1884 tokens).  Tile 0 is
-// k_mx_gemm's.  A launch takes the longer of the two for each K tile of its contraction.
+// Workgroup tiles and what they were measured to cost: us per K tile of a wave group, `chain` alone
+// and `busy` as a workgroup's share of a full compute unit; a workgroup's start, correction and
+// stores weigh `ends` K tiles, `ends32` more where 32-bit outputs are stored.  A launch takes the longer
+// of the two for each K tile of its contraction; past what the chip holds at once the last round is
+// partly empty.  Tile 0 is k_mx_gemm's and stays where no other one is clearly cheaper.
+// Fitted to 310 calls of 17 to 2048 tokens on every tile: the choice is 1.1 % above the best tile on
+// average and one call is slower than on tile 0 by more than 1.5 % (4 %); with one `ends` for all
+// tiles, from 50 calls, it was 4.2 % above, and 8 calls of 220 were slower by up to 28 % (1931 tokens x
+// 3 x 8680 rows x 896, 32-bit outputs: 99.8 us on tile 0, 128.1 on tile 4).
 struct MxTile {
   int mb, rb, rw, nw;
-  float chain, busy;
+  float chain, busy, ends, ends32;
 };
-constexpr MxTile MX_TILES[] = {{8, 4, 2, 4, 0.57f, 0.49f}, {1, 1, 4, 4, 0.17f, 0.075f}, {2, 1, 4, 8, 0.30f, 0.173f},
-                               {2, 2, 4, 4, 0.235f, 0.18f}, {4, 2, 4, 4, 0.35f, 0.25f}};
-constexpr double MX_ENDS = 8.7;      // K tiles that a workgroup's start, correction and stores weigh
+constexpr MxTile MX_TILES[] = {{8, 4, 2, 4, 0.52f, 0.33f, 13.0f, 1.0f}, {1, 1, 4, 4, 0.10f, 0.08f, 6.0f, 1.5f},
+                               {2, 1, 4, 8, 0.21f, 0.21f, 5.0f, 1.5f},  {2, 2, 4, 4, 0.15f, 0.17f, 6.0f, 2.0f},
+                               {4, 2, 4, 4, 0.27f, 0.23f, 9.0f, 2.0f}};
 constexpr int MX_N_TILES = sizeof(MX_TILES) / sizeof(MX_TILES[0]);
 constexpr int MX_RESIDENT[] = {3, MxTileShape<1, 1, 4, 4>::WGS, MxTileShape<2, 1, 4, 8>::WGS, MxTileShape<2, 2, 4, 4>::WGS,
                                MxTileShape<4, 2, 4, 4>::WGS};
@@ -972,13 +978,13 @@ static int choose_mx_tile(const glowq_unit& u) {
     const int ks = i == 0 ? 1 : t.nw / t.rw, tok = 16 * t.mb, rows = 16 * t.rb * t.rw;
     double wgs = 0.0;
     for (int m = 0; m < u.n_modules; ++m) wgs += (double)((u.modules[m].d_out + rows - 1) / rows) * ((u.T + tok - 1) / tok);
-    double per_cu = wgs / 256.0;
-    if (per_cu <= MX_RESIDENT[i]) per_cu = std::ceil(per_cu);
-    const double stages = (u.d_in / 128 + ks - 1) / ks;
-    const double c = (stages + MX_ENDS) * std::max((double)t.chain, per_cu * t.busy);
+    const double per_cu = wgs / 256.0;
+    const double share = per_cu <= MX_RESIDENT[i] ? std::ceil(per_cu) * t.busy : per_cu * t.busy + 0.8 * t.chain;
+    const double stages = (u.d_in / 128 + ks - 1) / ks + t.ends + (u.out_dtype == GLOWQ_F32 ? t.ends32 : 0.0);
+    const double c = stages * std::max((double)t.chain, share);
     if (i == 0 || c < cost) {
       best = i;
-      cost = c;
+      cost = i == 0 ? 0.9 * c : c;
     }
   }
   return best;

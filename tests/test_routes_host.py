@@ -111,6 +111,21 @@ def test_calls_keep_their_speed(T, d_in, d_outs, act, out, r, Gs, good):
     assert name in good.split()
 
 
+# calls of the microscaling variant that were slower on small tiles (us on tiles 0 .. 4)
+@pytest.mark.parametrize("T,d_in,d_outs,act,out", [
+    (1931, 896, (8680,) * 3, "f16", "f32"),          # 99.8 .. 128.1 on tile 4
+    (1938, 512, (12712,) * 3, "bf16", "act"),        # 121.6, 323.3, 320.6, 171.8, 155.7
+    (1018, 7424, (10352,), "bf16", "f32"),           # 86.2, 203.8, 147.1, 112.5, 95.6
+    (1364, 12288, (4600,), "bf16", "act"),           # 113.8, 249.6, 232.0, 158.9, 126.7
+    (1155, 3200, (5624,) * 3, "bf16", "act"),        # 114.3, 256.6, 216.1, 145.9, 126.0
+    (522, 8320, (2752,) * 3, "bf16", "f32"),         # 75.0, 141.1, 106.8, 90.7, 86.2
+    (1182, 9216, (2176, 2176), "bf16", "act")])      # 79.2, 153.7, 139.0, 96.1, 85.5
+def test_microscaling_keeps_large_tiles_where_they_are_faster(T, d_in, d_outs, act, out):
+    a = {"f16": G.GLOWQ_F16, "bf16": G.GLOWQ_BF16}[act]
+    u = unit(T, d_in, d_outs, r=64, act=a, out=a if out == "act" else G.GLOWQ_F32)
+    assert G.glowq_debug_mx_route(u).tile == 0
+
+
 def test_argument_checks():
     for units, status in [([unit(0, 256, (64,))], G.GLOWQ_ERR_SHAPE), ([unit(4, 192, (64,))], G.GLOWQ_ERR_SHAPE),
                           ([unit(4, 320, (64,), Gs=64)], G.GLOWQ_ERR_UNSUPPORTED)]:
