@@ -136,9 +136,9 @@ glowq_status glowq_prepare_weights(const uint32_t* wq, const uint16_t* scales,
  * projection, a few control and flag words).  glowq_workspace_init clears it; it must
  * be called once before the first forward call that uses the buffer.  After that one
  * buffer can serve any number of consecutive calls on one stream, eager or replayed
- * from a captured graph: a launch recognises its own projection by a tag that is
- * unique per kernel launch, so nothing in the buffer ever has to be reset.  Calls
- * that may overlap in time need separate workspaces.
+ * from a captured graph, over the same units or others: a launch recognises its own
+ * projection by a tag that is unique per kernel launch, so nothing in the buffer ever has
+ * to be reset.  Calls that may overlap in time need separate workspaces.
  *
  * A call of more than 64 tokens runs on large tiles, or on the small ones of the batched kernel
  * where its tiles would leave the chip idle.  On large tiles a unit whose contraction is long (d_in >= 8192) on few tiles
@@ -159,7 +159,9 @@ glowq_status glowq_prepare_weights(const uint32_t* wq, const uint16_t* scales,
  * equals that of a unit that is not restored).  The producers of R lead their launch
  * and wait for nothing, so this happens only if workgroups of a launch are kept from
  * running; the bound is there so that nothing can ever hang.  Status words stay set
- * until glowq_workspace_init.  glowq_workspace_status counts them:
+ * until glowq_workspace_init (a buffer that serves lists of units of different sizes has
+ * the slices in other places from call to call, and only the first one's word keeps its
+ * meaning).  glowq_workspace_status counts them:
  * it enqueues one small kernel that writes to *failed_units (DEVICE, 4-byte aligned)
  * the number of the `n_units` units whose status word is nonzero; it allocates
  * nothing and does not synchronise (read the word after the stream has run). */

@@ -50,6 +50,7 @@ struct PfUnit {
   float* Rpart;            // fp32 [parts][T][r]: the K parts' partial sums (parts > 1 only)
   uint32_t* flags;         // one word per 16-token block; word MB*mt is token tile mt's ready
                            // flag, word MB*mt + 1 counts the K parts of that tile that are done
+                           // (both carry the launch's tag)
   int parts;               // K parts of a projection tile (one workgroup each)
   int part_stages;         // 64-channel stages per part
   uint32_t* status;        // the unit's status word (see Control)
@@ -100,7 +101,9 @@ template <typename T> __device__ inline T* uniform_ptr(T* p) {
 // that R is ready well before the main tiles of the same unit reach their correction:
 // every part leaves its fp32 partial tile in the workspace and counts itself in; the
 // part that finds all others counted adds the partial tiles in part order (so the sum
-// does not depend on which one that is), rounds, stores and sets the flag.
+// does not depend on which one that is), rounds, stores and sets the flag.  The count carries
+// the launch's tag: what a call over other units left in the word (their layout may have
+// partial sums there) counts as zero.
 // X takes the same path as in the main tiles (LDS ring, swizzled rows); the rows of B
 // are read straight into operand registers, one stage ahead.
 template <int ACT, int MB>
@@ -228,9 +231,15 @@ __device__ inline void proj_tile(const PrefillArgs& a, uint16_t* xs) {
     __threadfence();
     __syncthreads();
     uint32_t* lds_word = (uint32_t*)xs;      // the X ring is idle from here on
-    if (tid == 0)
-      *lds_word = __hip_atomic_fetch_add(U.flags + MB * mt + 1, 1u, __ATOMIC_ACQ_REL,
-                                         __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) {
+      uint32_t* word = U.flags + MB * mt + 1;      // {28 bits of the tag, parts that are done}
+      const uint32_t key = (uint32_t)(launch_tag() >> 1) << 4;
+      uint32_t seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), done;
+      do done = (seen & ~15u) == key ? seen & 15u : 0u;      // (at most `parts` rounds: a failure is another part's success)
+      while (!__hip_atomic_compare_exchange_strong(word, &seen, key | (done + 1u), __ATOMIC_ACQ_REL, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT));
+      *lds_word = done;
+    }
     __syncthreads();
     const uint32_t arrived = *lds_word;
     if (arrived + 1 != (uint32_t)U.parts) return;   // uniform
@@ -254,7 +263,7 @@ __device__ inline void proj_tile(const PrefillArgs& a, uint16_t* xs) {
         acc[b][mb] = sum;
       }
     }
-    if (tid == 0)   // the next launch counts from zero again
+    if (tid == 0)   // (idle words are zero)
       __hip_atomic_store(U.flags + MB * mt + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 #pragma unroll
