@@ -179,7 +179,8 @@ static LaunchChoice choose_launch(const glowq_unit* units, int n_units, bool sla
     batch[c.n] = &units[c.n];
     ++c.n;
   }
-  const bool half = choose_prefill_tile(batch, c.n, &cost);
+  plan_prefill_slices(batch, c.n, slabs, c.slices);
+  const bool half = choose_prefill_tile(batch, c.slices, c.n, &cost);
   // Few or small tiles leave the tiled kernel's workgroups alone on their compute units with the
   // whole contraction each; there the smaller tiles of the batched kernel are faster.
   float small_cost = 0.f;
@@ -187,11 +188,11 @@ static LaunchChoice choose_launch(const glowq_unit* units, int n_units, bool sla
   if (small && small_cost < 0.95f * cost) {
     c.kernel = GLOWQ_ROUTE_BATCHED;
     c.tile = tile;
+    for (int& s : c.slices) s = 1;
     return c;
   }
   c.kernel = GLOWQ_ROUTE_TILED;
   c.tile = half ? 1 : 0;
-  plan_prefill_slices(batch, c.n, slabs, c.slices);
   return c;
 }
 

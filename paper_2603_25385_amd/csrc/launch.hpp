@@ -116,8 +116,8 @@ int prefill_max_modules();
 // K slices of every unit of a launch: where the unit's shapes ask for them, the workspace has the
 // slabs (`slabs`) and the module table has room
 void plan_prefill_slices(const glowq_unit* const* units, int n, bool slabs, int* slices);
-// whether the launch takes the half-size tiles, and what it is taken to cost
-bool choose_prefill_tile(const glowq_unit* const* units, int n, float* cost);
+// whether the launch, cut into these slices, takes the half-size tiles, and what it is taken to cost
+bool choose_prefill_tile(const glowq_unit* const* units, const int* slices, int n, float* cost);
 int prefill_wait_polls();
 hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorkspace* ws,
                                 const bool* restore, int n_units, bool half, const int* slices, hipStream_t st);

@@ -802,7 +802,7 @@ static inline int prefill_tile_blocks(int act_dtype, bool half) {
 struct PrefillCost {
   float start, ends, alone, pair, few, busy, sum;
 };
-static float prefill_cost_of(const glowq_unit* const* units, int n, bool half) {
+static float prefill_cost_of(const glowq_unit* const* units, const int* slices, int n, bool half) {
   const bool f16 = units[0]->act_dtype == GLOWQ_F16;
   const PrefillCost c = half ? (f16 ? PrefillCost{3.48f, 2.50f, 1.09f, 1.45f, 0.79f, 0.88f, 10.9f} : PrefillCost{0.04f, 5.01f, 1.17f, 2.07f, 0.94f, 5.33f, 10.9f})
                              : (f16 ? PrefillCost{1.78f, 4.88f, 1.43f, 3.42f, 0.73f, 0.34f, 0.5f} : PrefillCost{5.46f, 5.94f, 1.59f, 2.87f, 0.82f, 1.08f, 0.5f});
@@ -811,11 +811,13 @@ static float prefill_cost_of(const glowq_unit* const* units, int n, bool half) {
   for (int k = 0; k < n; ++k) {
     const glowq_unit& u = *units[k];
     const int tile_blocks = prefill_tile_blocks(u.act_dtype, half);
-    const int S = prefill_k_slices(u), kt = (u.d_in / 128 + S - 1) / S;
+    const int S = slices[k], kt = (u.d_in / 128 + S - 1) / S;
     double tiles = 0.0;
     for (int i = 0; i < u.n_modules; ++i)
       tiles += (double)(((u.modules[i].d_out + 15) / 16 + tile_blocks - 1) / tile_blocks) * ((u.T + 127) / 128) * S;
-    // (the projection's workgroups, about 2048 channels each, hold their places beside the tiles)
+    // (the projection's workgroups, about 2048 channels each, hold their places beside the tiles; counted
+    // for a unit that is not restored as well, so that the choice, and with it the bits of a unit's
+    // outputs, do not depend on the mask)
     const double proj = u.r > 0 ? (double)((u.T + 127) / 128) * std::min(8, (u.d_in + 2047) / 2048) : 0.0;
     wgs += tiles + proj;
     work += tiles * (kt + c.ends) + proj * std::min(kt, 8);
@@ -829,8 +831,8 @@ static float prefill_cost_of(const glowq_unit* const* units, int n, bool half) {
                                        : std::max((double)c.pair, c.busy * per_cu + 0.8 * c.alone);
   return (float)(c.start + sliced * c.sum + std::max((chain + c.ends) * (double)c.alone, work / wgs * share));
 }
-bool choose_prefill_tile(const glowq_unit* const* units, int n, float* cost) {
-  const float full = prefill_cost_of(units, n, false), half = prefill_cost_of(units, n, true);
+bool choose_prefill_tile(const glowq_unit* const* units, const int* slices, int n, float* cost) {
+  const float full = prefill_cost_of(units, slices, n, false), half = prefill_cost_of(units, slices, n, true);
   *cost = std::min(full, half);
   return half < 0.95f * full;
 }

@@ -40,6 +40,19 @@ def test_k_slices_need_their_slabs():
     assert route(512, 4096, (4096,)).k_slices == 1
 
 
+def test_the_choice_knows_whether_k_can_be_cut():
+    # without slabs (no workspace, glowq_group_forward_static) a long contraction stays in one piece, and
+    # the estimate must be that of one piece: 512 tokens x 2048 rows x 16384 on the tiled kernel's few
+    # workgroups take twice the batched kernel's time and more
+    assert route(512, 16384, (2048,)).k_slices == 4
+    for T, d_in, d_out in ((512, 16384, 2048), (300, 14336, 4096), (257, 16384, 2008)):
+        assert route(T, d_in, (d_out,)).kernel == G.GLOWQ_ROUTE_TILED
+        assert route(T, d_in, (d_out,), slabs=False).kernel == G.GLOWQ_ROUTE_BATCHED
+    # likewise where the module table of a launch has no room for the slices
+    full = [unit(700, 16384, (1000,))] + [unit(700, 256, (64,) * 5)] * 3
+    assert [r.k_slices for r in G.glowq_debug_route(full)] == [1] * 4
+
+
 def test_only_consumers_of_r_wait():
     # the projection's own workgroups wait for nothing, so launches whose consumers come in a launch of
     # their own have no wait at all, whether the projection is cut into K slices (past 4096 channels) or not
