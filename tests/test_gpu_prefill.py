@@ -55,3 +55,145 @@ def test_one_workspace_for_calls_of_different_sizes():
             check(ys, O.group_forward(units[k], True), TOL)
             first[k] = ys
         assert all(np.array_equal(a, b) for a, b in zip(first[k], ys)), k
+
+
+# (T, d_in, d_outs, types, tile): half-size tiles and large ones, a last token tile of one and of two
+# blocks, one K tile, ragged row blocks that straddle modules
+CASES = [(2056, 128, (264, 96, 40), ("f16", "bf16"), HALF), (2070, 640, (264, 96, 40), ("f16", "bf16"), HALF),
+         (2056, 128, (1000,), ("f16", "bf16"), HALF), (2070, 128, (3000, 3000, 3000), ("f16",), LARGE),
+         (2056, 128, (4008,), ("bf16",), LARGE), (2070, 256, (6008,), ("bf16",), LARGE)]
+
+
+@pytest.mark.parametrize("Gs,r", [(128, 72), (64, 16), (64, 128)])
+@pytest.mark.parametrize("T,d_in,d_outs,act,tile", [(T, d, o, a, t) for T, d, o, acts, t in CASES for a in acts])
+def test_tiles_match_the_oracle(T, d_in, d_outs, act, tile, Gs, r):
+    u = make(T, d_in, d_outs, act, Gs, r)
+    for restore, out in ((True, "act"), (True, "f32"), (False, "f32")):
+        du = DeviceUnit(u, out, 8)
+        assert route_of(du).tile == tile
+        ws = Workspace([du.desc])
+        G.glowq_group_forward(du.desc, restore, ws.ptr, ws.bytes, stream())
+        check(du.outputs(), O.group_forward(u, restore), TOL + (ULP[act] if out == "act" else 0.0))
+        ws.assert_idle()
+
+
+@pytest.mark.parametrize("act", ["f16", "bf16"])
+@pytest.mark.parametrize("r", [8, 24, 64, 120, 128])
+def test_every_rank_with_k_parts_of_the_projection(r, act):
+    # three parts of unequal length that the last one to finish adds; twice through one workspace
+    u = make(2056, 4352, (136, 40), act, r=r)
+    du = DeviceUnit(u)
+    route_of(du)
+    ws = Workspace([du.desc])
+    for _ in range(2):
+        du.clear()
+        G.glowq_group_forward(du.desc, True, ws.ptr, ws.bytes, stream())
+        check(du.outputs(), O.group_forward(u, True), TOL)
+        ws.assert_idle()
+
+
+@pytest.mark.parametrize("T,d_in,d_outs,act,out,tile,slices", [
+    (2056, 8320, (264, 40), "f16", "f32", HALF, 2), (2056, 8320, (264, 40), "bf16", "act", HALF, 2),
+    (2056, 12288, (72,), "f16", "act", HALF, 3), (257, 16384, (2008,), "bf16", "f32", HALF, 4),
+    (257, 12288, (4008,), "f16", "act", LARGE, 3), (520, 8192, (4008,), "bf16", "f32", LARGE, 2)])
+def test_k_slices(T, d_in, d_outs, act, out, tile, slices):
+    # two to four slices of unequal length (65 tiles: 32 + 33), each leaves an fp32 slab in the
+    # workspace, the first carries the correction, a second kernel adds them in slice order; ragged
+    # rows (40: a slab row of 40 floats), padded output rows, restored and not, the same bits every
+    # time, and against a call that cannot cut (no workspace)
+    u = make(T, d_in, d_outs, act)
+    du = DeviceUnit(u, out, 8)
+    r = route_of(du)
+    assert (r.tile, r.k_slices) == (tile, slices)
+    ws = Workspace([du.desc])
+    refs = {f: O.group_forward(u, f) for f in (True, False)}
+    tol = TOL + (ULP[act] if out == "act" else 0.0)
+    seen = {}
+    for restore in (True, False, True):
+        du.clear()
+        G.glowq_group_forward(du.desc, restore, ws.ptr, ws.bytes, stream())
+        ys = du.outputs()
+        check(ys, refs[restore], tol)
+        ws.assert_idle()
+        if restore in seen:
+            assert all(np.array_equal(a, b) for a, b in zip(seen[restore], ys))
+        seen[restore] = ys
+    du.clear()
+    G.glowq_group_forward(du.desc, False, 0, 0, stream())
+    check(du.outputs(), refs[False], tol)
+
+
+def test_k_slices_and_a_full_module_table():
+    # seven units in one launch, five of them long enough for K slices (four at 16384 channels, two at
+    # 8192): the table of 16 module entries has room for some of the slices only, so units cut four
+    # ways, two ways and not at all and ordinary units share it; masked and restored ones, called
+    # longest not first, twice through one workspace
+    shapes = [(256, (64, 40)), (16384, (40,)), (8192, (40, 24)), (16384, (24,)), (384, (136,)), (16384, (40,)), (8192, (72,))]
+    mask = [1, 1, 0, 1, 1, 0, 1]
+    units = [make(2056, d, o, "f16", r=16, seed=30 + i) for i, (d, o) in enumerate(shapes)]
+    dus = [DeviceUnit(u) for u in units]
+    routes = G.glowq_debug_route([d.desc for d in dus])
+    assert all(r.launch == 0 and r.kernel == G.GLOWQ_ROUTE_TILED for r in routes)
+    assert [r.k_slices for r in routes] == [1, 4, 2, 1, 1, 1, 2]
+    ws = Workspace([d.desc for d in dus])
+    refs = [O.group_forward(u, bool(f)) for u, f in zip(units, mask)]
+    for _ in range(2):
+        for d in dus:
+            d.clear()
+        G.glowq_block_forward([d.desc for d in dus], bytes(mask), ws.ptr, ws.bytes, stream())
+        for d, ref in zip(dus, refs):
+            check(d.outputs(), ref, TOL)
+        ws.assert_idle()
+
+
+@pytest.mark.parametrize("Gs", [128, 64])
+@pytest.mark.parametrize("act,d_out,tile", [("f16", 48, HALF), ("bf16", 48, HALF), ("f16", 9000, LARGE), ("bf16", 4008, LARGE)])
+def test_multiplies_with_the_stored_weight(act, d_out, tile, Gs):
+    # rows of the identity (and zeros up to the kernel's token count): every output is one weight as the
+    # kernel's own dequantiser made it, which must be round_act((q - z) s) bit for bit
+    T, d_in = 2056, 128
+    rng = np.random.default_rng(3)
+    q = rng.integers(0, 16, size=(d_out, d_in)).astype(np.uint8)
+    s_bits = rng.integers(1, 0x6C00, size=(d_out, d_in // Gs)).astype(np.uint16)
+    z_bits = O.f64_to_bits(rng.integers(0, 16, size=(d_out, d_in // Gs)).astype(np.float64), "f16")
+    X = np.zeros((T, d_in), np.uint16)
+    X[np.arange(d_in) * 16, np.arange(d_in)] = O.f64_to_bits(np.ones(1), act)[0]     # in every token tile
+    du = DeviceUnit(dict(act=act, G=Gs, r=0, d_in=d_in, B=None, X=X,
+                         modules=[dict(wq=O.pack_int4(q), scales=s_bits, zeros=z_bits, A=None)]))
+    assert route_of(du).tile == tile
+    ws = Workspace([du.desc])
+    G.glowq_group_forward(du.desc, False, ws.ptr, ws.bytes, stream())
+    y = du.outputs()[0]
+    seen = y[np.arange(d_in) * 16].T
+    ref = O.bits_to_f64(O.dequant_bits(q, s_bits, z_bits, Gs, act), act)
+    bad = np.argwhere(seen != ref)
+    assert bad.size == 0, (bad[:5], seen[tuple(bad[0])], ref[tuple(bad[0])])
+    rest = np.ones(T, bool)
+    rest[np.arange(d_in) * 16] = False
+    assert not y[rest].any()
+
+
+@pytest.mark.parametrize("act", ["f16", "bf16"])
+def test_handoff_in_a_row_and_in_graphs(act):
+    # the projection's parts, its flags and their consumers back to back: 200 launches, half of them
+    # replays of a captured call with eager calls in between, every result equal to the first one's bits
+    u = make(2056, 2304, (72, 40), act)
+    du = DeviceUnit(u)
+    route_of(du)
+    ws = Workspace([du.desc])
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    G.glowq_group_forward(du.desc, True, ws.ptr, ws.bytes, stream())
+    first = du.outputs()
+    check(first, O.group_forward(u, True), TOL)
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            G.glowq_group_forward(du.desc, True, ws.ptr, ws.bytes, torch.cuda.current_stream().cuda_stream)
+        for it in range(20):
+            du.clear()
+            for k in range(5):
+                graph.replay()
+                G.glowq_group_forward(du.desc, True, ws.ptr, ws.bytes, side.cuda_stream)
+            side.synchronize()
+            assert all(np.array_equal(a, b) for a, b in zip(first, du.outputs())), it
+    ws.assert_idle()
