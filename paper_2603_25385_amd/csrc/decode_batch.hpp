@@ -483,7 +483,7 @@ constexpr BatchTile BATCH_TILES[] = {
     {4, 1, 4, 4, 1.33f, 6.54f, {0.38f, 0.36f}, {0.38f, 0.41f}},
     {4, 2, 4, 4, 0.26f, 6.01f, {0.53f, 0.65f}, {0.52f, 0.58f}},
     {1, 2, 1, 4, 0.73f, 3.63f, {0.52f, 0.59f}, {0.54f, 0.40f}},
-    {1, 3, 1, 4, 0.25f, 6.50f, {0.74f, 0.74f}, {0.75f, 0.78f}},
+    {1, 3, 1, 4, 0.25f, 5.00f, {0.68f, 0.68f}, {0.68f, 0.72f}},
 };
 constexpr int BATCH_N_TILES = sizeof(BATCH_TILES) / sizeof(BATCH_TILES[0]);
 

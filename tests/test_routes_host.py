@@ -24,6 +24,14 @@ def test_classes_by_token_count():
                  (16, G.GLOWQ_ROUTE_MX_SMALL), (17, G.GLOWQ_ROUTE_MX_TILED)]
 
 
+def test_every_batched_tile_is_chosen_for_some_call():
+    tiles = {route(T, d_in, (rows,), r=64, act=act).tile
+             for act in (G.GLOWQ_F16, G.GLOWQ_BF16) for T in (5, 9, 18, 33, 50, 131)
+             for d_in in (128, 256, 384, 768, 1536, 3200, 4352, 8320) for rows in (304, 2008, 5000, 9000, 12008, 20008)
+             if route(T, d_in, (rows,), r=64, act=act).kernel == G.GLOWQ_ROUTE_BATCHED}
+    assert tiles == set(range(9))
+
+
 def test_units_that_share_a_launch():
     few = [unit(T, 256, (64,)) for T in (1, 1, 2, 1)]
     assert [r.launch for r in G.glowq_debug_route(few)] == [0, 0, 1, 2]
