@@ -1,5 +1,5 @@
-"""GPU parity of the batched kernel (more than four tokens): every workgroup tile its rule can
-choose, at the edges of tiles, token blocks, K tiles and wave groups."""
+"""GPU parity of the batched kernel (more than four tokens): edges of tiles, token blocks, K tiles and
+wave groups, and (test_every_tile) each workgroup tile that its rule chooses, asked of the library."""
 import numpy as np
 import pytest
 import torch
@@ -33,6 +33,31 @@ def test_tiles_match_the_oracle(T, d_in, d_outs, act, Gs):
         tol = TOL + (ULP[act] if out == "act" else 0.0)
         for y, ref in zip(ys, O.group_forward(u, restore)):
             assert np.isfinite(y).all() and rel_err(y, ref) <= tol
+
+
+# (T, d_in, rows, tile): binary16 up to 32 tokens, where the sums are scaled; beyond, where the weights
+# are rounded; bfloat16
+TILE_SHAPES = {
+    "exact": [(5, 256, (40, 264), 0), (5, 128, (40, 264), 1), (5, 768, (5000,), 2), (18, 896, (10008,), 3),
+              (18, 4352, (10008,), 4), (5, 1536, (5000,), 7), (5, 8320, (4440, 4440), 8)],
+    "f16": [(33, 256, (40, 264), 0), (33, 128, (40, 264), 1), (33, 768, (2008,), 2), (70, 128, (10008,), 3),
+            (33, 4352, (6008,), 4), (33, 3200, (12008,), 5), (50, 128, (20008,), 6), (33, 1536, (2008,), 7)],
+    "bf16": [(5, 384, (40, 264), 0), (5, 128, (40, 264), 1), (5, 1536, (10008,), 2), (18, 128, (10008,), 3),
+             (131, 6272, (4008,), 5), (131, 128, (10008,), 6), (5, 2176, (5000,), 7), (5, 8320, (4440, 4440), 8)]}
+
+
+@pytest.mark.parametrize("kind,T,d_in,d_outs,tile", [(k, *s) for k, shapes in TILE_SHAPES.items() for s in shapes])
+def test_every_tile(kind, T, d_in, d_outs, tile):
+    act = "bf16" if kind == "bf16" else "f16"
+    for Gs, r in ((128, 72), (64, 128)):
+        u = recipe_unit(O, 1, 0, T, r=r, shape=UnitShape("g", d_in, d_outs), act=act, G=Gs, method="alg1", qr="none")
+        for restore, out in ((True, "act"), (False, "f32")):
+            ys, du, _ = run_group(u, restore, out=out, ldy_pad=8)
+            got = G.glowq_debug_route([du.desc])[0]
+            assert (got.kernel, got.tile) == (G.GLOWQ_ROUTE_BATCHED, tile)
+            tol = TOL + (ULP[act] if out == "act" else 0.0)
+            for y, ref in zip(ys, O.group_forward(u, restore)):
+                assert np.isfinite(y).all() and rel_err(y, ref) <= tol
 
 
 # R small enough that the consumers add the projection's slices themselves, at its limits (512 ranks

@@ -1,5 +1,5 @@
 """GPU parity, forward (Sec. 3.3, Eqs. 8-9) at sizes the oracle finishes in
-seconds: the tiny workload through both kernel paths, ragged shapes, every rank,
+seconds: the tiny workload at token counts of every class, ragged shapes, every rank,
 the restore gating, and the identities the paper fixes."""
 import numpy as np
 import pytest
@@ -34,8 +34,8 @@ def test_tiny_workload(T):
 @pytest.mark.parametrize("act", ["f16", "bf16"])
 @pytest.mark.parametrize("T", [1, 3, 9, 20, 70, 257])
 def test_ragged_group(act, T):
-    # rows not a multiple of 32, three module sizes, two quantisation groups; 26 row blocks:
-    # the three-block groups of the 4 < T <= 32 path straddle the modules and end ragged
+    # rows not a multiple of 32, three module sizes, three K tiles; 26 row blocks, so that groups of
+    # them straddle the modules and end ragged
     shape = UnitShape("g", 384, (40, 264, 96))
     u = recipe_unit(O, 1, 0, T, r=24, shape=shape, act=act, G=128)
     ys, _, _ = run_group(u, True, ldy_pad=8)
@@ -69,10 +69,9 @@ def test_bf16_with_group_size_64(T):
 @pytest.mark.parametrize("act", ["f16", "bf16"])
 @pytest.mark.parametrize("T", [40, 130, 300])
 def test_long_contraction(act, T):
-    # d_in past 2048: the projection tiles of the tiled path work in K parts (here three
-    # of unequal length) and the last one to finish adds them; T = 130 ends in a token
-    # tile of a single 16-token block.  Twice through one workspace: the parts' arrival
-    # counter must be back at zero.
+    # d_in past 4096 on few rows: the batched kernel with its projection in K slices of unequal
+    # length and token tiles that end ragged, twice through one workspace (the tiled kernel's K
+    # parts: test_gpu_prefill.py)
     shape = UnitShape("g", 4352, (64, 40))
     u = recipe_unit(O, 1, 0, T, r=24, shape=shape, act=act, G=128)
     du = DeviceUnit(u)
@@ -88,11 +87,10 @@ def test_long_contraction(act, T):
 @pytest.mark.parametrize("act,d_in,T,out", [("f16", 8192, 70, "f32"), ("bf16", 8320, 130, "act"),
                                            ("f16", 12288, 200, "act"), ("bf16", 16384, 65, "f32")])
 def test_long_contraction_in_k_slices(act, d_in, T, out):
-    # 8192 channels and more on a handful of tiles: the launch cuts K into two to four slices
-    # (65 tiles into 32 + 33, 96 into three, 128 into four), each slice leaves an fp32 slab in
-    # the workspace, the first carries the correction, a second kernel adds them in slice
-    # order; ragged rows (40: a slab row of 40 floats), padded output rows, restored and not,
-    # twice through one workspace, and against a call that cannot cut (no workspace)
+    # 8192 channels and more on a handful of rows, where the workspace holds slabs for K slices but
+    # the batched kernel, which has its own way of sharing a contraction, is the faster one (slices
+    # on the tiled kernel: test_gpu_prefill.py); padded output rows, restored and not, twice
+    # through one workspace, and without one
     shape = UnitShape("s", d_in, (40, 264))
     u = recipe_unit(O, 1, 0, T, r=24, shape=shape, act=act, G=128)
     du = DeviceUnit(u, out, 8)
@@ -105,7 +103,7 @@ def test_long_contraction_in_k_slices(act, d_in, T, out):
         ys = du.outputs()
         _check(ys, O.group_forward(u, restore), tol)
         ws.assert_idle()
-        # the slices are added in a fixed order: the same bits every time
+        # the wave groups' sums are added in a fixed order: the same bits every time
         if restore in seen:
             assert all(np.array_equal(a, b) for a, b in zip(seen[restore], ys))
         seen[restore] = ys
@@ -146,12 +144,11 @@ def test_shared_projection(T):
 
 
 def test_token_independence_across_kernel_paths():
-    # column t of a 48-token call (tiled GEMM path) equals the 1-token call (streaming
-    # path).  The streaming path applies the group scale to the fp32 sum of x (q - z)
-    # instead of multiplying with the 16-bit rounded weight, so the two paths differ by
-    # the weight rounding (2^-11 per term, random sign) and by the tiled path's rounding of
-    # R to 16 bits: 7e-4 of the output's rms was measured here, each path being within a
-    # few 1e-4 of the oracle.
+    # column t of a 48-token call (batched kernel, rounded weights) equals the 1-token call
+    # (few-token kernel).  The latter applies the group scale to the fp32 sum of x (q - z)
+    # instead of multiplying with the 16-bit rounded weight, so the two differ by the weight
+    # rounding (2^-11 per term, random sign): 7e-4 of the output's rms was measured here, each
+    # being within a few 1e-4 of the oracle.
     u = recipe_unit(O, 1, 0, 48)
     many, _, _ = run_group(u, True)
     for t in (0, 17, 47):
@@ -180,11 +177,11 @@ def test_block_forward_with_mask():
 
 
 def test_block_forward_with_k_slices_and_a_full_module_table():
-    """Seven units of 70 tokens in one call, five of them with a contraction long enough to be
-    cut into K slices (four slices at 16384 channels, two at 8192): the launch's table of 16
-    module entries has room for some of the slices only, so units cut four ways, units cut two
-    ways or not at all and ordinary units share a launch (longest contraction first, which is
-    not the order of the call); masked and restored units, twice through one workspace."""
+    """Seven units of 70 tokens in one call, five of them with a contraction long enough for slabs of
+    K slices in their workspace, on so few rows that the batched kernel serves them all in one
+    launch (longest contraction first, which is not the order of the call); masked and restored
+    units, twice through one workspace.  (Slices and a full table on the tiled kernel:
+    test_gpu_prefill.py.)"""
     shapes = [UnitShape("a", 256, (64, 40)), UnitShape("d1", 16384, (40,)), UnitShape("d2", 8192, (40, 24)),
               UnitShape("d3", 16384, (24,)), UnitShape("b", 384, (136,)), UnitShape("d4", 16384, (40,)),
               UnitShape("d5", 8192, (72,))]
@@ -226,7 +223,7 @@ def test_block_forward_mixed_token_counts():
 def test_graph_replay_matches_eager(T):
     """A captured group forward replayed several times, with new activations written
     into the same buffers between replays, gives the eager result every time (the
-    single-launch decode path must tell one replay's projection from the previous)."""
+    kernel must tell one replay's projection from the previous)."""
     u = recipe_unit(O, 1, 0, T)
     du = DeviceUnit(u)
     ws = Workspace([du.desc])

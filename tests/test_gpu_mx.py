@@ -16,6 +16,9 @@ from util import rel_err
 
 pytestmark = pytest.mark.gpu
 TOL = 2e-3
+MX_TILE_SHAPES = [(300, 256, (20008,), 72, 0), (513, 256, (12000,), 24, 0), (384, 4352, (6000, 6008), 24, 0),
+                  (17, 128, (40,), 8, 1), (600, 640, (264, 96), 40, 2), (17, 128, (9000, 9008), 24, 3),
+                  (257, 128, (12008,), 16, 4)]
 ULP = {"f16": 2.0 ** -11, "bf16": 2.0 ** -8}
 
 
@@ -227,8 +230,8 @@ def test_calls_in_a_row_through_one_workspace():
 @pytest.mark.parametrize("act", ["f16", "bf16"])
 @pytest.mark.parametrize("T", [17, 48, 130, 300])
 def test_tiled_path(act, T):
-    # more than 16 tokens: the tiled product (token tiles of 128 with a ragged last one, row
-    # tiles of 128 with ragged modules, three K tiles), restored and not
+    # more than 16 tokens: the product on tiles (ragged last token tile, ragged modules, three K tiles),
+    # restored and not
     shape = UnitShape("g", 384, (40, 264, 136))
     u = make_unit(shape, T, 24, act, seed=16)
     du = MxDeviceUnit(u)
@@ -261,6 +264,20 @@ def test_tiled_path_exact_on_small_integers():
     assert np.array_equal(got, Xg @ Wg.T)
 
 
+# every tile of the product beyond 16 tokens (asked of the library): the 128 x 128 ones with a ragged
+# last token tile and a projection in K slices, and the small ones
+@pytest.mark.parametrize("act", ["f16", "bf16"])
+@pytest.mark.parametrize("T,d_in,d_outs,r,tile", MX_TILE_SHAPES)
+def test_every_tile(act, T, d_in, d_outs, r, tile):
+    u = make_unit(UnitShape("g", d_in, d_outs), T, r, act, seed=41)
+    for out, restore in (("act", True), ("f32", False)):
+        du = MxDeviceUnit(u, out=out)
+        assert G.glowq_debug_mx_route(du.desc).tile == tile
+        got = du.forward(restore)
+        for g, y in zip(got, MX.mx_group_forward(u, restore)):
+            assert np.isfinite(g).all() and rel_err(g, y) <= TOL + (ULP[act] if out == "act" else 0.0)
+
+
 def test_full_size_prefill():
     # 512 tokens on the q/k/v group of the 3B shapes (d = 3072, rows 3072 + 1024 + 1024), r = 64
     shape = UnitShape("qkv", 3072, (3072, 1024, 1024))
@@ -274,7 +291,7 @@ def test_full_size_prefill():
 
 # one K tile and fewer tokens than a tile; ragged row blocks and a token tile that ends in one block;
 # a contraction whose projection is cut into K slices, on few rows (groups of waves share K) and on
-# more; several tiles per compute unit; enough of them for the 128 x 128 tiles
+# more; several tiles per compute unit
 @pytest.mark.parametrize("act", ["f16", "bf16"])
 @pytest.mark.parametrize("T,d_in,d_outs,r", [(17, 128, (40,), 8), (40, 640, (264, 96), 72), (49, 4352, (136,), 24),
                                              (130, 8320, (72, 264), 128), (100, 256, (9000, 9008), 40),

@@ -79,15 +79,15 @@ def _weights_through_forward(mod, d_in, Gs, act, T):
     return seen
 
 
-# token counts: 1-2, 3-4 (few-token streaming kernels), 16 and 32 (streaming kernel with
-# one and two token blocks), 64 and d_in (tiled kernel with four and eight token blocks)
+# token counts: 1, 2, 4 (few-token kernels), 16 and 32 (batched kernel, scaled sums), 64 and d_in
+# (batched kernel, rounded weights); the tiled kernel: test_gpu_prefill.py
 @pytest.mark.parametrize("act", ["f16", "bf16"])
 @pytest.mark.parametrize("Gs", [128, 64])
 @pytest.mark.parametrize("T", [1, 2, 4, 16, 32, 64, 256])
 def test_forward_kernels_multiply_with_the_stored_weight(act, Gs, T):
-    """The dequantised weight is pinned bit for bit INSIDE every forward kernel (W4A16,
-    Sec. 4.1).  Tiled kernels and every bfloat16 path form round_act((q - z) s) and must
-    reproduce the oracle's bits; the binary16 streaming kernels (T <= 32) never round the
+    """The dequantised weight is pinned bit for bit INSIDE the few-token and batched kernels (W4A16,
+    Sec. 4.1).  Beyond 32 tokens and in bfloat16 they form round_act((q - z) s) and must
+    reproduce the oracle's bits; binary16 calls of up to 32 tokens never round the
     weight: they multiply the exact integer (q - z) and apply s to the fp32 sum, so what
     they multiply with is (q - z) s itself, which fp32 holds exactly (5 + 11 bits)."""
     d_out, d_in = 48, 256

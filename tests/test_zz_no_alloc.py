@@ -1,6 +1,6 @@
 """GPU check of glowq_group_forward_static, the entry point that allocates nothing: its
 output equals glowq_group_forward's on two calls in a row through the one scratch array,
-the second with a smaller input laid out differently (tiled path, then streaming path),
+the second with a smaller input laid out differently (batched kernel, then few-token kernel),
 and a unit whose scratch need exceeds the array is refused."""
 import numpy as np
 import pytest
@@ -27,7 +27,7 @@ def _both(u, restore):
 
 
 def test_static_scratch_entry_point_matches_the_workspace_one():
-    big = recipe_unit(O, 1, 0, 300, r=24, shape=UnitShape("g", 4352, (64, 40)), G=128)   # K parts
+    big = recipe_unit(O, 1, 0, 300, r=24, shape=UnitShape("g", 4352, (64, 40)), G=128)   # K slices
     small = recipe_unit(O, 1, 0, 3, r=16, shape=UnitShape("s", 256, (96, 32)), G=64)
     for u in (big, small, big):
         for restore in (True, False):
