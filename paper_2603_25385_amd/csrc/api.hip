@@ -326,7 +326,7 @@ glowq_status glowq_shared_proj(const glowq_unit* u, float* R_out, void* workspac
   if (misaligned(workspace)) return GLOWQ_ERR_ALIGN;
   UnitWorkspace ws = plan_unit_workspace(*u, (char*)workspace);
   if (workspace_bytes < ws.bytes) return GLOWQ_ERR_WORKSPACE;
-  return hip_status(launch_proj(*u, ws, R_out, false, (hipStream_t)stream));
+  return hip_status(launch_proj(*u, ws, R_out, (hipStream_t)stream));
 }
 
 glowq_status glowq_group_forward(const glowq_unit* u, int32_t restore, void* workspace,
@@ -541,7 +541,7 @@ glowq_status glowq_mx_quantize_activations(const void* X, int32_t T, int32_t d_i
   if (T < 1 || T > (1 << 20) || d_in < 32 || d_in > (1 << 16) || d_in % 32) return GLOWQ_ERR_SHAPE;
   if (act_dtype != GLOWQ_F16 && act_dtype != GLOWQ_BF16) return GLOWQ_ERR_DTYPE;
   if (misaligned(X) || misaligned(codes)) return GLOWQ_ERR_ALIGN;
-  return hip_status(launch_mx_quantize_x(X, T, d_in, act_dtype, codes, scales, false, (hipStream_t)stream));
+  return hip_status(launch_mx_quantize_x(X, T, d_in, act_dtype, codes, scales, (hipStream_t)stream));
 }
 
 // the unit checks of the ordinary forward without its group size (MX blocks are 32 channels)

@@ -139,7 +139,7 @@ static hipError_t launch_decode_small(const glowq_unit* const* units, const Unit
       b.n_prod[i] = 0;
       b.a[i].ctl = (Control*)ws[i].base;
       if (restore[i]) {
-        b.p[i] = make_proj_args(u, ws[i], nullptr, true);
+        b.p[i] = make_proj_args(u, ws[i], nullptr);
         b.n_prod[i] = (u.r * ws[i].ksplit + DEC_WAVES - 1) / DEC_WAVES;   // one wave per (rank, part)
       }
       b.wg_start[i] = wg;

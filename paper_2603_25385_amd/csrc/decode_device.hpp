@@ -395,31 +395,25 @@ __device__ inline void correction_take(CorrFrag& c, const uint32_t* lds_row, int
   if (c.active && c.ok) c.af = *(const u32x4_t*)(lds_row + 4 * lane);
 }
 
-// Folds the NW waves' fp32 tiles of one row block through LDS and stores the result.
-// lds: NW * TBK * 256 floats
-template <int ACT, int TBK, int NW = DEC_WAVES>
+// Folds the waves' fp32 tiles of one row block through LDS and stores the result.
+// lds: DEC_WAVES * 256 floats
+template <int ACT>
 __device__ inline void decode_reduce_store(const DecodeArgs& a, const ModuleArgs& M, int rb,
-                                           int wave, int lane, const float4_t (&acc)[TBK],
-                                           float* lds) {
+                                           int wave, int lane, const float4_t& acc, float* lds) {
 #pragma unroll
-  for (int tb = 0; tb < TBK; ++tb)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) lds[((wave * TBK + tb) * 4 + v) * 64 + lane] = acc[tb][v];
+  for (int v = 0; v < 4; ++v) lds[(wave * 4 + v) * 64 + lane] = acc[v];
   __syncthreads();
   if (wave >= 4) return;                         // (uniform per wave; no barrier follows in here)
-  const int v = wave, ln = lane;                 // 256 threads <-> (v, lane) of one token block
+  const int v = wave, ln = lane;                 // 256 threads <-> (v, lane) of the token block
   const int row = rb * 16 + (ln & 15);
+  const int t = 4 * (ln >> 4) + v;
+  if (t < a.T && row < M.d_out) {
+    float s = 0.f;
 #pragma unroll
-  for (int tb = 0; tb < TBK; ++tb) {
-    const int t = 16 * tb + 4 * (ln >> 4) + v;
-    if (t < a.T && row < M.d_out) {
-      float s = 0.f;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) s += lds[((w * TBK + tb) * 4 + v) * 64 + ln];
-      const size_t off = (size_t)t * M.ldy + row;
-      if (a.out_f32) ((float*)M.Y)[off] = s;
-      else ((uint16_t*)M.Y)[off] = to_act16<ACT>(s);
-    }
+    for (int w = 0; w < DEC_WAVES; ++w) s += lds[(w * 4 + v) * 64 + ln];
+    const size_t off = (size_t)t * M.ldy + row;
+    if (a.out_f32) ((float*)M.Y)[off] = s;
+    else ((uint16_t*)M.Y)[off] = to_act16<ACT>(s);
   }
 }
 
@@ -492,7 +486,7 @@ __device__ inline void decode_workgroup_small(const DecodeArgs& a_arg, const Pro
     if (r_fetch_finish<ACT>(p, rfetch, rf)) acc[0] = mfma16<ACT>(rf, cf.af, acc[0]);
     GLOWQ_WSTAMP(4);
   }
-  decode_reduce_store<ACT, 1>(a, M, rb, wave, lane, acc, lds);
+  decode_reduce_store<ACT>(a, M, rb, wave, lane, acc[0], lds);
   GLOWQ_WSTAMP(6);
   GLOWQ_WTRACE_FLUSH();
 }

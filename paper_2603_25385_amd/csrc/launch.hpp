@@ -70,7 +70,7 @@ MxWorkspace plan_mx_workspace(const glowq_unit& u);
 hipError_t launch_mx_prepare(const uint32_t* codes, const uint8_t* scales, int d_out, int d_in, void* prepared,
                              hipStream_t st);
 hipError_t launch_mx_quantize_x(const void* X, int T, int d_in, int act, uint8_t* codes, uint8_t* scales,
-                                bool fragment_order, hipStream_t st);
+                                hipStream_t st);
 hipError_t launch_mx_forward(const glowq_unit& u, bool restore, char* workspace, hipStream_t st);
 void mx_route(const glowq_unit& u, glowq_route* route);
 // slices' start offsets in units of 256 bytes (every slice is 256-byte aligned)
@@ -83,12 +83,11 @@ hipError_t launch_status_count(const void* ws, const StatusBatch& b, bool first,
                                hipStream_t st);
 
 struct ProjArgs;
-ProjArgs make_proj_args(const glowq_unit& u, const UnitWorkspace& ws, float* R32, bool want_r16);
+ProjArgs make_proj_args(const glowq_unit& u, const UnitWorkspace& ws, float* R32);
 
 // R = X B^T, stand-alone: fp32 partial sums per K slice, then a second launch adds them in
-// slice order into R32 (optional) and R16 (optional).
-hipError_t launch_proj(const glowq_unit& u, const UnitWorkspace& ws, float* R32, bool want_r16,
-                       hipStream_t st);
+// slice order into R32.
+hipError_t launch_proj(const glowq_unit& u, const UnitWorkspace& ws, float* R32, hipStream_t st);
 // T <= 4: streaming pass over the prepared weights; when restore, the projection runs
 // in the first workgroups of the same launch
 bool decode_batch_compatible(const glowq_unit& a, const glowq_unit& b);

@@ -142,10 +142,12 @@ __device__ inline void mx_quantize_block(const uint16_t* __restrict__ X, int T, 
   }
 }
 
-template <int ACT, bool FRAG>
+// The activations' codes in plain row order, for glowq_debug_mx_quantize_x alone (the forward
+// passes quantise in their first launch, in fragment order).
+template <int ACT>
 __global__ void __launch_bounds__(256) k_mx_quantize_x(const uint16_t* __restrict__ X, int T, int d_in,
                                                        uint8_t* __restrict__ codes, uint8_t* __restrict__ scales) {
-  mx_quantize_block<ACT, FRAG>(X, T, d_in, codes, scales, (long long)blockIdx.x * blockDim.x + threadIdx.x);
+  mx_quantize_block<ACT, false>(X, T, d_in, codes, scales, (long long)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // First launch of the forward (workgroups of 16 waves).  The leading workgroups compute the
@@ -908,17 +910,12 @@ hipError_t launch_mx_prepare(const uint32_t* codes, const uint8_t* scales, int d
 }
 
 hipError_t launch_mx_quantize_x(const void* X, int T, int d_in, int act, uint8_t* codes, uint8_t* scales,
-                                bool fragment_order, hipStream_t st) {
+                                hipStream_t st) {
   const long long n = (long long)T * (d_in / 16);
   dim3 grid((unsigned)((n + 255) / 256)), block(256);
   const uint16_t* x = (const uint16_t*)X;
-  if (act == GLOWQ_F16) {
-    if (fragment_order) k_mx_quantize_x<ACT_F16, true><<<grid, block, 0, st>>>(x, T, d_in, codes, scales);
-    else k_mx_quantize_x<ACT_F16, false><<<grid, block, 0, st>>>(x, T, d_in, codes, scales);
-  } else {
-    if (fragment_order) k_mx_quantize_x<ACT_BF16, true><<<grid, block, 0, st>>>(x, T, d_in, codes, scales);
-    else k_mx_quantize_x<ACT_BF16, false><<<grid, block, 0, st>>>(x, T, d_in, codes, scales);
-  }
+  if (act == GLOWQ_F16) k_mx_quantize_x<ACT_F16><<<grid, block, 0, st>>>(x, T, d_in, codes, scales);
+  else k_mx_quantize_x<ACT_BF16><<<grid, block, 0, st>>>(x, T, d_in, codes, scales);
   return hipGetLastError();
 }
 
@@ -1103,7 +1100,7 @@ static hipError_t launch_mx_small(const glowq_unit& u, bool restore, char* works
   p.kslice = ((u.d_in / 32 + want - 1) / want) * 32;
   p.ksplit = (u.d_in + p.kslice - 1) / p.kslice;
   p.Rpart = (float*)(workspace + w.off_rpart);
-  p.R32 = nullptr; p.R16 = nullptr; p.ctl = nullptr;
+  p.R32 = nullptr; p.ctl = nullptr;
   const int n_prod = corrected ? (u.r * p.ksplit + 3) / 4 : 0;        // one wave per (rank, part)
   const size_t lds = 4096 + (size_t)(u.d_in / 128) * (512 + 16) + 4 * MXS_MAX_PARTS * 1024;
   dim3 grid((unsigned)(n_prod + blocks)), block(256);

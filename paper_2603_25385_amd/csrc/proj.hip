@@ -66,15 +66,13 @@ __global__ void __launch_bounds__(256) k_proj_partial(ProjArgs a) {
   }
 }
 
-template <int ACT>
 __global__ void __launch_bounds__(256) k_proj_reduce(ProjArgs a) {
   const size_t n = (size_t)a.T * a.r;
   const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (e >= n) return;
   float s = 0.f;
   for (int z = 0; z < a.ksplit; ++z) s += a.Rpart[(size_t)z * n + e];   // slice order
-  if (a.R32) a.R32[e] = s;
-  if (a.R16) a.R16[e] = to_act16<ACT>(s);
+  a.R32[e] = s;
 }
 
 __global__ void k_fill_zero(uint32_t* p, long long n_words) {
@@ -111,7 +109,7 @@ hipError_t launch_status_count(const void* ws, const StatusBatch& b, bool first,
   return hipGetLastError();
 }
 
-ProjArgs make_proj_args(const glowq_unit& u, const UnitWorkspace& ws, float* R32, bool want_r16) {
+ProjArgs make_proj_args(const glowq_unit& u, const UnitWorkspace& ws, float* R32) {
   ProjArgs a;
   a.X = (const uint16_t*)u.X;
   a.B = (const uint16_t*)u.B;
@@ -122,14 +120,12 @@ ProjArgs make_proj_args(const glowq_unit& u, const UnitWorkspace& ws, float* R32
   a.kslice = ws.kslice;
   a.Rpart = (float*)(ws.base + ws.off_rpart);
   a.R32 = R32;
-  a.R16 = want_r16 ? (uint16_t*)(ws.base + ws.off_r16) : nullptr;
   a.ctl = (Control*)ws.base;
   return a;
 }
 
-hipError_t launch_proj(const glowq_unit& u, const UnitWorkspace& ws, float* R32, bool want_r16,
-                       hipStream_t st) {
-  ProjArgs a = make_proj_args(u, ws, R32, want_r16);
+hipError_t launch_proj(const glowq_unit& u, const UnitWorkspace& ws, float* R32, hipStream_t st) {
+  ProjArgs a = make_proj_args(u, ws, R32);
   // layout of the partial sums for this path: [slice][T][r]; slices as planned, but never
   // more than the partial-sum area (sized for the decode layout) can hold
   const size_t cap = (ws.off_r16 - ws.off_rpart) / ((size_t)u.T * u.r * sizeof(float));
@@ -143,13 +139,9 @@ hipError_t launch_proj(const glowq_unit& u, const UnitWorkspace& ws, float* R32,
   dim3 grid((unsigned)((u.T + 15) / 16), (unsigned)a.ksplit), block(256);
   const size_t n = (size_t)u.T * u.r;
   dim3 rgrid((unsigned)((n + 255) / 256));
-  if (u.act_dtype == GLOWQ_F16) {
-    k_proj_partial<ACT_F16><<<grid, block, 0, st>>>(a);
-    k_proj_reduce<ACT_F16><<<rgrid, block, 0, st>>>(a);
-  } else {
-    k_proj_partial<ACT_BF16><<<grid, block, 0, st>>>(a);
-    k_proj_reduce<ACT_BF16><<<rgrid, block, 0, st>>>(a);
-  }
+  if (u.act_dtype == GLOWQ_F16) k_proj_partial<ACT_F16><<<grid, block, 0, st>>>(a);
+  else k_proj_partial<ACT_BF16><<<grid, block, 0, st>>>(a);
+  k_proj_reduce<<<rgrid, block, 0, st>>>(a);
   return hipGetLastError();
 }
 

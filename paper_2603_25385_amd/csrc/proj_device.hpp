@@ -14,8 +14,7 @@ struct ProjArgs {
   int kslice;          // channels per slice, multiple of 32
   float* Rpart;        // stand-alone projection: fp32 [slice][T][r]; in-launch projection
                        // of the decode kernels: 8-byte slots {fp32 bits, launch tag}
-  float* R32;          // optional fp32 [T][r]
-  uint16_t* R16;       // optional act dtype [T][r]
+  float* R32;          // stand-alone projection: its result, fp32 [T][r]
   Control* ctl;        // control words of the unit's workspace slice
 };
 
