@@ -327,9 +327,8 @@ glowq_status glowq_factorize_unit(const glowq_unit* u, const float* const* W_mod
  *   launch (nothing to reset, graph replays included), every wait bounded; should a wait ever
  *   expire, the rows concerned are stored as NaN rather than without their correction.  Up to
  *   16 tokens otherwise: two launches (activation quantiser and projection; the weight
- *   stream).  More tokens: the activation quantiser, the stand-alone projection when restored,
- *   and a tiled product (128 tokens x 128 rows per workgroup).  Calls that share a workspace
- *   must not overlap. */
+ *   stream).  More tokens: two launches as well, the second a product tiled over tokens and rows
+ *   (glowq_debug_mx_route names the tile).  Calls that share a workspace must not overlap. */
 glowq_status glowq_mx_prepared_bytes(int32_t d_out, int32_t d_in, size_t* bytes);
 glowq_status glowq_mx_prepare_weights(const uint32_t* codes, const uint8_t* scales, int32_t d_out,
                                       int32_t d_in, void* w_prepared, void* stream);

@@ -11,10 +11,12 @@ struct UnitWorkspace {
   char* base;         // start of the slice (256-byte aligned)
   size_t bytes;       // size of the slice
   size_t off_counters;  // T > 64: per token tile, a ready flag and an arrival counter of K parts
-  size_t off_rpart;   // partial sums of the projection (T <= 64: 8-byte slots {fp32, launch tag},
-                      // [T][ksplit][r]; T > 64 and glowq_shared_proj: fp32 [part][T][r])
-  size_t off_r16;     // R in the activation type: T > 64 [T][r]; 4 < T <= 64 8-byte slots
-                      // {two ranks, launch tag}, [T][r / 2]
+  // The next two areas hold what the kernel that serves the call puts there (T > 64: either of two).
+  size_t off_rpart;   // partial sums of the projection: 8-byte slots {fp32, launch tag},
+                      // [T][ksplit][r] (few-token and batched kernels); fp32 [part][T][r] (tiled
+                      // kernel, glowq_shared_proj)
+  size_t off_r16;     // R in the activation type: 8-byte slots {two ranks, launch tag}, [T][r / 2]
+                      // (batched kernel); [T][r] (tiled kernel)
   size_t off_splitk;  // T > 64: fp32 slabs of a long contraction cut into K slices (0 bytes if not cut)
   size_t splitk_bytes;
   size_t ctl_bytes;   // leading bytes that must be zero between calls
@@ -26,7 +28,8 @@ struct UnitWorkspace {
   int pf_part_stages; // 64-channel stages per such part
 };
 
-// decode path = one pass over the weights with all tokens of the call in one workgroup
+// decode path: the few-token kernel (T <= 4) or the batched one, whatever the shapes; beyond it the
+// choice between the batched and the tiled kernel is made for each launch
 static inline bool is_decode(int T) { return T <= 64; }
 
 UnitWorkspace plan_unit_workspace(const glowq_unit& u, char* base);
@@ -95,9 +98,9 @@ int decode_max_batch();
 int decode_wait_polls();
 hipError_t launch_decode_multi(const glowq_unit* const* units, const UnitWorkspace* ws,
                                const bool* restore, int n, hipStream_t st);
-// 4 < T <= 64: the same with X shared through LDS; compatible units share a launch
-// T > 64 of few or small tiles goes the same way, up to this many tokens (the workspace of a unit
-// holds the slots up to here)
+// T > 4: the same with X shared through LDS; compatible units share a launch.  All calls of up to
+// 64 tokens go this way, those beyond where that is estimated to be the faster one, up to this
+// many tokens (the workspace of a unit holds the slots up to here)
 constexpr int BATCH_MAX_T = 2048;
 void plan_batch_projection(const glowq_unit& u, UnitWorkspace& w);
 // the workgroup tile for these units in one launch, and what it is taken to cost
@@ -107,8 +110,8 @@ bool batch_compatible(const glowq_unit& a, const glowq_unit& b);
 int batch_max_units();
 hipError_t launch_decode_batch(const glowq_unit* const* units, const UnitWorkspace* ws,
                                const bool* restore, int n, int tile, hipStream_t st);
-// T > 64: tiled matrix-core GEMM, correction folded in as an extra K slab.  One launch
-// covers several compatible units (same types, group size and token-tile size).
+// The other calls of T > 64: tiled matrix-core GEMM, correction folded in as an extra K slab.
+// One launch covers several compatible units (same types and group size).
 bool prefill_compatible(const glowq_unit& a, const glowq_unit& b);
 int prefill_max_units();
 int prefill_max_modules();

@@ -559,13 +559,15 @@ __global__ void __launch_bounds__(256, 4) k_mx_decode_small(MxArgs a, ProjArgs p
 // register holds staged data, three workgroups share a CU.  (Three buffers with the loads
 // two steps ahead, two workgroups per CU: no faster.  The register-resident loop of this
 // instruction measures 2.42 PFLOP/s on this machine, for fp8 x fp4 and fp4 x fp4 operands and
-// for the 32x32x64 shape alike - the rate of the 16-bit instructions, not twice it.)  Both tiles sit in LDS in fragment order, so that a wave's
+// for the 32x32x64 shape alike - the rate of the 16-bit instructions, not twice it.)  Smaller
+// tiles for launches that this one would not fill: k_mx_tile, see choose_mx_tile.  Both tiles sit
+// in LDS in fragment order, so that a wave's
 // fragment read is 1 KiB lane after lane (no bank conflict by construction): the weight tile
 // is the prepared layout as it is in memory; the activation tile is [token block][half]
 // [lane][16 bytes], which is how the quantiser leaves it in the workspace, so every load is
 // one contiguous KiB.  Slots of tokens past T hold whatever the workspace held (a row of the
-// first operand touches its own output row only, and those are not stored).  The correction (R from the stand-alone projection, in the activation type) is
-// r / 32 more 16-bit instructions per accumulator tile in the epilogue.
+// first operand touches its own output row only, and those are not stored).  The correction (R from the first
+// launch, in the activation type) is r / 32 more 16-bit instructions per accumulator tile in the epilogue.
 // ---------------------------------------------------------------------------------------
 constexpr int MXG_TOK = 128, MXG_ROWS = 128;
 constexpr int MXG_A = 0, MXG_B = 16384, MXG_ASC = 24576, MXG_BSC = 25088, MXG_BUF = 25600;   // byte offsets in a buffer
@@ -924,7 +926,7 @@ static size_t up256(size_t b) { return (b + 255) & ~(size_t)255; }
 MxWorkspace plan_mx_workspace(const glowq_unit& u) {
   MxWorkspace w;
   if (u.T > MX_MAX_TOKENS) {
-    // the tiled path: the unit's ordinary slice (partial sums and R of the stand-alone
+    // the tiled path: the unit's ordinary slice (partial sums and R of the first launch's
     // projection), then the quantised activations
     w.ks = w.kslice = 0;
     w.off_rpart = 0;

@@ -1,11 +1,12 @@
-// Prefill path (T > 64 tokens): Y_i = X dequant(W_q,i)^T + R A_i^T  (paper Eq. 9)
+// Tiled kernel (T > 64 tokens, unless the batched kernel is estimated to be faster, which it
+// can be up to BATCH_MAX_T): Y_i = X dequant(W_q,i)^T + R A_i^T  (paper Eq. 9)
 // as a tiled matrix-core GEMM with the correction folded in as r extra channels, and
 // R = X B^T (paper Eq. 8) computed by the leading tiles of the same launch.
 //
-// Workgroup tile: (16 MB) tokens x 256 rows (192 for bfloat16), four waves, each wave
-// 64 (48) rows x all tokens of the tile; at most 256 registers per lane, so two
-// workgroups share a compute unit and one's barrier or memory wait leaves the matrix
-// cores to the other.  Because every wave covers all tokens of the tile, each weight is
+// Workgroup tile: (16 MB) tokens x 256 rows (192 for bfloat16; half-size tiles of 128 rows
+// where choose_prefill_tile finds them cheaper), four waves, each wave 64 (48, 32) rows x all
+// tokens of the tile; at most 256 registers per lane, so two workgroups share a compute unit
+// and one's barrier or memory wait leaves the matrix cores to the other.  Because every wave covers all tokens of the tile, each weight is
 // dequantised once per workgroup (in registers: one rounding, the stored weight exactly)
 // and becomes the A operand of a 16x16x32 instruction.  Everything that moves is a
 // direct global->LDS load: X in 64-channel stages into a ring of three (the 16-byte
