@@ -235,10 +235,13 @@ __device__ inline void proj_tile(const PrefillArgs& a, uint16_t* xs) {
     if (tid == 0) {
       uint32_t* word = U.flags + MB * mt + 1;      // {28 bits of the tag, parts that are done}
       const uint32_t key = (uint32_t)(launch_tag() >> 1) << 4;
+      // (the fences stand outside the loop: each costs a pass over the L2)
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
       uint32_t seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), done;
       do done = (seen & ~15u) == key ? seen & 15u : 0u;      // (at most `parts` rounds: a failure is another part's success)
-      while (!__hip_atomic_compare_exchange_strong(word, &seen, key | (done + 1u), __ATOMIC_ACQ_REL, __ATOMIC_RELAXED,
+      while (!__hip_atomic_compare_exchange_strong(word, &seen, key | (done + 1u), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                    __HIP_MEMORY_SCOPE_AGENT));
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
       *lds_word = done;
     }
     __syncthreads();
