@@ -404,6 +404,19 @@ __device__ inline void after_wait32(uint32_t& v) { asm volatile("" : "+v"(v)); }
 // gives up (about a second and more: long enough for another stream's kernels to make room).
 constexpr int R_WAIT_POLLS = 1 << 20;
 
+// Two 16 x 16 results of neighbouring row blocks (lane (i, g): rows 4 g .. + 4 of token i) in the activation
+// type, exchanged between lane groups g and g ^ 1: lane (i, g) ends with rows 8 (g >> 1) .. + 8 of token i of
+// block g & 1.
+template <int ACT> __device__ inline u32x4_t acc_pack_rows(float4_t first, float4_t second) {
+  const uint32_t a0 = (uint32_t)to_act16<ACT>(first[0]) | ((uint32_t)to_act16<ACT>(first[1]) << 16);
+  const uint32_t a1 = (uint32_t)to_act16<ACT>(first[2]) | ((uint32_t)to_act16<ACT>(first[3]) << 16);
+  const uint32_t b0 = (uint32_t)to_act16<ACT>(second[0]) | ((uint32_t)to_act16<ACT>(second[1]) << 16);
+  const uint32_t b1 = (uint32_t)to_act16<ACT>(second[2]) | ((uint32_t)to_act16<ACT>(second[3]) << 16);
+  const auto lo = __builtin_amdgcn_permlane16_swap(a0, b0, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(a1, b1, false, false);
+  return u32x4_t{lo[0], hi[0], lo[1], hi[1]};
+}
+
 // Control words at the head of a unit's workspace slice.
 struct Control {
   uint32_t unused[3];

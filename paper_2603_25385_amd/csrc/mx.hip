@@ -557,16 +557,21 @@ __global__ void __launch_bounds__(256, 4) k_mx_decode_small(MxArgs a, ProjArgs p
 // at the top of step k every wave issues its share of step k + 1 into the other buffer,
 // multiplies step k, waits for its own loads and meets the others at one barrier.  No
 // register holds staged data, three workgroups share a CU.  (Three buffers with the loads
-// two steps ahead, two workgroups per CU: no faster.  The register-resident loop of this
-// instruction measures 2.42 PFLOP/s on this machine, for fp8 x fp4 and fp4 x fp4 operands and
-// for the 32x32x64 shape alike - the rate of the 16-bit instructions, not twice it.)  Smaller
-// tiles for launches that this one would not fill: k_mx_tile, see choose_mx_tile.  Both tiles sit
+// two steps ahead, two workgroups per CU: no faster.)  Smaller tiles for launches that this one would not fill:
+// k_mx_tile, see choose_mx_tile.  What bounds it: the instruction itself delivers 4.6 PFLOP/s from
+// registers (32 cycles for fp8 x fp4), this loop 2.2: waves of 64 x 64 read 96 of the 128 bytes that LDS
+// delivers a cycle, and the clock falls to 1.6 to 1.85 GHz under the load.  Tiles of 256 x 256 (256
+// accumulation registers, one wave per SIMD, a ring of three, workgroups that go from tile to tile) gain 4 % here and
+// up to 15 % on several times the work, and lose as much where their rounds come out uneven: not kept.
+// Weights are the first operand, so that a lane ends up with four rows of one token; two row blocks' rows are
+// exchanged between lane groups so that sixteen tokens' stores are 64 bytes each (2-byte stores, 32 bytes a
+// row: 2 x 11008 rows x 4096 at 2048 tokens 207 -> 184 us with it).  Both tiles sit
 // in LDS in fragment order, so that a wave's
 // fragment read is 1 KiB lane after lane (no bank conflict by construction): the weight tile
 // is the prepared layout as it is in memory; the activation tile is [token block][half]
 // [lane][16 bytes], which is how the quantiser leaves it in the workspace, so every load is
-// one contiguous KiB.  Slots of tokens past T hold whatever the workspace held (a row of the
-// first operand touches its own output row only, and those are not stored).  The correction (R from the first
+// one contiguous KiB.  Slots of tokens past T hold whatever the workspace held (a token's operand
+// touches its own outputs only, and those are not stored).  The correction (R from the first
 // launch, in the activation type) is r / 32 more 16-bit instructions per accumulator tile in the epilogue.
 // ---------------------------------------------------------------------------------------
 constexpr int MXG_TOK = 128, MXG_ROWS = 128;
@@ -660,7 +665,7 @@ __global__ void __launch_bounds__(256) k_mx_gemm(MxGemmArgs a) {
       const v8i_t A = {(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
 #pragma unroll
       for (int nb = 0; nb < 4; ++nb)
-        acc[tb][nb] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A, B[nb], acc[tb][nb], 0, 4, 0, sa, 0, sb[nb]);
+        acc[tb][nb] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(B[nb], A, acc[tb][nb], 4, 0, 0, sb[nb], 0, sa);
     }
     vm_wait<0>();          // this wave's loads of the next step have landed ...
     __syncthreads();       // ... and everybody's; everybody is done reading this step's buffer
@@ -680,24 +685,29 @@ __global__ void __launch_bounds__(256) k_mx_gemm(MxGemmArgs a) {
         const int tok = tok0 + 64 * wm + 16 * tb + i;
         const u32x4_t ra = (j0 < a.r && tok < a.T) ? *(const u32x4_t*)(a.R16 + (long long)tok * a.r + j0) : u32x4_t{0, 0, 0, 0};
 #pragma unroll
-        for (int nb = 0; nb < 4; ++nb) acc[tb][nb] = mfma16<ACT>(ra, rb[nb], acc[tb][nb]);
+        for (int nb = 0; nb < 4; ++nb) acc[tb][nb] = mfma16<ACT>(rb[nb], ra, acc[tb][nb]);
       }
     }
   }
+  // lane holds rows 4 g .. + 4 of each block and token i; 16-bit outputs: eight rows of a pair of blocks per store
 #pragma unroll
-  for (int tb = 0; tb < 4; ++tb)
+  for (int tb = 0; tb < 4; ++tb) {
+    const int tok = tok0 + 64 * wm + 16 * tb + i;
 #pragma unroll
-    for (int nb = 0; nb < 4; ++nb) {
-      const int row = (rb0 + 4 * wn + nb) * 16 + i;
+    for (int nb = 0; nb < 4; nb += 2) {
+      if (a.out_f32) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int tok = tok0 + 64 * wm + 16 * tb + 4 * g + v;
-        if (tok < a.T && row < m.d_out) {
-          if (a.out_f32) ((float*)m.Y)[(long long)tok * m.ldy + row] = acc[tb][nb][v];
-          else ((uint16_t*)m.Y)[(long long)tok * m.ldy + row] = to_act16<ACT>(acc[tb][nb][v]);
+        for (int q = 0; q < 2; ++q) {
+          const int row = (rb0 + 4 * wn + nb + q) * 16 + 4 * g;
+          if (tok < a.T && row < m.d_out) *(float4_t*)((float*)m.Y + (long long)tok * m.ldy + row) = acc[tb][nb + q];
         }
+      } else {
+        const int row = (rb0 + 4 * wn + nb + (g & 1)) * 16 + 8 * (g >> 1);
+        const u32x4_t v = acc_pack_rows<ACT>(acc[tb][nb], acc[tb][nb + 1]);
+        if (tok < a.T && row < m.d_out) *(u32x4_t*)((uint16_t*)m.Y + (long long)tok * m.ldy + row) = v;
       }
     }
+  }
 }
 
 // ---------------------------------------------------------------------------------------
