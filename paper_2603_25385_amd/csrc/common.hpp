@@ -396,6 +396,15 @@ __device__ inline void vm_load(u32x4_t& v, const void* p) {
 template <int N> __device__ inline void vm_wait() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
+// Stores at device scope: written through this XCD's L2, out once vm_wait<0> has returned
+__device__ inline void store16_device(void* p, u32x4_t v) {
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" : : "v"(p), "v"(v) : "memory");
+}
+__device__ inline void store8_device(void* p, uint32_t lo, uint32_t hi) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  const u32x2 v = {lo, hi};
+  asm volatile("global_store_dwordx2 %0, %1, off sc1\n\ts_nop 0" : : "v"(p), "v"(v) : "memory");
+}
 // ties a value to a point behind a wait, so that nothing that uses it moves above
 __device__ inline void after_wait(u32x4_t& v) { asm volatile("" : "+v"(v)); }
 __device__ inline void after_wait32(uint32_t& v) { asm volatile("" : "+v"(v)); }
