@@ -356,7 +356,7 @@ glowq_status glowq_mx_group_forward(const glowq_unit* u, int32_t restore, void* 
 enum {
   GLOWQ_ROUTE_FEW = 0,        /* up to four tokens, one pass over the weights                  */
   GLOWQ_ROUTE_BATCHED = 1,    /* batched kernel; tile: index of its workgroup tile             */
-  GLOWQ_ROUTE_TILED = 2,      /* tiled kernel; tile: 0 its large tiles, 1 the half-size ones   */
+  GLOWQ_ROUTE_TILED = 2,      /* tiled kernel; tile: 0 its large (or wide) tiles, 1 half-size  */
   GLOWQ_ROUTE_MX_ONE = 3,     /* microscaling, one launch                                      */
   GLOWQ_ROUTE_MX_SMALL = 4,   /* microscaling, up to 16 tokens, two launches                   */
   GLOWQ_ROUTE_MX_TILED = 5    /* microscaling, more tokens; tile: index of its workgroup tile  */
@@ -372,6 +372,9 @@ typedef struct {
 glowq_status glowq_debug_route(const glowq_unit* units, int32_t n_units, int32_t slabs,
                                glowq_route* routes);
 glowq_status glowq_debug_mx_route(const glowq_unit* u, glowq_route* route);
+/* tokens[i]: tokens of a workgroup tile of the tiled kernel (128, or 256 for the wide ones, which count as
+ * large), 0 for a unit that another kernel serves. */
+glowq_status glowq_debug_tile_tokens(const glowq_unit* units, int32_t n_units, int32_t slabs, int32_t* tokens);
 glowq_status glowq_debug_unpack(const void* w_prepared, int32_t d_out, int32_t d_in,
                                 int32_t group_size, uint8_t* q_out, void* stream);
 glowq_status glowq_debug_dequant(const void* w_prepared, int32_t d_out, int32_t d_in,

@@ -98,6 +98,7 @@ def _load():
         "glowq_mx_workspace_bytes": (ctypes.c_int, [up, ctypes.POINTER(sz)]),
         "glowq_mx_group_forward": (ctypes.c_int, [up, i32, vp, sz, vp]),
         "glowq_debug_route": (ctypes.c_int, [up, i32, i32, ctypes.POINTER(glowq_route)]),
+        "glowq_debug_tile_tokens": (ctypes.c_int, [up, i32, i32, ctypes.POINTER(i32)]),
         "glowq_debug_mx_route": (ctypes.c_int, [up, ctypes.POINTER(glowq_route)]),
         "glowq_debug_unpack": (ctypes.c_int, [vp, i32, i32, i32, vp, vp]),
         "glowq_debug_dequant": (ctypes.c_int, [vp, i32, i32, i32, i32, vp, vp]),
@@ -343,6 +344,14 @@ def glowq_debug_route(units: Sequence[glowq_unit], slabs: bool = True) -> list:
     routes = (glowq_route * len(units))()
     _check(_lib.glowq_debug_route(_units_array(units), len(units), 1 if slabs else 0, routes), "glowq_debug_route")
     return list(routes)
+
+
+def glowq_debug_tile_tokens(units: Sequence[glowq_unit], slabs: bool = True) -> list:
+    """Tokens of the tiled kernel's workgroup tiles, per unit (0: another kernel)."""
+    tokens = (ctypes.c_int32 * len(units))()
+    _check(_lib.glowq_debug_tile_tokens(_units_array(units), len(units), 1 if slabs else 0, tokens),
+           "glowq_debug_tile_tokens")
+    return list(tokens)
 
 
 def glowq_debug_mx_route(unit: glowq_unit) -> glowq_route:

@@ -149,7 +149,7 @@ constexpr int MAX_LAUNCH_UNITS = 32;
 struct LaunchChoice {
   int kernel;                      // GLOWQ_ROUTE_...
   int n;                           // units
-  int tile;                        // batched: the workgroup tile; tiled: 1 for the half-size tiles
+  int tile;                        // batched: the workgroup tile; tiled: PF_TILE_...
   int slices[MAX_LAUNCH_UNITS];    // K slices of every unit
 };
 static LaunchChoice choose_launch(const glowq_unit* units, int n_units, bool slabs) {
@@ -180,7 +180,7 @@ static LaunchChoice choose_launch(const glowq_unit* units, int n_units, bool sla
     ++c.n;
   }
   plan_prefill_slices(batch, c.n, slabs, c.slices);
-  const bool half = choose_prefill_tile(batch, c.slices, c.n, &cost);
+  const int large = choose_prefill_tile(batch, c.slices, c.n, &cost);
   // Few or small tiles leave the tiled kernel's workgroups alone on their compute units with the
   // whole contraction each; there the smaller tiles of the batched kernel are faster.
   float small_cost = 0.f;
@@ -192,7 +192,7 @@ static LaunchChoice choose_launch(const glowq_unit* units, int n_units, bool sla
     return c;
   }
   c.kernel = GLOWQ_ROUTE_TILED;
-  c.tile = half ? 1 : 0;
+  c.tile = large;
   return c;
 }
 
@@ -214,7 +214,7 @@ static glowq_status forward_all(const glowq_unit* units, int n_units, const uint
     }
     const hipError_t e = c.kernel == GLOWQ_ROUTE_FEW       ? launch_decode_multi(batch, ws, corr, c.n, st)
                          : c.kernel == GLOWQ_ROUTE_BATCHED ? launch_decode_batch(batch, ws, corr, c.n, c.tile, st)
-                                                           : launch_prefill_multi(batch, ws, corr, c.n, c.tile == 1, c.slices, st);
+                                                           : launch_prefill_multi(batch, ws, corr, c.n, c.tile, c.slices, st);
     if (e != hipSuccess) return hip_status(e);
   }
   return GLOWQ_OK;
@@ -572,8 +572,9 @@ glowq_status glowq_mx_group_forward(const glowq_unit* u, int32_t restore, void* 
   return hip_status(launch_mx_forward(*u, restore != 0, (char*)workspace, (hipStream_t)stream));
 }
 
-glowq_status glowq_debug_route(const glowq_unit* units, int32_t n_units, int32_t slabs, glowq_route* routes) {
-  if (!units || !routes) return GLOWQ_ERR_NULL;
+// routes and tokens: either may be missing
+static glowq_status debug_route(const glowq_unit* units, int32_t n_units, int32_t slabs, glowq_route* routes, int32_t* tokens) {
+  if (!units || (!routes && !tokens)) return GLOWQ_ERR_NULL;
   if (n_units < 1) return GLOWQ_ERR_SHAPE;
   for (int i = 0; i < n_units; ++i) {
     glowq_status s = validate(&units[i], false, false);
@@ -582,13 +583,23 @@ glowq_status glowq_debug_route(const glowq_unit* units, int32_t n_units, int32_t
   }
   for (int i = 0, launch = 0; i < n_units; ++launch) {
     const LaunchChoice c = choose_launch(units + i, n_units - i, slabs != 0);
-    for (int k = 0; k < c.n; ++k, ++i)
-      routes[i] = glowq_route{launch, c.kernel, c.tile, c.slices[k],
-                              c.kernel == GLOWQ_ROUTE_FEW       ? decode_wait_polls()
-                              : c.kernel == GLOWQ_ROUTE_BATCHED ? batch_wait_polls()
-                                                                : prefill_wait_polls()};
+    const bool tiled = c.kernel == GLOWQ_ROUTE_TILED, wide = tiled && c.tile == PF_TILE_WIDE;
+    for (int k = 0; k < c.n; ++k, ++i) {
+      if (routes)
+        routes[i] = glowq_route{launch, c.kernel, wide ? PF_TILE_LARGE : c.tile, c.slices[k],
+                                c.kernel == GLOWQ_ROUTE_FEW       ? decode_wait_polls()
+                                : c.kernel == GLOWQ_ROUTE_BATCHED ? batch_wait_polls()
+                                                                  : prefill_wait_polls()};
+      if (tokens) tokens[i] = wide ? 256 : tiled ? 128 : 0;
+    }
   }
   return GLOWQ_OK;
+}
+glowq_status glowq_debug_route(const glowq_unit* units, int32_t n_units, int32_t slabs, glowq_route* routes) {
+  return debug_route(units, n_units, slabs, routes, nullptr);
+}
+glowq_status glowq_debug_tile_tokens(const glowq_unit* units, int32_t n_units, int32_t slabs, int32_t* tokens) {
+  return debug_route(units, n_units, slabs, nullptr, tokens);
 }
 
 glowq_status glowq_debug_mx_route(const glowq_unit* u, glowq_route* route) {

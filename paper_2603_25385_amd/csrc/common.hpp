@@ -212,10 +212,11 @@ __device__ inline u32x4_t dequant_word<ACT_BF16>(uint32_t w, const GroupConst<AC
 // alternates between the two words, so that dependent instructions are two apart
 // (with two waves per SIMD the other wave's instructions fall in between as well).  Running idx =
 // 0 .. N_OPS-1 in order leaves in out[w] exactly what dequant_word returns for w[w].
-template <int ACT, int NW> struct DequantLockstep;
-template <int NW> struct DequantLockstep<ACT_F16, NW> {
-  static constexpr int PH = 15, GS = NW < 2 ? NW : 2;
-  static_assert(NW % GS == 0, "words are taken two at a time");
+// (GS: words taken at a time, two unless the caller has registers for more.)
+template <int ACT, int NW, int GS = (NW < 2 ? NW : 2)> struct DequantLockstep;
+template <int NW, int GS> struct DequantLockstep<ACT_F16, NW, GS> {
+  static constexpr int PH = 15;
+  static_assert(NW % GS == 0, "words are taken GS at a time");
   static constexpr int N_OPS = NW * PH;
   uint32_t ws[GS];   // the word, shifted for the pair in flight
   half2_t d[GS];     // (q - z) pair in flight
@@ -244,8 +245,8 @@ template <int NW> struct DequantLockstep<ACT_F16, NW> {
 // exact, and the packed fp32 -> bfloat16 conversion is the one rounding of the stored
 // weight.  c[w][0] = -(1024 + z) s and c[w][1] = -(64 + z) s of word w's group travel
 // beside the group constants (set by the caller when a new group starts).
-template <int NW> struct DequantLockstep<ACT_BF16, NW> {
-  static constexpr int PH = 17, GS = NW < 2 ? NW : 2;
+template <int NW, int GS> struct DequantLockstep<ACT_BF16, NW, GS> {
+  static constexpr int PH = 17;
   static constexpr int N_OPS = NW * PH;
   uint32_t ws[GS];   // the word shifted by 8
   uint32_t t[GS];    // binary16 pair in flight
@@ -290,13 +291,13 @@ template <int NW> struct DequantLockstep<ACT_BF16, NW> {
 
 // binary16 with two fewer instructions per word (needs one more constant per block and
 // one more register for the second magic constant).
-template <int NW> struct DequantLockstepF16Shiftless {
+template <int NW, int GS = (NW < 2 ? NW : 2)> struct DequantLockstepF16Shiftless {
   // Nibbles at bits 0-3 / 16-19 of a word become 1024 + q under the exponent of 1024
   // (0x6400), nibbles at bits 4-7 / 20-23 become 64 + q under the exponent of 64 (0x5400:
   // one unit in the last place is 1/16, so bit 4 weighs 1) -- no shift; the other four
   // nibbles take the same two forms after one shift by 8.  13 instructions per word.
-  static constexpr int PH = 13, GS = NW < 2 ? NW : 2;
-  static_assert(NW % GS == 0, "words are taken two at a time");
+  static constexpr int PH = 13;
+  static_assert(NW % GS == 0, "words are taken GS at a time");
   static constexpr int N_OPS = NW * PH;
   uint32_t ws[GS];   // the word shifted by 8
   half2_t d[GS];     // (q - z) pair in flight

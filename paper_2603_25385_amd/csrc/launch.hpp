@@ -118,11 +118,12 @@ int prefill_max_modules();
 // K slices of every unit of a launch: where the unit's shapes ask for them, the workspace has the
 // slabs (`slabs`) and the module table has room
 void plan_prefill_slices(const glowq_unit* const* units, int n, bool slabs, int* slices);
-// whether the launch, cut into these slices, takes the half-size tiles, and what it is taken to cost
-bool choose_prefill_tile(const glowq_unit* const* units, const int* slices, int n, float* cost);
+// the tiles that the launch, cut into these slices, takes, and what it is taken to cost
+enum { PF_TILE_LARGE = 0, PF_TILE_HALF = 1, PF_TILE_WIDE = 2 };
+int choose_prefill_tile(const glowq_unit* const* units, const int* slices, int n, float* cost);
 int prefill_wait_polls();
 hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorkspace* ws,
-                                const bool* restore, int n_units, bool half, const int* slices, hipStream_t st);
+                                const bool* restore, int n_units, int tile, const int* slices, hipStream_t st);
 int prefill_k_slices(const glowq_unit& u);
 size_t prefill_splitk_bytes(const glowq_unit& u);
 

@@ -3,8 +3,8 @@
 // as a tiled matrix-core GEMM with the correction folded in as r extra channels, and
 // R = X B^T (paper Eq. 8) computed by the leading tiles of the same launch.
 //
-// Workgroup tile: (16 MB) tokens x 256 rows (192 for bfloat16; half-size tiles of 128 rows
-// where choose_prefill_tile finds them cheaper), four waves, each wave 64 (48, 32) rows x all
+// Workgroup tile: (16 MB) tokens x 256 rows (192 for bfloat16; half-size tiles of 128 rows, or wide
+// ones of 256 tokens x 256 rows (prefill_wide.hpp), where choose_prefill_tile finds them cheaper), four waves, each wave 64 (48, 32) rows x all
 // tokens of the tile; at most 256 registers per lane, so two workgroups share a compute unit
 // and one's barrier or memory wait leaves the matrix cores to the other.  Because every wave covers all tokens of the tile, each weight is
 // dequantised once per workgroup (in registers: one rounding, the stored weight exactly)
@@ -17,6 +17,7 @@
 // four consecutive rows of one token and stores them with one 8- or 16-byte write.
 #include <type_traits>
 #include <algorithm>
+#include <cmath>
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -728,6 +729,10 @@ __global__ void __launch_bounds__(PfShape<ACT>::WAVES * 64, PfShape<ACT>::OCC) k
   GLOWQ_STAMP(6);
 }
 
+}  // namespace glowq
+#include "prefill_wide.hpp"
+namespace glowq {
+
 template <int ACT, int MB, int RB>
 static hipError_t launch_prefill_t(const PrefillArgs& a, int n_wgs, int G, hipStream_t st) {
   dim3 grid((unsigned)n_wgs), block(PfShape<ACT>::WAVES * 64);
@@ -735,8 +740,14 @@ static hipError_t launch_prefill_t(const PrefillArgs& a, int n_wgs, int G, hipSt
   else k_prefill<ACT, MB, RB, false><<<grid, block, 0, st>>>(a);
   return hipGetLastError();
 }
+template <int ACT> static hipError_t launch_wide(const PrefillArgs& a, int n_wgs, int G, hipStream_t st) {
+  dim3 grid((unsigned)n_wgs), block(WD_WAVES * 64);
+  if (G == 128) k_wide<ACT, true><<<grid, block, 0, st>>>(a);
+  else k_wide<ACT, false><<<grid, block, 0, st>>>(a);
+  return hipGetLastError();
+}
 
-constexpr int PF_MB = 8;          // 16-token blocks per tile
+constexpr int PF_MB = 8;          // 16-token blocks per tile (a projection tile's too, whatever the tile)
 
 // Slices of K for a unit whose tiles would each run a long contraction while most of the chip
 // idles: at least 8192 channels on at most 128 tiles (a quarter of the workgroups the chip
@@ -799,8 +810,9 @@ bool prefill_compatible(const glowq_unit& a, const glowq_unit& b) {
 // product, but twice as many workgroups where the large tiles are too few or the last of them
 // would run alone.
 constexpr int PF_HALF_RB = 2;
-static inline int prefill_tile_blocks(int act_dtype, bool half) {
-  if (half) return 4 * PF_HALF_RB;
+static inline int prefill_tile_blocks(int act_dtype, int tile) {
+  if (tile == PF_TILE_WIDE) return WD_BLOCKS;
+  if (tile == PF_TILE_HALF) return 4 * PF_HALF_RB;
   return act_dtype == GLOWQ_F16 ? PfShape<ACT_F16>::TILE_BLOCKS : PfShape<ACT_BF16>::TILE_BLOCKS;
 }
 
@@ -816,15 +828,15 @@ static inline int prefill_tile_blocks(int act_dtype, bool half) {
 struct PrefillCost {
   float start, ends, alone, pair, few, busy, sum;
 };
-static float prefill_cost_of(const glowq_unit* const* units, const int* slices, int n, bool half) {
-  const bool f16 = units[0]->act_dtype == GLOWQ_F16;
+static float prefill_cost_of(const glowq_unit* const* units, const int* slices, int n, int tile) {
+  const bool f16 = units[0]->act_dtype == GLOWQ_F16, half = tile == PF_TILE_HALF;
   const PrefillCost c = half ? (f16 ? PrefillCost{3.48f, 2.50f, 1.09f, 1.45f, 0.79f, 0.88f, 10.9f} : PrefillCost{0.04f, 5.01f, 1.17f, 2.07f, 0.94f, 5.33f, 10.9f})
                              : (f16 ? PrefillCost{1.78f, 4.88f, 1.43f, 3.42f, 0.73f, 0.34f, 0.5f} : PrefillCost{5.46f, 5.94f, 1.59f, 2.87f, 0.82f, 1.08f, 0.5f});
   double work = 0.0, wgs = 0.0;
   int chain = 0, sliced = 0;
   for (int k = 0; k < n; ++k) {
     const glowq_unit& u = *units[k];
-    const int tile_blocks = prefill_tile_blocks(u.act_dtype, half);
+    const int tile_blocks = prefill_tile_blocks(u.act_dtype, tile);
     const int S = slices[k], kt = (u.d_in / 128 + S - 1) / S;
     double tiles = 0.0;
     for (int i = 0; i < u.n_modules; ++i)
@@ -845,10 +857,54 @@ static float prefill_cost_of(const glowq_unit* const* units, const int* slices, 
                                        : std::max((double)c.pair, c.busy * per_cu + 0.8 * c.alone);
   return (float)(c.start + sliced * c.sum + std::max((chain + c.ends) * (double)c.alone, work / wgs * share));
 }
-bool choose_prefill_tile(const glowq_unit* const* units, const int* slices, int n, float* cost) {
-  const float full = prefill_cost_of(units, slices, n, false), half = prefill_cost_of(units, slices, n, true);
+// Wide tiles against large ones, for long contractions: both by one estimate, whose terms are physical enough to
+// compare them.  Per compute unit (two workgroups of a large tile count as one): us per K tile when only few of them
+// work and when all do (the clock falls), `ends` K tiles for a tile's start, correction and stores, `proj` per K
+// tile of a projection workgroup; a last round on part of the chip takes as long as its share of the chip makes it.
+// From 600 calls of 129 to 3000 tokens and of more than 40 us for each (mean error 4 % on wide, 8 % on large tiles).
+struct RoundsCost {
+  float start, ends, few, all, proj, sum;
+};
+static double prefill_rounds_cost(const glowq_unit* const* units, const int* slices, int n, bool wide, double* mean_ktiles) {
+  const bool f16 = units[0]->act_dtype == GLOWQ_F16;
+  const RoundsCost c = wide ? (f16 ? RoundsCost{3.70f, 5.13f, 1.86f, 2.55f, 0.27f, 4.8f} : RoundsCost{4.01f, 5.08f, 1.98f, 2.51f, 0.56f, 4.3f})
+                            : (f16 ? RoundsCost{3.75f, 5.46f, 1.34f, 2.94f, 0.52f, 5.4f} : RoundsCost{3.65f, 4.68f, 1.26f, 2.45f, 0.44f, 7.7f});
+  const int tile_blocks = prefill_tile_blocks(units[0]->act_dtype, wide ? PF_TILE_WIDE : PF_TILE_LARGE);
+  const int tokens = wide ? WD_TOK : 128;
+  const double per_cu = wide ? 1.0 : 2.0;
+  double work = 0.0, proj = 0.0, count = 0.0, ktiles = 0.0;
+  int chain = 0, last = 1 << 30, sliced = 0;
+  for (int k = 0; k < n; ++k) {
+    const glowq_unit& u = *units[k];
+    const int S = slices[k], kt = (u.d_in / 128 + S - 1) / S;
+    double tiles = 0.0;
+    for (int i = 0; i < u.n_modules; ++i)
+      tiles += (double)(((u.modules[i].d_out + 15) / 16 + tile_blocks - 1) / tile_blocks) * ((u.T + tokens - 1) / tokens) * S;
+    // (counted for a unit that is not restored as well, see prefill_cost_of)
+    if (u.r > 0) proj += (double)((u.T + 127) / 128) * std::min(8, (u.d_in + 2047) / 2048) * std::min(u.d_in / 128, 16);
+    work += tiles * (kt + c.ends);
+    count += tiles;
+    ktiles += tiles * kt;
+    chain = std::max(chain, kt);
+    last = std::min(last, kt);
+    sliced += S > 1 ? 1 : 0;
+  }
+  *mean_ktiles = ktiles / count;
+  const double len = last + c.ends, rounds = (work + c.proj * proj) / (per_cu * 256.0 * len), part = rounds - std::floor(rounds + 1e-9);
+  const double full = c.all * (rounds - part) * len + (part > 0.01 ? (c.few + (c.all - c.few) * part) * len : 0.0);
+  const double longest = (chain + c.ends) * (c.few + (c.all - c.few) * std::min(1.0, rounds));
+  return c.start + sliced * c.sum + std::max(longest, full);
+}
+int choose_prefill_tile(const glowq_unit* const* units, const int* slices, int n, float* cost) {
+  const float full = prefill_cost_of(units, slices, n, PF_TILE_LARGE), half = prefill_cost_of(units, slices, n, PF_TILE_HALF);
   *cost = std::min(full, half);
-  return half < 0.95f * full;
+  // Contractions of less than 3072 channels on average keep the smaller tiles: the 12 us that a wide tile's ends take
+  // are not covered by another workgroup's products.  So do calls of less than 384 tokens (one or two token tiles,
+  // where the estimates are not good enough to tell: 9 calls of 131 to 370 tokens lost 6 %).
+  double mean = 0.0;
+  const double wide = prefill_rounds_cost(units, slices, n, true, &mean);
+  if (units[0]->T >= 384 && mean >= 24.0 && wide < 0.95 * prefill_rounds_cost(units, slices, n, false, &mean)) return PF_TILE_WIDE;
+  return half < 0.95f * full ? PF_TILE_HALF : PF_TILE_LARGE;
 }
 
 void plan_prefill_slices(const glowq_unit* const* units, int n, bool slabs, int* slices) {
@@ -869,11 +925,12 @@ int prefill_wait_polls() { return R_WAIT_POLLS; }
 
 // units[i] uses workspace slice ws[i]; restore[i] says whether its R16 is valid.
 hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorkspace* ws,
-                                const bool* restore, int n_units, bool half, const int* slices, hipStream_t st) {
+                                const bool* restore, int n_units, int tile, const int* slices, hipStream_t st) {
   PrefillArgs a;
   const glowq_unit& u0 = *units[0];
   constexpr int MB = PF_MB;
-  const int tile_blocks = prefill_tile_blocks(u0.act_dtype, half);
+  const int tile_blocks = prefill_tile_blocks(u0.act_dtype, tile);
+  const int tile_tokens = tile == PF_TILE_WIDE ? WD_TOK : 16 * MB;
   // longest contraction first
   int order[PF_MAX_UNITS];
   for (int i = 0; i < n_units; ++i) order[i] = i;
@@ -915,7 +972,7 @@ hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorksp
     pu.K = u.d_in;
     pu.r = u.r;
     pu.restore = (restore[ui] && u.r > 0) ? 1 : 0;
-    pu.n_mtiles = (u.T + 16 * MB - 1) / (16 * MB);
+    pu.n_mtiles = (u.T + tile_tokens - 1) / tile_tokens;
     const int S = slices[ui], ktiles = u.d_in / 128;
     float* slab = (S > 1) ? (float*)(wsb + ws[ui].off_splitk) : nullptr;
     for (int i = 0; i < u.n_modules; ++i) {
@@ -954,7 +1011,8 @@ hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorksp
   a.out_f32 = (u0.out_dtype == GLOWQ_F32) ? 1 : 0;
   const bool f16 = (u0.act_dtype == GLOWQ_F16);
   hipError_t err;
-  if (half) err = f16 ? launch_prefill_t<ACT_F16, MB, PF_HALF_RB>(a, wg, u0.group_size, st)
+  if (tile == PF_TILE_WIDE) err = f16 ? launch_wide<ACT_F16>(a, wg, u0.group_size, st) : launch_wide<ACT_BF16>(a, wg, u0.group_size, st);
+  else if (tile == PF_TILE_HALF) err = f16 ? launch_prefill_t<ACT_F16, MB, PF_HALF_RB>(a, wg, u0.group_size, st)
                       : launch_prefill_t<ACT_BF16, MB, PF_HALF_RB>(a, wg, u0.group_size, st);
   else err = f16 ? launch_prefill_t<ACT_F16, MB, PfShape<ACT_F16>::RB>(a, wg, u0.group_size, st)
                  : launch_prefill_t<ACT_BF16, MB, PfShape<ACT_BF16>::RB>(a, wg, u0.group_size, st);

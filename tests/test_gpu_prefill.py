@@ -197,3 +197,39 @@ def test_handoff_in_a_row_and_in_graphs(act):
             side.synchronize()
             assert all(np.array_equal(a, b) for a, b in zip(first, du.outputs())), it
     ws.assert_idle()
+
+
+# the wide tiles (256 x 256): one row block and one token more than a tile, a last token tile of one 128-token
+# projection tile, ragged rows of several modules, both group sizes, one and two stages of ranks
+@pytest.mark.parametrize("T,d_in,d_outs,act,Gs,r", [
+    (1025, 3328, (6152, 6136), "f16", 64, 128), (1025, 3328, (6152, 6136), "bf16", 128, 72),
+    (1281, 3328, (10248,), "f16", 128, 8), (1281, 3328, (10248,), "bf16", 64, 120)])
+def test_wide_tiles_match_the_oracle(T, d_in, d_outs, act, Gs, r):
+    u = make(T, d_in, d_outs, act, Gs, r)
+    refs = {f: O.group_forward(u, f) for f in (True, False)}
+    for restore, out in ((True, "act"), (True, "f32"), (False, "act")):
+        du = DeviceUnit(u, out, 8)
+        route_of(du)
+        assert G.glowq_debug_tile_tokens([du.desc]) == [256]
+        ws = Workspace([du.desc])
+        G.glowq_group_forward(du.desc, restore, ws.ptr, ws.bytes, stream())
+        check(du.outputs(), refs[restore], TOL + (ULP[act] if out == "act" else 0.0))
+        ws.assert_idle()
+
+
+def test_wide_tiles_with_k_slices():
+    # a long contraction in three slices beside an ordinary unit, group size 64; twice through one workspace
+    units = [make(512, 3072, (12288, 12296), "bf16", 64, 24, seed=71), make(512, 12288, (1000,), "bf16", 64, 72, seed=72)]
+    dus = [DeviceUnit(u) for u in units]
+    descs = [d.desc for d in dus]
+    assert G.glowq_debug_tile_tokens(descs) == [256, 256]
+    assert [r.k_slices for r in G.glowq_debug_route(descs)] == [1, 3]
+    ws = Workspace(descs)
+    refs = [O.group_forward(u, True) for u in units]
+    for _ in range(2):
+        for d in dus:
+            d.clear()
+        G.glowq_block_forward(descs, bytes([1, 1]), ws.ptr, ws.bytes, stream())
+        for d, ref in zip(dus, refs):
+            check(d.outputs(), ref, TOL + ULP["bf16"])
+        ws.assert_idle()
