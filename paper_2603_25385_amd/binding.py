@@ -378,10 +378,11 @@ def glowq_probe_stream_read(src: int, nbytes: int, sink: int, stream: int = 0) -
         raise GlowqError(rc, "glowq_probe_stream_read")
 
 
-def glowq_probe_mfma(iters: int, bf16: bool, waves_per_simd: int, sink: int, stream: int = 0) -> float:
-    """Returns the floating-point operations of the launch."""
+def glowq_probe_mfma(iters: int, bf16: int, waves_per_simd: int, sink: int, stream: int = 0) -> float:
+    """Returns the floating-point operations of the launch.  bf16: the loop, numbered as in glowq_probe.h
+    (False and True are binary16 and bfloat16)."""
     fl = ctypes.c_double(0.0)
-    rc = _lib.glowq_probe_mfma(iters, 1 if bf16 else 0, waves_per_simd, sink or None,
+    rc = _lib.glowq_probe_mfma(iters, int(bf16), waves_per_simd, sink or None,
                                ctypes.byref(fl), stream or None)
     if rc != 0:
         raise GlowqError(rc, "glowq_probe_mfma")

@@ -267,3 +267,19 @@ def test_mx_argument_checks():
         with pytest.raises(G.GlowqError) as e:
             G.glowq_mx_group_forward(_unit(group_size=0, **{"T": 16, **kw}), 1, *args)
         assert e.value.status == status, (kw, args)
+
+
+@pytest.mark.parametrize("kind", [False, True, 0, 1, 2, 3, 4])
+def test_matrix_probe_runs_the_loop_that_was_asked_for(kind, monkeypatch):
+    # 2 to 4 are the block-scaled instruction; they must not arrive as the bfloat16 loop
+    seen = []
+
+    class Library:
+        @staticmethod
+        def glowq_probe_mfma(iters, loop, waves, sink, flops, stream):
+            seen.append((iters, loop, waves))
+            return 0
+
+    monkeypatch.setattr("paper_2603_25385_amd.binding._lib", Library)
+    G.glowq_probe_mfma(5, kind, 2, 0x1000)
+    assert seen == [(5, int(kind), 2)]
