@@ -17,7 +17,6 @@
 // four consecutive rows of one token and stores them with one 8- or 16-byte write.
 #include <type_traits>
 #include <algorithm>
-#include <cmath>
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -815,6 +814,12 @@ static inline int prefill_tile_blocks(int act_dtype, int tile) {
   if (tile == PF_TILE_HALF) return 4 * PF_HALF_RB;
   return act_dtype == GLOWQ_F16 ? PfShape<ACT_F16>::TILE_BLOCKS : PfShape<ACT_BF16>::TILE_BLOCKS;
 }
+// workgroup tiles of a unit (of one of its K slices)
+static inline long long prefill_tiles(const glowq_unit& u, int tile_blocks, int tokens) {
+  long long rows = 0;
+  for (int i = 0; i < u.n_modules; ++i) rows += ((u.modules[i].d_out + 15) / 16 + tile_blocks - 1) / tile_blocks;
+  return rows * ((u.T + tokens - 1) / tokens);
+}
 
 // What one launch over these units is taken to cost, in the same terms as the batched kernel's
 // tiles (BATCH_TILES), in us per K tile: for a workgroup alone on its compute unit, for two sharing
@@ -838,9 +843,7 @@ static float prefill_cost_of(const glowq_unit* const* units, const int* slices, 
     const glowq_unit& u = *units[k];
     const int tile_blocks = prefill_tile_blocks(u.act_dtype, tile);
     const int S = slices[k], kt = (u.d_in / 128 + S - 1) / S;
-    double tiles = 0.0;
-    for (int i = 0; i < u.n_modules; ++i)
-      tiles += (double)(((u.modules[i].d_out + 15) / 16 + tile_blocks - 1) / tile_blocks) * ((u.T + 127) / 128) * S;
+    const double tiles = (double)prefill_tiles(u, tile_blocks, 128) * S;
     // (the projection's workgroups, about 2048 channels each, hold their places beside the tiles; counted
     // for a unit that is not restored as well, so that the choice, and with it the bits of a unit's
     // outputs, do not depend on the mask)
@@ -857,43 +860,98 @@ static float prefill_cost_of(const glowq_unit* const* units, const int* slices, 
                                        : std::max((double)c.pair, c.busy * per_cu + 0.8 * c.alone);
   return (float)(c.start + sliced * c.sum + std::max((chain + c.ends) * (double)c.alone, work / wgs * share));
 }
-// Wide tiles against large ones, for long contractions: both by one estimate, whose terms are physical enough to
-// compare them.  Per compute unit (two workgroups of a large tile count as one): us per K tile when only few of them
-// work and when all do (the clock falls), `ends` K tiles for a tile's start, correction and stores, `proj` per K
-// tile of a projection workgroup; a last round on part of the chip takes as long as its share of the chip makes it.
-// From 600 calls of 129 to 3000 tokens and of more than 40 us for each (mean error 4 % on wide, 8 % on large tiles).
-struct RoundsCost {
-  float start, ends, few, all, proj, sum;
+// The units of a launch, longest contraction first
+static void longest_first(const glowq_unit* const* units, int n, int* order) {
+  for (int i = 0; i < n; ++i) order[i] = i;
+  for (int i = 1; i < n; ++i)
+    for (int j = i; j > 0 && units[order[j]]->d_in > units[order[j - 1]]->d_in; --j) std::swap(order[j], order[j - 1]);
+}
+// When the chip's places come free: workgroups start in launch order, each on the place that is free first.
+struct Places {
+  static constexpr int MOST = 512;
+  struct { double free; int count; } at[MOST];      // by time; the counts add up to `places`
+  int n = 1, places;
+  explicit Places(int p) : places(p) { at[0] = {0.0, p}; }
+  void run(long long wgs, double length) {
+    while (wgs > 0) {
+      if (wgs >= places && at[n - 1].free - at[0].free <= length) {      // one on every place
+        const long long rounds = wgs / places;
+        for (int i = 0; i < n; ++i) at[i].free += rounds * length;
+        wgs -= rounds * places;
+        continue;
+      }
+      const int take = (int)std::min<long long>(wgs, at[0].count);
+      const double end = at[0].free + length;
+      if (take == at[0].count) std::move(at + 1, at + n--, at);
+      else at[0].count -= take;
+      int i = n;
+      while (i > 0 && at[i - 1].free > end + 1e-6) --i;
+      if (i > 0 && at[i - 1].free > end - 1e-6) at[i - 1].count += take;
+      else {
+        std::move_backward(at + i, at + n, at + n + 1);
+        at[i] = {end, take};
+        ++n;
+      }
+      wgs -= take;
+    }
+  }
 };
-static double prefill_rounds_cost(const glowq_unit* const* units, const int* slices, int n, bool wide, double* mean_ktiles) {
-  const bool f16 = units[0]->act_dtype == GLOWQ_F16;
-  const RoundsCost c = wide ? (f16 ? RoundsCost{3.70f, 5.13f, 1.86f, 2.55f, 0.27f, 4.8f} : RoundsCost{4.01f, 5.08f, 1.98f, 2.51f, 0.56f, 4.3f})
-                            : (f16 ? RoundsCost{3.75f, 5.46f, 1.34f, 2.94f, 0.52f, 5.4f} : RoundsCost{3.65f, 4.68f, 1.26f, 2.45f, 0.44f, 7.7f});
-  const int tile_blocks = prefill_tile_blocks(units[0]->act_dtype, wide ? PF_TILE_WIDE : PF_TILE_LARGE);
-  const int tokens = wide ? WD_TOK : 128;
-  const double per_cu = wide ? 1.0 : 2.0;
-  double work = 0.0, proj = 0.0, count = 0.0, ktiles = 0.0;
-  int chain = 0, last = 1 << 30, sliced = 0;
+// Wide tiles against the smaller ones, for long contractions: all by one estimate, which fills the chip's places (one
+// per compute unit, two for large and half-size tiles) as the launch does: projection workgroups first, then tiles,
+// longest first.  Us per K tile of a place: `all` when all work; as places stay empty, `few` and `slope` up to half of
+// them and from `pair` on beyond, where compute units hold two (the clock falls throughout); `g64` times that with
+// groups of 64.  `ends` K tiles for a tile's start, correction and stores (`ends64` more past 64 ranks,
+// `ends32` for 32-bit outputs), `proj` us per K tile of a projection workgroup and `proj_ends` beside them.
+// Projection workgroups have to be places: with them as a little more work, 204 tiles + 72 projection workgroups
+// counted as one round of 256 (2969 tokens x 4104 rows x 4224: 137 us on wide tiles, 112 on large ones).
+// From 10000 calls of 384 to 3000 tokens and 2800 channels and more (mean error: wide 3 %, large 4, half-size 5).  Of 2900
+// others 714 take wide tiles: 10.5 % faster than the better of the smaller ones; 29 lose more than 3 %, 2 more than 8 %.
+struct PlacesCost {
+  float start, ends, ends64, ends32, few, slope, pair, all, proj, proj_ends, proj_ends64, sum, g64;
+};
+constexpr PlacesCost PLACES_COST[2][3] = {      // binary16, bfloat16; PF_TILE_LARGE, _HALF, _WIDE
+    {{3.91f, 4.18f, 2.34f, 0.00f, 1.39f, 0.71f, 2.46f, 3.08f, 5.37f, 0.74f, 0.08f, 6.39f, 1.04f},
+     {5.32f, 4.38f, 2.99f, 0.00f, 0.87f, 0.33f, 1.38f, 1.75f, 3.95f, 1.52f, 1.01f, 6.22f, 1.05f},
+     {0.00f, 5.54f, 1.13f, 0.73f, 1.87f, 0.76f, 2.25f, 2.63f, 2.29f, 7.60f, 8.52f, 4.78f, 1.00f}},
+    {{5.97f, 3.69f, 2.51f, 0.00f, 1.26f, 0.46f, 2.00f, 2.50f, 4.94f, 0.00f, 1.25f, 5.80f, 1.04f},
+     {6.24f, 3.73f, 3.18f, 0.00f, 0.94f, 0.31f, 1.51f, 1.80f, 2.61f, 9.04f, 0.03f, 5.46f, 1.03f},
+     {0.00f, 6.18f, 0.80f, 0.76f, 1.97f, 0.62f, 2.28f, 2.59f, 2.14f, 5.79f, 16.74f, 4.68f, 1.00f}}};
+static double prefill_places_cost(const glowq_unit* const* units, const int* slices, int n, int tile) {
+  const PlacesCost& c = PLACES_COST[units[0]->act_dtype == GLOWQ_F16 ? 0 : 1][tile];
+  const int tile_blocks = prefill_tile_blocks(units[0]->act_dtype, tile), tokens = tile == PF_TILE_WIDE ? WD_TOK : 128;
+  Places chip(tile == PF_TILE_WIDE ? 256 : 512);
+  int order[PF_MAX_UNITS], sliced = 0;
+  longest_first(units, n, order);
+  // (counted for a unit that is not restored as well, see prefill_cost_of)
   for (int k = 0; k < n; ++k) {
-    const glowq_unit& u = *units[k];
-    const int S = slices[k], kt = (u.d_in / 128 + S - 1) / S;
-    double tiles = 0.0;
-    for (int i = 0; i < u.n_modules; ++i)
-      tiles += (double)(((u.modules[i].d_out + 15) / 16 + tile_blocks - 1) / tile_blocks) * ((u.T + tokens - 1) / tokens) * S;
-    // (counted for a unit that is not restored as well, see prefill_cost_of)
-    if (u.r > 0) proj += (double)((u.T + 127) / 128) * std::min(8, (u.d_in + 2047) / 2048) * std::min(u.d_in / 128, 16);
-    work += tiles * (kt + c.ends);
-    count += tiles;
-    ktiles += tiles * kt;
-    chain = std::max(chain, kt);
-    last = std::min(last, kt);
+    const glowq_unit& u = *units[order[k]];
+    const int parts = std::min(8, (u.d_in + 2047) / 2048), kt = (u.d_in / 128 + parts - 1) / parts;
+    if (u.r > 0) chip.run((long long)((u.T + 127) / 128) * parts, (c.proj * kt + c.proj_ends + (u.r > 64 ? c.proj_ends64 : 0.f)) / c.all);
+  }
+  for (int k = 0; k < n; ++k) {
+    const glowq_unit& u = *units[order[k]];
+    const int S = slices[order[k]], kt = (u.d_in / 128 + S - 1) / S;
+    const float ends = c.ends + (u.r > 64 ? c.ends64 : 0.f) + (u.out_dtype == GLOWQ_F32 ? c.ends32 : 0.f);
+    chip.run(prefill_tiles(u, tile_blocks, tokens) * S, kt * (u.group_size == 64 ? c.g64 : 1.f) + ends);
     sliced += S > 1 ? 1 : 0;
   }
-  *mean_ktiles = ktiles / count;
-  const double len = last + c.ends, rounds = (work + c.proj * proj) / (per_cu * 256.0 * len), part = rounds - std::floor(rounds + 1e-9);
-  const double full = c.all * (rounds - part) * len + (part > 0.01 ? (c.few + (c.all - c.few) * part) * len : 0.0);
-  const double longest = (chain + c.ends) * (c.few + (c.all - c.few) * std::min(1.0, rounds));
-  return c.start + sliced * c.sum + std::max(longest, full);
+  const double full = chip.at[0].free, tail = chip.at[chip.n - 1].free - full;
+  double rest = 0.0;
+  for (int i = 0; i < chip.n; ++i) rest += (chip.at[i].free - full) * chip.at[i].count;
+  const double busy = tail > 0.0 ? rest / (tail * chip.places) : 0.0;
+  const double rate = busy <= 0.5 ? c.few + c.slope * busy : std::max(c.few + 0.5 * c.slope, c.pair + (c.all - c.pair) * (2.0 * busy - 1.0));
+  return c.start + sliced * c.sum + c.all * full + rate * tail;
+}
+// K tiles of a launch's wide tiles, on average
+static double prefill_mean_ktiles(const glowq_unit* const* units, const int* slices, int n) {
+  double tiles = 0.0, ktiles = 0.0;
+  for (int k = 0; k < n; ++k) {
+    const int S = slices[k];
+    const double t = (double)prefill_tiles(*units[k], WD_BLOCKS, WD_TOK) * S;
+    tiles += t;
+    ktiles += t * ((units[k]->d_in / 128 + S - 1) / S);
+  }
+  return ktiles / tiles;
 }
 int choose_prefill_tile(const glowq_unit* const* units, const int* slices, int n, float* cost) {
   const float full = prefill_cost_of(units, slices, n, PF_TILE_LARGE), half = prefill_cost_of(units, slices, n, PF_TILE_HALF);
@@ -901,9 +959,10 @@ int choose_prefill_tile(const glowq_unit* const* units, const int* slices, int n
   // Contractions of less than 3072 channels on average keep the smaller tiles: the 12 us that a wide tile's ends take
   // are not covered by another workgroup's products.  So do calls of less than 384 tokens (one or two token tiles,
   // where the estimates are not good enough to tell: 9 calls of 131 to 370 tokens lost 6 %).
-  double mean = 0.0;
-  const double wide = prefill_rounds_cost(units, slices, n, true, &mean);
-  if (units[0]->T >= 384 && mean >= 24.0 && wide < 0.95 * prefill_rounds_cost(units, slices, n, false, &mean)) return PF_TILE_WIDE;
+  if (units[0]->T >= 384 && prefill_mean_ktiles(units, slices, n) >= 24.0 &&
+      prefill_places_cost(units, slices, n, PF_TILE_WIDE) < std::min(prefill_places_cost(units, slices, n, PF_TILE_LARGE),
+                                                                     prefill_places_cost(units, slices, n, PF_TILE_HALF)))
+    return PF_TILE_WIDE;
   return half < 0.95f * full ? PF_TILE_HALF : PF_TILE_LARGE;
 }
 
@@ -933,11 +992,7 @@ hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorksp
   const int tile_tokens = tile == PF_TILE_WIDE ? WD_TOK : 16 * MB;
   // longest contraction first
   int order[PF_MAX_UNITS];
-  for (int i = 0; i < n_units; ++i) order[i] = i;
-  for (int i = 1; i < n_units; ++i)
-    for (int j = i; j > 0 && units[order[j]]->d_in > units[order[j - 1]]->d_in; --j) {
-      int t = order[j]; order[j] = order[j - 1]; order[j - 1] = t;
-    }
+  longest_first(units, n_units, order);
   // projection tiles of the restored units lead the grid
   int n_proj = 0;
   for (int oi = 0; oi < n_units; ++oi) {

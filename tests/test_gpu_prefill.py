@@ -200,10 +200,12 @@ def test_handoff_in_a_row_and_in_graphs(act):
 
 
 # the wide tiles (256 x 256): one row block and one token more than a tile, a last token tile of one 128-token
-# projection tile, ragged rows of several modules, both group sizes, one and two stages of ranks
+# projection tile, ragged rows of several modules, both group sizes, one and two stages of ranks.  Tiles and
+# projection workgroups stay within the chip's 256 places (6136 and 10248 rows in place of 5624 and 9224 are one tile
+# too many: 106 to 123 us on wide tiles, 90 to 104 on the smaller ones that such calls take)
 @pytest.mark.parametrize("T,d_in,d_outs,act,Gs,r", [
-    (1025, 3328, (6152, 6136), "f16", 64, 128), (1025, 3328, (6152, 6136), "bf16", 128, 72),
-    (1281, 3328, (10248,), "f16", 128, 8), (1281, 3328, (10248,), "bf16", 64, 120)])
+    (1025, 3328, (6152, 5624), "f16", 64, 128), (1025, 3328, (6152, 5624), "bf16", 128, 72),
+    (1281, 3328, (9224,), "f16", 128, 8), (1281, 3328, (9224,), "bf16", 64, 120)])
 def test_wide_tiles_match_the_oracle(T, d_in, d_outs, act, Gs, r):
     u = make(T, d_in, d_outs, act, Gs, r)
     refs = {f: O.group_forward(u, f) for f in (True, False)}

@@ -132,6 +132,42 @@ def test_calls_keep_their_speed(T, d_in, d_outs, act, out, r, Gs, good):
     assert name in good.split()
 
 
+def tile_tokens(units):
+    return set(G.glowq_debug_tile_tokens(units))
+
+
+def decoder_layers(hidden, kv, inter, layers, T, r, act, Gs=128):
+    shapes = [(hidden, (hidden, kv, kv)), (hidden, (hidden,)), (hidden, (inter, inter)), (inter, (hidden,))] * layers
+    return [unit(T, d, outs, r=r, Gs=Gs, act=act, out=act) for d, outs in shapes]
+
+
+# The projection's workgroups hold places of their own: calls whose wide tiles would fit one round (or a whole number)
+# without them, and do not beside them (us on wide tiles, on tiles of 128 tokens)
+@pytest.mark.parametrize("T,d_in,d_outs,act,out,r,Gs", [
+    (2969, 4224, (4104,), "f16", "act", 128, 128),       # 137.4, 112.3: 204 tiles and 72 projection workgroups
+    (1522, 3840, (3256,) * 3, "f16", "act", 16, 128),    # 127.8, 107.2
+    (1678, 3456, (4288,) * 2, "f16", "f32", 128, 64),    # 128.0, 108.5
+    (1066, 3968, (12328,), "f16", "f32", 128, 64),       # 137.3, 117.5
+    (2989, 5376, (2184,) * 2, "f16", "f32", 64, 128),    # 162.2, 139.6
+    (1821, 4480, (2120,) * 3, "f16", "f32", 64, 64),     # 136.7, 122.0
+    (2145, 4352, (2936,) * 2, "f16", "f32", 128, 64)])   # 139.9, 129.2
+def test_no_wide_tiles_where_the_projection_fills_the_round(T, d_in, d_outs, act, out, r, Gs):
+    a = {"f16": G.GLOWQ_F16, "bf16": G.GLOWQ_BF16}[act]
+    assert tile_tokens([unit(T, d_in, d_outs, r=r, Gs=Gs, act=a, out=a if out == "act" else G.GLOWQ_F32)]) == {128}
+
+
+def test_no_wide_tiles_where_their_rounds_come_out_uneven():
+    # tiles of several lengths, whose rounds are not those of one length (us on wide tiles, on tiles of 128 tokens)
+    assert tile_tokens(decoder_layers(4352, 4352, 2944, 1, 761, 16, G.GLOWQ_BF16)) == {128}      # 183.9, 166.4
+    assert tile_tokens(decoder_layers(3968, 3968, 12288, 2, 521, 128, G.GLOWQ_F16)) == {128}     # 529.4, 487.5
+
+
+def test_wide_tiles_where_they_are_faster():
+    assert tile_tokens([unit(2048, 4096, (11008,) * 2, r=64, act=G.GLOWQ_BF16, out=G.GLOWQ_BF16)]) == {256}
+    assert tile_tokens(decoder_layers(4096, 1024, 14336, 1, 512, 128, G.GLOWQ_F16)) == {256}
+    assert tile_tokens(decoder_layers(5120, 5120, 13824, 4, 1000, 64, G.GLOWQ_F16)) == {256}
+
+
 # calls of the microscaling variant that were slower on small tiles (us on tiles 0 .. 4)
 @pytest.mark.parametrize("T,d_in,d_outs,act,out", [
     (1931, 896, (8680,) * 3, "f16", "f32"),          # 99.8 .. 128.1 on tile 4
