@@ -959,10 +959,14 @@ int choose_prefill_tile(const glowq_unit* const* units, const int* slices, int n
   // Contractions of less than 3072 channels on average keep the smaller tiles: the 12 us that a wide tile's ends take
   // are not covered by another workgroup's products.  So do calls of less than 384 tokens (one or two token tiles,
   // where the estimates are not good enough to tell: 9 calls of 131 to 370 tokens lost 6 %).
-  if (units[0]->T >= 384 && prefill_mean_ktiles(units, slices, n) >= 24.0 &&
-      prefill_places_cost(units, slices, n, PF_TILE_WIDE) < std::min(prefill_places_cost(units, slices, n, PF_TILE_LARGE),
-                                                                     prefill_places_cost(units, slices, n, PF_TILE_HALF)))
-    return PF_TILE_WIDE;
+  if (units[0]->T >= 384 && prefill_mean_ktiles(units, slices, n) >= 24.0) {
+    const double wide = prefill_places_cost(units, slices, n, PF_TILE_WIDE);
+    const double small = std::min(prefill_places_cost(units, slices, n, PF_TILE_LARGE), prefill_places_cost(units, slices, n, PF_TILE_HALF));
+    if (wide < small) {
+      *cost = (float)wide;      // (what the batched kernel has to beat: 420 tokens x 2 x 8744 rows x 3968 97.6 us there, 78.3 here)
+      return PF_TILE_WIDE;
+    }
+  }
   return half < 0.95f * full ? PF_TILE_HALF : PF_TILE_LARGE;
 }
 

@@ -168,6 +168,19 @@ def test_wide_tiles_where_they_are_faster():
     assert tile_tokens(decoder_layers(5120, 5120, 13824, 4, 1000, 64, G.GLOWQ_F16)) == {256}
 
 
+# The batched kernel has to beat the tile that the call would take (us on wide tiles, on the batched kernel)
+@pytest.mark.parametrize("T,d_in,d_outs,out,r,Gs", [
+    (420, 3968, (8744,) * 2, "act", 128, 128),      # 78.3, 97.6
+    (385, 6528, (5512,) * 3, "f32", 128, 64),       # 119.3, 144.3
+    (394, 4224, (8712,) * 2, "f32", 128, 128),      # 87.1, 104.1
+    (388, 3456, (5784,) * 3, "f32", 16, 64),        # 72.9, 82.5
+    (407, 7296, (5760,) * 3, "f32", 16, 128),       # 134.7, 149.2
+    (428, 5888, (8464,) * 2, "act", 64, 128)])      # 111.9, 121.4
+def test_the_batched_kernel_is_compared_with_the_chosen_tile(T, d_in, d_outs, out, r, Gs):
+    u = unit(T, d_in, d_outs, r=r, Gs=Gs, out=G.GLOWQ_F16 if out == "act" else G.GLOWQ_F32)
+    assert tile_tokens([u]) == {256}
+
+
 # calls of the microscaling variant that were slower on small tiles (us on tiles 0 .. 4)
 @pytest.mark.parametrize("T,d_in,d_outs,act,out", [
     (1931, 896, (8680,) * 3, "f16", "f32"),          # 99.8 .. 128.1 on tile 4
