@@ -942,24 +942,30 @@ static double prefill_places_cost(const glowq_unit* const* units, const int* sli
   const double rate = busy <= 0.5 ? c.few + c.slope * busy : std::max(c.few + 0.5 * c.slope, c.pair + (c.all - c.pair) * (2.0 * busy - 1.0));
   return c.start + sliced * c.sum + c.all * full + rate * tail;
 }
-// K tiles of a launch's wide tiles, on average
-static double prefill_mean_ktiles(const glowq_unit* const* units, const int* slices, int n) {
-  double tiles = 0.0, ktiles = 0.0;
+// K tiles of a launch's wide tiles, on average, and the tokens of the call that an average K tile belongs to
+struct WideMeans {
+  double ktiles, tokens;
+};
+static WideMeans prefill_wide_means(const glowq_unit* const* units, const int* slices, int n) {
+  double tiles = 0.0, ktiles = 0.0, tokens = 0.0;
   for (int k = 0; k < n; ++k) {
     const int S = slices[k];
-    const double t = (double)prefill_tiles(*units[k], WD_BLOCKS, WD_TOK) * S;
+    const double t = (double)prefill_tiles(*units[k], WD_BLOCKS, WD_TOK) * S, work = t * ((units[k]->d_in / 128 + S - 1) / S);
     tiles += t;
-    ktiles += t * ((units[k]->d_in / 128 + S - 1) / S);
+    ktiles += work;
+    tokens += work * units[k]->T;
   }
-  return ktiles / tiles;
+  return WideMeans{ktiles / tiles, tokens / ktiles};
 }
 int choose_prefill_tile(const glowq_unit* const* units, const int* slices, int n, float* cost) {
   const float full = prefill_cost_of(units, slices, n, PF_TILE_LARGE), half = prefill_cost_of(units, slices, n, PF_TILE_HALF);
   *cost = std::min(full, half);
   // Contractions of less than 3072 channels on average keep the smaller tiles: the 12 us that a wide tile's ends take
   // are not covered by another workgroup's products.  So do calls of less than 384 tokens (one or two token tiles,
-  // where the estimates are not good enough to tell: 9 calls of 131 to 370 tokens lost 6 %).
-  if (units[0]->T >= 384 && prefill_mean_ktiles(units, slices, n) >= 24.0) {
+  // where the estimates are not good enough to tell: 9 calls of 131 to 370 tokens lost 6 %).  Both by the launch's
+  // work, so that the order of its units does not matter.
+  const WideMeans mean = prefill_wide_means(units, slices, n);
+  if (mean.tokens >= 384.0 && mean.ktiles >= 24.0) {
     const double wide = prefill_places_cost(units, slices, n, PF_TILE_WIDE);
     const double small = std::min(prefill_places_cost(units, slices, n, PF_TILE_LARGE), prefill_places_cost(units, slices, n, PF_TILE_HALF));
     if (wide < small) {

@@ -235,3 +235,27 @@ def test_wide_tiles_with_k_slices():
         for d, ref in zip(dus, refs):
             check(d.outputs(), ref, TOL + ULP["bf16"])
         ws.assert_idle()
+
+
+def long_units(act, Gs):
+    # an odd number of K tiles, a unit of one K tile, fewer tokens (a last token tile of 188 of 256), two stages of ranks
+    return [make(1025, 5248, (6152, 4360), act, Gs, 72, seed=81), make(1025, 128, (264, 40), act, Gs, 8, seed=82),
+            make(700, 3328, (2056,), act, Gs, 128, seed=83)]
+
+
+@pytest.mark.parametrize("act", ["f16", "bf16"])
+def test_wide_tiles_with_units_of_several_lengths(act):
+    units = long_units(act, 128)
+    dus = [DeviceUnit(u) for u in units]
+    refs = {f: [O.group_forward(u, f) for u in units] for f in (True, False)}
+    for order, mask in (((0, 1, 2), (1, 1, 1)), ((2, 1, 0), (1, 1, 1)), ((0, 1, 2), (1, 0, 1)), ((2, 1, 0), (0, 1, 1))):
+        descs = [dus[k].desc for k in order]
+        assert G.glowq_debug_tile_tokens(descs) == [256] * 3
+        assert all(r.launch == 0 for r in G.glowq_debug_route(descs))
+        ws = Workspace(descs)
+        for k in order:
+            dus[k].clear()
+        G.glowq_block_forward(descs, bytes(mask), ws.ptr, ws.bytes, stream())
+        for k, f in zip(order, mask):
+            check(dus[k].outputs(), refs[bool(f)][k], TOL)
+        ws.assert_idle()

@@ -168,6 +168,20 @@ def test_wide_tiles_where_they_are_faster():
     assert tile_tokens(decoder_layers(5120, 5120, 13824, 4, 1000, 64, G.GLOWQ_F16)) == {256}
 
 
+def test_the_order_of_units_does_not_decide_the_tile():
+    # units of several token counts in one launch: what most of its work belongs to decides, first or last
+    for act in (G.GLOWQ_F16, G.GLOWQ_BF16):
+        def of(T, rows):
+            return unit(T, 4096, rows, r=64, act=act, out=act)
+
+        for units, tokens in (([of(2048, (14336,) * 2), of(1024, (14336,) * 2), of(70, (1024,))], 256),
+                              ([of(2048, (1024,)), of(70, (32768,) * 3)], 128)):
+            for u in (units, units[::-1]):
+                routes = G.glowq_debug_route(u)
+                assert {r.launch for r in routes} == {0} and {r.kernel for r in routes} == {G.GLOWQ_ROUTE_TILED}
+                assert tile_tokens(u) == {tokens}
+
+
 # The batched kernel has to beat the tile that the call would take (us on wide tiles, on the batched kernel)
 @pytest.mark.parametrize("T,d_in,d_outs,out,r,Gs", [
     (420, 3968, (8744,) * 2, "act", 128, 128),      # 78.3, 97.6
