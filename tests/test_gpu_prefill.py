@@ -173,13 +173,38 @@ def test_multiplies_with_the_stored_weight(act, d_out, tile, Gs):
     assert not y[rest].any()
 
 
+@pytest.mark.parametrize("Gs", [128, 64])
 @pytest.mark.parametrize("act", ["f16", "bf16"])
-def test_handoff_in_a_row_and_in_graphs(act):
+def test_wide_tiles_multiply_with_the_stored_weight(act, Gs):
+    # the identity: every output is one weight as k_wide's dequantiser made it; 25 K tiles, ragged rows and tokens
+    d_in, d_out = 3200, 4104
+    rng = np.random.default_rng(4)
+    q = rng.integers(0, 16, size=(d_out, d_in)).astype(np.uint8)
+    s_bits = rng.integers(1, 0x6C00, size=(d_out, d_in // Gs)).astype(np.uint16)
+    z_bits = O.f64_to_bits(rng.integers(0, 16, size=(d_out, d_in // Gs)).astype(np.float64), "f16")
+    X = np.zeros((d_in, d_in), np.uint16)
+    np.fill_diagonal(X, O.f64_to_bits(np.ones(1), act)[0])
+    du = DeviceUnit(dict(act=act, G=Gs, r=0, d_in=d_in, B=None, X=X,
+                         modules=[dict(wq=O.pack_int4(q), scales=s_bits, zeros=z_bits, A=None)]))
+    route_of(du)
+    assert G.glowq_debug_tile_tokens([du.desc]) == [256]
+    ws = Workspace([du.desc])
+    G.glowq_group_forward(du.desc, False, ws.ptr, ws.bytes, stream())
+    seen = du.outputs()[0].T
+    ref = O.bits_to_f64(O.dequant_bits(q, s_bits, z_bits, Gs, act), act)
+    bad = np.argwhere(seen != ref)
+    assert bad.size == 0, (bad[:5], seen[tuple(bad[0])], ref[tuple(bad[0])])
+
+
+@pytest.mark.parametrize("T,d_in,d_outs,tokens", [(2056, 2304, (72, 40), 128), (1025, 4352, (10248,), 256)])
+@pytest.mark.parametrize("act", ["f16", "bf16"])
+def test_handoff_in_a_row_and_in_graphs(act, T, d_in, d_outs, tokens):
     # the projection's parts, its flags and their consumers back to back: 200 launches, half of them
     # replays of a captured call with eager calls in between, every result equal to the first one's bits
-    u = make(2056, 2304, (72, 40), act)
+    u = make(T, d_in, d_outs, act)
     du = DeviceUnit(u)
     route_of(du)
+    assert G.glowq_debug_tile_tokens([du.desc]) == [tokens]
     ws = Workspace([du.desc])
     side = torch.cuda.Stream()
     graph = torch.cuda.CUDAGraph()
@@ -259,3 +284,25 @@ def test_wide_tiles_with_units_of_several_lengths(act):
         for k, f in zip(order, mask):
             check(dus[k].outputs(), refs[bool(f)][k], TOL)
         ws.assert_idle()
+
+
+@pytest.mark.parametrize("Gs", [128, 64])
+@pytest.mark.parametrize("act", ["f16", "bf16"])
+def test_wide_tiles_give_the_bits_of_the_128_token_tiles(act, Gs):
+    # the same units beside one of a single K tile that moves the launch to the smaller tiles; R's partial sums, both
+    # output types, one unit masked
+    units = long_units(act, Gs)
+    extra = make(1025, 128, (12288,), act, Gs, 8, seed=84)
+    for out in ("act", "f32"):
+        dus = [DeviceUnit(u, out) for u in units]
+        short = DeviceUnit(extra, out)
+        seen = []
+        for descs, tokens in (([d.desc for d in dus], 256), ([d.desc for d in dus] + [short.desc], 128)):
+            assert G.glowq_debug_tile_tokens(descs) == [tokens] * len(descs)
+            ws = Workspace(descs)
+            for d in dus:
+                d.clear()
+            G.glowq_block_forward(descs, bytes([1, 0, 1, 1][:len(descs)]), ws.ptr, ws.bytes, stream())
+            seen.append([y for d in dus for y in d.outputs()])
+            ws.assert_idle()
+        assert all(np.isfinite(a).all() and np.array_equal(a, b) for a, b in zip(*seen))
