@@ -558,14 +558,14 @@ __global__ void __launch_bounds__(256, 4) k_mx_decode_small(MxArgs a, ProjArgs p
 // multiplies step k, waits for its own loads and meets the others at one barrier.  No
 // register holds staged data, three workgroups share a CU.  (Three buffers with the loads
 // two steps ahead, two workgroups per CU: no faster.)  Smaller tiles for launches that this one would not fill:
-// k_mx_tile, see choose_mx_tile.  What bounds it: the instruction itself delivers 4.6 PFLOP/s from
-// registers (32 cycles for fp8 x fp4), this loop 2.2: waves of 64 x 64 read 96 of the 128 bytes that LDS
-// delivers a cycle, and the clock falls to 1.6 to 1.85 GHz under the load.  Tiles of 256 x 256 (256
+// k_mx_tile, see choose_mx_tile.  What bounds it: the instruction itself delivers 4.9 PFLOP/s from
+// registers (32 cycles for fp8 x fp4), this kernel 2.07: waves of 64 x 64 read 96 of the 128 bytes that LDS
+// delivers a cycle (matrix pipe busy 0.55), and the clock falls to 1.8 GHz under the load.  Tiles of 256 x 256 (256
 // accumulation registers, one wave per SIMD, a ring of three, workgroups that go from tile to tile) gain 4 % here and
 // up to 15 % on several times the work, and lose as much where their rounds come out uneven: not kept.
 // Weights are the first operand, so that a lane ends up with four rows of one token; two row blocks' rows are
 // exchanged between lane groups so that sixteen tokens' stores are 64 bytes each (2-byte stores, 32 bytes a
-// row: 2 x 11008 rows x 4096 at 2048 tokens 207 -> 184 us with it).  Both tiles sit
+// row: the call with 2 x 11008 rows x 4096 at 2048 tokens 210 -> 200 us with it).  Both tiles sit
 // in LDS in fragment order, so that a wave's
 // fragment read is 1 KiB lane after lane (no bank conflict by construction): the weight tile
 // is the prepared layout as it is in memory; the activation tile is [token block][half]
@@ -670,7 +670,7 @@ __global__ void __launch_bounds__(256) k_mx_gemm(MxGemmArgs a) {
     vm_wait<0>();          // this wave's loads of the next step have landed ...
     __syncthreads();       // ... and everybody's; everybody is done reading this step's buffer
   }
-  // correction: + R A_i^T (token rows as A, weight rows as B; lane (i, g): ranks 32 s + 8 g .. + 8)
+  // correction: + R A_i^T (weight rows as the first operand, as above; lane (i, g): ranks 32 s + 8 g .. + 8)
   if (a.R16) {
     for (int s = 0; 32 * s < a.r; ++s) {
       const int j0 = 32 * s + 8 * g;
@@ -964,10 +964,10 @@ MxWorkspace plan_mx_workspace(const glowq_unit& u) {
 // stores weigh `ends` K tiles, `ends32` more where 32-bit outputs are stored.  A launch takes the longer
 // of the two for each K tile of its contraction; past what the chip holds at once the last round is
 // partly empty.  Tile 0 is k_mx_gemm's and stays where no other one is clearly cheaper.
-// Fitted to 310 calls of 17 to 2048 tokens on every tile: the choice is 1.1 % above the best tile on
-// average and one call is slower than on tile 0 by more than 1.5 % (4 %); with one `ends` for all
-// tiles, from 50 calls, it was 4.2 % above, and 8 calls of 220 were slower by up to 28 % (1931 tokens x
-// 3 x 8680 rows x 896, 32-bit outputs: 99.8 us on tile 0, 128.1 on tile 4).
+// Fitted to 310 calls of 17 to 2048 tokens on every tile (with one `ends` for all tiles, from 50 calls, the
+// choice was 4.2 % above the best tile; 1931 tokens x 3 x 8680 rows x 896, 32-bit outputs, 99.8 us on tile 0,
+// 128.1 on tile 4).  Tile 0's stores have become faster since: over 1200 calls the choice is 1.3 % above the best
+// tile, and 47 of the 1053 on small tiles are slower than tile 0 by more than 1.5 % (19 % at most, short contractions).
 struct MxTile {
   int mb, rb, rw, nw;
   float chain, busy, ends, ends32;

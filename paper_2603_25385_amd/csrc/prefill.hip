@@ -22,10 +22,8 @@
 
 namespace glowq {
 
-// Two waves per SIMD either way: binary16 runs two workgroups of four waves per compute
-// unit (64 rows per wave; a workgroup waiting at its barrier or for memory leaves the
-// matrix cores to the other one), bfloat16, whose dequantiser needs more registers, one
-// workgroup of eight waves (32 rows per wave).
+// Two workgroups of four waves per compute unit (two waves per SIMD): a workgroup waiting at
+// its barrier or for memory leaves the matrix cores to the other one.
 template <int ACT> struct PfShape {
   static constexpr int WAVES = 4;
   // 16-row blocks per wave: 256-row tiles for binary16; bfloat16, whose dequantiser
@@ -318,17 +316,6 @@ __device__ inline bool wait_tile_ready(const uint32_t* flag, uint32_t* status) {
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
   if (!ok && (threadIdx.x & 63) == 0) atomicOr(status, 1u);
   return ok;
-}
-// Eight 16-bit values read with device-scope loads: they bypass whatever this compute
-// unit or this XCD's L2 may still hold for the address from an earlier launch.
-__device__ inline u32x4_t load16_device(const uint16_t* p) {
-  const uint32_t* q = (const uint32_t*)p;
-  u32x4_t v;
-  v[0] = __hip_atomic_load(q + 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  v[1] = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  v[2] = __hip_atomic_load(q + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  v[3] = __hip_atomic_load(q + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return v;
 }
 
 template <int ACT, int MB, int RB, bool G128>
@@ -827,7 +814,9 @@ static inline long long prefill_tiles(const glowq_unit& u, int tile_blocks, int 
 // clock falls; `few`: what is left of that when only few do), and per workgroup when several rounds
 // keep all compute units busy.  A workgroup's start, correction and stores weigh `ends` K tiles; a
 // sliced unit's second launch costs `sum` us.
-// From 850 of the calls that are described there, on both tile sizes.  The half-size tiles took
+// From 850 of the calls that are described there, on both tile sizes, when the projection still handed R over with
+// fences (a launch of few tiles takes less now: of 796 calls of 384 tokens and more that keep the batched kernel by
+// this estimate 159 are over 10 % faster on one of these tiles).  The half-size tiles took
 // 502 tokens x 2 x 6240 rows x 6784 from 124 to 101 us and 1032 x 3 x 760 x 3840 from 48 to 39 us; on a
 // long prompt that fills the chip they are 4 to 13 % slower.
 struct PrefillCost {
@@ -904,8 +893,8 @@ struct Places {
 // `ends32` for 32-bit outputs), `proj` us per K tile of a projection workgroup and `proj_ends` beside them.
 // Projection workgroups have to be places: with them as a little more work, 204 tiles + 72 projection workgroups
 // counted as one round of 256 (2969 tokens x 4104 rows x 4224: 137 us on wide tiles, 112 on large ones).
-// From 10000 calls of 384 to 3000 tokens and 2800 channels and more (mean error: wide 3 %, large 4, half-size 5).  Of 2900
-// others 714 take wide tiles: 10.5 % faster than the better of the smaller ones; 29 lose more than 3 %, 2 more than 8 %.
+// From 10000 calls of 384 to 3000 tokens and 2800 channels and more (mean error: wide 3 %, large 4, half-size 5).  Of 3000
+// others 734 take wide tiles: 10.5 % faster than the better of the smaller ones; 28 lose more than 3 %, 2 more than 8 %.
 struct PlacesCost {
   float start, ends, ends64, ends32, few, slope, pair, all, proj, proj_ends, proj_ends64, sum, g64;
 };

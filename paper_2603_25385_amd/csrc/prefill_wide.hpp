@@ -11,8 +11,8 @@
 // placed by hand), so that the operand reads run ahead across the end of a stage and nothing waits there; the
 // stage before it is free, and the loads of the third stage from here go into its place.
 // Rows of X are XOR-swizzled by 16-byte chunks on the global-address side, as in k_prefill.
-// Measured against the 128-token tiles: 2 x 11008 rows x 4096 at 2048 tokens, bfloat16, 357 -> 292 us; four layers of
-// 5120 / 13824 at 1000 tokens 2163 -> 2013 us; a layer of 4096 / 14336 at 512 tokens 246 -> 212 us.  A tile of 4096
+// Measured against the 128-token tiles: 2 x 11008 rows x 4096 at 2048 tokens, bfloat16, 357 -> 294 us; four layers of
+// 5120 / 13824 at 1000 tokens 2167 -> 2027 us; a layer of 4096 / 14336 at 512 tokens 241 -> 217 us.  A tile of 4096
 // channels takes 151 (binary16) and 161 (bfloat16) of the 131 thousand cycles that its products need, at 1.7 to
 // 1.8 GHz: the chip's power sets the clock, and the same loop without the dequantiser is 12 to 17 % faster.
 #pragma once
@@ -69,6 +69,7 @@ __device__ inline uint32_t lds4(uint32_t addr) { return *(const __attribute__((a
 // acc += a x b with the sum in accumulation registers, in place.  As assembly: around the builtin the register
 // allocator moves the sums about (three copies per product).  It does not see the instruction's hazards either: an
 // operand has to be written two instructions ahead by the vector ALU, a sum to rest before it is read (acc_settle).
+// build.py reads the listing of every build for both.
 template <int ACT> __device__ inline void mfma_acc(float4_t& acc, u32x4_t a, u32x4_t b) {
   if constexpr (ACT == ACT_F16) asm("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
   else asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
