@@ -31,17 +31,28 @@ typedef double double4_t __attribute__((ext_vector_type(4)));
 
 constexpr int FZ_NT = 5;            // 16-column blocks per pass of a product (80 columns)
 constexpr int FZ_TARGET_WAVES = 4096;
+constexpr int NN_RB = 2;            // 16-row blocks of k_gemm_nn
+enum { FZ_SHORT, FZ_NN, FZ_TN };     // products: A B of any K, A B of a K in whole stages, A^T B
 
 // ---------------------------------------------------------------------------------------
 // the stack
 // ---------------------------------------------------------------------------------------
-__global__ void k_roots(const double* __restrict__ sigma, int d, double* root, double* inv_root) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= d) return;
-  const double s = sigma[k];
-  const double r = s > 0.0 ? sqrt(s) : 0.0;
-  root[k] = r;
-  inv_root[k] = r > 0.0 ? 1.0 / r : 0.0;      // (pseudo-inverse on a zero variance)
+// Thread idx: root[idx] and inv_root[idx] (no sigma: neither), element idx of Omega in rows of ld (the layout of every
+// narrow operand below; zeros behind column l), counter idx.
+__global__ void __launch_bounds__(256) k_setup(const double* __restrict__ sigma, int d, double* __restrict__ root,
+                                               double* __restrict__ inv_root, const double* __restrict__ Omega, int l,
+                                               int ld, double* __restrict__ Z, int* __restrict__ counters, int n_counters) {
+  const int idx = blockIdx.x * 256 + threadIdx.x;
+  if (idx < n_counters) counters[idx] = 0;
+  if (sigma && idx < d) {
+    const double s = sigma[idx];
+    const double r = s > 0.0 ? sqrt(s) : 0.0;
+    root[idx] = r;
+    inv_root[idx] = r > 0.0 ? 1.0 / r : 0.0;    // (pseudo-inverse on a zero variance)
+  }
+  if (idx >= d * ld) return;
+  const int k = idx / ld, c = idx - k * ld;
+  Z[idx] = c < l ? Omega[(long long)k * l + c] : 0.0;
 }
 
 // Ms[row_off + o][k] = (W[o][k] - What[o][k]) * root[k], What the stored 16-bit weight.
@@ -91,9 +102,9 @@ __global__ void __launch_bounds__(256) k_error_stack(const float* __restrict__ W
 struct GemmShape {
   int M, N, K;
   int n0;          // first column of this pass
-  int kslice;      // channels of K per wave (multiple of 16), four waves per slice
+  int kslice;      // k_gemm_nn: channels of K per wave (multiple of 16), four waves per slice; k_gemm_ring: stages per slice
   int n_slices;
-  int row_tiles;   // ceil(M / (16 RB))
+  int row_tiles;   // ceil(M / (16 RB)); k_gemm_ring: ceil(M / 64)
   const int* done; // iterated steps: nothing to do once *done <= pass (null: always run)
   int pass;
 };
@@ -182,61 +193,90 @@ __global__ void __launch_bounds__(256) k_gemm_nn(const double* A, long long lda,
       }
 }
 
-// C = A^T B, A [K][lda] (M columns) and B [K][ldb] (N columns) row-major: both operands are
-// read along their rows.
-template <int RB, int NT>
-__global__ void __launch_bounds__(256) k_gemm_tn(const double* __restrict__ A, long long lda,
-                                                 const double* __restrict__ B, long long ldb,
-                                                 double* __restrict__ P, long long ldp, GemmShape s) {
-  __shared__ double fold[RB * NT * 256];
-  const int wave = threadIdx.x >> 6;
-  const int tile = blockIdx.x % s.row_tiles, ks = blockIdx.x / s.row_tiles;
+// The products with the stack (and Gram matrices): C = A B or, TN, C = A^T B, by workgroups of 64
+// rows of C x 16 NT columns x a slice of K.  Both operands travel global -> LDS in stages of 32 channels
+// through two buffers (the next stage is on its way while one is multiplied), a wave owns 16 rows
+// and all columns.  The matrix instruction takes 64 cycles, so eight LDS reads and a barrier per 40 of
+// them cost nothing; what counts is that no wave waits for memory in front of its products and that
+// the narrow operand crosses the L2s once per 64 rows.  Two workgroups share a compute unit.  (Operands
+// straight to registers, 32 rows a workgroup and the channels dealt to its waves: 5120 x 80 over 3072
+// 81 us, 3072 x 80 over 5120 66 us; this 54 and 60.  The products alone, 64 cycles each at 2.4 GHz: 32 us.
+// Stages of 16 channels in a ring of four: 56 and 63 us, so memory is not what it waits for.)
+// A's rows are XOR-swizzled by 16-byte chunks on the global-address side where lanes read down a
+// column of them (A B).  lda, ldb even, both operands 16-byte aligned and readable up to a whole 16
+// columns; what is read there reaches only rows and columns of C that are not stored.  K is a multiple of 32, or TN:
+// channels past it are read from the last one and multiplied by zero.
+template <bool TN, int NT>
+__global__ void __launch_bounds__(256, 2) k_gemm_ring(const double* __restrict__ A, long long lda,
+                                                      const double* __restrict__ B, long long ldb,
+                                                      double* __restrict__ P, long long ldp, GemmShape s) {
+  constexpr int A_BYTES = 64 * 32 * 8, STAGE = A_BYTES + 32 * NT * 128;
+  __shared__ __attribute__((aligned(1024))) uint8_t ring[2 * STAGE];
   if (s.done && *s.done <= s.pass) return;
-  const int l = threadIdx.x & 63, i = l & 15, g = l >> 4;
-  const int kbeg = (4 * ks + wave) * s.kslice, kend = min(s.K, kbeg + s.kslice);
-  double4_t acc[RB][NT];
+  const int tile = blockIdx.x % s.row_tiles, ks = blockIdx.x / s.row_tiles;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, i = l & 15, g = l >> 4;
+  const int st0 = ks * s.kslice, n_st = min((s.K + 31) / 32 - st0, s.kslice);
+  const uint32_t lds0 = lds_address(ring);
+  auto issue = [&](int st, int buf) {
+    const int k0 = 32 * (st0 + st);
+    const uint32_t base = lds0 + (uint32_t)(buf * STAGE);
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[rb][nt] = double4_t{0.0, 0.0, 0.0, 0.0};
-  int acol[RB], bcol[NT];
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) acol[rb] = min(s.M - 1, tile * 16 * RB + rb * 16 + i);
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) bcol[nt] = min(s.N - 1, s.n0 + 16 * nt + i);
-  for (int k0 = kbeg; k0 < kend; k0 += 16) {
-    double a[4][RB], b[4][NT];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int kk = k0 + 4 * t + g, kc = min(kk, s.K - 1);
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        const double v = A[(long long)kc * lda + acol[rb]];
-        a[t][rb] = kk < kend ? v : 0.0;
+    for (int j = 0; j < 4; ++j) {
+      const int q = 4 * w + j;                       // a KiB: four rows of 32 channels, or two channels of 64 rows
+      const double* src;
+      if (TN) {
+        const long long col = min((long long)tile * 64 + 2 * (l & 31), lda - 2);
+        src = A + (long long)min(k0 + 2 * q + (l >> 5), s.K - 1) * lda + col;
+      } else {
+        const int row = 4 * q + g;
+        src = A + (long long)min(tile * 64 + row, s.M - 1) * lda + k0 + 2 * (i ^ (row & 15));
       }
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) b[t][nt] = B[(long long)kc * ldb + bcol[nt]];
+      lds_dma16(src, base + (uint32_t)q * 1024u);
     }
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int j = 0; j < NT; ++j) {
+      const int q = w * NT + j, piece = q * 64 + l, ch = piece / (8 * NT), at = piece - ch * (8 * NT);
+      lds_dma16(B + (long long)min(k0 + ch, s.K - 1) * ldb + s.n0 + 2 * at, base + A_BYTES + (uint32_t)q * 1024u);
+    }
+  };
+  double4_t acc[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) acc[nt] = double4_t{0.0, 0.0, 0.0, 0.0};
+  issue(0, 0);
+  vm_wait<0>();
+  __syncthreads();
+  for (int st = 0; st < n_st; ++st) {
+    const int buf = st & 1;
+    if (st + 1 < n_st) issue(st + 1, buf ^ 1);
+    const uint8_t* L = ring + buf * STAGE;
+    const double* Bl = (const double*)(L + A_BYTES);
+    const int left = s.K - 32 * (st0 + st);          // (TN: channels from here to the end)
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      // channels of instruction t: 4 t + g, or 8 (t >> 1) + 2 g + (t & 1) (a 16-byte chunk holds two)
+      const int ch = TN ? 4 * t + g : 8 * (t >> 1) + 2 * g + (t & 1);
+      double a;
+      if (TN) {
+        a = ((const double*)L)[ch * 64 + 16 * w + i];
+        a = ch < left ? a : 0.0;
+      } else {
+        a = ((const double*)(L + (16 * w + i) * 256 + (((4 * (t >> 1) + g) ^ i) << 4)))[t & 1];
+      }
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
-          acc[rb][nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t][rb], b[t][nt], acc[rb][nt], 0, 0, 0);
+        acc[nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, Bl[ch * (16 * NT) + 16 * nt + i], acc[nt], 0, 0, 0);
+    }
+    vm_wait<0>();          // this wave's loads of the next stage have landed ...
+    __syncthreads();       // ... and everybody's; everybody is done reading this one
   }
-  fold_waves<RB, NT>(acc, fold, wave, l);
-  if (wave != 0) return;
   double* Ps = P + (long long)ks * s.M * ldp;
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
+  for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int row = tile * 16 * RB + rb * 16 + g + 4 * v, col = s.n0 + 16 * nt + i;
-        if (row < s.M && col < s.N) Ps[(long long)row * ldp + col] = acc[rb][nt][v];
-      }
+    for (int v = 0; v < 4; ++v) {
+      const int row = tile * 64 + 16 * w + g + 4 * v, col = s.n0 + 16 * nt + i;
+      if (row < s.M && col < s.N) Ps[(long long)row * ldp + col] = acc[nt][v];
+    }
 }
 
 // C[row][col] (or C[col][row] when transposed) = sum over slices, in slice order
@@ -255,9 +295,10 @@ struct GemmPlan {
   int kslice, n_slices, row_tiles;
 };
 
-static GemmPlan plan_gemm(int M, int K, int RB) {
+// short contractions (k_gemm_nn)
+static GemmPlan plan_short(int M, int K) {
   GemmPlan p;
-  p.row_tiles = (M + 16 * RB - 1) / (16 * RB);
+  p.row_tiles = (M + 16 * NN_RB - 1) / (16 * NN_RB);
   int want = (FZ_TARGET_WAVES / 4 + p.row_tiles - 1) / p.row_tiles;
   const int max_slices = (K + 63) / 64;
   if (want > max_slices) want = max_slices;
@@ -268,31 +309,51 @@ static GemmPlan plan_gemm(int M, int K, int RB) {
   return p;
 }
 
-constexpr int NN_RB = 2, TN_RB = 2;
+// Products with the stack: the number of slices whose workgroups, dealt to 256 compute units, need the fewest
+// stages on the fullest one.  A workgroup's start and end weigh two stages; one that has a compute unit to itself
+// takes 8 % longer a stage (nothing covers its barriers); a slice's partial results weigh a twelfth.  (From 3 to 16 slices
+// of the two products named at k_gemm_ring; us: 3 / 4 / 5 / 6 / 8 / 10 / 12 / 16 slices of the first 55 / 73 / 63 / 54 / 60 /
+// 60 / 56 / 56, of the second 99 / 77 / 64 / 87 / 71 / 60 / 76 / 60.)
+static GemmPlan plan_ring(int M, int K) {
+  GemmPlan p;
+  p.row_tiles = (M + 63) / 64;
+  const int stages = (K + 31) / 32;
+  double best = 0.0;
+  for (int want = 1; want <= 16 && want <= stages; ++want) {
+    const int per = (stages + want - 1) / want, n = (stages + per - 1) / per;
+    const int rounds = (p.row_tiles * n + 255) / 256;
+    const double cost = (rounds == 1 ? 1.08 : rounds) * (per + 2) + 0.08 * n;
+    if (want == 1 || cost < best) {
+      best = cost;
+      p.kslice = per;
+      p.n_slices = n;
+    }
+  }
+  return p;
+}
 
-static size_t gemm_slice_doubles(int M, int N, int K, int RB) {
-  const GemmPlan p = plan_gemm(M, K, RB);
+static size_t slice_doubles(const GemmPlan& p, int M, int N) {
   return (size_t)p.n_slices * (size_t)M * (size_t)((N + 15) / 16 * 16);
 }
 
-template <bool TN, int NT>
+template <int KIND, int NT>
 static void launch_gemm_pass(const double* A, long long lda, const double* B, long long ldb, double* P,
                              long long ldp, const GemmShape& s, hipStream_t st) {
   dim3 grid((unsigned)(s.row_tiles * s.n_slices)), block(256);
-  if (TN) k_gemm_tn<TN_RB, NT><<<grid, block, 0, st>>>(A, lda, B, ldb, P, ldp, s);
-  else k_gemm_nn<NN_RB, NT><<<grid, block, 0, st>>>(A, lda, B, ldb, P, ldp, s);
+  if (KIND == FZ_SHORT) k_gemm_nn<NN_RB, NT><<<grid, block, 0, st>>>(A, lda, B, ldb, P, ldp, s);
+  else k_gemm_ring<KIND == FZ_TN, NT><<<grid, block, 0, st>>>(A, lda, B, ldb, P, ldp, s);
 }
 
-// C [M][N] = op(A) B through the slice buffer (C may be A: it is written when A has been read).
-// A short contraction on one pass of columns (A B, K <= 80) needs no slices: every workgroup has
-// the whole sum of its rows and writes them to C itself.
-template <bool TN>
+// C [M][N] = A B (FZ_NN: K a multiple of 32; FZ_SHORT: any K) or A^T B (FZ_TN) through the slice buffer (C may be A:
+// it is written when A has been read).  A short contraction on one pass of columns (K <= 80) needs no
+// slices: every workgroup has the whole sum of its rows and writes them to C itself.
+template <int KIND>
 static hipError_t gemm(const double* A, long long lda, const double* B, long long ldb, double* C,
                        long long ldc, bool c_transposed, int M, int N, int K, double* slices,
                        hipStream_t st, const int* done = nullptr, int pass = 0) {
-  GemmPlan p = plan_gemm(M, K, TN ? TN_RB : NN_RB);
+  GemmPlan p = KIND == FZ_SHORT ? plan_short(M, K) : plan_ring(M, K);
   long long ldp = (N + 15) / 16 * 16;
-  const bool direct = !TN && !c_transposed && K <= 16 * FZ_NT && N <= 16 * FZ_NT;
+  const bool direct = KIND == FZ_SHORT && !c_transposed && K <= 16 * FZ_NT && N <= 16 * FZ_NT;
   if (direct) {
     p.kslice = (K + 63) / 64 * 16;
     p.n_slices = 1;
@@ -307,11 +368,11 @@ static hipError_t gemm(const double* A, long long lda, const double* B, long lon
     s.n0 = n0;
     const int nt = (std::min(N - n0, 16 * FZ_NT) + 15) / 16;
     switch (nt) {
-      case 1: launch_gemm_pass<TN, 1>(A, lda, B, ldb, slices, ldp, s, st); break;
-      case 2: launch_gemm_pass<TN, 2>(A, lda, B, ldb, slices, ldp, s, st); break;
-      case 3: launch_gemm_pass<TN, 3>(A, lda, B, ldb, slices, ldp, s, st); break;
-      case 4: launch_gemm_pass<TN, 4>(A, lda, B, ldb, slices, ldp, s, st); break;
-      default: launch_gemm_pass<TN, 5>(A, lda, B, ldb, slices, ldp, s, st); break;
+      case 1: launch_gemm_pass<KIND, 1>(A, lda, B, ldb, slices, ldp, s, st); break;
+      case 2: launch_gemm_pass<KIND, 2>(A, lda, B, ldb, slices, ldp, s, st); break;
+      case 3: launch_gemm_pass<KIND, 3>(A, lda, B, ldb, slices, ldp, s, st); break;
+      case 4: launch_gemm_pass<KIND, 4>(A, lda, B, ldb, slices, ldp, s, st); break;
+      default: launch_gemm_pass<KIND, 5>(A, lda, B, ldb, slices, ldp, s, st); break;
     }
   }
   if (direct) return hipGetLastError();
@@ -990,13 +1051,13 @@ FactorizePlan plan_factorize(const glowq_unit& u, int r, int p) {
   f.off_gram = take((size_t)f.l * f.l16 * 8);
   f.off_lift = take((size_t)f.l * f.r16 * 8);
   f.off_a64 = take((size_t)m * f.r16 * 8);
-  size_t sl = gemm_slice_doubles((int)m, f.l, f.d, NN_RB);                      // Y = Ms Omega, Y = Ms Z
-  size_t s2 = gemm_slice_doubles(f.d, f.l, (int)m, TN_RB);                      // Z = Ms^T Y, Bs^T = Ms^T Q
-  size_t s3 = gemm_slice_doubles((int)m, r, f.l, NN_RB);                        // A = Q P
-  size_t s4 = gemm_slice_doubles(f.l, f.l, f.d, TN_RB);                         // Gram of Bs
-  size_t s5 = gemm_slice_doubles(f.d, f.l, f.l, NN_RB);                         // rows = Um^T Bs
-  size_t s6 = gemm_slice_doubles((int)m, f.l, f.l, NN_RB);                      // Y Tinv
-  size_t s7 = gemm_slice_doubles(f.l, f.l, (int)m, TN_RB);                      // Gram of Y
+  size_t sl = slice_doubles(plan_ring((int)m, f.d), (int)m, f.l);               // Y = Ms Omega, Y = Ms Z
+  const size_t s2 = slice_doubles(plan_ring(f.d, (int)m), f.d, f.l);            // Z = Ms^T Y, Bs^T = Ms^T Q
+  const size_t s3 = slice_doubles(plan_short((int)m, f.l), (int)m, r);          // A = Q P
+  const size_t s4 = slice_doubles(plan_ring(f.l, f.d), f.l, f.l);               // Gram of Bs
+  const size_t s5 = slice_doubles(plan_short(f.d, f.l), f.d, f.l);              // rows = Um^T Bs
+  const size_t s6 = slice_doubles(plan_short((int)m, f.l), (int)m, f.l);        // Y Tinv
+  const size_t s7 = slice_doubles(plan_ring(f.l, (int)m), f.l, f.l);            // Gram of Y
   for (size_t o : {s2, s3, s4, s5, s6, s7})
     if (o > sl) sl = o;
   f.off_slices = take(sl * 8);
@@ -1047,9 +1108,9 @@ hipError_t launch_factorize(const glowq_unit& u, const float* const* W_modules, 
   cb.norm = (double*)(ws + f.off_norm);
   cb.norm0 = (double*)(ws + f.off_norm0);
 
-  hipError_t err = launch_fill_zero(counters, FZ_MAX_SWEEPS * 4, st);
-  if (err != hipSuccess) return err;
-  if (sigma_x) k_roots<<<dim3((unsigned)((d + 255) / 256)), dim3(256), 0, st>>>(sigma_x, d, root, inv_root);
+  hipError_t err = hipSuccess;
+  k_setup<<<dim3((unsigned)((d * f.l16 + 255) / 256)), dim3(256), 0, st>>>(sigma_x, d, root, inv_root, Omega, l, f.l16, Z,
+                                                                          counters, FZ_MAX_SWEEPS);
   // the stack, scaled by Sigma_x^(1/2) (Alg. 1, core construction)
   long long row_off = 0;
   for (int i = 0; i < u.n_modules; ++i) {
@@ -1061,10 +1122,10 @@ hipError_t launch_factorize(const glowq_unit& u, const float* const* W_modules, 
     row_off += mod.d_out;
   }
   // sketch and power steps (Alg. 1, range finding)
-  err = gemm<false>(Ms, d, Omega, l, Y, f.l16, false, m, l, d, slices, st);
+  err = gemm<FZ_NN>(Ms, d, Z, f.l16, Y, f.l16, false, m, l, d, slices, st);
   for (int it = 0; it < q && err == hipSuccess; ++it) {
-    err = gemm<true>(Ms, d, Y, f.l16, Z, f.l16, false, d, l, m, slices, st);
-    if (err == hipSuccess) err = gemm<false>(Ms, d, Z, f.l16, Y, f.l16, false, m, l, d, slices, st);
+    err = gemm<FZ_TN>(Ms, d, Y, f.l16, Z, f.l16, false, d, l, m, slices, st);
+    if (err == hipSuccess) err = gemm<FZ_NN>(Ms, d, Z, f.l16, Y, f.l16, false, m, l, d, slices, st);
   }
   if (err != hipSuccess) return err;
   // orthonormal basis of the range, compressed matrix Bs = Q^T Ms and its SVD
@@ -1074,23 +1135,23 @@ hipError_t launch_factorize(const glowq_unit& u, const float* const* W_modules, 
     int* done = (int*)(ws + f.off_done);
     for (int pass = 0; pass < FZ_QR_PASSES; ++pass) {
       const int* stop = pass ? done : nullptr;
-      err = gemm<true>(Y, f.l16, Y, f.l16, gram, f.l16, false, l, l, m, slices, st, stop, pass);
+      err = gemm<FZ_TN>(Y, f.l16, Y, f.l16, gram, f.l16, false, l, l, m, slices, st, stop, pass);
       if (err != hipSuccess) return err;
       k_cholesky_step<<<dim3(1), dim3(1024), 0, st>>>(gram, f.l16, l, factor, f.l16, (double*)(ws + f.off_kept),
                                                       (int*)(ws + f.off_state), done, pass);
-      err = gemm<false>(Y, f.l16, factor, f.l16, Y, f.l16, false, m, l, l, slices, st, stop, pass);
+      err = gemm<FZ_SHORT>(Y, f.l16, factor, f.l16, Y, f.l16, false, m, l, l, slices, st, stop, pass);
       if (err != hipSuccess) return err;
     }
     double* BsT = Z;                                                               // [d][l16]
-    err = gemm<true>(Ms, d, Y, f.l16, BsT, f.l16, false, d, l, m, slices, st);     // Ms^T Q
+    err = gemm<FZ_TN>(Ms, d, Y, f.l16, BsT, f.l16, false, d, l, m, slices, st);     // Ms^T Q
     double* Um_old = (double*)(ws + f.off_um2);
     for (int pass = 0; pass < FZ_SVD_PASSES && err == hipSuccess; ++pass) {
       const int* stop = pass ? done + 1 : nullptr;
-      err = gemm<true>(BsT, f.l16, BsT, f.l16, gram, f.l16, false, l, l, d, slices, st, stop, pass);
+      err = gemm<FZ_TN>(BsT, f.l16, BsT, f.l16, gram, f.l16, false, l, l, d, slices, st, stop, pass);
       if (err != hipSuccess) return err;
       launch_row_rotations(gram, f.l16, l, factor, Um_old, Um, f.l16, done + 1, pass, st);
       // (a pass that found nothing to rotate has set the flag to its own number)
-      err = gemm<false>(BsT, f.l16, factor, f.l16, BsT, f.l16, false, d, l, l, slices, st, done + 1, pass);
+      err = gemm<FZ_SHORT>(BsT, f.l16, factor, f.l16, BsT, f.l16, false, d, l, l, slices, st, done + 1, pass);
       if (pass + 1 < FZ_SVD_PASSES) std::swap(Um, Um_old);
     }
     if (err != hipSuccess) return err;
@@ -1109,7 +1170,7 @@ hipError_t launch_factorize(const glowq_unit& u, const float* const* W_modules, 
         k_cgs<<<dim3((unsigned)f.n_groups), dim3(256), 0, st>>>(Y, f.l16, m, l, f.rpw, f.n_groups, 0, 2, cb);
       }
     }
-    err = gemm<true>(Ms, d, Y, f.l16, Bs, d, true, d, l, m, slices, st);           // (Ms^T Q)^T
+    err = gemm<FZ_TN>(Ms, d, Y, f.l16, Bs, d, true, d, l, m, slices, st);           // (Ms^T Q)^T
     if (err != hipSuccess) return err;
     k_identity<<<dim3((unsigned)((l * l + 255) / 256)), dim3(256), 0, st>>>(Um, f.l16, l);
     const int n = (l + 1) & ~1;
@@ -1124,7 +1185,7 @@ hipError_t launch_factorize(const glowq_unit& u, const float* const* W_modules, 
   k_sort_sigma<<<dim3(1), dim3(256), 0, st>>>(sig2, l, sigma_sorted, perm);
   // truncate, balance, lift
   k_build_lift<<<dim3((unsigned)((l * r + 255) / 256)), dim3(256), 0, st>>>(Um, f.l16, sigma_sorted, perm, l, r, lift, f.r16);
-  err = gemm<false>(Y, f.l16, lift, f.r16, A64, f.r16, false, m, r, l, slices, st);
+  err = gemm<FZ_SHORT>(Y, f.l16, lift, f.r16, A64, f.r16, false, m, r, l, slices, st);
   if (err != hipSuccess) return err;
   row_off = 0;
   for (int i = 0; i < u.n_modules; ++i) {
