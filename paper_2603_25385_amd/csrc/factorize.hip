@@ -30,9 +30,6 @@ namespace glowq {
 typedef double double4_t __attribute__((ext_vector_type(4)));
 
 constexpr int FZ_NT = 5;            // 16-column blocks per pass of a product (80 columns)
-constexpr int FZ_TARGET_WAVES = 4096;
-constexpr int NN_RB = 2;            // 16-row blocks of k_gemm_nn
-enum { FZ_SHORT, FZ_NN, FZ_TN };     // products: A B of any K, A B of a K in whole stages, A^T B
 
 // ---------------------------------------------------------------------------------------
 // the stack
@@ -102,11 +99,9 @@ __global__ void __launch_bounds__(256) k_error_stack(const float* __restrict__ W
 struct GemmShape {
   int M, N, K;
   int n0;          // first column of this pass
-  int kslice;      // k_gemm_nn: channels of K per wave (multiple of 16), four waves per slice; k_gemm_ring: stages per slice
+  int kslice;      // stages per slice
   int n_slices;
-  int row_tiles;   // ceil(M / (16 RB)); k_gemm_ring: ceil(M / 64)
-  const int* done; // iterated steps: nothing to do once *done <= pass (null: always run)
-  int pass;
+  int row_tiles;   // ceil(M / 64)
 };
 
 // the four waves' tiles added in wave order, in wave 0's registers
@@ -134,65 +129,6 @@ __device__ inline void fold_waves(double4_t (&acc)[RB][NT], double* fold, int wa
   }
 }
 
-// C = A B, A [M][lda] and B [K][ldb] row-major.  Within a step of 16 channels lane group g
-// owns channels 4g .. 4g + 3 (contiguous in a row of A); instruction t multiplies channel
-// 4g + t of every group.
-template <int RB, int NT>
-__global__ void __launch_bounds__(256) k_gemm_nn(const double* A, long long lda,
-                                                 const double* __restrict__ B, long long ldb,
-                                                 double* P, long long ldp, GemmShape s) {
-  __shared__ double fold[RB * NT * 256];
-  const int wave = threadIdx.x >> 6;
-  const int tile = blockIdx.x % s.row_tiles, ks = blockIdx.x / s.row_tiles;
-  if (s.done && *s.done <= s.pass) return;
-  const int l = threadIdx.x & 63, i = l & 15, g = l >> 4;
-  const int kbeg = (4 * ks + wave) * s.kslice, kend = min(s.K, kbeg + s.kslice);
-  double4_t acc[RB][NT];
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[rb][nt] = double4_t{0.0, 0.0, 0.0, 0.0};
-  const double* arow[RB];
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) arow[rb] = A + (long long)min(s.M - 1, tile * 16 * RB + rb * 16 + i) * lda;
-  int bcol[NT];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) bcol[nt] = min(s.N - 1, s.n0 + 16 * nt + i);
-  for (int k0 = kbeg; k0 < kend; k0 += 16) {
-    double a[RB][4], b[4][NT];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int kk = k0 + 4 * g + t, kc = min(kk, s.K - 1);
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        const double v = arow[rb][kc];
-        a[rb][t] = kk < kend ? v : 0.0;
-      }
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) b[t][nt] = B[(long long)kc * ldb + bcol[nt]];
-    }
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
-          acc[rb][nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rb][t], b[t][nt], acc[rb][nt], 0, 0, 0);
-  }
-  fold_waves<RB, NT>(acc, fold, wave, l);
-  if (wave != 0) return;
-  double* Ps = P + (long long)ks * s.M * ldp;
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int row = tile * 16 * RB + rb * 16 + g + 4 * v, col = s.n0 + 16 * nt + i;
-        if (row < s.M && col < s.N) Ps[(long long)row * ldp + col] = acc[rb][nt][v];
-      }
-}
-
 // The products with the stack (and Gram matrices): C = A B or, TN, C = A^T B, by workgroups of 64
 // rows of C x 16 NT columns x a slice of K.  Both operands travel global -> LDS in stages of 32 channels
 // through two buffers (the next stage is on its way while one is multiplied), a wave owns 16 rows
@@ -212,7 +148,6 @@ __global__ void __launch_bounds__(256, 2) k_gemm_ring(const double* __restrict__
                                                       double* __restrict__ P, long long ldp, GemmShape s) {
   constexpr int A_BYTES = 64 * 32 * 8, STAGE = A_BYTES + 32 * NT * 128;
   __shared__ __attribute__((aligned(1024))) uint8_t ring[2 * STAGE];
-  if (s.done && *s.done <= s.pass) return;
   const int tile = blockIdx.x % s.row_tiles, ks = blockIdx.x / s.row_tiles;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, i = l & 15, g = l >> 4;
   const int st0 = ks * s.kslice, n_st = min((s.K + 31) / 32 - st0, s.kslice);
@@ -281,9 +216,9 @@ __global__ void __launch_bounds__(256, 2) k_gemm_ring(const double* __restrict__
 
 // C[row][col] (or C[col][row] when transposed) = sum over slices, in slice order
 __global__ void k_reduce_slices(const double* __restrict__ P, long long ldp, int n_slices, int M, int N,
-                                double* __restrict__ C, long long ldc, int transposed, const int* done, int pass) {
+                                double* __restrict__ C, long long ldc, int transposed) {
   const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (long long)M * N || (done && *done <= pass)) return;
+  if (idx >= (long long)M * N) return;
   const int row = (int)(idx / N), col = (int)(idx - (long long)row * N);
   double sum = 0.0;
   for (int sl = 0; sl < n_slices; ++sl) sum += P[((long long)sl * M + row) * ldp + col];
@@ -294,20 +229,6 @@ __global__ void k_reduce_slices(const double* __restrict__ P, long long ldp, int
 struct GemmPlan {
   int kslice, n_slices, row_tiles;
 };
-
-// short contractions (k_gemm_nn)
-static GemmPlan plan_short(int M, int K) {
-  GemmPlan p;
-  p.row_tiles = (M + 16 * NN_RB - 1) / (16 * NN_RB);
-  int want = (FZ_TARGET_WAVES / 4 + p.row_tiles - 1) / p.row_tiles;
-  const int max_slices = (K + 63) / 64;
-  if (want > max_slices) want = max_slices;
-  if (want > 16) want = 16;
-  if (want < 1) want = 1;
-  p.kslice = (((K + 4 * want - 1) / (4 * want)) + 15) / 16 * 16;
-  p.n_slices = (K + 4 * p.kslice - 1) / (4 * p.kslice);
-  return p;
-}
 
 // Products with the stack: the number of slices whose workgroups, dealt to 256 compute units, need the fewest
 // stages on the fullest one.  A workgroup's start and end weigh two stages; one that has a compute unit to itself
@@ -336,57 +257,48 @@ static size_t slice_doubles(const GemmPlan& p, int M, int N) {
   return (size_t)p.n_slices * (size_t)M * (size_t)((N + 15) / 16 * 16);
 }
 
-template <int KIND, int NT>
+template <bool TN, int NT>
 static void launch_gemm_pass(const double* A, long long lda, const double* B, long long ldb, double* P,
                              long long ldp, const GemmShape& s, hipStream_t st) {
-  dim3 grid((unsigned)(s.row_tiles * s.n_slices)), block(256);
-  if (KIND == FZ_SHORT) k_gemm_nn<NN_RB, NT><<<grid, block, 0, st>>>(A, lda, B, ldb, P, ldp, s);
-  else k_gemm_ring<KIND == FZ_TN, NT><<<grid, block, 0, st>>>(A, lda, B, ldb, P, ldp, s);
+  k_gemm_ring<TN, NT><<<dim3((unsigned)(s.row_tiles * s.n_slices)), dim3(256), 0, st>>>(A, lda, B, ldb, P, ldp, s);
 }
 
-// C [M][N] = A B (FZ_NN: K a multiple of 32; FZ_SHORT: any K) or A^T B (FZ_TN) through the slice buffer (C may be A:
-// it is written when A has been read).  A short contraction on one pass of columns (K <= 80) needs no
-// slices: every workgroup has the whole sum of its rows and writes them to C itself.
-template <int KIND>
+// C [M][N] = A B (K a multiple of 32) or, TN, A^T B through the slice buffer.  `left`: the sum over the slices is left to
+// the caller, and *left their number.
+template <bool TN>
 static hipError_t gemm(const double* A, long long lda, const double* B, long long ldb, double* C,
                        long long ldc, bool c_transposed, int M, int N, int K, double* slices,
-                       hipStream_t st, const int* done = nullptr, int pass = 0) {
-  GemmPlan p = KIND == FZ_SHORT ? plan_short(M, K) : plan_ring(M, K);
-  long long ldp = (N + 15) / 16 * 16;
-  const bool direct = KIND == FZ_SHORT && !c_transposed && K <= 16 * FZ_NT && N <= 16 * FZ_NT;
-  if (direct) {
-    p.kslice = (K + 63) / 64 * 16;
-    p.n_slices = 1;
-    slices = C;
-    ldp = ldc;
-  }
+                       hipStream_t st, int* left = nullptr) {
+  const GemmPlan p = plan_ring(M, K);
+  const long long ldp = (N + 15) / 16 * 16;
   GemmShape s;
   s.M = M; s.N = N; s.K = K;
-  s.done = done; s.pass = pass;
   s.kslice = p.kslice; s.n_slices = p.n_slices; s.row_tiles = p.row_tiles;
   for (int n0 = 0; n0 < N; n0 += 16 * FZ_NT) {
     s.n0 = n0;
     const int nt = (std::min(N - n0, 16 * FZ_NT) + 15) / 16;
     switch (nt) {
-      case 1: launch_gemm_pass<KIND, 1>(A, lda, B, ldb, slices, ldp, s, st); break;
-      case 2: launch_gemm_pass<KIND, 2>(A, lda, B, ldb, slices, ldp, s, st); break;
-      case 3: launch_gemm_pass<KIND, 3>(A, lda, B, ldb, slices, ldp, s, st); break;
-      case 4: launch_gemm_pass<KIND, 4>(A, lda, B, ldb, slices, ldp, s, st); break;
-      default: launch_gemm_pass<KIND, 5>(A, lda, B, ldb, slices, ldp, s, st); break;
+      case 1: launch_gemm_pass<TN, 1>(A, lda, B, ldb, slices, ldp, s, st); break;
+      case 2: launch_gemm_pass<TN, 2>(A, lda, B, ldb, slices, ldp, s, st); break;
+      case 3: launch_gemm_pass<TN, 3>(A, lda, B, ldb, slices, ldp, s, st); break;
+      case 4: launch_gemm_pass<TN, 4>(A, lda, B, ldb, slices, ldp, s, st); break;
+      default: launch_gemm_pass<TN, 5>(A, lda, B, ldb, slices, ldp, s, st); break;
     }
   }
-  if (direct) return hipGetLastError();
+  if (left) {
+    *left = p.n_slices;
+    return hipGetLastError();
+  }
   const long long n = (long long)M * N;
   k_reduce_slices<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st>>>(slices, ldp, p.n_slices, M, N, C,
-                                                                          ldc, c_transposed ? 1 : 0, done, pass);
+                                                                          ldc, c_transposed ? 1 : 0);
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------------
 // Q = orth(Y) for sketches of up to FZ_SMALL columns: Cholesky QR, iterated.  A pass forms the
 // Gram matrix of Y (matrix cores), factors it in one workgroup's LDS and multiplies Y with the
-// inverse factor, so that a pass costs four launches whatever l is (80 columns x 5120 rows: 170 us;
-// column by column, three launches each, 1930 us).  A Cholesky factor of a Gram matrix only resolves columns whose part
+// inverse factor (k_pass; column by column, three launches each, 80 columns x 5120 rows took 1930 us).  A Cholesky factor of a Gram matrix only resolves columns whose part
 // outside the span of the columns before them is well above its rounding.  So a column whose
 // share of norm^2 outside that span falls below FZ_ACCEPT is deferred: this pass takes the
 // span out of it but does not project anybody on it, and the next pass, where it starts at
@@ -400,7 +312,7 @@ constexpr int FZ_SMALL = 128;
 constexpr int FZ_QR_PASSES = 6;
 constexpr double FZ_ACCEPT = 1e-8;
 constexpr double FZ_RANK_TOL2 = 1e-24;      // a column whose norm^2 fell by this factor is dependent
-constexpr int FZ_LD = FZ_SMALL + 2;
+constexpr int FZ_PASS_THREADS = 1024;
 enum { FZ_PENDING = 0, FZ_KEPT = 1, FZ_DROPPED = 2 };
 
 // 1 / sqrt(x) to working precision: the hardware's estimate and two Newton steps
@@ -525,18 +437,18 @@ __device__ inline void block_cholesky(double* S, int LD, int nb, double* E, doub
   __syncthreads();
 }
 
-// One workgroup.  G: Gram matrix [l][ldg]; Tinv (upper triangular): Y Tinv is the next Y.
-__global__ void __launch_bounds__(1024) k_cholesky_step(const double* __restrict__ G, long long ldg, int l,
-                                                        double* __restrict__ Tinv, long long ldt, double* kept,
-                                                        int* state, int* done, int pass) {
-  __shared__ double S[FZ_SMALL * FZ_LD], Rb[16 * FZ_LD], E[256], F[256], scale[FZ_SMALL];
-  __shared__ int st[FZ_SMALL], pending;
+// The factor of a pass of the orthonormalisation, by one workgroup.  S: Gram matrix (upper blocks, rows of LD);
+// Tinv (upper triangular): Y Tinv is the next Y.
+template <int NB, int LD>
+__device__ inline void cholesky_step(double* S, int l, double* Tinv, long long ldt, double* kept, int* state, int* done,
+                                     int pass) {
+  __shared__ double Rb[16 * LD], E[256], F[256], scale[16 * NB];
+  __shared__ int st[16 * NB], pending;
   __shared__ double least;
-  if (pass > 0 && *done <= pass) return;
-  const int t = threadIdx.x, nb = (l + 15) >> 4, n16 = 16 * nb, LD = n16 + 2;
+  const int t = threadIdx.x, nb = (l + 15) >> 4, n16 = 16 * nb;
   const bool last = pass == FZ_QR_PASSES - 1;
   if (t < n16) {
-    const double gg = t < l ? G[(long long)t * ldg + t] : 0.0;
+    const double gg = t < l ? S[t * LD + t] : 0.0;
     double k2 = pass && t < l ? kept[t] : 1.0;
     int s0 = pass && t < l ? state[t] : FZ_PENDING;
     if (pass && s0 == FZ_PENDING) k2 *= gg;
@@ -550,10 +462,10 @@ __global__ void __launch_bounds__(1024) k_cholesky_step(const double* __restrict
     pending = 0;
   }
   __syncthreads();
-  for (int idx = t; idx < n16 * n16; idx += 1024) {
+  for (int idx = t; idx < n16 * n16; idx += FZ_PASS_THREADS) {
     const int i = idx / n16, k = idx - i * n16;
     const double w = scale[i] * scale[k];
-    S[i * LD + k] = w > 0.0 && (i >> 4) <= (k >> 4) ? G[(long long)i * ldg + k] * w : 0.0;
+    S[i * LD + k] = w > 0.0 && (i >> 4) <= (k >> 4) ? S[i * LD + k] * w : 0.0;
   }
   block_cholesky<true>(S, LD, nb, E, F, Rb, [&](int j, double d, double& own) {
     // (wave 0 only.)  Kept: scaled to length one; deferred: as the projections left it; dropped:
@@ -568,7 +480,7 @@ __global__ void __launch_bounds__(1024) k_cholesky_step(const double* __restrict
     }
     return ri;
   });
-  for (int idx = t; idx < l * l; idx += 1024) {
+  for (int idx = t; idx < l * l; idx += FZ_PASS_THREADS) {
     const int i = idx / l, k = idx - i * l;
     Tinv[(long long)i * ldt + k] = k >= i ? scale[i] * S[i * LD + k] : 0.0;
   }
@@ -803,40 +715,39 @@ __device__ inline double row_sum16(double v) {
   return v;
 }
 
-// NQ: 16-element pieces of a column (l <= 16 NQ).  Zt[k] is column k of Z.
-template <int NQ>
-__global__ void __launch_bounds__(1024) k_row_rotations(const double* __restrict__ G, long long ldg, int l,
-                                                        double* __restrict__ U, const double* __restrict__ Um_old,
-                                                        double* __restrict__ Um_new, long long ldu, int* done, int pass) {
-  constexpr int LW = 16 * NQ, LD = LW + (NQ > 6 ? 4 : 16);      // (the pad spreads columns over the banks)
-  __shared__ double Zt[16 * NQ * LD];
+// NQ: 16-element pieces of a column (l <= 16 NQ).  Zt: Gram matrix (upper blocks, rows of LD), then Zt[k] is column k
+// of Z.  Returns true, with Zt's diagonal as it was, if the rows are orthogonal already; else U is the rotation, and
+// Um_new = Um_old U the rotations so far (pass 0: U).
+template <int NQ, int LD>
+__device__ inline bool rotation_step(double* Zt, int l, double* __restrict__ U, const double* __restrict__ Um_old,
+                                     double* __restrict__ Um_new, long long ldu, int pass) {
+  constexpr int LW = 16 * NQ;
   __shared__ double E[256], F[256], len2[16 * NQ], tiny[16 * NQ];
   __shared__ int rotated[2];
   const int t = threadIdx.x;
-  if (pass > 0 && *done <= pass) {
-    for (int idx = t; idx < l * l; idx += 1024) {
-      const int i = idx / l, k = idx - i * l;
-      Um_new[(long long)i * ldu + k] = Um_old[(long long)i * ldu + k];
-    }
-    return;
-  }
   if (t < LW) {
-    const double gg = t < l ? G[(long long)t * ldg + t] : 0.0;
+    const double gg = t < l ? Zt[t * LD + t] : 0.0;
     len2[t] = gg > 0.0 ? sqrt(gg) : 0.0;            // (row lengths for now)
     tiny[t] = 0.0;
   }
   if (t == 0) rotated[0] = 0;
   __syncthreads();
-  for (int idx = t; idx < LW * LW; idx += 1024) {
+  for (int idx = t; idx < LW * LW; idx += FZ_PASS_THREADS) {
     const int i = idx / LW, k = idx - i * LW;
     const double w = len2[i] * len2[k];
-    const double c = w > 0.0 ? G[(long long)i * ldg + k] / w : 0.0;
+    const bool upper = (i >> 4) <= (k >> 4);
+    const double c = upper && w > 0.0 ? Zt[i * LD + k] / w : 0.0;
     if (i != k && c * c > FZ_QUIET2) rotated[0] = 1;
-    Zt[i * LD + k] = (i >> 4) <= (k >> 4) ? c : 0.0;
   }
   __syncthreads();
-  const bool quiet = pass > 0 && rotated[0] == 0;   // already orthogonal: nothing to apply
-  if (!quiet) {
+  if (pass > 0 && rotated[0] == 0) return true;     // already orthogonal: nothing to apply
+  for (int idx = t; idx < LW * LW; idx += FZ_PASS_THREADS) {
+    const int i = idx / LW, k = idx - i * LW;
+    const double w = len2[i] * len2[k];
+    Zt[i * LD + k] = (i >> 4) <= (k >> 4) && w > 0.0 ? Zt[i * LD + k] / w : 0.0;
+  }
+  __syncthreads();
+  {
     block_cholesky<false>(Zt, LD, NQ, E, F, nullptr, [&](int j, double d, double& own) {
       const bool real = d > FZ_PIVOT;
       if (!real && t == 0) tiny[j] = sqrt(FZ_PIVOT);
@@ -845,13 +756,13 @@ __global__ void __launch_bounds__(1024) k_row_rotations(const double* __restrict
       return ri;
     });
     // column j of Z: row j of the factor, every element scaled back by its row's length
-    for (int idx = t; idx < LW * LW; idx += 1024) {
+    for (int idx = t; idx < LW * LW; idx += FZ_PASS_THREADS) {
       const int j = idx / LW, k = idx - j * LW;
       Zt[j * LD + k] = k < j ? 0.0 : (k == j && tiny[j] > 0.0 ? tiny[j] : Zt[j * LD + k]) * len2[k];
     }
   }
   const int n = (l + 1) & ~1, pairs = n / 2, p = t >> 4, sub = t & 15;
-  for (int sweep = 0; sweep < FZ_SMALL_SWEEPS && !quiet; ++sweep) {
+  for (int sweep = 0; sweep < FZ_SMALL_SWEEPS; ++sweep) {
     __syncthreads();
     if (t == 0) rotated[sweep & 1] = 0;
     for (int i = p; i < l; i += 64) {
@@ -911,7 +822,7 @@ __global__ void __launch_bounds__(1024) k_row_rotations(const double* __restrict
   }
   __syncthreads();
   // U = Z with columns of length one (a zero row of G is a direction of its own)
-  for (int i = p; i < l && !quiet; i += 64) {
+  for (int i = p; i < l; i += 64) {
     double s = 0.0;
     for (int q = 0; q < NQ; ++q) {
       const double x = Zt[i * LD + sub + 16 * q];
@@ -925,32 +836,263 @@ __global__ void __launch_bounds__(1024) k_row_rotations(const double* __restrict
     }
   }
   __syncthreads();
-  for (int idx = t; idx < l * l; idx += 1024) {
+  for (int idx = t; idx < l * l; idx += FZ_PASS_THREADS) {
     const int i = idx / l, k = idx - i * l;
     double v = Zt[k * LD + i];
-    if (!quiet) U[(long long)i * ldu + k] = v;
-    if (quiet) {
-      v = Um_old[(long long)i * ldu + k];
-    } else if (pass > 0) {
+    U[(long long)i * ldu + k] = v;
+    if (pass > 0) {
       v = 0.0;
       for (int c = 0; c < l; ++c) v += Um_old[(long long)i * ldu + c] * Zt[k * LD + c];
     }
     Um_new[(long long)i * ldu + k] = v;
   }
-  if (t == 0) *done = quiet ? pass : 1 << 30;
+  return false;
 }
 
-static void launch_row_rotations(const double* G, long long ldg, int l, double* U, const double* Um_old, double* Um_new,
-                                 long long ldu, int* done, int pass, hipStream_t st) {
-  const dim3 g(1), b(1024);
-  switch ((l + 15) / 16) {
-    case 1: case 2: k_row_rotations<2><<<g, b, 0, st>>>(G, ldg, l, U, Um_old, Um_new, ldu, done, pass); break;
-    case 3: k_row_rotations<3><<<g, b, 0, st>>>(G, ldg, l, U, Um_old, Um_new, ldu, done, pass); break;
-    case 4: k_row_rotations<4><<<g, b, 0, st>>>(G, ldg, l, U, Um_old, Um_new, ldu, done, pass); break;
-    case 5: k_row_rotations<5><<<g, b, 0, st>>>(G, ldg, l, U, Um_old, Um_new, ldu, done, pass); break;
-    case 6: k_row_rotations<6><<<g, b, 0, st>>>(G, ldg, l, U, Um_old, Um_new, ldu, done, pass); break;
-    default: k_row_rotations<8><<<g, b, 0, st>>>(G, ldg, l, U, Um_old, Um_new, ldu, done, pass); break;
+// ---------------------------------------------------------------------------------------
+// A pass of the orthonormalisation (rows of Y) or of the rotations (SVD: rows of Bs^T), one launch: every workgroup
+// takes its rows through LDS, 64 at a time, multiplies them with the factor of the pass before, stores them
+// and adds their part of the new Gram matrix; the workgroup that finds all others counted
+// adds the parts and takes the next factor from the sum.  As the launches gram, sum, factor and product a pass that had nothing
+// left to do cost four times 4.4 us (queued launches follow each other no faster), and there are four such passes for an
+// ordinary sketch.  Parts are added in two levels of about the square root of the workgroups, in workgroup order, so that no
+// workgroup reads all of them (80 parts of 30 KB at 80 columns); they travel past the L2s (device-scope stores,
+// a wait for them, a count).  The counts start at zero and whoever was last puts the zero back.  Nothing waits.
+// pass 0 adds the slices of the product before it into Y instead of applying a factor.
+// S2_FIGURES
+// ---------------------------------------------------------------------------------------
+struct PassArgs {
+  double* Y;               // [rows][ld]
+  const double* slices;    // [n_slices][rows][ld], read by pass 0
+  double* factor;          // [l][ld]
+  double* parts;           // [workgroups + groups][blocks][256]
+  int* counters;           // [groups + 1]
+  int rows, l, ld, n_slices;
+  int rows_per_wg, group, n_groups;     // rows of a workgroup (a multiple of 64), workgroups of a group
+  int* done;
+  int pass, passes;
+  // orthonormalisation
+  double* kept;
+  int* state;
+  // rotations; what the last pass leaves: singular values and their order, l x r matrix that takes Q to A
+  double* Um[2];           // pass p writes Um[p & 1]
+  int* sel;                // which of them holds the rotations
+  double* sigma_sorted;
+  int* perm;
+  double* sigma_out;       // or NULL
+  double* lift;            // [l][r16]
+  int r, r16;
+};
+constexpr int FZ_PASS_ROWS = 64, FZ_PASS_WGS = 128, FZ_PASS_GROUP = 12;
+constexpr int FZ_COUNTERS = 16;          // at least FZ_PASS_GROUP + 1, and FZ_MAX_SWEEPS
+
+__device__ inline double load_device(const double* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void store_device(double* p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// the caller's stores are out and it is counted; true for the workgroup that was last of n
+__device__ inline bool last_of(int* counter, int n) {
+  __shared__ int last;
+  vm_wait<0>();
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    last = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
+    if (last) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  __syncthreads();
+  return last != 0;
+}
+
+// The singular values from the Gram matrix of orthogonal rows (its diagonal), their descending order (equal values: lower
+// row first), and P[i][jr] = U~[i][perm jr] sqrt(sigma_jr), the l x r matrix that takes Q to A (Alg. 1, lift and balance)
+__device__ inline void sort_and_lift(const PassArgs& a, const double* S, int LD) {
+  __shared__ double sigma[FZ_SMALL];
+  __shared__ int order[FZ_SMALL];
+  const int t = threadIdx.x;
+  if (t < a.l) {
+    const double s = S[t * LD + t];
+    int rank = 0;
+    for (int b = 0; b < a.l; ++b) {
+      const double o = S[b * LD + b];
+      rank += (o > s || (o == s && b < t)) ? 1 : 0;
+    }
+    const double sg = sqrt(s);
+    sigma[rank] = sg;
+    order[rank] = t;
+    a.sigma_sorted[rank] = sg;
+    a.perm[rank] = t;
+    if (a.sigma_out) a.sigma_out[rank] = sg;
+  }
+  __syncthreads();
+  const double* Um = a.Um[*a.sel];
+  for (int idx = t; idx < a.l * a.r; idx += FZ_PASS_THREADS) {
+    const int i = idx / a.r, jr = idx - i * a.r;
+    a.lift[(long long)i * a.r16 + jr] = Um[(long long)i * a.ld + order[jr]] * sqrt(sigma[jr]);
+  }
+}
+
+template <int NB, bool SVD>
+__global__ void __launch_bounds__(FZ_PASS_THREADS) k_pass(PassArgs a) {
+  constexpr int LW = 16 * NB, LT = LW + 2, LD = SVD ? LW + (NB > 6 ? 4 : 16) : LW + 2;   // (the pad spreads columns over the banks)
+  constexpr int WAVES = FZ_PASS_THREADS / 64, BLOCKS = NB * (NB + 1) / 2, GB = (BLOCKS + WAVES - 1) / WAVES;
+  constexpr int RBS = FZ_PASS_ROWS / 16, TASKS = RBS * NB, AT = (TASKS + WAVES - 1) / WAVES;
+  constexpr int S_SIZE = LW * LD > FZ_PASS_ROWS * LT ? LW * LD : FZ_PASS_ROWS * LT;
+  __shared__ double S[S_SIZE];         // 64 rows of Y, then the Gram matrix
+  const bool apply = a.pass > 0;
+  const int done = apply ? *a.done : 0;
+  if (apply && done < a.pass) return;
+  const bool gram = SVD || !apply || (a.pass < a.passes && done != a.pass);
+  const int t = threadIdx.x, lane = t & 63, i = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6), wg = blockIdx.x;
+  auto block_at = [&](int b, int& I, int& K) {
+    for (I = 0; b >= NB - I; ++I) b -= NB - I;
+    K = I + b;
+  };
+  double4_t acc[GB];
+#pragma unroll
+  for (int q = 0; q < GB; ++q) acc[q] = double4_t{0.0, 0.0, 0.0, 0.0};
+  const int r_end = min(a.rows, (wg + 1) * a.rows_per_wg);
+  for (int r0 = wg * a.rows_per_wg; r0 < r_end; r0 += FZ_PASS_ROWS) {
+    for (int idx = t; idx < FZ_PASS_ROWS * LW / 2; idx += FZ_PASS_THREADS) {
+      const int row = idx / (LW / 2), c = 2 * (idx - row * (LW / 2));
+      double2 v = make_double2(0.0, 0.0);
+      if (r0 + row < r_end && c < a.l) {
+        const long long at = (long long)(r0 + row) * a.ld + c;
+        if (apply) {
+          v = *(const double2*)(a.Y + at);
+        } else {
+#pragma unroll 4
+          for (int sl = 0; sl < a.n_slices; ++sl) {
+            const double2 p = *(const double2*)(a.slices + (long long)sl * a.rows * a.ld + at);
+            v.x += p.x;
+            v.y += p.y;
+          }
+          *(double2*)(a.Y + at) = v;
+        }
+        if (c + 1 >= a.l) v.y = 0.0;
+      }
+      S[row * LT + c] = v.x;
+      S[row * LT + c + 1] = v.y;
+    }
+    __syncthreads();
+    if (apply) {
+      double4_t out[AT];
+#pragma unroll
+      for (int q = 0; q < AT; ++q) {
+        const int task = wave + WAVES * q, rb = task % RBS, cb = task / RBS, col = 16 * cb + i;
+        out[q] = double4_t{0.0, 0.0, 0.0, 0.0};
+        if (task < TASKS) {
+          for (int kb = 0; kb < (SVD ? NB : cb + 1); ++kb) {
+            double f[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const int ch = 16 * kb + 4 * e + g;
+              f[e] = ch < a.l && col < a.l ? a.factor[(long long)ch * a.ld + col] : 0.0;
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              out[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(S[(16 * rb + i) * LT + 16 * kb + 4 * e + g], f[e], out[q], 0, 0, 0);
+          }
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < AT; ++q) {
+        const int task = wave + WAVES * q, rb = task % RBS, cb = task / RBS, col = 16 * cb + i;
+        if (task < TASKS) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int row = 16 * rb + g + 4 * v;
+            S[row * LT + col] = out[q][v];
+            if (r0 + row < r_end && col < a.l) a.Y[(long long)(r0 + row) * a.ld + col] = out[q][v];
+          }
+        }
+      }
+      __syncthreads();
+    }
+    if (gram) {
+#pragma unroll
+      for (int q = 0; q < GB; ++q) {
+        const int b = wave + WAVES * q;
+        if (b < BLOCKS) {
+          int I, K;
+          block_at(b, I, K);
+#pragma unroll
+          for (int e = 0; e < FZ_PASS_ROWS / 4; ++e)
+            acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(S[(4 * e + g) * LT + 16 * I + i], S[(4 * e + g) * LT + 16 * K + i],
+                                                          acc[q], 0, 0, 0);
+        }
+      }
+    }
+    __syncthreads();
+  }
+  if (!gram) return;
+  constexpr int SIZE = BLOCKS * 256;   // a part: block after block, register after register
+#pragma unroll
+  for (int q = 0; q < GB; ++q) {
+    const int b = wave + WAVES * q;
+    if (b < BLOCKS) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) store_device(a.parts + (long long)wg * SIZE + b * 256 + v * 64 + lane, acc[q][v]);
+    }
+  }
+  const int grp = wg / a.group, first = grp * a.group, members = min(a.group, (int)gridDim.x - first);
+  auto sum = [&](const double* p, int n, int e) {
+    double v[FZ_PASS_GROUP], s = 0.0;
+#pragma unroll
+    for (int k = 0; k < FZ_PASS_GROUP; ++k) v[k] = load_device(p + (long long)min(k, n - 1) * SIZE + e);
+#pragma unroll
+    for (int k = 0; k < FZ_PASS_GROUP; ++k) s += k < n ? v[k] : 0.0;
+    return s;
+  };
+  if (!last_of(a.counters + grp, members)) return;
+  double* parts2 = a.parts + (long long)gridDim.x * SIZE;
+  for (int e = t; e < SIZE; e += FZ_PASS_THREADS) store_device(parts2 + (long long)grp * SIZE + e, sum(a.parts + (long long)first * SIZE, members, e));
+  if (!last_of(a.counters + a.n_groups, a.n_groups)) return;
+  for (int e = t; e < SIZE; e += FZ_PASS_THREADS) {
+    int I, K;
+    block_at(e >> 8, I, K);
+    S[(16 * I + ((e >> 4) & 3) + 4 * ((e >> 6) & 3)) * LD + 16 * K + (e & 15)] = sum(parts2, a.n_groups, e);
+  }
+  __syncthreads();
+  if constexpr (!SVD) {
+    cholesky_step<NB, LD>(S, a.l, a.factor, a.ld, a.kept, a.state, a.done, a.pass);
+  } else {
+    const bool orthogonal = a.pass == a.passes ||
+                            rotation_step<NB, LD>(S, a.l, a.factor, a.Um[(a.pass & 1) ^ 1], a.Um[a.pass & 1], a.ld, a.pass);
+    if (orthogonal) sort_and_lift(a, S, LD);
+    else if (t == 0) *a.sel = a.pass & 1;
+    if (t == 0) *a.done = orthogonal ? a.pass : 1 << 30;
+  }
+}
+
+template <bool SVD>
+static hipError_t launch_passes(PassArgs a, hipStream_t st) {
+  const int tiles = (a.rows + FZ_PASS_ROWS - 1) / FZ_PASS_ROWS, per = (tiles + FZ_PASS_WGS - 1) / FZ_PASS_WGS;
+  a.rows_per_wg = per * FZ_PASS_ROWS;
+  const int wgs = (tiles + per - 1) / per;
+  for (a.group = 1; a.group * a.group < wgs; ++a.group) {}
+  a.n_groups = (wgs + a.group - 1) / a.group;
+  const dim3 grid((unsigned)wgs), block(FZ_PASS_THREADS);
+  for (a.pass = 0; a.pass <= a.passes; ++a.pass) {
+    switch ((a.l + 15) / 16) {
+      case 1: case 2: k_pass<2, SVD><<<grid, block, 0, st>>>(a); break;
+      case 3: k_pass<3, SVD><<<grid, block, 0, st>>>(a); break;
+      case 4: k_pass<4, SVD><<<grid, block, 0, st>>>(a); break;
+      case 5: k_pass<5, SVD><<<grid, block, 0, st>>>(a); break;
+      case 6: k_pass<6, SVD><<<grid, block, 0, st>>>(a); break;
+      default: k_pass<8, SVD><<<grid, block, 0, st>>>(a); break;
+    }
+  }
+  return hipGetLastError();
+}
+
+// doubles of the parts of either kind of pass, whatever the rows
+static size_t pass_part_doubles(int l) {
+  const size_t nb = l > 96 ? 8 : std::max(2, (l + 15) / 16);
+  return (FZ_PASS_WGS + FZ_PASS_GROUP) * nb * (nb + 1) / 2 * 256;
 }
 
 __global__ void k_identity(double* U, long long ld, int l) {
@@ -995,28 +1137,100 @@ __global__ void k_build_lift(const double* __restrict__ Um, long long ldu, const
   P[(long long)i * ldp + jr] = Um[(long long)i * ldu + perm[jr]] * sqrt(sigma_sorted[jr]);
 }
 
-template <int ACT>
-__global__ void k_store_A(const double* __restrict__ A64, long long lda, long long row_off, int d_out, int r,
-                          uint16_t* __restrict__ A) {
-  const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (long long)d_out * r) return;
-  const long long o = idx / r;
-  const int j = (int)(idx - o * r);
-  A[idx] = (uint16_t)act16_round<ACT>(A64[(row_off + o) * lda + j]);
+// A_i = rows of Q P, B[jr][k] = row perm jr of Bs / sqrt(sigma_jr) * Sigma_x^(-1/2)[k], both rounded once to the
+// activation type.  The leading workgroups take 32 rows of Q x 16 NT columns of P each (the
+// channels dealt to the waves), the others 256 elements of B.
+struct LiftArgs {
+  const double* Q;         // [m][ldq], l columns
+  const double* P;         // [l][ldp], r columns
+  long long ldq, ldp;
+  int m, l, r, n0, row_tiles;
+  int n_modules, row_start[GLOWQ_MAX_MODULES];
+  uint16_t* A[GLOWQ_MAX_MODULES];
+  // element (a, i) of Um^T Bs at rows[a rs + i cs]
+  const double* rows;
+  long long rs, cs;
+  const double* sigma_sorted;
+  const int* perm;
+  const double* inv_root;  // or NULL
+  int d;
+  uint16_t* B;
+};
+
+template <int ACT, int NT>
+__global__ void __launch_bounds__(256) k_lift(LiftArgs a) {
+  __shared__ double fold[2 * NT * 256];
+  const int t = threadIdx.x;
+  if ((int)blockIdx.x >= a.row_tiles) {
+    const long long idx = (long long)((int)blockIdx.x - a.row_tiles) * 256 + t;
+    if (idx >= (long long)a.r * a.d) return;
+    const int jr = (int)(idx / a.d), k = (int)(idx - (long long)jr * a.d);
+    const double s = a.sigma_sorted[jr];
+    double v = s > 0.0 ? a.rows[(long long)a.perm[jr] * a.rs + k * a.cs] / sqrt(s) : 0.0;
+    if (a.inv_root) v *= a.inv_root[k];
+    a.B[idx] = (uint16_t)act16_round<ACT>(v);
+    return;
+  }
+  const int wave = t >> 6, l = t & 63, i = l & 15, g = l >> 4, row0 = (int)blockIdx.x * 32;
+  const int per = (a.l + 63) / 64 * 16, kbeg = wave * per, kend = min(a.l, kbeg + per);
+  double4_t acc[2][NT];
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) acc[rb][nt] = double4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int k0 = kbeg; k0 < kend; k0 += 4) {
+    const int k = k0 + g, kc = min(k, a.l - 1);
+    double q[2];
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) {
+      const double v = a.Q[(long long)min(a.m - 1, row0 + 16 * rb + i) * a.ldq + kc];
+      q[rb] = k < kend ? v : 0.0;
+    }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      const double b = a.P[(long long)kc * a.ldp + min(a.r - 1, a.n0 + 16 * nt + i)];
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) acc[rb][nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(q[rb], b, acc[rb][nt], 0, 0, 0);
+    }
+  }
+  fold_waves<2, NT>(acc, fold, wave, l);
+  if (wave != 0) return;
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int row = row0 + 16 * rb + g + 4 * v;
+      if (row >= a.m) continue;
+      int mi = 0;
+#pragma unroll
+      for (int q = 1; q < GLOWQ_MAX_MODULES; ++q)
+        if (q < a.n_modules && row >= a.row_start[q]) mi = q;
+      uint16_t* dst = a.A[mi] + (long long)(row - a.row_start[mi]) * a.r;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        const int col = a.n0 + 16 * nt + i;
+        if (col < a.r) dst[col] = (uint16_t)act16_round<ACT>(acc[rb][nt][v]);
+      }
+    }
 }
 
-// B[jr][k] = row perm jr of Bs / sqrt(sigma_jr) * Sigma_x^(-1/2)[k]
 template <int ACT>
-__global__ void k_store_B(const double* __restrict__ Bs, long long rs, long long cs, const double* sigma_sorted,
-                          const int* perm, const double* __restrict__ inv_root, int r, int d,
-                          uint16_t* __restrict__ B) {
-  const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (long long)r * d) return;
-  const int jr = (int)(idx / d), k = (int)(idx - (long long)jr * d);
-  const double s = sigma_sorted[jr];
-  double v = s > 0.0 ? Bs[(long long)perm[jr] * rs + k * cs] / sqrt(s) : 0.0;
-  if (inv_root) v *= inv_root[k];
-  B[idx] = (uint16_t)act16_round<ACT>(v);
+static hipError_t launch_lift(LiftArgs a, hipStream_t st) {
+  a.row_tiles = (a.m + 31) / 32;
+  for (a.n0 = 0; a.n0 < a.r; a.n0 += 16 * FZ_NT) {
+    // (B with the first pass of columns)
+    const unsigned n_b = a.n0 == 0 ? (unsigned)(((long long)a.r * a.d + 255) / 256) : 0u;
+    const dim3 grid((unsigned)a.row_tiles + n_b), block(256);
+    switch ((std::min(a.r - a.n0, 16 * FZ_NT) + 15) / 16) {
+      case 1: k_lift<ACT, 1><<<grid, block, 0, st>>>(a); break;
+      case 2: k_lift<ACT, 2><<<grid, block, 0, st>>>(a); break;
+      case 3: k_lift<ACT, 3><<<grid, block, 0, st>>>(a); break;
+      case 4: k_lift<ACT, 4><<<grid, block, 0, st>>>(a); break;
+      default: k_lift<ACT, 5><<<grid, block, 0, st>>>(a); break;
+    }
+  }
+  return hipGetLastError();
 }
 
 __global__ void k_copy_doubles(const double* src, double* dst, int n) {
@@ -1048,18 +1262,10 @@ FactorizePlan plan_factorize(const glowq_unit& u, int r, int p) {
   f.off_z = take((size_t)f.d * f.l16 * 8);
   f.off_bs = take((size_t)f.l * f.d * 8);
   f.off_ut = take((size_t)f.l * f.l16 * 8);
-  f.off_gram = take((size_t)f.l * f.l16 * 8);
+  f.off_parts = take(f.l <= FZ_SMALL ? pass_part_doubles(f.l) * 8 : 0);
   f.off_lift = take((size_t)f.l * f.r16 * 8);
-  f.off_a64 = take((size_t)m * f.r16 * 8);
-  size_t sl = slice_doubles(plan_ring((int)m, f.d), (int)m, f.l);               // Y = Ms Omega, Y = Ms Z
-  const size_t s2 = slice_doubles(plan_ring(f.d, (int)m), f.d, f.l);            // Z = Ms^T Y, Bs^T = Ms^T Q
-  const size_t s3 = slice_doubles(plan_short((int)m, f.l), (int)m, r);          // A = Q P
-  const size_t s4 = slice_doubles(plan_ring(f.l, f.d), f.l, f.l);               // Gram of Bs
-  const size_t s5 = slice_doubles(plan_short(f.d, f.l), f.d, f.l);              // rows = Um^T Bs
-  const size_t s6 = slice_doubles(plan_short((int)m, f.l), (int)m, f.l);        // Y Tinv
-  const size_t s7 = slice_doubles(plan_ring(f.l, (int)m), f.l, f.l);            // Gram of Y
-  for (size_t o : {s2, s3, s4, s5, s6, s7})
-    if (o > sl) sl = o;
+  const size_t sl = std::max(slice_doubles(plan_ring((int)m, f.d), (int)m, f.l),     // Y = Ms Omega, Y = Ms Z
+                             slice_doubles(plan_ring(f.d, (int)m), f.d, f.l));       // Z = Ms^T Y, Bs^T = Ms^T Q
   f.off_slices = take(sl * 8);
   f.off_root = take((size_t)f.d * 8);
   f.off_inv_root = take((size_t)f.d * 8);
@@ -1070,12 +1276,12 @@ FactorizePlan plan_factorize(const glowq_unit& u, int r, int p) {
   f.off_sig2 = take(256 * 8);
   f.off_sigma = take(256 * 8);
   f.off_perm = take(256 * 4);
-  f.off_counters = take(FZ_MAX_SWEEPS * 4);
+  f.off_counters = take(FZ_COUNTERS * 4);
   f.off_rot = take((size_t)f.l * f.l16 * 8);
   f.off_um2 = take((size_t)f.l * f.l16 * 8);
   f.off_kept = take(256 * 8);
   f.off_state = take(256 * 4);
-  f.off_done = take(2 * 4);
+  f.off_done = take(3 * 4);
   f.bytes = off;
   return f;
 }
@@ -1091,10 +1297,8 @@ hipError_t launch_factorize(const glowq_unit& u, const float* const* W_modules, 
   double* Z = (double*)(ws + f.off_z);
   double* Bs = (double*)(ws + f.off_bs);
   double* Um = (double*)(ws + f.off_ut);
-  double* gram = (double*)(ws + f.off_gram);
   double* lift = (double*)(ws + f.off_lift);
   double* factor = (double*)(ws + f.off_rot);      // [l][l16]: the matrix a pass multiplies with
-  double* A64 = (double*)(ws + f.off_a64);
   double* slices = (double*)(ws + f.off_slices);
   double* root = sigma_x ? (double*)(ws + f.off_root) : nullptr;
   double* inv_root = sigma_x ? (double*)(ws + f.off_inv_root) : nullptr;
@@ -1110,7 +1314,7 @@ hipError_t launch_factorize(const glowq_unit& u, const float* const* W_modules, 
 
   hipError_t err = hipSuccess;
   k_setup<<<dim3((unsigned)((d * f.l16 + 255) / 256)), dim3(256), 0, st>>>(sigma_x, d, root, inv_root, Omega, l, f.l16, Z,
-                                                                          counters, FZ_MAX_SWEEPS);
+                                                                          counters, FZ_COUNTERS);
   // the stack, scaled by Sigma_x^(1/2) (Alg. 1, core construction)
   long long row_off = 0;
   for (int i = 0; i < u.n_modules; ++i) {
@@ -1122,38 +1326,51 @@ hipError_t launch_factorize(const glowq_unit& u, const float* const* W_modules, 
     row_off += mod.d_out;
   }
   // sketch and power steps (Alg. 1, range finding)
-  err = gemm<FZ_NN>(Ms, d, Z, f.l16, Y, f.l16, false, m, l, d, slices, st);
+  const bool small = l <= FZ_SMALL;
+  int n_slices = 0;                                // (small: the first pass of the orthonormalisation adds the last ones)
+  err = gemm<false>(Ms, d, Z, f.l16, Y, f.l16, false, m, l, d, slices, st, small && q == 0 ? &n_slices : nullptr);
   for (int it = 0; it < q && err == hipSuccess; ++it) {
-    err = gemm<FZ_TN>(Ms, d, Y, f.l16, Z, f.l16, false, d, l, m, slices, st);
-    if (err == hipSuccess) err = gemm<FZ_NN>(Ms, d, Z, f.l16, Y, f.l16, false, m, l, d, slices, st);
+    err = gemm<true>(Ms, d, Y, f.l16, Z, f.l16, false, d, l, m, slices, st);
+    if (err == hipSuccess) err = gemm<false>(Ms, d, Z, f.l16, Y, f.l16, false, m, l, d, slices, st, small && it == q - 1 ? &n_slices : nullptr);
   }
   if (err != hipSuccess) return err;
   // orthonormal basis of the range, compressed matrix Bs = Q^T Ms and its SVD
   const double* rows;          // element (a, i) of Um^T Bs at a rows_rs + i rows_cs
   long long rows_rs, rows_cs;
-  if (l <= FZ_SMALL) {
+  if (small) {
     int* done = (int*)(ws + f.off_done);
-    for (int pass = 0; pass < FZ_QR_PASSES; ++pass) {
-      const int* stop = pass ? done : nullptr;
-      err = gemm<FZ_TN>(Y, f.l16, Y, f.l16, gram, f.l16, false, l, l, m, slices, st, stop, pass);
-      if (err != hipSuccess) return err;
-      k_cholesky_step<<<dim3(1), dim3(1024), 0, st>>>(gram, f.l16, l, factor, f.l16, (double*)(ws + f.off_kept),
-                                                      (int*)(ws + f.off_state), done, pass);
-      err = gemm<FZ_SHORT>(Y, f.l16, factor, f.l16, Y, f.l16, false, m, l, l, slices, st, stop, pass);
-      if (err != hipSuccess) return err;
-    }
+    PassArgs pa = {};
+    pa.slices = slices;
+    pa.factor = factor;
+    pa.parts = (double*)(ws + f.off_parts);
+    pa.counters = counters;
+    pa.l = l; pa.ld = f.l16;
+    pa.Y = Y;
+    pa.n_slices = n_slices;
+    pa.rows = m;
+    pa.done = done;
+    pa.passes = FZ_QR_PASSES;
+    pa.kept = (double*)(ws + f.off_kept);
+    pa.state = (int*)(ws + f.off_state);
+    err = launch_passes<false>(pa, st);
+    if (err != hipSuccess) return err;
     double* BsT = Z;                                                               // [d][l16]
-    err = gemm<FZ_TN>(Ms, d, Y, f.l16, BsT, f.l16, false, d, l, m, slices, st);     // Ms^T Q
-    double* Um_old = (double*)(ws + f.off_um2);
-    for (int pass = 0; pass < FZ_SVD_PASSES && err == hipSuccess; ++pass) {
-      const int* stop = pass ? done + 1 : nullptr;
-      err = gemm<FZ_TN>(BsT, f.l16, BsT, f.l16, gram, f.l16, false, l, l, d, slices, st, stop, pass);
-      if (err != hipSuccess) return err;
-      launch_row_rotations(gram, f.l16, l, factor, Um_old, Um, f.l16, done + 1, pass, st);
-      // (a pass that found nothing to rotate has set the flag to its own number)
-      err = gemm<FZ_SHORT>(BsT, f.l16, factor, f.l16, BsT, f.l16, false, d, l, l, slices, st, done + 1, pass);
-      if (pass + 1 < FZ_SVD_PASSES) std::swap(Um, Um_old);
-    }
+    err = gemm<true>(Ms, d, Y, f.l16, BsT, f.l16, false, d, l, m, slices, st, &n_slices);     // Ms^T Q
+    if (err != hipSuccess) return err;
+    pa.Y = BsT;
+    pa.n_slices = n_slices;
+    pa.rows = d;
+    pa.done = done + 1;
+    pa.passes = FZ_SVD_PASSES;
+    pa.Um[0] = Um;
+    pa.Um[1] = (double*)(ws + f.off_um2);
+    pa.sel = done + 2;
+    pa.sigma_sorted = sigma_sorted;
+    pa.perm = perm;
+    pa.sigma_out = sigma_out;
+    pa.lift = lift;
+    pa.r = r; pa.r16 = f.r16;
+    err = launch_passes<true>(pa, st);
     if (err != hipSuccess) return err;
     rows = BsT;
     rows_rs = 1;
@@ -1170,7 +1387,7 @@ hipError_t launch_factorize(const glowq_unit& u, const float* const* W_modules, 
         k_cgs<<<dim3((unsigned)f.n_groups), dim3(256), 0, st>>>(Y, f.l16, m, l, f.rpw, f.n_groups, 0, 2, cb);
       }
     }
-    err = gemm<FZ_TN>(Ms, d, Y, f.l16, Bs, d, true, d, l, m, slices, st);           // (Ms^T Q)^T
+    err = gemm<true>(Ms, d, Y, f.l16, Bs, d, true, d, l, m, slices, st);           // (Ms^T Q)^T
     if (err != hipSuccess) return err;
     k_identity<<<dim3((unsigned)((l * l + 255) / 256)), dim3(256), 0, st>>>(Um, f.l16, l);
     const int n = (l + 1) & ~1;
@@ -1180,30 +1397,31 @@ hipError_t launch_factorize(const glowq_unit& u, const float* const* W_modules, 
     rows = Bs;
     rows_rs = d;
     rows_cs = 1;
+    k_row_norms<<<dim3((unsigned)l), dim3(256), 0, st>>>(rows, rows_rs, rows_cs, d, sig2);
+    k_sort_sigma<<<dim3(1), dim3(256), 0, st>>>(sig2, l, sigma_sorted, perm);
+    // truncate, balance
+    k_build_lift<<<dim3((unsigned)((l * r + 255) / 256)), dim3(256), 0, st>>>(Um, f.l16, sigma_sorted, perm, l, r, lift, f.r16);
+    if (sigma_out) k_copy_doubles<<<dim3(1), dim3(256), 0, st>>>(sigma_sorted, sigma_out, l);
   }
-  k_row_norms<<<dim3((unsigned)l), dim3(256), 0, st>>>(rows, rows_rs, rows_cs, d, sig2);
-  k_sort_sigma<<<dim3(1), dim3(256), 0, st>>>(sig2, l, sigma_sorted, perm);
-  // truncate, balance, lift
-  k_build_lift<<<dim3((unsigned)((l * r + 255) / 256)), dim3(256), 0, st>>>(Um, f.l16, sigma_sorted, perm, l, r, lift, f.r16);
-  err = gemm<FZ_SHORT>(Y, f.l16, lift, f.r16, A64, f.r16, false, m, r, l, slices, st);
-  if (err != hipSuccess) return err;
+  // lift
+  LiftArgs la = {};
+  la.Q = Y; la.P = lift;
+  la.ldq = f.l16; la.ldp = f.r16;
+  la.m = m; la.l = l; la.r = r;
+  la.n_modules = u.n_modules;
   row_off = 0;
   for (int i = 0; i < u.n_modules; ++i) {
-    const glowq_module& mod = u.modules[i];
-    const long long n_el = (long long)mod.d_out * r;
-    dim3 grid((unsigned)((n_el + 255) / 256)), block(256);
-    if (f16) k_store_A<ACT_F16><<<grid, block, 0, st>>>(A64, f.r16, row_off, mod.d_out, r, (uint16_t*)A_out[i]);
-    else k_store_A<ACT_BF16><<<grid, block, 0, st>>>(A64, f.r16, row_off, mod.d_out, r, (uint16_t*)A_out[i]);
-    row_off += mod.d_out;
+    la.row_start[i] = (int)row_off;
+    la.A[i] = (uint16_t*)A_out[i];
+    row_off += u.modules[i].d_out;
   }
-  {
-    const long long n_el = (long long)r * d;
-    dim3 grid((unsigned)((n_el + 255) / 256)), block(256);
-    if (f16) k_store_B<ACT_F16><<<grid, block, 0, st>>>(rows, rows_rs, rows_cs, sigma_sorted, perm, inv_root, r, d, (uint16_t*)B_out);
-    else k_store_B<ACT_BF16><<<grid, block, 0, st>>>(rows, rows_rs, rows_cs, sigma_sorted, perm, inv_root, r, d, (uint16_t*)B_out);
-  }
-  if (sigma_out) k_copy_doubles<<<dim3(1), dim3(256), 0, st>>>(sigma_sorted, sigma_out, l);
-  return hipGetLastError();
+  la.rows = rows; la.rs = rows_rs; la.cs = rows_cs;
+  la.sigma_sorted = sigma_sorted;
+  la.perm = perm;
+  la.inv_root = inv_root;
+  la.d = d;
+  la.B = (uint16_t*)B_out;
+  return f16 ? launch_lift<ACT_F16>(la, st) : launch_lift<ACT_BF16>(la, st);
 }
 
 }  // namespace glowq
