@@ -339,14 +339,57 @@ __device__ inline double read_lane(double v, int lane) {
   return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
+// lane J's value of every row of 16 lanes, in all its lanes
+template <int J> __device__ inline double row_broadcast(double v) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x150 | J, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x150 | J, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+// lane `from`'s value (any lane of the wave)
+__device__ inline double lane_permute(double v, int from) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * from, (int)(uint32_t)u);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * from, (int)(uint32_t)(u >> 32));
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// Step J of a diagonal block (see block_cholesky): lane (i, g) holds rows 4 q + g of column i in a[q].
+// Columns behind J take the multiple of column J out of themselves, column J is scaled where it is the
+// inverse's.
+template <int J, class PIVOT>
+__device__ __attribute__((always_inline)) inline void diagonal_steps(double (&a)[4], int i, int g, bool& used, PIVOT& pivot) {
+  if constexpr (J < 16) {
+    constexpr int QJ = J >> 2, GJ = J & 3;
+    const double mine = lane_permute(a[QJ], i + 16 * GJ);          // row J of this lane's column
+    double own = 0.0;
+    const double ri = pivot.take(J, read_lane(a[QJ], J + 16 * GJ), own);
+    const double w = -mine * ri * ri;
+    const bool behind = i > J, at = i == J;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const double v = row_broadcast<J>(a[q]);
+      const double moved = __builtin_fma(v, w, a[q]), scaled = a[q] * own;
+      const bool above = q < QJ || (q == QJ && g < GJ);
+      double x = behind ? moved : (at && above ? scaled : a[q]);
+      if (q == QJ && g == GJ) x = behind ? w : (at ? own : a[q]);
+      a[q] = x;
+    }
+    if (at) used = ri > 0.0;
+    diagonal_steps<J + 1>(a, i, g, used, pivot);
+  }
+}
+
 // Cholesky factor R (upper, S = R^T R) of a symmetric matrix of nb x nb blocks of 16 in LDS
 // (S [16 nb][LD], upper blocks and whole diagonal blocks), by one workgroup; with INVERSE, S
 // ends as the upper triangular T = R^-1, without it as R.  Panels of 16 rows: one wave factors
-// and inverts the diagonal block with a column per lane, matrix instructions do the rest.  The
-// code is kept small on purpose: a lone workgroup that runs through it once is bound by fetching
-// its instructions (unrolled over registers, element by element, 80 columns took 230 us, this
-// about 20).  pivot(j, d, own) returns 1 / sqrt(d) if column j is to be used and 0 if not;
-// `own` then scales what stays of its own column in T.  E, F, Rb: LDS, 256, 256 and 16 LD
+// and inverts the diagonal block, four rows of a column per lane, matrix instructions do the rest.
+// The serial chain of the diagonal block's sixteen steps bounds it; what a step needs of a lane's own column
+// comes through a row broadcast, what it needs of the pivot row through one permutation under the
+// latency of the square root, and the decisions about pivots stay in registers until the panel is done (with a
+// column per lane and the pivots' state in LDS 80 columns took 41 us, now 25).
+// PIVOT: begin(J) before panel J's steps; take(j, d, own) returns 1 / sqrt(d) if column 16 J + j is to be used and 0 if not,
+// `own` then scales what stays of its own column in T; end(J).  E, F, Rb: LDS, 256, 256 and 16 LD
 // doubles (Rb only with INVERSE).
 template <bool INVERSE, class PIVOT>
 __device__ inline void block_cholesky(double* S, int LD, int nb, double* E, double* F, double* Rb, PIVOT pivot) {
@@ -366,35 +409,18 @@ __device__ inline void block_cholesky(double* S, int LD, int nb, double* E, doub
     double* Sj = S + 16 * J * LD;                    // block row J
     __syncthreads();
     if (wave == 0) {
-      double a[16];
+      double a[4];
       bool used = false;
 #pragma unroll
-      for (int k = 0; k < 16; ++k) a[k] = Sj[k * LD + 16 * J + i];
+      for (int q = 0; q < 4; ++q) a[q] = Sj[(4 * q + g) * LD + 16 * J + i];
+      pivot.begin(J);
+      diagonal_steps<0>(a, i, g, used, pivot);
+      pivot.end(J);
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        double own = 0.0;
-        const double ri = pivot(16 * J + j, read_lane(a[j], j), own);
-        const double w = -a[j] * ri * ri;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-          if (k == j) continue;
-          const double v = read_lane(a[k], j);
-          if (i > j) a[k] = __builtin_fma(v, w, a[k]);
-          else if (i == j && k < j) a[k] *= own;
-        }
-        if (i > j) a[j] = w;
-        else if (i == j) {
-          a[j] = own;
-          used = ri > 0.0;
-        }
-      }
-      if (lane < 16) {
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-          const double f = k <= i ? a[k] : 0.0;
-          F[k * 16 + i] = f;
-          E[k * 16 + i] = used ? f : 0.0;
-        }
+      for (int q = 0; q < 4; ++q) {
+        const double f = 4 * q + g <= i ? a[q] : 0.0;
+        F[(4 * q + g) * 16 + i] = f;
+        E[(4 * q + g) * 16 + i] = used ? f : 0.0;
       }
     }
     __syncthreads();
@@ -437,6 +463,38 @@ __device__ inline void block_cholesky(double* S, int LD, int nb, double* E, doub
   __syncthreads();
 }
 
+// The decisions about the columns of a sketch.  Kept: scaled to length one; deferred: as the projections left it; dropped:
+// cleared
+struct SketchPivot {
+  const double* scale;
+  int *st, *pending;
+  double* least;
+  bool last;
+  uint32_t dropped, kept, deferred;    // of the panel's columns
+  double lowest;
+  __device__ inline void begin(int J) {
+    dropped = (uint32_t)__builtin_amdgcn_ballot_w64(scale[16 * J + (threadIdx.x & 15)] == 0.0);
+    kept = deferred = 0;
+  }
+  __device__ inline double take(int j, double d, double& own) {
+    const bool out = (dropped >> j) & 1u, keep = !out && d > FZ_ACCEPT;
+    const double ri = keep ? inv_sqrt(d) : 0.0;
+    own = keep ? ri : (out || last ? 0.0 : 1.0);
+    lowest = keep ? fmin(lowest, d) : lowest;
+    kept |= (keep ? 1u : 0u) << j;
+    deferred |= (!keep && !out ? 1u : 0u) << j;
+    return ri;
+  }
+  __device__ inline void end(int J) {
+    const int t = threadIdx.x;
+    if (t < 16) st[16 * J + t] = (kept >> t) & 1u ? FZ_KEPT : ((deferred >> t) & 1u && !last ? FZ_PENDING : FZ_DROPPED);
+    if (t == 0) {
+      *least = lowest;
+      if (deferred) *pending = 1;
+    }
+  }
+};
+
 // The factor of a pass of the orthonormalisation, by one workgroup.  S: Gram matrix (upper blocks, rows of LD);
 // Tinv (upper triangular): Y Tinv is the next Y.
 template <int NB, int LD>
@@ -467,19 +525,7 @@ __device__ inline void cholesky_step(double* S, int l, double* Tinv, long long l
     const double w = scale[i] * scale[k];
     S[i * LD + k] = w > 0.0 && (i >> 4) <= (k >> 4) ? S[i * LD + k] * w : 0.0;
   }
-  block_cholesky<true>(S, LD, nb, E, F, Rb, [&](int j, double d, double& own) {
-    // (wave 0 only.)  Kept: scaled to length one; deferred: as the projections left it; dropped:
-    // cleared
-    const bool dropped = scale[j] == 0.0, keep = !dropped && d > FZ_ACCEPT;
-    const double ri = keep ? inv_sqrt(d) : 0.0;
-    own = keep ? ri : (dropped || last ? 0.0 : 1.0);
-    if (t == 0) {
-      st[j] = keep ? FZ_KEPT : (dropped || last ? FZ_DROPPED : FZ_PENDING);
-      if (keep) least = fmin(least, d);
-      else if (!dropped) pending = 1;
-    }
-    return ri;
-  });
+  block_cholesky<true>(S, LD, nb, E, F, Rb, SketchPivot{scale, st, &pending, &least, last, 0, 0, 0, 1.0});
   for (int idx = t; idx < l * l; idx += FZ_PASS_THREADS) {
     const int i = idx / l, k = idx - i * l;
     Tinv[(long long)i * ldt + k] = k >= i ? scale[i] * S[i * LD + k] : 0.0;
@@ -715,6 +761,22 @@ __device__ inline double row_sum16(double v) {
   return v;
 }
 
+struct GramPivot {
+  double* tiny;
+  uint32_t rounding;                   // the panel's columns whose pivot is only that
+  __device__ inline void begin(int) { rounding = 0; }
+  __device__ inline double take(int j, double d, double& own) {
+    const bool real = d > FZ_PIVOT;
+    own = real ? inv_sqrt(d) : 0.0;
+    rounding |= (real ? 0u : 1u) << j;
+    return own;
+  }
+  __device__ inline void end(int J) {
+    const int t = threadIdx.x;
+    if (t < 16 && ((rounding >> t) & 1u)) tiny[16 * J + t] = sqrt(FZ_PIVOT);
+  }
+};
+
 // NQ: 16-element pieces of a column (l <= 16 NQ).  Zt: Gram matrix (upper blocks, rows of LD), then Zt[k] is column k
 // of Z.  Returns true, with Zt's diagonal as it was, if the rows are orthogonal already; else U is the rotation, and
 // Um_new = Um_old U the rotations so far (pass 0: U).
@@ -748,13 +810,7 @@ __device__ inline bool rotation_step(double* Zt, int l, double* __restrict__ U, 
   }
   __syncthreads();
   {
-    block_cholesky<false>(Zt, LD, NQ, E, F, nullptr, [&](int j, double d, double& own) {
-      const bool real = d > FZ_PIVOT;
-      if (!real && t == 0) tiny[j] = sqrt(FZ_PIVOT);
-      const double ri = real ? inv_sqrt(d) : 0.0;
-      own = ri;
-      return ri;
-    });
+    block_cholesky<false>(Zt, LD, NQ, E, F, nullptr, GramPivot{tiny, 0});
     // column j of Z: row j of the factor, every element scaled back by its row's length
     for (int idx = t; idx < LW * LW; idx += FZ_PASS_THREADS) {
       const int j = idx / LW, k = idx - j * LW;
@@ -859,7 +915,7 @@ __device__ inline bool rotation_step(double* Zt, int l, double* __restrict__ U, 
 // workgroup reads all of them (80 parts of 30 KB at 80 columns); they travel past the L2s (device-scope stores,
 // a wait for them, a count).  The counts start at zero and whoever was last puts the zero back.  Nothing waits.
 // pass 0 adds the slices of the product before it into Y instead of applying a factor.
-// S2_FIGURES
+// 5120 x 80, us: a pass 80 -> 52 (25 of them the factor, 9 the sum of the parts), a pass with nothing to do 18.5 -> 4.5.
 // ---------------------------------------------------------------------------------------
 struct PassArgs {
   double* Y;               // [rows][ld]
