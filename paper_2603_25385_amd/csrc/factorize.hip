@@ -24,6 +24,7 @@
 #include "common.hpp"
 #include "launch.hpp"
 #include <algorithm>
+#include <utility>
 
 namespace glowq {
 
@@ -341,10 +342,8 @@ __device__ inline double read_lane(double v, int lane) {
 
 // lane J's value of every row of 16 lanes, in all its lanes
 template <int J> __device__ inline double row_broadcast(double v) {
-  const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x150 | J, 0xf, 0xf, true);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x150 | J, 0xf, 0xf, true);
-  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+  const long long u = __builtin_amdgcn_update_dpp(0ll, __builtin_bit_cast(long long, v), 0x150 | J, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, u);
 }
 // lane `from`'s value (any lane of the wave)
 __device__ inline double lane_permute(double v, int from) {
@@ -737,8 +736,8 @@ __global__ void __launch_bounds__(FZ_JT) k_jacobi_round(double* __restrict__ Bs,
 // length: a second pass removes what the first one's rounding left (relative to the largest
 // row), a third only runs when the second still found something to rotate.  Any orthogonal U is
 // exact work whatever G was, so a pivot that is only rounding is replaced by FZ_PIVOT and costs
-// convergence, not accuracy.  80 rows of 3072: 540 us, of them 510 in seven to eight sweeps of 79
-// rounds, bound by issue and LDS (1600 cycles a round); two-sided rotations with three barriers a
+// convergence, not accuracy.  Up to FZ_DIRECT rows the first pass takes the road below instead, where it can.  80 rows of 3072:
+// 510 us in seven to eight sweeps of 79 rounds, bound by issue and LDS (1600 cycles a round); two-sided rotations with three barriers a
 // round followed by one launch per round on the long rows took 1830 + 1620 us.
 constexpr int FZ_SVD_PASSES = 3;
 constexpr int FZ_SMALL_SWEEPS = 12;
@@ -776,6 +775,29 @@ struct GramPivot {
     if (t < 16 && ((rounding >> t) & 1u)) tiny[16 * J + t] = sqrt(FZ_PIVOT);
   }
 };
+
+__device__ inline double load_device(const double* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void store_device(double* p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// U from its columns in the rows of Zt; Um_new = Um_old U (pass 0: U)
+template <int LD>
+__device__ inline void store_rotation(const double* Zt, int l, double* __restrict__ U, const double* __restrict__ Um_old,
+                                      double* __restrict__ Um_new, long long ldu, int pass) {
+  const int t = threadIdx.x;
+  for (int idx = t; idx < l * l; idx += FZ_PASS_THREADS) {
+    const int i = idx / l, k = idx - i * l;
+    double v = Zt[k * LD + i];
+    U[(long long)i * ldu + k] = v;
+    if (pass > 0) {
+      v = 0.0;
+      for (int c = 0; c < l; ++c) v += Um_old[(long long)i * ldu + c] * Zt[k * LD + c];
+    }
+    Um_new[(long long)i * ldu + k] = v;
+  }
+}
 
 // NQ: 16-element pieces of a column (l <= 16 NQ).  Zt: Gram matrix (upper blocks, rows of LD), then Zt[k] is column k
 // of Z.  Returns true, with Zt's diagonal as it was, if the rows are orthogonal already; else U is the rotation, and
@@ -892,15 +914,350 @@ __device__ inline bool rotation_step(double* Zt, int l, double* __restrict__ U, 
     }
   }
   __syncthreads();
-  for (int idx = t; idx < l * l; idx += FZ_PASS_THREADS) {
-    const int i = idx / l, k = idx - i * l;
-    double v = Zt[k * LD + i];
-    U[(long long)i * ldu + k] = v;
-    if (pass > 0) {
-      v = 0.0;
-      for (int c = 0; c < l; ++c) v += Um_old[(long long)i * ldu + c] * Zt[k * LD + c];
+  store_rotation<LD>(Zt, l, U, Um_old, Um_new, ldu, pass);
+  return false;
+}
+
+// ---------------------------------------------------------------------------------------
+// The first rotation of up to FZ_DIRECT rows by another road: the eigenvectors of the Gram matrix, through its
+// tridiagonal form (Householder), bisection on sign counts of the leading minors, one twisted factorisation per eigenvalue
+// (Parlett and Dhillon: the solve starts at the row where it leaves the least residual), the
+// reflections applied backwards, and U <- U (3 - U^T U) / 2, which makes vectors of close eigenvalues
+// orthogonal to rounding.  A rotation to the accuracy of the largest row is all that the first pass has to give: any orthogonal U
+// is exact work, the next pass measures what is left on the rows themselves and rotates the rest away.  So a
+// spectrum that spans more than FZ_DIRECT_RANGE, and vectors that come out far from orthogonal
+// (eigenvalues equal to rounding), are left to the rotations below.  One workgroup: a chain of barriers (two a
+// column) and of dependent float64 instructions.
+// 80 rows of 3072, us: 155 (tridiagonal 64, bisection 37, twisted factorisations 32, reflections 12, orthogonality 10) where
+// the rotations take 510; what the rows have left is then 5e-16 of their lengths.
+// ---------------------------------------------------------------------------------------
+constexpr int FZ_DIRECT = 80;
+constexpr double FZ_DIRECT_RANGE = 1e-6;     // smallest over largest eigenvalue
+constexpr double FZ_ORTHO_TRIES = 0.25, FZ_ORTHO_ONE = 1e-8;   // |U^T U - 1| that can be mended at all, and by one step
+
+template <int CTRL> __device__ inline double dpp_move(double v) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+// sum over eight neighbouring lanes, in all of them: lanes ^ 1, ^ 2, and the mirror image
+__device__ inline double sum8(double v) {
+  v += dpp_move<0xB1>(v);
+  v += dpp_move<0x4E>(v);
+  v += dpp_move<0x141>(v);
+  return v;
+}
+// 1 / x to working precision: the hardware's estimate and two Newton steps
+__device__ inline double inv(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = __builtin_fma(y, __builtin_fma(-x, y, 1.0), y);
+  return __builtin_fma(y, __builtin_fma(-x, y, 1.0), y);
+}
+__device__ inline double pivot_guard(double q) { return fabs(q) < 0x1p-60 ? copysign(0x1p-60, q) : q; }
+
+// f(0), .. f(N - 1) with compile-time indexes
+template <class F, int... I> __device__ __attribute__((always_inline)) inline void static_for(F f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F> __device__ __attribute__((always_inline)) inline void static_for(F f) {
+  static_for(f, std::make_integer_sequence<int, N>{});
+}
+
+// How many eigenvalues of the tridiagonal matrix lie below x: sign changes of its leading minors,
+// p_i = (d_i - x) p_i-1 - e_i-1^2 p_i-2, their sign bits collected in a word.  de[i] = {d_i, -e_i-1^2}, zeros behind l;
+// sixteen elements travel in the lanes of a row and are broadcast from there.  One multiply-add of a step waits for the
+// step before (with two more of them in that chain 4100 cycles for 80 steps, now 3100).
+__device__ inline int eigenvalues_below(const double2* de, int l, double x) {
+  double p = 1.0, pp = 0.0;
+  int below = 0;
+  auto high = [](double v) { return (uint32_t)(__builtin_bit_cast(unsigned long long, v) >> 32); };
+  for (int i0 = 0; i0 < l; i0 += 16) {
+    const int n = min(16, l - i0);
+    const double2 v = de[i0 + (threadIdx.x & 15)];
+    uint32_t signs = high(p) >> 31;                  // of the minor before the chunk, then of its own
+    static_for<16>([&](auto J) __attribute__((always_inline)) {      // (behind l too: no branch parts the steps)
+      constexpr int j = J.value;
+      const double next = __builtin_fma(row_broadcast<j>(v.x) - x, p, row_broadcast<j>(v.y) * pp);
+      pp = p;
+      p = next;
+      signs = __builtin_amdgcn_alignbit(signs, high(p), 31);
+      if constexpr (j == 7 || j == 15) {
+        const int ex = max(__builtin_amdgcn_frexp_exp(p), __builtin_amdgcn_frexp_exp(pp));
+        p = __builtin_amdgcn_ldexp(p, -ex);
+        pp = __builtin_amdgcn_ldexp(pp, -ex);
+      }
+    });
+    below += __popc((signs ^ (signs >> 1)) & (((1u << n) - 1u) << (16 - n)));
+  }
+  return below;
+}
+
+// Zt: Gram matrix (upper blocks, rows of LD).  True: eigenvector k is row k of Zt, rows of LV, V undefined; false: Zt
+// undefined.  V: LDS,
+// 16 NQ rows of LV (lanes that go down a column of either meet other banks).
+template <int NQ, int LD, int LV>
+__device__ inline bool eigenvectors(double* Zt, double* V, int l) {
+  constexpr int LW = 16 * NQ, E = 2 * NQ;
+  __shared__ double pb[2 * LW], beta[LW], lam[LW], off[LW], len[LW];
+  __shared__ double2 de[LW];
+  __shared__ unsigned long long worst;
+  const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63, row = t >> 3, sub = t & 7;
+  const int i16 = lane & 15, g = lane >> 4;
+  // lanes 8 row .. 8 row + 7 hold a row of the matrix: columns sub + 8 q; scaled by a power of two to a largest element of about one
+  if (t == 0) {
+    double top = 0.0;
+    for (int i = 0; i < l; ++i) top = fmax(top, Zt[i * LD + i]);
+    pb[0] = top;
+  }
+  __syncthreads();
+  const double top = pb[0];
+  __syncthreads();
+  if (!(top > 0.0) || !(top < 1e300)) return false;
+  const int scale = -__builtin_amdgcn_frexp_exp(top);
+  double A[E];
+#pragma unroll
+  for (int q = 0; q < E; ++q) {
+    const int c = sub + 8 * q;
+    const bool upper = (row >> 4) <= (c >> 4);
+    A[q] = row < l && c < l ? __builtin_amdgcn_ldexp(upper ? Zt[row * LD + c] : Zt[c * LD + row], scale) : 0.0;
+  }
+  if (t < LW) {
+    de[t] = make_double2(0.0, 0.0);
+    beta[t] = off[t] = pb[t] = 0.0;
+  }
+  // H_k = 1 - beta_k v_k v_k^T takes column k's elements behind k + 1 to zero: its vector, by the wave of row k, an element or
+  // two per lane (by the row's eight lanes, ten elements each and their selects, a column took 2700 cycles, now 2000)
+  auto reflect = [&](int k) {
+    if (row == k) {
+#pragma unroll
+      for (int q = 0; q < E; ++q) pb[LW + sub + 8 * q] = A[q];
     }
-    Um_new[(long long)i * ldu + k] = v;
+    __builtin_amdgcn_wave_barrier();
+    constexpr int NE = (LW + 63) / 64;
+    const double* x = pb + LW;
+    double e[NE], s2 = 0.0;
+#pragma unroll
+    for (int n = 0; n < NE; ++n) {
+      const int c = lane + 64 * n;
+      e[n] = x[min(c, LW - 1)];
+      const double z = c > k + 1 && c < LW ? e[n] : 0.0;
+      s2 = __builtin_fma(z, z, s2);
+    }
+    const double x0 = k + 1 < l ? x[min(k + 1, LW - 1)] : 0.0, dk = x[k];
+    s2 = row_sum16(s2);
+    s2 = (read_lane(s2, 0) + read_lane(s2, 16)) + (read_lane(s2, 32) + read_lane(s2, 48));
+    double alpha = x0, v0 = 0.0, b = 0.0;
+    if (s2 > 0.0) {
+      const double n2 = __builtin_fma(x0, x0, s2), rs = inv_sqrt(n2);
+      double n = n2 * rs;
+      n = __builtin_fma(__builtin_fma(-n, n, n2), 0.5 * rs, n);
+      alpha = x0 >= 0.0 ? -n : n;
+      v0 = x0 - alpha;
+      b = inv(n * (n + fabs(x0)));
+    }
+#pragma unroll
+    for (int n = 0; n < NE; ++n) {
+      const int c = lane + 64 * n;
+      const double head = c == k + 1 ? v0 : 0.0, tail = b > 0.0 ? e[n] : 0.0;
+      if (c < LW) V[k * LV + c] = c > k + 1 ? tail : head;
+    }
+    if (lane == 0) {
+      de[k].x = dk;
+      beta[k] = b;
+      off[k] = alpha;
+      if (k + 1 < l) de[k + 1].y = -alpha * alpha;
+    }
+  };
+  __syncthreads();
+  if (wave == 0) reflect(0);
+  __syncthreads();
+  // A <- H_k A H_k = A - v w^T - w v^T, w = p - (beta / 2) (p.v) v, p = beta A v
+  static_for<NQ>([&](auto Q) {
+    constexpr int Q0 = 2 * Q.value;                  // columns up to 8 Q0 are done (a copy of the code for every 16: each is fetched once)
+    for (int k = 8 * Q0; k < min(8 * Q0 + 16, l - 2); ++k) {
+      const bool alive = 8 * wave + 7 > k && 8 * wave < l;       // (uniform) rows behind k are in this wave
+      double v[E], vr = 0.0, b = 0.0;
+      if (alive) {
+        double part[2] = {0.0, 0.0};
+#pragma unroll
+        for (int q = Q0; q < E; ++q) v[q] = V[k * LV + sub + 8 * q];
+        vr = V[k * LV + row];
+        b = beta[k];
+#pragma unroll
+        for (int q = Q0; q < E; ++q) part[q & 1] = __builtin_fma(A[q], v[q], part[q & 1]);
+        const double pr = sum8(part[0] + part[1]);
+        if (sub == 0) pb[row] = b * pr;
+      }
+      __syncthreads();
+      if (alive) {
+        double w[E], part[2] = {0.0, 0.0};
+#pragma unroll
+        for (int q = Q0; q < E; ++q) w[q] = pb[sub + 8 * q];
+        const double pr = pb[row];
+#pragma unroll
+        for (int q = Q0; q < E; ++q) part[q & 1] = __builtin_fma(v[q], w[q], part[q & 1]);
+        const double K = 0.5 * b * sum8(part[0] + part[1]);
+        const double wr = __builtin_fma(-K, vr, pr);
+#pragma unroll
+        for (int q = Q0; q < E; ++q) A[q] = __builtin_fma(-wr, v[q], __builtin_fma(-vr, __builtin_fma(-K, v[q], w[q]), A[q]));
+        if (wave == (k + 1) >> 3) reflect(k + 1);
+      }
+      __syncthreads();
+    }
+  });
+  if (wave == (l - 1) >> 3) reflect(l - 1);
+  __syncthreads();
+  // eigenvalue k by three points at a time, a lane each: two bits a round
+  if (wave < 4) {
+    const int k = 21 * wave + lane / 3, pt = lane - lane / 3 * 3, lead = lane / 3 * 3;
+    double lo = 1e300, hi = -1e300;
+    for (int i = lane; i < l; i += 64) {
+      const double r = (i > 0 ? fabs(off[i - 1]) : 0.0) + fabs(off[i]);
+      lo = fmin(lo, de[i].x - r);
+      hi = fmax(hi, de[i].x + r);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      lo = fmin(lo, __shfl_xor(lo, o, 64));
+      hi = fmax(hi, __shfl_xor(hi, o, 64));
+    }
+    lo -= 0x1p-48;
+    hi += 0x1p-48;
+    for (int it = 0; it < 29; ++it) {
+      const double step = 0.25 * (hi - lo);
+      const int n = eigenvalues_below(de, l, __builtin_fma((double)(pt + 1), step, lo));
+      const int n0 = __shfl(n, lead, 64), n1 = __shfl(n, lead + 1, 64), n2 = __shfl(n, lead + 2, 64);
+      const int j = n0 > k ? 0 : (n1 > k ? 1 : (n2 > k ? 2 : 3));      // the quarter that eigenvalue k is in
+      hi = j == 3 ? hi : __builtin_fma((double)(j + 1), step, lo);
+      lo = __builtin_fma((double)j, step, lo);
+    }
+    if (pt == 0 && lane < 63 && k < l) lam[k] = 0.5 * (lo + hi);
+  }
+  __syncthreads();
+  if (!(lam[0] > FZ_DIRECT_RANGE * lam[l - 1])) return false;
+  // T - lambda = L+ D+ L+^T = U- D- U-^T, lane t: eigenvalue t; D+ in column t of Zt, and once the row `at` of the least
+  // residual is known, D- behind it; then the vector from that row both ways in their place.  (D- in global memory, and every
+  // loop unrolled: 50 us, most of it for code that is fetched and run once.)
+  if (t < 128 && t < l) {
+    const double x = lam[t];
+    double* z = Zt + t;
+    double r = 0.0;
+    for (int i = 0; i < l; ++i) {
+      const double q = pivot_guard(__builtin_fma(de[i].y, r, de[i].x - x));       // (de[0].y is zero)
+      r = inv(q);
+      z[i * LV] = q;
+    }
+    double least = 1e300, e2 = 0.0;
+    int at = 0;
+    r = 0.0;
+    for (int i = l - 1; i >= 0; --i) {
+      const double d = de[i].x - x, q = pivot_guard(__builtin_fma(e2, r, d));
+      const double gm = fabs(z[i * LV] + q - d);
+      at = gm < least ? i : at;
+      least = fmin(gm, least);
+      r = inv(q);
+      e2 = de[i].y;
+    }
+    e2 = r = 0.0;
+    for (int i = l - 1; i > 0; --i) {
+      const double q = pivot_guard(__builtin_fma(e2, r, de[i].x - x));
+      r = inv(q);
+      e2 = de[i].y;
+      if (i > at) z[i * LV] = q;
+    }
+    double v = 1.0, n2 = 1.0;
+    for (int i = l - 1; i >= 0; --i) {
+      const double f = -off[i] * inv(z[i * LV]) * v;
+      v = i < at ? f : v;
+      n2 = i < at ? __builtin_fma(v, v, n2) : n2;
+      if (i <= at) z[i * LV] = v;
+    }
+    v = 1.0;
+    for (int i = 1; i < l; ++i) {
+      const double f = -off[i - 1] * inv(z[i * LV]) * v;
+      v = i > at ? f : v;
+      n2 = i > at ? __builtin_fma(v, v, n2) : n2;
+      if (i > at) z[i * LV] = v;
+    }
+    len[t] = inv_sqrt(n2);
+  }
+  __syncthreads();
+  // back through the reflections: lanes 8 row .. hold vector `row`
+  if (row < l) {
+#pragma unroll
+    for (int q = 0; q < E; ++q) A[q] = sub + 8 * q < l ? Zt[(sub + 8 * q) * LV + row] * len[row] : 0.0;
+    static_for<NQ>([&](auto Q) {
+      constexpr int Q0 = E - 2 - 2 * Q.value;
+      for (int k = min(8 * Q0 + 15, l - 3); k >= 8 * Q0; --k) {
+        double v[E], part[2] = {0.0, 0.0};
+#pragma unroll
+        for (int q = Q0; q < E; ++q) v[q] = V[k * LV + sub + 8 * q];
+        const double b = beta[k];
+#pragma unroll
+        for (int q = Q0; q < E; ++q) part[q & 1] = __builtin_fma(v[q], A[q], part[q & 1]);
+        const double dot = -b * sum8(part[0] + part[1]);
+#pragma unroll
+        for (int q = Q0; q < E; ++q) A[q] = __builtin_fma(dot, v[q], A[q]);
+      }
+    });
+  }
+  __syncthreads();
+  if (row < LW) {
+#pragma unroll
+    for (int q = 0; q < E; ++q) Zt[row * LV + sub + 8 * q] = row < l ? A[q] : 0.0;
+  }
+  // to orthogonal vectors: V = Zt Zt^T, Zt <- (3 - V) / 2 Zt
+  constexpr int WAVES = FZ_PASS_THREADS / 64, ALL = NQ * NQ, MY = (ALL + WAVES - 1) / WAVES;
+  for (int it = 0; it < 4; ++it) {
+    if (t == 0) worst = 0;
+    __syncthreads();
+    double4_t out[MY];
+    double far_off = 0.0;
+#pragma unroll
+    for (int m = 0; m < MY; ++m) {
+      const int b = wave + WAVES * m, I = b / NQ, K = b - I * NQ;
+      out[m] = double4_t{0.0, 0.0, 0.0, 0.0};
+      if (b < ALL) {
+#pragma unroll
+        for (int e = 0; e < 4 * NQ; ++e)
+          out[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(Zt[(16 * I + i16) * LV + 4 * e + g], Zt[(16 * K + i16) * LV + 4 * e + g], out[m], 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int r = 16 * I + g + 4 * v, c = 16 * K + i16;
+          const double o = r < l && c < l ? out[m][v] - (r == c ? 1.0 : 0.0) : 0.0;
+          far_off = fabs(o) < 1.0 ? fmax(far_off, fabs(o)) : 1.0;       // (a NaN counts as one)
+          V[r * LV + c] = r == c ? 1.0 - 0.5 * o : -0.5 * o;
+        }
+      }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) far_off = fmax(far_off, __shfl_xor(far_off, o, 64));
+    if (lane == 0) atomicMax(&worst, __builtin_bit_cast(unsigned long long, far_off));
+    __syncthreads();
+    const double dev = __builtin_bit_cast(double, worst);
+    if (!(dev < FZ_ORTHO_TRIES)) return false;
+#pragma unroll
+    for (int m = 0; m < MY; ++m) {
+      const int b = wave + WAVES * m, I = b / NQ, K = b - I * NQ;
+      out[m] = double4_t{0.0, 0.0, 0.0, 0.0};
+      if (b < ALL) {
+#pragma unroll
+        for (int e = 0; e < 4 * NQ; ++e)
+          out[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(V[(16 * I + i16) * LV + 4 * e + g], Zt[(4 * e + g) * LV + 16 * K + i16], out[m], 0, 0, 0);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < MY; ++m) {
+      const int b = wave + WAVES * m, I = b / NQ, K = b - I * NQ;
+      if (b < ALL) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) Zt[(16 * I + g + 4 * v) * LV + 16 * K + i16] = out[m][v];
+      }
+    }
+    __syncthreads();
+    if (dev < FZ_ORTHO_ONE) return true;
   }
   return false;
 }
@@ -942,12 +1299,6 @@ struct PassArgs {
 constexpr int FZ_PASS_ROWS = 64, FZ_PASS_WGS = 128, FZ_PASS_GROUP = 12;
 constexpr int FZ_COUNTERS = 16;          // at least FZ_PASS_GROUP + 1, and FZ_MAX_SWEEPS
 
-__device__ inline double load_device(const double* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ inline void store_device(double* p, double v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 // the caller's stores are out and it is counted; true for the workgroup that was last of n
 __device__ inline bool last_of(int* counter, int n) {
   __shared__ int last;
@@ -1107,15 +1458,33 @@ __global__ void __launch_bounds__(FZ_PASS_THREADS) k_pass(PassArgs a) {
   double* parts2 = a.parts + (long long)gridDim.x * SIZE;
   for (int e = t; e < SIZE; e += FZ_PASS_THREADS) store_device(parts2 + (long long)grp * SIZE + e, sum(a.parts + (long long)first * SIZE, members, e));
   if (!last_of(a.counters + a.n_groups, a.n_groups)) return;
-  for (int e = t; e < SIZE; e += FZ_PASS_THREADS) {
-    int I, K;
-    block_at(e >> 8, I, K);
-    S[(16 * I + ((e >> 4) & 3) + 4 * ((e >> 6) & 3)) * LD + 16 * K + (e & 15)] = sum(parts2, a.n_groups, e);
-  }
-  __syncthreads();
+  auto whole = [&]() {
+    for (int e = t; e < SIZE; e += FZ_PASS_THREADS) {
+      int I, K;
+      block_at(e >> 8, I, K);
+      S[(16 * I + ((e >> 4) & 3) + 4 * ((e >> 6) & 3)) * LD + 16 * K + (e & 15)] = sum(parts2, a.n_groups, e);
+    }
+    __syncthreads();
+  };
+  whole();
   if constexpr (!SVD) {
     cholesky_step<NB, LD>(S, a.l, a.factor, a.ld, a.kept, a.state, a.done, a.pass);
   } else {
+    if constexpr (16 * NB <= FZ_DIRECT) {
+      __shared__ double V[LW * LT];
+      if (a.pass == 0) {
+        if (eigenvectors<NB, LD, LT>(S, V, a.l)) {
+          store_rotation<LT>(S, a.l, a.factor, nullptr, a.Um[0], a.ld, 0);
+          if (t == 0) {
+            *a.sel = 0;
+            *a.done = 1 << 30;
+          }
+          return;
+        }
+        __syncthreads();
+        whole();
+      }
+    }
     const bool orthogonal = a.pass == a.passes ||
                             rotation_step<NB, LD>(S, a.l, a.factor, a.Um[(a.pass & 1) ^ 1], a.Um[a.pass & 1], a.ld, a.pass);
     if (orthogonal) sort_and_lift(a, S, LD);

@@ -234,3 +234,39 @@ def test_graded_spectrum():
     Q, _ = np.linalg.qr(E @ Omega)
     s = np.linalg.svd(Q.T @ E, compute_uv=False)
     np.testing.assert_allclose(sig, s, rtol=1e-7)
+
+
+@pytest.mark.parametrize("r,p", [(8, 0), (16, 1), (24, 7), (56, 7), (56, 9), (72, 7), (72, 8), (72, 9)])
+def test_first_rotation_by_eigenvectors_at_its_edges(r, p):
+    # a column less and more than whole blocks of 16, lanes with one and two elements of a column (64), the
+    # widest sketch that goes this way (80) and the narrowest that does not (81)
+    shape = UnitShape("g", 384, (136, 200))
+    u, W = make_unit(shape, "bf16", 128, seed=24)
+    Omega = np.random.default_rng(25).standard_normal((shape.d_in, r + p))
+    check_against_oracle(u, W, r, p, 2, Omega)
+
+
+def test_equal_singular_values():
+    # 24 equal singular values: the vectors of one eigenvalue are not unique and a solve for each of
+    # them gives nearly the same one, so the rotations have to take over; the values and the product A B are unique
+    shape = UnitShape("g", 256, (96, 136))
+    u, W0 = make_unit(shape, "f16", 128, seed=26)
+    What = [O.dequant(O.unpack_int4(m["wq"]), m["scales"], m["zeros"], 128, "f16") for m in u["modules"]]
+    rng = np.random.default_rng(27)
+    rows = sum(shape.d_outs)
+    U, _ = np.linalg.qr(rng.standard_normal((rows, 24)))
+    V, _ = np.linalg.qr(rng.standard_normal((256, 24)))
+    L = 0.5 * U @ V.T
+    W, o = [], 0
+    for Wh in What:
+        W.append((Wh + L[o:o + Wh.shape[0]]).astype(np.float32))
+        o += Wh.shape[0]
+    E = O.stack_errors(W, What)
+    Omega = rng.standard_normal((256, 32))
+    A_bits, B_bits, sig = gpu_factors(u, W, 24, 8, 2, Omega)
+    # (the rotations' last sweep leaves cosines of sqrt(1e-15) = 3.2e-8, which within a cluster is what its columns
+    # are away from orthogonal: its values are that near to the exact ones, relative to each other)
+    np.testing.assert_allclose(sig[:24], np.linalg.svd(E, compute_uv=False)[:24], rtol=3.2e-8)
+    A = O.bits_to_f64(np.concatenate(A_bits, axis=0), "f16")
+    B = O.bits_to_f64(B_bits, "f16")
+    assert np.linalg.norm(E - A @ B, "fro") <= 2e-3 * np.linalg.norm(E, "fro")   # 2^-11 per factor
