@@ -203,6 +203,19 @@ __device__ inline u32x4_t dequant_word<ACT_BF16>(uint32_t w, const GroupConst<AC
   return out;
 }
 
+// Two of the eight: the pair of nibbles in bits 0-3 and 16-19 of w, as dequant_word gives it
+template <int ACT> __device__ inline uint32_t dequant_pair(uint32_t w, const GroupConst<ACT>& g) {
+  if constexpr (ACT == ACT_F16) {
+    const half2_t d = __builtin_bit_cast(half2_t, (w & 0x000F000Fu) | 0x64006400u) + g.nb2;      // exact
+    return __builtin_bit_cast(uint32_t, d * g.s2);
+  } else {
+    bf16x2_t v;
+    v[0] = (__bf16)__builtin_fmaf((float)(w & 0xFu), g.s, g.nzs);
+    v[1] = (__bf16)__builtin_fmaf((float)((w >> 16) & 0xFu), g.s, g.nzs);
+    return __builtin_bit_cast(uint32_t, v);
+  }
+}
+
 // dequant_word for NW words at once, cut into single vector-ALU instructions for a
 // caller that schedules by hand.  Measured on gfx950 with one wave per SIMD: a matrix
 // instruction (16x16x32) takes 8 of its 16 cycles of issue, two more instructions ride

@@ -53,36 +53,54 @@ __global__ void __launch_bounds__(256) k_setup(const double* __restrict__ sigma,
   Z[idx] = c < l ? Omega[(long long)k * l + c] : 0.0;
 }
 
-// Ms[row_off + o][k] = (W[o][k] - What[o][k]) * root[k], What the stored 16-bit weight.
-// A block per tile record, lanes as in the record (row l & 15, channels 32 j + 8 (l >> 4)).
+// Ms[o][k] = (W[o][k] - What[o][k]) * root[k], What the stored 16-bit weight, rows of all modules one after the other.
+// A workgroup per tile record, four rows per wave, two channels per lane: a wave reads 512 contiguous bytes of
+// W and writes a contiguous KiB of Ms per row (with eight channels per lane, 64 bytes each a row apart, and a
+// launch per module: 5120 rows of 3072 in 100 us, now 30; the bytes at a copy's rate: 40).
+struct StackArgs {
+  const float* W[GLOWQ_MAX_MODULES];
+  const uint32_t* prepared[GLOWQ_MAX_MODULES];
+  int d_out[GLOWQ_MAX_MODULES], rec_start[GLOWQ_MAX_MODULES], n_modules;      // first record of a module
+  long long row_start[GLOWQ_MAX_MODULES];
+  int d_in, G;
+};
+
 template <int ACT>
-__global__ void __launch_bounds__(256) k_error_stack(const float* __restrict__ W, const void* prepared,
-                                                     int d_out, int d_in, int G,
-                                                     const double* __restrict__ root,
-                                                     double* __restrict__ Ms, long long row_off) {
-  PreparedView v = prepared_view(prepared, d_out, d_in, G);
-  const int n_rec = v.rows16 * v.ktiles;
-  const int j = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (int rec = (int)blockIdx.x; rec < n_rec; rec += (int)gridDim.x) {
-    const int rb = rec / v.ktiles, kt = rec - rb * v.ktiles;
-    const int row = rb * 16 + (lane & 15), k = kt * 128 + 32 * j + 8 * (lane >> 4);
-    if (row >= d_out) continue;
-    const uint32_t* r = tile_record(v, rb, kt);
-    GroupConst<ACT> g;
-    g.set(r[256 + 16 * ((k & 127) / G) + (row & 15)]);
-    const u32x4_t dq = dequant_word<ACT>(r[lane * 4 + j], g);
-    const float4_t* src = (const float4_t*)(W + (long long)row * d_in + k);
-    const float4_t w0 = src[0], w1 = src[1];
-    const float w[8] = {w0[0], w0[1], w0[2], w0[3], w1[0], w1[1], w1[2], w1[3]};
-    double* dst = Ms + (row_off + row) * (long long)d_in + k;
+__global__ void __launch_bounds__(256) k_error_stack(StackArgs a, const double* __restrict__ root, double* __restrict__ Ms) {
+  int mi = 0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const uint32_t word = dq[i >> 1];
-      const double wh = act16_value<ACT>((i & 1) ? (word >> 16) : (word & 0xffffu));
-      double e = (double)w[i] - wh;
-      if (root) e *= root[k + i];
-      dst[i] = e;
-    }
+  for (int q = 1; q < GLOWQ_MAX_MODULES; ++q)
+    if (q < a.n_modules && (int)blockIdx.x >= a.rec_start[q]) mi = q;
+  const int rec = (int)blockIdx.x - a.rec_start[mi], ktiles = a.d_in >> 7, d_out = a.d_out[mi];
+  const int rb = rec / ktiles, kt = rec - rb * ktiles;
+  const int lane = threadIdx.x & 63, row0 = 4 * (threadIdx.x >> 6);      // row within the record
+  const uint32_t* r = a.prepared[mi] + (long long)rec * prepared_rec_words(a.G);
+  const int k = kt * 128 + 2 * lane;
+  const float* W = a.W[mi] + (long long)(rb * 16 + row0) * a.d_in + k;
+  double* dst = Ms + (a.row_start[mi] + rb * 16 + row0) * a.d_in + k;
+  const int live = min(4, d_out - rb * 16 - row0);
+  // lane's pair of channels: nibbles i and i + 4 of word j of record lane row + 16 ((k >> 3) & 3)
+  const int word = 64 * ((lane >> 2) & 3) + (lane >> 4), i = lane & 3, sz = 256 + 16 * (2 * lane / a.G);
+  double2 rt = make_double2(1.0, 1.0);
+  if (root) rt = *(const double2*)(root + k);
+  float2 w[4];
+  uint32_t c[4], g[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (q < live) w[q] = *(const float2*)(W + (long long)q * a.d_in);
+    c[q] = r[4 * (row0 + q) + word];
+    g[q] = r[sz + row0 + q];
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (q >= live) break;
+    GroupConst<ACT> gc;
+    gc.set(g[q]);
+    const uint32_t pair = dequant_pair<ACT>(c[q] >> (4 * i), gc);
+    double2 e = make_double2((double)w[q].x - act16_value<ACT>(pair & 0xffffu), (double)w[q].y - act16_value<ACT>(pair >> 16));
+    e.x *= rt.x;
+    e.y *= rt.y;
+    *(double2*)(dst + (long long)q * a.d_in) = e;
   }
 }
 
@@ -1741,15 +1759,24 @@ hipError_t launch_factorize(const glowq_unit& u, const float* const* W_modules, 
   k_setup<<<dim3((unsigned)((d * f.l16 + 255) / 256)), dim3(256), 0, st>>>(sigma_x, d, root, inv_root, Omega, l, f.l16, Z,
                                                                           counters, FZ_COUNTERS);
   // the stack, scaled by Sigma_x^(1/2) (Alg. 1, core construction)
+  StackArgs sa = {};
+  sa.n_modules = u.n_modules;
+  sa.d_in = d;
+  sa.G = u.group_size;
   long long row_off = 0;
+  int recs = 0;
   for (int i = 0; i < u.n_modules; ++i) {
     const glowq_module& mod = u.modules[i];
-    const long long recs = (long long)((mod.d_out + 15) / 16) * (d / 128);
-    dim3 grid((unsigned)(recs < 4096 ? recs : 4096)), block(256);
-    if (f16) k_error_stack<ACT_F16><<<grid, block, 0, st>>>(W_modules[i], mod.w_prepared, mod.d_out, d, u.group_size, root, Ms, row_off);
-    else k_error_stack<ACT_BF16><<<grid, block, 0, st>>>(W_modules[i], mod.w_prepared, mod.d_out, d, u.group_size, root, Ms, row_off);
+    sa.W[i] = W_modules[i];
+    sa.prepared[i] = (const uint32_t*)mod.w_prepared;
+    sa.d_out[i] = mod.d_out;
+    sa.rec_start[i] = recs;
+    sa.row_start[i] = row_off;
+    recs += (mod.d_out + 15) / 16 * (d / 128);
     row_off += mod.d_out;
   }
+  if (f16) k_error_stack<ACT_F16><<<dim3((unsigned)recs), dim3(256), 0, st>>>(sa, root, Ms);
+  else k_error_stack<ACT_BF16><<<dim3((unsigned)recs), dim3(256), 0, st>>>(sa, root, Ms);
   // sketch and power steps (Alg. 1, range finding)
   const bool small = l <= FZ_SMALL;
   int n_slices = 0;                                // (small: the first pass of the orthonormalisation adds the last ones)

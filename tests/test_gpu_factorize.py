@@ -246,9 +246,10 @@ def test_first_rotation_by_eigenvectors_at_its_edges(r, p):
     check_against_oracle(u, W, r, p, 2, Omega)
 
 
-def test_equal_singular_values():
-    # 24 equal singular values: the vectors of one eigenvalue are not unique and a solve for each of
-    # them gives nearly the same one, so the rotations have to take over; the values and the product A B are unique
+@pytest.mark.parametrize("p", [0, 8])
+def test_equal_singular_values(p):
+    # 24 singular values equal to 1e-8: the vectors of one eigenvalue come out far from orthogonal (p = 0), or there are
+    # eight directions more than the range has (p = 8: the rotations take over); the values and the product A B are unique
     shape = UnitShape("g", 256, (96, 136))
     u, W0 = make_unit(shape, "f16", 128, seed=26)
     What = [O.dequant(O.unpack_int4(m["wq"]), m["scales"], m["zeros"], 128, "f16") for m in u["modules"]]
@@ -262,8 +263,8 @@ def test_equal_singular_values():
         W.append((Wh + L[o:o + Wh.shape[0]]).astype(np.float32))
         o += Wh.shape[0]
     E = O.stack_errors(W, What)
-    Omega = rng.standard_normal((256, 32))
-    A_bits, B_bits, sig = gpu_factors(u, W, 24, 8, 2, Omega)
+    Omega = rng.standard_normal((256, 24 + p))
+    A_bits, B_bits, sig = gpu_factors(u, W, 24, p, 2, Omega)
     # (the rotations' last sweep leaves cosines of sqrt(1e-15) = 3.2e-8, which within a cluster is what its columns
     # are away from orthogonal: its values are that near to the exact ones, relative to each other)
     np.testing.assert_allclose(sig[:24], np.linalg.svd(E, compute_uv=False)[:24], rtol=3.2e-8)
