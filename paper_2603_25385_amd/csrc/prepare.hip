@@ -142,131 +142,188 @@ __global__ void k_debug_dequant(const void* prepared, int d_out, int d_in, int G
   *(u32x4_t*)(w_out + (long long)row * d_in + k) = d;
 }
 
-// adds the block's two partial sums to out[0], out[1]
-__device__ inline void block_add2(double a, double b, double* out, double* lds) {
-  const int tid = threadIdx.x;
-  lds[tid] = a;
-  lds[blockDim.x + tid] = b;
-  __syncthreads();
-  for (int h = blockDim.x >> 1; h > 0; h >>= 1) {
-    if (tid < h) {
-      lds[tid] += lds[tid + h];
-      lds[blockDim.x + tid] += lds[blockDim.x + tid + h];
-    }
-    __syncthreads();
-  }
-  if (tid == 0) {
-    atomicAdd(&out[0], lds[0]);
-    atomicAdd(&out[1], lds[blockDim.x]);
-  }
-}
+// The sums behind the scores, one launch: the leading workgroups take tile records of all modules (Eq. 11: sum of
+// (W - What)^2 and of W^2, What the stored weight widened from the activation type), the next ones 128 rows of an A_i each
+// (column energies), the last ones a row of B each.  The workgroup that finds all others counted makes the scores of
+// the sums.  One wave per (tile record, word index j): lane l holds row l & 15, channels 32 j + 8 (l >> 4) .. + 8,
+// so a wave reads 16 rows x 128 contiguous bytes of the fp32 weights (the bytes that matter: 4 of 4.6 per
+// weight); four records are asked for together, since a record by itself leaves a workgroup waiting for memory most of
+// the time.  5120 rows of 3072, r = 64: 101 us as eight launches behind one another (a record at a time), now 26 and the fill.
+// scratch: pairs {error energy, weight energy} of IM_SLOTS groups of workgroups (so that few atomic adds meet at a sum),
+// column energies of A, row energies of B, count of workgroups.
+constexpr int IM_SLOTS = 32, IM_COL = 2 * IM_SLOTS, IM_ROW = IM_COL + GLOWQ_MAX_RANK, IM_COUNT = IM_ROW + GLOWQ_MAX_RANK;
+static_assert((IM_COUNT + 1) * 8 <= GLOWQ_IMPORTANCE_SCRATCH_BYTES, "the sums fit the scratch");
+constexpr int IM_RECS = 4, IM_ROWS = 128;         // records per turn; rows of A per workgroup
 
-// Eq. 11, numerator and denominator of one module: sums[0] += sum (W - What)^2,
-// sums[1] += sum W^2, What the stored weight widened from the activation type.  One wave
-// per (tile record, word index j): lane l holds row l & 15, channels 32 j + 8 (l >> 4) ..+8,
-// so a wave reads 16 rows x 128 contiguous bytes of the fp32 weights (the bytes that
-// matter: 4 of 4.6 per weight) and a record's four waves read its 1 KiB of words between
-// them.
-template <int ACT>
-__global__ void __launch_bounds__(256) k_error_energy(const float* __restrict__ W, const void* prepared,
-                                                      int d_out, int d_in, int G, double* sums) {
-  __shared__ double lds[512];
-  PreparedView v = prepared_view(prepared, d_out, d_in, G);
-  const int n_rec = v.rows16 * v.ktiles;          // (below 2^31: the layout's own limit)
-  const int j = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  double e = 0.0, ww = 0.0;
-  // (a block per record, grid-stride: few blocks, so that few atomic adds meet at the two
-  // sums, and the record's place is scalar arithmetic)
-  for (int rec = (int)blockIdx.x; rec < n_rec; rec += (int)gridDim.x) {
-    const int rb = rec / v.ktiles, kt = rec - rb * v.ktiles;
-    const int row = rb * 16 + (lane & 15), k = kt * 128 + 32 * j + 8 * (lane >> 4);
-    if (row >= d_out) continue;
-    const uint32_t* r = tile_record(v, rb, kt);
-    GroupConst<ACT> g;
-    g.set(r[256 + 16 * ((k & 127) / G) + (row & 15)]);
-    const u32x4_t d = dequant_word<ACT>(r[lane * 4 + j], g);
-    const float4_t* src = (const float4_t*)(W + (long long)row * d_in + k);
-    const float4_t w0 = __builtin_nontemporal_load(src), w1 = __builtin_nontemporal_load(src + 1);
-    const float w[8] = {w0[0], w0[1], w0[2], w0[3], w1[0], w1[1], w1[2], w1[3]};
+struct ImportanceArgs {
+  const float* W[GLOWQ_MAX_MODULES];
+  const uint32_t* prepared[GLOWQ_MAX_MODULES];
+  const uint16_t* A[GLOWQ_MAX_MODULES];
+  int d_out[GLOWQ_MAX_MODULES], rec_start[GLOWQ_MAX_MODULES], col_start[GLOWQ_MAX_MODULES], n_modules;
+  const uint16_t* B;
+  int d_in, G, r, n_recs, n_energy, n_cols;       // workgroups of the first two kinds
+  double* scratch;
+  double* scores;
+};
+
+// sum over the workgroup (256 threads); thread 0 has it
+__device__ inline double block_sum256(double v, double* lds4) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const uint32_t word = d[i >> 1];
-      const double wh = act16_value<ACT>((i & 1) ? (word >> 16) : (word & 0xffffu));
-      const double x = (double)w[i];
-      e += (x - wh) * (x - wh);
-      ww += x * x;
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) lds4[threadIdx.x >> 6] = v;
+  __syncthreads();
+  return (lds4[0] + lds4[1]) + (lds4[2] + lds4[3]);
+}
+
+template <int ACT>
+__global__ void __launch_bounds__(256) k_importance(ImportanceArgs a) {
+  __shared__ double part[256 * 9], four[4];
+  __shared__ int last;
+  const int t = threadIdx.x, wg = blockIdx.x;
+  if (wg < a.n_energy) {
+    const int j = t >> 6, lane = t & 63, ktiles = a.d_in >> 7, rec_words = prepared_rec_words(a.G);
+    double e = 0.0, ww = 0.0;
+    for (int rec0 = wg * IM_RECS; rec0 < a.n_recs; rec0 += a.n_energy * IM_RECS) {
+      float4_t w0[IM_RECS], w1[IM_RECS];
+      uint32_t word[IM_RECS], sz[IM_RECS];
+      bool live[IM_RECS];
+#pragma unroll
+      for (int q = 0; q < IM_RECS; ++q) {
+        const int all = min(rec0 + q, a.n_recs - 1);
+        int mi = 0;
+#pragma unroll
+        for (int m = 1; m < GLOWQ_MAX_MODULES; ++m)
+          if (m < a.n_modules && all >= a.rec_start[m]) mi = m;
+        const int rec = all - a.rec_start[mi], rb = rec / ktiles, kt = rec - rb * ktiles;
+        const int row = rb * 16 + (lane & 15), k = kt * 128 + 32 * j + 8 * (lane >> 4);
+        live[q] = rec0 + q < a.n_recs && row < a.d_out[mi];
+        const float4_t* src = (const float4_t*)(a.W[mi] + (long long)min(row, a.d_out[mi] - 1) * a.d_in + k);
+        w0[q] = __builtin_nontemporal_load(src);
+        w1[q] = __builtin_nontemporal_load(src + 1);
+        const uint32_t* r = a.prepared[mi] + (long long)rec * rec_words;
+        word[q] = r[lane * 4 + j];
+        sz[q] = r[256 + 16 * ((k & 127) / a.G) + (row & 15)];
+      }
+#pragma unroll
+      for (int q = 0; q < IM_RECS; ++q) {
+        GroupConst<ACT> g;
+        g.set(sz[q]);
+        const u32x4_t d = dequant_word<ACT>(word[q], g);
+        const float w[8] = {w0[q][0], w0[q][1], w0[q][2], w0[q][3], w1[q][0], w1[q][1], w1[q][2], w1[q][3]};
+        if (live[q]) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const uint32_t pair = d[i >> 1];
+            const double x = (double)w[i], err = x - act16_value<ACT>((i & 1) ? (pair >> 16) : (pair & 0xffffu));
+            e += err * err;
+            ww += x * x;
+          }
+        }
+      }
     }
+    e = block_sum256(e, four);
+    ww = block_sum256(ww, four);
+    if (t == 0) {
+      atomicAdd(&a.scratch[2 * (wg % IM_SLOTS)], e);
+      atomicAdd(&a.scratch[2 * (wg % IM_SLOTS) + 1], ww);
+    }
+  } else if (wg < a.n_energy + a.n_cols) {
+    const int at = wg - a.n_energy;
+    int mi = 0;
+#pragma unroll
+    for (int m = 1; m < GLOWQ_MAX_MODULES; ++m)
+      if (m < a.n_modules && at >= a.col_start[m]) mi = m;
+    // eight ranks per thread, as many rows at once as that leaves
+    const int pieces = a.r >> 3, rows = 256 / pieces, piece = t % pieces, sub = t / pieces;
+    const int o0 = (at - a.col_start[mi]) * IM_ROWS, o1 = min(a.d_out[mi], o0 + IM_ROWS);
+    double s[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (sub < rows) {
+#pragma unroll 4
+      for (int o = o0 + sub; o < o1; o += rows) {
+        const u32x4_t v = *(const u32x4_t*)(a.A[mi] + (long long)o * a.r + 8 * piece);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const uint32_t pair = v[i >> 1];
+          const double x = act16_value<ACT>((i & 1) ? (pair >> 16) : (pair & 0xffffu));
+          s[i] += x * x;
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) part[t * 9 + i] = s[i];
+    __syncthreads();
+    if (t < a.r) {
+      double sum = 0.0;
+      for (int q = 0; q < rows; ++q) sum += part[(q * pieces + (t >> 3)) * 9 + (t & 7)];
+      atomicAdd(&a.scratch[IM_COL + t], sum);
+    }
+  } else {
+    const int j = wg - a.n_energy - a.n_cols;
+    double s = 0.0;
+    for (int k = 8 * t; k < a.d_in; k += 2048) {
+      const u32x4_t v = *(const u32x4_t*)(a.B + (long long)j * a.d_in + k);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const uint32_t pair = v[i >> 1];
+        const double x = act16_value<ACT>((i & 1) ? (pair >> 16) : (pair & 0xffffu));
+        s += x * x;
+      }
+    }
+    s = block_sum256(s, four);
+    if (t == 0) atomicAdd(&a.scratch[IM_ROW + j], s);
   }
-  block_add2(e, ww, sums, lds);
-}
-
-// col_sq[j] += sum_o A[o][j]^2 over the rows of one module (A: [d_out][r])
-template <int ACT>
-__global__ void __launch_bounds__(256) k_factor_col_energy(const uint16_t* __restrict__ A, int d_out, int r,
-                                                           double* col_sq) {
-  const int j = threadIdx.x & 127, sub = threadIdx.x >> 7;     // two rows per pass
-  if (j >= r) return;
-  double s = 0.0;
-  for (int o = blockIdx.x * 64 + sub; o < min(d_out, (int)(blockIdx.x + 1) * 64); o += 2) {
-    const double a = act16_value<ACT>(A[(long long)o * r + j]);
-    s += a * a;
-  }
-  atomicAdd(&col_sq[j], s);
-}
-
-// row_sq[j] = sum_k B[j][k]^2 (B: [r][d_in]); one block per rank
-template <int ACT>
-__global__ void __launch_bounds__(256) k_factor_row_energy(const uint16_t* __restrict__ B, int d_in,
-                                                           double* row_sq) {
-  __shared__ double lds[512];
-  const int j = blockIdx.x;
-  double s = 0.0;
-  for (int k = threadIdx.x; k < d_in; k += blockDim.x) {
-    const double b = act16_value<ACT>(B[(long long)j * d_in + k]);
-    s += b * b;
-  }
-  block_add2(s, 0.0, row_sq + 2 * j, lds);      // (pairs: the second sum is unused)
-}
-
-// scratch: [0] error energy, [1] weight energy, [2 .. 2 + r) column energies of A,
-// [2 + 128 .. ) pairs {row energy of B, unused}.  scores[0] = g_ner, scores[1] = g_ec: the
-// balanced factors have orthogonal columns / rows with ||a_j||^2 = ||b_j||^2 = sigma_j
-// (Eqs. A.1.9a-b), so sum_j ||a_j||^2 ||b_j||^2 is the captured energy sum_j sigma_j^2.
-__global__ void k_importance_finish(const double* scratch, int r, double* scores) {
-  __shared__ double prod[GLOWQ_MAX_RANK];
-  const int t = threadIdx.x;                    // one block of GLOWQ_MAX_RANK threads
-  prod[t] = t < r ? scratch[2 + t] * scratch[2 + GLOWQ_MAX_RANK + 2 * t] : 0.0;
+  // the sums are out, then the workgroup is counted
+  vm_wait<0>();
+  __syncthreads();
+  if (t == 0) last = __hip_atomic_fetch_add((int*)&a.scratch[IM_COUNT], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+  __syncthreads();
+  if (!last) return;
+  // scores[0] = g_ner, scores[1] = g_ec: the balanced factors have orthogonal columns / rows with
+  // ||a_j||^2 = ||b_j||^2 = sigma_j (Eqs. A.1.9a-b), so sum_j ||a_j||^2 ||b_j||^2 is the captured energy sum_j sigma_j^2
+  auto sum_at = [&](int i) { return __hip_atomic_load(a.scratch + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  part[t] = t < 2 * IM_SLOTS ? sum_at(t) : 0.0;
+  part[256 + t] = t < a.r ? sum_at(IM_COL + t) * sum_at(IM_ROW + t) : 0.0;
   __syncthreads();
   if (t != 0) return;
-  const double e = scratch[0], w = scratch[1];
-  double cap = 0.0;
-  for (int j = 0; j < r; ++j) cap += prod[j];   // in rank order: the same sum every run
-  scores[0] = w > 0.0 ? e / w : 0.0;
-  scores[1] = e > 0.0 ? cap / e : 0.0;
+  double e = 0.0, w = 0.0, cap = 0.0;
+  for (int i = 0; i < IM_SLOTS; ++i) {
+    e += part[2 * i];
+    w += part[2 * i + 1];
+  }
+  for (int j = 0; j < a.r; ++j) cap += part[256 + j];
+  a.scores[0] = w > 0.0 ? e / w : 0.0;
+  a.scores[1] = e > 0.0 ? cap / e : 0.0;
 }
 
 hipError_t launch_importance(const glowq_unit& u, const float* const* W_modules, double* scratch,
                              double* scores, hipStream_t st) {
   hipError_t err = launch_fill_zero(scratch, GLOWQ_IMPORTANCE_SCRATCH_BYTES, st);
   if (err != hipSuccess) return err;
-  const bool f16 = u.act_dtype == GLOWQ_F16;
+  ImportanceArgs a = {};
+  a.n_modules = u.n_modules;
   for (int i = 0; i < u.n_modules; ++i) {
     const glowq_module& m = u.modules[i];
-    const long long blocks = (long long)((m.d_out + 15) / 16) * (u.d_in / 128);   // one per tile record
-    dim3 grid((unsigned)(blocks < 512 ? blocks : 512)), block(256);   // (few blocks: see k_error_energy)
-    if (f16) k_error_energy<ACT_F16><<<grid, block, 0, st>>>(W_modules[i], m.w_prepared, m.d_out, u.d_in, u.group_size, scratch);
-    else k_error_energy<ACT_BF16><<<grid, block, 0, st>>>(W_modules[i], m.w_prepared, m.d_out, u.d_in, u.group_size, scratch);
-    if (u.r > 0) {
-      dim3 cgrid((unsigned)((m.d_out + 63) / 64));
-      if (f16) k_factor_col_energy<ACT_F16><<<cgrid, block, 0, st>>>((const uint16_t*)m.A, m.d_out, u.r, scratch + 2);
-      else k_factor_col_energy<ACT_BF16><<<cgrid, block, 0, st>>>((const uint16_t*)m.A, m.d_out, u.r, scratch + 2);
-    }
+    a.W[i] = W_modules[i];
+    a.prepared[i] = (const uint32_t*)m.w_prepared;
+    a.A[i] = (const uint16_t*)m.A;
+    a.d_out[i] = m.d_out;
+    a.rec_start[i] = a.n_recs;
+    a.col_start[i] = a.n_cols;
+    a.n_recs += (m.d_out + 15) / 16 * (u.d_in / 128);
+    if (u.r > 0) a.n_cols += (m.d_out + IM_ROWS - 1) / IM_ROWS;
   }
-  if (u.r > 0) {
-    if (f16) k_factor_row_energy<ACT_F16><<<dim3((unsigned)u.r), dim3(256), 0, st>>>((const uint16_t*)u.B, u.d_in, scratch + 2 + GLOWQ_MAX_RANK);
-    else k_factor_row_energy<ACT_BF16><<<dim3((unsigned)u.r), dim3(256), 0, st>>>((const uint16_t*)u.B, u.d_in, scratch + 2 + GLOWQ_MAX_RANK);
-  }
-  k_importance_finish<<<1, GLOWQ_MAX_RANK, 0, st>>>(scratch, u.r, scores);
+  a.B = (const uint16_t*)u.B;
+  a.d_in = u.d_in;
+  a.G = u.group_size;
+  a.r = u.r;
+  const int turns = (a.n_recs + IM_RECS - 1) / IM_RECS;
+  a.n_energy = turns < 1024 ? turns : 1024;
+  a.scratch = scratch;
+  a.scores = scores;
+  const dim3 grid((unsigned)(a.n_energy + a.n_cols + u.r)), block(256);
+  if (u.act_dtype == GLOWQ_F16) k_importance<ACT_F16><<<grid, block, 0, st>>>(a);
+  else k_importance<ACT_BF16><<<grid, block, 0, st>>>(a);
   return hipGetLastError();
 }
 
