@@ -365,7 +365,8 @@ typedef struct {
   int32_t launch;      /* index of the launch; units of one launch share it                   */
   int32_t kernel;      /* GLOWQ_ROUTE_...                                                     */
   int32_t tile;        /* see above (0 where there is no choice)                              */
-  int32_t k_slices;    /* slices of K whose partial results a second kernel adds              */
+  int32_t k_slices;    /* slices of K whose partial results are added afterwards: by a tile's last
+                          workgroup (batched kernel) or by a second kernel (tiled)            */
   int32_t wait_polls;  /* looks that an in-launch wait for the projection takes before it
                           gives up; 0: nothing waits inside a launch                          */
 } glowq_route;

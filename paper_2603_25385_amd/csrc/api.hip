@@ -79,7 +79,7 @@ UnitWorkspace plan_unit_workspace(const glowq_unit& u, char* base) {
   w.off_r16 = align_up(w.off_rpart + rpart, 256);
   size_t r16 = (u.r > 0) ? (size_t)u.T * u.r * (u.T <= BATCH_MAX_T ? 4 : 2) : 0;
   w.off_splitk = align_up(w.off_r16 + r16, 256);
-  w.splitk_bytes = is_decode(u.T) ? 0 : prefill_splitk_bytes(u);
+  w.splitk_bytes = is_decode(u.T) ? batch_slab_bytes(u) : prefill_splitk_bytes(u);
   w.bytes = align_up(w.off_splitk + w.splitk_bytes, 256);
   return w;
 }
@@ -166,7 +166,7 @@ static LaunchChoice choose_launch(const glowq_unit* units, int n_units, bool sla
       ++c.n;
     }
     c.kernel = few ? GLOWQ_ROUTE_FEW : GLOWQ_ROUTE_BATCHED;
-    if (!few) c.tile = choose_batch_tile(batch, c.n, &cost);
+    if (!few) c.tile = choose_batch_tile(batch, c.n, &cost, slabs ? c.slices : nullptr);
     return c;
   }
   const int most = std::min(std::min(MAX_LAUNCH_UNITS, n_units), std::min(prefill_max_units(), batch_max_units()));
@@ -184,7 +184,7 @@ static LaunchChoice choose_launch(const glowq_unit* units, int n_units, bool sla
   // Few or small tiles leave the tiled kernel's workgroups alone on their compute units with the
   // whole contraction each; there the smaller tiles of the batched kernel are faster.
   float small_cost = 0.f;
-  const int tile = small ? choose_batch_tile(batch, c.n, &small_cost) : 0;
+  const int tile = small ? choose_batch_tile(batch, c.n, &small_cost, nullptr) : 0;
   if (small && small_cost < 0.95f * cost) {
     c.kernel = GLOWQ_ROUTE_BATCHED;
     c.tile = tile;
@@ -213,7 +213,7 @@ static glowq_status forward_all(const glowq_unit* units, int n_units, const uint
       if (c.kernel == GLOWQ_ROUTE_BATCHED && !is_decode(units[i].T)) plan_batch_projection(*batch[k], ws[k]);
     }
     const hipError_t e = c.kernel == GLOWQ_ROUTE_FEW       ? launch_decode_multi(batch, ws, corr, c.n, st)
-                         : c.kernel == GLOWQ_ROUTE_BATCHED ? launch_decode_batch(batch, ws, corr, c.n, c.tile, st)
+                         : c.kernel == GLOWQ_ROUTE_BATCHED ? launch_decode_batch(batch, ws, corr, c.n, c.tile, c.slices, st)
                                                            : launch_prefill_multi(batch, ws, corr, c.n, c.tile, c.slices, st);
     if (e != hipSuccess) return hip_status(e);
   }

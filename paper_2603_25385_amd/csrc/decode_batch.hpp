@@ -42,6 +42,7 @@
 namespace glowq {
 
 constexpr int BATCH_MAX_UNITS = 16;
+constexpr int BATCH_MAX_SLICES = 4;      // of K, across workgroups
 constexpr int BATCH_QUICK_POLLS = 64;    // looks at R with hardly a pause in between
 constexpr int BATCH_WB = 1024 + 256;      // bytes per wave and K tile: one record's words, its (s, z) words
 
@@ -54,7 +55,10 @@ struct BatchUnit {
   Control* ctl;
   int T, K, r, n_modules;
   int n_blocks;                // 16-row blocks of the unit
-  int n_groups, n_ttiles;      // its workgroups: groups of row blocks x tiles of 16 MB tokens
+  int n_groups, n_ttiles;      // its tiles: groups of row blocks x tiles of 16 MB tokens
+  int ks;                      // K slices: as many workgroups per tile (see plan_batch_slices)
+  uint32_t* count;             // ks > 1: per tile, slices that are done; their partial results
+  u32x4_t* slab;               // [slice][tile][row wave][row block][token block][lane]
   int restore, out_f32;        // restore 2: the consumers add the projection's slices (see plan_batch_projection)
   int ksplit, kslice;          // K slices of the projection
   int prod_start, n_prod;      // this unit's projection workgroups
@@ -239,7 +243,9 @@ template <int MB, int RB, int RW, int NW> struct BatchShape {
   static_assert(MB * 4096 + (KS - 1) * RW * RB * MB * 1024 <= LDS, "R and the fold fit the ring");
 };
 
-template <int ACT, int MB, int RB, int RW, int NW, bool EXACT, bool G128, int NB>
+// CUT: some unit's contraction is cut across workgroups (a launch without one runs the code without any of it: with it
+// 2 x 14336 rows x 4096 at 8 tokens, bfloat16, took 17.9 instead of 17.7 us).
+template <int ACT, int MB, int RB, int RW, int NW, bool EXACT, bool G128, bool CUT, int NB>
 __global__ void __launch_bounds__(NW * 64, (BatchShape<MB, RB, RW, NW>::WAVES_EU)) k_decode_batch(BatchArgs<NB> b) {
   using S = BatchShape<MB, RB, RW, NW>;
   __shared__ __attribute__((aligned(1024))) char ring[S::LDS];
@@ -257,11 +263,20 @@ __global__ void __launch_bounds__(NW * 64, (BatchShape<MB, RB, RW, NW>::WAVES_EU
   for (int i = 1; i < NB; ++i)
     if (i < b.n && (int)blockIdx.x >= b.u[i].wg_start) ui = i;
   const BatchUnit& u = b.u[ui];
-  int grp = (int)blockIdx.x - u.wg_start, tok0 = 0;
+  int grp = (int)blockIdx.x - u.wg_start, tok0 = 0, sl = 0;
+  const int ks = CUT ? u.ks : 1, n_tiles = u.n_groups * u.n_ttiles;
+  int sk0 = 0, span = u.K >> 7;                   // the slice's K tiles (the divisions stay off whole contractions' way)
+  if (CUT && ks > 1) {
+    sl = grp / n_tiles;
+    grp -= sl * n_tiles;
+    sk0 = (u.K >> 7) * sl / ks;
+    span = (u.K >> 7) * (sl + 1) / ks - sk0;
+  }
+  const int tile = grp;
   if (u.n_ttiles > 1) {
     // workgroups go to the eight XCDs round robin: residue class c takes the c-th eighth of the
     // list (token tile fastest), so that the token tiles of a row group share an L2
-    const int n_wg = u.n_groups * u.n_ttiles, c = grp & 7, t = c * (n_wg >> 3) + min(c, n_wg & 7) + (grp >> 3);
+    const int c = grp & 7, t = c * (n_tiles >> 3) + min(c, n_tiles & 7) + (grp >> 3);
     grp = t / u.n_ttiles;
     tok0 = (t - grp * u.n_ttiles) * 16 * MB;
   }
@@ -271,8 +286,8 @@ __global__ void __launch_bounds__(NW * 64, (BatchShape<MB, RB, RW, NW>::WAVES_EU
   const int rw = wave % RW, kg = wave / RW;
   constexpr int REC = G128 ? 1088 : 1152;        // bytes per tile record
   const int ktiles = u.K >> 7, T = u.T, K = u.K;
-  const int kt0 = ktiles * kg / S::KS, nkt = ktiles * (kg + 1) / S::KS - kt0;
-  const int n_st = (ktiles + S::KS - 1) / S::KS;  // every group runs this many stages
+  const int kt0 = sk0 + span * kg / S::KS, nkt = sk0 + span * (kg + 1) / S::KS - kt0;
+  const int n_st = (span + S::KS - 1) / S::KS;    // every group runs this many stages
 
   // this wave's 16-row blocks; past the unit's last one: that one again, not stored
   const int blk0 = (grp * RW + rw) * RB;
@@ -344,7 +359,7 @@ __global__ void __launch_bounds__(NW * 64, (BatchShape<MB, RB, RW, NW>::WAVES_EU
   // nothing may be on its way into LDS any more, and everybody is done reading it
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
-  const int restore = u.restore;
+  const int restore = sl == 0 ? u.restore : 0;   // (the first slice carries the correction)
   if (restore) {                                 // uniform; r > 0
     const int r = u.r, n_tok = min(T - tok0, 16 * MB);
     u32x4_t af[RB][4];
@@ -391,17 +406,68 @@ __global__ void __launch_bounds__(NW * 64, (BatchShape<MB, RB, RW, NW>::WAVES_EU
         for (int mb = 0; mb < MB; ++mb) at(kg - 1, b_, mb) = acc[b_][mb];
     }
     __syncthreads();
-    if (kg > 0) return;
+    if (kg == 0) {
 #pragma unroll
-    for (int g = 1; g < S::KS; ++g)
+      for (int g = 1; g < S::KS; ++g)
+#pragma unroll
+        for (int b_ = 0; b_ < RB; ++b_)
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb) {
+            const float4_t o = at(g - 1, b_, mb);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[b_][mb][v] += o[v];
+          }
+    } else if (ks == 1) {
+      return;
+    }
+  }
+  if (CUT && ks > 1) {
+    // The slice's sums go past the L2s to the unit's slab and the workgroup is counted (the word carries the
+    // launch's tag, as a projection tile's does); whoever finds all others counted adds the slices in their order.
+    constexpr int PIECES = RW * RB * MB * 64;
+    u32x4_t* mine = u.slab + (size_t)tile * PIECES + rw * (RB * MB * 64) + lane;
+    const size_t step = (size_t)n_tiles * PIECES;
+    if (kg == 0) {
 #pragma unroll
       for (int b_ = 0; b_ < RB; ++b_)
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-          const float4_t o = at(g - 1, b_, mb);
+        for (int mb = 0; mb < MB; ++mb) store16_device(mine + sl * step + (b_ * MB + mb) * 64, __builtin_bit_cast(u32x4_t, acc[b_][mb]));
+    }
+    uint32_t* word = u.count + tile;
+    uint32_t seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // (on its way with the stores)
+    vm_wait<0>();
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      const uint32_t key = (uint32_t)(launch_tag() >> 1) << 4;
+      uint32_t done;
+      do done = (seen & ~15u) == key ? seen & 15u : 0u;      // (at most ks rounds: a failure is another slice's success)
+      while (!__hip_atomic_compare_exchange_strong(word, &seen, key | (done + 1u), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT));
+      flag = done;
+    }
+    __syncthreads();
+    if (flag + 1u != (uint32_t)ks || kg > 0) return;
+    // (all slices' values of a block in flight together)
 #pragma unroll
-          for (int v = 0; v < 4; ++v) acc[b_][mb][v] += o[v];
+    for (int b_ = 0; b_ < RB; ++b_)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        unsigned long long v[BATCH_MAX_SLICES][2];
+#pragma unroll
+        for (int p = 0; p < BATCH_MAX_SLICES; ++p) {
+          const unsigned long long* q = (const unsigned long long*)(mine + min(p, ks - 1) * step + (b_ * MB + mb) * 64);
+          v[p][0] = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          v[p][1] = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
+        acc[b_][mb] = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int p = 0; p < BATCH_MAX_SLICES; ++p)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float x = __builtin_bit_cast(float, (uint32_t)(v[p][e >> 1] >> (32 * (e & 1))));
+            acc[b_][mb][e] += p < ks ? x : 0.f;
+          }
+      }
   }
 #pragma unroll
   for (int b_ = 0; b_ < RB; ++b_) {
@@ -496,50 +562,112 @@ constexpr int BATCH_RESIDENT[] = {batch_tile_resident<0>(), batch_tile_resident<
                                   batch_tile_resident<6>(), batch_tile_resident<7>(), batch_tile_resident<8>()};
 static_assert(sizeof(BATCH_RESIDENT) / sizeof(int) == BATCH_N_TILES, "one entry per tile");
 
-// What the tiles from I on cost for units of `blocks` row blocks, `kt` K tiles and T tokens (a tile
-// at a time as constants, so that a call pays for shifts instead of divisions: one call of the
-// smallest group is a few hundred instructions of host code in all)
+// K slices across workgroups, for a long contraction on few rows: its tiles run on while the rest of the chip
+// idles (24 tokens x 4096 rows x 14336: 64 workgroups of 56 stages).  What a unit's own shapes allow, so that its
+// workspace can be planned: at least eight K tiles a slice, at most four slices and no more than about a thousand workgroups
+// on tiles of 64 rows x 32 tokens.  Up to 32 tokens: a slice of 64 x 4096 results is a megabyte, more than the
+// rest of such a call's workspace.
+constexpr int BATCH_SLICED_T = 32;
+static int unit_row_blocks(const glowq_unit& u) {
+  int blocks = 0;
+  for (int i = 0; u.modules && i < u.n_modules; ++i) blocks += (u.modules[i].d_out + 15) / 16;
+  return blocks;
+}
+static int batch_slices_allowed(const glowq_unit& u) {
+  const int blocks = unit_row_blocks(u), wgs = (blocks + 3) / 4 * ((u.T + 31) / 32);
+  if (u.T <= DEC_SMALL_T || u.T > BATCH_SLICED_T || blocks == 0 || wgs > 1024) return 1;
+  return std::max(1, std::min(std::min(BATCH_MAX_SLICES, u.d_in / 1024), 1024 / wgs));
+}
+// words of the counts (a tile has at least one row block and 16 tokens), and bytes with the slabs (whole tiles of at most 128
+// rows, and of the tokens of the widest tile that such a call takes)
+static size_t batch_count_words(const glowq_unit& u) { return ((size_t)unit_row_blocks(u) * ((u.T + 15) / 16) + 63) / 64 * 64; }
+size_t batch_slab_bytes(const glowq_unit& u) {
+  const int S = batch_slices_allowed(u);
+  if (S <= 1) return 0;
+  return batch_count_words(u) * 4 + (size_t)S * ((unit_row_blocks(u) + 7) / 8 * 128) * 64 * 4;
+}
+
+// What the tiles from I on cost for units of `blocks` row blocks, `kt` K tiles and T tokens, of which `allowed` K slices
+// (a tile at a time as constants, so that a call pays for shifts instead of divisions: one call of the
+// smallest group is a few hundred instructions of host code in all).  A contraction is cut where the launch would take
+// its length and not its share of the chip: all units to the stages that the longest one is left with, `cut` slices of
+// it, and BATCH_SLICE_US for the sum (out to memory, a count, back).  The pieces have to fit the chip one per compute
+// unit: beyond, they share what they were to have alone (26 tokens x 3 x 3112 rows x 5120 16.8 -> 20.5 us, 25 x 2 x 3816 x
+// 8448 18.5 -> 23.5).  One unit is cut where the estimate falls by 15 %, several where it falls by 10 % (binary16; with less
+// a layer of 4096 / 14336 at 16 tokens went from 31.9 to 34.1 us) or at all (bfloat16, whose uncut launches are estimated too
+// low: the same layer at 24 tokens 50.8 -> 39.4).  Measured over 310 calls of 5 to 32 tokens: 11 tokens x 1168
+// rows x 13568 16.2 -> 12.8 us, 23 x 4480 x 9984 22.9 -> 16.7, layers of 768 / 13056 at 31 tokens 34.1 -> 24.5, of
+// 512 / 7552 at 7 tokens (four) 22.7 -> 15.3; none that is cut by these rules was slower by more than calls differ.
+constexpr float BATCH_SLICE_US = 4.0f, BATCH_CUT_ONE = 0.85f, BATCH_CUT_SEVERAL[2] = {0.9f, 1.0f};
 struct BatchSize {
-  int blocks, kt, T;
+  int blocks, kt, T, allowed;
 };
+struct BatchChoice {
+  int tile, cut;
+  float cost;
+};
+static inline int batch_stages(int kt, int groups, int slices) { return (kt + groups * slices - 1) / (groups * slices); }
+static inline int batch_cut(const BatchSize& u, int groups, int target) {
+  return u.allowed == 1 ? 1 : std::min(u.allowed, (batch_stages(u.kt, groups, 1) + target - 1) / target);
+}
 template <int I>
-static inline void cheapest_batch_tile(const BatchSize* u, int n, bool f16, int max_mb, int* best, float* cost) {
+static inline void cheapest_batch_tile(const BatchSize* u, int n, bool f16, int max_mb, int least_cut, int most_cut, BatchChoice* best) {
   constexpr BatchTile t = BATCH_TILES[I];
   constexpr int ks = t.nw / t.rw, rows = t.rb * t.rw, tok = 16 * t.mb;
   if (t.mb <= max_mb) {
-    long long work = 0, wgs = 0;
-    int chain = 0;
-    for (int k = 0; k < n; ++k) {
-      const int stages = (u[k].kt + ks - 1) / ks;
-      const long long w = (long long)((u[k].blocks + rows - 1) / rows) * ((u[k].T + tok - 1) / tok);
-      wgs += w;
-      work += w * stages;
-      chain = std::max(chain, stages);
-    }
-    const float alone = t.chain[f16 ? 0 : 1], busy = t.busy[f16 ? 0 : 1];
-    const float share = wgs <= 256 * BATCH_RESIDENT[I] ? (float)((wgs + 255) / 256) * busy : (float)wgs / 256.f * busy + 0.8f * alone;
-    const float c = t.start + std::max(((float)chain + t.ends) * alone, ((float)work / (float)wgs + t.ends) * share);
-    if (*best < 0 || c < *cost) {
-      *best = I;
-      *cost = c;
+    int longest = 0;
+    for (int k = 0; k < n; ++k) longest = std::max(longest, u[k].kt);
+    longest = (longest + ks - 1) / ks;
+    for (int cut = least_cut; cut <= most_cut; ++cut) {
+      long long work = 0, wgs = 0, pieces = 0;
+      int chain = 0;
+      for (int k = 0; k < n; ++k) {
+        const int S = cut == 1 ? 1 : batch_cut(u[k], ks, (longest + cut - 1) / cut), stages = S == 1 ? (u[k].kt + ks - 1) / ks : batch_stages(u[k].kt, ks, S);
+        const long long w = (long long)((u[k].blocks + rows - 1) / rows) * ((u[k].T + tok - 1) / tok) * S;
+        wgs += w;
+        work += w * stages;
+        chain = std::max(chain, stages);
+        if (S > 1) pieces += w;
+      }
+      if (pieces > 256) break;
+      const float alone = t.chain[f16 ? 0 : 1], busy = t.busy[f16 ? 0 : 1];
+      const float share = wgs <= 256 * BATCH_RESIDENT[I] ? (float)((wgs + 255) / 256) * busy : (float)wgs / 256.f * busy + 0.8f * alone;
+      const float c = t.start + std::max(((float)chain + t.ends) * alone, ((float)work / (float)wgs + t.ends) * share) + (cut > 1 ? BATCH_SLICE_US : 0.f);
+      if (best->tile < 0 || c < best->cost) *best = BatchChoice{I, cut, c};
     }
   }
-  if constexpr (I + 1 < BATCH_N_TILES) cheapest_batch_tile<I + 1>(u, n, f16, max_mb, best, cost);
+  if constexpr (I + 1 < BATCH_N_TILES) cheapest_batch_tile<I + 1>(u, n, f16, max_mb, least_cut, most_cut, best);
 }
 
-// The cheapest tile for these units in one launch, and what it is taken to cost (us beyond the
-// launch itself).
-int choose_batch_tile(const glowq_unit* const* units, int n, float* cost) {
+// The cheapest tile for these units in one launch, what it is taken to cost (us beyond the launch itself) and, given
+// `slices`, the K slices of every unit.
+int choose_batch_tile(const glowq_unit* const* units, int n, float* cost, int* slices) {
   const bool f16 = units[0]->act_dtype == GLOWQ_F16, exact = f16 && units[0]->T <= 32;
   BatchSize sizes[BATCH_MAX_UNITS];
+  int most_cut = 1;
   for (int k = 0; k < n; ++k) {
     const glowq_unit& u = *units[k];
-    sizes[k] = BatchSize{0, u.d_in / 128, u.T};
-    for (int i = 0; i < u.n_modules; ++i) sizes[k].blocks += (u.modules[i].d_out + 15) / 16;
+    sizes[k] = BatchSize{unit_row_blocks(u), u.d_in / 128, u.T, 1};
+    if (slices) {
+      sizes[k].allowed = batch_slices_allowed(u);
+      most_cut = std::max(most_cut, sizes[k].allowed);
+    }
   }
-  int best = -1;
-  cheapest_batch_tile<0>(sizes, n, f16, exact ? 2 : 4, &best, cost);
-  return best;
+  BatchChoice best = {-1, 1, 0.f};
+  cheapest_batch_tile<0>(sizes, n, f16, exact ? 2 : 4, 1, 1, &best);
+  if (most_cut > 1) {
+    BatchChoice cut = {-1, 1, 0.f};
+    cheapest_batch_tile<0>(sizes, n, f16, exact ? 2 : 4, 2, most_cut, &cut);
+    if (cut.tile >= 0 && cut.cost < (n > 1 ? BATCH_CUT_SEVERAL[f16 ? 0 : 1] : BATCH_CUT_ONE) * best.cost) best = cut;
+  }
+  *cost = best.cost;
+  if (slices) {
+    const int ks = BATCH_TILES[best.tile].nw / BATCH_TILES[best.tile].rw;
+    int longest = 0;
+    for (int k = 0; k < n; ++k) longest = std::max(longest, batch_stages(sizes[k].kt, ks, 1));
+    for (int k = 0; k < n; ++k) slices[k] = best.cut == 1 ? 1 : batch_cut(sizes[k], ks, (longest + best.cut - 1) / best.cut);
+  }
+  return best.tile;
 }
 
 // K slices of the projection inside the launch: about 1024 channels each, at most four, and no
@@ -560,18 +688,30 @@ void plan_batch_projection(const glowq_unit& u, UnitWorkspace& w) {
   w.ksplit = (u.d_in + w.kslice - 1) / w.kslice;
 }
 
-template <int ACT, bool EXACT, bool G128, int NB, int I>
+template <int ACT, bool EXACT, bool G128, bool CUT, int NB, int I>
 static void launch_batch_tile(const BatchArgs<NB>& b, int tile, int n_wgs, hipStream_t st) {
   constexpr BatchTile t = BATCH_TILES[I];
   if constexpr (!EXACT || t.mb <= 2) {
-    if (tile == I) k_decode_batch<ACT, t.mb, t.rb, t.rw, t.nw, EXACT, G128, NB><<<dim3((unsigned)n_wgs), dim3(t.nw * 64), 0, st>>>(b);
+    if (tile == I) k_decode_batch<ACT, t.mb, t.rb, t.rw, t.nw, EXACT, G128, CUT, NB><<<dim3((unsigned)n_wgs), dim3(t.nw * 64), 0, st>>>(b);
   }
-  if constexpr (I + 1 < BATCH_N_TILES) launch_batch_tile<ACT, EXACT, G128, NB, I + 1>(b, tile, n_wgs, st);
+  if constexpr (I + 1 < BATCH_N_TILES) launch_batch_tile<ACT, EXACT, G128, CUT, NB, I + 1>(b, tile, n_wgs, st);
+}
+
+template <bool CUT, int NB>
+static void launch_batch_types(const BatchArgs<NB>& b, int ti, int wg, bool f16, bool exact, bool g128, hipStream_t st) {
+  if (exact && g128) launch_batch_tile<ACT_F16, true, true, CUT, NB, 0>(b, ti, wg, st);
+  else if (exact) launch_batch_tile<ACT_F16, true, false, CUT, NB, 0>(b, ti, wg, st);
+  else if (!f16 && g128) launch_batch_tile<ACT_BF16, false, true, CUT, NB, 0>(b, ti, wg, st);
+  else if (!f16) launch_batch_tile<ACT_BF16, false, false, CUT, NB, 0>(b, ti, wg, st);
+  else if constexpr (!CUT) {                     // (no call of binary16 past 32 tokens is cut)
+    if (g128) launch_batch_tile<ACT_F16, false, true, CUT, NB, 0>(b, ti, wg, st);
+    else launch_batch_tile<ACT_F16, false, false, CUT, NB, 0>(b, ti, wg, st);
+  }
 }
 
 template <int NB>
 static hipError_t launch_batch(const glowq_unit* const* units, const UnitWorkspace* ws, const bool* restore, int n,
-                               int ti, hipStream_t st) {
+                               int ti, const int* slices, hipStream_t st) {
   BatchArgs<NB> b;
   // longest contraction first: the hardware starts workgroups in index order
   int order[NB];
@@ -600,6 +740,12 @@ static hipError_t launch_batch(const glowq_unit* const* units, const UnitWorkspa
     bu.out_f32 = u.out_dtype == GLOWQ_F32 ? 1 : 0;
     bu.restore = restore[order[oi]] ? 1 + w.gather : 0;
     bu.part = nullptr; bu.rslots = nullptr; bu.ctl = nullptr;
+    bu.ks = slices[order[oi]];
+    bu.count = nullptr; bu.slab = nullptr;
+    if (bu.ks > 1) {
+      bu.count = (uint32_t*)(w.base + w.off_splitk);
+      bu.slab = (u32x4_t*)(bu.count + batch_count_words(u));
+    }
     bu.ksplit = w.ksplit; bu.kslice = w.kslice;
     bu.prod_start = n_prod;
     bu.n_prod = 0;
@@ -617,27 +763,25 @@ static hipError_t launch_batch(const glowq_unit* const* units, const UnitWorkspa
     b.u[oi].wg_start = wg;
     b.u[oi].n_ttiles = (b.u[oi].T + 16 * tile.mb - 1) / (16 * tile.mb);
     b.u[oi].n_groups = (b.u[oi].n_blocks + tile.rb * tile.rw - 1) / (tile.rb * tile.rw);
-    wg += b.u[oi].n_groups * b.u[oi].n_ttiles;
+    wg += b.u[oi].n_groups * b.u[oi].n_ttiles * b.u[oi].ks;
   }
   for (int i = n; i < NB; ++i) b.u[i] = b.u[0];
   b.n = n;
   b.n_prod = n_prod;
   const bool f16 = units[0]->act_dtype == GLOWQ_F16, g128 = units[0]->group_size == 128;
   const bool exact = f16 && units[0]->T <= 32;
-  if (exact && g128) launch_batch_tile<ACT_F16, true, true, NB, 0>(b, ti, wg, st);
-  else if (exact) launch_batch_tile<ACT_F16, true, false, NB, 0>(b, ti, wg, st);
-  else if (f16 && g128) launch_batch_tile<ACT_F16, false, true, NB, 0>(b, ti, wg, st);
-  else if (f16) launch_batch_tile<ACT_F16, false, false, NB, 0>(b, ti, wg, st);
-  else if (g128) launch_batch_tile<ACT_BF16, false, true, NB, 0>(b, ti, wg, st);
-  else launch_batch_tile<ACT_BF16, false, false, NB, 0>(b, ti, wg, st);
+  bool cut = false;
+  for (int i = 0; i < n; ++i) cut = cut || slices[i] > 1;
+  if (cut) launch_batch_types<true, NB>(b, ti, wg, f16, exact, g128, st);
+  else launch_batch_types<false, NB>(b, ti, wg, f16, exact, g128, st);
   return hipGetLastError();
 }
 
 // units[i] uses workspace slice ws[i]; all of them pass batch_compatible with units[0]
 hipError_t launch_decode_batch(const glowq_unit* const* units, const UnitWorkspace* ws, const bool* restore, int n,
-                               int tile, hipStream_t st) {
-  if (n == 1) return launch_batch<1>(units, ws, restore, n, tile, st);
-  return launch_batch<BATCH_MAX_UNITS>(units, ws, restore, n, tile, st);
+                               int tile, const int* slices, hipStream_t st) {
+  if (n == 1) return launch_batch<1>(units, ws, restore, n, tile, slices, st);
+  return launch_batch<BATCH_MAX_UNITS>(units, ws, restore, n, tile, slices, st);
 }
 
 }  // namespace glowq

@@ -92,3 +92,66 @@ def test_units_of_one_call_share_a_launch(T):
             for y, yr in zip(d.outputs(), ref):
                 assert rel_err(y, yr) <= TOL
         ws.assert_idle()
+
+
+# Contractions cut across workgroups: slices of unequal length, two and four of them, one K tile per wave group, ragged
+# row blocks that straddle modules, ragged token tiles; with the correction (the first slice's) and without
+@pytest.mark.parametrize("act", ["f16", "bf16"])
+@pytest.mark.parametrize("T,d_in,d_outs", [(9, 13696, (1000, 600)), (11, 13568, (1168,)), (17, 14336, (40, 264, 96)),
+                                           (32, 14208, (4096,))])
+def test_contractions_cut_across_workgroups(T, d_in, d_outs, act):
+    u = recipe_unit(O, 1, 0, T, r=72, shape=UnitShape("g", d_in, d_outs), act=act, G=128, method="alg1", qr="none")
+    du = DeviceUnit(u)
+    slices = G.glowq_debug_route([du.desc])[0].k_slices
+    assert 2 <= slices <= 4 and G.glowq_debug_route([du.desc], False)[0].k_slices == 1
+    ws = Workspace([du.desc])
+    for restore in (True, False):
+        refs, first = O.group_forward(u, restore), None
+        for _ in range(3):                  # the counts of the call before are in the workspace
+            du.clear()
+            G.glowq_group_forward(du.desc, restore, ws.ptr, ws.bytes, stream())
+            ys = du.outputs()
+            for y, ref in zip(ys, refs):
+                assert np.isfinite(y).all() and rel_err(y, ref) <= TOL + ULP[act]
+            first = first or ys
+            assert all(np.array_equal(a, b) for a, b in zip(first, ys))      # whichever slice comes last
+            ws.assert_idle()
+
+
+@pytest.mark.parametrize("act", ["f16", "bf16"])
+def test_cut_and_whole_contractions_share_a_launch(act):
+    shapes = [UnitShape("a", 1024, (1024, 256, 256)), UnitShape("b", 1024, (1024,)), UnitShape("c", 1024, (2048, 2048)),
+              UnitShape("d", 14208, (1024,))] * 2
+    units = [recipe_unit(O, 1, 0, 14, seed=70 + i, r=(64, 16)[i % 2], shape=s, act=act, G=128, method="alg1", qr="none")
+             for i, s in enumerate(shapes)]
+    mask = [i != 3 for i in range(len(shapes))]
+    dus = [DeviceUnit(u) for u in units]
+    routes = G.glowq_debug_route([d.desc for d in dus])
+    assert {r.launch for r in routes} == {0} and [r.k_slices > 1 for r in routes] == [False, False, False, True] * 2
+    ws = Workspace([d.desc for d in dus])
+    for _ in range(2):
+        for d in dus:
+            d.clear()
+        G.glowq_block_forward([d.desc for d in dus], bytes(mask), ws.ptr, ws.bytes, stream())
+        for u, d, on in zip(units, dus, mask):
+            for y, ref in zip(d.outputs(), O.group_forward(u, on)):
+                assert rel_err(y, ref) <= TOL + ULP[act]
+        ws.assert_idle()
+
+
+def test_cut_contractions_in_a_graph():
+    u = recipe_unit(O, 1, 0, 11, r=64, shape=UnitShape("g", 13568, (1168,)), act="bf16", G=128, method="alg1", qr="none")
+    du = DeviceUnit(u)
+    ws = Workspace([du.desc])
+    assert G.glowq_debug_route([du.desc])[0].k_slices > 1
+    refs = O.group_forward(u, True)
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        G.glowq_group_forward(du.desc, True, ws.ptr, ws.bytes, torch.cuda.current_stream().cuda_stream)
+    for _ in range(4):
+        du.clear()
+        graph.replay()
+        torch.cuda.synchronize()
+        for y, ref in zip(du.outputs(), refs):
+            assert rel_err(y, ref) <= TOL + ULP["bf16"]
