@@ -41,6 +41,7 @@ template <int ACT> struct PfShape {
 constexpr int PF_MAX_UNITS = 8;
 constexpr int PF_MAX_MODS = 16;
 constexpr int PF_PANEL = 2;       // token tiles per panel of the tile order (see k_prefill)
+constexpr int PF_MB = 8;          // 16-token blocks per tile, at most (a projection tile's, whatever the tile)
 
 struct PfUnit {
   const uint16_t* X;
@@ -323,13 +324,15 @@ __global__ void __launch_bounds__(PfShape<ACT>::WAVES * 64, PfShape<ACT>::OCC) k
   constexpr int PF_WAVES = PfShape<ACT>::WAVES;
   constexpr int MT = 16 * MB;          // tokens per workgroup tile
   constexpr int XR = PF_WAVES * 8;     // X rows covered by one load instruction of the workgroup
-  constexpr int XI = MT / XR;          // 16-byte X loads per thread and stage
+  constexpr int XI = (MT + XR - 1) / XR;      // 16-byte X loads per thread and stage
   constexpr int RW = G128 ? 272 : 288; // words per tile record
-  // one stage = MT rows x 64 channels, 128 bytes per row, no padding; a ring of three:
+  // one stage = MT rows x 64 channels, 128 bytes per row (places for 128 rows), no padding; a ring of three:
   // the stage being read, the next one (landed or landing), the one after (landing)
   constexpr int NBUF = 3;
-  constexpr uint32_t STAGE_BYTES = MT * 64 * 2;
-  __shared__ __attribute__((aligned(1024))) uint16_t xs[NBUF * MT * 64];
+  constexpr int SR = 16 * PF_MB;
+  static_assert(MB <= PF_MB, "a stage holds the tile's rows");
+  constexpr uint32_t STAGE_BYTES = SR * 64 * 2;
+  __shared__ __attribute__((aligned(1024))) uint16_t xs[NBUF * SR * 64];
   // per wave: its RB tile records of the next tile (1 KiB of words each, then 512 bytes
   // for their scale/zero words), landed here by the same kind of load and taken into
   // registers once per tile
@@ -340,7 +343,7 @@ __global__ void __launch_bounds__(PfShape<ACT>::WAVES * 64, PfShape<ACT>::OCC) k
   __shared__ uint32_t corr_failed;
 
   if ((int)blockIdx.x < a.n_proj_wgs) {
-    proj_tile<ACT, MB>(a, xs);
+    proj_tile<ACT, PF_MB>(a, xs);
     return;
   }
   int mi = 0;
@@ -409,7 +412,7 @@ __global__ void __launch_bounds__(PfShape<ACT>::WAVES * 64, PfShape<ACT>::OCC) k
     const int st = min(stage, nstages - 1);
     __builtin_amdgcn_global_load_lds(
         (const __attribute__((address_space(1))) void*)((const char*)(xtile + st * 64) + xoff[i]),
-        (__attribute__((address_space(3))) void*)(xs + slot * (MT * 64) + (XR * i + 8 * wave) * 64),
+        (__attribute__((address_space(3))) void*)(xs + slot * (SR * 64) + (XR * i + 8 * wave) * 64),
         16, 0, 0);
   };
   // The operand reads are issued as assembly, because the compiler orders every LDS
@@ -632,7 +635,10 @@ __global__ void __launch_bounds__(PfShape<ACT>::WAVES * 64, PfShape<ACT>::OCC) k
           const int row = min((nb0 + b) * 16 + n, M.d_out - 1);   // clamped like the tiles
           if (rs < rstages) vm_load(af[rs][jj][b], M.A + (size_t)row * U.r + (j0 < U.r ? j0 : 0));
         }
-    const bool ready = wait_tile_ready(U.flags + MB * mt, U.status);
+    // (the tile's tokens may lie in two of the projection's tiles)
+    const int pt = tok0 / (16 * PF_MB), pt_end = (min(tok0 + MT, U.T) - 1) / (16 * PF_MB);
+    bool ready = wait_tile_ready(U.flags + PF_MB * pt, U.status);
+    if (MB < PF_MB && pt_end > pt) ready = wait_tile_ready(U.flags + PF_MB * pt_end, U.status) && ready;
     if (!ready && lane == 0) atomicOr(&corr_failed, 1u);
     if (ready) {
       const uint16_t* rtile = uniform_ptr(U.R16 + (size_t)tok0 * U.r);
@@ -647,7 +653,7 @@ __global__ void __launch_bounds__(PfShape<ACT>::WAVES * 64, PfShape<ACT>::OCC) k
           if (rs < rstages)
             __builtin_amdgcn_global_load_lds(
                 (const __attribute__((address_space(1))) void*)((const char*)rtile + off),
-                (__attribute__((address_space(3))) void*)(xs + rs * (MT * 64) + (XR * i + 8 * wave) * 64),
+                (__attribute__((address_space(3))) void*)(xs + rs * (SR * 64) + (XR * i + 8 * wave) * 64),
                 16, 0, /*device scope*/ 16);
         }
     }
@@ -720,10 +726,19 @@ __global__ void __launch_bounds__(PfShape<ACT>::WAVES * 64, PfShape<ACT>::OCC) k
 namespace glowq {
 
 template <int ACT, int MB, int RB>
-static hipError_t launch_prefill_t(const PrefillArgs& a, int n_wgs, int G, hipStream_t st) {
+static void launch_prefill_g(const PrefillArgs& a, int n_wgs, int G, hipStream_t st) {
   dim3 grid((unsigned)n_wgs), block(PfShape<ACT>::WAVES * 64);
   if (G == 128) k_prefill<ACT, MB, RB, true><<<grid, block, 0, st>>>(a);
   else k_prefill<ACT, MB, RB, false><<<grid, block, 0, st>>>(a);
+}
+template <int ACT, int RB>
+static hipError_t launch_prefill_t(const PrefillArgs& a, int mb, int n_wgs, int G, hipStream_t st) {
+  switch (mb) {
+    case 5: launch_prefill_g<ACT, 5, RB>(a, n_wgs, G, st); break;
+    case 6: launch_prefill_g<ACT, 6, RB>(a, n_wgs, G, st); break;
+    case 7: launch_prefill_g<ACT, 7, RB>(a, n_wgs, G, st); break;
+    default: launch_prefill_g<ACT, 8, RB>(a, n_wgs, G, st); break;
+  }
   return hipGetLastError();
 }
 template <int ACT> static hipError_t launch_wide(const PrefillArgs& a, int n_wgs, int G, hipStream_t st) {
@@ -732,8 +747,6 @@ template <int ACT> static hipError_t launch_wide(const PrefillArgs& a, int n_wgs
   else k_wide<ACT, false><<<grid, block, 0, st>>>(a);
   return hipGetLastError();
 }
-
-constexpr int PF_MB = 8;          // 16-token blocks per tile (a projection tile's too, whatever the tile)
 
 // Slices of K for a unit whose tiles would each run a long contraction while most of the chip
 // idles: at least 8192 channels on at most 128 tiles (a quarter of the workgroups the chip
@@ -808,6 +821,20 @@ static inline long long prefill_tiles(const glowq_unit& u, int tile_blocks, int 
   return rows * ((u.T + tokens - 1) / tokens);
 }
 
+// Tokens of a launch's (large or half-size) tiles: the tokens of a unit dealt evenly to as many tiles as tiles of 128
+// would be, in blocks of 16, the most that a unit asks for.  (A tile's products and its reads of X go with its
+// tokens, the dequantiser and the weights do not.  Layers of 4096 / 11008 and 4096 / 14336, us, tiles of 128 tokens and these: 70
+// tokens 72 -> 60, 140 tokens 112 -> 88, 200 tokens 132 -> 126, 260 tokens 174 -> 146, 300 tokens 165 -> 152; 110 other
+// calls of 65 to 384 tokens 2.4 % on average, 24 % at most.)
+static int prefill_token_blocks(const glowq_unit* const* units, int n) {
+  int mb = 5;
+  for (int k = 0; k < n; ++k) {
+    const int tiles = (units[k]->T + 16 * PF_MB - 1) / (16 * PF_MB);
+    mb = std::max(mb, (units[k]->T + 16 * tiles - 1) / (16 * tiles));
+  }
+  return mb;
+}
+
 // What one launch over these units is taken to cost, in the same terms as the batched kernel's
 // tiles (BATCH_TILES), in us per K tile: for a workgroup alone on its compute unit, for two sharing
 // one (the vector ALU and the matrix pipe take turns, so a second workgroup adds little, and the
@@ -826,6 +853,8 @@ static float prefill_cost_of(const glowq_unit* const* units, const int* slices, 
   const bool f16 = units[0]->act_dtype == GLOWQ_F16, half = tile == PF_TILE_HALF;
   const PrefillCost c = half ? (f16 ? PrefillCost{3.48f, 2.50f, 1.09f, 1.45f, 0.79f, 0.88f, 10.9f} : PrefillCost{0.04f, 5.01f, 1.17f, 2.07f, 0.94f, 5.33f, 10.9f})
                              : (f16 ? PrefillCost{1.78f, 4.88f, 1.43f, 3.42f, 0.73f, 0.34f, 0.5f} : PrefillCost{5.46f, 5.94f, 1.59f, 2.87f, 0.82f, 1.08f, 0.5f});
+  // (half of a K tile's time goes with the tile's tokens)
+  const double tokens = 0.5 + 0.5 * prefill_token_blocks(units, n) / PF_MB;
   double work = 0.0, wgs = 0.0;
   int chain = 0, sliced = 0;
   for (int k = 0; k < n; ++k) {
@@ -838,7 +867,7 @@ static float prefill_cost_of(const glowq_unit* const* units, const int* slices, 
     // outputs, do not depend on the mask)
     const double proj = u.r > 0 ? (double)((u.T + 127) / 128) * std::min(8, (u.d_in + 2047) / 2048) : 0.0;
     wgs += tiles + proj;
-    work += tiles * (kt + c.ends) + proj * std::min(kt, 8);
+    work += tiles * (tokens * kt + c.ends) + proj * std::min(kt, 8);
     chain = std::max(chain, kt);
     sliced += S > 1 ? 1 : 0;
   }
@@ -847,7 +876,7 @@ static float prefill_cost_of(const glowq_unit* const* units, const int* slices, 
   const double share = per_cu <= 1.0   ? c.alone
                        : per_cu <= 2.0 ? c.pair * (c.few + (1.0 - c.few) * (per_cu - 1.0))
                                        : std::max((double)c.pair, c.busy * per_cu + 0.8 * c.alone);
-  return (float)(c.start + sliced * c.sum + std::max((chain + c.ends) * (double)c.alone, work / wgs * share));
+  return (float)(c.start + sliced * c.sum + std::max((tokens * chain + c.ends) * (double)c.alone, work / wgs * share));
 }
 // The units of a launch, longest contraction first
 static void longest_first(const glowq_unit* const* units, int n, int* order) {
@@ -986,9 +1015,8 @@ hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorksp
                                 const bool* restore, int n_units, int tile, const int* slices, hipStream_t st) {
   PrefillArgs a;
   const glowq_unit& u0 = *units[0];
-  constexpr int MB = PF_MB;
   const int tile_blocks = prefill_tile_blocks(u0.act_dtype, tile);
-  const int tile_tokens = tile == PF_TILE_WIDE ? WD_TOK : 16 * MB;
+  const int mb = prefill_token_blocks(units, n_units), tile_tokens = tile == PF_TILE_WIDE ? WD_TOK : 16 * mb;
   // longest contraction first
   int order[PF_MAX_UNITS];
   longest_first(units, n_units, order);
@@ -998,7 +1026,7 @@ hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorksp
     const int ui = order[oi];
     const glowq_unit& u = *units[ui];
     PfUnit& pu = a.unit[oi];
-    const int n_mtiles = (u.T + 16 * MB - 1) / (16 * MB);
+    const int n_mtiles = (u.T + 16 * PF_MB - 1) / (16 * PF_MB);
     pu.proj_start = -1;
     pu.parts = ws[ui].pf_parts;
     pu.part_stages = ws[ui].pf_part_stages;
@@ -1066,10 +1094,10 @@ hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorksp
   const bool f16 = (u0.act_dtype == GLOWQ_F16);
   hipError_t err;
   if (tile == PF_TILE_WIDE) err = f16 ? launch_wide<ACT_F16>(a, wg, u0.group_size, st) : launch_wide<ACT_BF16>(a, wg, u0.group_size, st);
-  else if (tile == PF_TILE_HALF) err = f16 ? launch_prefill_t<ACT_F16, MB, PF_HALF_RB>(a, wg, u0.group_size, st)
-                      : launch_prefill_t<ACT_BF16, MB, PF_HALF_RB>(a, wg, u0.group_size, st);
-  else err = f16 ? launch_prefill_t<ACT_F16, MB, PfShape<ACT_F16>::RB>(a, wg, u0.group_size, st)
-                 : launch_prefill_t<ACT_BF16, MB, PfShape<ACT_BF16>::RB>(a, wg, u0.group_size, st);
+  else if (tile == PF_TILE_HALF) err = f16 ? launch_prefill_t<ACT_F16, PF_HALF_RB>(a, mb, wg, u0.group_size, st)
+                                           : launch_prefill_t<ACT_BF16, PF_HALF_RB>(a, mb, wg, u0.group_size, st);
+  else err = f16 ? launch_prefill_t<ACT_F16, PfShape<ACT_F16>::RB>(a, mb, wg, u0.group_size, st)
+                 : launch_prefill_t<ACT_BF16, PfShape<ACT_BF16>::RB>(a, mb, wg, u0.group_size, st);
   if (err != hipSuccess) return err;
   // the sliced units' outputs
   for (int ui = 0; ui < n_units; ++ui) {
