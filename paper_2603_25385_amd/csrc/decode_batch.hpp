@@ -574,9 +574,10 @@ static int unit_row_blocks(const glowq_unit& u) {
   return blocks;
 }
 static int batch_slices_allowed(const glowq_unit& u) {
-  const int blocks = unit_row_blocks(u), wgs = (blocks + 3) / 4 * ((u.T + 31) / 32);
-  if (u.T <= DEC_SMALL_T || u.T > BATCH_SLICED_T || blocks == 0 || wgs > 1024) return 1;
-  return std::max(1, std::min(std::min(BATCH_MAX_SLICES, u.d_in / 1024), 1024 / wgs));
+  if (u.d_in < 2048 || u.T <= DEC_SMALL_T || u.T > BATCH_SLICED_T) return 1;
+  const int wgs = (unit_row_blocks(u) + 3) / 4;
+  if (wgs == 0 || wgs > 512) return 1;
+  return std::min(std::min(BATCH_MAX_SLICES, u.d_in / 1024), 1024 / wgs);
 }
 // words of the counts (a tile has at least one row block and 16 tokens), and bytes with the slabs (whole tiles of at most 128
 // rows, and of the tokens of the widest tile that such a call takes)
@@ -688,24 +689,44 @@ void plan_batch_projection(const glowq_unit& u, UnitWorkspace& w) {
   w.ksplit = (u.d_in + w.kslice - 1) / w.kslice;
 }
 
+// Token blocks of a launch's tiles: those of the tile, or three instead of four where every unit's tokens, dealt evenly to as
+// many tiles, fit them (33 to 48 tokens, 65 to 96, ..): a quarter less of X and of the products, and on tiles of
+// 64 rows three workgroups per compute unit instead of two.  (Us on four blocks and on three: 88 tokens x 2 x 3272 rows x
+// 4224 21.3 and 17.4, 46 x 3 x 5048 x 11008 46.6 and 41.1, 141 x 3 x 3256 x 9600 65.2 and 56.9, four layers of 4992 / 1920 at
+// 47 tokens 68.8 and 62.0.)
+static int batch_token_blocks(const glowq_unit* const* units, int n, int tile) {
+  if (BATCH_TILES[tile].mb != 4) return BATCH_TILES[tile].mb;
+  for (int k = 0; k < n; ++k) {
+    const int tiles = (units[k]->T + 63) / 64;
+    if (units[k]->T > 48 * tiles) return 4;
+  }
+  return 3;
+}
+
 template <int ACT, bool EXACT, bool G128, bool CUT, int NB, int I>
-static void launch_batch_tile(const BatchArgs<NB>& b, int tile, int n_wgs, hipStream_t st) {
+static void launch_batch_tile(const BatchArgs<NB>& b, int tile, int mb, int n_wgs, hipStream_t st) {
   constexpr BatchTile t = BATCH_TILES[I];
+  if constexpr (!EXACT && !CUT && t.mb == 4) {
+    if (tile == I && mb == 3) {
+      k_decode_batch<ACT, 3, t.rb, t.rw, t.nw, EXACT, G128, CUT, NB><<<dim3((unsigned)n_wgs), dim3(t.nw * 64), 0, st>>>(b);
+      return;
+    }
+  }
   if constexpr (!EXACT || t.mb <= 2) {
     if (tile == I) k_decode_batch<ACT, t.mb, t.rb, t.rw, t.nw, EXACT, G128, CUT, NB><<<dim3((unsigned)n_wgs), dim3(t.nw * 64), 0, st>>>(b);
   }
-  if constexpr (I + 1 < BATCH_N_TILES) launch_batch_tile<ACT, EXACT, G128, CUT, NB, I + 1>(b, tile, n_wgs, st);
+  if constexpr (I + 1 < BATCH_N_TILES) launch_batch_tile<ACT, EXACT, G128, CUT, NB, I + 1>(b, tile, mb, n_wgs, st);
 }
 
 template <bool CUT, int NB>
-static void launch_batch_types(const BatchArgs<NB>& b, int ti, int wg, bool f16, bool exact, bool g128, hipStream_t st) {
-  if (exact && g128) launch_batch_tile<ACT_F16, true, true, CUT, NB, 0>(b, ti, wg, st);
-  else if (exact) launch_batch_tile<ACT_F16, true, false, CUT, NB, 0>(b, ti, wg, st);
-  else if (!f16 && g128) launch_batch_tile<ACT_BF16, false, true, CUT, NB, 0>(b, ti, wg, st);
-  else if (!f16) launch_batch_tile<ACT_BF16, false, false, CUT, NB, 0>(b, ti, wg, st);
+static void launch_batch_types(const BatchArgs<NB>& b, int ti, int mb, int wg, bool f16, bool exact, bool g128, hipStream_t st) {
+  if (exact && g128) launch_batch_tile<ACT_F16, true, true, CUT, NB, 0>(b, ti, mb, wg, st);
+  else if (exact) launch_batch_tile<ACT_F16, true, false, CUT, NB, 0>(b, ti, mb, wg, st);
+  else if (!f16 && g128) launch_batch_tile<ACT_BF16, false, true, CUT, NB, 0>(b, ti, mb, wg, st);
+  else if (!f16) launch_batch_tile<ACT_BF16, false, false, CUT, NB, 0>(b, ti, mb, wg, st);
   else if constexpr (!CUT) {                     // (no call of binary16 past 32 tokens is cut)
-    if (g128) launch_batch_tile<ACT_F16, false, true, CUT, NB, 0>(b, ti, wg, st);
-    else launch_batch_tile<ACT_F16, false, false, CUT, NB, 0>(b, ti, wg, st);
+    if (g128) launch_batch_tile<ACT_F16, false, true, CUT, NB, 0>(b, ti, mb, wg, st);
+    else launch_batch_tile<ACT_F16, false, false, CUT, NB, 0>(b, ti, mb, wg, st);
   }
 }
 
@@ -758,10 +779,13 @@ static hipError_t launch_batch(const glowq_unit* const* units, const UnitWorkspa
     }
   }
   const BatchTile tile = BATCH_TILES[ti];
+  bool cut = false;
+  for (int i = 0; i < n; ++i) cut = cut || slices[i] > 1;
+  const int mb = cut ? tile.mb : batch_token_blocks(units, n, ti);
   int wg = n_prod;
   for (int oi = 0; oi < n; ++oi) {
     b.u[oi].wg_start = wg;
-    b.u[oi].n_ttiles = (b.u[oi].T + 16 * tile.mb - 1) / (16 * tile.mb);
+    b.u[oi].n_ttiles = (b.u[oi].T + 16 * mb - 1) / (16 * mb);
     b.u[oi].n_groups = (b.u[oi].n_blocks + tile.rb * tile.rw - 1) / (tile.rb * tile.rw);
     wg += b.u[oi].n_groups * b.u[oi].n_ttiles * b.u[oi].ks;
   }
@@ -770,10 +794,8 @@ static hipError_t launch_batch(const glowq_unit* const* units, const UnitWorkspa
   b.n_prod = n_prod;
   const bool f16 = units[0]->act_dtype == GLOWQ_F16, g128 = units[0]->group_size == 128;
   const bool exact = f16 && units[0]->T <= 32;
-  bool cut = false;
-  for (int i = 0; i < n; ++i) cut = cut || slices[i] > 1;
-  if (cut) launch_batch_types<true, NB>(b, ti, wg, f16, exact, g128, st);
-  else launch_batch_types<false, NB>(b, ti, wg, f16, exact, g128, st);
+  if (cut) launch_batch_types<true, NB>(b, ti, mb, wg, f16, exact, g128, st);
+  else launch_batch_types<false, NB>(b, ti, mb, wg, f16, exact, g128, st);
   return hipGetLastError();
 }
 

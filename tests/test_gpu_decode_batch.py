@@ -155,3 +155,18 @@ def test_cut_contractions_in_a_graph():
         torch.cuda.synchronize()
         for y, ref in zip(du.outputs(), refs):
             assert rel_err(y, ref) <= TOL + ULP["bf16"]
+
+
+# Tiles of 64 tokens that hold 48 of them: the last call that fits and the first that does not, in one, two and three token tiles
+@pytest.mark.parametrize("T,d_in,d_outs,act,tile", [
+    (48, 2688, (12008,), "f16", 5), (49, 2688, (10008,), "f16", 5), (96, 2688, (6008,), "f16", 5), (97, 2688, (6008,), "f16", 5),
+    (48, 640, (20008,), "f16", 6), (49, 128, (20008,), "f16", 6), (96, 128, (12008,), "f16", 6), (145, 128, (8008,), "f16", 6),
+    (144, 5888, (4008,), "bf16", 5), (145, 5888, (4008,), "bf16", 5), (144, 128, (10008,), "bf16", 6), (145, 128, (10008,), "bf16", 6)])
+def test_tiles_of_three_token_blocks(T, d_in, d_outs, act, tile):
+    u = recipe_unit(O, 1, 0, T, r=72, shape=UnitShape("g", d_in, d_outs), act=act, G=64, method="alg1", qr="none")
+    for restore in (True, False):
+        ys, du, _ = run_group(u, restore, out="act", ldy_pad=8)
+        r = G.glowq_debug_route([du.desc])[0]
+        assert (r.kernel, r.tile) == (G.GLOWQ_ROUTE_BATCHED, tile)
+        for y, ref in zip(ys, O.group_forward(u, restore)):
+            assert np.isfinite(y).all() and rel_err(y, ref) <= TOL + ULP[act]
