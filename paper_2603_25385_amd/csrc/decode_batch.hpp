@@ -564,7 +564,7 @@ static_assert(sizeof(BATCH_RESIDENT) / sizeof(int) == BATCH_N_TILES, "one entry 
 
 // K slices across workgroups, for a long contraction on few rows: its tiles run on while the rest of the chip
 // idles (24 tokens x 4096 rows x 14336: 64 workgroups of 56 stages).  What a unit's own shapes allow, so that its
-// workspace can be planned: at least eight K tiles a slice, at most four slices and no more than about a thousand workgroups
+// workspace can be planned: 32 K tiles and more, at least eight a slice, at most four slices and no more than about a thousand workgroups
 // on tiles of 64 rows x 32 tokens.  Up to 32 tokens: a slice of 64 x 4096 results is a megabyte, more than the
 // rest of such a call's workspace.
 constexpr int BATCH_SLICED_T = 32;
@@ -574,7 +574,7 @@ static int unit_row_blocks(const glowq_unit& u) {
   return blocks;
 }
 static int batch_slices_allowed(const glowq_unit& u) {
-  if (u.d_in < 2048 || u.T <= DEC_SMALL_T || u.T > BATCH_SLICED_T) return 1;
+  if (u.d_in < 4096 || u.T <= DEC_SMALL_T || u.T > BATCH_SLICED_T) return 1;
   const int wgs = (unit_row_blocks(u) + 3) / 4;
   if (wgs == 0 || wgs > 512) return 1;
   return std::min(std::min(BATCH_MAX_SLICES, u.d_in / 1024), 1024 / wgs);
@@ -612,18 +612,40 @@ static inline int batch_cut(const BatchSize& u, int groups, int target) {
   return u.allowed == 1 ? 1 : std::min(u.allowed, (batch_stages(u.kt, groups, 1) + target - 1) / target);
 }
 template <int I>
-static inline void cheapest_batch_tile(const BatchSize* u, int n, bool f16, int max_mb, int least_cut, int most_cut, BatchChoice* best) {
+static inline void cheapest_batch_tile(const BatchSize* u, int n, bool f16, int max_mb, BatchChoice* best) {
   constexpr BatchTile t = BATCH_TILES[I];
   constexpr int ks = t.nw / t.rw, rows = t.rb * t.rw, tok = 16 * t.mb;
   if (t.mb <= max_mb) {
-    int longest = 0;
-    for (int k = 0; k < n; ++k) longest = std::max(longest, u[k].kt);
-    longest = (longest + ks - 1) / ks;
-    for (int cut = least_cut; cut <= most_cut; ++cut) {
+    long long work = 0, wgs = 0;
+    int chain = 0;
+    for (int k = 0; k < n; ++k) {
+      const int stages = (u[k].kt + ks - 1) / ks;
+      const long long w = (long long)((u[k].blocks + rows - 1) / rows) * ((u[k].T + tok - 1) / tok);
+      wgs += w;
+      work += w * stages;
+      chain = std::max(chain, stages);
+    }
+    const float alone = t.chain[f16 ? 0 : 1], busy = t.busy[f16 ? 0 : 1];
+    const float share = wgs <= 256 * BATCH_RESIDENT[I] ? (float)((wgs + 255) / 256) * busy : (float)wgs / 256.f * busy + 0.8f * alone;
+    const float c = t.start + std::max(((float)chain + t.ends) * alone, ((float)work / (float)wgs + t.ends) * share);
+    if (best->tile < 0 || c < best->cost) *best = BatchChoice{I, 1, c};
+  }
+  if constexpr (I + 1 < BATCH_N_TILES) cheapest_batch_tile<I + 1>(u, n, f16, max_mb, best);
+}
+// the same with every number of slices from two on
+static void cheapest_cut_tile(const BatchSize* u, int n, bool f16, int max_mb, int most_cut, BatchChoice* best) {
+  int longest_kt = 0;
+  for (int k = 0; k < n; ++k) longest_kt = std::max(longest_kt, u[k].kt);
+  for (int i = 0; i < BATCH_N_TILES; ++i) {
+    const BatchTile& t = BATCH_TILES[i];
+    if (t.mb > max_mb) continue;
+    const int ks = t.nw / t.rw, rows = t.rb * t.rw, tok = 16 * t.mb, longest = batch_stages(longest_kt, ks, 1);
+    const float alone = t.chain[f16 ? 0 : 1], busy = t.busy[f16 ? 0 : 1];
+    for (int cut = 2; cut <= most_cut; ++cut) {
       long long work = 0, wgs = 0, pieces = 0;
       int chain = 0;
       for (int k = 0; k < n; ++k) {
-        const int S = cut == 1 ? 1 : batch_cut(u[k], ks, (longest + cut - 1) / cut), stages = S == 1 ? (u[k].kt + ks - 1) / ks : batch_stages(u[k].kt, ks, S);
+        const int S = batch_cut(u[k], ks, (longest + cut - 1) / cut), stages = batch_stages(u[k].kt, ks, S);
         const long long w = (long long)((u[k].blocks + rows - 1) / rows) * ((u[k].T + tok - 1) / tok) * S;
         wgs += w;
         work += w * stages;
@@ -631,13 +653,11 @@ static inline void cheapest_batch_tile(const BatchSize* u, int n, bool f16, int 
         if (S > 1) pieces += w;
       }
       if (pieces > 256) break;
-      const float alone = t.chain[f16 ? 0 : 1], busy = t.busy[f16 ? 0 : 1];
-      const float share = wgs <= 256 * BATCH_RESIDENT[I] ? (float)((wgs + 255) / 256) * busy : (float)wgs / 256.f * busy + 0.8f * alone;
-      const float c = t.start + std::max(((float)chain + t.ends) * alone, ((float)work / (float)wgs + t.ends) * share) + (cut > 1 ? BATCH_SLICE_US : 0.f);
-      if (best->tile < 0 || c < best->cost) *best = BatchChoice{I, cut, c};
+      const float share = wgs <= 256 * BATCH_RESIDENT[i] ? (float)((wgs + 255) / 256) * busy : (float)wgs / 256.f * busy + 0.8f * alone;
+      const float c = t.start + std::max(((float)chain + t.ends) * alone, ((float)work / (float)wgs + t.ends) * share) + BATCH_SLICE_US;
+      if (best->tile < 0 || c < best->cost) *best = BatchChoice{i, cut, c};
     }
   }
-  if constexpr (I + 1 < BATCH_N_TILES) cheapest_batch_tile<I + 1>(u, n, f16, max_mb, least_cut, most_cut, best);
 }
 
 // The cheapest tile for these units in one launch, what it is taken to cost (us beyond the launch itself) and, given
@@ -655,10 +675,10 @@ int choose_batch_tile(const glowq_unit* const* units, int n, float* cost, int* s
     }
   }
   BatchChoice best = {-1, 1, 0.f};
-  cheapest_batch_tile<0>(sizes, n, f16, exact ? 2 : 4, 1, 1, &best);
-  if (most_cut > 1) {
+  cheapest_batch_tile<0>(sizes, n, f16, exact ? 2 : 4, &best);
+  if (most_cut > 1 && best.cost > 2.f * BATCH_SLICE_US) {
     BatchChoice cut = {-1, 1, 0.f};
-    cheapest_batch_tile<0>(sizes, n, f16, exact ? 2 : 4, 2, most_cut, &cut);
+    cheapest_cut_tile(sizes, n, f16, exact ? 2 : 4, most_cut, &cut);
     if (cut.tile >= 0 && cut.cost < (n > 1 ? BATCH_CUT_SEVERAL[f16 ? 0 : 1] : BATCH_CUT_ONE) * best.cost) best = cut;
   }
   *cost = best.cost;
