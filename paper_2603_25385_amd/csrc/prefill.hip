@@ -765,6 +765,10 @@ int prefill_k_slices(const glowq_unit& u) {
   for (int i = 0; i < u.n_modules; ++i)
     tiles += (((u.modules[i].d_out + 15) / 16 + tile_blocks - 1) / tile_blocks) * n_mtiles;
   if (tiles > 128) return 1;
+  // (one token tile, binary16: slices of at most 38 K tiles, since they are what such a launch ends with; us by layer,
+  // 4096 / 11008 at 70 / 100 / 128 tokens, in two slices and in three: 64.0, 77.4, 86.3 and 61.7, 69.8, 74.6.  bfloat16's
+  // dequantiser fills the compute units that the shorter slices would leave: 71.6 and 72.4 at 100 tokens)
+  if (u.T <= 128 && u.act_dtype == GLOWQ_F16) return std::min(4, (ktiles + 37) / 38);
   return std::min(4, ktiles / 32);
 }
 // fp32 slab of one slice: [T][ldp], ldp = d_out rounded up to 4 (16-byte stores)
