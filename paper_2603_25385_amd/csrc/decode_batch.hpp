@@ -596,10 +596,14 @@ size_t batch_slab_bytes(const glowq_unit& u) {
 // unit: beyond, they share what they were to have alone (26 tokens x 3 x 3112 rows x 5120 16.8 -> 20.5 us, 25 x 2 x 3816 x
 // 8448 18.5 -> 23.5).  One unit is cut where the estimate falls by 15 %, several where it falls by 10 % (binary16; with less
 // a layer of 4096 / 14336 at 16 tokens went from 31.9 to 34.1 us) or at all (bfloat16, whose uncut launches are estimated too
-// low: the same layer at 24 tokens 50.8 -> 39.4).  Measured over 310 calls of 5 to 32 tokens: 11 tokens x 1168
-// rows x 13568 16.2 -> 12.8 us, 23 x 4480 x 9984 22.9 -> 16.7, layers of 768 / 13056 at 31 tokens 34.1 -> 24.5, of
-// 512 / 7552 at 7 tokens (four) 22.7 -> 15.3; none that is cut by these rules was slower by more than calls differ.
+// low: the same layer at 24 tokens 50.8 -> 39.4).  A unit with a correction that is alone in its launch is cut from
+// 4096 rows and nine tokens on: a slice that waits for the projection of a long contraction ends no earlier than the whole
+// one, and the sum comes on top (64 single units, cold operands, us uncut and cut: 10 tokens x 3 x 192 rows x 9088 11.1 and
+// 13.4, 9 x 3 x 1280 x 13568 16.5 and 20.3, 6 x 2 x 2704 x 9984 14.4 and 15.5; 10 x 4768 x 11264 16.5 and 14.6,
+// 29 x 4336 x 8448 19.2 and 15.0, 19 x 2 x 2136 x 10880 24.5 and 19.8).  Layers of 768 / 13056 at 31 tokens 34.1 -> 24.5,
+// of 512 / 7552 at 7 tokens (four) 22.7 -> 15.3.
 constexpr float BATCH_SLICE_US = 4.0f, BATCH_CUT_ONE = 0.85f, BATCH_CUT_SEVERAL[2] = {0.9f, 1.0f};
+constexpr int BATCH_CUT_ONE_BLOCKS = 256, BATCH_CUT_ONE_T = 9;
 struct BatchSize {
   int blocks, kt, T, allowed;
 };
@@ -674,6 +678,7 @@ int choose_batch_tile(const glowq_unit* const* units, int n, float* cost, int* s
       most_cut = std::max(most_cut, sizes[k].allowed);
     }
   }
+  if (n == 1 && units[0]->r > 0 && (sizes[0].blocks < BATCH_CUT_ONE_BLOCKS || sizes[0].T < BATCH_CUT_ONE_T)) most_cut = 1;
   BatchChoice best = {-1, 1, 0.f};
   cheapest_batch_tile<0>(sizes, n, f16, exact ? 2 : 4, &best);
   if (most_cut > 1 && best.cost > 2.f * BATCH_SLICE_US) {

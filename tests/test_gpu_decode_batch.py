@@ -94,28 +94,38 @@ def test_units_of_one_call_share_a_launch(T):
         ws.assert_idle()
 
 
-# Contractions cut across workgroups: slices of unequal length, two and four of them, one K tile per wave group, ragged
-# row blocks that straddle modules, ragged token tiles; with the correction (the first slice's) and without
+# Contractions cut across workgroups: slices of unequal length, two to four of them, one K tile per wave group, ragged
+# row blocks that straddle modules, ragged token tiles; with the correction (the first slice's) and without; one unit
+# alone and two of a kind
 @pytest.mark.parametrize("act", ["f16", "bf16"])
-@pytest.mark.parametrize("T,d_in,d_outs", [(9, 13696, (1000, 600)), (11, 13568, (1168,)), (17, 14336, (40, 264, 96)),
-                                           (32, 14208, (4096,))])
-def test_contractions_cut_across_workgroups(T, d_in, d_outs, act):
+@pytest.mark.parametrize("T,d_in,d_outs,n", [(9, 13696, (1000, 600), 2), (11, 13568, (1168,), 2), (17, 14336, (40, 264, 96), 2),
+                                             (9, 13696, (2600, 1512), 1), (32, 14208, (4096,), 1)])
+def test_contractions_cut_across_workgroups(T, d_in, d_outs, n, act):
     u = recipe_unit(O, 1, 0, T, r=72, shape=UnitShape("g", d_in, d_outs), act=act, G=128, method="alg1", qr="none")
-    du = DeviceUnit(u)
-    slices = G.glowq_debug_route([du.desc])[0].k_slices
-    assert 2 <= slices <= 4 and G.glowq_debug_route([du.desc], False)[0].k_slices == 1
-    ws = Workspace([du.desc])
+    dus = [DeviceUnit(u) for _ in range(n)]
+    descs = [d.desc for d in dus]
+    assert all(2 <= r.k_slices <= 4 for r in G.glowq_debug_route(descs))
+    assert all(r.k_slices == 1 for r in G.glowq_debug_route(descs, False))
+    ws = Workspace(descs)
     for restore in (True, False):
         refs, first = O.group_forward(u, restore), None
         for _ in range(3):                  # the counts of the call before are in the workspace
-            du.clear()
-            G.glowq_group_forward(du.desc, restore, ws.ptr, ws.bytes, stream())
-            ys = du.outputs()
-            for y, ref in zip(ys, refs):
+            for d in dus:
+                d.clear()
+            G.glowq_block_forward(descs, bytes([restore] * n), ws.ptr, ws.bytes, stream())
+            ys = [y for d in dus for y in d.outputs()]
+            for y, ref in zip(ys, refs * n):
                 assert np.isfinite(y).all() and rel_err(y, ref) <= TOL + ULP[act]
             first = first or ys
             assert all(np.array_equal(a, b) for a, b in zip(first, ys))      # whichever slice comes last
             ws.assert_idle()
+
+
+# A unit with a correction alone in its launch is cut from 4096 rows and nine tokens on
+@pytest.mark.parametrize("T,rows,cut", [(9, 4096, True), (8, 4096, False), (9, 4080, False), (11, 1168, False)])
+def test_lone_units_are_cut_from_a_size_on(T, rows, cut):
+    u = recipe_unit(O, 1, 0, T, r=16, shape=UnitShape("g", 13568, (rows,)), act="bf16", G=128, method="alg1", qr="none")
+    assert (G.glowq_debug_route([DeviceUnit(u).desc])[0].k_slices > 1) == cut
 
 
 @pytest.mark.parametrize("act", ["f16", "bf16"])
@@ -140,7 +150,7 @@ def test_cut_and_whole_contractions_share_a_launch(act):
 
 
 def test_cut_contractions_in_a_graph():
-    u = recipe_unit(O, 1, 0, 11, r=64, shape=UnitShape("g", 13568, (1168,)), act="bf16", G=128, method="alg1", qr="none")
+    u = recipe_unit(O, 1, 0, 11, r=64, shape=UnitShape("g", 13568, (4176,)), act="bf16", G=128, method="alg1", qr="none")
     du = DeviceUnit(u)
     ws = Workspace([du.desc])
     assert G.glowq_debug_route([du.desc])[0].k_slices > 1
