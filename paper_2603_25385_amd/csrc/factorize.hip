@@ -23,6 +23,7 @@
 // results do not depend on timing.
 #include "common.hpp"
 #include "launch.hpp"
+#include "ranking.hpp"
 #include <algorithm>
 #include <utility>
 
@@ -1330,8 +1331,8 @@ __device__ inline bool last_of(int* counter, int n) {
   return last != 0;
 }
 
-// The singular values from the Gram matrix of orthogonal rows (its diagonal), their descending order (equal values: lower
-// row first), and P[i][jr] = U~[i][perm jr] sqrt(sigma_jr), the l x r matrix that takes Q to A (Alg. 1, lift and balance)
+// The singular values from the Gram matrix of orthogonal rows (its diagonal), their order (see
+// ranks_before), and P[i][jr] = U~[i][perm jr] sqrt(sigma_jr), the l x r matrix that takes Q to A (Alg. 1, lift and balance)
 __device__ inline void sort_and_lift(const PassArgs& a, const double* S, int LD) {
   __shared__ double sigma[FZ_SMALL];
   __shared__ int order[FZ_SMALL];
@@ -1339,10 +1340,7 @@ __device__ inline void sort_and_lift(const PassArgs& a, const double* S, int LD)
   if (t < a.l) {
     const double s = S[t * LD + t];
     int rank = 0;
-    for (int b = 0; b < a.l; ++b) {
-      const double o = S[b * LD + b];
-      rank += (o > s || (o == s && b < t)) ? 1 : 0;
-    }
+    for (int b = 0; b < a.l; ++b) rank += ranks_before(S[b * LD + b], b, s, t) ? 1 : 0;
     const double sg = sqrt(s);
     sigma[rank] = sg;
     order[rank] = t;
@@ -1556,16 +1554,13 @@ __global__ void __launch_bounds__(256) k_row_norms(const double* __restrict__ Bs
   if (threadIdx.x == 0) sig2[blockIdx.x] = s;
 }
 
-// descending order of the singular values (equal values: lower row first); one block
+// order of the singular values (see ranks_before); one block
 __global__ void __launch_bounds__(256) k_sort_sigma(const double* sig2, int l, double* sigma_sorted, int* perm) {
   const int a = threadIdx.x;
   if (a >= l) return;
   const double s = sig2[a];
   int rank = 0;
-  for (int b = 0; b < l; ++b) {
-    const double o = sig2[b];
-    rank += (o > s || (o == s && b < a)) ? 1 : 0;
-  }
+  for (int b = 0; b < l; ++b) rank += ranks_before(sig2[b], b, s, a) ? 1 : 0;
   sigma_sorted[rank] = sqrt(s);
   perm[rank] = a;
 }

@@ -271,3 +271,17 @@ def test_equal_singular_values(p):
     A = O.bits_to_f64(np.concatenate(A_bits, axis=0), "f16")
     B = O.bits_to_f64(B_bits, "f16")
     assert np.linalg.norm(E - A @ B, "fro") <= 2e-3 * np.linalg.norm(E, "fro")   # 2^-11 per factor
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("r,p", [(16, 8), (80, 8), (128, 8)])
+def test_weights_that_are_not_finite(r, p, bad):
+    # every singular value comes out NaN: their order still has to be one (it indexes rows and columns).  The three
+    # sketches end in three places: eigenvectors refused, rotations, a launch per round
+    shape = UnitShape("g", 256, (96, 136))
+    u, W = make_unit(shape, "f16", 128, seed=28)
+    W[1] = np.array(W[1], np.float32)
+    W[1][77, 130] = bad
+    Omega = np.random.default_rng(29).standard_normal((shape.d_in, r + p))
+    A, B, sig = gpu_factors(u, W, r, p, 1, Omega)
+    assert np.isnan(sig).all() and (B == 0).all()

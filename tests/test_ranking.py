@@ -1,0 +1,46 @@
+"""The order of the singular values is a permutation for any values (host build of the library's own rule)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+MAIN = r"""
+#include <hip/hip_runtime.h>
+#include <cmath>
+#include <cstdio>
+#include "ranking.hpp"
+int main() {
+  const double values[] = {NAN, INFINITY, 2.0, 0.0, -0.0, -NAN, -INFINITY};
+  enum { N = 5, V = sizeof values / sizeof *values };
+  int total = 1, bad = 0;
+  for (int i = 0; i < N; ++i) total *= V;
+  for (int code = 0; code < total; ++code) {           // every list of N of the values
+    double s[N], sorted[N];
+    bool seen[N] = {};
+    for (int i = 0, c = code; i < N; ++i, c /= V) s[i] = values[c % V];
+    for (int a = 0; a < N; ++a) {
+      int rank = 0;
+      for (int b = 0; b < N; ++b) rank += glowq::ranks_before(s[b], b, s[a], a) ? 1 : 0;
+      if (rank >= N || seen[rank]) { ++bad; continue; }
+      seen[rank] = true;
+      sorted[rank] = s[a];
+    }
+    for (int i = 0; i + 1 < N && !bad; ++i)            // descending, NaN behind all numbers
+      bad += std::isnan(sorted[i]) ? !std::isnan(sorted[i + 1]) : sorted[i] < sorted[i + 1];
+  }
+  printf("%d of %d lists out of order\n", bad, total);
+  return bad != 0;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not available")
+def test_ranks_are_a_permutation(tmp_path):
+    src, exe = tmp_path / "ranking.hip", str(tmp_path / "ranking")
+    src.write_text(MAIN)
+    subprocess.run(["hipcc", "--offload-arch=gfx950", "-O1", "-std=c++17", "-I" + os.path.join(ROOT, "paper_2603_25385_amd", "csrc"),
+                    str(src), "-o", exe], check=True, capture_output=True)
+    p = subprocess.run([exe], capture_output=True, text=True)
+    assert p.returncode == 0, p.stdout + p.stderr
