@@ -152,8 +152,17 @@ glowq_status glowq_prepare_weights(const uint32_t* wq, const uint16_t* scales,
  * shapes ask for is refused with GLOWQ_ERR_WORKSPACE.  Calls without a workspace
  * (no unit restored) and glowq_group_forward_static multiply such a unit in one piece.
  *
+ * A call of 5 to 32 tokens cuts long contractions on few rows as well, where the pieces of a
+ * launch fit the chip (glowq_debug_route tells).  Their partial results lie behind the slices of
+ * all units, in a room that the launches of a call share (8 MB at most; none for most calls).
+ * glowq_workspace_bytes counts it, from descriptors with modules.  The room is not required: a
+ * workspace that holds the slices serves the call, with whole contractions where the room is too
+ * small.  Up to 64 tokens the slices do not get smaller as tokens are added, so a workspace that is
+ * made for the most tokens serves all calls of the same units with fewer (from five on).
+ *
  * Unit i's slice starts at the sum of glowq_workspace_bytes of the units before it
- * (in the order of the forward call).  Word 3 of a slice (byte offset 12) is the
+ * (in the order of the forward call), each alone and, up to 64 tokens, without its modules: the room
+ * for partial results is not part of a slice.  Word 3 of a slice (byte offset 12) is the
  * unit's status word: nonzero means that a bounded in-kernel wait for the projection
  * expired and the correction R A_i^T of that unit was LEFT OUT of Y (the output then
  * equals that of a unit that is not restored).  The producers of R lead their launch
@@ -220,8 +229,8 @@ glowq_status glowq_block_forward(const glowq_unit* units, int32_t n_units,
  * unit of its own and forwards all of them as one block, so launches are shared as
  * in glowq_block_forward, and only the projections and the reads of B multiply.
  * Every unit needs r > 0; all units are corrected (no restore mask).  The workspace
- * holds one slice per module, in the same order, each as long as
- * glowq_workspace_bytes of that one-module unit: size it with
+ * holds one slice per module, in the same order, each as long as that of a unit with this one
+ * module, and the room behind them: size it with
  * glowq_layerwise_workspace_bytes, zero it with glowq_workspace_init.  Status words:
  * word 3 of each slice, as described above. */
 glowq_status glowq_layerwise_workspace_bytes(const glowq_unit* units, int32_t n_units,

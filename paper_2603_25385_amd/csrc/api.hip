@@ -2,6 +2,7 @@
 // argument checks, workspace planning and dispatch to the HIP kernels.  Nothing in
 // this file allocates, synchronises or keeps state.
 #include <algorithm>
+#include <cstdint>
 #include <mutex>
 #include <vector>
 #include "common.hpp"
@@ -79,7 +80,7 @@ UnitWorkspace plan_unit_workspace(const glowq_unit& u, char* base) {
   w.off_r16 = align_up(w.off_rpart + rpart, 256);
   size_t r16 = (u.r > 0) ? (size_t)u.T * u.r * (u.T <= BATCH_MAX_T ? 4 : 2) : 0;
   w.off_splitk = align_up(w.off_r16 + r16, 256);
-  w.splitk_bytes = is_decode(u.T) ? batch_slab_bytes(u) : prefill_splitk_bytes(u);
+  w.splitk_bytes = is_decode(u.T) ? 0 : prefill_splitk_bytes(u);
   w.bytes = align_up(w.off_splitk + w.splitk_bytes, 256);
   return w;
 }
@@ -151,8 +152,10 @@ struct LaunchChoice {
   int n;                           // units
   int tile;                        // batched: the workgroup tile; tiled: PF_TILE_...
   int slices[MAX_LAUNCH_UNITS];    // K slices of every unit
+  size_t room;                     // bytes for partial results behind the units' workspace slices
 };
-static LaunchChoice choose_launch(const glowq_unit* units, int n_units, bool slabs) {
+// slabs: the units' workspace slices hold the slabs of K slices; room: bytes behind all slices
+static LaunchChoice choose_launch(const glowq_unit* units, int n_units, bool slabs, size_t room) {
   LaunchChoice c = {};
   const glowq_unit* batch[MAX_LAUNCH_UNITS];
   for (int& s : c.slices) s = 1;
@@ -166,7 +169,15 @@ static LaunchChoice choose_launch(const glowq_unit* units, int n_units, bool sla
       ++c.n;
     }
     c.kernel = few ? GLOWQ_ROUTE_FEW : GLOWQ_ROUTE_BATCHED;
-    if (!few) c.tile = choose_batch_tile(batch, c.n, &cost, slabs ? c.slices : nullptr);
+    if (!few) {
+      c.tile = choose_batch_tile(batch, c.n, &cost, room ? c.slices : nullptr);
+      c.room = batch_slab_bytes(batch, c.n, c.tile, c.slices);
+      if (c.room > room) {         // whole contractions then, as without any
+        for (int& s : c.slices) s = 1;
+        c.room = 0;
+        c.tile = choose_batch_tile(batch, c.n, &cost, nullptr);
+      }
+    }
     return c;
   }
   const int most = std::min(std::min(MAX_LAUNCH_UNITS, n_units), std::min(prefill_max_units(), batch_max_units()));
@@ -196,12 +207,30 @@ static LaunchChoice choose_launch(const glowq_unit* units, int n_units, bool sla
   return c;
 }
 
-// Enqueue all units, launch by launch.  slabs: the workspace holds the slabs of K slices.
+// What the launches of a call take behind the units' workspace slices (no more than one of them at a time)
+static size_t batch_room(const glowq_unit* units, int n_units) {
+  size_t room = 0;
+  for (int i = 0; i < n_units; ++i)
+    if (!units[i].modules) return 0;
+  for (int i = 0; i < n_units;) {
+    if (units[i].T <= 4 || !is_decode(units[i].T)) {
+      ++i;
+      continue;
+    }
+    const LaunchChoice c = choose_launch(units + i, n_units - i, false, SIZE_MAX);
+    room = std::max(room, c.room);
+    i += c.n;
+  }
+  return room;
+}
+
+// Enqueue all units, launch by launch.  slabs: the units' workspace slices hold the slabs of K slices; room: bytes
+// behind all slices, which every launch may use (they run one behind the other).
 static glowq_status forward_all(const glowq_unit* units, int n_units, const uint8_t* mask,
-                                char* workspace, bool slabs, hipStream_t st) {
+                                char* workspace, bool slabs, char* behind, size_t room, hipStream_t st) {
   size_t off = 0;
   for (int i = 0; i < n_units;) {
-    const LaunchChoice c = choose_launch(units + i, n_units - i, slabs);
+    const LaunchChoice c = choose_launch(units + i, n_units - i, slabs, room);
     const glowq_unit* batch[MAX_LAUNCH_UNITS];
     UnitWorkspace ws[MAX_LAUNCH_UNITS];
     bool corr[MAX_LAUNCH_UNITS];
@@ -213,7 +242,7 @@ static glowq_status forward_all(const glowq_unit* units, int n_units, const uint
       if (c.kernel == GLOWQ_ROUTE_BATCHED && !is_decode(units[i].T)) plan_batch_projection(*batch[k], ws[k]);
     }
     const hipError_t e = c.kernel == GLOWQ_ROUTE_FEW       ? launch_decode_multi(batch, ws, corr, c.n, st)
-                         : c.kernel == GLOWQ_ROUTE_BATCHED ? launch_decode_batch(batch, ws, corr, c.n, c.tile, c.slices, st)
+                         : c.kernel == GLOWQ_ROUTE_BATCHED ? launch_decode_batch(batch, ws, corr, c.n, c.tile, c.slices, behind, st)
                                                            : launch_prefill_multi(batch, ws, corr, c.n, c.tile, c.slices, st);
     if (e != hipSuccess) return hip_status(e);
   }
@@ -275,7 +304,7 @@ glowq_status glowq_workspace_bytes(const glowq_unit* units, int32_t n_units, siz
     if (s != GLOWQ_OK) return s;
     total += plan_unit_workspace(units[i], nullptr).bytes;
   }
-  *bytes = total;
+  *bytes = total + batch_room(units, n_units);
   return GLOWQ_OK;
 }
 
@@ -340,7 +369,7 @@ glowq_status glowq_group_forward_static(const glowq_unit* u, int32_t restore, vo
   glowq_status s = validate(u, true, corrected);
   if (s != GLOWQ_OK) return s;
   uint8_t mask = restore ? 1 : 0;
-  if (!corrected) return forward_all(u, 1, &mask, nullptr, false, (hipStream_t)stream);
+  if (!corrected) return forward_all(u, 1, &mask, nullptr, false, nullptr, 0, (hipStream_t)stream);
   // (the static array holds the projection's words; a long contraction is not cut here)
   const UnitWorkspace plan = plan_unit_workspace(*u, nullptr);
   if (plan.off_splitk > (size_t)GLOWQ_STATIC_SCRATCH_BYTES) return GLOWQ_ERR_WORKSPACE;
@@ -352,7 +381,7 @@ glowq_status glowq_group_forward_static(const glowq_unit* u, int32_t restore, vo
   // node, so that the call can be captured into a graph)
   e = launch_fill_zero(scratch, plan.ctl_bytes, (hipStream_t)stream);
   if (e != hipSuccess) return hip_status(e);
-  return forward_all(u, 1, &mask, (char*)scratch, false, (hipStream_t)stream);
+  return forward_all(u, 1, &mask, (char*)scratch, false, nullptr, 0, (hipStream_t)stream);
 }
 
 glowq_status glowq_block_forward(const glowq_unit* units, int32_t n_units,
@@ -377,7 +406,8 @@ glowq_status glowq_block_forward(const glowq_unit* units, int32_t n_units,
   }
   // (with no unit restored the workspace may be absent or of any size)
   const bool whole = workspace && workspace_bytes >= need && !misaligned(workspace);
-  return forward_all(units, n_units, restore_mask, whole ? (char*)workspace : nullptr, whole, (hipStream_t)stream);
+  return forward_all(units, n_units, restore_mask, whole ? (char*)workspace : nullptr, whole,
+                     whole ? (char*)workspace + need : nullptr, whole ? workspace_bytes - need : 0, (hipStream_t)stream);
 }
 
 // Every module of the units as a one-module unit, module j (counted over all units) with
@@ -582,7 +612,7 @@ static glowq_status debug_route(const glowq_unit* units, int32_t n_units, int32_
     if (!units[i].modules) return GLOWQ_ERR_NULL;
   }
   for (int i = 0, launch = 0; i < n_units; ++launch) {
-    const LaunchChoice c = choose_launch(units + i, n_units - i, slabs != 0);
+    const LaunchChoice c = choose_launch(units + i, n_units - i, slabs != 0, slabs ? SIZE_MAX : 0);
     const bool tiled = c.kernel == GLOWQ_ROUTE_TILED, wide = tiled && c.tile == PF_TILE_WIDE;
     for (int k = 0; k < c.n; ++k, ++i) {
       if (routes)

@@ -56,7 +56,7 @@ struct BatchUnit {
   int T, K, r, n_modules;
   int n_blocks;                // 16-row blocks of the unit
   int n_groups, n_ttiles;      // its tiles: groups of row blocks x tiles of 16 MB tokens
-  int ks;                      // K slices: as many workgroups per tile (see plan_batch_slices)
+  int ks;                      // K slices: as many workgroups per tile (see choose_batch_tile)
   uint32_t* count;             // ks > 1: per tile, slices that are done; their partial results
   u32x4_t* slab;               // [slice][tile][row wave][row block][token block][lane]
   int restore, out_f32;        // restore 2: the consumers add the projection's slices (see plan_batch_projection)
@@ -563,10 +563,9 @@ constexpr int BATCH_RESIDENT[] = {batch_tile_resident<0>(), batch_tile_resident<
 static_assert(sizeof(BATCH_RESIDENT) / sizeof(int) == BATCH_N_TILES, "one entry per tile");
 
 // K slices across workgroups, for a long contraction on few rows: its tiles run on while the rest of the chip
-// idles (24 tokens x 4096 rows x 14336: 64 workgroups of 56 stages).  What a unit's own shapes allow, so that its
-// workspace can be planned: 32 K tiles and more, at least eight a slice, at most four slices and no more than about a thousand workgroups
-// on tiles of 64 rows x 32 tokens.  Up to 32 tokens: a slice of 64 x 4096 results is a megabyte, more than the
-// rest of such a call's workspace.
+// idles (24 tokens x 4096 rows x 14336: 64 workgroups of 56 stages).  What a unit's own shapes allow: 32 K tiles and
+// more, at least eight a slice, at most four slices and no more than about a thousand workgroups on tiles of 64 rows x
+// 32 tokens.  Up to 32 tokens: a slice of 64 x 4096 results is a megabyte, out to memory and back.
 constexpr int BATCH_SLICED_T = 32;
 static int unit_row_blocks(const glowq_unit& u) {
   int blocks = 0;
@@ -579,13 +578,21 @@ static int batch_slices_allowed(const glowq_unit& u) {
   if (wgs == 0 || wgs > 512) return 1;
   return std::min(std::min(BATCH_MAX_SLICES, u.d_in / 1024), 1024 / wgs);
 }
-// words of the counts (a tile has at least one row block and 16 tokens), and bytes with the slabs (whole tiles of at most 128
-// rows, and of the tokens of the widest tile that such a call takes)
-static size_t batch_count_words(const glowq_unit& u) { return ((size_t)unit_row_blocks(u) * ((u.T + 15) / 16) + 63) / 64 * 64; }
-size_t batch_slab_bytes(const glowq_unit& u) {
-  const int S = batch_slices_allowed(u);
-  if (S <= 1) return 0;
-  return batch_count_words(u) * 4 + (size_t)S * ((unit_row_blocks(u) + 7) / 8 * 128) * 64 * 4;
+// A cut unit's place in the launch's room for partial results: a count per tile, then the slabs.  The room is what the
+// launch takes and not what its units might (a launch whose pieces do not fit the chip is not cut), and the launches of
+// a call, one behind the other on the stream, use the same: at most 256 pieces of 32 KB.  (As a part of every unit's
+// slice, by its own shapes, it was 1.6 GB of a stack of 40 layers of 5120 / 13824 at 8 tokens, where nothing is cut.)
+static inline int batch_tiles(const glowq_unit& u, const BatchTile& t) {
+  return ((unit_row_blocks(u) + t.rb * t.rw - 1) / (t.rb * t.rw)) * ((u.T + 16 * t.mb - 1) / (16 * t.mb));
+}
+static inline size_t batch_count_bytes(const glowq_unit& u, const BatchTile& t) { return ((size_t)batch_tiles(u, t) * 4 + 255) / 256 * 256; }
+static inline size_t batch_unit_slab_bytes(const glowq_unit& u, const BatchTile& t, int ks) {
+  return ks == 1 ? 0 : batch_count_bytes(u, t) + (size_t)ks * batch_tiles(u, t) * (t.rw * t.rb * t.mb * 1024);
+}
+size_t batch_slab_bytes(const glowq_unit* const* units, int n, int tile, const int* slices) {
+  size_t bytes = 0;
+  for (int k = 0; k < n; ++k) bytes += batch_unit_slab_bytes(*units[k], BATCH_TILES[tile], slices[k]);
+  return bytes;
 }
 
 // What the tiles from I on cost for units of `blocks` row blocks, `kt` K tiles and T tokens, of which `allowed` K slices
@@ -757,8 +764,9 @@ static void launch_batch_types(const BatchArgs<NB>& b, int ti, int mb, int wg, b
 
 template <int NB>
 static hipError_t launch_batch(const glowq_unit* const* units, const UnitWorkspace* ws, const bool* restore, int n,
-                               int ti, const int* slices, hipStream_t st) {
+                               int ti, const int* slices, char* slabs, hipStream_t st) {
   BatchArgs<NB> b;
+  const BatchTile tile = BATCH_TILES[ti];
   // longest contraction first: the hardware starts workgroups in index order
   int order[NB];
   for (int i = 0; i < n; ++i) order[i] = i;
@@ -789,8 +797,9 @@ static hipError_t launch_batch(const glowq_unit* const* units, const UnitWorkspa
     bu.ks = slices[order[oi]];
     bu.count = nullptr; bu.slab = nullptr;
     if (bu.ks > 1) {
-      bu.count = (uint32_t*)(w.base + w.off_splitk);
-      bu.slab = (u32x4_t*)(bu.count + batch_count_words(u));
+      bu.count = (uint32_t*)slabs;
+      bu.slab = (u32x4_t*)(slabs + batch_count_bytes(u, tile));
+      slabs += batch_unit_slab_bytes(u, tile, bu.ks);
     }
     bu.ksplit = w.ksplit; bu.kslice = w.kslice;
     bu.prod_start = n_prod;
@@ -803,7 +812,6 @@ static hipError_t launch_batch(const glowq_unit* const* units, const UnitWorkspa
       n_prod += bu.n_prod;
     }
   }
-  const BatchTile tile = BATCH_TILES[ti];
   bool cut = false;
   for (int i = 0; i < n; ++i) cut = cut || slices[i] > 1;
   const int mb = cut ? tile.mb : batch_token_blocks(units, n, ti);
@@ -824,11 +832,11 @@ static hipError_t launch_batch(const glowq_unit* const* units, const UnitWorkspa
   return hipGetLastError();
 }
 
-// units[i] uses workspace slice ws[i]; all of them pass batch_compatible with units[0]
+// units[i] uses workspace slice ws[i]; all of them pass batch_compatible with units[0].  slabs: batch_slab_bytes of them
 hipError_t launch_decode_batch(const glowq_unit* const* units, const UnitWorkspace* ws, const bool* restore, int n,
-                               int tile, const int* slices, hipStream_t st) {
-  if (n == 1) return launch_batch<1>(units, ws, restore, n, tile, slices, st);
-  return launch_batch<BATCH_MAX_UNITS>(units, ws, restore, n, tile, slices, st);
+                               int tile, const int* slices, char* slabs, hipStream_t st) {
+  if (n == 1) return launch_batch<1>(units, ws, restore, n, tile, slices, slabs, st);
+  return launch_batch<BATCH_MAX_UNITS>(units, ws, restore, n, tile, slices, slabs, st);
 }
 
 }  // namespace glowq

@@ -17,8 +17,7 @@ struct UnitWorkspace {
                       // kernel, glowq_shared_proj)
   size_t off_r16;     // R in the activation type: 8-byte slots {two ranks, launch tag}, [T][r / 2]
                       // (batched kernel); [T][r] (tiled kernel)
-  size_t off_splitk;  // T > 4: fp32 slabs of a long contraction cut into K slices (0 bytes if not cut), of the batched
-                      // kernel (behind their counts) or the tiled one
+  size_t off_splitk;  // T > 64: fp32 slabs of a long contraction cut into K slices (0 bytes if not cut)
   size_t splitk_bytes;
   size_t ctl_bytes;   // leading bytes that must be zero between calls
   int ksplit;         // K slices of the projection
@@ -104,15 +103,16 @@ hipError_t launch_decode_multi(const glowq_unit* const* units, const UnitWorkspa
 // many tokens (the workspace of a unit holds the slots up to here)
 constexpr int BATCH_MAX_T = 2048;
 void plan_batch_projection(const glowq_unit& u, UnitWorkspace& w);
-// the workgroup tile for these units in one launch, what it is taken to cost and, where the workspace has their slabs
-// (else NULL), the K slices of every unit
+// the workgroup tile for these units in one launch, what it is taken to cost and, where contractions may be cut (else
+// NULL), the K slices of every unit; then the bytes behind the units' workspace slices that such a launch keeps its
+// partial results in
 int choose_batch_tile(const glowq_unit* const* units, int n, float* cost, int* slices);
 int batch_wait_polls();
 bool batch_compatible(const glowq_unit& a, const glowq_unit& b);
 int batch_max_units();
-size_t batch_slab_bytes(const glowq_unit& u);
-hipError_t launch_decode_batch(const glowq_unit* const* units, const UnitWorkspace* ws,
-                               const bool* restore, int n, int tile, const int* slices, hipStream_t st);
+size_t batch_slab_bytes(const glowq_unit* const* units, int n, int tile, const int* slices);
+hipError_t launch_decode_batch(const glowq_unit* const* units, const UnitWorkspace* ws, const bool* restore, int n,
+                               int tile, const int* slices, char* slabs, hipStream_t st);
 // The other calls of T > 64: tiled matrix-core GEMM, correction folded in as an extra K slab.
 // One launch covers several compatible units (same types and group size).
 bool prefill_compatible(const glowq_unit& a, const glowq_unit& b);

@@ -283,3 +283,43 @@ def test_matrix_probe_runs_the_loop_that_was_asked_for(kind, monkeypatch):
     monkeypatch.setattr("paper_2603_25385_amd.binding._lib", Library)
     G.glowq_probe_mfma(5, kind, 2, 0x1000)
     assert seen == [(5, int(kind), 2)]
+
+
+def _stack(hidden, kv, inter, layers, T, r, act=None):
+    shapes = [(hidden, [hidden, kv, kv]), (hidden, [hidden]), (hidden, [inter, inter]), (inter, [hidden])] * layers
+    return [G.make_unit(0, 0, [G.make_module(0, 0, 0, o, o) for o in outs], T, d, r, 128, act, act) for d, outs in shapes]
+
+
+def _bare(units):
+    """The same without modules."""
+    out = []
+    for u in units:
+        v = type(u).from_buffer_copy(u)
+        v.modules = None
+        out.append(v)
+    return out
+
+
+@pytest.mark.parametrize("act", [G.GLOWQ_F16, G.GLOWQ_BF16])
+@pytest.mark.parametrize("hidden,kv,inter,layers", [(4096, 4096, 11008, 32), (4096, 1024, 14336, 32), (5120, 5120, 13824, 40),
+                                                    (4096, 1024, 14336, 1), (512, 512, 7552, 4)])
+def test_workspace_of_calls_that_may_be_cut(hidden, kv, inter, layers, act):
+    """Partial results of up to 32 tokens lie behind the slices, as much as the call's largest launch takes: none where
+    nothing is cut.  The slices alone, which a call has to have, grow with the tokens up to 64."""
+    last = 0
+    for T in (5, 8, 9, 16, 17, 24, 32, 33, 48, 64):
+        units = _stack(hidden, kv, inter, layers, T, 128, act)
+        need, slices = G.glowq_workspace_bytes(units), G.glowq_workspace_bytes(_bare(units))
+        assert slices == sum(G.glowq_workspace_bytes(_bare([u])) for u in units)
+        cut = any(r.k_slices > 1 for r in G.glowq_debug_route(units))
+        assert slices < need <= slices + (8 << 20) + 4096 if cut else need == slices
+        assert not cut or layers <= 4
+        assert slices >= last
+        last = slices
+    eight = _stack(5120, 5120, 13824, 40, 8, 128, act)
+    assert G.glowq_workspace_bytes(eight) < 20 << 20
+
+
+def test_workspace_of_one_unit_that_is_never_cut():
+    u = _stack(4096, 1024, 14336, 1, 8, 128, G.GLOWQ_F16)[2]            # gate and up
+    assert G.glowq_workspace_bytes([u]) == G.glowq_workspace_bytes(_bare([u]))

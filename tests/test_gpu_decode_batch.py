@@ -167,6 +167,49 @@ def test_cut_contractions_in_a_graph():
             assert rel_err(y, ref) <= TOL + ULP["bf16"]
 
 
+# The room for the slices' partial results lies behind the units' slices of the workspace and is not required
+@pytest.mark.parametrize("act", ["f16", "bf16"])
+@pytest.mark.parametrize("T,d_in,d_outs,n", [(24, 14208, (4096,), 1), (9, 13696, (1000, 600), 2)])
+def test_room_for_partial_results_is_optional(T, d_in, d_outs, n, act):
+    u = recipe_unit(O, 1, 0, T, r=72, shape=UnitShape("g", d_in, d_outs), act=act, G=128, method="alg1", qr="none")
+    dus = [DeviceUnit(u) for _ in range(n)]
+    descs = [d.desc for d in dus]
+    need, slices = G.glowq_workspace_bytes(descs), 0
+    for d in descs:
+        bare = G.glowq_unit.from_buffer_copy(d)
+        bare.modules = None
+        slices += G.glowq_workspace_bytes([bare])
+    assert need > slices and all(r.k_slices > 1 for r in G.glowq_debug_route(descs))
+    refs, failed = O.group_forward(u, True), torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    for nbytes, cut in ((need, True), (need - 256, False), (slices, False), (need, True)):
+        buf = torch.zeros(need + 4096, dtype=torch.uint8, device="cuda")
+        buf[slices:] = 0xA5
+        for _ in range(2):
+            for d in dus:
+                d.clear()
+            G.glowq_block_forward(descs, bytes([1] * n), buf.data_ptr(), nbytes, stream())
+            for y, ref in zip([y for d in dus for y in d.outputs()], refs * n):
+                assert np.isfinite(y).all() and rel_err(y, ref) <= TOL + ULP[act]
+        G.glowq_workspace_status(descs, buf.data_ptr(), nbytes, failed.data_ptr(), stream())
+        torch.cuda.synchronize()
+        assert int(failed.item()) == 0
+        assert bool((buf[slices:need] != 0xA5).any()) == cut and bool((buf[need:] == 0xA5).all())
+    with pytest.raises(G.GlowqError) as e:
+        G.glowq_block_forward(descs, bytes([1] * n), buf.data_ptr(), slices - 1, stream())
+    assert e.value.status == G.GLOWQ_ERR_WORKSPACE
+
+
+def test_a_workspace_for_64_tokens_serves_fewer():
+    u = recipe_unit(O, 1, 0, 64, r=72, shape=UnitShape("g", 14208, (4096,)), act="bf16", G=128, method="alg1", qr="none")
+    du = DeviceUnit(u)
+    ws = Workspace([du.desc])
+    for T in (64, 32, 24, 11, 5):
+        du.clear()
+        G.glowq_group_forward(du.describe(T=T), True, ws.ptr, ws.bytes, stream())
+        for y, ref in zip(du.outputs(T), O.group_forward(dict(u, X=u["X"][:T]), True)):
+            assert rel_err(y, ref) <= TOL + ULP["bf16"]
+
+
 # Tiles of 64 tokens that hold 48 of them: the last call that fits and the first that does not, in one, two and three token tiles
 @pytest.mark.parametrize("T,d_in,d_outs,act,tile", [
     (48, 2688, (12008,), "f16", 5), (49, 2688, (10008,), "f16", 5), (96, 2688, (6008,), "f16", 5), (97, 2688, (6008,), "f16", 5),
