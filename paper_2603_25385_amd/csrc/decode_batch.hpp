@@ -33,6 +33,7 @@
 // moved 98 KB of device-scope loads per workgroup; a small R is gathered that way all the same, see
 // plan_batch_projection.)
 #pragma once
+#include "arrivals.hpp"
 #include "common.hpp"
 #include "decode_device.hpp"
 #include "proj_device.hpp"
@@ -43,6 +44,7 @@ namespace glowq {
 
 constexpr int BATCH_MAX_UNITS = 16;
 constexpr int BATCH_MAX_SLICES = 4;      // of K, across workgroups
+static_assert(BATCH_MAX_SLICES < 1 << ARRIVAL_BITS, "a count of slices");
 constexpr int BATCH_QUICK_POLLS = 64;    // looks at R with hardly a pause in between
 constexpr int BATCH_WB = 1024 + 256;      // bytes per wave and K tile: one record's words, its (s, z) words
 
@@ -57,7 +59,7 @@ struct BatchUnit {
   int n_blocks;                // 16-row blocks of the unit
   int n_groups, n_ttiles;      // its tiles: groups of row blocks x tiles of 16 MB tokens
   int ks;                      // K slices: as many workgroups per tile (see choose_batch_tile)
-  uint32_t* count;             // ks > 1: per tile, slices that are done; their partial results
+  unsigned long long* count;   // ks > 1: per tile, slices that are done (see arrivals.hpp); their partial results
   u32x4_t* slab;               // [slice][tile][row wave][row block][token block][lane]
   int restore, out_f32;        // restore 2: the consumers add the projection's slices (see plan_batch_projection)
   int ksplit, kslice;          // K slices of the projection
@@ -423,7 +425,7 @@ __global__ void __launch_bounds__(NW * 64, (BatchShape<MB, RB, RW, NW>::WAVES_EU
   }
   if (CUT && ks > 1) {
     // The slice's sums go past the L2s to the unit's slab and the workgroup is counted (the word carries the
-    // launch's tag, as a projection tile's does); whoever finds all others counted adds the slices in their order.
+    // launch's tag); whoever finds all others counted adds the slices in their order.
     constexpr int PIECES = RW * RB * MB * 64;
     u32x4_t* mine = u.slab + (size_t)tile * PIECES + rw * (RB * MB * 64) + lane;
     const size_t step = (size_t)n_tiles * PIECES;
@@ -433,14 +435,14 @@ __global__ void __launch_bounds__(NW * 64, (BatchShape<MB, RB, RW, NW>::WAVES_EU
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) store16_device(mine + sl * step + (b_ * MB + mb) * 64, __builtin_bit_cast(u32x4_t, acc[b_][mb]));
     }
-    uint32_t* word = u.count + tile;
-    uint32_t seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // (on its way with the stores)
+    unsigned long long* word = u.count + tile;
+    unsigned long long seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // (on its way with the stores)
     vm_wait<0>();
     __syncthreads();
     if (threadIdx.x == 0) {
-      const uint32_t key = (uint32_t)(launch_tag() >> 1) << 4;
+      const unsigned long long key = arrival_key(launch_tag());
       uint32_t done;
-      do done = (seen & ~15u) == key ? seen & 15u : 0u;      // (at most ks rounds: a failure is another slice's success)
+      do done = arrivals(seen, key);                         // (at most ks rounds: a failure is another slice's success)
       while (!__hip_atomic_compare_exchange_strong(word, &seen, key | (done + 1u), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                    __HIP_MEMORY_SCOPE_AGENT));
       flag = done;
@@ -585,7 +587,7 @@ static int batch_slices_allowed(const glowq_unit& u) {
 static inline int batch_tiles(const glowq_unit& u, const BatchTile& t) {
   return ((unit_row_blocks(u) + t.rb * t.rw - 1) / (t.rb * t.rw)) * ((u.T + 16 * t.mb - 1) / (16 * t.mb));
 }
-static inline size_t batch_count_bytes(const glowq_unit& u, const BatchTile& t) { return ((size_t)batch_tiles(u, t) * 4 + 255) / 256 * 256; }
+static inline size_t batch_count_bytes(const glowq_unit& u, const BatchTile& t) { return ((size_t)batch_tiles(u, t) * 8 + 255) / 256 * 256; }
 static inline size_t batch_unit_slab_bytes(const glowq_unit& u, const BatchTile& t, int ks) {
   return ks == 1 ? 0 : batch_count_bytes(u, t) + (size_t)ks * batch_tiles(u, t) * (t.rw * t.rb * t.mb * 1024);
 }
@@ -797,7 +799,7 @@ static hipError_t launch_batch(const glowq_unit* const* units, const UnitWorkspa
     bu.ks = slices[order[oi]];
     bu.count = nullptr; bu.slab = nullptr;
     if (bu.ks > 1) {
-      bu.count = (uint32_t*)slabs;
+      bu.count = (unsigned long long*)slabs;
       bu.slab = (u32x4_t*)(slabs + batch_count_bytes(u, tile));
       slabs += batch_unit_slab_bytes(u, tile, bu.ks);
     }

@@ -1,4 +1,5 @@
-"""The order of the singular values is a permutation for any values (host build of the library's own rule)."""
+"""Rules of device code that a host build can run: the order of the singular values is a permutation for any
+values, and a word that another launch or other data left behind is no count."""
 import os
 import shutil
 import subprocess
@@ -6,7 +7,7 @@ import subprocess
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-MAIN = r"""
+RANKING = r"""
 #include <hip/hip_runtime.h>
 #include <cmath>
 #include <cstdio>
@@ -34,12 +35,29 @@ int main() {
   return bad != 0;
 }
 """
+ARRIVALS = r"""
+#include <hip/hip_runtime.h>
+#include <cstdio>
+#include "arrivals.hpp"
+int main() {
+  const unsigned long long tag = 0x0123456789abcdefull, key = glowq::arrival_key(tag);
+  int bad = 0;
+  for (unsigned n = 0; n < 1u << glowq::ARRIVAL_BITS; ++n) {
+    bad += glowq::arrivals(key | n, key) != n;
+    for (int bit = glowq::ARRIVAL_BITS; bit < 64; ++bit) bad += glowq::arrivals((key | n) ^ 1ull << bit, key) != 0;
+    for (unsigned other = 2; other < 64; other += 2) bad += glowq::arrivals(glowq::arrival_key(tag + other) | n, key) != 0;
+  }
+  printf("%d words misread\n", bad);
+  return bad != 0;
+}
+"""
 
 
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not available")
-def test_ranks_are_a_permutation(tmp_path):
-    src, exe = tmp_path / "ranking.hip", str(tmp_path / "ranking")
-    src.write_text(MAIN)
+@pytest.mark.parametrize("main", [RANKING, ARRIVALS], ids=["ranking", "arrivals"])
+def test_rule(main, tmp_path):
+    src, exe = tmp_path / "rule.hip", str(tmp_path / "rule")
+    src.write_text(main)
     subprocess.run(["hipcc", "--offload-arch=gfx950", "-O1", "-std=c++17", "-I" + os.path.join(ROOT, "paper_2603_25385_amd", "csrc"),
                     str(src), "-o", exe], check=True, capture_output=True)
     p = subprocess.run([exe], capture_output=True, text=True)
