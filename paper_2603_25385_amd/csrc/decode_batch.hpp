@@ -609,10 +609,17 @@ size_t batch_slab_bytes(const glowq_unit* const* units, int n, int tile, const i
 // 4096 rows and nine tokens on: a slice that waits for the projection of a long contraction ends no earlier than the whole
 // one, and the sum comes on top (64 single units, cold operands, us uncut and cut: 10 tokens x 3 x 192 rows x 9088 11.1 and
 // 13.4, 9 x 3 x 1280 x 13568 16.5 and 20.3, 6 x 2 x 2704 x 9984 14.4 and 15.5; 10 x 4768 x 11264 16.5 and 14.6,
-// 29 x 4336 x 8448 19.2 and 15.0, 19 x 2 x 2136 x 10880 24.5 and 19.8).  Layers of 768 / 13056 at 31 tokens 34.1 -> 24.5,
+// 29 x 4336 x 8448 19.2 and 15.0, 19 x 2 x 2136 x 10880 24.5 and 19.8); in binary16 up to 5120 rows, where three slices
+// fill the chip (17 tokens x 3 x 1712 x 11520 22.0 and 24.4, 14 x 3 x 1768 x 10624 18.9 and 22.0).  Layers of 768 / 13056 at 31 tokens 34.1 -> 24.5,
 // of 512 / 7552 at 7 tokens (four) 22.7 -> 15.3.
+// Several units wait for their projections as well, unless these are small (16 ranks): a launch of less than 400 row blocks
+// is not cut, and the wait, BATCH_WAIT_US per K tile of the longest cut contraction, has to leave a microsecond.  (Uncut and cut: two
+// of 10 tokens x 3 x 192 rows x 9088, r = 64, 12.9 and 14.6 us, four of 13 x 480 x 9088 15.7 and 18.7, two of 11 x 1168 x 13568 19.2
+// and 21.3.  Of 1800 launches that were cut, 600 of them of one to four whole layers, 400 were more than 3 % slower for it, 40 % at
+// most; of the 1114 that this leaves 29 are, 19 % at most, and the mean gain is 15 %; 11 of the whole layers run uncut.)
 constexpr float BATCH_SLICE_US = 4.0f, BATCH_CUT_ONE = 0.85f, BATCH_CUT_SEVERAL[2] = {0.9f, 1.0f};
-constexpr int BATCH_CUT_ONE_BLOCKS = 256, BATCH_CUT_ONE_T = 9;
+constexpr float BATCH_WAIT_US = 5.0f / 32.0f;
+constexpr int BATCH_CUT_ONE_BLOCKS = 256, BATCH_CUT_ONE_MOST_F16 = 320, BATCH_CUT_ONE_T = 9, BATCH_CUT_BLOCKS = 400, BATCH_CUT_RANKS = 16;
 struct BatchSize {
   int blocks, kt, T, allowed;
 };
@@ -678,22 +685,27 @@ static void cheapest_cut_tile(const BatchSize* u, int n, bool f16, int max_mb, i
 int choose_batch_tile(const glowq_unit* const* units, int n, float* cost, int* slices) {
   const bool f16 = units[0]->act_dtype == GLOWQ_F16, exact = f16 && units[0]->T <= 32;
   BatchSize sizes[BATCH_MAX_UNITS];
-  int most_cut = 1;
+  int most_cut = 1, blocks = 0, waiting_kt = 0;
   for (int k = 0; k < n; ++k) {
     const glowq_unit& u = *units[k];
     sizes[k] = BatchSize{unit_row_blocks(u), u.d_in / 128, u.T, 1};
+    blocks += sizes[k].blocks;
     if (slices) {
       sizes[k].allowed = batch_slices_allowed(u);
       most_cut = std::max(most_cut, sizes[k].allowed);
+      if (sizes[k].allowed > 1 && u.r > BATCH_CUT_RANKS) waiting_kt = std::max(waiting_kt, sizes[k].kt);
     }
   }
-  if (n == 1 && units[0]->r > 0 && (sizes[0].blocks < BATCH_CUT_ONE_BLOCKS || sizes[0].T < BATCH_CUT_ONE_T)) most_cut = 1;
+  if (n == 1 && units[0]->r > 0 &&
+      (blocks < BATCH_CUT_ONE_BLOCKS || (f16 && blocks > BATCH_CUT_ONE_MOST_F16) || sizes[0].T < BATCH_CUT_ONE_T)) most_cut = 1;
+  if (n > 1 && waiting_kt > 0 && blocks < BATCH_CUT_BLOCKS) most_cut = 1;
   BatchChoice best = {-1, 1, 0.f};
   cheapest_batch_tile<0>(sizes, n, f16, exact ? 2 : 4, &best);
   if (most_cut > 1 && best.cost > 2.f * BATCH_SLICE_US) {
     BatchChoice cut = {-1, 1, 0.f};
     cheapest_cut_tile(sizes, n, f16, exact ? 2 : 4, most_cut, &cut);
-    if (cut.tile >= 0 && cut.cost < (n > 1 ? BATCH_CUT_SEVERAL[f16 ? 0 : 1] : BATCH_CUT_ONE) * best.cost) best = cut;
+    const float wait = n > 1 && waiting_kt > 0 ? std::max(cut.cost - BATCH_SLICE_US, BATCH_WAIT_US * (float)waiting_kt) + 1.f : 0.f;
+    if (cut.tile >= 0 && cut.cost < (n > 1 ? BATCH_CUT_SEVERAL[f16 ? 0 : 1] : BATCH_CUT_ONE) * best.cost && wait < best.cost) best = cut;
   }
   *cost = best.cost;
   if (slices) {

@@ -98,10 +98,11 @@ def test_units_of_one_call_share_a_launch(T):
 # row blocks that straddle modules, ragged token tiles; with the correction (the first slice's) and without; one unit
 # alone and two of a kind
 @pytest.mark.parametrize("act", ["f16", "bf16"])
-@pytest.mark.parametrize("T,d_in,d_outs,n", [(9, 13696, (1000, 600), 2), (11, 13568, (1168,), 2), (17, 14336, (40, 264, 96), 2),
-                                             (9, 13696, (2600, 1512), 1), (32, 14208, (4096,), 1)])
-def test_contractions_cut_across_workgroups(T, d_in, d_outs, n, act):
-    u = recipe_unit(O, 1, 0, T, r=72, shape=UnitShape("g", d_in, d_outs), act=act, G=128, method="alg1", qr="none")
+@pytest.mark.parametrize("T,d_in,d_outs,n,r", [
+    (9, 13696, (1000, 600), 2, 16), (11, 13568, (1168,), 2, 16), (17, 14336, (40, 264, 96), 2, 16), (20, 13824, (1768, 2080), 2, 72),
+    (27, 14208, (3304,), 2, 72), (9, 13696, (2600, 1512), 1, 72), (32, 14208, (4096,), 1, 72)])
+def test_contractions_cut_across_workgroups(T, d_in, d_outs, n, r, act):
+    u = recipe_unit(O, 1, 0, T, r=r, shape=UnitShape("g", d_in, d_outs), act=act, G=128, method="alg1", qr="none")
     dus = [DeviceUnit(u) for _ in range(n)]
     descs = [d.desc for d in dus]
     assert all(2 <= r.k_slices <= 4 for r in G.glowq_debug_route(descs))
@@ -169,9 +170,9 @@ def test_cut_contractions_in_a_graph():
 
 # The room for the slices' partial results lies behind the units' slices of the workspace and is not required
 @pytest.mark.parametrize("act", ["f16", "bf16"])
-@pytest.mark.parametrize("T,d_in,d_outs,n", [(24, 14208, (4096,), 1), (9, 13696, (1000, 600), 2)])
-def test_room_for_partial_results_is_optional(T, d_in, d_outs, n, act):
-    u = recipe_unit(O, 1, 0, T, r=72, shape=UnitShape("g", d_in, d_outs), act=act, G=128, method="alg1", qr="none")
+@pytest.mark.parametrize("T,d_in,d_outs,n,r", [(24, 14208, (4096,), 1, 72), (9, 13696, (1000, 600), 2, 16)])
+def test_room_for_partial_results_is_optional(T, d_in, d_outs, n, r, act):
+    u = recipe_unit(O, 1, 0, T, r=r, shape=UnitShape("g", d_in, d_outs), act=act, G=128, method="alg1", qr="none")
     dus = [DeviceUnit(u) for _ in range(n)]
     descs = [d.desc for d in dus]
     need, slices = G.glowq_workspace_bytes(descs), 0

@@ -210,6 +210,32 @@ def test_microscaling_keeps_large_tiles_where_they_are_faster(T, d_in, d_outs, a
     assert G.glowq_debug_mx_route(u).tile == 0
 
 
+# Units that wait for projections are not cut where that took longer (us whole, cut)
+@pytest.mark.parametrize("units,T,r,act", [
+    ([(9088, (192,) * 3)] * 2, 10, 64, "f16"),          # 12.9, 14.6
+    ([(9088, (192,) * 3)] * 4, 10, 64, "bf16"),         # 15.5, 17.9
+    ([(13568, (1168,))] * 2, 11, 64, "f16"),            # 19.2, 21.3
+    ([(13568, (1168,))] * 4, 11, 64, "bf16"),           # 23.2, 25.8
+    ([(9088, (480,))] * 4, 13, 64, "bf16"),             # 15.7, 18.7
+    ([(8320, (424,))] * 2, 10, 128, "f16"),             # 11.8, 14.6
+    ([(11136, (256,) * 2)] * 2, 31, 128, "bf16"),       # 17.6, 22.2
+    ([(13056, (3056,))] * 2, 11, 128, "bf16"),          # 24.0, 33.7
+    ([(9472, (1392,)), (2816, (4504,))], 8, 64, "bf16"),           # 16.3, 17.6
+    # one that would fill the chip with three slices
+    ([(10624, (1768,) * 3)], 14, 128, "f16"),           # 18.9, 22.0
+    ([(11520, (1712,) * 3)], 17, 128, "f16")])          # 22.0, 24.4
+def test_corrected_units_run_whole_where_that_is_faster(units, T, r, act):
+    a = {"f16": G.GLOWQ_F16, "bf16": G.GLOWQ_BF16}[act]
+    assert all(x.k_slices == 1 for x in G.glowq_debug_route([unit(T, d, o, r=r, act=a, out=a) for d, o in units]))
+
+
+def test_whole_layers_are_cut_where_that_is_faster():
+    for hidden, kv, inter, layers, T, r, act in [(4096, 1024, 14336, 1, 24, 128, G.GLOWQ_F16), (4096, 1024, 14336, 1, 24, 128, G.GLOWQ_BF16),
+                                                 (768, 768, 13056, 1, 31, 64, G.GLOWQ_F16), (512, 512, 7552, 4, 7, 64, G.GLOWQ_BF16)]:
+        ks = [x.k_slices for x in G.glowq_debug_route(decoder_layers(hidden, kv, inter, layers, T, r, act))]
+        assert min(ks[3::4]) > 1
+
+
 def test_argument_checks():
     for units, status in [([unit(0, 256, (64,))], G.GLOWQ_ERR_SHAPE), ([unit(4, 192, (64,))], G.GLOWQ_ERR_SHAPE),
                           ([unit(4, 320, (64,), Gs=64)], G.GLOWQ_ERR_UNSUPPORTED)]:
