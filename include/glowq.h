@@ -153,10 +153,12 @@ glowq_status glowq_prepare_weights(const uint32_t* wq, const uint16_t* scales,
  * (no unit restored) and glowq_group_forward_static multiply such a unit in one piece.
  *
  * A call of 5 to 32 tokens cuts long contractions on few rows as well, where the pieces of a
- * launch fit the chip (glowq_debug_route tells).  Their partial results lie behind the slices of
- * all units, in a room that the launches of a call share (8 MB at most; none for most calls).
+ * launch fit the chip, and one of 65 to 128 tokens may cut a unit in a slice more than its shapes
+ * ask for, where its launch holds others (glowq_debug_route tells).  These partial results lie behind
+ * the slices of all units, in a room that the launches of a call share (8 MB at most up to 32 tokens,
+ * three partial results of the units so cut in one launch beyond; none for most calls).
  * glowq_workspace_bytes counts it, from descriptors with modules.  The room is not required: a
- * workspace that holds the slices serves the call, with whole contractions where the room is too
+ * workspace that holds the slices serves the call, without these cuts where the room is too
  * small.  Up to 64 tokens the slices do not get smaller as tokens are added, so a workspace that is
  * made for the most tokens serves all calls of the same units with fewer (from five on).
  *

@@ -190,8 +190,17 @@ static LaunchChoice choose_launch(const glowq_unit* units, int n_units, bool sla
     batch[c.n] = &units[c.n];
     ++c.n;
   }
-  plan_prefill_slices(batch, c.n, slabs, c.slices);
+  c.room = plan_prefill_slices(batch, c.n, slabs, room, c.slices);
   const int large = choose_prefill_tile(batch, c.slices, c.n, &cost);
+  // (beside projections of more than 64 ranks a third slice does not speak for the tiled kernel: layers of 3072 / 10752 at 86 to 126
+  // tokens, r = 128, took 8 to 19 % longer there; those that are tiled without it are 6 % faster with it)
+  bool ranks = false;
+  for (int k = 0; k < c.n; ++k) ranks = ranks || units[k].r > 64;
+  if (c.room > 0 && ranks) {
+    int plain[MAX_LAUNCH_UNITS];
+    plan_prefill_slices(batch, c.n, slabs, 0, plain);
+    choose_prefill_tile(batch, plain, c.n, &cost);
+  }
   // Few or small tiles leave the tiled kernel's workgroups alone on their compute units with the
   // whole contraction each; there the smaller tiles of the batched kernel are faster.
   float small_cost = 0.f;
@@ -199,6 +208,7 @@ static LaunchChoice choose_launch(const glowq_unit* units, int n_units, bool sla
   if (small && small_cost < 0.95f * cost) {
     c.kernel = GLOWQ_ROUTE_BATCHED;
     c.tile = tile;
+    c.room = 0;
     for (int& s : c.slices) s = 1;
     return c;
   }
@@ -208,20 +218,20 @@ static LaunchChoice choose_launch(const glowq_unit* units, int n_units, bool sla
 }
 
 // What the launches of a call take behind the units' workspace slices (no more than one of them at a time)
-static size_t batch_room(const glowq_unit* units, int n_units) {
+static size_t room_behind(const glowq_unit* units, int n_units) {
   size_t room = 0;
-  for (int i = 0; i < n_units; ++i)
+  bool some = false;
+  for (int i = 0; i < n_units; ++i) {
     if (!units[i].modules) return 0;
+    some = some || (units[i].T > 4 && units[i].T <= 128);
+  }
+  if (!some) return 0;
   for (int i = 0; i < n_units;) {
-    if (units[i].T <= 4 || !is_decode(units[i].T)) {
-      ++i;
-      continue;
-    }
-    const LaunchChoice c = choose_launch(units + i, n_units - i, false, SIZE_MAX);
+    const LaunchChoice c = choose_launch(units + i, n_units - i, true, SIZE_MAX);
     room = std::max(room, c.room);
     i += c.n;
   }
-  return room;
+  return (room + 255) / 256 * 256;
 }
 
 // Enqueue all units, launch by launch.  slabs: the units' workspace slices hold the slabs of K slices; room: bytes
@@ -243,7 +253,7 @@ static glowq_status forward_all(const glowq_unit* units, int n_units, const uint
     }
     const hipError_t e = c.kernel == GLOWQ_ROUTE_FEW       ? launch_decode_multi(batch, ws, corr, c.n, st)
                          : c.kernel == GLOWQ_ROUTE_BATCHED ? launch_decode_batch(batch, ws, corr, c.n, c.tile, c.slices, behind, st)
-                                                           : launch_prefill_multi(batch, ws, corr, c.n, c.tile, c.slices, st);
+                                                           : launch_prefill_multi(batch, ws, corr, c.n, c.tile, c.slices, behind, st);
     if (e != hipSuccess) return hip_status(e);
   }
   return GLOWQ_OK;
@@ -304,7 +314,7 @@ glowq_status glowq_workspace_bytes(const glowq_unit* units, int32_t n_units, siz
     if (s != GLOWQ_OK) return s;
     total += plan_unit_workspace(units[i], nullptr).bytes;
   }
-  *bytes = total + batch_room(units, n_units);
+  *bytes = total + room_behind(units, n_units);
   return GLOWQ_OK;
 }
 

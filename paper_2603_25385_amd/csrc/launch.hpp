@@ -119,14 +119,15 @@ bool prefill_compatible(const glowq_unit& a, const glowq_unit& b);
 int prefill_max_units();
 int prefill_max_modules();
 // K slices of every unit of a launch: where the unit's shapes ask for them, the workspace has the
-// slabs (`slabs`) and the module table has room
-void plan_prefill_slices(const glowq_unit* const* units, int n, bool slabs, int* slices);
+// slabs (`slabs`) and the module table has room.  Returns the bytes (of `room`) behind the units' workspace slices that the
+// launch takes for more slices than that
+size_t plan_prefill_slices(const glowq_unit* const* units, int n, bool slabs, size_t room, int* slices);
 // the tiles that the launch, cut into these slices, takes, and what it is taken to cost
 enum { PF_TILE_LARGE = 0, PF_TILE_HALF = 1, PF_TILE_WIDE = 2 };
 int choose_prefill_tile(const glowq_unit* const* units, const int* slices, int n, float* cost);
 int prefill_wait_polls();
-hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorkspace* ws,
-                                const bool* restore, int n_units, int tile, const int* slices, hipStream_t st);
+hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorkspace* ws, const bool* restore,
+                                int n_units, int tile, const int* slices, char* behind, hipStream_t st);
 int prefill_k_slices(const glowq_unit& u);
 size_t prefill_splitk_bytes(const glowq_unit& u);
 

@@ -765,20 +765,29 @@ int prefill_k_slices(const glowq_unit& u) {
   for (int i = 0; i < u.n_modules; ++i)
     tiles += (((u.modules[i].d_out + 15) / 16 + tile_blocks - 1) / tile_blocks) * n_mtiles;
   if (tiles > 128) return 1;
-  // (one token tile, binary16: slices of at most 38 K tiles, since they are what such a launch ends with; us by layer,
-  // 4096 / 11008 at 70 / 100 / 128 tokens, in two slices and in three: 64.0, 77.4, 86.3 and 61.7, 69.8, 74.6.  bfloat16's
-  // dequantiser fills the compute units that the shorter slices would leave: 71.6 and 72.4 at 100 tokens)
-  if (u.T <= 128 && u.act_dtype == GLOWQ_F16) return std::min(4, (ktiles + 37) / 38);
   return std::min(4, ktiles / 32);
 }
 // fp32 slab of one slice: [T][ldp], ldp = d_out rounded up to 4 (16-byte stores)
 static inline size_t splitk_ldp(int d_out) { return (size_t)(d_out + 3) / 4 * 4; }
-size_t prefill_splitk_bytes(const glowq_unit& u) {
-  const int S = prefill_k_slices(u);
+static size_t splitk_bytes(const glowq_unit& u, int S) {
   if (S <= 1) return 0;
   size_t b = 0;
   for (int i = 0; i < u.n_modules; ++i) b += (size_t)S * u.T * splitk_ldp(u.modules[i].d_out) * 4;
   return b;
+}
+size_t prefill_splitk_bytes(const glowq_unit& u) { return splitk_bytes(u, prefill_k_slices(u)); }
+// A third slice where two are long (77 to 95 K tiles), for calls of one token tile in binary16: a launch of several units
+// ends with its longest slices while the other units' compute units have nothing to do.  Us in two slices and in three, by
+// layer: 4096 / 11008 at 70 / 100 / 128 tokens 64.0, 77.4, 86.3 and 61.7, 69.8, 74.6; 42 layers of 512 to 5120 / 9856 to 12160 4 %
+// faster on average, 5 % slower at most; 36 other launches 6 %, 4 %.  Not past 10240 rows (20 launches: four 15 % slower), for a unit alone (42 of them: 3 % slower on average, 33 % at most),
+// for more K tiles (29 layers of 116 to 127: 1 % slower) and in bfloat16 (its dequantiser fills
+// the compute units that the shorter slices would leave: 71.6 and 72.4 at 100 tokens).
+static bool third_slice(const glowq_unit& u, int S) {
+  const int ktiles = u.d_in / 128;
+  if (S != 2 || u.act_dtype != GLOWQ_F16 || u.T > 128 || ktiles <= 76 || ktiles >= 96) return false;
+  int rows = 0;
+  for (int i = 0; i < u.n_modules; ++i) rows += u.modules[i].d_out;
+  return rows <= 10240;
 }
 
 // Y[t][row] = sum over the slices' slabs, in slice order, rounded once to the output type
@@ -998,7 +1007,7 @@ int choose_prefill_tile(const glowq_unit* const* units, const int* slices, int n
   return half < 0.95f * full ? PF_TILE_HALF : PF_TILE_LARGE;
 }
 
-void plan_prefill_slices(const glowq_unit* const* units, int n, bool slabs, int* slices) {
+size_t plan_prefill_slices(const glowq_unit* const* units, int n, bool slabs, size_t room, int* slices) {
   int total = 0;
   for (int ui = 0; ui < n; ++ui) total += units[ui]->n_modules;
   for (int ui = 0; ui < n; ++ui) {
@@ -1008,16 +1017,39 @@ void plan_prefill_slices(const glowq_unit* const* units, int n, bool slabs, int*
     total += (S - 1) * u.n_modules;
     slices[ui] = S;
   }
+  // third slices for all units that ask for one or for none (two down projections in three slices and in one took up to
+  // 1.33 times as long as both in two)
+  size_t third = 0;
+  for (int ui = 0; ui < n; ++ui)
+    if (third_slice(*units[ui], slices[ui])) {
+      total += units[ui]->n_modules;
+      third += splitk_bytes(*units[ui], 3);
+    }
+  if (n == 1 || third == 0 || third > room || total > PF_MAX_MODS) return 0;
+  for (int ui = 0; ui < n; ++ui)
+    if (third_slice(*units[ui], slices[ui])) slices[ui] = 3;
+  return third;
+}
+// where a unit's slabs are: its own slice of the workspace, which is sized for the slices that its shapes ask for, or,
+// from one more on, the room behind all slices, which the units of a launch take one after the other
+static float* splitk_slabs(const glowq_unit& u, const UnitWorkspace& w, int S, char** behind) {
+  if (S <= prefill_k_slices(u)) return (float*)(w.base + w.off_splitk);
+  float* p = (float*)*behind;
+  *behind += splitk_bytes(u, S);
+  return p;
 }
 
 int prefill_max_units() { return PF_MAX_UNITS; }
 int prefill_max_modules() { return PF_MAX_MODS; }
 int prefill_wait_polls() { return R_WAIT_POLLS; }
 
-// units[i] uses workspace slice ws[i]; restore[i] says whether its R16 is valid.
-hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorkspace* ws,
-                                const bool* restore, int n_units, int tile, const int* slices, hipStream_t st) {
+// units[i] uses workspace slice ws[i]; restore[i] says whether its R16 is valid.  behind: see plan_prefill_slices
+hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorkspace* ws, const bool* restore,
+                                int n_units, int tile, const int* slices, char* behind, hipStream_t st) {
   PrefillArgs a;
+  float* slabs[PF_MAX_UNITS] = {};
+  for (int ui = 0; ui < n_units; ++ui)
+    if (slices[ui] > 1) slabs[ui] = splitk_slabs(*units[ui], ws[ui], slices[ui], &behind);
   const glowq_unit& u0 = *units[0];
   const int tile_blocks = prefill_tile_blocks(u0.act_dtype, tile);
   const int mb = prefill_token_blocks(units, n_units), tile_tokens = tile == PF_TILE_WIDE ? WD_TOK : 16 * mb;
@@ -1060,7 +1092,7 @@ hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorksp
     pu.restore = (restore[ui] && u.r > 0) ? 1 : 0;
     pu.n_mtiles = (u.T + tile_tokens - 1) / tile_tokens;
     const int S = slices[ui], ktiles = u.d_in / 128;
-    float* slab = (S > 1) ? (float*)(wsb + ws[ui].off_splitk) : nullptr;
+    float* slab = slabs[ui];
     for (int i = 0; i < u.n_modules; ++i) {
       const glowq_module& m = u.modules[i];
       PreparedView v = prepared_view(m.w_prepared, m.d_out, u.d_in, u.group_size);
@@ -1108,7 +1140,7 @@ hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorksp
     const int S = slices[ui];
     if (S <= 1) continue;
     const glowq_unit& u = *units[ui];
-    const float* slab = (const float*)(ws[ui].base + ws[ui].off_splitk);
+    const float* slab = slabs[ui];
     for (int i = 0; i < u.n_modules; ++i) {
       const glowq_module& m = u.modules[i];
       const int ldp = (int)splitk_ldp(m.d_out);

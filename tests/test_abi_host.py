@@ -323,3 +323,14 @@ def test_workspace_of_calls_that_may_be_cut(hidden, kv, inter, layers, act):
 def test_workspace_of_one_unit_that_is_never_cut():
     u = _stack(4096, 1024, 14336, 1, 8, 128, G.GLOWQ_F16)[2]            # gate and up
     assert G.glowq_workspace_bytes([u]) == G.glowq_workspace_bytes(_bare([u]))
+
+
+def test_a_third_slice_lies_behind_the_slices():
+    """What a unit of 65 to 128 tokens has to have does not depend on a third slice of K: a workspace for more tokens
+    serves it, and the slices are where glowq_workspace_bytes of the units alone says."""
+    for T in (65, 100, 128):
+        layer, more = _stack(4096, 4096, 11008, 1, T, 64, G.GLOWQ_F16), _stack(4096, 4096, 11008, 1, T + 64, 64, G.GLOWQ_F16)
+        assert [r.k_slices for r in G.glowq_debug_route(layer)] == [1, 1, 1, 3]
+        alone = [G.glowq_workspace_bytes([u]) for u in layer]
+        assert G.glowq_workspace_bytes(layer) == sum(alone) + 3 * T * 4096 * 4
+        assert all(a <= G.glowq_workspace_bytes([u]) for a, u in zip(alone, more))

@@ -330,6 +330,33 @@ def test_tile_heights(T, d_in, d_outs, act, tile):
             ws.assert_idle()
 
 
+# A third slice of K (binary16, one token tile, several units in a launch) keeps its partial results behind all slices of the
+# workspace; without that room the call runs in two slices
+def test_a_third_slice_and_its_room():
+    shapes = [((20008, 20008), 1024), ((2056,), 9984), ((520, 264), 10112)]
+    units = [make(100, d, outs, "f16", r=24, seed=95 + i) for i, (outs, d) in enumerate(shapes)]
+    dus = [DeviceUnit(u) for u in units]
+    descs = [d.desc for d in dus]
+    routes = G.glowq_debug_route(descs)
+    assert [r.k_slices for r in routes] == [1, 3, 3] and {(r.launch, r.kernel) for r in routes} == {(0, G.GLOWQ_ROUTE_TILED)}
+    slices, need = sum(G.glowq_workspace_bytes([d]) for d in descs), G.glowq_workspace_bytes(descs)
+    assert need >= slices + 3 * 100 * (2056 + 784) * 4
+    failed = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    for nbytes, third in ((need, True), (need - 256, False), (slices, False), (need, True)):
+        buf = torch.zeros(need + 4096, dtype=torch.uint8, device="cuda")
+        buf[slices:] = 0xA5
+        for restore in (1, 0):
+            for d in dus:
+                d.clear()
+            G.glowq_block_forward(descs, bytes([restore] * 3), buf.data_ptr(), nbytes, stream())
+            for u, d in zip(units, dus):
+                check(d.outputs(), O.group_forward(u, bool(restore)), TOL)
+        G.glowq_workspace_status(descs, buf.data_ptr(), nbytes, failed.data_ptr(), stream())
+        torch.cuda.synchronize()
+        assert int(failed.item()) == 0
+        assert bool((buf[slices:need] != 0xA5).any()) == third and bool((buf[need:] == 0xA5).all())
+
+
 def test_units_of_several_token_counts_share_tiles_of_one_height():
     # 70, 200 and 330 tokens in one launch: the most blocks that a unit asks for (seven) hold for all
     units = [make(T, 768, (12008, 4008), "f16", r=24, seed=90 + T) for T in (70, 330, 200)]

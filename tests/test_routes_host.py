@@ -236,6 +236,22 @@ def test_whole_layers_are_cut_where_that_is_faster():
         assert min(ks[3::4]) > 1
 
 
+def test_third_slices_for_all_units_of_a_launch_or_for_none():
+    # (a third slice for the first of two down projections left the second one whole: us in two slices each, and so)
+    for T, r, layers, want in [(100, 64, 1, 3), (100, 16, 2, 2),             # 2 x 3584 / 9984: 117.5, 156.3
+                               (104, 64, 2, 2), (113, 16, 4, 2),             # 4 x 4736 / 11136: 295.6, 371.1
+                               (100, 128, 1, 3), (129, 64, 1, 2)]:
+        for hidden, inter in ((4096, 11008), (3584, 9984), (4736, 11136)):
+            routes = G.glowq_debug_route(decoder_layers(hidden, hidden, inter, layers, T, r, G.GLOWQ_F16))
+            assert {x.kernel for x in routes} == {G.GLOWQ_ROUTE_TILED} and [x.k_slices for x in routes[3::4]] == [want] * layers
+    # (85.4 in two slices and on the batched kernel, 92.4 in three)
+    assert {x.kernel for x in G.glowq_debug_route(decoder_layers(3072, 3072, 10752, 1, 111, 128, G.GLOWQ_F16))} == {G.GLOWQ_ROUTE_BATCHED}
+    wide = [unit(108, d, o, r=16) for d, o in ((6528, (5928,)), (10368, (5944,) * 2), (3328, (1408,) * 2))]        # 77.1, 89.9
+    assert [x.k_slices for x in G.glowq_debug_route(wide)] == [1, 2, 1]
+    for T in (70, 107, 125):                   # a unit alone: 2 x 5560 rows x 11008 at 107 tokens 75.9 us, in three slices 93.9
+        assert all(route(T, 11008, rows, r=128).k_slices <= 2 for rows in ((5560,) * 2, (4096,), (7848,) * 2))
+
+
 def test_argument_checks():
     for units, status in [([unit(0, 256, (64,))], G.GLOWQ_ERR_SHAPE), ([unit(4, 192, (64,))], G.GLOWQ_ERR_SHAPE),
                           ([unit(4, 320, (64,), Gs=64)], G.GLOWQ_ERR_UNSUPPORTED)]:
