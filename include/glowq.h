@@ -384,9 +384,12 @@ typedef struct {
 glowq_status glowq_debug_route(const glowq_unit* units, int32_t n_units, int32_t slabs,
                                glowq_route* routes);
 glowq_status glowq_debug_mx_route(const glowq_unit* u, glowq_route* route);
-/* tokens[i]: tokens of a workgroup tile of the tiled kernel (128, of which a call may leave up to three sixteens out,
- * or 256 for the wide ones, which count as large), 0 for a unit that another kernel serves. */
+/* glowq_debug_tile_tokens: which tiles of the tiled kernel serve unit i, by the most tokens that they hold: 128, or 256 for
+ * the wide ones, which count as large; 0 for a unit that another kernel serves.
+ * glowq_debug_tile_height: tokens of the workgroup tiles that the launch is made with, for the tiled kernel (80, 96, 112, 128 or
+ * 256) and the batched one (16, 32, 48 or 64); 0 for a unit that another kernel serves. */
 glowq_status glowq_debug_tile_tokens(const glowq_unit* units, int32_t n_units, int32_t slabs, int32_t* tokens);
+glowq_status glowq_debug_tile_height(const glowq_unit* units, int32_t n_units, int32_t slabs, int32_t* tokens);
 glowq_status glowq_debug_unpack(const void* w_prepared, int32_t d_out, int32_t d_in,
                                 int32_t group_size, uint8_t* q_out, void* stream);
 glowq_status glowq_debug_dequant(const void* w_prepared, int32_t d_out, int32_t d_in,

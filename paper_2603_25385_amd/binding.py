@@ -99,6 +99,7 @@ def _load():
         "glowq_mx_group_forward": (ctypes.c_int, [up, i32, vp, sz, vp]),
         "glowq_debug_route": (ctypes.c_int, [up, i32, i32, ctypes.POINTER(glowq_route)]),
         "glowq_debug_tile_tokens": (ctypes.c_int, [up, i32, i32, ctypes.POINTER(i32)]),
+        "glowq_debug_tile_height": (ctypes.c_int, [up, i32, i32, ctypes.POINTER(i32)]),
         "glowq_debug_mx_route": (ctypes.c_int, [up, ctypes.POINTER(glowq_route)]),
         "glowq_debug_unpack": (ctypes.c_int, [vp, i32, i32, i32, vp, vp]),
         "glowq_debug_dequant": (ctypes.c_int, [vp, i32, i32, i32, i32, vp, vp]),
@@ -347,10 +348,18 @@ def glowq_debug_route(units: Sequence[glowq_unit], slabs: bool = True) -> list:
 
 
 def glowq_debug_tile_tokens(units: Sequence[glowq_unit], slabs: bool = True) -> list:
-    """Tokens of the tiled kernel's workgroup tiles, per unit (0: another kernel)."""
+    """Most tokens of the tiled kernel's kind of workgroup tiles, per unit (0: another kernel)."""
     tokens = (ctypes.c_int32 * len(units))()
     _check(_lib.glowq_debug_tile_tokens(_units_array(units), len(units), 1 if slabs else 0, tokens),
            "glowq_debug_tile_tokens")
+    return list(tokens)
+
+
+def glowq_debug_tile_height(units: Sequence[glowq_unit], slabs: bool = True) -> list:
+    """Tokens of the workgroup tiles that the launch is made with, per unit (0: neither the tiled nor the batched kernel)."""
+    tokens = (ctypes.c_int32 * len(units))()
+    _check(_lib.glowq_debug_tile_height(_units_array(units), len(units), 1 if slabs else 0, tokens),
+           "glowq_debug_tile_height")
     return list(tokens)
 
 

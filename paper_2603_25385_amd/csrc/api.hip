@@ -612,9 +612,10 @@ glowq_status glowq_mx_group_forward(const glowq_unit* u, int32_t restore, void* 
   return hip_status(launch_mx_forward(*u, restore != 0, (char*)workspace, (hipStream_t)stream));
 }
 
-// routes and tokens: either may be missing
-static glowq_status debug_route(const glowq_unit* units, int32_t n_units, int32_t slabs, glowq_route* routes, int32_t* tokens) {
-  if (!units || (!routes && !tokens)) return GLOWQ_ERR_NULL;
+// routes, tokens and heights: any of them may be missing
+static glowq_status debug_route(const glowq_unit* units, int32_t n_units, int32_t slabs, glowq_route* routes, int32_t* tokens,
+                                int32_t* heights) {
+  if (!units || (!routes && !tokens && !heights)) return GLOWQ_ERR_NULL;
   if (n_units < 1) return GLOWQ_ERR_SHAPE;
   for (int i = 0; i < n_units; ++i) {
     glowq_status s = validate(&units[i], false, false);
@@ -624,6 +625,10 @@ static glowq_status debug_route(const glowq_unit* units, int32_t n_units, int32_
   for (int i = 0, launch = 0; i < n_units; ++launch) {
     const LaunchChoice c = choose_launch(units + i, n_units - i, slabs != 0, slabs ? SIZE_MAX : 0);
     const bool tiled = c.kernel == GLOWQ_ROUTE_TILED, wide = tiled && c.tile == PF_TILE_WIDE;
+    const glowq_unit* batch[MAX_LAUNCH_UNITS];
+    for (int k = 0; k < c.n; ++k) batch[k] = &units[i + k];
+    const int blocks = tiled ? prefill_token_blocks(batch, c.n, c.tile)
+                             : c.kernel == GLOWQ_ROUTE_BATCHED ? batch_token_blocks(batch, c.n, c.tile, c.slices) : 0;
     for (int k = 0; k < c.n; ++k, ++i) {
       if (routes)
         routes[i] = glowq_route{launch, c.kernel, wide ? PF_TILE_LARGE : c.tile, c.slices[k],
@@ -631,15 +636,19 @@ static glowq_status debug_route(const glowq_unit* units, int32_t n_units, int32_
                                 : c.kernel == GLOWQ_ROUTE_BATCHED ? batch_wait_polls()
                                                                   : prefill_wait_polls()};
       if (tokens) tokens[i] = wide ? 256 : tiled ? 128 : 0;
+      if (heights) heights[i] = 16 * blocks;
     }
   }
   return GLOWQ_OK;
 }
 glowq_status glowq_debug_route(const glowq_unit* units, int32_t n_units, int32_t slabs, glowq_route* routes) {
-  return debug_route(units, n_units, slabs, routes, nullptr);
+  return debug_route(units, n_units, slabs, routes, nullptr, nullptr);
 }
 glowq_status glowq_debug_tile_tokens(const glowq_unit* units, int32_t n_units, int32_t slabs, int32_t* tokens) {
-  return debug_route(units, n_units, slabs, nullptr, tokens);
+  return debug_route(units, n_units, slabs, nullptr, tokens, nullptr);
+}
+glowq_status glowq_debug_tile_height(const glowq_unit* units, int32_t n_units, int32_t slabs, int32_t* tokens) {
+  return debug_route(units, n_units, slabs, nullptr, nullptr, tokens);
 }
 
 glowq_status glowq_debug_mx_route(const glowq_unit* u, glowq_route* route) {

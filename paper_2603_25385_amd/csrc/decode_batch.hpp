@@ -735,16 +735,16 @@ void plan_batch_projection(const glowq_unit& u, UnitWorkspace& w) {
   w.ksplit = (u.d_in + w.kslice - 1) / w.kslice;
 }
 
-// Token blocks of a launch's tiles: those of the tile, or three instead of four where every unit's tokens, dealt evenly to as
-// many tiles, fit them (33 to 48 tokens, 65 to 96, ..): a quarter less of X and of the products, and on tiles of
+// Token blocks of a launch's tiles: those of the tile, or three instead of four where nothing is cut and every unit's tokens,
+// dealt evenly to as many tiles, fit them (33 to 48 tokens, 65 to 96, ..): a quarter less of X and of the products, and on tiles of
 // 64 rows three workgroups per compute unit instead of two.  (Us on four blocks and on three: 88 tokens x 2 x 3272 rows x
 // 4224 21.3 and 17.4, 46 x 3 x 5048 x 11008 46.6 and 41.1, 141 x 3 x 3256 x 9600 65.2 and 56.9, four layers of 4992 / 1920 at
 // 47 tokens 68.8 and 62.0.)
-static int batch_token_blocks(const glowq_unit* const* units, int n, int tile) {
+int batch_token_blocks(const glowq_unit* const* units, int n, int tile, const int* slices) {
   if (BATCH_TILES[tile].mb != 4) return BATCH_TILES[tile].mb;
   for (int k = 0; k < n; ++k) {
     const int tiles = (units[k]->T + 63) / 64;
-    if (units[k]->T > 48 * tiles) return 4;
+    if (slices[k] > 1 || units[k]->T > 48 * tiles) return 4;
   }
   return 3;
 }
@@ -828,7 +828,7 @@ static hipError_t launch_batch(const glowq_unit* const* units, const UnitWorkspa
   }
   bool cut = false;
   for (int i = 0; i < n; ++i) cut = cut || slices[i] > 1;
-  const int mb = cut ? tile.mb : batch_token_blocks(units, n, ti);
+  const int mb = batch_token_blocks(units, n, ti, slices);
   int wg = n_prod;
   for (int oi = 0; oi < n; ++oi) {
     b.u[oi].wg_start = wg;

@@ -111,6 +111,7 @@ int batch_wait_polls();
 bool batch_compatible(const glowq_unit& a, const glowq_unit& b);
 int batch_max_units();
 size_t batch_slab_bytes(const glowq_unit* const* units, int n, int tile, const int* slices);
+int batch_token_blocks(const glowq_unit* const* units, int n, int tile, const int* slices);     // of 16, in the launch's tiles
 hipError_t launch_decode_batch(const glowq_unit* const* units, const UnitWorkspace* ws, const bool* restore, int n,
                                int tile, const int* slices, char* slabs, hipStream_t st);
 // The other calls of T > 64: tiled matrix-core GEMM, correction folded in as an extra K slab.
@@ -125,6 +126,7 @@ size_t plan_prefill_slices(const glowq_unit* const* units, int n, bool slabs, si
 // the tiles that the launch, cut into these slices, takes, and what it is taken to cost
 enum { PF_TILE_LARGE = 0, PF_TILE_HALF = 1, PF_TILE_WIDE = 2 };
 int choose_prefill_tile(const glowq_unit* const* units, const int* slices, int n, float* cost);
+int prefill_token_blocks(const glowq_unit* const* units, int n, int tile);
 int prefill_wait_polls();
 hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorkspace* ws, const bool* restore,
                                 int n_units, int tile, const int* slices, char* behind, hipStream_t st);

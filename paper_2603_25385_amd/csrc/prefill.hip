@@ -839,7 +839,8 @@ static inline long long prefill_tiles(const glowq_unit& u, int tile_blocks, int 
 // tokens, the dequantiser and the weights do not.  Layers of 4096 / 11008 and 4096 / 14336, us, tiles of 128 tokens and these: 70
 // tokens 72 -> 60, 140 tokens 112 -> 88, 200 tokens 132 -> 126, 260 tokens 174 -> 146, 300 tokens 165 -> 152; 110 other
 // calls of 65 to 384 tokens 2.4 % on average, 24 % at most.)
-static int prefill_token_blocks(const glowq_unit* const* units, int n) {
+int prefill_token_blocks(const glowq_unit* const* units, int n, int tile) {
+  if (tile == PF_TILE_WIDE) return WD_TOK / 16;
   int mb = 5;
   for (int k = 0; k < n; ++k) {
     const int tiles = (units[k]->T + 16 * PF_MB - 1) / (16 * PF_MB);
@@ -867,7 +868,7 @@ static float prefill_cost_of(const glowq_unit* const* units, const int* slices, 
   const PrefillCost c = half ? (f16 ? PrefillCost{3.48f, 2.50f, 1.09f, 1.45f, 0.79f, 0.88f, 10.9f} : PrefillCost{0.04f, 5.01f, 1.17f, 2.07f, 0.94f, 5.33f, 10.9f})
                              : (f16 ? PrefillCost{1.78f, 4.88f, 1.43f, 3.42f, 0.73f, 0.34f, 0.5f} : PrefillCost{5.46f, 5.94f, 1.59f, 2.87f, 0.82f, 1.08f, 0.5f});
   // (half of a K tile's time goes with the tile's tokens)
-  const double tokens = 0.5 + 0.5 * prefill_token_blocks(units, n) / PF_MB;
+  const double tokens = 0.5 + 0.5 * prefill_token_blocks(units, n, tile) / PF_MB;
   double work = 0.0, wgs = 0.0;
   int chain = 0, sliced = 0;
   for (int k = 0; k < n; ++k) {
@@ -1052,7 +1053,7 @@ hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorksp
     if (slices[ui] > 1) slabs[ui] = splitk_slabs(*units[ui], ws[ui], slices[ui], &behind);
   const glowq_unit& u0 = *units[0];
   const int tile_blocks = prefill_tile_blocks(u0.act_dtype, tile);
-  const int mb = prefill_token_blocks(units, n_units), tile_tokens = tile == PF_TILE_WIDE ? WD_TOK : 16 * mb;
+  const int mb = prefill_token_blocks(units, n_units, tile), tile_tokens = 16 * mb;
   // longest contraction first
   int order[PF_MAX_UNITS];
   longest_first(units, n_units, order);

@@ -222,5 +222,6 @@ def test_tiles_of_three_token_blocks(T, d_in, d_outs, act, tile):
         ys, du, _ = run_group(u, restore, out="act", ldy_pad=8)
         r = G.glowq_debug_route([du.desc])[0]
         assert (r.kernel, r.tile) == (G.GLOWQ_ROUTE_BATCHED, tile)
+        assert G.glowq_debug_tile_height([du.desc]) == [48 if T % 48 == 0 else 64]
         for y, ref in zip(ys, O.group_forward(u, restore)):
             assert np.isfinite(y).all() and rel_err(y, ref) <= TOL + ULP[act]

@@ -311,17 +311,17 @@ def test_wide_tiles_give_the_bits_of_the_128_token_tiles(act, Gs):
 # Tiles of 80, 96, 112 and 128 tokens (a call's tokens dealt evenly to as many tiles as tiles of 128 would be), first and
 # last of each height, in one, two and three token tiles: the second tile of 140 tokens takes its R from both of the
 # projection's tiles of 128
-@pytest.mark.parametrize("T,d_in,d_outs,act,tile", [
-    (70, 1152, (10008, 10008), "f16", HALF), (80, 1152, (10008, 10008), "bf16", HALF), (81, 768, (12008, 12008), "f16", HALF),
-    (96, 768, (12008, 12008), "bf16", HALF), (97, 768, (12008, 12008), "bf16", HALF), (112, 768, (12008, 12008), "f16", HALF),
-    (113, 768, (12008, 12008), "f16", HALF), (140, 768, (12008, 12008), "f16", HALF), (157, 768, (12008, 12008), "bf16", HALF),
-    (200, 768, (8232, 8232), "bf16", HALF), (300, 768, (8232, 8232), "f16", HALF), (90, 256, (26008,) * 3, "bf16", LARGE),
-    (140, 256, (26008,) * 3, "f16", LARGE), (200, 256, (20008, 20008), "bf16", LARGE), (260, 256, (26008, 26008), "f16", LARGE)])
-def test_tile_heights(T, d_in, d_outs, act, tile):
+@pytest.mark.parametrize("T,d_in,d_outs,act,tile,height", [
+    (70, 1152, (10008, 10008), "f16", HALF, 80), (80, 1152, (10008, 10008), "bf16", HALF, 80), (81, 768, (12008, 12008), "f16", HALF, 96),
+    (96, 768, (12008, 12008), "bf16", HALF, 96), (97, 768, (12008, 12008), "bf16", HALF, 112), (112, 768, (12008, 12008), "f16", HALF, 112),
+    (113, 768, (12008, 12008), "f16", HALF, 128), (140, 768, (12008, 12008), "f16", HALF, 80), (157, 768, (12008, 12008), "bf16", HALF, 80),
+    (200, 768, (8232, 8232), "bf16", HALF, 112), (300, 768, (8232, 8232), "f16", HALF, 112), (90, 256, (26008,) * 3, "bf16", LARGE, 96),
+    (140, 256, (26008,) * 3, "f16", LARGE, 80), (200, 256, (20008, 20008), "bf16", LARGE, 112), (260, 256, (26008, 26008), "f16", LARGE, 96)])
+def test_tile_heights(T, d_in, d_outs, act, tile, height):
     for Gs, r in ((128, 72), (64, 128)):
         u = make(T, d_in, d_outs, act, Gs, r)
         du = DeviceUnit(u, "act", 8)
-        assert route_of(du).tile == tile
+        assert route_of(du).tile == tile and G.glowq_debug_tile_height([du.desc]) == [height]
         ws = Workspace([du.desc])
         for restore in (True, False):
             du.clear()
@@ -363,6 +363,7 @@ def test_units_of_several_token_counts_share_tiles_of_one_height():
     dus = [DeviceUnit(u) for u in units]
     routes = G.glowq_debug_route([d.desc for d in dus])
     assert {(r.launch, r.kernel) for r in routes} == {(0, G.GLOWQ_ROUTE_TILED)}
+    assert G.glowq_debug_tile_height([d.desc for d in dus]) == [112] * 3
     ws = Workspace([d.desc for d in dus])
     G.glowq_block_forward([d.desc for d in dus], bytes([1, 1, 1]), ws.ptr, ws.bytes, stream())
     for u, d in zip(units, dus):

@@ -252,6 +252,17 @@ def test_third_slices_for_all_units_of_a_launch_or_for_none():
         assert all(route(T, 11008, rows, r=128).k_slices <= 2 for rows in ((5560,) * 2, (4096,), (7848,) * 2))
 
 
+def test_tile_heights_are_those_of_the_launch():
+    for T, height in [(65, 80), (80, 80), (81, 96), (97, 112), (113, 128), (129, 80), (300, 112), (521, 112), (1024, 128)]:
+        u = unit(T, 768, (16008,) * 3, act=G.GLOWQ_BF16, out=G.GLOWQ_BF16)
+        assert G.glowq_debug_tile_height([u]) == [height] and G.glowq_debug_tile_tokens([u]) == [128]
+    assert G.glowq_debug_tile_height([unit(2048, 4096, (11008,) * 2, r=64, act=G.GLOWQ_BF16, out=G.GLOWQ_BF16)]) == [256]
+    # batched: 48 of the 64 tokens that tiles 5 and 6 hold
+    for T, d, rows, height in [(48, 2688, 12008, 48), (49, 2688, 10008, 64), (16, 1024, 4096, 16), (32, 2048, 14336, 32)]:
+        assert G.glowq_debug_tile_height([unit(T, d, (rows,))]) == [height]
+    assert G.glowq_debug_tile_height([unit(4, 1024, (4096,))]) == [0]
+
+
 def test_argument_checks():
     for units, status in [([unit(0, 256, (64,))], G.GLOWQ_ERR_SHAPE), ([unit(4, 192, (64,))], G.GLOWQ_ERR_SHAPE),
                           ([unit(4, 320, (64,), Gs=64)], G.GLOWQ_ERR_UNSUPPORTED)]:
