@@ -301,8 +301,8 @@ glowq_status glowq_quantize_rtn(const float* W, int32_t d_out, int32_t d_in, int
  * float64.  sigma_out: DEVICE double [r + p] or NULL, the singular values of Q^T M in
  * descending order (the first r are those of the factors: |A[:,j]|^2 = |B[j,:]|^2 =
  * sigma_j for sigma_x = 1).  All arithmetic is float64 with sums in a fixed order: the
- * same inputs give the same bits.  The call enqueues a few thousand small launches on
- * `stream` and returns; it allocates nothing. */
+ * same inputs give the same bits.  The call enqueues its launches on `stream` (about
+ * thirty for r + p <= 128, some thousands for wider sketches) and returns; it allocates nothing. */
 #define GLOWQ_MAX_SKETCH 256
 #define GLOWQ_MAX_POWER_STEPS 8
 glowq_status glowq_factorize_workspace_bytes(const glowq_unit* u, int32_t r, int32_t p,

@@ -474,7 +474,6 @@ glowq_status glowq_unit_importance(const glowq_unit* u, const float* const* W_mo
   glowq_status s = validate(u, false, false);
   if (s != GLOWQ_OK) return s;
   if (!u->modules) return GLOWQ_ERR_NULL;
-  static_assert(GLOWQ_IMPORTANCE_SCRATCH_BYTES >= (2 + 3 * GLOWQ_MAX_RANK) * sizeof(double), "scratch layout");
   if (((uintptr_t)scratch & 7u) || ((uintptr_t)scores & 7u)) return GLOWQ_ERR_ALIGN;
   if (u->r > 0 && (!u->B || misaligned(u->B))) return u->B ? GLOWQ_ERR_ALIGN : GLOWQ_ERR_NULL;
   for (int i = 0; i < u->n_modules; ++i) {

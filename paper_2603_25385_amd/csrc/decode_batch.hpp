@@ -597,6 +597,7 @@ size_t batch_slab_bytes(const glowq_unit* const* units, int n, int tile, const i
   return bytes;
 }
 
+// (Tiles of 64 tokens are priced with four token blocks, as in the fit, also where a launch has three.)
 // What the tiles from I on cost for units of `blocks` row blocks, `kt` K tiles and T tokens, of which `allowed` K slices
 // (a tile at a time as constants, so that a call pays for shifts instead of divisions: one call of the
 // smallest group is a few hundred instructions of host code in all).  A contraction is cut where the launch would take

@@ -18,8 +18,8 @@
 // matrix or a Householder QR of the stack would cost m d^2 operations against
 // (2q + 2) m d (r + p) for the products.
 //
-// The matrix products are float64 matrix-core contractions (16x16x4), one wave per output
-// tile and K slice, partial results in slices that a second kernel adds in slice order, so
+// The matrix products are float64 matrix-core contractions (16x16x4); where K is cut into slices
+// their partial results are added in slice order, and the Gram matrices' parts in workgroup order, so
 // results do not depend on timing.
 #include "common.hpp"
 #include "launch.hpp"
@@ -107,14 +107,8 @@ __global__ void __launch_bounds__(256) k_error_stack(StackArgs a, const double* 
 
 // ---------------------------------------------------------------------------------------
 // float64 products on the matrix cores.  v_mfma_f64_16x16x4: lane l holds A[l & 15][l >> 4],
-// B[l >> 4][l & 15] and, in register v, D[(l >> 4) + 4 v][l & 15].
-// One workgroup owns a tile of 16 RB rows x 16 NT columns over one K slice, its four waves a
-// quarter of the slice each: their sums meet in LDS in wave order and go to slice ks of P
-// ([KS][M][ldp]).  (A slice per wave wrote and read four times as many partial tiles: 84 MB for
-// 3072 x 80 over 5120; the next step's operands loaded a step ahead cost the registers of half
-// the waves and 15 % of the time.)  Operands come straight from global memory (the small one
-// stays in the L2s); rows, columns and K past the edge are clamped on the load and dropped
-// (zeroed, for K) afterwards.
+// B[l >> 4][l & 15] and, in register v, D[(l >> 4) + 4 v][l & 15].  Slice ks of a product goes to
+// P[ks][M][ldp]; rows, columns and K past the edge are clamped on the load and dropped (zeroed, for K) afterwards.
 // ---------------------------------------------------------------------------------------
 struct GemmShape {
   int M, N, K;
@@ -124,7 +118,7 @@ struct GemmShape {
   int row_tiles;   // ceil(M / 64)
 };
 
-// the four waves' tiles added in wave order, in wave 0's registers
+// the four waves' tiles added in wave order, in wave 0's registers (k_lift, whose waves share the contraction)
 template <int RB, int NT>
 __device__ inline void fold_waves(double4_t (&acc)[RB][NT], double* fold, int wave, int lane) {
   for (int w = 1; w < 4; ++w) {
@@ -950,6 +944,7 @@ __device__ inline bool rotation_step(double* Zt, int l, double* __restrict__ U, 
 // 80 rows of 3072, us: 155 (tridiagonal 64, bisection 37, twisted factorisations 32, reflections 12, orthogonality 10) where
 // the rotations take 510; what the rows have left is then 5e-16 of their lengths.
 // ---------------------------------------------------------------------------------------
+// (both matrices of 96 columns, with the pads that spread their columns over the banks, are past the LDS)
 constexpr int FZ_DIRECT = 80;
 constexpr double FZ_DIRECT_RANGE = 1e-6;     // smallest over largest eigenvalue
 constexpr double FZ_ORTHO_TRIES = 0.25, FZ_ORTHO_ONE = 1e-8;   // |U^T U - 1| that can be mended at all, and by one step

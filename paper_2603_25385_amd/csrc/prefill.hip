@@ -948,6 +948,8 @@ constexpr PlacesCost PLACES_COST[2][3] = {      // binary16, bfloat16; PF_TILE_L
     {{5.97f, 3.69f, 2.51f, 0.00f, 1.26f, 0.46f, 2.00f, 2.50f, 4.94f, 0.00f, 1.25f, 5.80f, 1.04f},
      {6.24f, 3.73f, 3.18f, 0.00f, 0.94f, 0.31f, 1.51f, 1.80f, 2.61f, 9.04f, 0.03f, 5.46f, 1.03f},
      {0.00f, 6.18f, 0.80f, 0.76f, 1.97f, 0.62f, 2.28f, 2.59f, 2.14f, 5.79f, 16.74f, 4.68f, 1.00f}}};
+// (Tiles of 128 tokens throughout, as the calls that the constants were taken from ran: from 384 tokens on the height that
+// deals them evenly, 112 or 128, leaves as many tiles, and a tile's time by its tokens is less than the estimate's error.)
 static double prefill_places_cost(const glowq_unit* const* units, const int* slices, int n, int tile) {
   const PlacesCost& c = PLACES_COST[units[0]->act_dtype == GLOWQ_F16 ? 0 : 1][tile];
   const int tile_blocks = prefill_tile_blocks(units[0]->act_dtype, tile), tokens = tile == PF_TILE_WIDE ? WD_TOK : 128;
