@@ -194,9 +194,9 @@ static LaunchChoice choose_launch(const glowq_unit* units, int n_units, bool sla
   const int large = choose_prefill_tile(batch, c.slices, c.n, &cost);
   // (beside projections of more than 64 ranks a third slice does not speak for the tiled kernel: layers of 3072 / 10752 at 86 to 126
   // tokens, r = 128, took 8 to 19 % longer there; those that are tiled without it are 6 % faster with it)
-  bool ranks = false;
-  for (int k = 0; k < c.n; ++k) ranks = ranks || units[k].r > 64;
-  if (c.room > 0 && ranks) {
+  int ranks = 0;
+  for (int k = 0; k < c.n; ++k) ranks = std::max(ranks, units[k].r);
+  if (c.room > 0 && ranks > 64) {
     int plain[MAX_LAUNCH_UNITS];
     plan_prefill_slices(batch, c.n, slabs, 0, plain);
     choose_prefill_tile(batch, plain, c.n, &cost);
@@ -205,6 +205,16 @@ static LaunchChoice choose_launch(const glowq_unit* units, int n_units, bool sla
   // whole contraction each; there the smaller tiles of the batched kernel are faster.
   float small_cost = 0.f;
   const int tile = small ? choose_batch_tile(batch, c.n, &small_cost, nullptr) : 0;
+  // Short launches on half-size tiles wait for their projections, whose tiles hold 128 tokens whatever the others hold:
+  // there the fewer tokens do not speak for the tiled kernel.  (Us on the batched kernel and on half-size tiles: 172 tokens x 3 x
+  // 5384 rows x 3200, r = 128, 44.5 and 58.9; 151 x 2 x 5536 x 2048 29.9 and 43.3; a layer of 2944 / 3072 at 67 tokens 33.2 and 47.0.  Of
+  // 498 random calls of 65 to 400 tokens that the fewer tokens moved to the tiled kernel 97 were more than 5 % slower there; of
+  // the 391 that still are 33.  Us of the batched kernel's estimate; in bfloat16 below 16 as many gain as lose.)
+  constexpr float SHORT_US[2][2] = {{0.f, 50.f}, {16.f, 40.f}};
+  constexpr int SHORT_RANKS = 16;
+  const float* us = SHORT_US[units[0].act_dtype == GLOWQ_F16 ? 0 : 1];
+  if (small && large == PF_TILE_HALF && ranks > SHORT_RANKS && small_cost >= us[0] && small_cost < us[1])
+    choose_prefill_tile(batch, c.slices, c.n, &cost, false);
   if (small && small_cost < 0.95f * cost) {
     c.kernel = GLOWQ_ROUTE_BATCHED;
     c.tile = tile;

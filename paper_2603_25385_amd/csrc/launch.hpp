@@ -123,9 +123,10 @@ int prefill_max_modules();
 // slabs (`slabs`) and the module table has room.  Returns the bytes (of `room`) behind the units' workspace slices that the
 // launch takes for more slices than that
 size_t plan_prefill_slices(const glowq_unit* const* units, int n, bool slabs, size_t room, int* slices);
-// the tiles that the launch, cut into these slices, takes, and what it is taken to cost
+// the tiles that the launch, cut into these slices, takes, and what it is taken to cost (dealt false: on tiles that all hold
+// 128 tokens)
 enum { PF_TILE_LARGE = 0, PF_TILE_HALF = 1, PF_TILE_WIDE = 2 };
-int choose_prefill_tile(const glowq_unit* const* units, const int* slices, int n, float* cost);
+int choose_prefill_tile(const glowq_unit* const* units, const int* slices, int n, float* cost, bool dealt = true);
 int prefill_token_blocks(const glowq_unit* const* units, int n, int tile);
 int prefill_wait_polls();
 hipError_t launch_prefill_multi(const glowq_unit* const* units, const UnitWorkspace* ws, const bool* restore,

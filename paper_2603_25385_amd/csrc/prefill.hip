@@ -863,12 +863,12 @@ int prefill_token_blocks(const glowq_unit* const* units, int n, int tile) {
 struct PrefillCost {
   float start, ends, alone, pair, few, busy, sum;
 };
-static float prefill_cost_of(const glowq_unit* const* units, const int* slices, int n, int tile) {
+static float prefill_cost_of(const glowq_unit* const* units, const int* slices, int n, int tile, bool dealt) {
   const bool f16 = units[0]->act_dtype == GLOWQ_F16, half = tile == PF_TILE_HALF;
   const PrefillCost c = half ? (f16 ? PrefillCost{3.48f, 2.50f, 1.09f, 1.45f, 0.79f, 0.88f, 10.9f} : PrefillCost{0.04f, 5.01f, 1.17f, 2.07f, 0.94f, 5.33f, 10.9f})
                              : (f16 ? PrefillCost{1.78f, 4.88f, 1.43f, 3.42f, 0.73f, 0.34f, 0.5f} : PrefillCost{5.46f, 5.94f, 1.59f, 2.87f, 0.82f, 1.08f, 0.5f});
-  // (half of a K tile's time goes with the tile's tokens)
-  const double tokens = 0.5 + 0.5 * prefill_token_blocks(units, n, tile) / PF_MB;
+  // (half of a K tile's time goes with the tile's tokens; not dealt: as if every tile held 128)
+  const double tokens = dealt ? 0.5 + 0.5 * prefill_token_blocks(units, n, tile) / PF_MB : 1.0;
   double work = 0.0, wgs = 0.0;
   int chain = 0, sliced = 0;
   for (int k = 0; k < n; ++k) {
@@ -991,8 +991,8 @@ static WideMeans prefill_wide_means(const glowq_unit* const* units, const int* s
   }
   return WideMeans{ktiles / tiles, tokens / ktiles};
 }
-int choose_prefill_tile(const glowq_unit* const* units, const int* slices, int n, float* cost) {
-  const float full = prefill_cost_of(units, slices, n, PF_TILE_LARGE), half = prefill_cost_of(units, slices, n, PF_TILE_HALF);
+int choose_prefill_tile(const glowq_unit* const* units, const int* slices, int n, float* cost, bool dealt) {
+  const float full = prefill_cost_of(units, slices, n, PF_TILE_LARGE, dealt), half = prefill_cost_of(units, slices, n, PF_TILE_HALF, dealt);
   *cost = std::min(full, half);
   // Contractions of less than 3072 channels on average keep the smaller tiles: the 12 us that a wide tile's ends take
   // are not covered by another workgroup's products.  So do calls of less than 384 tokens (one or two token tiles,

@@ -252,6 +252,21 @@ def test_third_slices_for_all_units_of_a_launch_or_for_none():
         assert all(route(T, 11008, rows, r=128).k_slices <= 2 for rows in ((5560,) * 2, (4096,), (7848,) * 2))
 
 
+# Short calls with a correction that fewer tokens a tile moved to half-size tiles (us on the batched kernel, on these)
+@pytest.mark.parametrize("T,d_in,d_outs,r,Gs,act", [
+    (172, 3200, (5384,) * 3, 128, 64, "f16"),       # 44.5, 58.9
+    (151, 2048, (5536,) * 2, 128, 128, "f16"),      # 29.9, 43.3
+    (65, 1280, (5576,) * 3, 64, 128, "f16"),        # 20.4, 24.8
+    (94, 2048, (5904,) * 3, 64, 64, "f16"),         # 28.7, 36.7
+    (179, 2048, (5728,) * 3, 64, 128, "f16"),       # 30.9, 39.4
+    (66, 3968, (6040,) * 3, 128, 128, "bf16")])     # 44.7, 54.3
+def test_short_corrected_calls_keep_the_batched_kernel(T, d_in, d_outs, r, Gs, act):
+    a = {"f16": G.GLOWQ_F16, "bf16": G.GLOWQ_BF16}[act]
+    assert route(T, d_in, d_outs, r=r, Gs=Gs, act=a, out=a).kernel == G.GLOWQ_ROUTE_BATCHED
+    layer = decoder_layers(2944, 736, 3072, 1, 67, 128, G.GLOWQ_F16)           # 33.2, 47.0
+    assert {x.kernel for x in G.glowq_debug_route(layer)} == {G.GLOWQ_ROUTE_BATCHED}
+
+
 def test_tile_heights_are_those_of_the_launch():
     for T, height in [(65, 80), (80, 80), (81, 96), (97, 112), (113, 128), (129, 80), (300, 112), (521, 112), (1024, 128)]:
         u = unit(T, 768, (16008,) * 3, act=G.GLOWQ_BF16, out=G.GLOWQ_BF16)
