@@ -778,10 +778,11 @@ static size_t splitk_bytes(const glowq_unit& u, int S) {
 size_t prefill_splitk_bytes(const glowq_unit& u) { return splitk_bytes(u, prefill_k_slices(u)); }
 // A third slice where two are long (77 to 95 K tiles), for calls of one token tile in binary16: a launch of several units
 // ends with its longest slices while the other units' compute units have nothing to do.  Us in two slices and in three, by
-// layer: 4096 / 11008 at 70 / 100 / 128 tokens 64.0, 77.4, 86.3 and 61.7, 69.8, 74.6; 42 layers of 512 to 5120 / 9856 to 12160 4 %
-// faster on average, 5 % slower at most; 36 other launches 6 %, 4 %.  Not past 10240 rows (20 launches: four 15 % slower), for a unit alone (42 of them: 3 % slower on average, 33 % at most),
-// for more K tiles (29 layers of 116 to 127: 1 % slower) and in bfloat16 (its dequantiser fills
-// the compute units that the shorter slices would leave: 71.6 and 72.4 at 100 tokens).
+// layer: 4096 / 11008 at 70 / 100 / 128 tokens 64.0, 77.4, 86.3 and 61.7, 69.8, 74.6; 42 layers of 512 to 5120 / 9856 to
+// 12160 4 % faster on average, 5 % slower at most; 36 other launches 6 % and 4 %.  Not past 10240 rows (20 launches: four
+// 15 % slower), for a unit alone (42 of them: 3 % slower on average, 33 % at most), for more K tiles (29 layers of 116 to
+// 127: 1 % slower) and in bfloat16 (its dequantiser fills the compute units that the shorter slices would leave: 71.6 and
+// 72.4 at 100 tokens).
 static bool third_slice(const glowq_unit& u, int S) {
   const int ktiles = u.d_in / 128;
   if (S != 2 || u.act_dtype != GLOWQ_F16 || u.T > 128 || ktiles <= 76 || ktiles >= 96) return false;
