@@ -1327,15 +1327,14 @@ __device__ inline bool last_of(int* counter, int n) {
 }
 
 // The singular values from the Gram matrix of orthogonal rows (its diagonal), their order (see
-// ranks_before), and P[i][jr] = U~[i][perm jr] sqrt(sigma_jr), the l x r matrix that takes Q to A (Alg. 1, lift and balance)
+// rank_of), and P[i][jr] = U~[i][perm jr] sqrt(sigma_jr), the l x r matrix that takes Q to A (Alg. 1, lift and balance)
 __device__ inline void sort_and_lift(const PassArgs& a, const double* S, int LD) {
   __shared__ double sigma[FZ_SMALL];
   __shared__ int order[FZ_SMALL];
   const int t = threadIdx.x;
   if (t < a.l) {
     const double s = S[t * LD + t];
-    int rank = 0;
-    for (int b = 0; b < a.l; ++b) rank += ranks_before(S[b * LD + b], b, s, t) ? 1 : 0;
+    const int rank = rank_of([&](int b) { return S[b * LD + b]; }, a.l, t);
     const double sg = sqrt(s);
     sigma[rank] = sg;
     order[rank] = t;
@@ -1549,13 +1548,12 @@ __global__ void __launch_bounds__(256) k_row_norms(const double* __restrict__ Bs
   if (threadIdx.x == 0) sig2[blockIdx.x] = s;
 }
 
-// order of the singular values (see ranks_before); one block
+// order of the singular values (see rank_of); one block
 __global__ void __launch_bounds__(256) k_sort_sigma(const double* sig2, int l, double* sigma_sorted, int* perm) {
   const int a = threadIdx.x;
   if (a >= l) return;
   const double s = sig2[a];
-  int rank = 0;
-  for (int b = 0; b < l; ++b) rank += ranks_before(sig2[b], b, s, a) ? 1 : 0;
+  const int rank = rank_of([&](int b) { return sig2[b]; }, l, a);
   sigma_sorted[rank] = sqrt(s);
   perm[rank] = a;
 }

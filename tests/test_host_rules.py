@@ -22,8 +22,7 @@ int main() {
     bool seen[N] = {};
     for (int i = 0, c = code; i < N; ++i, c /= V) s[i] = values[c % V];
     for (int a = 0; a < N; ++a) {
-      int rank = 0;
-      for (int b = 0; b < N; ++b) rank += glowq::ranks_before(s[b], b, s[a], a) ? 1 : 0;
+      const int rank = glowq::rank_of([&](int b) { return s[b]; }, N, a);
       if (rank >= N || seen[rank]) { ++bad; continue; }
       seen[rank] = true;
       sorted[rank] = s[a];
