@@ -370,7 +370,8 @@ enum {
   GLOWQ_ROUTE_TILED = 2,      /* tiled kernel; tile: 0 its large (or wide) tiles, 1 half-size  */
   GLOWQ_ROUTE_MX_ONE = 3,     /* microscaling, one launch                                      */
   GLOWQ_ROUTE_MX_SMALL = 4,   /* microscaling, up to 16 tokens, two launches                   */
-  GLOWQ_ROUTE_MX_TILED = 5    /* microscaling, more tokens; tile: index of its workgroup tile  */
+  GLOWQ_ROUTE_MX_TILED = 5    /* microscaling, more tokens; tile: index of its workgroup tile
+                                 (0: its large or wide ones)                                   */
 };
 typedef struct {
   int32_t launch;      /* index of the launch; units of one launch share it                   */
@@ -387,7 +388,9 @@ glowq_status glowq_debug_mx_route(const glowq_unit* u, glowq_route* route);
 /* glowq_debug_tile_tokens: which tiles of the tiled kernel serve unit i, by the most tokens that they hold: 128, or 256 for
  * the wide ones, which count as large; 0 for a unit that another kernel serves.
  * glowq_debug_tile_height: tokens of the workgroup tiles that the launch is made with, for the tiled kernel (80, 96, 112, 128 or
- * 256) and the batched one (16, 32, 48 or 64); 0 for a unit that another kernel serves. */
+ * 256) and the batched one (16, 32, 48 or 64); 0 for a unit that another kernel serves.
+ * glowq_debug_mx_tile_tokens: the same for a microscaling call (16, 32 or 64 on small tiles, 128, 256 on wide ones). */
+glowq_status glowq_debug_mx_tile_tokens(const glowq_unit* u, int32_t* tokens);
 glowq_status glowq_debug_tile_tokens(const glowq_unit* units, int32_t n_units, int32_t slabs, int32_t* tokens);
 glowq_status glowq_debug_tile_height(const glowq_unit* units, int32_t n_units, int32_t slabs, int32_t* tokens);
 glowq_status glowq_debug_unpack(const void* w_prepared, int32_t d_out, int32_t d_in,

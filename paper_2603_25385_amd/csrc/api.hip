@@ -667,6 +667,13 @@ glowq_status glowq_debug_mx_route(const glowq_unit* u, glowq_route* route) {
   mx_route(*u, route);
   return GLOWQ_OK;
 }
+glowq_status glowq_debug_mx_tile_tokens(const glowq_unit* u, int32_t* tokens) {
+  glowq_status s = validate_mx(u, false, false);
+  if (s != GLOWQ_OK) return s;
+  if (!tokens || !u->modules) return GLOWQ_ERR_NULL;
+  *tokens = mx_tile_tokens(*u);
+  return GLOWQ_OK;
+}
 
 glowq_status glowq_debug_unpack(const void* w_prepared, int32_t d_out, int32_t d_in,
                                 int32_t group_size, uint8_t* q_out, void* stream) {

@@ -29,9 +29,9 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
 FILE_FLAGS = {"decode.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 # Kernels that count their own outstanding memory operations (hand-placed s_waitcnt): a
 # register spill would add loads of the compiler's to that count, so they must have none.
-NO_SPILL = ("k_prefill", "k_wide")
+NO_SPILL = ("k_prefill", "k_wide", "k_mx_wide")
 # ... and whose sums live in accumulation registers on purpose (no load writes those)
-ACC_REGS = ("k_wide",)
+ACC_REGS = ("k_wide", "k_mx_wide")
 
 
 def check_no_spills(src: str, remarks: str) -> None:
@@ -53,16 +53,18 @@ def check_no_spills(src: str, remarks: str) -> None:
 
 
 # Kernels whose products are assembly: the compiler places no wait states around them.
-ASM_PRODUCTS = {"prefill.hip": "k_wide"}
+ASM_PRODUCTS = {"prefill.hip": "k_wide", "mx.hip": "k_mx_wide"}
+# ... and whose sums are accumulation registers named by number: nothing else may live there
+NAMED_SUMS = ("k_mx_wide",)
 OPERAND_STATES = 2       # from a vector-ALU write of an operand (a sum) to the product
 SUM_STATES = 18          # from a product to anything else that names its sum
 
 
 def _registers(operand: str) -> set:
-    m = re.fullmatch(r"([va])(?:(\d+)|\[(\d+):(\d+)\])", operand.strip())
+    m = re.fullmatch(r"([va])(?:(\d+)|\[(\w+)(?::(\w+))?\])", operand.strip())
     if not m:
         return set()
-    lo, hi = (int(m[2]), int(m[2])) if m[2] else (int(m[3]), int(m[4]))
+    lo, hi = (int(m[2]), int(m[2])) if m[2] else (int(m[3], 0), int(m[4] or m[3], 0))
     return {(m[1], k) for k in range(lo, hi + 1)}
 
 
@@ -118,7 +120,7 @@ def check_products(src: str, assembly: str, kernel: str) -> int:
             count += 1
             if ops[0] != ops[3]:
                 raise RuntimeError(f"{src}: {names[k]}: a product does not add in place")
-            reads = set().union(*map(_registers, ops[1:]))
+            reads = set().union(*(_registers(o.split(" ")[0]) for o in ops[1:]))
             for j, _ in before(k, OPERAND_STATES):
                 if ins[j][0].startswith("v_") and not ins[j][0].startswith("v_mfma"):
                     wrote = set().union(*map(_registers, ins[j][1][:2 if "swap" in ins[j][0] else 1]))
@@ -126,6 +128,9 @@ def check_products(src: str, assembly: str, kernel: str) -> int:
                         fail(k, j, "follows too closely the write of its operand")
         else:
             mine = {r for o in ops for r in _registers(o.split(" ")[0]) if r[0] == "a"}
+            if mine and any(n in names[k] for n in NAMED_SUMS):
+                if name != "v_accvgpr_read_b32" and (name, ops[1:]) != ("v_accvgpr_write_b32", ["0"]):
+                    raise RuntimeError(f"{src}: {names[k]}: '{name} {', '.join(ops)}' touches a sum")
             for j, _ in before(k, SUM_STATES) if mine else ():
                 if product(j) and _registers(ins[j][1][0]) & mine:
                     fail(k, j, "uses too early the sum")

@@ -76,6 +76,7 @@ hipError_t launch_mx_quantize_x(const void* X, int T, int d_in, int act, uint8_t
                                 hipStream_t st);
 hipError_t launch_mx_forward(const glowq_unit& u, bool restore, char* workspace, hipStream_t st);
 void mx_route(const glowq_unit& u, glowq_route* route);
+int mx_tile_tokens(const glowq_unit& u);      // tokens of the call's workgroup tiles (0: not tiled)
 // slices' start offsets in units of 256 bytes (every slice is 256-byte aligned)
 constexpr int STATUS_BATCH = 256;
 struct StatusBatch {

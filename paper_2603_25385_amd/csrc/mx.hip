@@ -23,10 +23,12 @@
 #include <cmath>
 #include "common.hpp"
 #include "launch.hpp"
+#include "wide.hpp"
 #include "proj_device.hpp"
 
 namespace glowq {
 
+typedef int v4i_t __attribute__((ext_vector_type(4)));
 typedef int v8i_t __attribute__((ext_vector_type(8)));
 
 // ---------------------------------------------------------------------------------------
@@ -558,11 +560,9 @@ __global__ void __launch_bounds__(256, 4) k_mx_decode_small(MxArgs a, ProjArgs p
 // multiplies step k, waits for its own loads and meets the others at one barrier.  No
 // register holds staged data, three workgroups share a CU.  (Three buffers with the loads
 // two steps ahead, two workgroups per CU: no faster.)  Smaller tiles for launches that this one would not fill:
-// k_mx_tile, see choose_mx_tile.  What bounds it: the instruction itself delivers 4.9 PFLOP/s from
-// registers (32 cycles for fp8 x fp4), this kernel 2.07: waves of 64 x 64 read 96 of the 128 bytes that LDS
-// delivers a cycle (matrix pipe busy 0.55), and the clock falls to 1.8 GHz under the load.  Tiles of 256 x 256 (256
-// accumulation registers, one wave per SIMD, a ring of three, workgroups that go from tile to tile) gain 4 % here and
-// up to 15 % on several times the work, and lose as much where their rounds come out uneven: not kept.
+// k_mx_tile, see choose_mx_tile; larger ones for launches that fill the chip with them: k_mx_wide.  What bounds it: the
+// instruction itself delivers 4.9 PFLOP/s from registers (32 cycles for fp8 x fp4), this kernel 2.07: waves of 64 x 64 read
+// 96 of the 128 bytes that LDS delivers a cycle (matrix pipe busy 0.55), and the clock falls to 1.8 GHz under the load.
 // Weights are the first operand, so that a lane ends up with four rows of one token; two row blocks' rows are
 // exchanged between lane groups so that sixteen tokens' stores are 64 bytes each (2-byte stores, 32 bytes a
 // row: the call with 2 x 11008 rows x 4096 at 2048 tokens 210 -> 200 us with it).  Both tiles sit
@@ -574,7 +574,7 @@ __global__ void __launch_bounds__(256, 4) k_mx_decode_small(MxArgs a, ProjArgs p
 // touches its own outputs only, and those are not stored).  The correction (R from the first
 // launch, in the activation type) is r / 32 more 16-bit instructions per accumulator tile in the epilogue.
 // ---------------------------------------------------------------------------------------
-constexpr int MXG_TOK = 128, MXG_ROWS = 128;
+constexpr int MXG_TOK = 128;
 constexpr int MXG_A = 0, MXG_B = 16384, MXG_ASC = 24576, MXG_BSC = 25088, MXG_BUF = 25600;   // byte offsets in a buffer
 constexpr int MXG_DEPTH = 2;      // LDS buffers
 
@@ -880,6 +880,10 @@ __global__ void __launch_bounds__(NW * 64, (MxTileShape<MB, RB, RW, NW>::WGS * N
   }
 }
 
+}  // namespace glowq
+#include "mx_wide.hpp"
+namespace glowq {
+
 // First launch of a call of more than 16 tokens: the leading workgroups compute R = X B^T (16
 // tokens, 32 ranks, a K slice each: a lone workgroup reads its operands at about 50 GB/s, so a long
 // contraction in one piece took 27 us), the others quantise the activations.  (As three launches,
@@ -979,9 +983,9 @@ constexpr int MX_N_TILES = sizeof(MX_TILES) / sizeof(MX_TILES[0]);
 constexpr int MX_RESIDENT[] = {3, MxTileShape<1, 1, 4, 4>::WGS, MxTileShape<2, 1, 4, 8>::WGS, MxTileShape<2, 2, 4, 4>::WGS,
                                MxTileShape<4, 2, 4, 4>::WGS};
 
-static int choose_mx_tile(const glowq_unit& u) {
+static int choose_mx_tile(const glowq_unit& u, double* best_cost = nullptr) {
   int best = 0;
-  double cost = 0.0;
+  double cost = 0.0, weighed = 0.0;
   for (int i = 0; i < MX_N_TILES; ++i) {
     const MxTile& t = MX_TILES[i];
     const int ks = i == 0 ? 1 : t.nw / t.rw, tok = 16 * t.mb, rows = 16 * t.rb * t.rw;
@@ -991,12 +995,34 @@ static int choose_mx_tile(const glowq_unit& u) {
     const double share = per_cu <= MX_RESIDENT[i] ? std::ceil(per_cu) * t.busy : per_cu * t.busy + 0.8 * t.chain;
     const double stages = (u.d_in / 128 + ks - 1) / ks + t.ends + (u.out_dtype == GLOWQ_F32 ? t.ends32 : 0.0);
     const double c = stages * std::max((double)t.chain, share);
-    if (i == 0 || c < cost) {
+    if (i == 0 || c < weighed) {
       best = i;
-      cost = i == 0 ? 0.9 * c : c;
+      cost = c;
+      weighed = i == 0 ? 0.9 * c : c;
     }
   }
+  if (best_cost) *best_cost = cost;
   return best;
+}
+// Wide tiles (k_mx_wide) against the best of the others, in us: a round of 256 tiles costs 1.29 per K tile, a last one that
+// is partly empty from 0.85 on (the clock rises), a tile's ends seven K tiles and 3.4 more with 32-bit outputs, beside 10.7
+// for the launch and the first loads; what the other tiles cost is theirs and 9.  From 190 calls of 150 to 3000 tokens that
+// have 48 wide tiles and more (mean error 6 and 11 %).  Contractions of less than 2048 channels keep the other tiles: a
+// wide tile's ends are not covered by another workgroup's products, and 11 of 14 calls that lost had fewer.  Restored or
+// not does not enter.
+static bool choose_mx_wide(const glowq_unit& u) {
+  const int ktiles = u.d_in / 128;
+  if (ktiles < 16) return false;
+  long long tiles = 0;
+  for (int m = 0; m < u.n_modules; ++m) {
+    if (u.modules[m].ldy >= 1 << 22) return false;        // (32-bit offsets within a tile's outputs)
+    tiles += (long long)((u.modules[m].d_out + MXW_TOK - 1) / MXW_TOK) * ((u.T + MXW_TOK - 1) / MXW_TOK);
+  }
+  const double ends = ktiles + 7.0 + (u.out_dtype == GLOWQ_F32 ? 3.4 : 0.0), tail = (double)(tiles % 256) / 256.0;
+  const double wide = 10.7 + ends * (1.29 * (double)(tiles / 256) + (tail > 0.0 ? 0.85 + 0.44 * tail : 0.0));
+  double others;
+  choose_mx_tile(u, &others);
+  return wide < 0.95 * (others + 9.0);
 }
 
 template <int ACT, int I>
@@ -1036,7 +1062,8 @@ static hipError_t launch_mx_gemm(const glowq_unit& u, bool restore, char* worksp
   if (f16) k_mx_front_tiles<ACT_F16><<<fgrid, dim3(MX_FRONT_THREADS), 0, st>>>(fa);
   else k_mx_front_tiles<ACT_BF16><<<fgrid, dim3(MX_FRONT_THREADS), 0, st>>>(fa);
   const int ti = choose_mx_tile(u);
-  const int tile_tok = 16 * MX_TILES[ti].mb, tile_rows = 16 * MX_TILES[ti].rb * MX_TILES[ti].rw;
+  const bool wide = choose_mx_wide(u);
+  const int tile_tok = wide ? MXW_TOK : 16 * MX_TILES[ti].mb, tile_rows = wide ? MXW_TOK : 16 * MX_TILES[ti].rb * MX_TILES[ti].rw;
   MxGemmArgs a;
   a.n_modules = u.n_modules;
   a.tok_tiles = (u.T + tile_tok - 1) / tile_tok;
@@ -1058,7 +1085,11 @@ static hipError_t launch_mx_gemm(const glowq_unit& u, bool restore, char* worksp
   a.R16 = corrected ? fa.R16 : nullptr;
   a.T = u.T; a.d_in = u.d_in; a.r = u.r;
   a.out_f32 = u.out_dtype == GLOWQ_F32;
-  if (ti > 0) {
+  if (wide) {
+    dim3 grid((unsigned)std::min(blocks, 256));
+    if (f16) k_mx_wide<ACT_F16><<<grid, dim3(256), 0, st>>>(a, blocks);
+    else k_mx_wide<ACT_BF16><<<grid, dim3(256), 0, st>>>(a, blocks);
+  } else if (ti > 0) {
     if (f16) launch_mx_tile<ACT_F16, 1>(a, ti, blocks, st);
     else launch_mx_tile<ACT_BF16, 1>(a, ti, blocks, st);
   } else if (f16) k_mx_gemm<ACT_F16><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(a);
@@ -1121,11 +1152,15 @@ static hipError_t launch_mx_small(const glowq_unit& u, bool restore, char* works
   return hipGetLastError();
 }
 
+int mx_tile_tokens(const glowq_unit& u) {
+  return u.T <= MX_MAX_TOKENS ? 0 : choose_mx_wide(u) ? MXW_TOK : 16 * MX_TILES[choose_mx_tile(u)].mb;
+}
+
 void mx_route(const glowq_unit& u, glowq_route* route) {
   *route = glowq_route{0, GLOWQ_ROUTE_MX_SMALL, 0, 1, 0};
   if (u.T > MX_MAX_TOKENS) {
     route->kernel = GLOWQ_ROUTE_MX_TILED;
-    route->tile = choose_mx_tile(u);
+    route->tile = choose_mx_wide(u) ? 0 : choose_mx_tile(u);
   } else if (mx_one_launch(u)) {
     route->kernel = GLOWQ_ROUTE_MX_ONE;
     route->wait_polls = MXS_WAIT_POLLS;

@@ -19,6 +19,7 @@
 #include <algorithm>
 #include "common.hpp"
 #include "launch.hpp"
+#include "wide.hpp"
 
 namespace glowq {
 
@@ -84,14 +85,6 @@ struct PrefillArgs {
   int out_f32;
 };
 
-
-// a pointer that is the same in every lane, moved to scalar registers
-template <typename T> __device__ inline T* uniform_ptr(T* p) {
-  const unsigned long long v = (unsigned long long)p;
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return (T*)(((unsigned long long)hi << 32) | lo);
-}
 
 // The end of a projection tile of 16 MB tokens: its part of R leaves the accumulators (lane: token (mb, n), ranks
 // 16 (wave RBP + b) + 4 kq + {0..3}); see proj_tile.  lds_word: four bytes of LDS that nobody else uses.

@@ -16,17 +16,8 @@
 // channels takes 151 (binary16) and 161 (bfloat16) of the 131 thousand cycles that its products need, at 1.7 to
 // 1.8 GHz: the chip's power sets the clock, and the same loop without the dequantiser is 12 to 17 % faster.
 #pragma once
-#include <utility>
 
 namespace glowq {
-
-// f(0), f(1), .. f(N - 1) with compile-time indexes (the K tile's body is past what `#pragma unroll` unrolls)
-template <class F, int... I> __device__ __attribute__((always_inline)) inline void for_each_index(F f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, class F> __device__ __attribute__((always_inline)) inline void for_each_index(F f) {
-  for_each_index(f, std::make_integer_sequence<int, N>{});
-}
 
 constexpr int WD_WAVES = 4, WD_RB = 4, WD_MB = 16;          // 16-row blocks per wave, 16-token blocks per tile
 constexpr int WD_TOK = 16 * WD_MB, WD_BLOCKS = WD_WAVES * WD_RB;
@@ -35,16 +26,6 @@ constexpr int WD_STAGE = WD_TOK * 64 * 2;                   // bytes of a stage 
 constexpr int WD_WSTG = WD_RB * 1024 + 512;                 // bytes of a wave's weight stage
 constexpr int WD_LDS = WD_RING * WD_STAGE + WD_WAVES * WD_WSTG;
 
-// Direct global -> LDS loads with a uniform base and a 32-bit byte offset per lane: no vector-ALU address arithmetic
-__device__ inline void lds_dma16_off(const void* base, uint32_t off, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base), "s"(lds_base) : "memory", "m0");
-}
-__device__ inline void lds_dma16_off_coherent(const void* base, uint32_t off, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 sc1" : : "v"(off), "s"(base), "s"(lds_base) : "memory", "m0");
-}
-__device__ inline void lds_dma4_off(const void* base, uint32_t off, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" : : "v"(off), "s"(base), "s"(lds_base) : "memory", "m0");
-}
 // The same with a product between the write of m0 and the load that reads it
 template <int ACT, int IMM> __device__ inline void mfma_dma16(float4_t& acc, u32x4_t a, u32x4_t b, const void* base, uint32_t off, uint32_t lds_base) {
   if constexpr (ACT == ACT_F16)
@@ -62,21 +43,6 @@ template <int ACT, int IMM> __device__ inline void mfma_dma4(float4_t& acc, u32x
     asm volatile("s_add_u32 m0, %5, %6\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\tglobal_load_lds_dword %3, %4"
                  : "+a"(acc) : "v"(a), "v"(b), "v"(off), "s"(base), "s"(lds_base), "n"(IMM) : "memory", "m0", "scc");
 }
-// LDS reads that the compiler sees (it places their waits; the direct loads above are unknown to it)
-__device__ inline u32x4_t lds16(uint32_t addr) { return *(const __attribute__((address_space(3))) u32x4_t*)addr; }
-__device__ inline uint32_t lds4(uint32_t addr) { return *(const __attribute__((address_space(3))) uint32_t*)addr; }
-
-// acc += a x b with the sum in accumulation registers, in place.  As assembly: around the builtin the register
-// allocator moves the sums about (three copies per product).  It does not see the instruction's hazards either: an
-// operand has to be written two instructions ahead by the vector ALU, a sum to rest before it is read (acc_settle).
-// build.py reads the listing of every build for both.
-template <int ACT> __device__ inline void mfma_acc(float4_t& acc, u32x4_t a, u32x4_t b) {
-  if constexpr (ACT == ACT_F16) asm("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
-  else asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
-}
-__device__ inline void acc_settle() { asm volatile("s_nop 15\n\ts_nop 15"); }
-__device__ inline void acc_settled(float4_t& acc) { asm volatile("" : "+a"(acc)); }     // nothing that reads it moves above
-
 // Instructions that the slots before slot `end` of step j have room for beside their product, operand read, wait
 // and direct load
 template <int NWL> constexpr int wide_room(int j, int end) {

@@ -44,3 +44,26 @@ def test_hazards_are_found(lines):
 
 def test_other_kernels_are_left_to_the_compiler():
     assert check("v_mov_b32_e32 v7, v1", PRODUCT, kernel="k_other") == 0
+
+
+NAMED = "v_mfma_scale_f32_16x16x128_f8f6f4 a[64:0x43], v[4:7], v[8:15], a[64:0x43], v1, v2 op_sel_hi:[0,0,0] cbsz:4"
+
+
+@pytest.mark.parametrize("lines,ok", [
+    (("v_accvgpr_write_b32 a[0x43], 0", "s_nop 1", NAMED, "s_nop 15", "s_nop 15", "v_accvgpr_read_b32 v1, a[0x42]"), True),
+    ((NAMED, "s_nop 15", "v_accvgpr_read_b32 v1, a[0x42]"), False),                # too early
+    (("v_accvgpr_write_b32 a[0x43], 0", NAMED), False),
+    (("v_mov_b32_e32 v2, v9", "s_nop 0", NAMED), False),                           # a block scale
+    (("v_accvgpr_write_b32 a9, v1", "s_nop 15", "s_nop 15", NAMED), False),        # something else in a sum's register
+    (("ds_read_b128 a[0:3], v1", "s_nop 15", "s_nop 15", NAMED), False),
+])
+def test_sums_that_are_named_by_number(lines, ok):
+    def run():
+        text = "_Z9k_mx_wide:\n" + "".join(f"\t{l}\n" for l in lines) + "\ts_endpgm\n"
+        return hip_build.check_products("x.hip", text, "k_mx_wide")
+
+    if ok:
+        assert run() == 1
+    else:
+        with pytest.raises(RuntimeError):
+            run()

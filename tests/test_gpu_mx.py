@@ -320,3 +320,20 @@ def test_tiled_calls_in_a_row_with_a_sliced_projection(T, d_in, r):
         for _ in range(50):
             G.glowq_mx_group_forward(du.desc, 1, du.ws.data_ptr(), du.ws_bytes, stream())
         assert all(np.array_equal(a, b) for a, b in zip(first, du.forward(True)))
+
+
+# wide tiles (256 x 256, asked of the library): ragged tokens, rows that end in the middle of a block pair and of a wave's
+# half, odd and even counts of K tiles, ranks with and without whole steps of 32, a second tile per workgroup in the stream
+@pytest.mark.parametrize("act,T,d_in,d_outs,r,out", [
+    ("f16", 440, 2048, (8312, 8312), 64, "act"), ("bf16", 929, 2176, (6104, 6232), 72, "f32"),
+    ("bf16", 1173, 2048, (7472, 7368), 128, "act"), ("f16", 1425, 2304, (4056, 4184), 24, "f32")])
+def test_wide_tiles(act, T, d_in, d_outs, r, out):
+    u = make_unit(UnitShape("g", d_in, d_outs), T, r, act, seed=51)
+    du = MxDeviceUnit(u, out=out)
+    assert G.glowq_debug_mx_tile_tokens(du.desc) == 256 and G.glowq_debug_mx_route(du.desc).tile == 0
+    for restore in (True, False):
+        got = du.forward(restore)
+        for g, y in zip(got, MX.mx_group_forward(u, restore)):
+            assert np.isfinite(g).all() and rel_err(g, y) <= TOL + (ULP[act] if out == "act" else 0.0)
+    again = du.forward(False)
+    assert all(np.array_equal(a, b) for a, b in zip(got, again))
