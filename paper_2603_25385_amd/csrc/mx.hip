@@ -66,14 +66,14 @@ __device__ inline float act16_f32(uint32_t h) {
 }
 
 // Sixteen consecutive channels of one token (lo, hi: their 16-bit patterns), half of an MX
-// block; the other half is with the neighbouring lane (lane ^ 1), so both lanes of a pair
+// block; the other half is with the lane `lane ^ OTHER`, so both lanes of a pair
 // must call this together.  Returns the sixteen E4M3 codes and the block's E8M0 scale code.
 // Everything is exact but the one rounding to E4M3: the block maximum through the integer
 // patterns of the magnitudes (they order as the values do), the values as fp32, the division
 // by the power of two as a product, the clamp to +-448 (a scaled magnitude lies below 512),
 // and the rounding itself by the conversion instruction (nearest even, subnormal codes kept,
 // a zero keeps its sign bit, which the product ignores: the stored code of a zero is +0).
-template <int ACT>
+template <int ACT, int OTHER = 1>
 __device__ inline void mx_quantize16(const u32x4_t lo, const u32x4_t hi, u32x4_t& codes, int& scale_code) {
   typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
   u16x2_t mm = {0, 0};
@@ -83,7 +83,7 @@ __device__ inline void mx_quantize16(const u32x4_t lo, const u32x4_t hi, u32x4_t
     mm = __builtin_elementwise_max(mm, __builtin_elementwise_max(a, c));
   }
   uint32_t m16 = max((uint32_t)mm[0], (uint32_t)mm[1]);
-  m16 = max(m16, (uint32_t)__shfl_xor((int)m16, 1, 64));
+  m16 = max(m16, (uint32_t)__shfl_xor((int)m16, OTHER, 64));
   int shared = 0;
   if (m16 != 0u) {
     const uint32_t mmax = __builtin_bit_cast(uint32_t, act16_f32<ACT>(m16));
@@ -884,29 +884,115 @@ __global__ void __launch_bounds__(NW * 64, (MxTileShape<MB, RB, RW, NW>::WGS * N
 #include "mx_wide.hpp"
 namespace glowq {
 
-// First launch of a call of more than 16 tokens: the leading workgroups compute R = X B^T (16
-// tokens, 32 ranks, a K slice each: a lone workgroup reads its operands at about 50 GB/s, so a long
-// contraction in one piece took 27 us), the others quantise the activations.  (As three launches,
-// the quantiser, the projection's slices and their sum, this took 11 to 15 us.)
+// First launch of a call of more than 16 tokens: the activations' codes and R = X B^T from one read of X.  A workgroup
+// takes 16 or 32 tokens, a K slice and some of the ranks, its waves the slice's K tiles in turn.  A wave holds X as the quantiser wants it
+// (lane (token, g): channels 64 half + 16 g .. + 16 of the tile), which is an operand of the 16-bit instruction as it
+// stands when B's channels are taken in the same order; the codes of a half leave as one contiguous KiB.
 struct MxFrontTiles {
-  ProjSliced p;              // p.B NULL when not restored
+  const uint16_t* X;
+  const uint16_t* B;         // act dtype [r][d_in], or NULL when not restored
+  unsigned long long* slots; // {fp32, launch tag} of the slices' partial sums: (t ksplit + slice) r + rank (ksplit > 1 only)
   uint16_t* R16;             // act dtype [T][r]
   uint8_t* xcodes;
   uint8_t* xscales;
-  int n_proj;
+  int T, d_in, r;
+  int ksplit, slice_tiles;   // slices of K, K tiles per slice
+  int groups;                // of 16 NB ranks; the first one's workgroups store the codes
 };
 
-template <int ACT>
-__global__ void __launch_bounds__(MX_FRONT_THREADS) k_mx_front_tiles(MxFrontTiles a) {
-  __shared__ float part[MX_FRONT_THREADS / 64 * PROJ_NB * 256];
-  if ((int)blockIdx.x >= a.n_proj) {
-    mx_quantize_block<ACT, true>(a.p.X, a.p.T, a.p.K, a.xcodes, a.xscales,
-                                 (long long)((int)blockIdx.x - a.n_proj) * MX_FRONT_THREADS + threadIdx.x);
-    return;
+// NB: 16-rank blocks of a workgroup (0: codes only), TB: 16-token blocks, NW: waves
+template <int ACT, int NB, int TB, int NW>
+__global__ void __launch_bounds__(NW * 64) k_mx_front_tiles(MxFrontTiles a) {
+  const int l = threadIdx.x & 63, i = l & 15, g = l >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int kz = (int)blockIdx.x % a.ksplit, rest = (int)blockIdx.x / a.ksplit;
+  const int rank0 = rest % a.groups * 16 * NB, tb0 = rest / a.groups * TB;
+  const int ktiles = a.d_in / 128, k_end = min(ktiles, (kz + 1) * a.slice_tiles);
+  const uint16_t* xrow[TB];      // tokens past T (ranks past r): the last one again, not stored
+#pragma unroll
+  for (int t = 0; t < TB; ++t) xrow[t] = a.X + (size_t)min((tb0 + t) * 16 + i, a.T - 1) * a.d_in + 16 * g;
+  const uint16_t* brow[NB > 0 ? NB : 1];
+  float4_t acc[NB > 0 ? NB : 1][TB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    brow[nb] = a.B + (size_t)min(rank0 + nb * 16 + i, a.r - 1) * a.d_in + 16 * g;
+#pragma unroll
+    for (int t = 0; t < TB; ++t) acc[nb][t] = float4_t{0.f, 0.f, 0.f, 0.f};
   }
-  proj_sliced<ACT, MX_FRONT_THREADS / 64>(a.p, (int)blockIdx.x, part, [&](int t, int rank, uint32_t pair, uint32_t) {
-    ((uint32_t*)a.R16)[((long long)t * a.p.r + rank) >> 1] = pair;
-  });
+  for (int kt = kz * a.slice_tiles + w; kt < k_end; kt += NW) {
+    u32x4_t x[TB][2][2];         // [token block][half][eight channels]
+#pragma unroll
+    for (int t = 0; t < TB; ++t)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) x[t][h][e] = *(const u32x4_t*)(xrow[t] + (size_t)kt * 128 + 64 * h + 8 * e);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      u32x4_t b[NB > 0 ? NB : 1][2];
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) b[nb][e] = *(const u32x4_t*)(brow[nb] + (size_t)kt * 128 + 64 * h + 8 * e);
+#pragma unroll
+      for (int t = 0; t < TB; ++t) {
+        if (rank0 > 0) continue;       // uniform
+        u32x4_t c;
+        int sc;
+        mx_quantize16<ACT, 16>(x[t][h][0], x[t][h][1], c, sc);
+        if ((tb0 + t) * 16 + i < a.T) {
+          const size_t tile = (size_t)(tb0 + t) * ktiles + kt;
+          *(u32x4_t*)(a.xcodes + (tile * 2 + h) * 1024 + l * 16) = c;
+          if (!(g & 1)) a.xscales[tile * 64 + i + 16 * (2 * h + (g >> 1))] = (uint8_t)sc;
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+          for (int t = 0; t < TB; ++t) acc[nb][t] = mfma16<ACT>(x[t][h][e], b[nb][e], acc[nb][t]);   // D[token][rank]
+    }
+  }
+  if constexpr (NB > 0) {
+    // the waves' sums meet in LDS: [wave][token block][rank block][4][lane]; then thread -> (token, pair of ranks)
+    __shared__ float part[NW * TB * NB * 256];
+    constexpr int PAIRS = TB * 16 * NB * 8, NP = (PAIRS + NW * 64 - 1) / (NW * 64);
+    const uint32_t tag = (uint32_t)(launch_tag() & 0xffffffffull);
+#pragma unroll
+    for (int t = 0; t < TB; ++t)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) part[(((w * TB + t) * NB + nb) * 4 + v) * 64 + l] = acc[nb][t][v];
+    __syncthreads();
+    float s[NP][2];
+    unsigned long long* slot[NP];
+    int tok[NP], rank[NP];
+    bool live[NP];
+#pragma unroll
+    for (int n = 0; n < NP; ++n) {
+      const int p = (int)threadIdx.x + n * NW * 64, tl = p / (NB * 8) & 15, t = p / (NB * 8) >> 4;
+      rank[n] = rank0 + p % (NB * 8) * 2;
+      tok[n] = (tb0 + t) * 16 + tl;
+      live[n] = p < PAIRS && tok[n] < a.T && rank[n] < a.r;
+      slot[n] = a.slots + (size_t)tok[n] * a.ksplit * a.r + rank[n];
+      s[n][0] = s[n][1] = 0.f;
+      if (!live[n]) continue;
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int rl = rank[n] - rank0 + e, ln = (rl & 15) + 16 * (tl >> 2);
+#pragma unroll
+        for (int q = 0; q < NW; ++q) s[n][e] += part[(((q * TB + t) * NB + (rl >> 4)) * 4 + (tl & 3)) * 64 + ln];
+      }
+      if (a.ksplit > 1) publish_slice(slot[n], kz, a.r, tag, s[n]);
+    }
+    if (a.ksplit > 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // (counts stores, too)
+#pragma unroll
+    for (int n = 0; n < NP; ++n)
+      if (live[n] && (a.ksplit == 1 || look_at_slices(slot[n], a.ksplit, a.r, tag, s[n])))
+        ((uint32_t*)a.R16)[((size_t)tok[n] * a.r + rank[n]) >> 1] = (uint32_t)to_act16<ACT>(s[n][0]) | ((uint32_t)to_act16<ACT>(s[n][1]) << 16);
+  }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1032,14 +1118,52 @@ static void launch_mx_tile(const MxGemmArgs& a, int tile, int n_wgs, hipStream_t
   if constexpr (I + 1 < MX_N_TILES) launch_mx_tile<ACT, I + 1>(a, tile, n_wgs, st);
 }
 
-// K slices of the projection: the sum over slices costs about 3 us more than a slice's own work, so
-// only contractions past 4096 channels are cut, in slices of about 2048, at most four (the area
-// of partial sums holds their slots) and no more than 256 workgroups
-static int mx_proj_slices(const glowq_unit& u, int* kslice) {
-  const int pieces16 = (u.T + 15) / 16 * std::max(1, (u.r + 31) / 32);
-  const int want = u.d_in <= 4096 ? 1 : std::max(1, std::min(std::min(4, (u.d_in + 2047) / 2048), 256 / pieces16));
-  *kslice = (u.d_in / 32 + want - 1) / want * 32;
-  return (u.d_in + *kslice - 1) / *kslice;
+// The shape of that launch: what a workgroup takes.  A K tile costs a wave its operands (0.4 for a token block, 0.5 for a
+// rank block, a quarter of that more for a second token block), more workgroups than 200 share compute units, and slices
+// meet at a price of 0.5 (us; at most four of them: the area of partial sums holds their slots).  Fitted to 120 calls of
+// 20 to 2048 tokens, 1024 to 14336 channels and 16 to 128 ranks on every shape: 0.9 % above the best one on average, and
+// 22 % below what three kinds of workgroups took that each read X for themselves (2048 tokens x 4096, r = 64, 18 -> 15 us;
+// x 14336 62 -> 30).  Sixteen waves where eight would take three K tiles or more each and few workgroups are at work.
+struct MxFrontShape {
+  int tb, nb, waves, ksplit, slice_tiles;
+};
+static MxFrontShape choose_mx_front(const glowq_unit& u, bool corrected) {
+  const int ktiles = u.d_in / 128, tokens16 = (u.T + 15) / 16, blocks = corrected ? (u.r + 15) / 16 : 0;
+  auto sliced = [&](int tb, int nb, int waves, int want) {
+    const int tiles = (ktiles + want - 1) / want;
+    return MxFrontShape{tb, nb, waves, (ktiles + tiles - 1) / tiles, tiles};
+  };
+  // codes alone: a K tile per wave as long as that is not too many workgroups
+  if (blocks == 0) return sliced(1, 0, 8, std::max(1, std::min((ktiles + 7) / 8, 1024 / tokens16)));
+  const int top = blocks <= 2 ? 2 : blocks <= 4 ? 4 : 8;
+  MxFrontShape best{};
+  double cost = 0.0;
+  for (int tb = 1; tb <= 2; ++tb)
+    for (int nb = 2; nb <= top; nb *= 2)
+      for (int waves = 8; waves <= (tb == 1 && nb == 2 ? 16 : 8); waves += 8)
+        for (int want = 1; want <= std::min(4, ktiles); want *= 2) {
+          const MxFrontShape s = sliced(tb, nb, waves, want);
+          const double wgs = (double)((tokens16 + tb - 1) / tb) * ((blocks + nb - 1) / nb) * s.ksplit * (waves / 8);
+          const double tile = 0.4 * tb + 0.5 * nb * (tb == 2 ? 1.25 : 1.0);
+          const double c = (waves == 16 ? 0.5 : 0.0) + (s.ksplit > 1 ? 0.5 : 0.0) +
+                           (s.slice_tiles + waves - 1) / waves * tile * (1.0 + 0.9 * std::max(0.0, wgs / 200.0 - 1.0));
+          if (best.tb == 0 || c < cost) {
+            best = s;
+            cost = c;
+          }
+        }
+  return best;
+}
+template <int ACT, int NB, int TB, int NW> static void launch_mx_front_n(const MxFrontTiles& a, hipStream_t st) {
+  const dim3 grid((unsigned)((a.T + 16 * TB - 1) / (16 * TB) * a.groups * a.ksplit));
+  k_mx_front_tiles<ACT, NB, TB, NW><<<grid, dim3(NW * 64), 0, st>>>(a);
+}
+template <int ACT> static void launch_mx_front(const MxFrontTiles& a, const MxFrontShape& s, hipStream_t st) {
+  if (s.nb == 0) launch_mx_front_n<ACT, 0, 1, 8>(a, st);
+  else if (s.nb == 2 && s.waves == 16) launch_mx_front_n<ACT, 2, 1, 16>(a, st);
+  else if (s.nb == 2) s.tb == 1 ? launch_mx_front_n<ACT, 2, 1, 8>(a, st) : launch_mx_front_n<ACT, 2, 2, 8>(a, st);
+  else if (s.nb == 4) s.tb == 1 ? launch_mx_front_n<ACT, 4, 1, 8>(a, st) : launch_mx_front_n<ACT, 4, 2, 8>(a, st);
+  else s.tb == 1 ? launch_mx_front_n<ACT, 8, 1, 8>(a, st) : launch_mx_front_n<ACT, 8, 2, 8>(a, st);
 }
 
 static hipError_t launch_mx_gemm(const glowq_unit& u, bool restore, char* workspace, hipStream_t st) {
@@ -1048,19 +1172,20 @@ static hipError_t launch_mx_gemm(const glowq_unit& u, bool restore, char* worksp
   uint8_t* xscales = (uint8_t*)(workspace + w.off_xscales);
   const bool corrected = restore && u.r > 0, f16 = u.act_dtype == GLOWQ_F16;
   const UnitWorkspace uw = plan_unit_workspace(u, workspace);
-  int kslice = 0;
-  const int ksplit = mx_proj_slices(u, &kslice);
   MxFrontTiles fa;
-  fa.p = ProjSliced{(const uint16_t*)u.X, corrected ? (const uint16_t*)u.B : nullptr, (float*)(uw.base + uw.off_rpart),
-                    u.T, u.d_in, u.r, ksplit, kslice, false};
+  fa.X = (const uint16_t*)u.X;
+  fa.B = corrected ? (const uint16_t*)u.B : nullptr;
+  fa.slots = (unsigned long long*)(uw.base + uw.off_rpart);
   fa.R16 = (uint16_t*)(uw.base + uw.off_r16);
   fa.xcodes = xcodes;
   fa.xscales = xscales;
-  fa.n_proj = corrected ? (u.T + 15) / 16 * ((u.r + 31) / 32) * ksplit : 0;
-  const long long pieces = (long long)u.T * (u.d_in / 16);
-  dim3 fgrid((unsigned)((pieces + MX_FRONT_THREADS - 1) / MX_FRONT_THREADS + fa.n_proj));
-  if (f16) k_mx_front_tiles<ACT_F16><<<fgrid, dim3(MX_FRONT_THREADS), 0, st>>>(fa);
-  else k_mx_front_tiles<ACT_BF16><<<fgrid, dim3(MX_FRONT_THREADS), 0, st>>>(fa);
+  fa.T = u.T; fa.d_in = u.d_in; fa.r = u.r;
+  const MxFrontShape front = choose_mx_front(u, corrected);
+  fa.groups = front.nb == 0 ? 1 : ((u.r + 15) / 16 + front.nb - 1) / front.nb;
+  fa.ksplit = front.ksplit;
+  fa.slice_tiles = front.slice_tiles;
+  if (f16) launch_mx_front<ACT_F16>(fa, front, st);
+  else launch_mx_front<ACT_BF16>(fa, front, st);
   const int ti = choose_mx_tile(u);
   const bool wide = choose_mx_wide(u);
   const int tile_tok = wide ? MXW_TOK : 16 * MX_TILES[ti].mb, tile_rows = wide ? MXW_TOK : 16 * MX_TILES[ti].rb * MX_TILES[ti].rw;

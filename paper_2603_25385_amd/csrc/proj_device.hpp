@@ -100,6 +100,35 @@ __device__ inline void load4_device(u32x4_t (&v)[4], const void* p0, const void*
                : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]) : "v"(p0), "v"(p1), "v"(p2), "v"(p3) : "memory");
 }
 
+// Two neighbouring ranks' sums of one K slice (s) are published as self-validating slots {fp32, launch tag} (q: slice 0's
+// first one, slices r apart, at most four), and nobody waits for anybody: a thread whose own slots are out looks at its
+// elements' slots of all slices once.  If they are complete, s receives their sum in slice order.  Of two slices at least
+// one finds the other's slots: a look is issued when the thread's own stores have completed at device scope, so the later
+// of the two looks comes behind both stores.  Several may find them all; they hand out the same bits.
+__device__ inline void publish_slice(unsigned long long* q, int slice, int r, uint32_t tag, const float (&s)[2]) {
+  const unsigned long long tag_hi = (unsigned long long)tag << 32;
+#pragma unroll
+  for (int e = 0; e < 2; ++e)
+    __hip_atomic_store(q + (size_t)slice * r + e, tag_hi | (unsigned long long)__builtin_bit_cast(uint32_t, s[e]),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline bool look_at_slices(const unsigned long long* q, int ksplit, int r, uint32_t tag, float (&s)[2]) {
+  u32x4_t v[4];
+  load4_device(v, q, q + (size_t)min(1, ksplit - 1) * r, q + (size_t)min(2, ksplit - 1) * r, q + (size_t)(ksplit - 1) * r);
+  bool all = true;
+  s[0] = s[1] = 0.f;
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const uint32_t w0 = v[p][0], t0 = v[p][1], w1 = v[p][2], t1 = v[p][3];
+    all = all && t0 == tag && t1 == tag;
+    if (p < ksplit) {
+      s[0] += __builtin_bit_cast(float, w0);
+      s[1] += __builtin_bit_cast(float, w1);
+    }
+  }
+  return all;
+}
+
 constexpr int PROJ_NB = 2;               // 16-rank blocks per workgroup
 struct ProjSliced {
   const uint16_t* X;
@@ -109,13 +138,9 @@ struct ProjSliced {
   bool slots_only;         // the slices (two at least) stay apart, for the consumers to add
 };
 
-// One workgroup of NW waves: tokens 16 tb .., K slice kz, ranks 32 ng .. + 32.  Slices are
-// published as self-validating slots, and nobody waits for anybody: a thread whose own slots are
-// out looks at its elements' slots of all slices once, and whoever finds them complete adds them in
-// slice order; out(t, rank, pair, tag) receives two ranks rounded to the activation type.  Of two
-// slices at least one finds the other's slots: a look is issued when the thread's own stores have
-// completed at device scope, so the later of the two looks comes behind both stores.  Several may
-// find them all; they hand out the same bits.  lds: NW * PROJ_NB * 256 floats.
+// One workgroup of NW waves: tokens 16 tb .., K slice kz, ranks 32 ng .. + 32.  Whoever finds all slices complete adds
+// them (see publish_slice); out(t, rank, pair, tag) receives two ranks rounded to the activation type.  lds: NW *
+// PROJ_NB * 256 floats.
 template <int ACT, int NW, class OUT>
 __device__ inline void proj_sliced(const ProjSliced& u, int local, float* lds, OUT out) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -171,30 +196,12 @@ __device__ inline void proj_sliced(const ProjSliced& u, int local, float* lds, O
     for (int w = 0; w < NW; ++w) s[e] += lds[((w * PROJ_NB + (rl >> 4)) * 4 + (tl & 3)) * 64 + ln];
   }
   const uint32_t tag = (uint32_t)(launch_tag() & 0xffffffffull);
-  const unsigned long long tag_hi = (unsigned long long)tag << 32;
   if (ksplit > 1) {
-    unsigned long long* slot = (unsigned long long*)u.part + ((size_t)t * ksplit + kz) * r + rank;
-#pragma unroll
-    for (int e = 0; e < 2; ++e)
-      __hip_atomic_store(slot + e, tag_hi | (unsigned long long)__builtin_bit_cast(uint32_t, s[e]),
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    unsigned long long* q = (unsigned long long*)u.part + (size_t)t * ksplit * r + rank;
+    publish_slice(q, kz, r, tag, s);
     if (u.slots_only) return;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // (counts stores, too)
-    const unsigned long long* q = (const unsigned long long*)u.part + (size_t)t * ksplit * r + rank;
-    u32x4_t v[4];
-    load4_device(v, q, q + (size_t)min(1, ksplit - 1) * r, q + (size_t)min(2, ksplit - 1) * r, q + (size_t)(ksplit - 1) * r);
-    bool all = true;
-    s[0] = s[1] = 0.f;
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      const uint32_t w0 = v[p][0], t0 = v[p][1], w1 = v[p][2], t1 = v[p][3];
-      all = all && t0 == tag && t1 == tag;
-      if (p < ksplit) {
-        s[0] += __builtin_bit_cast(float, w0);
-        s[1] += __builtin_bit_cast(float, w1);
-      }
-    }
-    if (!all) return;
+    if (!look_at_slices(q, ksplit, r, tag, s)) return;
   }
   const uint32_t pk = (uint32_t)to_act16<ACT>(s[0]) | ((uint32_t)to_act16<ACT>(s[1]) << 16);
   out(t, rank, pk, tag);

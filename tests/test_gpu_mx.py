@@ -337,3 +337,17 @@ def test_wide_tiles(act, T, d_in, d_outs, r, out):
             assert np.isfinite(g).all() and rel_err(g, y) <= TOL + (ULP[act] if out == "act" else 0.0)
     again = du.forward(False)
     assert all(np.array_equal(a, b) for a, b in zip(got, again))
+
+
+# the first launch's shapes: one and two token blocks, 32 ranks to all of them, whole contractions and slices, sixteen waves,
+# codes alone, ranks and tokens that end inside a block
+@pytest.mark.parametrize("act", ["f16", "bf16"])
+@pytest.mark.parametrize("T,d_in,r", [(17, 128, 8), (33, 4224, 40), (50, 8320, 72), (130, 1152, 128), (530, 8320, 128),
+                                      (700, 2048, 104), (1500, 1024, 48), (1500, 4224, 72), (2048, 384, 16)])
+def test_projection_and_codes_of_the_first_launch(act, T, d_in, r):
+    u = make_unit(UnitShape("g", d_in, (136,)), T, r, act, seed=52)
+    du = MxDeviceUnit(u)
+    for restore in (True, False):
+        got = du.forward(restore)
+        for g, y in zip(got, MX.mx_group_forward(u, restore)):
+            assert np.isfinite(g).all() and rel_err(g, y) <= TOL
