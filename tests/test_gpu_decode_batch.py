@@ -225,3 +225,26 @@ def test_tiles_of_three_token_blocks(T, d_in, d_outs, act, tile):
         assert G.glowq_debug_tile_height([du.desc]) == [48 if T % 48 == 0 else 64]
         for y, ref in zip(ys, O.group_forward(u, restore)):
             assert np.isfinite(y).all() and rel_err(y, ref) <= TOL + ULP[act]
+
+
+# tiles of 128 rows, which launches of several units take: rows that end inside a workgroup and straddle modules, ragged
+# tokens, whole contractions and cut ones, both kinds of dequantisation
+@pytest.mark.parametrize("act,T,d_in,d_outs,n,r,slices", [
+    ("f16", 21, 1152, (4096, 2056), 12, 16, 1), ("bf16", 21, 1152, (6152,), 12, 72, 1), ("f16", 21, 8320, (520, 512), 8, 72, 3),
+    ("bf16", 31, 8320, (1032,), 12, 16, 2), ("f16", 45, 4224, (3080,), 12, 72, 1), ("bf16", 61, 4224, (3072, 8), 12, 16, 1)])
+def test_tiles_of_128_rows(act, T, d_in, d_outs, n, r, slices):
+    for Gs in (128, 64):
+        u = recipe_unit(O, 1, 0, T, r=r, shape=UnitShape("g", d_in, d_outs), act=act, G=Gs, method="alg1", qr="none")
+        dus = [DeviceUnit(u) for _ in range(n)]
+        descs = [d.desc for d in dus]
+        assert {(q.kernel, q.tile, q.k_slices, q.launch) for q in G.glowq_debug_route(descs)} == {(G.GLOWQ_ROUTE_BATCHED, 9, slices, 0)}
+        ws = Workspace(descs)
+        for mask in ([True] * n, [i % 3 == 1 for i in range(n)]):
+            for d in dus:
+                d.clear()
+            G.glowq_block_forward(descs, bytes(mask), ws.ptr, ws.bytes, stream())
+            refs = {on: O.group_forward(u, on) for on in set(mask)}
+            for d, on in zip(dus, mask):
+                for y, ref in zip(d.outputs(), refs[on]):
+                    assert np.isfinite(y).all() and rel_err(y, ref) <= TOL
+            ws.assert_idle()
