@@ -224,6 +224,7 @@ static LaunchChoice choose_launch(const glowq_unit* units, int n_units, bool sla
   }
   c.kernel = GLOWQ_ROUTE_TILED;
   c.tile = large;
+  if (large == PF_TILE_WIDE) fewer_wide_slices(batch, c.n, c.slices);
   return c;
 }
 

@@ -124,6 +124,8 @@ int prefill_max_modules();
 // slabs (`slabs`) and the module table has room.  Returns the bytes (of `room`) behind the units' workspace slices that the
 // launch takes for more slices than that
 size_t plan_prefill_slices(const glowq_unit* const* units, int n, bool slabs, size_t room, int* slices);
+// ... and fewer of them where a launch of several units on wide tiles is taken to end sooner so
+void fewer_wide_slices(const glowq_unit* const* units, int n, int* slices);
 // the tiles that the launch, cut into these slices, takes, and what it is taken to cost (dealt false: on tiles that all hold
 // 128 tokens)
 enum { PF_TILE_LARGE = 0, PF_TILE_HALF = 1, PF_TILE_WIDE = 2 };

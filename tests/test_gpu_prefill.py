@@ -262,6 +262,27 @@ def test_wide_tiles_with_k_slices():
         ws.assert_idle()
 
 
+# fewer slices beside other units than the unit's shapes ask for (one per 4096 channels, four at most), or none; ragged rows, a
+# last token tile of one
+@pytest.mark.parametrize("act,T,short,d_in,d_outs,slices", [
+    ("f16", 500, (3072, (9896, 8056)), 12416, (2832, 4112), 2), ("bf16", 513, (3200, (9328, 11560)), 16512, (2216, 2080), 2),
+    ("bf16", 513, (3200, (11840, 7456, 13112)), 8192, (1488, 1928), 1)])
+def test_wide_tiles_with_fewer_k_slices(act, T, short, d_in, d_outs, slices):
+    units = [make(T, *short, act, seed=74), make(T, d_in, d_outs, act, seed=75)]
+    dus = [DeviceUnit(u, "act", 8) for u in units]
+    descs = [d.desc for d in dus]
+    assert G.glowq_debug_tile_tokens(descs) == [256, 256]
+    assert [r.k_slices for r in G.glowq_debug_route(descs)] == [1, slices]
+    ws = Workspace(descs)
+    for mask in ((1, 1), (0, 1), (1, 0)):
+        for d in dus:
+            d.clear()
+        G.glowq_block_forward(descs, bytes(mask), ws.ptr, ws.bytes, stream())
+        for d, u, m in zip(dus, units, mask):
+            check(d.outputs(), O.group_forward(u, bool(m)), TOL + ULP[act])
+        ws.assert_idle()
+
+
 def long_units(act, Gs):
     # an odd number of K tiles, a unit of one K tile, fewer tokens (a last token tile of 188 of 256), two stages of ranks
     return [make(1025, 5248, (6152, 4360), act, Gs, 72, seed=81), make(1025, 128, (264, 40), act, Gs, 8, seed=82),
