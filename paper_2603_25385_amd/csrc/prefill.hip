@@ -1009,11 +1009,12 @@ int choose_prefill_tile(const glowq_unit* const* units, const int* slices, int n
 // round.  At most two slices, or none, where the same estimate sees 2 % in it.  Of 1150 layers (1024 to 8192 channels, 12288 to
 // 32768 inner ones, 384 to 1300 tokens, 3 or 4 slices by their shapes) 313 take fewer: 2.4 % faster on average, a tenth of
 // them 7 %, three more than 3 % slower; 5120 / 15744 at 512 tokens, bfloat16, 346 -> 298 us, 4096 / 14336 at 512 209 -> 202.
-// Two slices throughout were 1 % slower than those of the shapes.  A unit alone keeps them: nothing runs beside its tiles.
+// Two slices throughout were 1 % slower than those of the shapes.  A unit alone keeps them: nothing runs beside its tiles.  So do
+// 32-bit outputs, where a longer chain of sums would show (error against 64 bits 1.25e-6 in three slices, 1.26e-6 in two).
 void fewer_wide_slices(const glowq_unit* const* units, int n, int* slices) {
   int most = 0;
   for (int k = 0; k < n; ++k) most = std::max(most, slices[k]);
-  if (n == 1 || most == 1) return;
+  if (n == 1 || most == 1 || units[0]->out_dtype == GLOWQ_F32) return;
   double least = 0.98 * prefill_places_cost(units, slices, n, PF_TILE_WIDE);
   for (int s = std::min(2, most - 1); s >= 1; --s) {
     int fewer[PF_MAX_UNITS];

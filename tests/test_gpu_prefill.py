@@ -273,6 +273,8 @@ def test_wide_tiles_with_fewer_k_slices(act, T, short, d_in, d_outs, slices):
     descs = [d.desc for d in dus]
     assert G.glowq_debug_tile_tokens(descs) == [256, 256]
     assert [r.k_slices for r in G.glowq_debug_route(descs)] == [1, slices]
+    wider = [DeviceUnit(u, "f32", 8) for u in units]              # 32-bit outputs keep them
+    assert [r.k_slices for r in G.glowq_debug_route([d.desc for d in wider])] == [1, min(4, d_in // 4096)]
     ws = Workspace(descs)
     for mask in ((1, 1), (0, 1), (1, 0)):
         for d in dus:
