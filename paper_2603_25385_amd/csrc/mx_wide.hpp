@@ -236,7 +236,7 @@ __global__ void __launch_bounds__(256, 1) k_mx_wide(MxGemmArgs a, int n_tiles) {
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
         if (32 * s < a.r) {        // uniform
-          // ranks past r: zeros here, words of a valid rank from R; rows and tokens past the last are that one again
+          // ranks past r: zeros on both sides (R may hold infinities); rows and tokens past the last are that one again
           const int j0 = 32 * s + 8 * g;
           const uint32_t at = 2u * (uint32_t)min(j0, a.r - 8);
           u32x4_t av[8], rv[8];
@@ -247,7 +247,7 @@ __global__ void __launch_bounds__(256, 1) k_mx_wide(MxGemmArgs a, int n_tiles) {
           }
 #pragma unroll
           for (int r = 0; r < 8; ++r)
-            if (j0 >= a.r) av[r] = u32x4_t{0, 0, 0, 0};
+            if (j0 >= a.r) av[r] = rv[r] = u32x4_t{0, 0, 0, 0};
           __builtin_amdgcn_sched_barrier(0);
           asm volatile("s_nop 1");       // (operands that the vector ALU wrote)
           for_each_index<64>([&](auto Q) __attribute__((always_inline)) { sum_mfma16<ACT, Q.value>(av[Q.value % 8], rv[Q.value / 8]); });

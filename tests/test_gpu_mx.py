@@ -12,7 +12,7 @@ from glowq_inputs import UnitShape, gen_activations, gen_module_weight
 from oracle import glowq_oracle as O
 from oracle import mx_oracle as MX
 from gpu_util import ACT_CODE, TORCH_ACT, dev_bits, stream
-from util import rel_err
+from util import add_stored_projection, check_with_infinities, overflow_one_rank, rel_err
 
 pytestmark = pytest.mark.gpu
 TOL = 2e-3
@@ -337,6 +337,24 @@ def test_wide_tiles(act, T, d_in, d_outs, r, out):
             assert np.isfinite(g).all() and rel_err(g, y) <= TOL + (ULP[act] if out == "act" else 0.0)
     again = du.forward(False)
     assert all(np.array_equal(a, b) for a, b in zip(got, again))
+
+
+# a rank of R past the activation type's range: infinite outputs of that token's, on every kind of tile, and no NaN from
+# the operand words past the last rank (r = 72, 24, 8: not a multiple of the instruction's 32)
+@pytest.mark.parametrize("act", ["f16", "bf16"])
+@pytest.mark.parametrize("T,d_in,d_outs,r,tokens", [(929, 2176, (6104, 6232), 72, 256), (1425, 2304, (4056, 4184), 24, 256),
+                                                    (513, 256, (12000,), 8, 128), (600, 640, (264, 96), 72, 32)])
+def test_infinite_rank(act, T, d_in, d_outs, r, tokens):
+    u = make_unit(UnitShape("g", d_in, d_outs), T, 0, act, seed=53)
+    rng = np.random.default_rng(54)
+    u["r"], u["B"] = r, O.f64_to_bits(0.02 * rng.standard_normal((r, d_in)), act)
+    for m in u["modules"]:
+        m["A"] = O.f64_to_bits(0.02 * rng.standard_normal((m["d_out"], r)), act)
+    overflow_one_rank(O, u, r - 3)
+    du = MxDeviceUnit(u)
+    assert G.glowq_debug_mx_tile_tokens(du.desc) == tokens
+    for got, want in zip(du.forward(True), add_stored_projection(O, u, MX.mx_group_forward(u, False))):
+        check_with_infinities(got, want, TOL)
 
 
 # the first launch's shapes: one and two token blocks, 32 ranks to all of them, whole contractions and slices, sixteen waves,

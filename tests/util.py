@@ -34,3 +34,34 @@ def recipe_unit(oracle, cfg_id, unit_index, T, r=None, method="svd", shape=None,
     unit = oracle.build_unit(W, X, r, G, act, method=method, Omega=Omega, qr=qr)
     unit["W"] = W
     return unit
+
+
+def overflow_one_rank(oracle, u, rank):
+    """Operands of `u` changed so that R leaves the activation type's range at this rank for a
+    few tokens (infinities of both signs) and is as finite as before elsewhere; no element of A is zero."""
+    act, T = u["act"], u["X"].shape[0]
+    big = {"f16": 3e4, "bf16": 1e30}[act]
+    X, B = oracle.bits_to_f64(u["X"], act), oracle.bits_to_f64(u["B"], act)
+    B[rank] = 0.0
+    X[:, 5] = 0.0
+    B[:, 5] = 0.0
+    B[rank, 5] = big
+    X[[0, T // 2, T - 1], 5] = big * np.array([1.0, -1.0, 1.0])
+    u["X"], u["B"] = oracle.f64_to_bits(X, act), oracle.f64_to_bits(B, act)
+    for m in u["modules"]:
+        A = oracle.bits_to_f64(m["A"], act)
+        m["A"] = oracle.f64_to_bits(np.where(A == 0.0, 1.0, A), act)
+
+
+def add_stored_projection(oracle, u, plain):
+    """Outputs without the correction plus R A_i^T, R as it is stored: rounded to the activation type."""
+    R = oracle.bits_to_f64(oracle.f64_to_bits(oracle.shared_proj(u["X"], u["B"], u["act"]), u["act"]), u["act"])
+    return [y + R @ oracle.bits_to_f64(m["A"], u["act"]).T for y, m in zip(plain, u["modules"])]
+
+
+def check_with_infinities(got, want, tol):
+    inf = np.isinf(want)
+    assert inf.any() and not np.isnan(want).any() and not np.isnan(got).any()
+    assert np.array_equal(np.isinf(got), inf) and np.array_equal(got[inf], want[inf])
+    e = rel_err(got[~inf], want[~inf])
+    assert e <= tol, e
