@@ -349,13 +349,23 @@ __global__ void __launch_bounds__(WD_WAVES * 64, 1) k_wide(PrefillArgs a) {
         for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
           for (int b = 0; b < RB; ++b) {
-            // ranks past r: zeros here, words of a valid rank from R
+            // ranks past r: zeros
             const int j0 = 64 * rs + 32 * jj + 8 * kq;
             const int row = min((nb0 + b) * 16 + n, M.d_out - 1);
             af[rs][jj][b] = u32x4_t{0u, 0u, 0u, 0u};
             if (j0 < U.r) af[rs][jj][b] = *(const u32x4_t*)(M.A + (size_t)row * U.r + j0);
           }
       vm_wait<0>();
+      // ... and zeros in LDS over the valid rank's words that were loaded there (R may hold infinities): each thread in
+      // the places that its own loads have filled
+      if (U.r & 31) {
+#pragma unroll
+        for (int rs = 0; rs < 2; ++rs)
+          if (rs < rstages && 64 * rs + 8 * ((tid & 7) ^ ((tid >> 4) & 7)) >= U.r)
+#pragma unroll
+            for (int i = 0; i < XI; ++i)
+              *(__attribute__((address_space(3))) u32x4_t*)(xland + rs * WD_STAGE + i * 4096 + lane * 16) = u32x4_t{0u, 0u, 0u, 0u};
+      }
       __syncthreads();
 #pragma unroll
       for (int rs = 0; rs < 2; ++rs)

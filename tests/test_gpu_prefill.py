@@ -8,7 +8,7 @@ import paper_2603_25385_amd as G
 from glowq_inputs import UnitShape
 from oracle import glowq_oracle as O
 from gpu_util import DeviceUnit, Workspace, stream
-from util import recipe_unit, rel_err
+from util import add_stored_projection, check_with_infinities, overflow_one_rank, recipe_unit, rel_err
 
 pytestmark = pytest.mark.gpu
 TOL = 2e-3                     # the forward's bar: fp32 accumulation, R rounded once
@@ -31,6 +31,17 @@ def check(ys, refs, tol):
         assert y.shape == ref.shape and np.isfinite(y).all()
         e = rel_err(y, ref)
         assert e <= tol, e
+
+
+def check_infinite_rank(T, d_in, d_outs, act, r):
+    u = make(T, d_in, d_outs, act, 128, r)
+    overflow_one_rank(O, u, r - 3)
+    du = DeviceUnit(u)
+    ws = Workspace([du.desc])
+    G.glowq_group_forward(du.desc, True, ws.ptr, ws.bytes, stream())
+    for got, want in zip(du.outputs(), add_stored_projection(O, u, O.group_forward(u, False))):
+        check_with_infinities(got, want, TOL)
+    return du
 
 
 def test_one_workspace_for_calls_of_different_sizes():
@@ -242,6 +253,15 @@ def test_wide_tiles_match_the_oracle(T, d_in, d_outs, act, Gs, r):
         G.glowq_group_forward(du.desc, restore, ws.ptr, ws.bytes, stream())
         check(du.outputs(), refs[restore], TOL + (ULP[act] if out == "act" else 0.0))
         ws.assert_idle()
+
+
+# a rank of R past the activation type's range: infinite outputs of that token's and no NaN from the operand words past
+# the last rank, one stage of ranks and two
+@pytest.mark.parametrize("act", ["f16", "bf16"])
+@pytest.mark.parametrize("T,d_in,d_outs,r", [(1025, 3328, (6152, 5624), 72), (1281, 3328, (9224,), 8)])
+def test_infinite_rank_on_wide_tiles(T, d_in, d_outs, act, r):
+    du = check_infinite_rank(T, d_in, d_outs, act, r)
+    assert G.glowq_debug_tile_tokens([du.desc]) == [256]
 
 
 def test_wide_tiles_with_k_slices():
