@@ -533,7 +533,7 @@ int batch_wait_polls() { return R_WAIT_POLLS; }
 // 14336 channels), each on every tile, beyond 64 tokens also on the tiled kernel, and the constants
 // fitted to the choice: it is 1.5 % above the best on average up to 64 tokens and 2.1 % beyond (1.6 %
 // and 0.7 % in 380 and 70 other calls); with constants of 70 calls and no `ends` it was 4.6 % and 5.6 %.
-// The last two tiles are for 5 to 16 tokens on some thousand rows and a long contraction, where one
+// The two tiles of two and three row blocks per wave are for 5 to 16 tokens on some thousand rows and a long contraction, where one
 // row block per wave leaves a compute unit with one workgroup and a half, and four waves side by side
 // leave most compute units empty: 5 tokens x 6456 rows x 8448 17.8 -> 13.4 us, 5 x 3 x 3320 x 12928
 // 36.0 -> 25.9 (three row blocks).  A ring deeper than three stages was slower for both (1.07 and
@@ -553,10 +553,20 @@ constexpr BatchTile BATCH_TILES[] = {
     {4, 2, 4, 4, 0.26f, 6.01f, {0.53f, 0.65f}, {0.52f, 0.58f}},
     {1, 2, 1, 4, 0.73f, 3.63f, {0.52f, 0.59f}, {0.54f, 0.40f}},
     {1, 3, 1, 4, 0.25f, 5.00f, {0.68f, 0.68f}, {0.68f, 0.72f}},
-    // (128 rows on eight waves side by side: chosen by the estimate for large calls alone)
-    {2, 1, 8, 8, 0.f, 0.f, {0.f, 0.f}, {0.f, 0.f}},
+    {2, 1, 8, 8, 0.28f, 9.30f, {0.33f, 0.36f}, {0.17f, 0.17f}},
 };
-constexpr int BATCH_N_TILES = sizeof(BATCH_TILES) / sizeof(BATCH_TILES[0]), BATCH_N_PRICED = 9;
+constexpr int BATCH_N_TILES = sizeof(BATCH_TILES) / sizeof(BATCH_TILES[0]);
+// The last tile, 128 rows on eight waves side by side, is for launches of several units of more than 16 tokens that take longer by
+// the other tiles' estimate: up to 32 tokens from 14 us on, 33 to 64 from 38 us on.  Its workgroups read X half as often as tiles
+// of 64 rows.  Its constants are those of 1791 and 1070 such launches (one to four layers, two to six equal units) on every
+// tile and, up to 32 tokens, in one to four slices: beside the other tiles it takes 9.5 % off the time on average up to 32 tokens in
+// binary16 and 7.4 in bfloat16, 2.6 and 1.9 beyond; 4.0, 6.4, 2.7 and 2.9 % of the launches are more than 3 % slower for it.  (An
+// estimate of nine constants for every tile, of the kind below, took 8.9, 6.8, 0.4 and 0 % off, 5.4, 7.7, 18 and 17 % of the
+// launches were slower, 1.5 times as long at most.)  4096 / 14336 at 24 tokens, binary16, 44.8 -> 41.6 us.
+constexpr int BATCH_TALL = BATCH_N_TILES - 1;
+constexpr BatchTile BATCH_TALL_33 = {2, 1, 8, 8, 0.23f, 4.89f, {0.36f, 0.47f}, {0.32f, 0.34f}};      // at 33 to 64 tokens
+constexpr float BATCH_LONG_US = 14.f, BATCH_LONG_US_33 = 38.f;
+constexpr float BATCH_TALL_48 = 1.1f;          // up to 48 tokens the tiles of 64 are smaller than they are priced
 
 template <int I> constexpr int batch_tile_resident() {
   constexpr BatchTile t = BATCH_TILES[I];
@@ -636,128 +646,85 @@ static inline int batch_stages(int kt, int groups, int slices) { return (kt + gr
 static inline int batch_cut(const BatchSize& u, int groups, int target) {
   return u.allowed == 1 ? 1 : std::min(u.allowed, (batch_stages(u.kt, groups, 1) + target - 1) / target);
 }
+// What tile I costs, the units cut so that the longest is left with 1 / cut of its stages; pieces: workgroups of units that are.
+struct BatchWork {
+  long long work, wgs, pieces;
+  int chain;
+};
+static inline BatchWork batch_work(const BatchTile& t, const BatchSize* u, int n, int cut) {
+  const int ks = t.nw / t.rw, rows = t.rb * t.rw, tok = 16 * t.mb;
+  BatchWork w = {0, 0, 0, 0};
+  int target = 0;
+  if (cut > 1) {
+    for (int k = 0; k < n; ++k) target = std::max(target, batch_stages(u[k].kt, ks, 1));
+    target = (target + cut - 1) / cut;
+  }
+  for (int k = 0; k < n; ++k) {
+    const int S = cut > 1 ? batch_cut(u[k], ks, target) : 1, stages = batch_stages(u[k].kt, ks, S);
+    const long long wgs = (long long)((u[k].blocks + rows - 1) / rows) * ((u[k].T + tok - 1) / tok) * S;
+    w.wgs += wgs;
+    w.work += wgs * stages;
+    w.chain = std::max(w.chain, stages);
+    if (S > 1) w.pieces += wgs;
+  }
+  return w;
+}
+static inline float batch_cost(const BatchTile& t, int resident, const BatchWork& w, bool f16, int cut) {
+  const float alone = t.chain[f16 ? 0 : 1], busy = t.busy[f16 ? 0 : 1];
+  const float share = w.wgs <= 256 * resident ? (float)((w.wgs + 255) / 256) * busy : (float)w.wgs / 256.f * busy + 0.8f * alone;
+  return t.start + std::max(((float)w.chain + t.ends) * alone, ((float)w.work / (float)w.wgs + t.ends) * share) + (cut > 1 ? BATCH_SLICE_US : 0.f);
+}
 template <int I>
 static inline void cheapest_batch_tile(const BatchSize* u, int n, bool f16, int max_mb, BatchChoice* best) {
   constexpr BatchTile t = BATCH_TILES[I];
-  constexpr int ks = t.nw / t.rw, rows = t.rb * t.rw, tok = 16 * t.mb;
   if (t.mb <= max_mb) {
-    long long work = 0, wgs = 0;
-    int chain = 0;
-    for (int k = 0; k < n; ++k) {
-      const int stages = (u[k].kt + ks - 1) / ks;
-      const long long w = (long long)((u[k].blocks + rows - 1) / rows) * ((u[k].T + tok - 1) / tok);
-      wgs += w;
-      work += w * stages;
-      chain = std::max(chain, stages);
-    }
-    const float alone = t.chain[f16 ? 0 : 1], busy = t.busy[f16 ? 0 : 1];
-    const float share = wgs <= 256 * BATCH_RESIDENT[I] ? (float)((wgs + 255) / 256) * busy : (float)wgs / 256.f * busy + 0.8f * alone;
-    const float c = t.start + std::max(((float)chain + t.ends) * alone, ((float)work / (float)wgs + t.ends) * share);
+    const float c = batch_cost(t, BATCH_RESIDENT[I], batch_work(t, u, n, 1), f16, 1);
     if (best->tile < 0 || c < best->cost) *best = BatchChoice{I, 1, c};
   }
-  if constexpr (I + 1 < BATCH_N_PRICED) cheapest_batch_tile<I + 1>(u, n, f16, max_mb, best);
+  if constexpr (I + 1 < BATCH_TALL) cheapest_batch_tile<I + 1>(u, n, f16, max_mb, best);
 }
-// the same with every number of slices from two on
-static void cheapest_cut_tile(const BatchSize* u, int n, bool f16, int max_mb, int most_cut, BatchChoice* best) {
-  int longest_kt = 0;
-  for (int k = 0; k < n; ++k) longest_kt = std::max(longest_kt, u[k].kt);
-  for (int i = 0; i < BATCH_N_PRICED; ++i) {
-    const BatchTile& t = BATCH_TILES[i];
-    if (t.mb > max_mb) continue;
-    const int ks = t.nw / t.rw, rows = t.rb * t.rw, tok = 16 * t.mb, longest = batch_stages(longest_kt, ks, 1);
-    const float alone = t.chain[f16 ? 0 : 1], busy = t.busy[f16 ? 0 : 1];
-    for (int cut = 2; cut <= most_cut; ++cut) {
-      long long work = 0, wgs = 0, pieces = 0;
-      int chain = 0;
-      for (int k = 0; k < n; ++k) {
-        const int S = batch_cut(u[k], ks, (longest + cut - 1) / cut), stages = batch_stages(u[k].kt, ks, S);
-        const long long w = (long long)((u[k].blocks + rows - 1) / rows) * ((u[k].T + tok - 1) / tok) * S;
-        wgs += w;
-        work += w * stages;
-        chain = std::max(chain, stages);
-        if (S > 1) pieces += w;
-      }
-      if (pieces > 256) break;
-      const float share = wgs <= 256 * BATCH_RESIDENT[i] ? (float)((wgs + 255) / 256) * busy : (float)wgs / 256.f * busy + 0.8f * alone;
-      const float c = t.start + std::max(((float)chain + t.ends) * alone, ((float)work / (float)wgs + t.ends) * share) + BATCH_SLICE_US;
-      if (best->tile < 0 || c < best->cost) *best = BatchChoice{i, cut, c};
-    }
+// the same with every number of slices from two on, on one tile
+static void cheapest_cut(int tile, const BatchTile& t, const BatchSize* u, int n, bool f16, int most_cut, BatchChoice* best) {
+  for (int cut = 2; cut <= most_cut; ++cut) {
+    const BatchWork w = batch_work(t, u, n, cut);
+    if (w.pieces > 256) break;
+    const float c = batch_cost(t, BATCH_RESIDENT[tile], w, f16, cut);
+    if (best->tile < 0 || c < best->cost) *best = BatchChoice{tile, cut, c};
   }
 }
 
-// A finer estimate for launches of several units that take longer: up to 32 tokens from 14 us on, 33 to 64 from 38 us on.  It
-// adds the length of the longest chain and the chip's share (the longer of both
-// counts whole, `both` of the other one), counts workgroups that do not fill whole rounds half, the projection's workgroups
-// (`proj`: whole places for several us), the call's tokens (`tok`: X is read again by every workgroup) and groups of 64
-// (`g64`); `slice`: the sum of a cut.  Us; tile, then constants.  From 7800 calls of 5 to 32 tokens (one unit to three layers)
-// and 9700 of 33 to 64, each on these tiles and with one to four slices.  The estimate above was 13, 25 and 34 % off the best
-// tile at 30, 60 and 100 us, this one is 4, 2.5 and 0.5; of the calls that it serves 8 % are more than 3 % slower.  Half of the
-// gain is the tile of 128 rows: its workgroups read X half as often as tiles of 64 (layers of 4096 / 14336 at 24 tokens, f16:
-// 46 -> 42 us; two of 5120 / 13824 at 30 tokens, bf16: 128 -> 106).  Shorter calls gain nothing, single units up to 16
-// tokens lose 2 %.
+// Several units of up to 16 tokens that take longer: the estimate above takes tiles whose waves share the contraction too often, and cuts
+// too seldom.  This one is for the two that are best there, 16 rows and 64, in one to four slices: the length of the longest chain
+// and the chip's share (the longer of both counts whole, `both` of the other one), workgroups that do not fill whole rounds
+// counted half, the projection's workgroups (`proj`: whole places for several us), the call's tokens (`tok`) and groups of 64 (`g64`);
+// `slice`: the sum of a cut.  Us.  It is heard where the estimate above has its choice within 15 % of its own, and in bfloat16 not
+// where that takes two or three row blocks per wave.  Of 2909 launches on every tile it makes them 2.7 % faster in binary16 and 2.3 in
+// bfloat16; 4.6 and 5.6 % of them are more than 3 % slower, 13 % at most.  (Heard always, and with the other tiles, 2.3 and 2.1 % faster,
+// 9 and 10 % slower, up to 1.5 times as long.  With the rule for the wait for R, which has to leave a microsecond where the
+// estimate above cuts, both lose: binary16 gains 2.1 instead of 2.6 % at 10 % distance, and more launches are slower, not fewer.)
 struct BatchFine {
   int tile;
   float start, ends, alone, busy, proj, tok, both, slice, g64;
 };
-constexpr int BATCH_N_FINE = 8;
-constexpr BatchFine BATCH_FINE[2][2][BATCH_N_FINE] = {      // up to 32 tokens, more; binary16, bfloat16 (unused entries: tile -1)
-    {{{0, 1.725f, 4.684f, 0.367f, 0.383f, 7.843f, 0.159f, 0.266f, 2.802f, 0.003f},
-      {1, 1.138f, 7.195f, 0.238f, 0.176f, 4.603f, -0.054f, 0.225f, 2.191f, 0.018f},
-      {3, 0.589f, 8.674f, 0.298f, 0.235f, 5.322f, 0.166f, 0.160f, 1.899f, 0.028f},
-      {7, 2.550f, 4.747f, 0.429f, 0.452f, 6.479f, 0.073f, 0.202f, 2.279f, 0.011f},
-      {8, 2.047f, 7.119f, 0.522f, 0.688f, 11.649f, 0.023f, 0.111f, 1.635f, 0.031f},
-      {9, 0.000f, 11.158f, 0.384f, 0.394f, 6.354f, 0.070f, 0.118f, 1.931f, 0.038f},
-      {-1}, {-1}},
-     {{0, 1.874f, 4.249f, 0.384f, 0.399f, 8.406f, 0.163f, 0.190f, 2.783f, 0.006f},
-      {1, 1.295f, 6.049f, 0.281f, 0.193f, 5.445f, -0.057f, 0.222f, 1.612f, 0.024f},
-      {3, 0.512f, 7.571f, 0.327f, 0.251f, 6.057f, 0.102f, 0.160f, 1.673f, 0.023f},
-      {5, 0.000f, 7.418f, 0.419f, 0.345f, 3.750f, 0.053f, 0.000f, 4.236f, 0.027f},
-      {6, 0.000f, 6.818f, 0.626f, 0.591f, 4.334f, 0.016f, 0.048f, 4.895f, 0.030f},
-      {7, 2.513f, 3.889f, 0.522f, 0.501f, 6.382f, 0.058f, 0.086f, 2.057f, 0.009f},
-      {8, 1.928f, 4.660f, 0.690f, 0.893f, 10.767f, 0.002f, 0.073f, 1.207f, 0.032f},
-      {9, 0.000f, 9.170f, 0.463f, 0.444f, 7.380f, 0.024f, 0.086f, 1.944f, 0.025f}}},
-    {{{3, 2.414f, 4.650f, 0.309f, 0.270f, 5.125f, 0.033f, 0.155f, 9.354f, 0.012f},
-      {5, 0.000f, 9.217f, 0.240f, 0.234f, 6.776f, 0.305f, 0.380f, 1.480f, -0.004f},
-      {6, 0.000f, 7.212f, 0.432f, 0.380f, 7.669f, 0.147f, 0.375f, 2.000f, 0.006f},
-      {9, 2.112f, 6.406f, 0.392f, 0.371f, 6.814f, 0.019f, 0.134f, 2.000f, 0.010f},
-      {-1}, {-1}, {-1}, {-1}},
-     {{3, 1.489f, 5.490f, 0.329f, 0.274f, 4.963f, 0.022f, 0.210f, 0.774f, 0.010f},
-      {5, 0.000f, 9.930f, 0.254f, 0.237f, 6.467f, 0.287f, 0.355f, 2.032f, 0.010f},
-      {6, 0.000f, 5.134f, 0.495f, 0.427f, 8.467f, 0.144f, 0.303f, 2.000f, 0.018f},
-      {9, 1.649f, 7.151f, 0.446f, 0.394f, 6.547f, 0.010f, 0.142f, 1.862f, 0.026f},
-      {-1}, {-1}, {-1}, {-1}}}};
-constexpr float BATCH_FINE_FROM = 14.f, BATCH_FINE_FROM_33 = 38.f;
-static bool batch_fine_applies(int n, int T, float cost) {
-  return n > 1 && T <= 64 && cost >= (T > 32 ? BATCH_FINE_FROM_33 : BATCH_FINE_FROM);
-}
+constexpr BatchFine BATCH_FINE[2][2] = {      // binary16, bfloat16
+    {{0, 1.725f, 4.684f, 0.367f, 0.383f, 7.843f, 0.159f, 0.266f, 2.802f, 0.003f},
+     {1, 1.138f, 7.195f, 0.238f, 0.176f, 4.603f, -0.054f, 0.225f, 2.191f, 0.018f}},
+    {{0, 1.874f, 4.249f, 0.384f, 0.399f, 8.406f, 0.163f, 0.190f, 2.783f, 0.006f},
+     {1, 1.295f, 6.049f, 0.281f, 0.193f, 5.445f, -0.057f, 0.222f, 1.612f, 0.024f}}};
+constexpr float BATCH_FINE_NEAR = 1.15f;
 // proj: projection workgroups of the launch, restored or not
 static BatchChoice cheapest_fine_tile(const BatchSize* u, int n, bool f16, bool g64, float proj, int most_cut) {
-  int longest_kt = 0, T = 0;
-  for (int k = 0; k < n; ++k) {
-    longest_kt = std::max(longest_kt, u[k].kt);
-    T = std::max(T, u[k].T);
-  }
+  int T = 0;
+  for (int k = 0; k < n; ++k) T = std::max(T, u[k].T);
   BatchChoice best = {-1, 1, 0.f};
-  for (const BatchFine& c : BATCH_FINE[T > 32 ? 1 : 0][f16 ? 0 : 1]) {
-    if (c.tile < 0) break;
-    const BatchTile& t = BATCH_TILES[c.tile];
-    const int ks = t.nw / t.rw, rows = t.rb * t.rw, tok = 16 * t.mb, longest = batch_stages(longest_kt, ks, 1);
+  for (const BatchFine& c : BATCH_FINE[f16 ? 0 : 1]) {
     const float scale = (1.f + c.tok * (float)(T - 16) / 16.f) * (g64 ? 1.f + c.g64 : 1.f);
     for (int cut = 1; cut <= most_cut; ++cut) {
-      float work = 0.f, wgs = 0.f, pieces = 0.f;
-      int chain = 0;
-      for (int k = 0; k < n; ++k) {
-        const int S = cut == 1 ? 1 : batch_cut(u[k], ks, (longest + cut - 1) / cut), stages = batch_stages(u[k].kt, ks, S);
-        const float w = (float)(((u[k].blocks + rows - 1) / rows) * ((u[k].T + tok - 1) / tok) * S);
-        wgs += w;
-        work += w * (float)stages;
-        chain = std::max(chain, stages);
-        if (S > 1) pieces += w;
-      }
-      if (cut > 1 && (pieces == 0.f || pieces > 256.f)) break;
-      const float per_cu = wgs / 256.f, whole = per_cu <= (float)BATCH_RESIDENT[c.tile] ? std::ceil(per_cu) / per_cu : 1.f;
-      const float a = ((float)chain + c.ends) * c.alone * scale;
-      const float b = ((work + c.ends * wgs) * c.busy * scale * (0.5f + 0.5f * whole) + proj * c.proj) / 256.f;
+      const BatchWork w = batch_work(BATCH_TILES[c.tile], u, n, cut);
+      if (cut > 1 && (w.pieces == 0 || w.pieces > 256)) break;
+      const float wgs = (float)w.wgs, per_cu = wgs / 256.f, whole = per_cu <= (float)BATCH_RESIDENT[c.tile] ? std::ceil(per_cu) / per_cu : 1.f;
+      const float a = ((float)w.chain + c.ends) * c.alone * scale;
+      const float b = (((float)w.work + c.ends * wgs) * c.busy * scale * (0.5f + 0.5f * whole) + proj * c.proj) / 256.f;
       const float cost = c.start + std::max(a, b) + c.both * std::min(a, b) + (cut > 1 ? c.slice : 0.f);
       if (best.tile < 0 || cost < best.cost) best = BatchChoice{c.tile, cut, cost};
     }
@@ -784,21 +751,35 @@ int choose_batch_tile(const glowq_unit* const* units, int n, float* cost, int* s
   if (n == 1 && units[0]->r > 0 &&
       (blocks < BATCH_CUT_ONE_BLOCKS || (f16 && blocks > BATCH_CUT_ONE_MOST_F16) || sizes[0].T < BATCH_CUT_ONE_T)) most_cut = 1;
   if (n > 1 && waiting_kt > 0 && blocks < BATCH_CUT_BLOCKS) most_cut = 1;
-  BatchChoice best = {-1, 1, 0.f};
-  cheapest_batch_tile<0>(sizes, n, f16, exact ? 2 : 4, &best);
-  if (most_cut > 1 && best.cost > 2.f * BATCH_SLICE_US) {
-    BatchChoice cut = {-1, 1, 0.f};
-    cheapest_cut_tile(sizes, n, f16, exact ? 2 : 4, most_cut, &cut);
+  const int max_mb = exact ? 2 : 4;
+  BatchChoice whole = {-1, 1, 0.f}, cut = {-1, 1, 0.f};
+  cheapest_batch_tile<0>(sizes, n, f16, max_mb, &whole);
+  if (most_cut > 1 && whole.cost > 2.f * BATCH_SLICE_US)
+    for (int i = 0; i < BATCH_TALL; ++i)
+      if (BATCH_TILES[i].mb <= max_mb) cheapest_cut(i, BATCH_TILES[i], sizes, n, f16, most_cut, &cut);
+  auto of_both = [&]() {
     const float wait = n > 1 && waiting_kt > 0 ? std::max(cut.cost - BATCH_SLICE_US, BATCH_WAIT_US * (float)waiting_kt) + 1.f : 0.f;
-    if (cut.tile >= 0 && cut.cost < (n > 1 ? BATCH_CUT_SEVERAL[f16 ? 0 : 1] : BATCH_CUT_ONE) * best.cost && wait < best.cost) best = cut;
-  }
-  if (batch_fine_applies(n, units[0]->T, best.cost)) {
-    float proj = 0.f;
-    for (int k = 0; k < n; ++k)
-      proj += (float)((units[k]->T + 15) / 16 * std::min(4, (units[k]->d_in + 1023) / 1024) * ((units[k]->r + 31) / 32));
-    const float coarse = best.cost;
-    best = cheapest_fine_tile(sizes, n, f16, units[0]->group_size == 64, proj, most_cut);
-    best.cost = coarse;
+    const bool better = cut.tile >= 0 && cut.cost < (n > 1 ? BATCH_CUT_SEVERAL[f16 ? 0 : 1] : BATCH_CUT_ONE) * whole.cost && wait < whole.cost;
+    return better ? cut : whole;
+  };
+  BatchChoice best = of_both();
+  const int T = units[0]->T;
+  if (n > 1 && T <= 64 && best.cost >= (T > 32 ? BATCH_LONG_US_33 : BATCH_LONG_US)) {
+    if (T > 16) {
+      const BatchTile& tall = T > 32 ? BATCH_TALL_33 : BATCH_TILES[BATCH_TALL];
+      const float c = batch_cost(tall, BATCH_RESIDENT[BATCH_TALL], batch_work(tall, sizes, n, 1), f16, 1) * (T > 32 && T <= 48 ? BATCH_TALL_48 : 1.f);
+      cheapest_cut(BATCH_TALL, tall, sizes, n, f16, most_cut, &cut);
+      if (c < whole.cost) whole = BatchChoice{BATCH_TALL, 1, c};
+      best = of_both();
+    } else if (f16 || BATCH_TILES[best.tile].rb == 1) {
+      float proj = 0.f;
+      for (int k = 0; k < n; ++k)
+        proj += (float)((units[k]->T + 15) / 16 * std::min(4, (units[k]->d_in + 1023) / 1024) * ((units[k]->r + 31) / 32));
+      const BatchChoice fine = cheapest_fine_tile(sizes, n, f16, units[0]->group_size == 64, proj, most_cut);
+      const BatchTile& t = BATCH_TILES[fine.tile];
+      const float c = batch_cost(t, BATCH_RESIDENT[fine.tile], batch_work(t, sizes, n, fine.cut), f16, fine.cut);
+      if (c <= BATCH_FINE_NEAR * best.cost) best = BatchChoice{fine.tile, fine.cut, c};
+    }
   }
   *cost = best.cost;
   if (slices) {
@@ -854,7 +835,7 @@ static void launch_batch_tile(const BatchArgs<NB>& b, int tile, int mb, int n_wg
   if constexpr (!EXACT || t.mb <= 2) {
     if (tile == I) k_decode_batch<ACT, t.mb, t.rb, t.rw, t.nw, EXACT, G128, CUT, NB><<<dim3((unsigned)n_wgs), dim3(t.nw * 64), 0, st>>>(b);
   }
-  if constexpr (I + 1 < BATCH_N_TILES) launch_batch_tile<ACT, EXACT, G128, CUT, NB, I + 1>(b, tile, mb, n_wgs, st);
+  if constexpr (I + 1 < (NB > 1 ? BATCH_N_TILES : BATCH_TALL)) launch_batch_tile<ACT, EXACT, G128, CUT, NB, I + 1>(b, tile, mb, n_wgs, st);
 }
 
 template <bool CUT, int NB>

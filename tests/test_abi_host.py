@@ -320,6 +320,19 @@ def test_workspace_of_calls_that_may_be_cut(hidden, kv, inter, layers, act):
     assert G.glowq_workspace_bytes(eight) < 20 << 20
 
 
+@pytest.mark.parametrize("hidden,kv,inter,layers,T,r,act,tile", [
+    (1280, 1280, 21760, 1, 48, 128, G.GLOWQ_BF16, 2), (1152, 1152, 25344, 1, 34, 72, G.GLOWQ_F16, 2), (1920, 480, 23040, 1, 40, 72, G.GLOWQ_F16, 2),
+    (4096, 1024, 14336, 1, 24, 128, G.GLOWQ_F16, 9), (5120, 5120, 13824, 2, 30, 64, G.GLOWQ_BF16, 9)])
+def test_tiles_of_launches_of_several_units(hidden, kv, inter, layers, T, r, act, tile):
+    """The tile that was measured to be the best one: us on tile 2 and 3 of the first three 52.4 and 73.6, 53.3 and 76.0, 54.5
+    and 76.3.  Tiles of 128 rows are for several units of more than 16 tokens."""
+    units = _stack(hidden, kv, inter, layers, T, r, act)
+    assert {q.tile for q in G.glowq_debug_route(units)} == {tile}
+    for u in units:
+        assert G.glowq_debug_route([u])[0].tile != 9
+    assert all(q.tile != 9 for n in (5, 8, 16) for q in G.glowq_debug_route(_stack(hidden, kv, inter, layers, n, r, act)))
+
+
 def test_workspace_of_one_unit_that_is_never_cut():
     u = _stack(4096, 1024, 14336, 1, 8, 128, G.GLOWQ_F16)[2]            # gate and up
     assert G.glowq_workspace_bytes([u]) == G.glowq_workspace_bytes(_bare([u]))
