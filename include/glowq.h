@@ -391,6 +391,9 @@ glowq_status glowq_debug_mx_route(const glowq_unit* u, glowq_route* route);
  * 256) and the batched one (16, 32, 48 or 64); 0 for a unit that another kernel serves.
  * glowq_debug_mx_tile_tokens: the same for a microscaling call (16, 32 or 64 on small tiles, 128, 256 on wide ones). */
 glowq_status glowq_debug_mx_tile_tokens(const glowq_unit* u, int32_t* tokens);
+/* What a workgroup of the first launch of a restored microscaling call takes: shape[0] token blocks and shape[1] rank blocks of
+ * 16, on shape[2] waves, the contraction in shape[3] slices; zeros up to 16 tokens and where r is 0. */
+glowq_status glowq_debug_mx_front(const glowq_unit* u, int32_t shape[4]);
 glowq_status glowq_debug_tile_tokens(const glowq_unit* units, int32_t n_units, int32_t slabs, int32_t* tokens);
 glowq_status glowq_debug_tile_height(const glowq_unit* units, int32_t n_units, int32_t slabs, int32_t* tokens);
 glowq_status glowq_debug_unpack(const void* w_prepared, int32_t d_out, int32_t d_in,

@@ -102,6 +102,7 @@ def _load():
         "glowq_debug_tile_height": (ctypes.c_int, [up, i32, i32, ctypes.POINTER(i32)]),
         "glowq_debug_mx_route": (ctypes.c_int, [up, ctypes.POINTER(glowq_route)]),
         "glowq_debug_mx_tile_tokens": (ctypes.c_int, [up, ctypes.POINTER(i32)]),
+        "glowq_debug_mx_front": (ctypes.c_int, [up, ctypes.POINTER(i32)]),
         "glowq_debug_unpack": (ctypes.c_int, [vp, i32, i32, i32, vp, vp]),
         "glowq_debug_dequant": (ctypes.c_int, [vp, i32, i32, i32, i32, vp, vp]),
         # include/glowq_probe.h
@@ -374,6 +375,12 @@ def glowq_debug_mx_tile_tokens(unit: glowq_unit) -> int:
     tokens = ctypes.c_int32()
     _check(_lib.glowq_debug_mx_tile_tokens(ctypes.byref(unit), ctypes.byref(tokens)), "glowq_debug_mx_tile_tokens")
     return tokens.value
+
+
+def glowq_debug_mx_front(unit: glowq_unit) -> tuple:
+    shape = (ctypes.c_int32 * 4)()
+    _check(_lib.glowq_debug_mx_front(ctypes.byref(unit), shape), "glowq_debug_mx_front")
+    return tuple(shape)
 
 
 def glowq_debug_unpack(w_prepared: int, d_out: int, d_in: int, group_size: int, q_out: int,

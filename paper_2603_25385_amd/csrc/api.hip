@@ -676,6 +676,14 @@ glowq_status glowq_debug_mx_tile_tokens(const glowq_unit* u, int32_t* tokens) {
   return GLOWQ_OK;
 }
 
+glowq_status glowq_debug_mx_front(const glowq_unit* u, int32_t* shape) {
+  glowq_status s = validate_mx(u, false, false);
+  if (s != GLOWQ_OK) return s;
+  if (!shape) return GLOWQ_ERR_NULL;
+  mx_front_shape(*u, shape);
+  return GLOWQ_OK;
+}
+
 glowq_status glowq_debug_unpack(const void* w_prepared, int32_t d_out, int32_t d_in,
                                 int32_t group_size, uint8_t* q_out, void* stream) {
   if (!w_prepared || !q_out) return GLOWQ_ERR_NULL;

@@ -13,8 +13,9 @@ struct UnitWorkspace {
   size_t off_counters;  // T > 64: per token tile, a ready flag and an arrival counter of K parts
   // The next two areas hold what the kernel that serves the call puts there (T > 64: either of two).
   size_t off_rpart;   // partial sums of the projection: 8-byte slots {fp32, launch tag},
-                      // [T][ksplit][r] (few-token and batched kernels); fp32 [part][T][r] (tiled
-                      // kernel, glowq_shared_proj)
+                      // [T][ksplit][r] (few-token and batched kernels; first launch of a microscaling call,
+                      // at most four slices: past 64 tokens these fill the area); fp32 [part][T][r] (tiled kernel,
+                      // glowq_shared_proj)
   size_t off_r16;     // R in the activation type: 8-byte slots {two ranks, launch tag}, [T][r / 2]
                       // (batched kernel); [T][r] (tiled kernel)
   size_t off_splitk;  // T > 64: fp32 slabs of a long contraction cut into K slices (0 bytes if not cut)
@@ -76,6 +77,7 @@ hipError_t launch_mx_quantize_x(const void* X, int T, int d_in, int act, uint8_t
                                 hipStream_t st);
 hipError_t launch_mx_forward(const glowq_unit& u, bool restore, char* workspace, hipStream_t st);
 void mx_route(const glowq_unit& u, glowq_route* route);
+void mx_front_shape(const glowq_unit& u, int32_t* shape);      // of the first launch: token blocks, rank blocks, waves, slices
 int mx_tile_tokens(const glowq_unit& u);      // tokens of the call's workgroup tiles (0: not tiled)
 // slices' start offsets in units of 256 bytes (every slice is 256-byte aligned)
 constexpr int STATUS_BATCH = 256;

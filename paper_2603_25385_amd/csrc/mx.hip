@@ -585,7 +585,8 @@ struct MxGemmArgs {
   const uint8_t* xscales;
   const uint16_t* R16;                  // act dtype [T][r], or NULL when not restored
   int T, d_in, r, out_f32;
-  int tok_tiles;                        // ceil(T / 128); token tiles of a row tile are neighbours in the grid
+  int tok_tiles;                        // of the launch's height (256 tokens on wide tiles, 128, 16 to 64 on small ones); the order of the
+                                        // tiles is the kernels': small ones and those of 128 take a row tile's one after the other
 };
 
 template <int ACT>
@@ -1131,6 +1132,7 @@ static void launch_mx_tile(const MxGemmArgs& a, int tile, int n_wgs, hipStream_t
 // 20 to 2048 tokens, 1024 to 14336 channels and 16 to 128 ranks on every shape: 0.9 % above the best one on average, and
 // 22 % below what three kinds of workgroups took that each read X for themselves (2048 tokens x 4096, r = 64, 18 -> 15 us;
 // x 14336 62 -> 30).  Sixteen waves where eight would take three K tiles or more each and few workgroups are at work.
+constexpr int MX_FRONT_SLICES = 4;       // (look_at_slices reads as many)
 struct MxFrontShape {
   int tb, nb, waves, ksplit, slice_tiles;
 };
@@ -1143,10 +1145,11 @@ static MxFrontShape choose_mx_front(const glowq_unit& u) {
   const int top = blocks <= 2 ? 2 : blocks <= 4 ? 4 : 8;
   MxFrontShape best{};
   double cost = 0.0;
+  // (a token block alone with more than two rank blocks is never the cheapest)
   for (int tb = 1; tb <= 2; ++tb)
-    for (int nb = 2; nb <= top; nb *= 2)
+    for (int nb = 2; nb <= (tb == 1 ? 2 : top); nb *= 2)
       for (int waves = 8; waves <= (tb == 1 && nb == 2 ? 16 : 8); waves += 8)
-        for (int want = 1; want <= std::min(4, ktiles); want *= 2) {
+        for (int want = 1; want <= std::min(MX_FRONT_SLICES, ktiles); want *= 2) {
           const MxFrontShape s = sliced(tb, nb, waves, want);
           const double wgs = (double)((tokens16 + tb - 1) / tb) * ((blocks + nb - 1) / nb) * s.ksplit * (waves / 8);
           const double tile = 0.4 * tb + 0.5 * nb * (tb == 2 ? 1.25 : 1.0);
@@ -1164,10 +1167,10 @@ template <int ACT, int NB, int TB, int NW> static void launch_mx_front_n(const M
   k_mx_front_tiles<ACT, NB, TB, NW><<<grid, dim3(NW * 64), 0, st>>>(a);
 }
 template <int ACT> static void launch_mx_front(const MxFrontTiles& a, const MxFrontShape& s, hipStream_t st) {
-  if (s.nb == 2 && s.waves == 16) launch_mx_front_n<ACT, 2, 1, 16>(a, st);
-  else if (s.nb == 2) s.tb == 1 ? launch_mx_front_n<ACT, 2, 1, 8>(a, st) : launch_mx_front_n<ACT, 2, 2, 8>(a, st);
-  else if (s.nb == 4) s.tb == 1 ? launch_mx_front_n<ACT, 4, 1, 8>(a, st) : launch_mx_front_n<ACT, 4, 2, 8>(a, st);
-  else s.tb == 1 ? launch_mx_front_n<ACT, 8, 1, 8>(a, st) : launch_mx_front_n<ACT, 8, 2, 8>(a, st);
+  if (s.tb == 1) s.waves == 16 ? launch_mx_front_n<ACT, 2, 1, 16>(a, st) : launch_mx_front_n<ACT, 2, 1, 8>(a, st);
+  else if (s.nb == 2) launch_mx_front_n<ACT, 2, 2, 8>(a, st);
+  else if (s.nb == 4) launch_mx_front_n<ACT, 4, 2, 8>(a, st);
+  else launch_mx_front_n<ACT, 8, 2, 8>(a, st);
 }
 
 static hipError_t launch_mx_gemm(const glowq_unit& u, bool restore, char* workspace, hipStream_t st) {
@@ -1190,6 +1193,7 @@ static hipError_t launch_mx_gemm(const glowq_unit& u, bool restore, char* worksp
     fa.groups = ((u.r + 15) / 16 + front.nb - 1) / front.nb;
     fa.ksplit = front.ksplit;
     fa.slice_tiles = front.slice_tiles;
+    if (front.ksplit > 1 && (size_t)front.ksplit * u.T * u.r * 8 > uw.off_r16 - uw.off_rpart) return hipErrorInvalidValue;
     if (f16) launch_mx_front<ACT_F16>(fa, front, st);
     else launch_mx_front<ACT_BF16>(fa, front, st);
   } else {
@@ -1289,6 +1293,12 @@ static hipError_t launch_mx_small(const glowq_unit& u, bool restore, char* works
   return hipGetLastError();
 }
 
+void mx_front_shape(const glowq_unit& u, int32_t* shape) {
+  for (int i = 0; i < 4; ++i) shape[i] = 0;
+  if (u.T <= MX_MAX_TOKENS || u.r == 0) return;
+  const MxFrontShape s = choose_mx_front(u);
+  shape[0] = s.tb; shape[1] = s.nb; shape[2] = s.waves; shape[3] = s.ksplit;
+}
 int mx_tile_tokens(const glowq_unit& u) {
   return u.T <= MX_MAX_TOKENS ? 0 : choose_mx_wide(u) ? MXW_TOK : 16 * MX_TILES[choose_mx_tile(u)].mb;
 }
