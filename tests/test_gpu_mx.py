@@ -339,6 +339,19 @@ def test_wide_tiles(act, T, d_in, d_outs, r, out):
     assert all(np.array_equal(a, b) for a, b in zip(got, again))
 
 
+# three tiles per workgroup in one stream, the third in another module than the first: 390 + 126 + 138 of them on 256 workgroups
+@pytest.mark.parametrize("act", ["f16", "bf16"])
+def test_wide_tiles_three_to_a_workgroup(act):
+    u = make_unit(UnitShape("g", 2048, (16504, 5304, 5752)), 1300, 72, act, seed=55)
+    want = {on: MX.mx_group_forward(u, on) for on in (True, False)}
+    for out in ("act", "f32"):
+        du = MxDeviceUnit(u, out=out)
+        assert G.glowq_debug_mx_tile_tokens(du.desc) == 256
+        for restore in (True, False):
+            for g, y in zip(du.forward(restore), want[restore]):
+                assert np.isfinite(g).all() and rel_err(g, y) <= TOL + (ULP[act] if out == "act" else 0.0)
+
+
 # a rank of R past the activation type's range: infinite outputs of that token's, on every kind of tile, and no NaN from
 # the operand words past the last rank (r = 72, 24, 8: not a multiple of the instruction's 32)
 @pytest.mark.parametrize("act", ["f16", "bf16"])
