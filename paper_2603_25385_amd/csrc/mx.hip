@@ -1065,7 +1065,8 @@ MxWorkspace plan_mx_workspace(const glowq_unit& u) {
 // Fitted to 310 calls of 17 to 2048 tokens on every tile (with one `ends` for all tiles, from 50 calls, the
 // choice was 4.2 % above the best tile; 1931 tokens x 3 x 8680 rows x 896, 32-bit outputs, 99.8 us on tile 0,
 // 128.1 on tile 4).  Tile 0's stores have become faster since: over 1200 calls the choice is 1.3 % above the best
-// tile, and 47 of the 1053 on small tiles are slower than tile 0 by more than 1.5 % (19 % at most, short contractions).
+// tile, and 47 of the 1053 on small tiles are slower than tile 0 by more than 1.5 % (19 % at most, short contractions); over
+// 5232 more of 17 to 3000 tokens 1.4 %.
 struct MxTile {
   int mb, rb, rw, nw;
   float chain, busy, ends, ends32;
@@ -1100,10 +1101,13 @@ static int choose_mx_tile(const glowq_unit& u, double* best_cost = nullptr) {
 }
 // Wide tiles (k_mx_wide) against the best of the others, in us: a round of 256 tiles costs 1.29 per K tile, a last one that
 // is partly empty from 0.85 on (the clock rises), a tile's ends seven K tiles and 3.4 more with 32-bit outputs, beside 10.7
-// for the launch and the first loads; what the other tiles cost is theirs and 9.  From 190 calls of 150 to 3000 tokens that
+// for the launch and the first loads; what the other tiles cost is their estimate and 9 (tile 0's is high since its stores
+// became faster, which the line between the two was fitted with).  From 190 calls of 150 to 3000 tokens that
 // have 48 wide tiles and more (mean error 6 and 11 %).  Contractions of less than 2048 channels keep the other tiles: a
 // wide tile's ends are not covered by another workgroup's products, and 11 of 14 calls that lost had fewer.  Restored or
-// not does not enter.
+// not does not enter.  Of 5463 other calls 231 take wide tiles, 21 % faster on average than on the best of the others, 3
+// of them 3 to 5 % slower; 78 of 3528 that could take them and do not would be more than 5 % faster (24 of these have less than
+// 2048 channels).  Of 337000 random shapes of fewer than 128 wide tiles none takes them.
 static bool choose_mx_wide(const glowq_unit& u) {
   const int ktiles = u.d_in / 128;
   if (ktiles < 16) return false;
@@ -1129,9 +1133,12 @@ static void launch_mx_tile(const MxGemmArgs& a, int tile, int n_wgs, hipStream_t
 // The shape of that launch: what a workgroup takes.  A K tile costs a wave its operands (0.4 for a token block, 0.5 for a
 // rank block, a quarter of that more for a second token block), more workgroups than 200 share compute units, and slices
 // meet at a price of 0.5 (us; at most four of them: the area of partial sums holds their slots).  Fitted to 120 calls of
-// 20 to 2048 tokens, 1024 to 14336 channels and 16 to 128 ranks on every shape: 0.9 % above the best one on average, and
-// 22 % below what three kinds of workgroups took that each read X for themselves (2048 tokens x 4096, r = 64, 18 -> 15 us;
-// x 14336 62 -> 30).  Sixteen waves where eight would take three K tiles or more each and few workgroups are at work.
+// 20 to 2048 tokens, 1024 to 14336 channels and 16 to 128 ranks on every shape, 22 % below what three kinds of workgroups
+// took that each read X for themselves (2048 tokens x 4096, r = 64, 18 -> 15 us; x 14336 62 -> 30); 323 restored calls are
+// 14 % faster as a whole for it, none more than 2 % slower.  Over 3225 other calls the launch alone is 1 to 2 % above the best
+// shape up to 512 tokens, 5 to 1100 and 10 beyond (four slices where two were enough: 2442 tokens x 2304, r = 64,
+// 20.4 and 13.6), which is 1.4 % of a call on average.
+// Sixteen waves where eight would take three K tiles or more each and few workgroups are at work.
 constexpr int MX_FRONT_SLICES = 4;       // (look_at_slices reads as many)
 struct MxFrontShape {
   int tb, nb, waves, ksplit, slice_tiles;

@@ -1006,11 +1006,15 @@ int choose_prefill_tile(const glowq_unit* const* units, const int* slices, int n
 
 // Slices by a unit's own shapes let its tiles end with those of the units beside it; on wide tiles, one per compute unit, a
 // launch of several rounds may end sooner with fewer of them: each has a tile's ends, its partial result and a part of the last
-// round.  At most two slices, or none, where the same estimate sees 2 % in it.  Of 1150 layers (1024 to 8192 channels, 12288 to
-// 32768 inner ones, 384 to 1300 tokens, 3 or 4 slices by their shapes) 313 take fewer: 2.4 % faster on average, a tenth of
-// them 7 %, three more than 3 % slower; 5120 / 15744 at 512 tokens, bfloat16, 346 -> 298 us, 4096 / 14336 at 512 209 -> 202.
+// round.  At most two slices, or none, where the same estimate sees 2 % in it.  Of 1883 layers, one or two in a launch (1024 to
+// 8192 channels, 12288 to 32768 inner ones, 384 to 1300 tokens, 3 or 4 slices by their shapes) 704 take fewer: 4.4 % faster on
+// average, a tenth of them 10 %; 47 are more than 3 % slower, 14 % at most, 35 of these in two slices instead of four (asked for
+// 5 % by the estimate, 345 take fewer and 16 lose, and all layers together gain 1.2 instead of 1.7 %).
+// 4096 / 14336 at 512 tokens 213.5 -> 206.2 us.
 // Two slices throughout were 1 % slower than those of the shapes.  A unit alone keeps them: nothing runs beside its tiles.  So do
-// 32-bit outputs, where a longer chain of sums would show (error against 64 bits 1.25e-6 in three slices, 1.26e-6 in two).
+// 32-bit outputs, where a longer chain of sums shows: over 1355 layers the cut unit's error against 64 bits grows by 4 % on average and 16 %
+// at most from four slices to two, by 11 and 41 % to one (binary16; from three 1 and 5 %, 5 and 18 %), its largest error
+// up to twofold.  In 16 bits the last rounding is eighty times those errors and more.
 void fewer_wide_slices(const glowq_unit* const* units, int n, int* slices) {
   int most = 0;
   for (int k = 0; k < n; ++k) most = std::max(most, slices[k]);
