@@ -11,7 +11,8 @@
 //    stage ahead;
 //  - slots of one product, each with at most one operand read or one direct load beside it, the loads spread over the
 //    whole stage (over half of it: 5 % slower), no branch (the stream passes from tile to tile by selects).
-// 2 x 11008 rows x 4096 at 2048 tokens, bfloat16, r = 64: the kernel 170 -> 145 us under the profiler, the call 192 -> 161 without.  In the loop the matrix pipe is busy
+// 2 x 11008 rows x 4096 at 2048 tokens, bfloat16, r = 64: the kernel 170 -> 145 us within a call of 193 -> 162
+// (182 -> 154 under the profiler).  In the loop the matrix pipe is busy
 // 0.89 of the cycles at 1.88 GHz; with nothing but the products (no loads, no LDS) 0.97 at 2.03: 1.22 against 1.05 us a
 // stage.  The rest are a tile's ends (stores of all workgroups at once 5 us, correction 2.5) and the last round of 0.69.
 #pragma once
