@@ -622,8 +622,8 @@ __global__ void __launch_bounds__(PfShape<ACT>::WAVES * 64, PfShape<ACT>::OCC) k
       for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
         for (int b = 0; b < RB; ++b) {
-          // ranks past r: operand words of rank 0 here, R words of a valid rank below,
-          // and the product left out
+          // ranks past r: operand words of rank 0 here, R words of a valid rank below, zeros for
+          // both in the product (either may hold infinities)
           const int j0 = 64 * rs + 32 * jj + 8 * kq;
           const int row = min((nb0 + b) * 16 + n, M.d_out - 1);   // clamped like the tiles
           if (rs < rstages) vm_load(af[rs][jj][b], M.A + (size_t)row * U.r + (j0 < U.r ? j0 : 0));
@@ -658,6 +658,16 @@ __global__ void __launch_bounds__(PfShape<ACT>::WAVES * 64, PfShape<ACT>::OCC) k
 #pragma unroll
         for (int b = 0; b < RB; ++b)
           if (rs < rstages) after_wait(af[rs][jj][b]);
+    // R's words past r: zeros, each thread in the places that its own loads have filled
+    if (ready && (U.r & 31)) {
+#pragma unroll
+      for (int rs = 0; rs < 2; ++rs)
+#pragma unroll
+        for (int i = 0; i < XI; ++i)
+          if (rs < rstages && 64 * rs + 8 * ((tid & 7) ^ (((XR * i + (tid >> 3)) >> 1) & 7)) >= U.r)
+            *(u32x4_t*)(xs + rs * (SR * 64) + (XR * i + 8 * wave) * 64 + lane * 8) = u32x4_t{0u, 0u, 0u, 0u};
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
     __builtin_amdgcn_s_barrier();
     if (corr_failed == 0) {
 #pragma unroll

@@ -258,6 +258,13 @@ def test_wide_tiles_match_the_oracle(T, d_in, d_outs, act, Gs, r):
 # a rank of R past the activation type's range: infinite outputs of that token's and no NaN from the operand words past
 # the last rank, one stage of ranks and two
 @pytest.mark.parametrize("act", ["f16", "bf16"])
+@pytest.mark.parametrize("T,d_in,d_outs,r,tile", [(300, 1024, (8200,), 72, 1), (300, 1024, (8200,), 8, 1), (1100, 512, (16392,), 24, 0)])
+def test_infinite_rank_on_large_and_half_tiles(T, d_in, d_outs, act, r, tile):
+    route = route_of(check_infinite_rank(T, d_in, d_outs, act, r))
+    assert (route.kernel, route.tile) == (G.GLOWQ_ROUTE_TILED, tile)
+
+
+@pytest.mark.parametrize("act", ["f16", "bf16"])
 @pytest.mark.parametrize("T,d_in,d_outs,r", [(1025, 3328, (6152, 5624), 72), (1281, 3328, (9224,), 8)])
 def test_infinite_rank_on_wide_tiles(T, d_in, d_outs, act, r):
     du = check_infinite_rank(T, d_in, d_outs, act, r)
