@@ -562,7 +562,7 @@ constexpr int BATCH_N_TILES = sizeof(BATCH_TILES) / sizeof(BATCH_TILES[0]);
 // tile and, up to 32 tokens, in one to four slices: beside the other tiles it takes 9.5 % off the time on average up to 32 tokens in
 // binary16 and 7.4 in bfloat16, 2.6 and 1.9 beyond; 4.0, 6.4, 2.7 and 2.9 % of the launches are more than 3 % slower for it.  (An
 // estimate of nine constants for every tile, of the kind below, took 8.9, 6.8, 0.4 and 0 % off, 5.4, 7.7, 18 and 17 % of the
-// launches were slower, 1.5 times as long at most.)  4096 / 14336 at 24 tokens, binary16, 44.8 -> 41.6 us.
+// launches were slower, 1.5 times as long at most.)  4096 / 14336 at 24 tokens, binary16, 44.8 -> 41.7 us.
 constexpr int BATCH_TALL = BATCH_N_TILES - 1;
 constexpr BatchTile BATCH_TALL_33 = {2, 1, 8, 8, 0.23f, 4.89f, {0.36f, 0.47f}, {0.32f, 0.34f}};      // at 33 to 64 tokens
 constexpr float BATCH_LONG_US = 14.f, BATCH_LONG_US_33 = 38.f;

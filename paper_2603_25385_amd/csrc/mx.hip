@@ -885,22 +885,24 @@ __global__ void __launch_bounds__(NW * 64, (MxTileShape<MB, RB, RW, NW>::WGS * N
 #include "mx_wide.hpp"
 namespace glowq {
 
-// First launch of a call of more than 16 tokens that is not restored: the activations' codes alone, by threads that read a
-// wave's 2 KiB of a token in one piece.  (On workgroups of the kernel below without its ranks, a wave a K tile of 16 tokens, calls
-// of 18 to 500 tokens took 3 % longer, up to 9: 21 tokens x 3840 rows x 896 7.0 -> 7.7 us, 115 x 3 x 1200 x 1024 8.2 -> 8.9.)
+// First launch of a call of more than 16 tokens that is not restored, up to two million activations: the codes alone, by threads that read a
+// wave's 2 KiB of a token in one piece.  Beyond, the kernel below without its ranks, whose waves write a K tile's codes of 16 tokens
+// as contiguous KiBs (here a wave writes 64 pieces of 16 bytes, each in a line of its own, which the L2s gather while they hold them
+// all).  Of 8716 calls these here took 0.3 to 0.4 us less than those below up to 1.5 million activations, as long at 2 to 2.5, 1.3 us more at 4 to 6, 6.8
+// at 10 to 20 million (21 tokens x 3840 rows x 896 7.0 and 7.7 us, 1707 x 608 x 13440 72.9 and 57.4).
 template <int ACT>
 __global__ void __launch_bounds__(MX_FRONT_THREADS) k_mx_codes(const uint16_t* __restrict__ X, int T, int d_in,
                                                                uint8_t* __restrict__ codes, uint8_t* __restrict__ scales) {
   mx_quantize_block<ACT, true>(X, T, d_in, codes, scales, (long long)blockIdx.x * MX_FRONT_THREADS + threadIdx.x);
 }
 
-// ... and of one that is: the activations' codes and R = X B^T from one read of X.  A workgroup
+// ... and of one that is restored: the activations' codes and R = X B^T from one read of X.  A workgroup
 // takes 16 or 32 tokens, a K slice and some of the ranks, its waves the slice's K tiles in turn.  A wave holds X as the quantiser wants it
 // (lane (token, g): channels 64 half + 16 g .. + 16 of the tile), which is an operand of the 16-bit instruction as it
 // stands when B's channels are taken in the same order; the codes of a half leave as one contiguous KiB.
 struct MxFrontTiles {
   const uint16_t* X;
-  const uint16_t* B;         // act dtype [r][d_in]
+  const uint16_t* B;         // act dtype [r][d_in], or NULL when not restored
   unsigned long long* slots; // {fp32, launch tag} of the slices' partial sums: (t ksplit + slice) r + rank (ksplit > 1 only)
   uint16_t* R16;             // act dtype [T][r]
   uint8_t* xcodes;
@@ -910,7 +912,7 @@ struct MxFrontTiles {
   int groups;                // of 16 NB ranks; the first one's workgroups store the codes
 };
 
-// NB: 16-rank blocks of a workgroup, TB: 16-token blocks, NW: waves
+// NB: 16-rank blocks of a workgroup (0: codes only), TB: 16-token blocks, NW: waves
 template <int ACT, int NB, int TB, int NW>
 __global__ void __launch_bounds__(NW * 64) k_mx_front_tiles(MxFrontTiles a) {
   const int l = threadIdx.x & 63, i = l & 15, g = l >> 4;
@@ -921,8 +923,8 @@ __global__ void __launch_bounds__(NW * 64) k_mx_front_tiles(MxFrontTiles a) {
   const uint16_t* xrow[TB];      // tokens past T (ranks past r): the last one again, not stored
 #pragma unroll
   for (int t = 0; t < TB; ++t) xrow[t] = a.X + (size_t)min((tb0 + t) * 16 + i, a.T - 1) * a.d_in + 16 * g;
-  const uint16_t* brow[NB];
-  float4_t acc[NB][TB];
+  const uint16_t* brow[NB > 0 ? NB : 1];
+  float4_t acc[NB > 0 ? NB : 1][TB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     brow[nb] = a.B + (size_t)min(rank0 + nb * 16 + i, a.r - 1) * a.d_in + 16 * g;
@@ -939,7 +941,7 @@ __global__ void __launch_bounds__(NW * 64) k_mx_front_tiles(MxFrontTiles a) {
         for (int e = 0; e < 2; ++e) x[t][h][e] = *(const u32x4_t*)(xrow[t] + (size_t)kt * 128 + 64 * h + 8 * e);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      u32x4_t b[NB][2];
+      u32x4_t b[NB > 0 ? NB : 1][2];
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -964,43 +966,45 @@ __global__ void __launch_bounds__(NW * 64) k_mx_front_tiles(MxFrontTiles a) {
           for (int t = 0; t < TB; ++t) acc[nb][t] = mfma16<ACT>(x[t][h][e], b[nb][e], acc[nb][t]);   // D[token][rank]
     }
   }
-  // the waves' sums meet in LDS: [wave][token block][rank block][4][lane]; then thread -> (token, pair of ranks)
-  __shared__ float part[NW * TB * NB * 256];
-  constexpr int PAIRS = TB * 16 * NB * 8, NP = (PAIRS + NW * 64 - 1) / (NW * 64);
-  const uint32_t tag = (uint32_t)(launch_tag() & 0xffffffffull);
+  if constexpr (NB > 0) {
+    // the waves' sums meet in LDS: [wave][token block][rank block][4][lane]; then thread -> (token, pair of ranks)
+    __shared__ float part[NW * TB * NB * 256];
+    constexpr int PAIRS = TB * 16 * NB * 8, NP = (PAIRS + NW * 64 - 1) / (NW * 64);
+    const uint32_t tag = (uint32_t)(launch_tag() & 0xffffffffull);
 #pragma unroll
-  for (int t = 0; t < TB; ++t)
+    for (int t = 0; t < TB; ++t)
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
+      for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) part[(((w * TB + t) * NB + nb) * 4 + v) * 64 + l] = acc[nb][t][v];
-  __syncthreads();
-  float s[NP][2];
-  unsigned long long* slot[NP];
-  int tok[NP], rank[NP];
-  bool live[NP];
+        for (int v = 0; v < 4; ++v) part[(((w * TB + t) * NB + nb) * 4 + v) * 64 + l] = acc[nb][t][v];
+    __syncthreads();
+    float s[NP][2];
+    unsigned long long* slot[NP];
+    int tok[NP], rank[NP];
+    bool live[NP];
 #pragma unroll
-  for (int n = 0; n < NP; ++n) {
-    const int p = (int)threadIdx.x + n * NW * 64, tl = p / (NB * 8) & 15, t = p / (NB * 8) >> 4;
-    rank[n] = rank0 + p % (NB * 8) * 2;
-    tok[n] = (tb0 + t) * 16 + tl;
-    live[n] = p < PAIRS && tok[n] < a.T && rank[n] < a.r;
-    slot[n] = a.slots + (size_t)tok[n] * a.ksplit * a.r + rank[n];
-    s[n][0] = s[n][1] = 0.f;
-    if (!live[n]) continue;
+    for (int n = 0; n < NP; ++n) {
+      const int p = (int)threadIdx.x + n * NW * 64, tl = p / (NB * 8) & 15, t = p / (NB * 8) >> 4;
+      rank[n] = rank0 + p % (NB * 8) * 2;
+      tok[n] = (tb0 + t) * 16 + tl;
+      live[n] = p < PAIRS && tok[n] < a.T && rank[n] < a.r;
+      slot[n] = a.slots + (size_t)tok[n] * a.ksplit * a.r + rank[n];
+      s[n][0] = s[n][1] = 0.f;
+      if (!live[n]) continue;
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int rl = rank[n] - rank0 + e, ln = (rl & 15) + 16 * (tl >> 2);
+      for (int e = 0; e < 2; ++e) {
+        const int rl = rank[n] - rank0 + e, ln = (rl & 15) + 16 * (tl >> 2);
 #pragma unroll
-      for (int q = 0; q < NW; ++q) s[n][e] += part[(((q * TB + t) * NB + (rl >> 4)) * 4 + (tl & 3)) * 64 + ln];
+        for (int q = 0; q < NW; ++q) s[n][e] += part[(((q * TB + t) * NB + (rl >> 4)) * 4 + (tl & 3)) * 64 + ln];
+      }
+      if (a.ksplit > 1) publish_slice(slot[n], kz, a.r, tag, s[n]);
     }
-    if (a.ksplit > 1) publish_slice(slot[n], kz, a.r, tag, s[n]);
-  }
-  if (a.ksplit > 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // (counts stores, too)
+    if (a.ksplit > 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // (counts stores, too)
 #pragma unroll
-  for (int n = 0; n < NP; ++n)
-    if (live[n] && (a.ksplit == 1 || look_at_slices(slot[n], a.ksplit, a.r, tag, s[n])))
-      ((uint32_t*)a.R16)[((size_t)tok[n] * a.r + rank[n]) >> 1] = (uint32_t)to_act16<ACT>(s[n][0]) | ((uint32_t)to_act16<ACT>(s[n][1]) << 16);
+    for (int n = 0; n < NP; ++n)
+      if (live[n] && (a.ksplit == 1 || look_at_slices(slot[n], a.ksplit, a.r, tag, s[n])))
+        ((uint32_t*)a.R16)[((size_t)tok[n] * a.r + rank[n]) >> 1] = (uint32_t)to_act16<ACT>(s[n][0]) | ((uint32_t)to_act16<ACT>(s[n][1]) << 16);
+  }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1139,16 +1143,19 @@ static void launch_mx_tile(const MxGemmArgs& a, int tile, int n_wgs, hipStream_t
 // shape up to 512 tokens, 5 to 1100 and 10 beyond (four slices where two were enough: 2442 tokens x 2304, r = 64,
 // 20.4 and 13.6), which is 1.4 % of a call on average.
 // Sixteen waves where eight would take three K tiles or more each and few workgroups are at work.
+constexpr long long MX_CODES_ALONE = 2 << 20;      // activations of a call that is not restored: more of them by k_mx_front_tiles
 constexpr int MX_FRONT_SLICES = 4;       // (look_at_slices reads as many)
 struct MxFrontShape {
   int tb, nb, waves, ksplit, slice_tiles;
 };
-static MxFrontShape choose_mx_front(const glowq_unit& u) {
-  const int ktiles = u.d_in / 128, tokens16 = (u.T + 15) / 16, blocks = (u.r + 15) / 16;
+static MxFrontShape choose_mx_front(const glowq_unit& u, bool corrected) {
+  const int ktiles = u.d_in / 128, tokens16 = (u.T + 15) / 16, blocks = corrected ? (u.r + 15) / 16 : 0;
   auto sliced = [&](int tb, int nb, int waves, int want) {
     const int tiles = (ktiles + want - 1) / want;
     return MxFrontShape{tb, nb, waves, (ktiles + tiles - 1) / tiles, tiles};
   };
+  // codes alone: a K tile per wave as long as that is not too many workgroups
+  if (blocks == 0) return sliced(1, 0, 8, std::max(1, std::min((ktiles + 7) / 8, 1024 / tokens16)));
   const int top = blocks <= 2 ? 2 : blocks <= 4 ? 4 : 8;
   MxFrontShape best{};
   double cost = 0.0;
@@ -1174,7 +1181,8 @@ template <int ACT, int NB, int TB, int NW> static void launch_mx_front_n(const M
   k_mx_front_tiles<ACT, NB, TB, NW><<<grid, dim3(NW * 64), 0, st>>>(a);
 }
 template <int ACT> static void launch_mx_front(const MxFrontTiles& a, const MxFrontShape& s, hipStream_t st) {
-  if (s.tb == 1) s.waves == 16 ? launch_mx_front_n<ACT, 2, 1, 16>(a, st) : launch_mx_front_n<ACT, 2, 1, 8>(a, st);
+  if (s.nb == 0) launch_mx_front_n<ACT, 0, 1, 8>(a, st);
+  else if (s.tb == 1) s.waves == 16 ? launch_mx_front_n<ACT, 2, 1, 16>(a, st) : launch_mx_front_n<ACT, 2, 1, 8>(a, st);
   else if (s.nb == 2) launch_mx_front_n<ACT, 2, 2, 8>(a, st);
   else if (s.nb == 4) launch_mx_front_n<ACT, 4, 2, 8>(a, st);
   else launch_mx_front_n<ACT, 8, 2, 8>(a, st);
@@ -1187,20 +1195,20 @@ static hipError_t launch_mx_gemm(const glowq_unit& u, bool restore, char* worksp
   const bool corrected = restore && u.r > 0, f16 = u.act_dtype == GLOWQ_F16;
   const UnitWorkspace uw = plan_unit_workspace(u, workspace);
   uint16_t* R16 = (uint16_t*)(uw.base + uw.off_r16);
-  if (corrected) {
+  if (corrected || (long long)u.T * u.d_in > MX_CODES_ALONE) {
     MxFrontTiles fa;
     fa.X = (const uint16_t*)u.X;
-    fa.B = (const uint16_t*)u.B;
+    fa.B = corrected ? (const uint16_t*)u.B : nullptr;
     fa.slots = (unsigned long long*)(uw.base + uw.off_rpart);
     fa.R16 = R16;
     fa.xcodes = xcodes;
     fa.xscales = xscales;
     fa.T = u.T; fa.d_in = u.d_in; fa.r = u.r;
-    const MxFrontShape front = choose_mx_front(u);
-    fa.groups = ((u.r + 15) / 16 + front.nb - 1) / front.nb;
+    const MxFrontShape front = choose_mx_front(u, corrected);
+    fa.groups = front.nb == 0 ? 1 : ((u.r + 15) / 16 + front.nb - 1) / front.nb;
     fa.ksplit = front.ksplit;
     fa.slice_tiles = front.slice_tiles;
-    if (front.ksplit > 1 && (size_t)front.ksplit * u.T * u.r * 8 > uw.off_r16 - uw.off_rpart) return hipErrorInvalidValue;
+    if (corrected && front.ksplit > 1 && (size_t)front.ksplit * u.T * u.r * 8 > uw.off_r16 - uw.off_rpart) return hipErrorInvalidValue;
     if (f16) launch_mx_front<ACT_F16>(fa, front, st);
     else launch_mx_front<ACT_BF16>(fa, front, st);
   } else {
@@ -1303,7 +1311,7 @@ static hipError_t launch_mx_small(const glowq_unit& u, bool restore, char* works
 void mx_front_shape(const glowq_unit& u, int32_t* shape) {
   for (int i = 0; i < 4; ++i) shape[i] = 0;
   if (u.T <= MX_MAX_TOKENS || u.r == 0) return;
-  const MxFrontShape s = choose_mx_front(u);
+  const MxFrontShape s = choose_mx_front(u, true);
   shape[0] = s.tb; shape[1] = s.nb; shape[2] = s.waves; shape[3] = s.ksplit;
 }
 int mx_tile_tokens(const glowq_unit& u) {

@@ -1020,7 +1020,7 @@ int choose_prefill_tile(const glowq_unit* const* units, const int* slices, int n
 // 8192 channels, 12288 to 32768 inner ones, 384 to 1300 tokens, 3 or 4 slices by their shapes) 704 take fewer: 4.4 % faster on
 // average, a tenth of them 10 %; 47 are more than 3 % slower, 14 % at most, 35 of these in two slices instead of four (asked for
 // 5 % by the estimate, 345 take fewer and 16 lose, and all layers together gain 1.2 instead of 1.7 %).
-// 4096 / 14336 at 512 tokens 213.5 -> 206.2 us.
+// 4096 / 14336 at 512 tokens 212.4 -> 206.5 us.
 // Two slices throughout were 1 % slower than those of the shapes.  A unit alone keeps them: nothing runs beside its tiles.  So do
 // 32-bit outputs, where a longer chain of sums shows: over 1355 layers the cut unit's error against 64 bits grows by 4 % on average and 16 %
 // at most from four slices to two, by 11 and 41 % to one (binary16; from three 1 and 5 %, 5 and 18 %), its largest error
