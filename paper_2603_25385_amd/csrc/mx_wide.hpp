@@ -242,13 +242,16 @@ __global__ void __launch_bounds__(256, 1) k_mx_wide(MxGemmArgs a, int n_tiles) {
           const uint32_t at = 2u * (uint32_t)min(j0, a.r - 8);
           u32x4_t av[8], rv[8];
 #pragma unroll
-          for (int r = 0; r < 8; ++r) {
+          for (int r = 0; r < 8; ++r)
             av[r] = *(const __attribute__((address_space(1))) u32x4_t*)(abase + (2u * (uint32_t)(min(r * 16 + i, max(rows, 1) - 1) * a.r) + at));
-            rv[r] = *(const __attribute__((address_space(1))) u32x4_t*)(rbase + (2u * (uint32_t)(min(r * 16 + i, max(toks, 1) - 1) * a.r) + at));
-          }
 #pragma unroll
           for (int r = 0; r < 8; ++r)
-            if (j0 >= a.r) av[r] = rv[r] = u32x4_t{0, 0, 0, 0};
+            rv[r] = *(const __attribute__((address_space(1))) u32x4_t*)(rbase + (2u * (uint32_t)(min(r * 16 + i, max(toks, 1) - 1) * a.r) + at));
+          if (32 * s + 32 > a.r) {         // uniform: whole steps multiply while R's later words are on their way
+#pragma unroll
+            for (int r = 0; r < 8; ++r)
+              if (j0 >= a.r) av[r] = rv[r] = u32x4_t{0, 0, 0, 0};
+          }
           __builtin_amdgcn_sched_barrier(0);
           asm volatile("s_nop 1");       // (operands that the vector ALU wrote)
           for_each_index<64>([&](auto Q) __attribute__((always_inline)) { sum_mfma16<ACT, Q.value>(av[Q.value % 8], rv[Q.value / 8]); });
