@@ -371,14 +371,15 @@ def test_infinite_rank(act, T, d_in, d_outs, r, tokens):
 
 
 # the first launch's shapes (asked of the library: token blocks, rank blocks, waves, slices): one and two token blocks, 32 ranks
-# to all of them, whole contractions and slices, sixteen waves, codes alone, ranks and tokens that end inside a block
+# to all of them, whole contractions and slices, sixteen waves, codes alone (by a launch of their own up to 512 x 4096 of them), ranks
+# and tokens that end inside a block
 @pytest.mark.parametrize("act", ["f16", "bf16"])
 @pytest.mark.parametrize("T,d_in,r,shape", [
     (17, 128, 8, (1, 2, 8, 1)), (33, 4224, 40, (1, 2, 16, 4)), (50, 8320, 72, (1, 2, 16, 4)), (130, 1152, 128, (1, 2, 8, 2)),
     (530, 8320, 128, (2, 2, 8, 4)), (700, 2048, 104, (2, 2, 8, 2)), (1500, 1024, 48, (1, 2, 8, 1)), (1500, 4224, 72, (2, 2, 8, 2)),
     (2048, 384, 16, (1, 2, 8, 1)), (2670, 128, 104, (2, 4, 8, 1)), (1329, 1152, 104, (2, 4, 8, 2)), (2041, 4096, 64, (2, 4, 8, 4)),
     (1762, 8320, 56, (2, 4, 8, 4)), (5905, 128, 104, (2, 8, 8, 1)), (2961, 1152, 104, (2, 8, 8, 2)), (1981, 7808, 128, (2, 8, 8, 4)),
-    (1721, 10880, 120, (2, 8, 8, 4))])
+    (1721, 10880, 120, (2, 8, 8, 4)), (512, 4096, 8, (1, 2, 8, 4)), (513, 4096, 8, (1, 2, 8, 4))])
 def test_projection_and_codes_of_the_first_launch(act, T, d_in, r, shape):
     u = make_unit(UnitShape("g", d_in, (136,)), T, r, act, seed=52)
     du = MxDeviceUnit(u)
